@@ -138,8 +138,7 @@ int dfa_delta(const dfa_shape* sh, const void* o, const void* dO, float* delta, 
  *   A NULL output selects what is computed: dq == NULL gives dk, dv only; dk == dv == NULL
  *   gives dq only (so a worker can send one while the other is still being computed); dk
  *   and dv are given together; all three NULL is DFA_ERR_NULL.
- * The bf16 path runs two kernels (dk/dv, then dq) and is deterministic; the fp32 path adds dq
- * with fp32 atomics, so its rounding order (not its value beyond rounding) can differ between runs.
+ * No path uses atomics: the summation order is fixed and repeated calls agree bit for bit.
  */
 int dfa_chunk_bwd(const dfa_shape* sh, const void* q, const void* k, const void* v,
                   const float* lse, const float* delta, const void* dO,

@@ -1,298 +1,491 @@
-// fp32 mode of the chunk kernels: plain fp32 FMA arithmetic, LDS-tiled, any s_q / s_k.
-// This is the precision-reference mode of the library (small problems, 1e-5 agreement with
-// fp64); the bf16 MFMA kernels are the fast path.  Tiling: a workgroup of 256 threads owns
-// 64 query rows (forward) or 64 key rows (backward) and streams the other operand in tiles
-// through LDS; online softmax follows the forward pseudo-code of Appendix A (running row
-// maximum m and row sum l, old terms multiplied by exp(m_old - m_new)).
+// fp32 mode of the chunk kernels: fp32 operands, products and sums throughout, any s_q / s_k.
+// This is the precision-reference mode of the library (1e-5 agreement with fp64); the bf16 kernels
+// are the fast path.
+//
+// All products run on v_mfma_f32_32x32x2_f32 (64 cycles each, 256 FLOP per clock and CU: with the
+// packed vector forms unused it is twice the vector rate, and it needs a 64th of the operand reads of
+// a 4x4 micro-tile).  Its layout, lane l, r = l % 32, h = l / 32:
+//   A operand: A[r][h]    B operand: B[h][r]    C/D (16 fp32): C[(i/4)*8 + 4h + i%4][r]
+// Two consequences shape every kernel here:
+//  * the contraction index only has to match between A and B, so a product over d takes d = 8t + 4h + e
+//    in step 4t + e: one 16-byte read of a row serves four steps, and a C tile is fed back as B
+//    operands register by register (register i holds contraction rows (i/4)*8 + 4h + i%4);
+//  * the rows of C may be any rows: column block j of a d-wide result holds d = NB m + j
+//    (NB = d / 32), so the A operands of all NB blocks come from ONE read of NB consecutive floats
+//    and the results leave in runs of NB floats.
+// A wavefront owns 32 rows of the stationary operand and walks over 32-row blocks of the other,
+// which four wavefronts share through LDS (rows padded by 4 floats: both kinds of reads are free of
+// bank conflicts).  The four wavefronts of a workgroup are NR row blocks x NS = 4 / NR parts of every
+// tile; with NS > 1 the partial results of the parts are combined through LDS at the end.  NS = 4 is
+// for calls with few rows: it gives four times the workgroups, each with a quarter of the serial work.
+#include <mutex>
+
 #include "dfa_internal.h"
 
 namespace dfa {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int NT = 256;        // threads per workgroup: 4 wavefronts
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
 
 struct F32Params {
   const float *q, *k, *v, *dO, *lse_in, *delta;
   void* o; float* lse;
   float *dq, *dk, *dv;
-  int s_q, s_k, group, causal, o_bf16, accumulate;
+  int s_q, s_k, h_q, h_kv, group, causal, o_bf16, accumulate;
+  int nx_kv, n_kv;             // dk/dv: row blocks per key/value head, workgroups (they come first)
+  int nx_q;                    // forward, dq: row blocks per query head
   float scale;
   int64_t q_sh, q_ss, kv_sh, kv_ss, o_sh, o_ss, l_sh, dq_sh, dq_ss, dkv_sh, dkv_ss;
 };
 
-// rows x D tile from global (row stride ss) into LDS (row stride LD); rows >= nrows become 0
-template <int D, int ROWS, int LD>
-__device__ inline void load_tile(float* dst, const float* src, int64_t ss, int row0, int nrows) {
-  constexpr int C4 = D / 4;
-  for (int i = threadIdx.x; i < ROWS * C4; i += kThreads) {
-    const int r = i / C4, c = i % C4;
-    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (row0 + r < nrows) x = *reinterpret_cast<const float4*>(src + static_cast<int64_t>(row0 + r) * ss + c * 4);
-    *reinterpret_cast<float4*>(dst + r * LD + c * 4) = x;
+template <int NB> struct Run;      // NB consecutive floats
+template <> struct Run<4> { typedef f32x4 type; };
+template <> struct Run<2> { typedef f32x2 type; };
+
+template <int NB>
+__device__ __forceinline__ void zero(f32x16 (&c)[NB]) {
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) c[j][i] = 0.f;
+}
+
+// One 32-row block as a B operand over d, straight from global memory: lane holds row `row`,
+// d = 8t + 4h .. +3; rows past the end are zero.
+template <int D>
+__device__ __forceinline__ void load_rows(f32x4 (&b)[D / 8], const float* src, int64_t ss, int row, bool ok, int hh) {
+  const float* p = src + static_cast<int64_t>(ok ? row : 0) * ss + 4 * hh;
+#pragma unroll
+  for (int t = 0; t < D / 8; ++t) {
+    b[t] = *reinterpret_cast<const f32x4*>(p + 8 * t);
+    if (!ok) b[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 }
 
+// A pair of ROWS x D tiles on their way from global memory to LDS.  load() issues the reads of a tile
+// while the tile before it is computed on; store() writes what has arrived.  Rows past the end are zero.
+template <int D, int ROWS>
+struct TilePair {
+  static constexpr int LD = D + 4, C4 = D / 4, N = ROWS * C4 / NT;
+  f32x4 a[N], b[N];
+  __device__ __forceinline__ void load(const float* A, const float* B, int64_t ss, int row0, int nrows) {
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const int i = threadIdx.x + n * NT, r = row0 + i / C4, c = (i % C4) * 4;
+      const int64_t off = static_cast<int64_t>(min(r, nrows - 1)) * ss + c;
+      a[n] = *reinterpret_cast<const f32x4*>(A + off);
+      b[n] = *reinterpret_cast<const f32x4*>(B + off);
+    }
+  }
+  __device__ __forceinline__ void store(float* As, float* Bs, int row0, int nrows) const {
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const int i = threadIdx.x + n * NT, r = i / C4, c = (i % C4) * 4;
+      const bool ok = row0 + r < nrows;
+      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+      *reinterpret_cast<f32x4*>(As + r * LD + c) = ok ? a[n] : z;
+      *reinterpret_cast<f32x4*>(Bs + r * LD + c) = ok ? b[n] : z;
+    }
+  }
+};
+
+// C += X Y^T over d: X is a 32-row block in LDS (row r of it for lane r), Y a register operand.
 template <int D>
-__global__ void __launch_bounds__(kThreads) k_fwd_f32(F32Params p) {
-  constexpr int BQ = 64, BK = 64, LD = D + 4, LS = BK + 1, NC = D / 16;
-  extern __shared__ __align__(16) float smem[];
-  float* Qs = smem;
-  float* Ks = Qs + BQ * LD;
-  float* Vs = Ks + BK * LD;
-  float* Ss = Vs + BK * LD;
-  float* row_m = Ss + BQ * LS;
-  float* row_l = row_m + BQ;
-  float* row_a = row_l + BQ;
-  const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
-  const int h = blockIdx.y, kh = h / p.group, q0 = blockIdx.x * BQ;
-  const float* qg = p.q + h * p.q_sh;
-  const float* kg = p.k + kh * p.kv_sh;
-  const float* vg = p.v + kh * p.kv_sh;
-
-  load_tile<D, BQ, LD>(Qs, qg, p.q_ss, q0, p.s_q);
-  // Empty state, or (accumulate) the state of the earlier key/value chunks: the normalised output
-  // with its logsumexp is the running (o, m, l) with m = lse and l = 1.
-  if (tid < BQ) {
-    float m0 = -INFINITY;
-    if (p.accumulate && q0 + tid < p.s_q) m0 = p.lse[h * p.l_sh + q0 + tid];
-    row_m[tid] = m0; row_l[tid] = m0 > -INFINITY ? 1.f : 0.f;
-  }
-  float acc[4][NC];
+__device__ __forceinline__ void row_product(f32x16& c, const float* Xs, const f32x4 (&y)[D / 8], int r32, int hh) {
+  const float* x = Xs + r32 * (D + 4) + 4 * hh;
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int qi = q0 + ty * 4 + a;
-    const bool have = p.accumulate && qi < p.s_q && p.lse[h * p.l_sh + qi] > -INFINITY;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      float x = 0.f;
-      if (have) {
-        const int64_t off = h * p.o_sh + static_cast<int64_t>(qi) * p.o_ss + tx + 16 * c;
-        x = p.o_bf16 ? static_cast<float>(static_cast<const __bf16*>(p.o)[off]) : static_cast<const float*>(p.o)[off];
-      }
-      acc[a][c] = x;
-    }
-  }
-
-  const int k_end = p.causal ? min(p.s_k, q0 + BQ) : p.s_k;
-  for (int k0 = 0; k0 < k_end; k0 += BK) {
-    __syncthreads();
-    load_tile<D, BK, LD>(Ks, kg, p.kv_ss, k0, p.s_k);
-    load_tile<D, BK, LD>(Vs, vg, p.kv_ss, k0, p.s_k);
-    __syncthreads();
-    // s = scale * q k^T on a 4x4 micro-tile per thread
-    float s[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) s[a][b] = 0.f;
-    for (int c = 0; c < D; c += 4) {
-      float4 qa[4], kb[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) qa[a] = *reinterpret_cast<const float4*>(Qs + (ty * 4 + a) * LD + c);
-#pragma unroll
-      for (int b = 0; b < 4; ++b) kb[b] = *reinterpret_cast<const float4*>(Ks + (tx * 4 + b) * LD + c);
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          s[a][b] = fmaf(qa[a].x, kb[b].x, s[a][b]); s[a][b] = fmaf(qa[a].y, kb[b].y, s[a][b]);
-          s[a][b] = fmaf(qa[a].z, kb[b].z, s[a][b]); s[a][b] = fmaf(qa[a].w, kb[b].w, s[a][b]);
-        }
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int qi = q0 + ty * 4 + a, kj = k0 + tx * 4 + b;
-        const bool vis = kj < p.s_k && (!p.causal || kj <= qi);
-        Ss[(ty * 4 + a) * LS + tx * 4 + b] = vis ? s[a][b] * p.scale : -INFINITY;
-      }
-    __syncthreads();
-    {  // online softmax: 4 adjacent lanes per row, 16 columns each
-      const int row = tid / 4, part = tid % 4;
-      float* sr = Ss + row * LS + part * 16;
-      float mx = -INFINITY;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) mx = fmaxf(mx, sr[j]);
-      mx = fmaxf(mx, __shfl_xor(mx, 1)); mx = fmaxf(mx, __shfl_xor(mx, 2));
-      const float m_old = row_m[row];
-      const float m_new = fmaxf(m_old, mx);
-      const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-      float sum = 0.f;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) { const float e = expf(sr[j] - m_safe); sr[j] = e; sum += e; }
-      sum += __shfl_xor(sum, 1); sum += __shfl_xor(sum, 2);
-      const float alpha = expf(m_old - m_safe);   // exp(-inf) = 0 on the first tile
-      const float l_old = row_l[row];
-      __builtin_amdgcn_wave_barrier();
-      if (part == 0) { row_m[row] = m_new; row_l[row] = l_old * alpha + sum; row_a[row] = alpha; }
-    }
-    __syncthreads();
-    float al[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) al[a] = row_a[ty * 4 + a];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int c = 0; c < NC; ++c) acc[a][c] *= al[a];
-    for (int j = 0; j < BK; ++j) {
-      float pj[4], vv[NC];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) pj[a] = Ss[(ty * 4 + a) * LS + j];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) vv[c] = Vs[j * LD + tx + 16 * c];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) acc[a][c] = fmaf(pj[a], vv[c], acc[a][c]);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int r = ty * 4 + a, qi = q0 + r;
-    if (qi >= p.s_q) continue;
-    const float l = row_l[r];
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const float val = acc[a][c] * inv;
-      const int64_t off = h * p.o_sh + static_cast<int64_t>(qi) * p.o_ss + tx + 16 * c;
-      if (p.o_bf16) static_cast<__bf16*>(p.o)[off] = static_cast<__bf16>(val);
-      else static_cast<float*>(p.o)[off] = val;
-    }
-    if (tx == 0) p.lse[h * p.l_sh + qi] = l > 0.f ? row_m[r] + logf(l) : -INFINITY;
+  for (int t = 0; t < D / 8; ++t) {
+    const f32x4 a = *reinterpret_cast<const f32x4*>(x + 8 * t);
+    c = mfma_f32(a.x, y[t].x, c);
+    c = mfma_f32(a.y, y[t].y, c);
+    c = mfma_f32(a.z, y[t].z, c);
+    c = mfma_f32(a.w, y[t].w, c);
   }
 }
 
-// Backward, key-stationary: a workgroup owns 64 key rows of one kv head and walks over the
-// query heads of its group and their query tiles (32 rows).  dk, dv are accumulated in
-// registers and written once; dq contributions are added to global memory with fp32 atomics.
+// The same with Y (32 rows too) in LDS.
 template <int D>
-__global__ void __launch_bounds__(kThreads) k_bwd_f32(F32Params p) {
-  constexpr int BK = 64, BQ = 32, LD = D + 4, LS = BK + 1, NC = D / 16, NQ = D / 8;
+__device__ __forceinline__ void row_product(f32x16& c, const float* Xs, const float* Ys, int r32, int hh) {
+  const float* x = Xs + r32 * (D + 4) + 4 * hh;
+  const float* y = Ys + r32 * (D + 4) + 4 * hh;
+#pragma unroll
+  for (int t = 0; t < D / 8; ++t) {
+    const f32x4 a = *reinterpret_cast<const f32x4*>(x + 8 * t), b = *reinterpret_cast<const f32x4*>(y + 8 * t);
+    c = mfma_f32(a.x, b.x, c);
+    c = mfma_f32(a.y, b.y, c);
+    c = mfma_f32(a.z, b.z, c);
+    c = mfma_f32(a.w, b.w, c);
+  }
+}
+
+// acc^T += X^T W: X is a 32-row block in LDS, W a C tile (its rows are X's rows).
+template <int D>
+__device__ __forceinline__ void col_product(f32x16 (&acc)[D / 32], const float* Xs, const f32x16& w, int r32, int hh) {
+  constexpr int NB = D / 32;
+  typedef typename Run<NB>::type run_t;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const run_t a = *reinterpret_cast<const run_t*>(Xs + ((i >> 2) * 8 + 4 * hh + (i & 3)) * (D + 4) + NB * r32);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[j] = mfma_f32(a[j], w[i], acc[j]);
+  }
+}
+
+// Sum of a result over the NS parts of a row block, left in part 0: `x` is LDS space for
+// 4 * NV * 64 floats (NV registers of the result per lane).
+template <int NB>
+__device__ __forceinline__ void put_result(float* x, const f32x16 (&c)[NB], int lane) {
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[(j * 16 + i) * 64 + lane] = c[j][i];
+}
+template <int NB>
+__device__ __forceinline__ void add_result(const float* x, f32x16 (&c)[NB], int lane, float f) {
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) c[j][i] = fmaf(x[(j * 16 + i) * 64 + lane], f, c[j][i]);
+}
+
+// Row `dst` (+)= f * result
+template <int D>
+__device__ __forceinline__ void write_grad(float* dst, const f32x16 (&c)[D / 32], float f, int accumulate, int hh) {
+  constexpr int NB = D / 32;
+  typedef typename Run<NB>::type run_t;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    float* p = dst + NB * ((i >> 2) * 8 + 4 * hh + (i & 3));
+    run_t x;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) x[j] = c[j][i] * f;
+    if (accumulate) x += *reinterpret_cast<const run_t*>(p);
+    *reinterpret_cast<run_t*>(p) = x;
+  }
+}
+
+// Keys per LDS tile of the forward: 32 per part, and at least 64 (a single part then takes two blocks in
+// turn).  The backward holds more in registers and takes 32 rows per part throughout.
+template <int NS> constexpr int kTile = NS == 4 ? 128 : 64;
+
+template <int D, int ROWS>
+constexpr size_t smem_bytes() { return sizeof(float) * (2 * ROWS * (D + 4) + 2 * ROWS); }
+
+// Forward.  Online softmax as in the pseudo-code of Appendix A (running row maximum m and row sum l,
+// old terms multiplied by exp(m_old - m_new)); a lane holds the scores of ONE query.
+template <int D, int NS>
+__global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(F32Params p) {
+  constexpr int NR = 4 / NS, NB = D / 32, LD = D + 4, BK = kTile<NS>;
+  typedef typename Run<NB>::type run_t;
   extern __shared__ __align__(16) float smem[];
   float* Ks = smem;
   float* Vs = Ks + BK * LD;
-  float* Qs = Vs + BK * LD;
-  float* Gs = Qs + BQ * LD;       // dO tile
-  float* Ps = Gs + BQ * LD;       // P
-  float* Ts = Ps + BQ * LS;       // scale * dS
-  float* row_L = Ts + BQ * LS;
-  float* row_D = row_L + BQ;
-  const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
-  const int kh = blockIdx.y, k0 = blockIdx.x * BK;
-  load_tile<D, BK, LD>(Ks, p.k + kh * p.kv_sh, p.kv_ss, k0, p.s_k);
-  load_tile<D, BK, LD>(Vs, p.v + kh * p.kv_sh, p.kv_ss, k0, p.s_k);
-  float dk[4][NC], dv[4][NC];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int c = 0; c < NC; ++c) { dk[a][c] = 0.f; dv[a][c] = 0.f; }
+  const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rb = wave % NR, part = wave / NR;
+  const int h = blockIdx.x / p.nx_q, kh = h / p.group;
+  int xq = blockIdx.x % p.nx_q;
+  if (p.causal) xq = p.nx_q - 1 - xq;       // longest rows first
+  const int q0 = xq * NR * 32, q0w = q0 + rb * 32, qrow = q0w + r32;
+  const bool qvalid = qrow < p.s_q;
+  const float* kg = p.k + kh * p.kv_sh;
+  const float* vg = p.v + kh * p.kv_sh;
+  const int k_end = p.causal ? min(p.s_k, q0 + NR * 32) : p.s_k;
 
-  const int q_begin = p.causal ? (k0 / BQ) * BQ : 0;
-  for (int hq = kh * p.group; hq < (kh + 1) * p.group; ++hq) {
-    for (int q0 = q_begin; q0 < p.s_q; q0 += BQ) {
-      __syncthreads();
-      load_tile<D, BQ, LD>(Qs, p.q + hq * p.q_sh, p.q_ss, q0, p.s_q);
-      load_tile<D, BQ, LD>(Gs, p.dO + hq * p.q_sh, p.q_ss, q0, p.s_q);
-      if (tid < BQ) {
-        const bool ok = q0 + tid < p.s_q;
-        row_L[tid] = ok ? p.lse_in[hq * p.l_sh + q0 + tid] : -INFINITY;
-        row_D[tid] = ok ? p.delta[hq * p.l_sh + q0 + tid] : 0.f;
-      }
-      __syncthreads();
-      {  // s = q k^T and dp = dO v^T on a 2x4 micro-tile: rows ty*2+a, cols tx*4+b
-        float s[2][4], dp[2][4];
+  TilePair<D, BK> tile;
+  tile.load(kg, vg, p.kv_ss, 0, p.s_k);
+  f32x4 q[D / 8];
+  load_rows<D>(q, p.q + h * p.q_sh, p.q_ss, qrow, qvalid, hh);
+
+  // Empty state, or (accumulate, first part) the state of the earlier key/value chunks: the normalised
+  // output with its logsumexp is the running (o, m, l) with m = lse and l = 1.
+  f32x16 o[NB];
+  zero(o);
+  float m_run = -INFINITY, l_run = 0.f;      // l_run: this lane's half of the row sum
+  const int64_t obase = h * p.o_sh + static_cast<int64_t>(qvalid ? qrow : 0) * p.o_ss;
+  if (p.accumulate && part == 0 && qvalid) {
+    const float L = p.lse[h * p.l_sh + qrow];
+    if (L > -INFINITY) {
+      m_run = L;
+      l_run = hh == 0 ? 1.f : 0.f;
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+      for (int i = 0; i < 16; ++i)
 #pragma unroll
-          for (int b = 0; b < 4; ++b) { s[a][b] = 0.f; dp[a][b] = 0.f; }
-        for (int c = 0; c < D; c += 4) {
-          float4 qa[2], ga[2], kb[4], vb[4];
-#pragma unroll
-          for (int a = 0; a < 2; ++a) {
-            qa[a] = *reinterpret_cast<const float4*>(Qs + (ty * 2 + a) * LD + c);
-            ga[a] = *reinterpret_cast<const float4*>(Gs + (ty * 2 + a) * LD + c);
-          }
-#pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            kb[b] = *reinterpret_cast<const float4*>(Ks + (tx * 4 + b) * LD + c);
-            vb[b] = *reinterpret_cast<const float4*>(Vs + (tx * 4 + b) * LD + c);
-          }
-#pragma unroll
-          for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              s[a][b] = fmaf(qa[a].x, kb[b].x, s[a][b]); s[a][b] = fmaf(qa[a].y, kb[b].y, s[a][b]);
-              s[a][b] = fmaf(qa[a].z, kb[b].z, s[a][b]); s[a][b] = fmaf(qa[a].w, kb[b].w, s[a][b]);
-              dp[a][b] = fmaf(ga[a].x, vb[b].x, dp[a][b]); dp[a][b] = fmaf(ga[a].y, vb[b].y, dp[a][b]);
-              dp[a][b] = fmaf(ga[a].z, vb[b].z, dp[a][b]); dp[a][b] = fmaf(ga[a].w, vb[b].w, dp[a][b]);
-            }
+        for (int j = 0; j < NB; ++j) {
+          const int64_t off = obase + NB * ((i >> 2) * 8 + 4 * hh + (i & 3)) + j;
+          o[j][i] = p.o_bf16 ? static_cast<float>(static_cast<const __bf16*>(p.o)[off]) : static_cast<const float*>(p.o)[off];
         }
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          const int r = ty * 2 + a, qi = q0 + r;
-          const float L = row_L[r], Dl = row_D[r];
-#pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            const int kj = k0 + tx * 4 + b;
-            const bool vis = qi < p.s_q && kj < p.s_k && (!p.causal || kj <= qi) && L > -INFINITY;
-            const float pr = vis ? expf(s[a][b] * p.scale - L) : 0.f;
-            Ps[r * LS + tx * 4 + b] = pr;
-            Ts[r * LS + tx * 4 + b] = pr * (dp[a][b] - Dl) * p.scale;
-          }
-        }
-      }
-      __syncthreads();
-      // dv_j += sum_i P_ij dO_i ; dk_j += sum_i (scale dS_ij) q_i   (key rows ty*4+a, cols tx+16c)
-      for (int i = 0; i < BQ; ++i) {
-        float pj[4], tj[4], gv[NC], qv[NC];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) { pj[a] = Ps[i * LS + ty * 4 + a]; tj[a] = Ts[i * LS + ty * 4 + a]; }
-#pragma unroll
-        for (int c = 0; c < NC; ++c) { gv[c] = Gs[i * LD + tx + 16 * c]; qv[c] = Qs[i * LD + tx + 16 * c]; }
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int c = 0; c < NC; ++c) { dv[a][c] = fmaf(pj[a], gv[c], dv[a][c]); dk[a][c] = fmaf(tj[a], qv[c], dk[a][c]); }
-      }
-      if (p.dq) {  // dq_i += sum_j (scale dS_ij) k_j : row tid/8, cols (tid%8) + 8c
-        const int r = tid / 8, cx = tid % 8;
-        float dqa[NQ];
-#pragma unroll
-        for (int c = 0; c < NQ; ++c) dqa[c] = 0.f;
-        for (int j = 0; j < BK; ++j) {
-          const float t = Ts[r * LS + j];
-#pragma unroll
-          for (int c = 0; c < NQ; ++c) dqa[c] = fmaf(t, Ks[j * LD + cx + 8 * c], dqa[c]);
-        }
-        if (q0 + r < p.s_q) {
-          float* dst = p.dq + hq * p.dq_sh + static_cast<int64_t>(q0 + r) * p.dq_ss;
-#pragma unroll
-          for (int c = 0; c < NQ; ++c) atomicAdd(dst + cx + 8 * c, dqa[c]);
-        }
-      }
     }
   }
+
+  for (int k0 = 0; k0 < k_end; k0 += BK) {
+    if (k0) __syncthreads();                 // the tile before has been read
+    tile.store(Ks, Vs, k0, p.s_k);
+    __syncthreads();
+    if (k0 + BK < k_end) tile.load(kg, vg, p.kv_ss, k0 + BK, p.s_k);
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int kj = k0 + ty * 4 + a;
-    if (kj >= p.s_k || !p.dk) continue;
-    float* dkp = p.dk + kh * p.dkv_sh + static_cast<int64_t>(kj) * p.dkv_ss;
-    float* dvp = p.dv + kh * p.dkv_sh + static_cast<int64_t>(kj) * p.dkv_ss;
+    for (int kb = part * 32; kb < BK; kb += NS * 32) {
+      const int kb0 = k0 + kb;
+      if (kb0 >= p.s_k || (p.causal && kb0 > q0w + 31)) break;
+      f32x16 s;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int col = tx + 16 * c;
-      if (p.accumulate) { dkp[col] += dk[a][c]; dvp[col] += dv[a][c]; }
-      else { dkp[col] = dk[a][c]; dvp[col] = dv[a][c]; }
+      for (int i = 0; i < 16; ++i) s[i] = 0.f;
+      row_product<D>(s, Ks + kb * LD, q, r32, hh);
+      float mx = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int kvi = kb0 + (i >> 2) * 8 + 4 * hh + (i & 3);
+        s[i] = kvi < p.s_k && !(p.causal && kvi > qrow) ? s[i] * p.scale : -INFINITY;
+        mx = fmaxf(mx, s[i]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float m_new = fmaxf(m_run, mx);
+      const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = expf(m_run - m_safe);   // exp(-inf) = 0 on the first block
+      float sum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) { s[i] = expf(s[i] - m_safe); sum += s[i]; }
+      m_run = m_new;
+      l_run = l_run * alpha + sum;
+      if (__any(alpha != 1.f)) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[j][i] *= alpha;
+      }
+      col_product<D>(o, Vs + kb * LD, s, r32, hh);
     }
   }
+
+  float l_tot = l_run + __shfl_xor(l_run, 32);
+  if constexpr (NS > 1) {       // combine the parts: exact, against the largest of their maxima
+    constexpr int NV = NB * 16;
+    float* st = smem + 4 * NV * 64;          // m, l of every wavefront's 32 rows
+    __syncthreads();
+    if (part > 0) put_result<NB>(smem + wave * NV * 64, o, lane);
+    if (hh == 0) { st[wave * 64 + r32] = m_run; st[wave * 64 + 32 + r32] = l_tot; }
+    __syncthreads();
+    if (part > 0) return;
+    float m = m_run;
+#pragma unroll
+    for (int s = 1; s < NS; ++s) m = fmaxf(m, st[(s * NR + rb) * 64 + r32]);
+    const float m_safe = m == -INFINITY ? 0.f : m;
+    const float f0 = expf(m_run - m_safe);
+    l_tot *= f0;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[j][i] *= f0;
+#pragma unroll
+    for (int s = 1; s < NS; ++s) {
+      const int w = s * NR + rb;
+      const float f = expf(st[w * 64 + r32] - m_safe);
+      l_tot = fmaf(st[w * 64 + 32 + r32], f, l_tot);
+      add_result<NB>(smem + w * NV * 64, o, lane, f);
+    }
+    m_run = m;
+  }
+  if (!qvalid) return;
+  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  if (hh == 0) p.lse[h * p.l_sh + qrow] = l_tot > 0.f ? m_run + logf(l_tot) : -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int64_t off = obase + NB * ((i >> 2) * 8 + 4 * hh + (i & 3));
+    if (p.o_bf16) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j) static_cast<__bf16*>(p.o)[off + j] = static_cast<__bf16>(o[j][i] * inv);
+    } else {
+      run_t x;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) x[j] = o[j][i] * inv;
+      *reinterpret_cast<run_t*>(static_cast<float*>(p.o) + off) = x;
+    }
+  }
+}
+
+// dk, dv of one workgroup's key rows: K and V rows in registers, Q / dO tiles (with lse and D) in LDS,
+// summed over the query heads of the group.
+// V_LDS: at d = 128 with 128-row tiles K, V, dK, dV and the tile on its way are more registers than
+// there are; V (the same 32 rows for all four wavefronts) then stays in LDS.
+template <int D, int NS> constexpr bool kVLds = D == 128 && NS == 4;
+template <int D, int NS>
+__device__ __forceinline__ void bwd_dkdv(const F32Params& p, int item, float* smem) {
+  constexpr int NR = 4 / NS, NB = D / 32, LD = D + 4, BQ = 32 * NS;
+  constexpr bool V_LDS = kVLds<D, NS>;
+  float* Qs = smem;
+  float* Gs = Qs + BQ * LD;
+  float* Ls = Gs + BQ * LD;
+  float* Ds = Ls + BQ;
+  float* Vs = Ds + BQ;
+  const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rb = wave % NR, part = wave / NR;
+  const int kh = item / p.nx_kv, k0 = (item % p.nx_kv) * NR * 32, k0w = k0 + rb * 32, kvrow = k0w + r32;
+  const bool kvalid = kvrow < p.s_k;
+  const int q_begin = p.causal ? k0 : 0;
+
+  TilePair<D, BQ> tile;
+  float ld = 0.f;                            // lse (first BQ threads) or D (next BQ) of the tile on its way
+  auto load = [&](int hq, int q0) {
+    tile.load(p.q + hq * p.q_sh, p.dO + hq * p.q_sh, p.q_ss, q0, p.s_q);
+    if (tid < 2 * BQ) {
+      const int r = q0 + tid % BQ;
+      const float* src = (tid < BQ ? p.lse_in : p.delta) + hq * p.l_sh;
+      ld = r < p.s_q ? src[r] : tid < BQ ? -INFINITY : 0.f;
+    }
+  };
+  int hq = kh * p.group, q0 = q_begin;
+  const int h_end = hq + p.group;
+  load(hq, q0);
+  f32x4 k[D / 8], v[V_LDS ? 1 : D / 8];
+  load_rows<D>(k, p.k + kh * p.kv_sh, p.kv_ss, kvrow, kvalid, hh);
+  if constexpr (V_LDS) {
+    for (int i = tid; i < 32 * (D / 4); i += NT) {
+      const int r = k0 + i / (D / 4), c = (i % (D / 4)) * 4;
+      f32x4 x = {0.f, 0.f, 0.f, 0.f};
+      if (r < p.s_k) x = *reinterpret_cast<const f32x4*>(p.v + kh * p.kv_sh + static_cast<int64_t>(r) * p.kv_ss + c);
+      *reinterpret_cast<f32x4*>(Vs + (r - k0) * LD + c) = x;
+    }
+  } else {
+    load_rows<D>(v, p.v + kh * p.kv_sh, p.kv_ss, kvrow, kvalid, hh);
+  }
+  f32x16 dk[NB], dv[NB];
+  zero(dk);
+  zero(dv);
+  for (bool first = true; hq < h_end; first = false) {
+    if (!first) __syncthreads();
+    tile.store(Qs, Gs, q0, p.s_q);
+    if (tid < 2 * BQ) Ls[tid] = ld;          // Ds follows Ls
+    __syncthreads();
+    const int q0t = q0 + part * 32;          // this wavefront's 32 rows of the tile
+    q0 += BQ;
+    if (q0 >= p.s_q) { q0 = q_begin; ++hq; }
+    if (hq < h_end) load(hq, q0);
+    if (q0t >= p.s_q || (p.causal && k0w > q0t + 31)) continue;
+    const float* Qw = Qs + part * 32 * LD;
+    const float* Gw = Gs + part * 32 * LD;
+    f32x16 s, dp;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
+    row_product<D>(s, Qw, k, r32, hh);
+    if constexpr (V_LDS) row_product<D>(dp, Gw, Vs, r32, hh);
+    else row_product<D>(dp, Gw, v, r32, hh);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int r = (i >> 2) * 8 + 4 * hh + (i & 3);
+      const float L = Ls[part * 32 + r];      // -inf for rows past the end and empty rows
+      const bool vis = L > -INFINITY && !(p.causal && kvrow > q0t + r);
+      s[i] = vis ? expf(s[i] * p.scale - L) : 0.f;
+      dp[i] = s[i] * (dp[i] - Ds[part * 32 + r]);
+    }
+    col_product<D>(dv, Gw, s, r32, hh);
+    col_product<D>(dk, Qw, dp, r32, hh);
+  }
+  if constexpr (NS > 1) {
+    constexpr int NV = NB * 16;
+    __syncthreads();
+    if (part > 0) {
+      float* x = smem + (wave - NR) * 2 * NV * 64;
+      put_result<NB>(x, dk, lane);
+      put_result<NB>(x + NV * 64, dv, lane);
+    }
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (int s = 1; s < NS; ++s) {
+      const float* x = smem + (s * NR + rb - NR) * 2 * NV * 64;
+      add_result<NB>(x, dk, lane, 1.f);
+      add_result<NB>(x + NV * 64, dv, lane, 1.f);
+    }
+  }
+  if (!kvalid) return;
+  const int64_t off = kh * p.dkv_sh + static_cast<int64_t>(kvrow) * p.dkv_ss;
+  write_grad<D>(p.dk + off, dk, p.scale, p.accumulate, hh);
+  write_grad<D>(p.dv + off, dv, 1.f, p.accumulate, hh);
+}
+
+// dq of one workgroup's query rows: Q and dO rows in registers, K / V tiles in LDS.
+template <int D, int NS>
+__device__ __forceinline__ void bwd_dq(const F32Params& p, int item, float* smem) {
+  constexpr int NR = 4 / NS, NB = D / 32, LD = D + 4, BK = 32 * NS;
+  float* Ks = smem;
+  float* Vs = Ks + BK * LD;
+  const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rb = wave % NR, part = wave / NR;
+  const int h = item / p.nx_q, kh = h / p.group;
+  int xq = item % p.nx_q;
+  if (p.causal) xq = p.nx_q - 1 - xq;
+  const int q0 = xq * NR * 32, q0w = q0 + rb * 32, qrow = q0w + r32;
+  const bool qvalid = qrow < p.s_q;
+  const float* kg = p.k + kh * p.kv_sh;
+  const float* vg = p.v + kh * p.kv_sh;
+  const int k_end = p.causal ? min(p.s_k, q0 + NR * 32) : p.s_k;
+
+  TilePair<D, BK> tile;
+  tile.load(kg, vg, p.kv_ss, 0, p.s_k);
+  f32x4 q[D / 8], g[D / 8];
+  load_rows<D>(q, p.q + h * p.q_sh, p.q_ss, qrow, qvalid, hh);
+  load_rows<D>(g, p.dO + h * p.q_sh, p.q_ss, qrow, qvalid, hh);
+  const float L = qvalid ? p.lse_in[h * p.l_sh + qrow] : -INFINITY;
+  const float Dr = qvalid ? p.delta[h * p.l_sh + qrow] : 0.f;
+  f32x16 dq[NB];
+  zero(dq);
+  for (int k0 = 0; k0 < k_end; k0 += BK) {
+    if (k0) __syncthreads();
+    tile.store(Ks, Vs, k0, p.s_k);
+    __syncthreads();
+    if (k0 + BK < k_end) tile.load(kg, vg, p.kv_ss, k0 + BK, p.s_k);
+    const int kb0 = k0 + part * 32;
+    if (kb0 >= p.s_k || (p.causal && kb0 > q0w + 31)) continue;
+    const float* Kw = Ks + part * 32 * LD;
+    f32x16 s, dp;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
+    row_product<D>(s, Kw, q, r32, hh);
+    row_product<D>(dp, Vs + part * 32 * LD, g, r32, hh);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int kvi = kb0 + (i >> 2) * 8 + 4 * hh + (i & 3);
+      const bool vis = kvi < p.s_k && L > -INFINITY && !(p.causal && kvi > qrow);
+      const float pr = vis ? expf(s[i] * p.scale - L) : 0.f;
+      dp[i] = pr * (dp[i] - Dr);
+    }
+    col_product<D>(dq, Kw, dp, r32, hh);
+  }
+  if constexpr (NS > 1) {
+    constexpr int NV = NB * 16;
+    __syncthreads();
+    if (part > 0) put_result<NB>(smem + wave * NV * 64, dq, lane);
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (int s = 1; s < NS; ++s) add_result<NB>(smem + (s * NR + rb) * NV * 64, dq, lane, 1.f);
+  }
+  if (!qvalid) return;
+  write_grad<D>(p.dq + h * p.dq_sh + static_cast<int64_t>(qrow) * p.dq_ss, dq, p.scale, p.accumulate, hh);
+}
+
+// Backward: 7 products in two kinds of workgroups of ONE launch (dk/dv first, they are the longer
+// ones), each output written once: no atomics, no zero fill, a fixed order of summation.  The fused
+// form (5 products, dq added with fp32 atomics) left a short chunk with as few workgroups as it has key
+// tiles.
+template <int D, int NS>
+__global__ void __launch_bounds__(NT, 1) k_bwd_f32(F32Params p) {
+  extern __shared__ __align__(16) float smem[];
+  const int item = blockIdx.x;
+  if (item < p.n_kv) bwd_dkdv<D, NS>(p, item, smem);
+  else bwd_dq<D, NS>(p, item - p.n_kv, smem);
 }
 
 F32Params make_params(const dfa_shape& sh) {
   F32Params p{};
-  p.s_q = sh.s_q; p.s_k = sh.s_k; p.group = sh.h_q / sh.h_kv; p.causal = sh.causal;
+  p.s_q = sh.s_q; p.s_k = sh.s_k; p.h_q = sh.h_q; p.h_kv = sh.h_kv; p.group = sh.h_q / sh.h_kv; p.causal = sh.causal;
   p.o_bf16 = sh.o_dtype == DFA_BF16; p.scale = sh.scale;
   p.q_sh = sh.q_stride_h; p.q_ss = sh.q_stride_s; p.kv_sh = sh.kv_stride_h; p.kv_ss = sh.kv_stride_s;
   p.o_sh = sh.o_stride_h; p.o_ss = sh.o_stride_s; p.l_sh = sh.lse_stride_h;
@@ -300,10 +493,44 @@ F32Params make_params(const dfa_shape& sh) {
   return p;
 }
 
-template <typename K>
-int set_smem(K kernel, size_t bytes) {
-  return hip_status(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes)));
+// More than 64 KB of dynamic LDS needs the opt-in, once per kernel and process (thread-safe).
+template <void (*KERNEL)(F32Params)>
+int launch(const F32Params& p, int64_t blocks, size_t smem, hipStream_t st) {
+  static std::once_flag once;
+  static int attr_rc = DFA_OK;
+  std::call_once(once, [smem] {
+    attr_rc = hip_status(hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem)));
+  });
+  if (attr_rc) return attr_rc;
+  if (blocks > (1 << 30)) return DFA_ERR_SHAPE;
+  KERNEL<<<static_cast<int>(blocks), NT, smem, st>>>(p);
+  return last_launch_status();
+}
+
+int64_t blocks_of(int rows, int per) { return (static_cast<int64_t>(rows) + per - 1) / per; }
+
+template <int D, int NS>
+int fwd(F32Params p, hipStream_t st) {
+  const int rows = 32 * (4 / NS);
+  // tiles; the combination of the parts takes 4 results and 256 floats of row statistics
+  const size_t comb = NS > 1 ? sizeof(float) * (4 * (D / 32) * 16 * 64 + 256) : 0;
+  const size_t tiles = smem_bytes<D, kTile<NS>>();
+  p.nx_q = static_cast<int>(blocks_of(p.s_q, rows));
+  return launch<k_fwd_f32<D, NS>>(p, static_cast<int64_t>(p.nx_q) * p.h_q, tiles > comb ? tiles : comb, st);
+}
+
+template <int D, int NS>
+int bwd(F32Params p, hipStream_t st) {
+  const int rows = 32 * (4 / NS);
+  const size_t comb = NS > 1 ? sizeof(float) * (4 - 4 / NS) * 2 * (D / 32) * 16 * 64 : 0;
+  const size_t tiles = smem_bytes<D, 32 * NS>() + (kVLds<D, NS> ? sizeof(float) * 32 * (D + 4) : 0);
+  p.nx_kv = static_cast<int>(blocks_of(p.s_k, rows));
+  p.nx_q = static_cast<int>(blocks_of(p.s_q, rows));
+  const int64_t n_kv = p.dk ? static_cast<int64_t>(p.nx_kv) * p.h_kv : 0, n_q = p.dq ? static_cast<int64_t>(p.nx_q) * p.h_q : 0;
+  if (n_kv > (1 << 30)) return DFA_ERR_SHAPE;
+  p.n_kv = static_cast<int>(n_kv);
+  return launch<k_bwd_f32<D, NS>>(p, n_kv + n_q, tiles > comb ? tiles : comb, st);
 }
 
 }  // namespace
@@ -312,13 +539,16 @@ int launch_fwd_f32(const dfa_shape& sh, const float* q, const float* k, const fl
                    void* o, float* lse, int accumulate, hipStream_t st) {
   F32Params p = make_params(sh);
   p.q = q; p.k = k; p.v = v; p.o = o; p.lse = lse; p.accumulate = accumulate;
-  dim3 grid((sh.s_q + 63) / 64, sh.h_q);
-  const int D = sh.d;
-  const size_t smem = sizeof(float) * (3 * 64 * (D + 4) + 64 * 65 + 3 * 64);
-  int rc;
-  if (D == 128) { if ((rc = set_smem(k_fwd_f32<128>, smem))) return rc; k_fwd_f32<128><<<grid, kThreads, smem, st>>>(p); }
-  else { if ((rc = set_smem(k_fwd_f32<64>, smem))) return rc; k_fwd_f32<64><<<grid, kThreads, smem, st>>>(p); }
-  return last_launch_status();
+  // Parts per tile.  A workgroup with more parts is done sooner, but stages every tile for fewer rows and
+  // runs fewer wavefronts per SIMD.  us per full pair, d = 128, with 1 / 2 / 4 parts:
+  //   8 heads x 256 rows 47 / 29 / 22, 32 x 256 49 / 31 / 28, 8 x 1024 174 / 103 / 71 (<= 256 workgroups of
+  //   4 parts: one round),  32 x 1024 190 / 183 / 271,  32 x 4096 2361 / 2501 / 3920 (116 TFLOP/s with 1);
+  //   causal, 32 x 4096: 2322 / 2043 / 2579 (64-row blocks share out the diagonal better than 128-row ones).
+  // The vector-FMA kernel this one replaced took 610 us at 8 x 1024.
+  const int64_t wg2 = blocks_of(sh.s_q, 64) * sh.h_q, wg4 = blocks_of(sh.s_q, 32) * sh.h_q;
+  const int parts = wg4 <= 256 ? 4 : wg2 <= 512 || sh.causal ? 2 : 1;
+  if (sh.d == 128) return parts == 4 ? fwd<128, 4>(p, st) : parts == 2 ? fwd<128, 2>(p, st) : fwd<128, 1>(p, st);
+  return parts == 4 ? fwd<64, 4>(p, st) : parts == 2 ? fwd<64, 2>(p, st) : fwd<64, 1>(p, st);
 }
 
 int launch_bwd_f32(const dfa_shape& sh, const float* q, const float* k, const float* v,
@@ -327,17 +557,17 @@ int launch_bwd_f32(const dfa_shape& sh, const float* q, const float* k, const fl
   F32Params p = make_params(sh);
   p.q = q; p.k = k; p.v = v; p.lse_in = lse; p.delta = delta; p.dO = dO;
   p.dq = dq; p.dk = dk; p.dv = dv; p.accumulate = accumulate;
-  int rc;
-  if (!accumulate && dq) {
-    rc = launch_fill_zero_rows(dq, sh.h_q, sh.s_q, sh.d, sh.dq_stride_h, sh.dq_stride_s, st);
-    if (rc) return rc;
-  }
-  dim3 grid((sh.s_k + 63) / 64, sh.h_kv);
-  const int D = sh.d;
-  const size_t smem = sizeof(float) * (2 * 64 * (D + 4) + 2 * 32 * (D + 4) + 2 * 32 * 65 + 2 * 32);
-  if (D == 128) { if ((rc = set_smem(k_bwd_f32<128>, smem))) return rc; k_bwd_f32<128><<<grid, kThreads, smem, st>>>(p); }
-  else { if ((rc = set_smem(k_bwd_f32<64>, smem))) return rc; k_bwd_f32<64><<<grid, kThreads, smem, st>>>(p); }
-  return last_launch_status();
+  // Parts per tile, as in the forward; us per full pair (dk, dv and dq), d = 128, with 1 / 2 / 4 parts:
+  //   8 / 2 heads x 1024 rows 1183 / 647 / 371 (320 workgroups of 4 parts),  32 x 256 87 / 57 / 72 (256
+  //   workgroups of 2),  32 x 1024 547 / 604 / 725,  32 x 4096 8370 / 9210 / 11380 (82 TFLOP/s with 1);
+  //   causal, 32 x 4096 8240 / 7050 / 6960, 32 x 1024 545 / 593 / 725.
+  // The vector-FMA kernel this one replaced (dq by atomics) took 2.9 ms at 8 / 2 x 1024.
+  auto workgroups = [&](int rows) {
+    return (dk ? blocks_of(sh.s_k, rows) * sh.h_kv : 0) + (dq ? blocks_of(sh.s_q, rows) * sh.h_q : 0);
+  };
+  const int parts = workgroups(32) <= 384 ? 4 : workgroups(64) <= 512 || (sh.causal && workgroups(128) >= 1024) ? 2 : 1;
+  if (sh.d == 128) return parts == 4 ? bwd<128, 4>(p, st) : parts == 2 ? bwd<128, 2>(p, st) : bwd<128, 1>(p, st);
+  return parts == 4 ? bwd<64, 4>(p, st) : parts == 2 ? bwd<64, 2>(p, st) : bwd<64, 1>(p, st);
 }
 
 }  // namespace dfa
