@@ -35,6 +35,46 @@ struct FwdParams {
   int64_t q_sh, q_ss, kv_sh, kv_ss, o_sh, o_ss, l_sh;
 };
 
+// O^T tile of one query row per lane, read from (the state of earlier chunks) and written to memory
+__device__ __forceinline__ void load_o(f32x16 (&o)[4], const FwdParams& p, int head, int qrow, int hh) {
+  const int64_t obase = head * p.o_sh + static_cast<int64_t>(qrow) * p.o_ss;
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+      const int col = db * 32 + g4 * 8 + hh * 4;
+      if (p.o_bf16) {
+        const bf16x4 b = *reinterpret_cast<const bf16x4*>(static_cast<const __bf16*>(p.o) + obase + col);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[db][g4 * 4 + e] = static_cast<float>(b[e]);
+      } else {
+        const float4 x = *reinterpret_cast<const float4*>(static_cast<const float*>(p.o) + obase + col);
+        o[db][g4 * 4] = x.x; o[db][g4 * 4 + 1] = x.y; o[db][g4 * 4 + 2] = x.z; o[db][g4 * 4 + 3] = x.w;
+      }
+    }
+}
+__device__ __forceinline__ void store_o(const f32x16 (&o)[4], const FwdParams& p, int head, int qrow, int hh, float inv) {
+  const int64_t obase = head * p.o_sh + static_cast<int64_t>(qrow) * p.o_ss;
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+      const int col = db * 32 + g4 * 8 + hh * 4;
+      const float x0 = o[db][g4 * 4 + 0] * inv, x1 = o[db][g4 * 4 + 1] * inv;
+      const float x2 = o[db][g4 * 4 + 2] * inv, x3 = o[db][g4 * 4 + 3] * inv;
+      if (p.o_bf16) {
+        bf16x4 b; b[0] = static_cast<__bf16>(x0); b[1] = static_cast<__bf16>(x1);
+        b[2] = static_cast<__bf16>(x2); b[3] = static_cast<__bf16>(x3);
+        *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o) + obase + col) = b;
+      } else {
+        *reinterpret_cast<float4*>(static_cast<float*>(p.o) + obase + col) = make_float4(x0, x1, x2, x3);
+      }
+    }
+}
+
+// CAUSAL: the diagonal pair.  Its row sums are taken over the fp32 weights; those of a full pair over the
+// bf16-rounded weights that multiply V, as in the other full-pair forms.
+template <bool FULL>
 __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(FwdParams p) {
   extern __shared__ __align__(16) char smem[];   // two (K tile, V tile) buffers
 
@@ -90,21 +130,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(FwdParams p) {
     if (L > -INFINITY) {
       m_run = L / p.scale;
       l_run = hh == 0 ? 1.f : 0.f;
-      const int64_t obase = head * p.o_sh + static_cast<int64_t>(qrow) * p.o_ss;
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          const int col = db * 32 + g4 * 8 + hh * 4;
-          if (p.o_bf16) {
-            const bf16x4 b = *reinterpret_cast<const bf16x4*>(static_cast<const __bf16*>(p.o) + obase + col);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[db][g4 * 4 + e] = static_cast<float>(b[e]);
-          } else {
-            const float4 x = *reinterpret_cast<const float4*>(static_cast<const float*>(p.o) + obase + col);
-            o[db][g4 * 4] = x.x; o[db][g4 * 4 + 1] = x.y; o[db][g4 * 4 + 2] = x.z; o[db][g4 * 4 + 3] = x.w;
-          }
-        }
+      load_o(o, p, head, qrow, hh);
     }
   }
 
@@ -124,7 +150,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(FwdParams p) {
   // taken against the stale maximum - they stay below 2^8, harmless in fp32 / bf16 - and O needs
   // no rescaling; the final division by the row sum makes the result independent of the reference.
   // Returns the factor O has to be multiplied by (1 when the reference did not move).
-  auto softmax_block = [&](f32x16& s) {
+  auto softmax_block = [&](f32x16& s, bf16x8 (&pb)[2]) {
     float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
 #pragma unroll
     for (int j = 3; j < 15; j += 2) mx = fmaxf(fmaxf(mx, s[j]), s[j + 1]);
@@ -144,9 +170,10 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(FwdParams p) {
     for (int j = 0; j < 16; ++j) {
       const float e = __builtin_amdgcn_exp2f(fmaf(s[j], c2, -mc));
       s[j] = e;
-      sum += e;
+      if (!FULL) sum += e;
     }
-    l_run += sum;
+    pb[0] = pack8(s, 0); pb[1] = pack8(s, 8);
+    l_run += FULL ? sum8(pb[0], 0.f) + sum8(pb[1], 0.f) : sum;
     return alpha;
   };
   auto rescale_o = [&](float alpha) {
@@ -221,8 +248,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(FwdParams p) {
         }
         gv[0] = lds_gather(Vs, g_base);
         gv[1] = lds_gather(Vs, g_base + 64);
-        alpha0 = softmax_block(s0);
-        pb0[0] = pack8(s0, 0); pb0[1] = pack8(s0, 8);
+        alpha0 = softmax_block(s0, pb0);
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 MFMA
@@ -243,8 +269,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(FwdParams p) {
           const int n = i + 2;    // next gather: block 0 second half, then block 1
           gv[i & 1] = lds_gather(Vs, g_base + (n >> 2) * 16 * kRowBytes + (n & 3) * 64);
         }
-        alpha1 = softmax_block(s1);
-        pb1[0] = pack8(s1, 0); pb1[1] = pack8(s1, 8);
+        alpha1 = softmax_block(s1, pb1);
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -279,22 +304,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(FwdParams p) {
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   if (qvalid) {
     if (hh == 0) p.lse[head * p.l_sh + qrow] = l_tot > 0.f ? m_run * p.scale + logf(l_tot) : -INFINITY;
-    const int64_t obase = head * p.o_sh + static_cast<int64_t>(qrow) * p.o_ss;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int col = db * 32 + g4 * 8 + hh * 4;
-        const float x0 = o[db][g4 * 4 + 0] * inv, x1 = o[db][g4 * 4 + 1] * inv;
-        const float x2 = o[db][g4 * 4 + 2] * inv, x3 = o[db][g4 * 4 + 3] * inv;
-        if (p.o_bf16) {
-          bf16x4 b; b[0] = static_cast<__bf16>(x0); b[1] = static_cast<__bf16>(x1);
-          b[2] = static_cast<__bf16>(x2); b[3] = static_cast<__bf16>(x3);
-          *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o) + obase + col) = b;
-        } else {
-          *reinterpret_cast<float4*>(static_cast<float*>(p.o) + obase + col) = make_float4(x0, x1, x2, x3);
-        }
-      }
+    store_o(o, p, head, qrow, hh, inv);
   }
 }
 
@@ -311,8 +321,8 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(FwdParams p) {
 // A wavefront overlaps nothing with itself (measured), different wavefronts of a SIMD do: here the
 // exponentials of two S wavefronts run under the MFMAs of all four.  Measured against the
 // 4-wavefront kernel above: 10 % faster on a 4096 x 4096 pair in spite of a lower clock under
-// load (1.8 GHz); 5 % slower on the causal diagonal pair (256-row granularity), which therefore
-// stays with the kernel above.
+// load (1.8 GHz).  On the causal diagonal pair its 256-row granularity costs half a row block per row
+// of tiles: slower than the kernel above up to about 6000 rows, 8 % faster at 16384.
 // ============================================================================================
 namespace full_pair {
 
@@ -329,7 +339,8 @@ constexpr int OFF_ST = OFF_AL + 2 * AL_BYTES;  // 1 / row sum, written once by t
 constexpr int SMEM_BYTES = OFF_ST + AL_BYTES;
 
 // RAGGED: s_k is no multiple of the 64-row tile, so the last K/V tile has rows past the end.
-template <bool RAGGED>
+// CAUSAL: the diagonal pair; its row sums are taken over the fp32 weights, as in the other causal forms.
+template <bool RAGGED, bool CAUSAL>
 __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(FwdParams p) {
   extern __shared__ __align__(16) char smem[];
 
@@ -338,7 +349,7 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(FwdParams p) {
   if (item >= p.total) return;
   const int head = item / p.ntq;
   int tq = item % p.ntq;
-  if (p.causal) tq = p.ntq - 1 - tq;      // longest rows first
+  if (CAUSAL) tq = p.ntq - 1 - tq;      // longest rows first
   const int kh = head / p.group;
   const int q0 = tq * BMW;
 
@@ -348,7 +359,7 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(FwdParams p) {
   const int r32 = lane & 31, hh = lane >> 5;
   const float c2 = p.scale * LOG2E;
 
-  const int k_end = p.causal ? min(p.s_k, q0 + BMW) : p.s_k;
+  const int k_end = CAUSAL ? min(p.s_k, q0 + BMW) : p.s_k;
   const int ntiles = (k_end + BN - 1) / BN;
 
   if (!pv_wave) {
@@ -395,7 +406,7 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(FwdParams p) {
                                          wave < 4 ? smem + OFF_K + ((it + 1) & 1) * TILE_BYTES
                                                   : smem + OFF_V + ((it + 1) % 3) * TILE_BYTES,
                                          wave & 3, lane);
-      const bool active = !(p.causal && k0 > q0w + 31);   // else: the whole tile lies above this block's diagonal
+      const bool active = !(CAUSAL && k0 > q0w + 31);   // else: the whole tile lies above this block's diagonal
       if (!active) {
         tile_copy_piece<0>(cn); tile_copy_piece<1>(cn); tile_copy_piece<2>(cn); tile_copy_piece<3>(cn);
         if ((wave & 3) == 0) tile_copy_piece<4>(cn);
@@ -435,12 +446,12 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(FwdParams p) {
           }
           __builtin_amdgcn_s_setprio(0);
           if (COPIES && (wave & 3) == 0) tile_copy_piece<4>(cn);
-          if ((k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w)) {
+          if ((k0 + BN > p.s_k) || (CAUSAL && k0 + BN - 1 > q0w)) {
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
               const int kvi = k0 + (j >> 2) * 8 + hh * 4 + (j & 3);
-              if (kvi >= p.s_k || (p.causal && kvi > qrow)) s0[j] = -INFINITY;
-              if (kvi + 32 >= p.s_k || (p.causal && kvi + 32 > qrow)) s1[j] = -INFINITY;
+              if (kvi >= p.s_k || (CAUSAL && kvi > qrow)) s0[j] = -INFINITY;
+              if (kvi + 32 >= p.s_k || (CAUSAL && kvi + 32 > qrow)) s1[j] = -INFINITY;
             }
           }
         };
@@ -470,10 +481,15 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(FwdParams p) {
             s1[j] = __builtin_amdgcn_exp2f(fmaf(s1[j], c2, -mc));
           }
           p0 = pack8(s0, 0); p1 = pack8(s0, 8); p2 = pack8(s1, 0); p3 = pack8(s1, 8);
-          // two independent chains, so that the adds do not wait for one another
+          // independent chains, so that the adds do not wait for one another
+          if constexpr (CAUSAL) {
+            float a[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < 16; ++j) { a[j & 1] += s0[j]; a[2 + (j & 1)] += s1[j]; }
+            return (a[0] + a[1]) + (a[2] + a[3]);
+          }
           const float sa = sum8(p2, sum8(p0, 0.f)), sb = sum8(p3, sum8(p1, 0.f));
-          const float sum = sa + sb;
-          return sum;
+          return sa + sb;
         };
         // Online softmax of the 64-key tile (exp2 domain) against a reference maximum that is only
         // moved when it has to be.  A tile is first exponentiated against the reference as it stands,
@@ -526,27 +542,11 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(FwdParams p) {
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 16; ++j) o[i][j] = 0.f;
-    if (p.accumulate && qvalid && p.lse[head * p.l_sh + qrow] > -INFINITY) {
-      const int64_t obase = head * p.o_sh + static_cast<int64_t>(qrow) * p.o_ss;
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          const int col = db * 32 + g4 * 8 + hh * 4;
-          if (p.o_bf16) {
-            const bf16x4 x = *reinterpret_cast<const bf16x4*>(static_cast<const __bf16*>(p.o) + obase + col);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[db][g4 * 4 + e] = static_cast<float>(x[e]);
-          } else {
-            const float4 x = *reinterpret_cast<const float4*>(static_cast<const float*>(p.o) + obase + col);
-            o[db][g4 * 4] = x.x; o[db][g4 * 4 + 1] = x.y; o[db][g4 * 4 + 2] = x.z; o[db][g4 * 4 + 3] = x.w;
-          }
-        }
-    }
+    if (p.accumulate && qvalid && p.lse[head * p.l_sh + qrow] > -INFINITY) load_o(o, p, head, qrow, hh);
     // O^T = O^T * factor + V^T P^T for tile t (skipped when the tile lies above the block's diagonal)
     auto pv_tile = [&](int t) {
       const int k0 = t * BN;
-      if (p.causal && k0 > q0w + 31) return;
+      if (CAUSAL && k0 > q0w + 31) return;
       const char* Vs = smem + OFF_V + (t % 3) * TILE_BYTES;
       const char* px = smem + OFF_PX + (t & 1) * PX_BYTES + sw * 4096 + lane * 16;
       const float a = reinterpret_cast<const float*>(smem + OFF_AL)[(t & 1) * (AL_BYTES / 4) + sw * 32 + r32];
@@ -587,27 +587,250 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(FwdParams p) {
 
     if (qvalid) {
       const float inv = reinterpret_cast<const float*>(smem + OFF_ST)[sw * 32 + r32];
-      const int64_t obase = head * p.o_sh + static_cast<int64_t>(qrow) * p.o_ss;
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          const int col = db * 32 + g4 * 8 + hh * 4;
-          const float x0 = o[db][g4 * 4 + 0] * inv, x1 = o[db][g4 * 4 + 1] * inv;
-          const float x2 = o[db][g4 * 4 + 2] * inv, x3 = o[db][g4 * 4 + 3] * inv;
-          if (p.o_bf16) {
-            bf16x4 x; x[0] = static_cast<__bf16>(x0); x[1] = static_cast<__bf16>(x1);
-            x[2] = static_cast<__bf16>(x2); x[3] = static_cast<__bf16>(x3);
-            *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o) + obase + col) = x;
-          } else {
-            *reinterpret_cast<float4*>(static_cast<float*>(p.o) + obase + col) = make_float4(x0, x1, x2, x3);
-          }
-        }
+      store_o(o, p, head, qrow, hh, inv);
     }
   }
 }
 
 }  // namespace full_pair
+
+// ============================================================================================
+// Forward for calls with few query rows, full or causal: a workgroup owns 64 rows (2 blocks of 32) and its wavefronts
+// divide the KEYS as well, NS parts of 32 keys per tile (NS = 2: 4 wavefronts, 64-key tiles, two
+// workgroups per CU; NS = 4: 8 wavefronts, 128-key tiles, one workgroup per CU).  Every wavefront runs its
+// own online softmax over its keys; the parts of a row block are combined through LDS at the end.
+// Such a call is bound by the serial walk over the key tiles with most CUs idle: this form has 2-4
+// times the workgroups and each wavefront 1/NS of the walk (8 heads x 2048 x 2048: 52 us with 256-row
+// workgroups, 43 with 128-row ones, 34 here).  Where the device is full it is the slowest form: one
+// 32-key block per wavefront and tile leaves its exponentials uncovered.
+// The matrix pipes have room here, so the weights enter the second product as two bf16 values, the
+// rounded weight and its remainder (o is then off by 2^-17 of a weight instead of 2^-9, for 1 us of 18 at 8 heads x 1024), and the row sums
+// are fp32 sums of the fp32 weights.
+// ============================================================================================
+namespace split {
+
+constexpr int RB = 2, BMS = RB * 32;           // row blocks, query rows per workgroup
+template <int NS> constexpr int kKeys = 32 * NS;                          // keys per tile
+template <int NS> constexpr int kTilesBytes = 2 * (kKeys<NS> / BN) * TILE_BYTES;      // K and V of one tile
+template <int NS> constexpr int kSmem = 2 * kTilesBytes<NS>;
+constexpr int RES_BYTES = 64 * 64 * 4;         // a wavefront's O^T, 64 registers per lane
+
+template <int NS, bool CAUSAL>
+__global__ void __launch_bounds__(RB * NS * 64, NS == 2 ? 2 : 1) k_fwd_bf16(FwdParams p) {
+  constexpr int SUB = kKeys<NS> / BN;          // 64-row sub-tiles of a K (or V) tile
+  extern __shared__ __align__(16) char smem[]; // two buffers of (SUB K sub-tiles, SUB V sub-tiles)
+
+  const int bid = blockIdx.x;
+  const int item = (bid & 7) * p.per_xcd + (bid >> 3);   // contiguous (head, query tile) range per XCD
+  if (item >= p.total) return;
+  const int head = item / p.ntq;
+  int tq = item % p.ntq;
+  if (CAUSAL) tq = p.ntq - 1 - tq;           // longest rows first
+  const int kh = head / p.group;
+  const int q0 = tq * BMS;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rb = wave % RB, part = wave / RB;
+  const int r32 = lane & 31, hh = lane >> 5;
+  const int q0w = q0 + rb * 32;
+  const int qrow = q0w + r32;
+  const bool qvalid = qrow < p.s_q;
+  const int a_base = tile_off(r32, hh);
+  const int g_base = gather_base(lane);
+  const float c2 = p.scale * LOG2E;
+
+  const char* kg = reinterpret_cast<const char*>(p.k + kh * p.kv_sh);
+  const char* vg = reinterpret_cast<const char*>(p.v + kh * p.kv_sh);
+  const uint32_t kv_rowbytes = static_cast<uint32_t>(p.kv_ss) * 2;
+  const int k_end = CAUSAL ? min(p.s_k, q0 + BMS) : p.s_k;
+  const int ntiles = (k_end + kKeys<NS> - 1) / kKeys<NS>;
+  // wavefronts 4s .. 4s + 3 copy sub-tile s of K and of V
+  const int cw = wave & 3, sub = wave >> 2;
+  const TileLane tl = tile_lane(cw, lane, kv_rowbytes);
+  const int last = p.s_k - 1;
+  const int koff = sub * TILE_BYTES, voff = (SUB + sub) * TILE_BYTES;
+  // rows past the end are clamped to the last row (and masked); a sub-tile wholly past it likewise
+  tile_dma(kg, kv_rowbytes, sub * BN, last, tl, smem + koff, cw, lane);
+  tile_dma(vg, kv_rowbytes, sub * BN, last, tl, smem + voff, cw, lane);
+
+  bf16x8 qreg[8];
+  {
+    const __bf16* qp = p.q + head * p.q_sh + static_cast<int64_t>(qvalid ? qrow : 0) * p.q_ss + 8 * hh;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      uint4 raw = *reinterpret_cast<const uint4*>(qp + 16 * ks);
+      if (!qvalid) raw = make_uint4(0, 0, 0, 0);
+      qreg[ks] = __builtin_bit_cast(bf16x8, raw);
+    }
+  }
+  f32x16 o[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) o[i][j] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;        // raw-score units; l_run: this lane's half of the row sum
+  if (p.accumulate && part == 0 && qvalid) {   // the state of the earlier chunks goes into the first part
+    const float L = p.lse[head * p.l_sh + qrow];
+    if (L > -INFINITY) {
+      m_run = L / p.scale;
+      l_run = hh == 0 ? 1.f : 0.f;
+      load_o(o, p, head, qrow, hh);
+    }
+  }
+  lds_dma_wait();
+  __syncthreads();
+
+  for (int it = 0; it < ntiles; ++it) {
+    const int k0 = it * kKeys<NS>;
+    const char* buf = smem + (it & 1) * kTilesBytes<NS>;
+    char* nbuf = smem + ((it & 1) ^ 1) * kTilesBytes<NS>;
+    const int kn = (it + 1 < ntiles ? k0 + kKeys<NS> : k0) + sub * BN;
+    const TileCopy ck = tile_copy_plan(kg, kv_rowbytes, kn, last, tl, nbuf + koff, cw, lane);
+    const TileCopy cv = tile_copy_plan(vg, kv_rowbytes, kn, last, tl, nbuf + voff, cw, lane);
+    const int kb0 = k0 + part * 32;            // this wavefront's 32 keys
+    const char* Ks = buf + (part >> 1) * TILE_BYTES;
+    const char* Vs = Ks + SUB * TILE_BYTES;
+    const int row = (part & 1) * 32 * kRowBytes;
+    if (kb0 < p.s_k && !(CAUSAL && kb0 > q0w + 31)) {
+      bf16x8 ka[4], gv[4];
+      f32x16 s;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) s[j] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) ka[ks] = lds_read_b128(Ks, a_base + row + ks * 32);
+      DFA_SCHED_FENCE();
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {         // S^T = K Q^T
+        s = mfma32(ka[ks & 3], qreg[ks], s);
+        if (ks < 4) ka[ks & 3] = lds_read_b128(Ks, a_base + row + (ks + 4) * 32);
+        if (ks == 0) tile_copy_piece<0>(ck);
+        if (ks == 2) tile_copy_piece<1>(ck);
+        if (ks == 4) tile_copy_piece<2>(ck);
+        if (ks == 6) tile_copy_piece<3>(ck);
+        DFA_SCHED_FENCE();
+      }
+      if (cw == 0) { tile_copy_piece<4>(ck); tile_copy_piece<4>(cv); }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) gv[i] = lds_gather(Vs, g_base + row + i * 64);
+      if (kb0 + 32 > p.s_k || (CAUSAL && kb0 + 31 > q0w)) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          const int kvi = kb0 + (j >> 2) * 8 + hh * 4 + (j & 3);
+          if (kvi >= p.s_k || (CAUSAL && kvi > qrow)) s[j] = -INFINITY;
+        }
+      }
+      // online softmax with the lazy running maximum of the 128-row kernel
+      float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
+#pragma unroll
+      for (int j = 3; j < 15; j += 2) mx = fmaxf(fmaxf(mx, s[j]), s[j + 1]);
+      mx = fmaxf(mx, s[15]);
+      float alpha = 1.f;
+      if (__any((mx - m_run) * c2 > 8.f)) {
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m_run, mx);
+        const float mc_new = (m_new == -INFINITY) ? 0.f : m_new * c2;
+        alpha = __builtin_amdgcn_exp2f(m_run * c2 - mc_new);
+        m_run = m_new;
+        l_run *= alpha;
+      }
+      const float mc = (m_run == -INFINITY) ? 0.f : m_run * c2;
+      float sum = 0.f;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], c2, -mc));
+        sum += s[j];
+      }
+      l_run += sum;
+      if (__any(alpha != 1.f)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) o[i][j] *= alpha;
+      }
+      bf16x8 pb[2], pl[2];                     // the weights, and what rounding them to bf16 left over
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        pb[u] = pack8(s, 8 * u);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[8 * u + e] -= static_cast<float>(pb[u][e]);
+        pl[u] = pack8(s, 8 * u);
+      }
+      DFA_SCHED_FENCE();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {            // O^T += V^T P^T
+        o[i & 3] = mfma32(gv[i & 3], pb[i >> 2], o[i & 3]);
+        o[i & 3] = mfma32(gv[i & 3], pl[i >> 2], o[i & 3]);
+        if (i < 4) gv[i & 3] = lds_gather(Vs, g_base + row + 16 * kRowBytes + i * 64);
+        if (i == 0) tile_copy_piece<0>(cv);
+        if (i == 2) tile_copy_piece<1>(cv);
+        if (i == 4) tile_copy_piece<2>(cv);
+        if (i == 6) tile_copy_piece<3>(cv);
+        DFA_SCHED_FENCE();
+      }
+    } else {                                   // nothing for this wavefront: only its share of the copies
+      tile_copy_piece<0>(ck); tile_copy_piece<1>(ck); tile_copy_piece<2>(ck); tile_copy_piece<3>(ck);
+      tile_copy_piece<0>(cv); tile_copy_piece<1>(cv); tile_copy_piece<2>(cv); tile_copy_piece<3>(cv);
+      if (cw == 0) { tile_copy_piece<4>(ck); tile_copy_piece<4>(cv); }
+    }
+    lds_dma_wait();
+    __syncthreads();
+  }
+
+  // combine the parts of a row block in part 0, against the largest of their reference maxima
+  float l_tot = l_run + __shfl_xor(l_run, 32);
+  float* st = reinterpret_cast<float*>(smem + RB * (NS - 1) * RES_BYTES);      // (m, l) per part and row
+  if (part > 0) {
+    float* x = reinterpret_cast<float*>(smem + (wave - RB) * RES_BYTES) + lane;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[(i * 16 + j) * 64] = o[i][j];
+    if (hh == 0) { st[wave * 64 + r32] = m_run; st[wave * 64 + 32 + r32] = l_tot; }
+  }
+  __syncthreads();
+  if (part > 0) return;
+  float m = m_run;
+#pragma unroll
+  for (int s = 1; s < NS; ++s) m = fmaxf(m, st[(s * RB + rb) * 64 + r32]);
+  const float mc = (m == -INFINITY) ? 0.f : m * c2;
+  const float f0 = __builtin_amdgcn_exp2f(m_run * c2 - mc);
+  l_tot *= f0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) o[i][j] *= f0;
+#pragma unroll 1      // (unrolled, the reads of all parts are hoisted and spill)
+  for (int s = 1; s < NS; ++s) {
+    const int w = s * RB + rb;
+    const float f = __builtin_amdgcn_exp2f(st[w * 64 + r32] * c2 - mc);
+    l_tot = fmaf(st[w * 64 + 32 + r32], f, l_tot);
+    const float* x = reinterpret_cast<const float*>(smem + (w - RB) * RES_BYTES) + lane;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) o[i][j] = fmaf(x[(i * 16 + j) * 64], f, o[i][j]);
+  }
+  if (!qvalid) return;
+  if (hh == 0) p.lse[head * p.l_sh + qrow] = l_tot > 0.f ? m * p.scale + logf(l_tot) : -INFINITY;
+  store_o(o, p, head, qrow, hh, l_tot > 0.f ? 1.f / l_tot : 0.f);
+}
+
+}  // namespace split
+
+// > 64 KB of dynamic LDS needs the opt-in, once per kernel and process (thread-safe)
+template <void (*KERNEL)(FwdParams)>
+int launch(const FwdParams& p, int threads, int smem, hipStream_t st) {
+  static std::once_flag once;
+  static int attr_rc = DFA_OK;
+  std::call_once(once, [smem] {
+    attr_rc = hip_status(hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+  });
+  if (attr_rc) return attr_rc;
+  KERNEL<<<p.per_xcd * 8, threads, smem, st>>>(p);
+  return last_launch_status();
+}
 
 }  // namespace
 
@@ -620,43 +843,59 @@ int launch_fwd_bf16(const dfa_shape& sh, const void* q, const void* k, const voi
   p.o_bf16 = sh.o_dtype == DFA_BF16; p.scale = sh.scale; p.accumulate = accumulate;
   p.q_sh = sh.q_stride_h; p.q_ss = sh.q_stride_s; p.kv_sh = sh.kv_stride_h; p.kv_ss = sh.kv_stride_s;
   p.o_sh = sh.o_stride_h; p.o_ss = sh.o_stride_s; p.l_sh = sh.lse_stride_h;
-  if (!sh.causal) {   // full pairs: the wavefront-specialised kernel; the diagonal pair keeps the finer 128-row tiling
-    p.ntq = (sh.s_q + full_pair::BMW - 1) / full_pair::BMW;
+  auto grid = [&](int rows) {
+    p.ntq = (sh.s_q + rows - 1) / rows;
     p.total = p.ntq * sh.h_q;
     p.per_xcd = (p.total + 7) / 8;
-    // > 64 KB of dynamic LDS needs the opt-in, once per process (thread-safe)
-    static std::once_flag once;
-    static int attr_rc = DFA_OK;
-    std::call_once(once, [] {
-      for (const void* f : {reinterpret_cast<const void*>(full_pair::k_fwd_bf16<false>),
-                            reinterpret_cast<const void*>(full_pair::k_fwd_bf16<true>)}) {
-        const int rc = hip_status(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                      full_pair::SMEM_BYTES));
-        if (rc) attr_rc = rc;
-      }
-    });
-    if (attr_rc) return attr_rc;
-    if (sh.s_k % BN == 0)
-      full_pair::k_fwd_bf16<false><<<p.per_xcd * 8, full_pair::NT, full_pair::SMEM_BYTES, st>>>(p);
-    else
-      full_pair::k_fwd_bf16<true><<<p.per_xcd * 8, full_pair::NT, full_pair::SMEM_BYTES, st>>>(p);
-    return last_launch_status();
+  };
+  // Which form.  us per call on one box, d = 128, 256-row / 128-row / 64-row NS = 2 / 64-row NS = 4 workgroups:
+  //   full pairs    8 heads x 256 rows 13.5 / 9.6 / 8.6 / 9.5    x 1024 30.5 / 24.2 / 22 / 18.4
+  //                 x 2048 52.5 / 42.7 / 40 / 34.2 (256 64-row workgroups)   x 4096 97 / 82 / 100 / 105
+  //                 x 8192 242 / 270 / 344 / 382    32 heads x 1024 32.8 / 27.2 / 29.6 / 34.5
+  //                 x 2777 162 / 147 / 184 / 205 (352 256-row workgroups)      x 4096 250 / 273 / 356 / 381
+  //   causal        8 heads x 1024 29.9 / 24.8 / 21.5 / 19.4   x 4096 95 / 85 / 78 / 69
+  //                 x 16384 492 / 564 / 720 / 800
+  //                 32 heads x 1024 31.5 / 26.4 / 27.1 / 30.9   x 4096 179 / 174 / 195 / 221
+  //                 x 8192 515 / 563 / 715 / 791   x 16384 1950 / 2112 / 2748 / 2985
+  auto count = [&](int rows) { return (static_cast<int64_t>(sh.s_q) + rows - 1) / rows * sh.h_q; };
+  const int64_t n256 = count(256), n128 = count(128), n64 = count(64);
+  bool wide;          // 256 rows
+  int parts = 0;      // 64 rows with this many parts
+  if (sh.causal) {
+    // The diagonal's longest row block sets the time of a call that does not fill the device, so long
+    // chunks are split further; the 256-row form needs chunks long enough that its masked half tiles do
+    // not count.
+    if (n64 <= 256 || (n64 <= 512 && sh.s_q >= 2048)) parts = 4;
+    wide = n256 >= 512 && sh.s_q >= 6144;
+  } else {
+    // One round of 64-row workgroups at most: split the keys.  The 128-row form (10 % slower per row, two
+    // workgroups per CU) where it needs one workgroup per CU at most, or where the last round of 256-row
+    // workgroups would be half empty or worse.
+    if (n64 <= 256) parts = 4;
+    const int64_t last_round = n256 % 256;
+    wide = n128 > 256 && !(n256 > 256 && n256 < 768 && last_round > 0 && last_round <= 128);
   }
-  p.ntq = (sh.s_q + BM - 1) / BM;
-  const int64_t total = static_cast<int64_t>(p.ntq) * sh.h_q;
-  if (total > (1 << 30)) return DFA_ERR_SHAPE;
-  p.total = static_cast<int>(total);
-  p.per_xcd = (p.total + 7) / 8;
-  const size_t smem = 4 * TILE_BYTES;     // two (K, V) buffers; above 64 KB needs the opt-in once
-  static std::once_flag once;
-  static int attr_rc = DFA_OK;
-  std::call_once(once, [smem] {
-    attr_rc = hip_status(hipFuncSetAttribute(reinterpret_cast<const void*>(k_fwd_bf16),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(smem)));
-  });
-  if (attr_rc) return attr_rc;
-  k_fwd_bf16<<<p.per_xcd * 8, NTHREADS, smem, st>>>(p);
-  return last_launch_status();
+  if (parts && sh.s_k <= 256) parts = 2;      // two 128-key tiles at most: the smaller tiles start sooner
+  if (sh.causal && n128 > (1 << 30)) return DFA_ERR_SHAPE;
+  if (parts) {
+    grid(split::BMS);
+    if (parts == 2) return sh.causal ? launch<split::k_fwd_bf16<2, true>>(p, 256, split::kSmem<2>, st)
+                                     : launch<split::k_fwd_bf16<2, false>>(p, 256, split::kSmem<2>, st);
+    return sh.causal ? launch<split::k_fwd_bf16<4, true>>(p, 512, split::kSmem<4>, st)
+                     : launch<split::k_fwd_bf16<4, false>>(p, 512, split::kSmem<4>, st);
+  }
+  if (!wide) {
+    grid(BM);
+    return sh.causal ? launch<k_fwd_bf16<false>>(p, NTHREADS, 4 * TILE_BYTES, st)
+                     : launch<k_fwd_bf16<true>>(p, NTHREADS, 4 * TILE_BYTES, st);
+  }
+  grid(full_pair::BMW);
+  constexpr int nt = full_pair::NT, smem = full_pair::SMEM_BYTES;
+  const bool ragged = sh.s_k % BN != 0;
+  if (sh.causal) return ragged ? launch<full_pair::k_fwd_bf16<true, true>>(p, nt, smem, st)
+                               : launch<full_pair::k_fwd_bf16<false, true>>(p, nt, smem, st);
+  return ragged ? launch<full_pair::k_fwd_bf16<true, false>>(p, nt, smem, st)
+                : launch<full_pair::k_fwd_bf16<false, false>>(p, nt, smem, st);
 }
 
 }  // namespace dfa

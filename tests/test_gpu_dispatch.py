@@ -1,8 +1,13 @@
 """GPU parity at the sizes where the launch rules change kernel forms: the smallest calls that reach
 each form, with remainders on both axes, against the fp64 oracle (bounds as in the parity tests)."""
+import math
+
 import pytest
 import torch
 
+import paper_2310_03294_amd as dfa
+from gpu_util import TOL, case, dev, maxerr, np64
+from oracle import attention as A
 from test_gpu_parity_small import _run_pair
 
 pytestmark = pytest.mark.gpu
@@ -24,3 +29,66 @@ F32_PARTS = [
 def test_f32_parts(shape, d):
     h_q, h_kv, s_q, s_k, causal = shape
     _run_pair(torch.float32, h_q, h_kv, s_q, s_k, d, causal)
+
+
+# bf16 forward: 64-row workgroups with 2 or 4 parts of the keys, 128-row or 256-row workgroups.
+FWD_FORMS = [
+    # h_q, h_kv, s_q, s_k, causal
+    (4, 2, 129, 256, False),      # 64 rows, 2 parts; one row past a block
+    (4, 2, 257, 97, False),       # the same, fewer keys than two tiles
+    (4, 2, 200, 257, False),      # 64 rows, 4 parts: one key past two tiles
+    (2, 2, 65, 31, False),        # fewer keys than one part's block: parts without keys
+    (3, 3, 70, 1153, False),
+    (96, 32, 190, 300, False),    # 128 rows (288 64-row workgroups)
+    (130, 130, 300, 333, False),  # 128 rows: 260 256-row workgroups would leave a last round of 4
+    (200, 100, 300, 129, False),  # 256 rows, last round of 144
+    (4, 2, 200, 200, True),       # 64 rows, 2 parts
+    (4, 2, 450, 450, True),       # 64 rows, 4 parts
+    (70, 35, 260, 260, True),     # 128 rows
+]
+
+
+@pytest.mark.parametrize("shape", FWD_FORMS)
+def test_bf16_forward_forms(shape):
+    """Forward from the empty state and from the state of another chunk, fp32 and bf16 output."""
+    h_q, h_kv, s_q, s_k, causal = shape
+    d, tol = 128, TOL[torch.bfloat16]
+    q, k, v, _ = case(5000 + s_q + s_k, h_q, h_kv, s_q, s_k, d, torch.bfloat16)
+    scale = d ** -0.5
+    Q, K, V = (t.to(dev()) for t in (q, k, v))
+    O, L = A.attention_fwd(np64(q), np64(k), np64(v), scale, causal=causal)
+    for o_dtype in (torch.float32, torch.bfloat16):
+        o, lse = dfa.dfa_chunk_fwd(Q, K, V, causal, scale, o_dtype=o_dtype)
+        assert maxerr(o, O) <= tol and maxerr(lse, L) <= tol
+        if causal:      # its row sums are fp32 sums of the fp32 weights
+            assert maxerr(lse, L) <= 1e-4
+        # continued from itself: the same o, twice the weight
+        dfa.dfa_chunk_fwd_acc(Q, K, V, causal, scale, o, lse)
+        assert maxerr(o, O) <= tol and maxerr(lse, L + math.log(2)) <= tol
+
+
+@pytest.mark.parametrize("h_q,s", [(8, 3300), (22, 6150), (22, 6144)])
+def test_bf16_forward_forms_long_causal(h_q, s):
+    """64-row workgroups with 4 parts on a long diagonal chunk, 256-row workgroups (ragged and whole tiles)."""
+    d, tol = 128, TOL[torch.bfloat16]
+    q, k, v, _ = case(6000 + s, h_q, 1, s, s, d, torch.bfloat16)
+    Q, K, V = (t.to(dev()) for t in (q, k, v))
+    o, lse = dfa.dfa_chunk_fwd(Q, K, V, True, d ** -0.5)
+    rows = sorted({0, 1, 31, 32, 63, 64, 65, 255, 256, 257, s // 2, s - 257, s - 65, s - 2, s - 1})
+    for h in (0, h_q - 1):
+        O, L = A.rows_fwd(np64(q[h, rows]), rows, np64(k[0]), np64(v[0]), d ** -0.5)
+        assert maxerr(o[h, rows], O) <= tol and maxerr(lse[h, rows], L) <= 1e-4
+
+
+@pytest.mark.parametrize("shape", [(4, 4, 64, 640, False), (4, 4, 640, 640, True)])
+def test_bf16_forward_parts_far_apart(shape):
+    """Parts of the keys whose scores differ by hundreds: the other parts' weights underflow."""
+    h_q, h_kv, s_q, s_k, causal = shape
+    d, scale = 128, 1.0
+    q, k, v, _ = case(7000, h_q, h_kv, s_q, s_k, d, torch.bfloat16)
+    k = (k * torch.linspace(0.01, 4.0, s_k)[None, :, None]).to(torch.bfloat16)      # grows along the keys
+    for kk in (k, k.flip(1).contiguous()):
+        o, lse = dfa.dfa_chunk_fwd(q.to(dev()), kk.to(dev()), v.to(dev()), causal, scale)
+        O, L = A.attention_fwd(np64(q), np64(kk), np64(v), scale, causal=causal)
+        # |v| reaches 4.5; a weight is off by 2^-9 of itself
+        assert maxerr(o, O) <= 2e-2 and maxerr(lse, L) <= 2e-2 + 2.0 ** -20 * abs(L).max()
