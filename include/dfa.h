@@ -144,6 +144,24 @@ int dfa_chunk_bwd(const dfa_shape* sh, const void* q, const void* k, const void*
                   const float* lse, const float* delta, const void* dO,
                   float* dq, float* dk, float* dv, int accumulate, void* stream);
 
+/*
+ * dfa_chunk_bwd_batch - dfa_chunk_bwd of n_pairs pairs of one shape and one set of strides as one
+ * piece of work, with dq and dk, dv accumulated into or overwritten independently of each other.
+ * `pairs` is a HOST array, read before the call returns.  The pairs are computed at the same time:
+ * no output may overlap another pair's, and all pairs select the same outputs (DFA_ERR_ARG
+ * otherwise).  n_pairs == 0 is a no-op.  Results of a pair are those of dfa_chunk_bwd up to the order
+ * of summation, which depends on the shape and n_pairs alone.
+ */
+typedef struct {
+  const void *q, *k, *v;
+  const float *lse, *delta;
+  const void* dO;
+  float *dq, *dk, *dv;
+  int32_t accumulate_dq, accumulate_dkv;   /* 0 overwrites, otherwise adds */
+} dfa_bwd_pair;
+
+int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t n_pairs, void* stream);
+
 /* Step kinds of the balanced schedule. */
 typedef enum { DFA_STEP_IDLE = 0, DFA_STEP_DIAG = 1, DFA_STEP_OWN = 2, DFA_STEP_HELP = 3 } dfa_step_kind;
 

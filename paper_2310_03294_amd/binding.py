@@ -44,6 +44,11 @@ class DfaMergeDesc(ctypes.Structure):
                 ("b_stride_h", ctypes.c_int64), ("b_stride_s", ctypes.c_int64), ("lse_b_stride_h", ctypes.c_int64)]
 
 
+class DfaBwdPair(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("q", "k", "v", "lse", "delta", "dO", "dq", "dk", "dv")] + [
+        ("accumulate_dq", ctypes.c_int32), ("accumulate_dkv", ctypes.c_int32)]
+
+
 class DfaStep(ctypes.Structure):
     _fields_ = [("t", ctypes.c_int32), ("kind", ctypes.c_int32), ("q_chunk", ctypes.c_int32),
                 ("kv_chunk", ctypes.c_int32), ("send_to", ctypes.c_int32), ("recv_from", ctypes.c_int32)]
@@ -51,8 +56,8 @@ class DfaStep(ctypes.Structure):
 
 Step = collections.namedtuple("Step", "t kind q_chunk kv_chunk send_to recv_from")
 
-EXPORTS = ("dfa_chunk_fwd", "dfa_chunk_fwd_acc", "dfa_merge", "dfa_delta", "dfa_chunk_bwd", "dfa_schedule",
-           "dfa_schedule_mode", "dfa_schedule_window", "dfa_mfma_probe", "dfa_mfma_probe_data", "dfa_status_str",
+EXPORTS = ("dfa_chunk_fwd", "dfa_chunk_fwd_acc", "dfa_merge", "dfa_delta", "dfa_chunk_bwd",
+           "dfa_chunk_bwd_batch", "dfa_schedule", "dfa_schedule_mode", "dfa_schedule_window", "dfa_mfma_probe", "dfa_mfma_probe_data", "dfa_status_str",
            "dfa_version")
 
 
@@ -77,6 +82,7 @@ def load_library():
     lib.dfa_merge.argtypes = [ctypes.POINTER(DfaMergeDesc), vp, vp, vp, vp, vp]
     lib.dfa_delta.argtypes = [shp, vp, vp, vp, vp]
     lib.dfa_chunk_bwd.argtypes = [shp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_int, vp]
+    lib.dfa_chunk_bwd_batch.argtypes = [shp, ctypes.POINTER(DfaBwdPair), i32, vp]
     lib.dfa_schedule.argtypes = [i32, i32, ctypes.POINTER(DfaStep), i32]
     lib.dfa_schedule_mode.argtypes = [i32, i32, i32, ctypes.POINTER(DfaStep), i32]
     lib.dfa_schedule_window.argtypes = [i32, i32, i32, ctypes.POINTER(DfaStep), i32]
@@ -209,10 +215,8 @@ def dfa_delta(o, dO, delta=None, stream=None):
     return delta
 
 
-def dfa_chunk_bwd(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale, accumulate=False, stream=None):
-    """dq, dk, dv contributions of one chunk pair from the saved logsumexp and D (no forward re-run).
-    dq=None computes only dk, dv; dk=dv=None computes only dq."""
-    lib = load_library()
+def _bwd_shape(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale):
+    """Checks one pair's operands and describes them."""
     if v.shape != k.shape or v.stride() != k.stride():
         raise ValueError("k and v must share shape and strides")
     if dO.shape != q.shape or dO.stride() != q.stride():
@@ -228,14 +232,24 @@ def dfa_chunk_bwd(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale, accumulate
     for t in (dq, dk, dv, lse, delta):
         if t is not None and t.dtype != torch.float32:
             raise TypeError("dq, dk, dv, lse, delta are fp32")
-    sh = _make_shape(q, k, causal, scale, _dt(q), lse=lse, dq=dq, dkv=dk)
+    return _make_shape(q, k, causal, scale, _dt(q), lse=lse, dq=dq, dkv=dk)
 
-    def ptr(t):
-        return None if t is None else t.data_ptr()
 
-    _check(lib.dfa_chunk_bwd(ctypes.byref(sh), q.data_ptr(), k.data_ptr(), v.data_ptr(), lse.data_ptr(),
-                             delta.data_ptr(), dO.data_ptr(), ptr(dq), ptr(dk), ptr(dv),
-                             int(bool(accumulate)), _stream(stream)), "dfa_chunk_bwd")
+def _ptr(t):
+    return None if t is None else t.data_ptr()
+
+
+def dfa_chunk_bwd(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale, accumulate=False, stream=None,
+                  accumulate_dkv=None):
+    """dq, dk, dv contributions of one chunk pair from the saved logsumexp and D (no forward re-run).
+    dq=None computes only dk, dv; dk=dv=None computes only dq.
+    accumulate_dkv: whether dk, dv are added to, where that differs from dq (None: as accumulate)."""
+    lib = load_library()
+    sh = _bwd_shape(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale)
+    pair = DfaBwdPair(q.data_ptr(), k.data_ptr(), v.data_ptr(), lse.data_ptr(), delta.data_ptr(), dO.data_ptr(),
+                      _ptr(dq), _ptr(dk), _ptr(dv), bool(accumulate),
+                      bool(accumulate if accumulate_dkv is None else accumulate_dkv))
+    _check(lib.dfa_chunk_bwd_batch(ctypes.byref(sh), ctypes.byref(pair), 1, _stream(stream)), "dfa_chunk_bwd")
     return dq, dk, dv
 
 

@@ -114,18 +114,23 @@ extern "C" int dfa_delta(const dfa_shape* sh, const void* o, const void* dO, flo
   return dfa::launch_delta(*sh, o, dO, delta, static_cast<hipStream_t>(stream));
 }
 
-extern "C" int dfa_chunk_bwd(const dfa_shape* sh, const void* q, const void* k, const void* v,
-                             const float* lse, const float* delta, const void* dO,
-                             float* dq, float* dk, float* dv, int accumulate, void* stream) {
+extern "C" int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t n_pairs, void* stream) {
   int rc = check_common(sh);
   if (rc != DFA_OK) return rc;
-  if (!q || !k || !v || !lse || !delta || !dO) return DFA_ERR_NULL;
-  // dq alone, (dk, dv) alone, or all three: a NULL output selects which gradients are computed
-  if ((dk == nullptr) != (dv == nullptr)) return DFA_ERR_NULL;
-  if (!dq && !dk) return DFA_ERR_NULL;
-  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(dO) || !aligned16(dq) ||
-      !aligned16(dk) || !aligned16(dv))
-    return DFA_ERR_SHAPE;
+  if (n_pairs < 0) return DFA_ERR_ARG;
+  if (n_pairs == 0) return DFA_OK;
+  if (!pairs) return DFA_ERR_NULL;
+  for (int i = 0; i < n_pairs; ++i) {
+    const dfa_bwd_pair& p = pairs[i];
+    if (!p.q || !p.k || !p.v || !p.lse || !p.delta || !p.dO) return DFA_ERR_NULL;
+    // dq alone, (dk, dv) alone, or all three: a NULL output selects which gradients are computed
+    if ((p.dk == nullptr) != (p.dv == nullptr)) return DFA_ERR_NULL;
+    if (!p.dq && !p.dk) return DFA_ERR_NULL;
+    if ((p.dq == nullptr) != (pairs[0].dq == nullptr) || (p.dk == nullptr) != (pairs[0].dk == nullptr)) return DFA_ERR_ARG;
+    if (!aligned16(p.q) || !aligned16(p.k) || !aligned16(p.v) || !aligned16(p.dO) || !aligned16(p.dq) ||
+        !aligned16(p.dk) || !aligned16(p.dv))
+      return DFA_ERR_SHAPE;
+  }
   if (!stride_ok(sh->q_stride_h, sh->q_stride_s, sh->d, sh->s_q) ||
       !stride_ok(sh->kv_stride_h, sh->kv_stride_s, sh->d, sh->s_k) ||
       !stride_ok(sh->dq_stride_h, sh->dq_stride_s, sh->d, sh->s_q) ||
@@ -135,18 +140,24 @@ extern "C" int dfa_chunk_bwd(const dfa_shape* sh, const void* q, const void* k, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (sh->s_q == 0 || sh->s_k == 0) {
     // nothing flows through an empty pair; honour "overwrite" semantics
-    if (!accumulate) {
-      if (sh->s_q > 0 && dq) { rc = dfa::launch_fill_zero_rows(dq, sh->h_q, sh->s_q, sh->d, sh->dq_stride_h, sh->dq_stride_s, st); if (rc) return rc; }
-      if (sh->s_k > 0 && dk) {
-        rc = dfa::launch_fill_zero_rows(dk, sh->h_kv, sh->s_k, sh->d, sh->dkv_stride_h, sh->dkv_stride_s, st); if (rc) return rc;
-        rc = dfa::launch_fill_zero_rows(dv, sh->h_kv, sh->s_k, sh->d, sh->dkv_stride_h, sh->dkv_stride_s, st); if (rc) return rc;
+    for (int i = 0; i < n_pairs; ++i) {
+      const dfa_bwd_pair& p = pairs[i];
+      if (sh->s_q > 0 && p.dq && !p.accumulate_dq) {
+        rc = dfa::launch_fill_zero_rows(p.dq, sh->h_q, sh->s_q, sh->d, sh->dq_stride_h, sh->dq_stride_s, st); if (rc) return rc;
+      }
+      if (sh->s_k > 0 && p.dk && !p.accumulate_dkv) {
+        rc = dfa::launch_fill_zero_rows(p.dk, sh->h_kv, sh->s_k, sh->d, sh->dkv_stride_h, sh->dkv_stride_s, st); if (rc) return rc;
+        rc = dfa::launch_fill_zero_rows(p.dv, sh->h_kv, sh->s_k, sh->d, sh->dkv_stride_h, sh->dkv_stride_s, st); if (rc) return rc;
       }
     }
     return DFA_OK;
   }
-  if (sh->dtype == DFA_F32)
-    return dfa::launch_bwd_f32(*sh, static_cast<const float*>(q), static_cast<const float*>(k),
-                               static_cast<const float*>(v), lse, delta, static_cast<const float*>(dO),
-                               dq, dk, dv, accumulate, st);
-  return dfa::launch_bwd_bf16(*sh, q, k, v, lse, delta, dO, dq, dk, dv, accumulate, st);
+  return sh->dtype == DFA_F32 ? dfa::launch_bwd_f32(*sh, pairs, n_pairs, st) : dfa::launch_bwd_bf16(*sh, pairs, n_pairs, st);
+}
+
+extern "C" int dfa_chunk_bwd(const dfa_shape* sh, const void* q, const void* k, const void* v,
+                             const float* lse, const float* delta, const void* dO,
+                             float* dq, float* dk, float* dv, int accumulate, void* stream) {
+  const dfa_bwd_pair p{q, k, v, lse, delta, dO, dq, dk, dv, accumulate != 0, accumulate != 0};
+  return dfa_chunk_bwd_batch(sh, &p, 1, stream);
 }

@@ -35,16 +35,25 @@ __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-struct F32Params {
-  const float *q, *k, *v, *dO, *lse_in, *delta;
-  void* o; float* lse;
+// The operands of one (query chunk, key/value chunk) pair of the backward.
+struct Pair {
+  const float *q, *k, *v, *dO, *lse, *delta;
   float *dq, *dk, *dv;
+  int acc_q, acc_kv;           // add to what dq / dk, dv hold
+};
+constexpr int MAX_PAIRS = 16;  // per launch: the pairs travel in the kernel arguments
+
+struct F32Params {
+  const float *q, *k, *v;
+  void* o; float* lse;
   int s_q, s_k, h_q, h_kv, group, causal, o_bf16, accumulate;
-  int nx_kv, n_kv;             // dk/dv: row blocks per key/value head, workgroups (they come first)
-  int nx_q;                    // forward, dq: row blocks per query head
+  int nx_kv, n_kv;             // dk/dv: row blocks per key/value head, workgroups of a pair
+  int nx_q, n_q;               // forward, dq: row blocks per query head; dq: workgroups of a pair
+  int pairs;
   float scale;
   int64_t q_sh, q_ss, kv_sh, kv_ss, o_sh, o_ss, l_sh, dq_sh, dq_ss, dkv_sh, dkv_ss;
 };
+struct F32BwdParams : F32Params { Pair pair[MAX_PAIRS]; };
 
 template <int NB> struct Run;      // NB consecutive floats
 template <> struct Run<4> { typedef f32x4 type; };
@@ -316,7 +325,7 @@ __global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(F32Params p) {
 // there are; V (the same 32 rows for all four wavefronts) then stays in LDS.
 template <int D, int NS> constexpr bool kVLds = D == 128 && NS == 4;
 template <int D, int NS>
-__device__ __forceinline__ void bwd_dkdv(const F32Params& p, int item, float* smem) {
+__device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int item, float* smem) {
   constexpr int NR = 4 / NS, NB = D / 32, LD = D + 4, BQ = 32 * NS;
   constexpr bool V_LDS = kVLds<D, NS>;
   float* Qs = smem;
@@ -333,10 +342,10 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, int item, float* sm
   TilePair<D, BQ> tile;
   float ld = 0.f;                            // lse (first BQ threads) or D (next BQ) of the tile on its way
   auto load = [&](int hq, int q0) {
-    tile.load(p.q + hq * p.q_sh, p.dO + hq * p.q_sh, p.q_ss, q0, p.s_q);
+    tile.load(pr.q + hq * p.q_sh, pr.dO + hq * p.q_sh, p.q_ss, q0, p.s_q);
     if (tid < 2 * BQ) {
       const int r = q0 + tid % BQ;
-      const float* src = (tid < BQ ? p.lse_in : p.delta) + hq * p.l_sh;
+      const float* src = (tid < BQ ? pr.lse : pr.delta) + hq * p.l_sh;
       ld = r < p.s_q ? src[r] : tid < BQ ? -INFINITY : 0.f;
     }
   };
@@ -344,16 +353,16 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, int item, float* sm
   const int h_end = hq + p.group;
   load(hq, q0);
   f32x4 k[D / 8], v[V_LDS ? 1 : D / 8];
-  load_rows<D>(k, p.k + kh * p.kv_sh, p.kv_ss, kvrow, kvalid, hh);
+  load_rows<D>(k, pr.k + kh * p.kv_sh, p.kv_ss, kvrow, kvalid, hh);
   if constexpr (V_LDS) {
     for (int i = tid; i < 32 * (D / 4); i += NT) {
       const int r = k0 + i / (D / 4), c = (i % (D / 4)) * 4;
       f32x4 x = {0.f, 0.f, 0.f, 0.f};
-      if (r < p.s_k) x = *reinterpret_cast<const f32x4*>(p.v + kh * p.kv_sh + static_cast<int64_t>(r) * p.kv_ss + c);
+      if (r < p.s_k) x = *reinterpret_cast<const f32x4*>(pr.v + kh * p.kv_sh + static_cast<int64_t>(r) * p.kv_ss + c);
       *reinterpret_cast<f32x4*>(Vs + (r - k0) * LD + c) = x;
     }
   } else {
-    load_rows<D>(v, p.v + kh * p.kv_sh, p.kv_ss, kvrow, kvalid, hh);
+    load_rows<D>(v, pr.v + kh * p.kv_sh, p.kv_ss, kvrow, kvalid, hh);
   }
   f32x16 dk[NB], dv[NB];
   zero(dk);
@@ -406,13 +415,13 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, int item, float* sm
   }
   if (!kvalid) return;
   const int64_t off = kh * p.dkv_sh + static_cast<int64_t>(kvrow) * p.dkv_ss;
-  write_grad<D>(p.dk + off, dk, p.scale, p.accumulate, hh);
-  write_grad<D>(p.dv + off, dv, 1.f, p.accumulate, hh);
+  write_grad<D>(pr.dk + off, dk, p.scale, pr.acc_kv, hh);
+  write_grad<D>(pr.dv + off, dv, 1.f, pr.acc_kv, hh);
 }
 
 // dq of one workgroup's query rows: Q and dO rows in registers, K / V tiles in LDS.
 template <int D, int NS>
-__device__ __forceinline__ void bwd_dq(const F32Params& p, int item, float* smem) {
+__device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int item, float* smem) {
   constexpr int NR = 4 / NS, NB = D / 32, LD = D + 4, BK = 32 * NS;
   float* Ks = smem;
   float* Vs = Ks + BK * LD;
@@ -423,17 +432,17 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, int item, float* smem
   if (p.causal) xq = p.nx_q - 1 - xq;
   const int q0 = xq * NR * 32, q0w = q0 + rb * 32, qrow = q0w + r32;
   const bool qvalid = qrow < p.s_q;
-  const float* kg = p.k + kh * p.kv_sh;
-  const float* vg = p.v + kh * p.kv_sh;
+  const float* kg = pr.k + kh * p.kv_sh;
+  const float* vg = pr.v + kh * p.kv_sh;
   const int k_end = p.causal ? min(p.s_k, q0 + NR * 32) : p.s_k;
 
   TilePair<D, BK> tile;
   tile.load(kg, vg, p.kv_ss, 0, p.s_k);
   f32x4 q[D / 8], g[D / 8];
-  load_rows<D>(q, p.q + h * p.q_sh, p.q_ss, qrow, qvalid, hh);
-  load_rows<D>(g, p.dO + h * p.q_sh, p.q_ss, qrow, qvalid, hh);
-  const float L = qvalid ? p.lse_in[h * p.l_sh + qrow] : -INFINITY;
-  const float Dr = qvalid ? p.delta[h * p.l_sh + qrow] : 0.f;
+  load_rows<D>(q, pr.q + h * p.q_sh, p.q_ss, qrow, qvalid, hh);
+  load_rows<D>(g, pr.dO + h * p.q_sh, p.q_ss, qrow, qvalid, hh);
+  const float L = qvalid ? pr.lse[h * p.l_sh + qrow] : -INFINITY;
+  const float Dr = qvalid ? pr.delta[h * p.l_sh + qrow] : 0.f;
   f32x16 dq[NB];
   zero(dq);
   for (int k0 = 0; k0 < k_end; k0 += BK) {
@@ -468,7 +477,7 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, int item, float* smem
     for (int s = 1; s < NS; ++s) add_result<NB>(smem + (s * NR + rb) * NV * 64, dq, lane, 1.f);
   }
   if (!qvalid) return;
-  write_grad<D>(p.dq + h * p.dq_sh + static_cast<int64_t>(qrow) * p.dq_ss, dq, p.scale, p.accumulate, hh);
+  write_grad<D>(pr.dq + h * p.dq_sh + static_cast<int64_t>(qrow) * p.dq_ss, dq, p.scale, pr.acc_q, hh);
 }
 
 // Backward: 7 products in two kinds of workgroups of ONE launch (dk/dv first, they are the longer
@@ -476,11 +485,15 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, int item, float* smem
 // form (5 products, dq added with fp32 atomics) left a short chunk with as few workgroups as it has key
 // tiles.
 template <int D, int NS>
-__global__ void __launch_bounds__(NT, 1) k_bwd_f32(F32Params p) {
+__global__ void __launch_bounds__(NT, 1) k_bwd_f32(F32BwdParams p) {
   extern __shared__ __align__(16) float smem[];
-  const int item = blockIdx.x;
-  if (item < p.n_kv) bwd_dkdv<D, NS>(p, item, smem);
-  else bwd_dq<D, NS>(p, item - p.n_kv, smem);
+  int item = blockIdx.x;
+  if (item < p.n_kv * p.pairs) {
+    bwd_dkdv<D, NS>(p, p.pair[item / p.n_kv], item % p.n_kv, smem);
+  } else {
+    item -= p.n_kv * p.pairs;
+    bwd_dq<D, NS>(p, p.pair[item / p.n_q], item % p.n_q, smem);
+  }
 }
 
 F32Params make_params(const dfa_shape& sh) {
@@ -494,8 +507,8 @@ F32Params make_params(const dfa_shape& sh) {
 }
 
 // More than 64 KB of dynamic LDS needs the opt-in, once per kernel and process (thread-safe).
-template <void (*KERNEL)(F32Params)>
-int launch(const F32Params& p, int64_t blocks, size_t smem, hipStream_t st) {
+template <class P, void (*KERNEL)(P)>
+int launch(const P& p, int64_t blocks, size_t smem, hipStream_t st) {
   static std::once_flag once;
   static int attr_rc = DFA_OK;
   std::call_once(once, [smem] {
@@ -517,20 +530,22 @@ int fwd(F32Params p, hipStream_t st) {
   const size_t comb = NS > 1 ? sizeof(float) * (4 * (D / 32) * 16 * 64 + 256) : 0;
   const size_t tiles = smem_bytes<D, kTile<NS>>();
   p.nx_q = static_cast<int>(blocks_of(p.s_q, rows));
-  return launch<k_fwd_f32<D, NS>>(p, static_cast<int64_t>(p.nx_q) * p.h_q, tiles > comb ? tiles : comb, st);
+  return launch<F32Params, k_fwd_f32<D, NS>>(p, static_cast<int64_t>(p.nx_q) * p.h_q, tiles > comb ? tiles : comb, st);
 }
 
 template <int D, int NS>
-int bwd(F32Params p, hipStream_t st) {
+int bwd(F32BwdParams p, hipStream_t st) {
   const int rows = 32 * (4 / NS);
   const size_t comb = NS > 1 ? sizeof(float) * (4 - 4 / NS) * 2 * (D / 32) * 16 * 64 : 0;
   const size_t tiles = smem_bytes<D, 32 * NS>() + (kVLds<D, NS> ? sizeof(float) * 32 * (D + 4) : 0);
   p.nx_kv = static_cast<int>(blocks_of(p.s_k, rows));
   p.nx_q = static_cast<int>(blocks_of(p.s_q, rows));
-  const int64_t n_kv = p.dk ? static_cast<int64_t>(p.nx_kv) * p.h_kv : 0, n_q = p.dq ? static_cast<int64_t>(p.nx_q) * p.h_q : 0;
-  if (n_kv > (1 << 30)) return DFA_ERR_SHAPE;
+  const int64_t n_kv = p.pair[0].dk ? static_cast<int64_t>(p.nx_kv) * p.h_kv : 0;
+  const int64_t n_q = p.pair[0].dq ? static_cast<int64_t>(p.nx_q) * p.h_q : 0;
+  if (n_kv * p.pairs > (1 << 30)) return DFA_ERR_SHAPE;
   p.n_kv = static_cast<int>(n_kv);
-  return launch<k_bwd_f32<D, NS>>(p, n_kv + n_q, tiles > comb ? tiles : comb, st);
+  p.n_q = static_cast<int>(n_q);
+  return launch<F32BwdParams, k_bwd_f32<D, NS>>(p, (n_kv + n_q) * p.pairs, tiles > comb ? tiles : comb, st);
 }
 
 }  // namespace
@@ -551,19 +566,28 @@ int launch_fwd_f32(const dfa_shape& sh, const float* q, const float* k, const fl
   return parts == 4 ? fwd<64, 4>(p, st) : parts == 2 ? fwd<64, 2>(p, st) : fwd<64, 1>(p, st);
 }
 
-int launch_bwd_f32(const dfa_shape& sh, const float* q, const float* k, const float* v,
-                   const float* lse, const float* delta, const float* dO,
-                   float* dq, float* dk, float* dv, int accumulate, hipStream_t st) {
-  F32Params p = make_params(sh);
-  p.q = q; p.k = k; p.v = v; p.lse_in = lse; p.delta = delta; p.dO = dO;
-  p.dq = dq; p.dk = dk; p.dv = dv; p.accumulate = accumulate;
+int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, hipStream_t st) {
+  for (; n > MAX_PAIRS; pairs += MAX_PAIRS, n -= MAX_PAIRS) {
+    const int rc = launch_bwd_f32(sh, pairs, MAX_PAIRS, st);
+    if (rc) return rc;
+  }
+  F32BwdParams p{};
+  static_cast<F32Params&>(p) = make_params(sh);
+  p.pairs = n;
+  for (int i = 0; i < n; ++i) {
+    const dfa_bwd_pair& x = pairs[i];
+    p.pair[i] = Pair{static_cast<const float*>(x.q), static_cast<const float*>(x.k), static_cast<const float*>(x.v),
+                     static_cast<const float*>(x.dO), x.lse, x.delta, x.dq, x.dk, x.dv, x.accumulate_dq,
+                     x.accumulate_dkv};
+  }
   // Parts per tile, as in the forward; us per full pair (dk, dv and dq), d = 128, with 1 / 2 / 4 parts:
   //   8 / 2 heads x 1024 rows 1183 / 647 / 371 (320 workgroups of 4 parts),  32 x 256 87 / 57 / 72 (256
   //   workgroups of 2),  32 x 1024 547 / 604 / 725,  32 x 4096 8370 / 9210 / 11380 (82 TFLOP/s with 1);
   //   causal, 32 x 4096 8240 / 7050 / 6960, 32 x 1024 545 / 593 / 725.
   // The vector-FMA kernel this one replaced (dq by atomics) took 2.9 ms at 8 / 2 x 1024.
   auto workgroups = [&](int rows) {
-    return (dk ? blocks_of(sh.s_k, rows) * sh.h_kv : 0) + (dq ? blocks_of(sh.s_q, rows) * sh.h_q : 0);
+    return ((pairs[0].dk ? blocks_of(sh.s_k, rows) * sh.h_kv : 0) +
+            (pairs[0].dq ? blocks_of(sh.s_q, rows) * sh.h_q : 0)) * n;
   };
   const int parts = workgroups(32) <= 384 ? 4 : workgroups(64) <= 512 || (sh.causal && workgroups(128) >= 1024) ? 2 : 1;
   if (sh.d == 128) return parts == 4 ? bwd<128, 4>(p, st) : parts == 2 ? bwd<128, 2>(p, st) : bwd<128, 1>(p, st);

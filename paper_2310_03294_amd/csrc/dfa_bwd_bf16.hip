@@ -1,7 +1,8 @@
 // bf16 backward chunk kernels for gfx950: dq, dk, dv contributions of one chunk pair from the
 // saved logsumexp and D = rowsum(dO o O), without re-running the forward (Section 3.3).
 //
-// Two kernels, no atomics, deterministic:
+// Two kinds of workgroups, no atomics, deterministic; a call that wants all gradients launches both kinds
+// at once (k_bwd_bf16), a call that wants one side launches that kind alone:
 //
 //  k_bwd_dkdv_bf16 (key-stationary).  A workgroup of 8 wavefronts owns 128 key rows of one kv
 //  head and walks over the query heads of the group and their query tiles of 64 rows, staged
@@ -18,10 +19,10 @@
 //  fills the gaps instead of delaying them.
 //  dv / dk are written once per workgroup (summed over the group's query heads in registers).
 //
-//  k_bwd_dq_bf16 (query-stationary).  A workgroup of 4 wavefronts owns 128 query rows of one head
-//  (Q^T, dO^T, lse, D in registers) and walks over the key/value chunk in tiles of 64 rows in
-//  LDS: S^T = K Q^T, dP^T = V dO^T (keys x queries: each lane holds 16 keys of ONE query, so lse
-//  and D are per-lane scalars), dS^T from registers as the B operand of dQ^T += K^T dS^T.
+//  k_bwd_dq_bf16 (query-stationary).  A workgroup owns 128 or 256 query rows of one head (Q^T, dO^T,
+//  lse, D in registers) and walks over the key/value chunk in tiles of 64 rows in LDS: S^T = K Q^T,
+//  dP^T = V dO^T (keys x queries: each lane holds 16 keys of ONE query, so lse and D are per-lane
+//  scalars), dS^T from registers as the B operand of dQ^T += K^T dS^T.
 //
 // The fused alternative (one kernel, dq by fp32 atomics) was measured first: the L2 atomic units
 // retire about one fp32 atomic per clock and channel (~3.1e11 per second on the whole chip),
@@ -35,17 +36,32 @@
 namespace dfa {
 namespace {
 
-constexpr int NTHREADS = 256;
 constexpr float LOG2E = 1.4426950408889634f;
 
-struct BwdParams {
+// Workgroups of one kind: tiles per head, (head, tile) items of one pair, of all pairs, and per XCD.
+struct Items { int ntile, per_pair, total, per_xcd; };
+
+// The operands of one (query chunk, key/value chunk) pair.
+struct Pair {
   const __bf16 *q, *k, *v, *dO;
   const float *lse, *delta;
   float *dq, *dk, *dv;
-  int s_q, s_k, h_q, h_kv, group, causal, accumulate, ntile, total, per_xcd;
+  int acc_q, acc_kv;         // add to what dq / dk, dv hold
+};
+constexpr int64_t MAX_BLOCKS = 1 << 22;      // of 512 threads: half of what a grid takes
+constexpr int MAX_PAIRS = 16;       // per launch: the pairs travel in the kernel arguments
+
+struct BwdParams {
+  Pair pair[MAX_PAIRS];
+  int s_q, s_k, h_q, h_kv, group, causal, q_first;
+  Items kv_items, q_items;
   float scale;
   int64_t q_sh, q_ss, kv_sh, kv_ss, l_sh, dq_sh, dq_ss, dkv_sh, dkv_ss;
 };
+
+// XCD-aware mapping: workgroup ids go round-robin over the 8 XCDs; every XCD gets a contiguous range of
+// (head, tile) items, so that the tiles of one head share Q/dO (or K/V) in one L2.
+__device__ __forceinline__ int item_of(const Items& it, int bid) { return (bid & 7) * it.per_xcd + (bid >> 3); }
 
 // ============================================================================================
 // dK, dV
@@ -194,16 +210,11 @@ __device__ __forceinline__ void col_products(f32x16 (&acc)[4], const char* Ys, i
 
 // RAGGED: s_q is no multiple of the 64-row tile, so a head's last tile has rows past the end.
 template <bool RAGGED>
-__global__ void __launch_bounds__(NT, 2) k_bwd_dkdv_bf16(BwdParams p) {
-  extern __shared__ __align__(16) char smem[];
-
-  // XCD-aware mapping: workgroup ids go round-robin over the 8 XCDs; give every XCD a contiguous
-  // range of (kv head, key tile) items so that the tiles of one head share Q/dO in one L2.
-  const int bid = blockIdx.x;
-  const int item = (bid & 7) * p.per_xcd + (bid >> 3);
-  if (item >= p.total) return;
-  const int kh = item / p.ntile;
-  const int tk = item % p.ntile;     // causal: low key tiles meet the most query tiles and come first
+__device__ __forceinline__ void dkdv(const BwdParams& p, int item, char* smem) {
+  const Pair& pr = p.pair[item / p.kv_items.per_pair];
+  item %= p.kv_items.per_pair;
+  const int kh = item / p.kv_items.ntile;
+  const int tk = item % p.kv_items.ntile;  // causal: low key tiles meet the most query tiles and come first
   const int k0 = tk * BN;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -220,7 +231,7 @@ __global__ void __launch_bounds__(NT, 2) k_bwd_dkdv_bf16(BwdParams p) {
   // B operands over d of this wavefront's 32 keys: K^T for an S wavefront, V^T for a dP wavefront
   bf16x8 bT[8];
   {
-    const __bf16* src = dp_wave ? p.v : p.k;
+    const __bf16* src = dp_wave ? pr.v : pr.k;
     const int64_t off = kh * p.kv_sh + static_cast<int64_t>(kvalid ? kvrow : 0) * p.kv_ss + 8 * hh;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
@@ -251,9 +262,9 @@ __global__ void __launch_bounds__(NT, 2) k_bwd_dkdv_bf16(BwdParams p) {
   QTileCursor cur, curl;
   {
     const int hq0 = kh * p.group;
-    cur.qh = reinterpret_cast<const char*>(p.q + hq0 * p.q_sh);
-    cur.gh = reinterpret_cast<const char*>(p.dO + hq0 * p.q_sh);
-    cur.ldh = (kb == 1 ? p.delta : p.lse) + hq0 * p.l_sh;
+    cur.qh = reinterpret_cast<const char*>(pr.q + hq0 * p.q_sh);
+    cur.gh = reinterpret_cast<const char*>(pr.dO + hq0 * p.q_sh);
+    cur.ldh = (kb == 1 ? pr.delta : pr.lse) + hq0 * p.l_sh;
     cur.q0 = q_begin;
     curl = cur;
   }
@@ -429,7 +440,7 @@ __global__ void __launch_bounds__(NT, 2) k_bwd_dkdv_bf16(BwdParams p) {
 
 
   if (kvalid) {
-    float* dst = (dp_wave ? p.dk : p.dv) + kh * p.dkv_sh + static_cast<int64_t>(kvrow) * p.dkv_ss;
+    float* dst = (dp_wave ? pr.dk : pr.dv) + kh * p.dkv_sh + static_cast<int64_t>(kvrow) * p.dkv_ss;
     const float f = dp_wave ? p.scale : 1.f;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
@@ -438,7 +449,7 @@ __global__ void __launch_bounds__(NT, 2) k_bwd_dkdv_bf16(BwdParams p) {
         const int col = db * 32 + g4 * 8 + hh * 4;
         float4 a = make_float4(acc[db][g4 * 4] * f, acc[db][g4 * 4 + 1] * f, acc[db][g4 * 4 + 2] * f,
                                acc[db][g4 * 4 + 3] * f);
-        if (p.accumulate) {
+        if (pr.acc_kv) {
           const float4 a0 = *reinterpret_cast<const float4*>(dst + col);
           a.x += a0.x; a.y += a0.y; a.z += a0.z; a.w += a0.w;
         }
@@ -457,36 +468,36 @@ namespace qs {
 constexpr int BN = 64;      // key rows per LDS tile
 constexpr int TILE_BYTES = BN * kRowBytes;
 
-// NW wavefronts of 32 query rows each per workgroup, two wavefronts per SIMD either way: NW = 4 (128
-// rows, two workgroups per CU, scheduled independently of each other) or NW = 8 (256 rows, one
-// workgroup per CU: every K/V tile copy and every barrier serve twice the rows; measured 2-3 %
-// faster on long chunks, where the copies are what the second independent workgroup used to hide, and
-// no faster on short ones and on the causal diagonal pair, which keep the 128-row form).
-template <int NW>
-__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdParams p) {
-  constexpr int BM = NW * 32;     // query rows per workgroup
-  extern __shared__ __align__(16) char smem[];   // two (K tile, V tile) buffers
-
-  const int bid = blockIdx.x;
-  const int item = (bid & 7) * p.per_xcd + (bid >> 3);   // contiguous (head, query tile) range per XCD
-  if (item >= p.total) return;
-  const int head = item / p.ntile;
-  int tq = item % p.ntile;
-  if (p.causal) tq = p.ntile - 1 - tq;      // longest rows first
+// NW wavefronts, NW / NS row blocks of 32 query rows each times NS parts of every key tile; two wavefronts
+// per SIMD either way: NW = 4 (128 rows, two workgroups per CU, scheduled independently of each other) or
+// NW = 8, NS = 1 (256 rows, one workgroup per CU: every K/V tile copy and every barrier serve twice the
+// rows; measured 2-3 % faster on long chunks, where the copies are what the second independent workgroup
+// used to hide, and no faster on short ones and on the causal diagonal pair, which keep the 128-row form).
+// NW = 8, NS = 2 (128 rows, one workgroup per CU, half the serial walk each) is for calls that do not fill
+// the device; the sums of the two parts are added through LDS at the end.
+template <int NW, int NS>
+__device__ __forceinline__ void dq(const BwdParams& p, int item, char* smem) {   // smem: two (K tile, V tile) buffers
+  constexpr int BM = NW / NS * 32;     // query rows per workgroup
+  const Pair& pr = p.pair[item / p.q_items.per_pair];
+  item %= p.q_items.per_pair;
+  const int head = item / p.q_items.ntile;
+  int tq = item % p.q_items.ntile;
+  if (p.causal) tq = p.q_items.ntile - 1 - tq;      // longest rows first
   const int kh = head / p.group;
   const int q0 = tq * BM;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps tile branches scalar
   const int r32 = lane & 31, hh = lane >> 5;
-  const int q0w = q0 + wave * 32;
+  const int rb = wave % (NW / NS), part = wave / (NW / NS);    // row block, part of every key tile
+  const int q0w = q0 + rb * 32;
   const int qrow = q0w + r32;
   const bool qvalid = qrow < p.s_q;
   const int a_base = tile_off(r32, hh);
   const int g_base = gather_base(lane);
 
-  const char* kg = reinterpret_cast<const char*>(p.k + kh * p.kv_sh);
-  const char* vg = reinterpret_cast<const char*>(p.v + kh * p.kv_sh);
+  const char* kg = reinterpret_cast<const char*>(pr.k + kh * p.kv_sh);
+  const char* vg = reinterpret_cast<const char*>(pr.v + kh * p.kv_sh);
   const uint32_t kv_rowbytes = static_cast<uint32_t>(p.kv_ss) * 2;
   // Tile copies: with 4 wavefronts each moves its quarter of the K tile and of the V tile; with 8,
   // wavefronts 0-3 move the K tile and 4-7 the V tile.
@@ -499,8 +510,8 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPar
     const int64_t off = head * p.q_sh + static_cast<int64_t>(qvalid ? qrow : 0) * p.q_ss + 8 * hh;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      uint4 a = *reinterpret_cast<const uint4*>(p.q + off + 16 * ks);
-      uint4 b = *reinterpret_cast<const uint4*>(p.dO + off + 16 * ks);
+      uint4 a = *reinterpret_cast<const uint4*>(pr.q + off + 16 * ks);
+      uint4 b = *reinterpret_cast<const uint4*>(pr.dO + off + 16 * ks);
       if (!qvalid) { a = make_uint4(0, 0, 0, 0); b = make_uint4(0, 0, 0, 0); }
       qB[ks] = __builtin_bit_cast(bf16x8, a);
       gB[ks] = __builtin_bit_cast(bf16x8, b);
@@ -508,9 +519,9 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPar
   }
   float Lr = INFINITY, Dr = 0.f;          // +inf makes P exactly 0 for rows past the end
   if (qvalid) {
-    const float L = p.lse[head * p.l_sh + qrow];
+    const float L = pr.lse[head * p.l_sh + qrow];
     Lr = L > -INFINITY ? L * LOG2E : INFINITY;
-    Dr = p.delta[head * p.l_sh + qrow];
+    Dr = pr.delta[head * p.l_sh + qrow];
   }
 
   // -D of the lane's query row in every element: the accumulator the dP^T products start from,
@@ -552,7 +563,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPar
                                        v_wave ? Kn + TILE_BYTES : Kn, cw, lane);
     const TileCopy cv = tile_copy_plan(vg, kv_rowbytes, kn0, p.s_k - 1, tl, Kn + TILE_BYTES, cw, lane);
 
-    const bool active = !(p.causal && k0 > q0w + 31);
+    const bool active = !(p.causal && k0 + (NS == 2 ? part * 32 : 0) > q0w + 31);
     if (!active) {      // nothing to compute for this wavefront's rows: only its share of the copies
       tile_copy_piece<0>(ck); tile_copy_piece<1>(ck); tile_copy_piece<2>(ck); tile_copy_piece<3>(ck);
       if (cw == 0) tile_copy_piece<4>(ck);
@@ -564,7 +575,8 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPar
     if (active) {
       const bool need_mask = (k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w);
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
+      for (int n = 0; n < 2 / NS; ++n) {
+        const int nb = NS == 2 ? part : n;       // 32-key block of the tile
         // S^T = K Q^T, dP^T = V dO^T for 32 keys; row reads run 4 steps ahead
         bf16x8 ka[4], va[4];
         f32x16 s, dp;
@@ -581,8 +593,8 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPar
         for (int ks = 0; ks < 8; ++ks) {
           s = mfma32(ka[ks & 3], qB[ks], s);
           dp = mfma32(va[ks & 3], gB[ks], ks == 0 ? negD : dp);      // the chain starts from -D
-          if (NW == 4 || nb == 0) {   // one piece of the next tiles every other step
-            const TileCopy& c = nb == 0 ? ck : cv;
+          if (NW == 4 || n == 0) {   // one piece of the next tiles every other step
+            const TileCopy& c = n == 0 ? ck : cv;
             if (ks == 0) tile_copy_piece<0>(c);
             if (ks == 2) tile_copy_piece<1>(c);
             if (ks == 4) tile_copy_piece<2>(c);
@@ -608,7 +620,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPar
             if (kvi >= p.s_k || (p.causal && kvi > qrow)) dp[j] = 0.f;
           }
         }
-        if (cw == 0 && (NW == 4 || nb == 0)) tile_copy_piece<4>(nb == 0 ? ck : cv);
+        if (cw == 0 && (NW == 4 || n == 0)) tile_copy_piece<4>(n == 0 ? ck : cv);
         // dQ^T += K^T dS^T: 2 contraction steps of 16 keys, 4 blocks of 32 columns
         bf16x8 sb[2], gk[2];
         sb[0] = pack8(dp, 0); sb[1] = pack8(dp, 8);
@@ -629,8 +641,23 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPar
     __syncthreads();
   }
 
+  if constexpr (NS == 2) {      // the second part's sums through LDS (the tiles are no longer needed)
+    float* x = reinterpret_cast<float*>(smem) + rb * 4096 + lane;
+    if (part == 1) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[(i * 16 + j) * 64] = dqT[i][j];
+    }
+    __syncthreads();
+    if (part == 1) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) dqT[i][j] += x[(i * 16 + j) * 64];
+  }
   if (qvalid) {
-    float* dst = p.dq + head * p.dq_sh + static_cast<int64_t>(qrow) * p.dq_ss;
+    float* dst = pr.dq + head * p.dq_sh + static_cast<int64_t>(qrow) * p.dq_ss;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -638,7 +665,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPar
         const int col = db * 32 + g4 * 8 + hh * 4;
         float4 a = make_float4(dqT[db][g4 * 4] * p.scale, dqT[db][g4 * 4 + 1] * p.scale,
                                dqT[db][g4 * 4 + 2] * p.scale, dqT[db][g4 * 4 + 3] * p.scale);
-        if (p.accumulate) {
+        if (pr.acc_q) {
           const float4 a0 = *reinterpret_cast<const float4*>(dst + col);
           a.x += a0.x; a.y += a0.y; a.z += a0.z; a.w += a0.w;
         }
@@ -648,71 +675,126 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPar
 }
 
 }  // namespace qs
+
+// The kernels: dk, dv alone, dq alone, and both kinds of workgroups in one launch.
+template <bool RAGGED>
+__global__ void __launch_bounds__(kv::NT, 2) k_bwd_dkdv_bf16(BwdParams p) {
+  extern __shared__ __align__(16) char smem[];
+  const int item = item_of(p.kv_items, blockIdx.x);
+  if (item < p.kv_items.total) kv::dkdv<RAGGED>(p, item, smem);
+}
+
+template <int NW>
+__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdParams p) {
+  extern __shared__ __align__(16) char smem[];
+  const int item = item_of(p.q_items, blockIdx.x);
+  if (item < p.q_items.total) qs::dq<NW, 1>(p, item, smem);
+}
+
+template <bool RAGGED, int NS>
+__global__ void __launch_bounds__(kv::NT, 2) k_bwd_bf16(BwdParams p) {
+  extern __shared__ __align__(16) char smem[];
+  const int n_kv = p.kv_items.per_xcd * 8, n_q = p.q_items.per_xcd * 8;
+  const int bid = blockIdx.x;
+  if (p.q_first ? bid >= n_q : bid < n_kv) {
+    const int item = item_of(p.kv_items, p.q_first ? bid - n_q : bid);
+    if (item < p.kv_items.total) kv::dkdv<RAGGED>(p, item, smem);
+  } else {
+    const int item = item_of(p.q_items, p.q_first ? bid : bid - n_kv);
+    if (item < p.q_items.total) qs::dq<8, NS>(p, item, smem);
+  }
+}
+
+// > 64 KB of dynamic LDS needs the opt-in, once per kernel and process (thread-safe)
+template <void (*KERNEL)(BwdParams)>
+int launch(const BwdParams& p, int64_t blocks, int threads, int smem, hipStream_t st) {
+  static std::once_flag once;
+  static int attr_rc = DFA_OK;
+  std::call_once(once, [smem] {
+    attr_rc = hip_status(hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+  });
+  if (attr_rc) return attr_rc;
+  KERNEL<<<static_cast<int>(blocks), threads, smem, st>>>(p);
+  return last_launch_status();
+}
+
+// Items of `rows` rows each of `heads` heads and `pairs` pairs; false: more than a launch takes.
+bool make_items(Items& it, int s, int rows, int heads, int pairs) {
+  const int64_t n = (static_cast<int64_t>(s) + rows - 1) / rows, total = n * heads * pairs;
+  if (total > (1 << 29)) return false;
+  it.ntile = static_cast<int>(n);
+  it.per_pair = static_cast<int>(n * heads);
+  it.total = static_cast<int>(total);
+  it.per_xcd = (it.total + 7) / 8;
+  return true;
+}
+
 }  // namespace
 
-int launch_bwd_bf16(const dfa_shape& sh, const void* q, const void* k, const void* v,
-                    const float* lse, const float* delta, const void* dO,
-                    float* dq, float* dk, float* dv, int accumulate, hipStream_t st) {
+int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, hipStream_t st) {
+  for (; n > MAX_PAIRS; pairs += MAX_PAIRS, n -= MAX_PAIRS) {
+    const int rc = launch_bwd_bf16(sh, pairs, MAX_PAIRS, st);
+    if (rc) return rc;
+  }
   BwdParams p{};
-  p.q = static_cast<const __bf16*>(q); p.k = static_cast<const __bf16*>(k); p.v = static_cast<const __bf16*>(v);
-  p.dO = static_cast<const __bf16*>(dO); p.lse = lse; p.delta = delta; p.dq = dq; p.dk = dk; p.dv = dv;
+  for (int i = 0; i < n; ++i) {
+    const dfa_bwd_pair& x = pairs[i];
+    p.pair[i] = Pair{static_cast<const __bf16*>(x.q), static_cast<const __bf16*>(x.k), static_cast<const __bf16*>(x.v),
+                     static_cast<const __bf16*>(x.dO), x.lse, x.delta, x.dq, x.dk, x.dv, x.accumulate_dq,
+                     x.accumulate_dkv};
+  }
   p.s_q = sh.s_q; p.s_k = sh.s_k; p.h_q = sh.h_q; p.h_kv = sh.h_kv; p.group = sh.h_q / sh.h_kv;
-  p.causal = sh.causal; p.accumulate = accumulate; p.scale = sh.scale;
+  p.causal = sh.causal; p.scale = sh.scale;
   p.q_sh = sh.q_stride_h; p.q_ss = sh.q_stride_s; p.kv_sh = sh.kv_stride_h; p.kv_ss = sh.kv_stride_s;
   p.l_sh = sh.lse_stride_h; p.dq_sh = sh.dq_stride_h; p.dq_ss = sh.dq_stride_s;
   p.dkv_sh = sh.dkv_stride_h; p.dkv_ss = sh.dkv_stride_s;
 
-  if (dk) {  // dK, dV
-    BwdParams a = p;
-    a.ntile = (sh.s_k + kv::BN - 1) / kv::BN;
-    const int64_t total = static_cast<int64_t>(a.ntile) * sh.h_kv;
-    if (total > (1 << 30)) return DFA_ERR_SHAPE;
-    a.total = static_cast<int>(total);
-    a.per_xcd = (a.total + 7) / 8;
-    const size_t smem = kv::SMEM_BYTES;
-    // > 64 KB of dynamic LDS needs the opt-in, once per process (thread-safe)
-    static std::once_flag once;
-    static int attr_rc = DFA_OK;
-    std::call_once(once, [smem] {
-      for (const void* f : {reinterpret_cast<const void*>(kv::k_bwd_dkdv_bf16<false>),
-                            reinterpret_cast<const void*>(kv::k_bwd_dkdv_bf16<true>)}) {
-        const int rc = hip_status(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                      static_cast<int>(smem)));
-        if (rc) attr_rc = rc;
+  const bool ragged = sh.s_q % kv::BM != 0, dq = pairs[0].dq, dk = pairs[0].dk;
+  if (dk && !make_items(p.kv_items, sh.s_k, kv::BN, sh.h_kv, n)) return DFA_ERR_SHAPE;
+  if (dk && dq) {
+    // Both kinds in one launch: the second kind's workgroups fill the CUs that the first leaves idle.  us per
+    // call, two launches / here:  8 heads x 512 rows 35 / 19, x 2048 98 / 60, x 4096 225 / 212;  32 x 4096
+    // 823 / 804, x 16384 12364 / 12350;  32 over 8 heads x 1024 119 / 91, x 4096 802 / 783, causal 560 / 475.
+    // (Within 2 % either way where the last round of workgroups decides, e.g. 32 x 2777 426 / 435.)
+    // dq by 128-row workgroups with two key parts while all workgroups still run at once (8 x 2048: 60, with
+    // 256 rows 72), by 256-row ones if that makes them (8 x 2304: 84, with 128 rows 108), then by 128-row
+    // ones again as long as they are the smaller steps to balance (8 x 2777: 130 against 146; at 32 x 2048
+    // 227 against 217).
+    auto count = [&](int rows) { return (static_cast<int64_t>(sh.s_q) + rows - 1) / rows * sh.h_q * n; };
+    const int64_t n_kv = p.kv_items.total, n256 = count(256);
+    const bool split = n_kv + count(128) <= 256 || (n_kv + n256 > 256 && n256 <= 128);
+    // The longer workgroups first: a dk/dv workgroup walks over all query heads of its group.
+    p.q_first = sh.h_q == sh.h_kv;
+    if (!make_items(p.q_items, sh.s_q, split ? 128 : 256, sh.h_q, n)) return DFA_ERR_SHAPE;
+    const int64_t blocks = 8 * (static_cast<int64_t>(p.kv_items.per_xcd) + p.q_items.per_xcd);
+    if (blocks > MAX_BLOCKS) {       // one kind, one pair at a time
+      for (int i = 0; i < n; ++i) {
+        dfa_bwd_pair a = pairs[i], b = pairs[i];
+        a.dq = nullptr; b.dk = b.dv = nullptr;
+        int rc = launch_bwd_bf16(sh, &a, 1, st);
+        if (!rc) rc = launch_bwd_bf16(sh, &b, 1, st);
+        if (rc) return rc;
       }
-    });
-    if (attr_rc) return attr_rc;
-    if (sh.s_q % kv::BM == 0) kv::k_bwd_dkdv_bf16<false><<<a.per_xcd * 8, kv::NT, smem, st>>>(a);
-    else kv::k_bwd_dkdv_bf16<true><<<a.per_xcd * 8, kv::NT, smem, st>>>(a);
-    const int rc = last_launch_status();
-    if (rc) return rc;
+      return DFA_OK;
+    }
+    if (split)
+      return ragged ? launch<k_bwd_bf16<true, 2>>(p, blocks, kv::NT, kv::SMEM_BYTES, st)
+                    : launch<k_bwd_bf16<false, 2>>(p, blocks, kv::NT, kv::SMEM_BYTES, st);
+    return ragged ? launch<k_bwd_bf16<true, 1>>(p, blocks, kv::NT, kv::SMEM_BYTES, st)
+                  : launch<k_bwd_bf16<false, 1>>(p, blocks, kv::NT, kv::SMEM_BYTES, st);
   }
-  if (dq) {  // dQ
-    BwdParams b = p;
-    const size_t smem = 4 * qs::TILE_BYTES;
-    static std::once_flag once;
-    static int attr_rc = DFA_OK;
-    std::call_once(once, [smem] {
-      for (const void* f : {reinterpret_cast<const void*>(qs::k_bwd_dq_bf16<4>),
-                            reinterpret_cast<const void*>(qs::k_bwd_dq_bf16<8>)}) {
-        const int rc = hip_status(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                      static_cast<int>(smem)));
-        if (rc) attr_rc = rc;
-      }
-    });
-    if (attr_rc) return attr_rc;
-    // 256-row workgroups for long unmasked chunks (at least four of them per CU), 128 rows otherwise
-    const bool wide = !sh.causal && static_cast<int64_t>(sh.h_q) * ((sh.s_q + 255) / 256) >= 1024;
-    const int bm = wide ? 256 : 128;
-    b.ntile = (sh.s_q + bm - 1) / bm;
-    const int64_t total = static_cast<int64_t>(b.ntile) * sh.h_q;
-    if (total > (1 << 30)) return DFA_ERR_SHAPE;
-    b.total = static_cast<int>(total);
-    b.per_xcd = (b.total + 7) / 8;
-    if (wide) qs::k_bwd_dq_bf16<8><<<b.per_xcd * 8, 512, smem, st>>>(b);
-    else qs::k_bwd_dq_bf16<4><<<b.per_xcd * 8, 256, smem, st>>>(b);
+  if (dk) {
+    const int64_t blocks = 8 * static_cast<int64_t>(p.kv_items.per_xcd);
+    return ragged ? launch<k_bwd_dkdv_bf16<true>>(p, blocks, kv::NT, kv::SMEM_BYTES, st)
+                  : launch<k_bwd_dkdv_bf16<false>>(p, blocks, kv::NT, kv::SMEM_BYTES, st);
   }
-  return last_launch_status();
+  // dq alone: 256-row workgroups for long unmasked chunks (at least four of them per CU), 128 rows otherwise
+  const bool wide = !sh.causal && (static_cast<int64_t>(sh.s_q) + 255) / 256 * sh.h_q * n >= 1024;
+  if (!make_items(p.q_items, sh.s_q, wide ? 256 : 128, sh.h_q, n)) return DFA_ERR_SHAPE;
+  const int64_t blocks = 8 * static_cast<int64_t>(p.q_items.per_xcd);
+  return wide ? launch<k_bwd_dq_bf16<8>>(p, blocks, 512, 4 * qs::TILE_BYTES, st)
+              : launch<k_bwd_dq_bf16<4>>(p, blocks, 256, 4 * qs::TILE_BYTES, st);
 }
 
 }  // namespace dfa

@@ -138,12 +138,8 @@ def backward_worker(Q, K, V, dO, scale, P, w, bufs: Buffers, mode="balanced", wi
         diag = st.kind == B.DFA_STEP_DIAG
         acc_q = touched is None or qc in touched["dq"]
         acc_kv = touched is None or kc in touched["dkv"]
-        if acc_q == acc_kv:
-            B.dfa_chunk_bwd(*args, _chunk(bufs.dQ, qc, c), _chunk(bufs.dK, kc, c), _chunk(bufs.dV, kc, c), diag, scale,
-                            accumulate=acc_q)
-        else:   # one side starts fresh, the other accumulates: the two halves of the call, one after the other
-            B.dfa_chunk_bwd(*args, None, _chunk(bufs.dK, kc, c), _chunk(bufs.dV, kc, c), diag, scale, accumulate=acc_kv)
-            B.dfa_chunk_bwd(*args, _chunk(bufs.dQ, qc, c), None, None, diag, scale, accumulate=acc_q)
+        B.dfa_chunk_bwd(*args, _chunk(bufs.dQ, qc, c), _chunk(bufs.dK, kc, c), _chunk(bufs.dV, kc, c), diag, scale,
+                        accumulate=acc_q, accumulate_dkv=acc_kv)
         if touched is not None:
             touched["dq"].add(qc); touched["dkv"].add(kc)
 

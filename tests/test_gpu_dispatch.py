@@ -92,3 +92,42 @@ def test_bf16_forward_parts_far_apart(shape):
         O, L = A.attention_fwd(np64(q), np64(kk), np64(v), scale, causal=causal)
         # |v| reaches 4.5; a weight is off by 2^-9 of itself
         assert maxerr(o, O) <= 2e-2 and maxerr(lse, L) <= 2e-2 + 2.0 ** -20 * abs(L).max()
+
+
+# bf16 backward: dq by 128-row workgroups with two key parts or by 256-row ones, next to the dk/dv workgroups.
+BWD_FORMS = [
+    # h_q, h_kv, s_q, s_k, causal
+    (4, 2, 129, 97, False),       # 128 rows, two parts; one row past a block, keys of the last tile in part 0 only
+    (3, 3, 70, 161, False),       # the same, one key in the last tile's second part
+    (2, 1, 300, 300, True),
+    (80, 80, 200, 130, False),    # 256 rows: 160 + 80 workgroups run at once, 160 + 160 would not
+    (110, 55, 140, 320, False),   # 128 rows again: 165 + 110 workgroups
+    (140, 140, 140, 140, True),   # 256 rows, more than one round, causal
+]
+
+
+@pytest.mark.parametrize("shape", BWD_FORMS)
+def test_bf16_backward_forms(shape):
+    """All gradients of one call, and dq and dk, dv of calls that want one side, with every mix of overwriting
+    and adding."""
+    h_q, h_kv, s_q, s_k, causal = shape
+    d, tol = 128, TOL[torch.bfloat16]
+    scale = d ** -0.5
+    q, k, v, do = case(8000 + s_q + s_k, h_q, h_kv, s_q, s_k, d, torch.bfloat16)
+    q64, k64, v64, do64 = (np64(t) for t in (q, k, v, do))
+    O, L = A.attention_fwd(q64, k64, v64, scale, causal=causal)
+    want = A.attention_bwd(q64, k64, v64, do64, scale, causal=causal)
+    Q, K, V, dO = (t.to(dev()) for t in (q, k, v, do))
+    lse = torch.from_numpy(L).float().to(dev())
+    delta = torch.from_numpy(A.delta_rows(O, do64)).float().to(dev())
+    # gradients of the short causal rows and sums over a group are larger than those of long chunks
+    bound = [tol * max(1.0, abs(w).max() / 4) for w in want]
+    for acc_q, acc_kv in ((False, False), (True, False), (False, True), (True, True)):
+        got = [torch.full(w.shape, 0.5, device=dev()) for w in want]
+        dfa.dfa_chunk_bwd(Q, K, V, lse, delta, dO, *got, causal, scale, accumulate=acc_q, accumulate_dkv=acc_kv)
+        for g, w, b, a in zip(got, want, bound, (acc_q, acc_kv, acc_kv)):
+            assert maxerr(g, w + (0.5 if a else 0.0)) <= b
+    dq = dfa.dfa_chunk_bwd(Q, K, V, lse, delta, dO, torch.empty_like(got[0]), None, None, causal, scale)[0]
+    _, dk, dv = dfa.dfa_chunk_bwd(Q, K, V, lse, delta, dO, None, *(torch.empty_like(g) for g in got[1:]), causal, scale)
+    for g, w, b in zip((dq, dk, dv), want, bound):
+        assert maxerr(g, w) <= b
