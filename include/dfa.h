@@ -149,8 +149,10 @@ int dfa_chunk_bwd(const dfa_shape* sh, const void* q, const void* k, const void*
  * piece of work, with dq and dk, dv accumulated into or overwritten independently of each other.
  * `pairs` is a HOST array, read before the call returns.  The pairs are computed at the same time:
  * no output may overlap another pair's, and all pairs select the same outputs (DFA_ERR_ARG
- * otherwise).  n_pairs == 0 is a no-op.  Results of a pair are those of dfa_chunk_bwd up to the order
- * of summation, which depends on the shape and n_pairs alone.
+ * otherwise).  `workspace`: scratch in device memory, 16-byte aligned, not to be used by anything
+ * else until the work on `stream` is done; dfa_chunk_bwd_workspace() bytes let it choose freely how to
+ * divide the work, with fewer bytes or NULL it is divided without.  n_pairs == 0 is a no-op.  Results of a pair are those of dfa_chunk_bwd up to the order
+ * of summation, which depends on the shape, n_pairs and workspace_bytes alone.
  */
 typedef struct {
   const void *q, *k, *v;
@@ -160,7 +162,13 @@ typedef struct {
   int32_t accumulate_dq, accumulate_dkv;   /* 0 overwrites, otherwise adds */
 } dfa_bwd_pair;
 
-int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t n_pairs, void* stream);
+int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t n_pairs, void* workspace,
+                        int64_t workspace_bytes, void* stream);
+
+/* Bytes of scratch that dfa_chunk_bwd_batch can use for n_pairs pairs of this shape when dq and / or
+ * dk, dv are wanted (0 where it needs none), or a negative dfa_status.  Pure host function; strides
+ * are not looked at.  At most 128 MiB. */
+int64_t dfa_chunk_bwd_workspace(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int32_t want_dkv);
 
 /* Step kinds of the balanced schedule. */
 typedef enum { DFA_STEP_IDLE = 0, DFA_STEP_DIAG = 1, DFA_STEP_OWN = 2, DFA_STEP_HELP = 3 } dfa_step_kind;

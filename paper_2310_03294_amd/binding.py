@@ -57,7 +57,7 @@ class DfaStep(ctypes.Structure):
 Step = collections.namedtuple("Step", "t kind q_chunk kv_chunk send_to recv_from")
 
 EXPORTS = ("dfa_chunk_fwd", "dfa_chunk_fwd_acc", "dfa_merge", "dfa_delta", "dfa_chunk_bwd",
-           "dfa_chunk_bwd_batch", "dfa_schedule", "dfa_schedule_mode", "dfa_schedule_window", "dfa_mfma_probe", "dfa_mfma_probe_data", "dfa_status_str",
+           "dfa_chunk_bwd_batch", "dfa_chunk_bwd_workspace", "dfa_schedule", "dfa_schedule_mode", "dfa_schedule_window", "dfa_mfma_probe", "dfa_mfma_probe_data", "dfa_status_str",
            "dfa_version")
 
 
@@ -82,7 +82,7 @@ def load_library():
     lib.dfa_merge.argtypes = [ctypes.POINTER(DfaMergeDesc), vp, vp, vp, vp, vp]
     lib.dfa_delta.argtypes = [shp, vp, vp, vp, vp]
     lib.dfa_chunk_bwd.argtypes = [shp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_int, vp]
-    lib.dfa_chunk_bwd_batch.argtypes = [shp, ctypes.POINTER(DfaBwdPair), i32, vp]
+    lib.dfa_chunk_bwd_batch.argtypes = [shp, ctypes.POINTER(DfaBwdPair), i32, vp, i64, vp]
     lib.dfa_schedule.argtypes = [i32, i32, ctypes.POINTER(DfaStep), i32]
     lib.dfa_schedule_mode.argtypes = [i32, i32, i32, ctypes.POINTER(DfaStep), i32]
     lib.dfa_schedule_window.argtypes = [i32, i32, i32, ctypes.POINTER(DfaStep), i32]
@@ -93,9 +93,11 @@ def load_library():
     lib.dfa_status_str.argtypes = [ctypes.c_int]
     lib.dfa_status_str.restype = ctypes.c_char_p
     lib.dfa_version.argtypes = []
+    lib.dfa_chunk_bwd_workspace.argtypes = [shp, i32, i32, i32]
     for name in EXPORTS:
         if name not in ("dfa_status_str",):
             getattr(lib, name).restype = ctypes.c_int
+    lib.dfa_chunk_bwd_workspace.restype = i64
     _lib = lib
     return lib
 
@@ -239,6 +241,20 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+def _workspace(n, stream):
+    """Scratch of n bytes for one call on `stream`: (tensor or None, bytes).  It comes from the caching
+    allocator of that stream, so that the stream's order protects it when it is let go after the call; a
+    stream known by its handle alone gets none, unless it is the current one."""
+    if n <= 0:
+        return None, 0
+    if stream is None or _stream(stream) == torch.cuda.current_stream().cuda_stream:
+        return torch.empty(n, dtype=torch.uint8, device="cuda"), n
+    if isinstance(stream, torch.cuda.Stream):
+        with torch.cuda.stream(stream):
+            return torch.empty(n, dtype=torch.uint8, device="cuda"), n
+    return None, 0
+
+
 def dfa_chunk_bwd(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale, accumulate=False, stream=None,
                   accumulate_dkv=None):
     """dq, dk, dv contributions of one chunk pair from the saved logsumexp and D (no forward re-run).
@@ -249,7 +265,8 @@ def dfa_chunk_bwd(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale, accumulate
     pair = DfaBwdPair(q.data_ptr(), k.data_ptr(), v.data_ptr(), lse.data_ptr(), delta.data_ptr(), dO.data_ptr(),
                       _ptr(dq), _ptr(dk), _ptr(dv), bool(accumulate),
                       bool(accumulate if accumulate_dkv is None else accumulate_dkv))
-    _check(lib.dfa_chunk_bwd_batch(ctypes.byref(sh), ctypes.byref(pair), 1, _stream(stream)), "dfa_chunk_bwd")
+    ws, n = _workspace(lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), 1, dq is not None, dk is not None), stream)
+    _check(lib.dfa_chunk_bwd_batch(ctypes.byref(sh), ctypes.byref(pair), 1, _ptr(ws), n, _stream(stream)), "dfa_chunk_bwd")
     return dq, dk, dv
 
 

@@ -114,7 +114,8 @@ extern "C" int dfa_delta(const dfa_shape* sh, const void* o, const void* dO, flo
   return dfa::launch_delta(*sh, o, dO, delta, static_cast<hipStream_t>(stream));
 }
 
-extern "C" int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t n_pairs, void* stream) {
+extern "C" int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t n_pairs, void* workspace,
+                                   int64_t workspace_bytes, void* stream) {
   int rc = check_common(sh);
   if (rc != DFA_OK) return rc;
   if (n_pairs < 0) return DFA_ERR_ARG;
@@ -137,6 +138,8 @@ extern "C" int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pair
       !stride_ok(sh->dkv_stride_h, sh->dkv_stride_s, sh->d, sh->s_k))
     return DFA_ERR_SHAPE;
   if (!row_stride_ok(sh->lse_stride_h, sh->s_q)) return DFA_ERR_SHAPE;
+  if (workspace_bytes < 0) return DFA_ERR_ARG;
+  if (!aligned16(workspace)) return DFA_ERR_SHAPE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (sh->s_q == 0 || sh->s_k == 0) {
     // nothing flows through an empty pair; honour "overwrite" semantics
@@ -152,12 +155,20 @@ extern "C" int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pair
     }
     return DFA_OK;
   }
-  return sh->dtype == DFA_F32 ? dfa::launch_bwd_f32(*sh, pairs, n_pairs, st) : dfa::launch_bwd_bf16(*sh, pairs, n_pairs, st);
+  return sh->dtype == DFA_F32 ? dfa::launch_bwd_f32(*sh, pairs, n_pairs, st) : dfa::launch_bwd_bf16(*sh, pairs, n_pairs, workspace, workspace_bytes, st);
+}
+
+extern "C" int64_t dfa_chunk_bwd_workspace(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int32_t want_dkv) {
+  const int rc = check_common(sh);
+  if (rc != DFA_OK) return rc;
+  if (n_pairs < 0) return DFA_ERR_ARG;
+  if (n_pairs == 0 || sh->s_q == 0 || sh->s_k == 0 || sh->dtype == DFA_F32) return 0;
+  return dfa::bwd_bf16_workspace(*sh, n_pairs, want_dq != 0, want_dkv != 0);
 }
 
 extern "C" int dfa_chunk_bwd(const dfa_shape* sh, const void* q, const void* k, const void* v,
                              const float* lse, const float* delta, const void* dO,
                              float* dq, float* dk, float* dv, int accumulate, void* stream) {
   const dfa_bwd_pair p{q, k, v, lse, delta, dO, dq, dk, dv, accumulate != 0, accumulate != 0};
-  return dfa_chunk_bwd_batch(sh, &p, 1, stream);
+  return dfa_chunk_bwd_batch(sh, &p, 1, nullptr, 0, stream);
 }

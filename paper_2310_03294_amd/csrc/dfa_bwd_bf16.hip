@@ -28,7 +28,9 @@
 // retire about one fp32 atomic per clock and channel (~3.1e11 per second on the whole chip),
 // which caps a 128-key workgroup tile at ~400 TFLOP/s no matter how the rest is scheduled.
 // Recomputing S and dP in a second kernel costs 7 products instead of 5 but has no such cap.
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "dfa_internal.h"
 #include "dfa_mfma.h"
@@ -48,16 +50,26 @@ struct Pair {
   float *dq, *dk, *dv;
   int acc_q, acc_kv;         // add to what dq / dk, dv hold
 };
-constexpr int64_t MAX_BLOCKS = 1 << 22;      // of 512 threads: half of what a grid takes
 constexpr int MAX_PAIRS = 16;       // per launch: the pairs travel in the kernel arguments
 
 struct BwdParams {
-  Pair pair[MAX_PAIRS];
   int s_q, s_k, h_q, h_kv, group, causal, q_first;
+  int parts;                 // dk, dv: workgroups that share the query tiles of a key tile
+  f32x4* partial;            // parts > 1: their sums, PART_F4 per workgroup
   Items kv_items, q_items;
   float scale;
   int64_t q_sh, q_ss, kv_sh, kv_ss, l_sh, dq_sh, dq_ss, dkv_sh, dkv_ss;
 };
+
+// One pair's operands are read together with everything else; picking them from a list first costs every
+// workgroup another round trip to the argument memory (1 % of a call of 4096 workgroups).
+template <int NP> struct BwdPairs : BwdParams { Pair pair[NP]; };
+template <int NP>
+__device__ __forceinline__ const Pair& pair_of(const BwdPairs<NP>& p, const Items& it, int item) {
+  return p.pair[NP == 1 ? 0 : item / it.per_pair];
+}
+template <int NP>
+__device__ __forceinline__ int item_in_pair(const Items& it, int item) { return NP == 1 ? item : item % it.per_pair; }
 
 // XCD-aware mapping: workgroup ids go round-robin over the 8 XCDs; every XCD gets a contiguous range of
 // (head, tile) items, so that the tiles of one head share Q/dO (or K/V) in one L2.
@@ -80,6 +92,8 @@ constexpr int OFF_G = OFF_Q + 3 * QTILE_BYTES;
 constexpr int OFF_LD = OFF_G + 2 * QTILE_BYTES;
 constexpr int OFF_PX = OFF_LD + 3 * LD_BYTES;
 constexpr int SMEM_BYTES = OFF_PX + 2 * PX_BYTES;
+// dk and dv of a workgroup in its own order: (wavefront, four registers, lane), 128 KB
+constexpr int PART_F4 = 8 * 16 * 64;
 
 // The Q and dO tiles go from global memory straight into LDS (global_load_lds_dwordx4: every
 // lane supplies its own global address, the wavefront's 64 x 16 bytes land contiguously at the
@@ -209,12 +223,12 @@ __device__ __forceinline__ void col_products(f32x16 (&acc)[4], const char* Ys, i
 }
 
 // RAGGED: s_q is no multiple of the 64-row tile, so a head's last tile has rows past the end.
-template <bool RAGGED>
-__device__ __forceinline__ void dkdv(const BwdParams& p, int item, char* smem) {
-  const Pair& pr = p.pair[item / p.kv_items.per_pair];
-  item %= p.kv_items.per_pair;
-  const int kh = item / p.kv_items.ntile;
+// PARTS: several workgroups share the query tiles of a key tile.
+template <bool RAGGED, bool PARTS>
+__device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int item, f32x4* partial, char* smem) {
   const int tk = item % p.kv_items.ntile;  // causal: low key tiles meet the most query tiles and come first
+  const int part = PARTS ? item / p.kv_items.ntile % p.parts : 0;
+  const int kh = PARTS ? item / p.kv_items.ntile / p.parts : item / p.kv_items.ntile;
   const int k0 = tk * BN;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -251,7 +265,15 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, int item, char* smem) {
   const float c2 = p.scale * LOG2E;
   const int q_begin = p.causal ? k0 : 0;            // k0 is a multiple of BM
   const int ntq = (p.s_q - q_begin + BM - 1) / BM;  // query tiles per head for this key tile
-  const int niter = ntq * p.group;
+  // this workgroup's share of the group's ntq * group query tiles
+  const int walk = ntq * p.group;
+  const int it0 = PARTS ? static_cast<int>(static_cast<int64_t>(walk) * part / p.parts) : 0;
+  const int niter = PARTS ? static_cast<int>(static_cast<int64_t>(walk) * (part + 1) / p.parts) - it0 : walk;
+  if (PARTS && niter == 0) {          // more parts than tiles (the last key tiles of a diagonal chunk)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) partial[(wave * 16 + i) * 64 + lane] = f32x4{0.f, 0.f, 0.f, 0.f};
+    return;
+  }
 
   // Tile staging.  Two cursors: `cur` for the tile copies (tile t + 1 during slot t; Q by the S
   // wavefronts, dO by the dP wavefronts), `curl` for lse / D (S wavefronts), which pass through a
@@ -261,11 +283,11 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, int item, char* smem) {
   QTileRegs tr;
   QTileCursor cur, curl;
   {
-    const int hq0 = kh * p.group;
+    const int hq0 = kh * p.group + it0 / ntq;
     cur.qh = reinterpret_cast<const char*>(pr.q + hq0 * p.q_sh);
     cur.gh = reinterpret_cast<const char*>(pr.dO + hq0 * p.q_sh);
     cur.ldh = (kb == 1 ? pr.delta : pr.lse) + hq0 * p.l_sh;
-    cur.q0 = q_begin;
+    cur.q0 = q_begin + it0 % ntq * BM;
     curl = cur;
   }
   const int q_end = q_begin + ntq * BM;
@@ -293,7 +315,7 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, int item, char* smem) {
 #pragma unroll
   for (int j = 0; j < 16; ++j) zero[j] = 0.f;
   if (!dp_wave) {
-    int q0 = q_begin;      // first query row of tile `it`
+    int q0 = q_begin + it0 % ntq * BM;      // first query row of tile `it`
     for (int it = 0; it < niter; ++it) {
       const bool more = it + 1 < niter;
       const int next = slot == 2 ? 0 : slot + 1;
@@ -438,8 +460,15 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, int item, char* smem) {
     __syncthreads();
   }
 
-
-  if (kvalid) {
+  if constexpr (PARTS) {     // k_reduce_dkdv adds the parts up
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      f32x4 a;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = acc[i >> 2][(i & 3) * 4 + e];
+      partial[(wave * 16 + i) * 64 + lane] = a;
+    }
+  } else if (kvalid) {
     float* dst = (dp_wave ? pr.dk : pr.dv) + kh * p.dkv_sh + static_cast<int64_t>(kvrow) * p.dkv_ss;
     const float f = dp_wave ? p.scale : 1.f;
 #pragma unroll
@@ -476,10 +505,8 @@ constexpr int TILE_BYTES = BN * kRowBytes;
 // NW = 8, NS = 2 (128 rows, one workgroup per CU, half the serial walk each) is for calls that do not fill
 // the device; the sums of the two parts are added through LDS at the end.
 template <int NW, int NS>
-__device__ __forceinline__ void dq(const BwdParams& p, int item, char* smem) {   // smem: two (K tile, V tile) buffers
+__device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item, char* smem) {   // smem: two (K tile, V tile) buffers
   constexpr int BM = NW / NS * 32;     // query rows per workgroup
-  const Pair& pr = p.pair[item / p.q_items.per_pair];
-  item %= p.q_items.per_pair;
   const int head = item / p.q_items.ntile;
   int tq = item % p.q_items.ntile;
   if (p.causal) tq = p.q_items.ntile - 1 - tq;      // longest rows first
@@ -676,38 +703,77 @@ __device__ __forceinline__ void dq(const BwdParams& p, int item, char* smem) {  
 
 }  // namespace qs
 
-// The kernels: dk, dv alone, dq alone, and both kinds of workgroups in one launch.
-template <bool RAGGED>
-__global__ void __launch_bounds__(kv::NT, 2) k_bwd_dkdv_bf16(BwdParams p) {
-  extern __shared__ __align__(16) char smem[];
-  const int item = item_of(p.kv_items, blockIdx.x);
-  if (item < p.kv_items.total) kv::dkdv<RAGGED>(p, item, smem);
-}
-
-template <int NW>
-__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdParams p) {
-  extern __shared__ __align__(16) char smem[];
-  const int item = item_of(p.q_items, blockIdx.x);
-  if (item < p.q_items.total) qs::dq<NW, 1>(p, item, smem);
-}
-
-template <bool RAGGED, int NS>
-__global__ void __launch_bounds__(kv::NT, 2) k_bwd_bf16(BwdParams p) {
-  extern __shared__ __align__(16) char smem[];
-  const int n_kv = p.kv_items.per_xcd * 8, n_q = p.q_items.per_xcd * 8;
-  const int bid = blockIdx.x;
-  if (p.q_first ? bid >= n_q : bid < n_kv) {
-    const int item = item_of(p.kv_items, p.q_first ? bid - n_q : bid);
-    if (item < p.kv_items.total) kv::dkdv<RAGGED>(p, item, smem);
-  } else {
-    const int item = item_of(p.q_items, p.q_first ? bid : bid - n_kv);
-    if (item < p.q_items.total) qs::dq<8, NS>(p, item, smem);
+// dk, dv of a key tile from the sums of its parts: grid (4 column blocks, key tiles), 512 threads in the
+// order of the workgroups that wrote them.  The order of the sum is that of the parts.
+__global__ void __launch_bounds__(kv::NT) k_reduce_dkdv(BwdPairs<MAX_PAIRS> p) {
+  const int tile = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tk = tile % p.kv_items.ntile, pk = tile / p.kv_items.ntile;      // pk: pair * h_kv + kv head
+  const Pair& pr = p.pair[pk / p.h_kv];
+  const bool is_dk = wave >= 4;
+  const int row = tk * kv::BN + (wave & 3) * 32 + (lane & 31);
+  if (row >= p.s_k) return;
+  const int64_t step = static_cast<int64_t>(p.kv_items.ntile) * kv::PART_F4;
+  const f32x4* src = p.partial + (static_cast<int64_t>(pk) * p.parts * p.kv_items.ntile + tk) * kv::PART_F4 +
+                     (wave * 16 + blockIdx.x * 4) * 64 + lane;
+  f32x4 a[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = src[i * 64];
+  for (int s = 1; s < p.parts; ++s) {
+    src += step;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] += src[i * 64];
+  }
+  float* dst = (is_dk ? pr.dk : pr.dv) + (pk % p.h_kv) * p.dkv_sh + static_cast<int64_t>(row) * p.dkv_ss +
+               blockIdx.x * 32 + (lane >> 5) * 4;
+  const float f = is_dk ? p.scale : 1.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f32x4* d = reinterpret_cast<f32x4*>(dst + i * 8);
+    f32x4 x = a[i] * f;
+    if (pr.acc_kv) x += *d;
+    *d = x;
   }
 }
 
+// The kernels: dk, dv alone, dq alone, and both kinds of workgroups in one launch; of NP pairs at most.
+template <bool RAGGED, bool PARTS, int NP>
+__device__ __forceinline__ void run_dkdv(const BwdPairs<NP>& p, int bid, char* smem) {
+  const int item = item_of(p.kv_items, bid);
+  if (item < p.kv_items.total)
+    kv::dkdv<RAGGED, PARTS>(p, pair_of(p, p.kv_items, item), item_in_pair<NP>(p.kv_items, item),
+                            p.partial + static_cast<int64_t>(item) * kv::PART_F4, smem);
+}
+template <int NW, int NS, int NP>
+__device__ __forceinline__ void run_dq(const BwdPairs<NP>& p, int bid, char* smem) {
+  const int item = item_of(p.q_items, bid);
+  if (item < p.q_items.total)
+    qs::dq<NW, NS>(p, pair_of(p, p.q_items, item), item_in_pair<NP>(p.q_items, item), smem);
+}
+
+template <bool RAGGED, bool PARTS, int NP>
+__global__ void __launch_bounds__(kv::NT, 2) k_bwd_dkdv_bf16(BwdPairs<NP> p) {
+  extern __shared__ __align__(16) char smem[];
+  run_dkdv<RAGGED, PARTS, NP>(p, blockIdx.x, smem);
+}
+
+template <int NW, int NP>
+__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPairs<NP> p) {
+  extern __shared__ __align__(16) char smem[];
+  run_dq<NW, 1, NP>(p, blockIdx.x, smem);
+}
+
+template <bool RAGGED, int NS, bool PARTS, int NP>
+__global__ void __launch_bounds__(kv::NT, 2) k_bwd_bf16(BwdPairs<NP> p) {
+  extern __shared__ __align__(16) char smem[];
+  const int n_kv = p.kv_items.per_xcd * 8, n_q = p.q_items.per_xcd * 8;
+  const int bid = blockIdx.x;
+  if (p.q_first ? bid >= n_q : bid < n_kv) run_dkdv<RAGGED, PARTS, NP>(p, p.q_first ? bid - n_q : bid, smem);
+  else run_dq<8, NS, NP>(p, p.q_first ? bid : bid - n_kv, smem);
+}
+
 // > 64 KB of dynamic LDS needs the opt-in, once per kernel and process (thread-safe)
-template <void (*KERNEL)(BwdParams)>
-int launch(const BwdParams& p, int64_t blocks, int threads, int smem, hipStream_t st) {
+template <int NP, void (*KERNEL)(BwdPairs<NP>)>
+int launch(const BwdPairs<MAX_PAIRS>& all, int64_t blocks, int threads, int smem, hipStream_t st) {
   static std::once_flag once;
   static int attr_rc = DFA_OK;
   std::call_once(once, [smem] {
@@ -715,11 +781,18 @@ int launch(const BwdParams& p, int64_t blocks, int threads, int smem, hipStream_
                                              hipFuncAttributeMaxDynamicSharedMemorySize, smem));
   });
   if (attr_rc) return attr_rc;
+  BwdPairs<NP> p;
+  static_cast<BwdParams&>(p) = all;
+  for (int i = 0; i < NP; ++i) p.pair[i] = all.pair[i];
   KERNEL<<<static_cast<int>(blocks), threads, smem, st>>>(p);
   return last_launch_status();
 }
 
-// Items of `rows` rows each of `heads` heads and `pairs` pairs; false: more than a launch takes.
+// f(true) or f(false), as a compile-time constant
+template <class F>
+int with(bool b, F f) { return b ? f(std::true_type{}) : f(std::false_type{}); }
+
+// Items of `rows` rows each of `heads` heads (or heads x parts) and `pairs` pairs; false: more than a launch takes.
 bool make_items(Items& it, int s, int rows, int heads, int pairs) {
   const int64_t n = (static_cast<int64_t>(s) + rows - 1) / rows, total = n * heads * pairs;
   if (total > (1 << 29)) return false;
@@ -730,14 +803,66 @@ bool make_items(Items& it, int s, int rows, int heads, int pairs) {
   return true;
 }
 
+int64_t blocks_of(int rows, int per) { return (static_cast<int64_t>(rows) + per - 1) / per; }
+
+constexpr int64_t PART_BYTES = kv::PART_F4 * 16;
+
+// How a call's work is divided: dq by 128-row workgroups with two key parts (split) or 256-row ones, and
+// `parts` workgroups per key tile for dk, dv.
+struct Plan { bool split; int parts; double us; };
+
+// dq by 128-row workgroups with two key parts while all workgroups still run at once (8 heads x 2048: 60
+// us, with 256 rows 72), by 256-row ones if that makes them (8 x 2304: 84, with 128 rows 108), then by
+// 128-row ones again as long as they are the smaller steps to balance (8 x 2777: 130 against 146; at
+// 32 x 2048 227 against 217).
+bool split_dq(int64_t n_kv, int64_t n256, int64_t n128) {
+  return n_kv + n128 <= 256 || (n_kv + n256 > 256 && n256 <= 128);
+}
+
+// Parts.  A dk/dv workgroup walks over the query tiles of its whole group of heads, and with grouped heads
+// there are few of them.  `parts` workgroups share the walk, and their sums (128 KB each) go through
+// memory and a second launch: worth it where a few long workgroups would be alone on the device at the end.
+// The estimate, with what one box measured for its terms: 8 us per workgroup and 1.35 per query tile (dk,
+// dv) or 1.9 per key tile (dq, 256 rows); a call that runs in one round takes its longest workgroup, a
+// longer one the device's even share and about half a workgroup; the sums move at 2.5 TB/s.  Parts that
+// do not divide the group stride over heads and share less in the L2 (15 %).  us per call with 1 / 2 / 4
+// parts: 8 over 2 heads x 1024 87 / 51 / 35, x 4096 341 / 217 / 212, x 8192 814 / 761 / 767; 32 over 8 x
+// 1024 91 / 66 / 73, x 1500 diagonal 135 / 101 / 103, x 4096 756 / 779 / 810; 8 heads of their own x 1024
+// 31 / 36 / 38.
+Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
+  const int group = sh.h_q / sh.h_kv;
+  const int64_t kv1 = dk ? blocks_of(sh.s_k, kv::BN) * sh.h_kv * pairs : 0;
+  const int64_t n256 = dq ? blocks_of(sh.s_q, 256) * sh.h_q * pairs : 0;
+  const int64_t n128 = dq ? blocks_of(sh.s_q, 128) * sh.h_q * pairs : 0;
+  const double walk_kv = 1.35 * group * blocks_of(sh.s_q, kv::BM), walk_q = 1.9 * blocks_of(sh.s_k, qs::BN);
+  const double mean = sh.causal ? 0.5 : 1.0;           // of a walk
+  Plan best{};
+  for (int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+    const int64_t n_kv = kv1 * parts;
+    if (parts > 1 && (!dk || parts > 4 * group || n_kv > 1024 || n_kv * PART_BYTES > ws_bytes)) break;
+    Plan x{dq && split_dq(n_kv, n256, n128), parts, 0.};
+    const int64_t n_q = x.split ? n128 : n256;
+    const double t_kv = dk ? 8 + walk_kv / parts : 0, w_q = x.split ? walk_q / 2 : walk_q, t_q = dq ? 8 + w_q : 0;
+    x.us = std::max(t_kv, t_q);
+    if (n_kv + n_q > 256) {
+      const double share = (n_kv * (8 + walk_kv * mean / parts) + n_q * (8 + w_q * mean)) / 256;
+      x.us = std::max(x.us, share + 0.45 * x.us);
+    }
+    if (parts > 1) x.us = (x.us + 4 + n_kv * (2 * PART_BYTES / 2.5e6)) * (group % parts ? 1.15 : 1.0);
+    if (parts == 1 || x.us < (best.parts == 1 ? 0.92 : 1.0) * best.us) best = x;
+  }
+  return best;
+}
+
 }  // namespace
 
-int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, hipStream_t st) {
+int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void* ws, int64_t ws_bytes,
+                    hipStream_t st) {
   for (; n > MAX_PAIRS; pairs += MAX_PAIRS, n -= MAX_PAIRS) {
-    const int rc = launch_bwd_bf16(sh, pairs, MAX_PAIRS, st);
+    const int rc = launch_bwd_bf16(sh, pairs, MAX_PAIRS, ws, ws_bytes, st);
     if (rc) return rc;
   }
-  BwdParams p{};
+  BwdPairs<MAX_PAIRS> p{};
   for (int i = 0; i < n; ++i) {
     const dfa_bwd_pair& x = pairs[i];
     p.pair[i] = Pair{static_cast<const __bf16*>(x.q), static_cast<const __bf16*>(x.k), static_cast<const __bf16*>(x.v),
@@ -751,50 +876,71 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, hipSt
   p.dkv_sh = sh.dkv_stride_h; p.dkv_ss = sh.dkv_stride_s;
 
   const bool ragged = sh.s_q % kv::BM != 0, dq = pairs[0].dq, dk = pairs[0].dk;
-  if (dk && !make_items(p.kv_items, sh.s_k, kv::BN, sh.h_kv, n)) return DFA_ERR_SHAPE;
+  const Plan pl = plan(sh, n, dq, dk, ws ? ws_bytes : 0);
+  p.parts = pl.parts;
+  p.partial = static_cast<f32x4*>(ws);
+  if (dk && !make_items(p.kv_items, sh.s_k, kv::BN, sh.h_kv * p.parts, n)) return DFA_ERR_SHAPE;
+  auto reduce = [&] {
+    if (p.parts == 1) return static_cast<int>(DFA_OK);
+    k_reduce_dkdv<<<dim3(4, p.kv_items.total / p.parts), kv::NT, 0, st>>>(p);
+    return last_launch_status();
+  };
   if (dk && dq) {
     // Both kinds in one launch: the second kind's workgroups fill the CUs that the first leaves idle.  us per
     // call, two launches / here:  8 heads x 512 rows 35 / 19, x 2048 98 / 60, x 4096 225 / 212;  32 x 4096
     // 823 / 804, x 16384 12364 / 12350;  32 over 8 heads x 1024 119 / 91, x 4096 802 / 783, causal 560 / 475.
     // (Within 2 % either way where the last round of workgroups decides, e.g. 32 x 2777 426 / 435.)
-    // dq by 128-row workgroups with two key parts while all workgroups still run at once (8 x 2048: 60, with
-    // 256 rows 72), by 256-row ones if that makes them (8 x 2304: 84, with 128 rows 108), then by 128-row
-    // ones again as long as they are the smaller steps to balance (8 x 2777: 130 against 146; at 32 x 2048
-    // 227 against 217).
-    auto count = [&](int rows) { return (static_cast<int64_t>(sh.s_q) + rows - 1) / rows * sh.h_q * n; };
-    const int64_t n_kv = p.kv_items.total, n256 = count(256);
-    const bool split = n_kv + count(128) <= 256 || (n_kv + n256 > 256 && n256 <= 128);
-    // The longer workgroups first: a dk/dv workgroup walks over all query heads of its group.
-    p.q_first = sh.h_q == sh.h_kv;
-    if (!make_items(p.q_items, sh.s_q, split ? 128 : 256, sh.h_q, n)) return DFA_ERR_SHAPE;
+    // The longer workgroups first: a dk/dv workgroup walks over its part of the query heads of a group.
+    p.q_first = p.group <= p.parts;
+    if (!make_items(p.q_items, sh.s_q, pl.split ? 128 : 256, sh.h_q, n)) return DFA_ERR_SHAPE;
     const int64_t blocks = 8 * (static_cast<int64_t>(p.kv_items.per_xcd) + p.q_items.per_xcd);
-    if (blocks > MAX_BLOCKS) {       // one kind, one pair at a time
+    // Ten rounds of workgroups and more: nothing is left to fill, and each kind alone has the better use of
+    // the L2 (32 heads x 12000 6775 against 6808 us).  (Nor would a grid take more than 2^23 of them.)
+    if (p.kv_items.total >= 2560) {
       for (int i = 0; i < n; ++i) {
         dfa_bwd_pair a = pairs[i], b = pairs[i];
         a.dq = nullptr; b.dk = b.dv = nullptr;
-        int rc = launch_bwd_bf16(sh, &a, 1, st);
-        if (!rc) rc = launch_bwd_bf16(sh, &b, 1, st);
+        int rc = launch_bwd_bf16(sh, &a, 1, nullptr, 0, st);
+        if (!rc) rc = launch_bwd_bf16(sh, &b, 1, nullptr, 0, st);
         if (rc) return rc;
       }
       return DFA_OK;
     }
-    if (split)
-      return ragged ? launch<k_bwd_bf16<true, 2>>(p, blocks, kv::NT, kv::SMEM_BYTES, st)
-                    : launch<k_bwd_bf16<false, 2>>(p, blocks, kv::NT, kv::SMEM_BYTES, st);
-    return ragged ? launch<k_bwd_bf16<true, 1>>(p, blocks, kv::NT, kv::SMEM_BYTES, st)
-                  : launch<k_bwd_bf16<false, 1>>(p, blocks, kv::NT, kv::SMEM_BYTES, st);
+    const int rc = with(n > 1, [&](auto m) {
+      constexpr int NP = m() ? MAX_PAIRS : 1;
+      return with(ragged, [&](auto r) {
+        return with(p.parts > 1, [&](auto s) {
+          return pl.split ? launch<NP, k_bwd_bf16<r(), 2, s(), NP>>(p, blocks, kv::NT, kv::SMEM_BYTES, st)
+                          : launch<NP, k_bwd_bf16<r(), 1, s(), NP>>(p, blocks, kv::NT, kv::SMEM_BYTES, st);
+        });
+      });
+    });
+    return rc ? rc : reduce();
   }
-  if (dk) {
-    const int64_t blocks = 8 * static_cast<int64_t>(p.kv_items.per_xcd);
-    return ragged ? launch<k_bwd_dkdv_bf16<true>>(p, blocks, kv::NT, kv::SMEM_BYTES, st)
-                  : launch<k_bwd_dkdv_bf16<false>>(p, blocks, kv::NT, kv::SMEM_BYTES, st);
-  }
-  // dq alone: 256-row workgroups for long unmasked chunks (at least four of them per CU), 128 rows otherwise
-  const bool wide = !sh.causal && (static_cast<int64_t>(sh.s_q) + 255) / 256 * sh.h_q * n >= 1024;
-  if (!make_items(p.q_items, sh.s_q, wide ? 256 : 128, sh.h_q, n)) return DFA_ERR_SHAPE;
-  const int64_t blocks = 8 * static_cast<int64_t>(p.q_items.per_xcd);
-  return wide ? launch<k_bwd_dq_bf16<8>>(p, blocks, 512, 4 * qs::TILE_BYTES, st)
-              : launch<k_bwd_dq_bf16<4>>(p, blocks, 256, 4 * qs::TILE_BYTES, st);
+  return with(n > 1, [&](auto m) {
+    constexpr int NP = m() ? MAX_PAIRS : 1;
+    if (dk) {
+      const int64_t blocks = 8 * static_cast<int64_t>(p.kv_items.per_xcd);
+      const int rc = with(ragged, [&](auto r) {
+        return with(p.parts > 1, [&](auto s) {
+          return launch<NP, k_bwd_dkdv_bf16<r(), s(), NP>>(p, blocks, kv::NT, kv::SMEM_BYTES, st);
+        });
+      });
+      return rc ? rc : reduce();
+    }
+    // dq alone: 256-row workgroups for long unmasked chunks (at least four of them per CU), 128 rows otherwise
+    const bool wide = !sh.causal && blocks_of(sh.s_q, 256) * sh.h_q * n >= 1024;
+    if (!make_items(p.q_items, sh.s_q, wide ? 256 : 128, sh.h_q, n)) return static_cast<int>(DFA_ERR_SHAPE);
+    const int64_t blocks = 8 * static_cast<int64_t>(p.q_items.per_xcd);
+    return wide ? launch<NP, k_bwd_dq_bf16<8, NP>>(p, blocks, 512, 4 * qs::TILE_BYTES, st)
+                : launch<NP, k_bwd_dq_bf16<4, NP>>(p, blocks, 256, 4 * qs::TILE_BYTES, st);
+  });
+}
+
+int64_t bwd_bf16_workspace(const dfa_shape& sh, int n, bool dq, bool dk) {
+  const int per = std::min(n, MAX_PAIRS);
+  const Plan pl = plan(sh, per, dq, dk, INT64_MAX);
+  return pl.parts > 1 ? pl.parts * blocks_of(sh.s_k, kv::BN) * sh.h_kv * per * PART_BYTES : 0;
 }
 
 }  // namespace dfa

@@ -1,11 +1,13 @@
 """GPU parity at the sizes where the launch rules change kernel forms: the smallest calls that reach
 each form, with remainders on both axes, against the fp64 oracle (bounds as in the parity tests)."""
+import ctypes
 import math
 
 import pytest
 import torch
 
 import paper_2310_03294_amd as dfa
+from paper_2310_03294_amd import binding as B
 from gpu_util import TOL, case, dev, maxerr, np64
 from oracle import attention as A
 from test_gpu_parity_small import _run_pair
@@ -131,3 +133,47 @@ def test_bf16_backward_forms(shape):
     _, dk, dv = dfa.dfa_chunk_bwd(Q, K, V, lse, delta, dO, None, *(torch.empty_like(g) for g in got[1:]), causal, scale)
     for g, w, b in zip((dq, dk, dv), want, bound):
         assert maxerr(g, w) <= b
+
+
+# dk, dv by several workgroups per key tile: (heads, rows, keys, causal).
+BWD_PARTS = [
+    (3, 1, 129, 70, False),       # 3 parts, one head each
+    (8, 1, 260, 300, False),      # 8 parts, remainders on both axes
+    (12, 2, 300, 130, False),     # parts that cut through heads
+    (8, 1, 700, 700, True),       # the last key tiles have few query tiles
+    (16, 1, 40, 40, True),        # more parts than a tile has heads to give, or as many
+]
+
+
+@pytest.mark.parametrize("shape", BWD_PARTS)
+def test_bf16_backward_parts(shape):
+    """Against the oracle, and against the same call without scratch (one workgroup per key tile)."""
+    h_q, h_kv, s_q, s_k, causal = shape
+    d, tol = 128, TOL[torch.bfloat16]
+    scale = d ** -0.5
+    q, k, v, do = case(9000 + s_q + s_k, h_q, h_kv, s_q, s_k, d, torch.bfloat16)
+    q64, k64, v64, do64 = (np64(t) for t in (q, k, v, do))
+    O, L = A.attention_fwd(q64, k64, v64, scale, causal=causal)
+    want = A.attention_bwd(q64, k64, v64, do64, scale, causal=causal)
+    bound = [tol * max(1.0, abs(w).max() / 4) for w in want]
+    Q, K, V, dO = (t.to(dev()) for t in (q, k, v, do))
+    lse = torch.from_numpy(L).float().to(dev())
+    delta = torch.from_numpy(A.delta_rows(O, do64)).float().to(dev())
+    lib = B.load_library()
+    for want_dq in (True, False):
+        for acc in (False, True):
+            got = [torch.full(w.shape, 0.5, device=dev()) for w in want]
+            alone = [g.clone() for g in got]
+            dfa.dfa_chunk_bwd(Q, K, V, lse, delta, dO, got[0] if want_dq else None, got[1], got[2], causal, scale,
+                              accumulate=acc)
+            sh = B._bwd_shape(Q, K, V, lse, delta, dO, alone[0], alone[1], alone[2], causal, scale)
+            assert lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), 1, want_dq, 1) > 0
+            pair = B.DfaBwdPair(Q.data_ptr(), K.data_ptr(), V.data_ptr(), lse.data_ptr(), delta.data_ptr(),
+                                dO.data_ptr(), alone[0].data_ptr() if want_dq else None, alone[1].data_ptr(),
+                                alone[2].data_ptr(), acc, acc)
+            assert lib.dfa_chunk_bwd_batch(ctypes.byref(sh), ctypes.byref(pair), 1, None, 0,
+                                           torch.cuda.current_stream().cuda_stream) == 0
+            for i in (0, 1, 2) if want_dq else (1, 2):
+                assert maxerr(got[i], want[i] + (0.5 if acc else 0.0)) <= bound[i]
+                # the same products, summed in another order in fp32
+                assert (got[i] - alone[i]).abs().max().item() <= 1e-5 * max(1.0, abs(want[i]).max())
