@@ -100,6 +100,23 @@ int dfa_chunk_fwd_acc(const dfa_shape* sh, const void* q, const void* k, const v
                       void* o, float* lse, void* stream);
 
 /*
+ * dfa_chunk_fwd_batch - n_pairs forward calls of one shape (dfa_chunk_fwd, or dfa_chunk_fwd_acc where
+ * accumulate != 0) as one piece of work: what the workers of a schedule compute in one time step, on
+ * one device.  `pairs` is a HOST array, read before the call returns.  The pairs are computed at the
+ * same time: no output may overlap another pair's operands.  q, k, v share the strides of `sh`; o and
+ * lse have their own (those of `sh` are not looked at).  n_pairs == 0 is a no-op.
+ */
+typedef struct {
+  const void *q, *k, *v;
+  void* o;
+  float* lse;
+  int64_t o_stride_h, o_stride_s, lse_stride_h;
+  int32_t accumulate, reserved;
+} dfa_fwd_pair;
+
+int dfa_chunk_fwd_batch(const dfa_shape* sh, const dfa_fwd_pair* pairs, int32_t n_pairs, void* stream);
+
+/*
  * dfa_merge - the rescale(o, s, o', s') update of the balanced schedule (Section 3.2,
  * Algorithm 2): exact combination of two partial results for the same query rows,
  *   lse = log(e^lse_a + e^lse_b),  o = e^(lse_a-lse) o_a + e^(lse_b-lse) o_b,
@@ -115,6 +132,17 @@ typedef struct {
 
 int dfa_merge(const dfa_merge_desc* md, void* o_a, float* lse_a,
               const void* o_b, const float* lse_b, void* stream);
+
+/* dfa_merge_batch - n_pairs merges of one shape and one set of strides at once; the operands of the
+ * pairs must not overlap.  `pairs` is a HOST array, read before the call returns. */
+typedef struct {
+  void* o_a;
+  float* lse_a;
+  const void* o_b;
+  const float* lse_b;
+} dfa_merge_pair;
+
+int dfa_merge_batch(const dfa_merge_desc* md, const dfa_merge_pair* pairs, int32_t n_pairs, void* stream);
 
 /*
  * dfa_delta - D_i = sum_c dO_ic * O_ic for every query row, from the FINAL merged

@@ -8,10 +8,13 @@ from .binding import (  # noqa: F401
     DfaError,
     Step,
     dfa_chunk_bwd,
+    dfa_chunk_bwd_batch,
     dfa_chunk_fwd,
     dfa_chunk_fwd_acc,
+    dfa_chunk_fwd_batch,
     dfa_delta,
     dfa_merge,
+    dfa_merge_batch,
     dfa_mfma_probe,
     dfa_mfma_probe_data,
     dfa_schedule,

@@ -65,13 +65,10 @@ def _backward(q, k, v, o, lse, d_o, scale, P):
     h_q, n, d = q.shape
     c = n // P
     d_o = d_o.to(q.dtype).contiguous()
-    bufs = driver.Buffers(h_q, k.shape[0], n, d, P, q.device, grads=True, outputs=False)
+    bufs = driver.Buffers(h_q, k.shape[0], n, d, P, q.device, grads=True, outputs=False, zero_grads=n % P != 0)
     bufs.O, bufs.L = o, lse
-    for w in range(P):
-        B.dfa_delta(o[:, w * c:(w + 1) * c], d_o[:, w * c:(w + 1) * c], delta=bufs.delta[:, w * c:(w + 1) * c])
-    touched = driver.new_pass()
-    for w in range(P):
-        driver.backward_worker(q, k, v, d_o, scale, P, w, bufs, with_delta=False, touched=touched)
+    B.dfa_delta(o[:, :c * P], d_o[:, :c * P], delta=bufs.delta[:, :c * P])
+    driver.backward_all_workers(q, k, v, d_o, scale, P, bufs)
     if keep_fp32_grads:
         last_fp32_grads = (bufs.dQ, bufs.dK, bufs.dV)
     return bufs.dQ.to(q.dtype), bufs.dK.to(k.dtype), bufs.dV.to(v.dtype)

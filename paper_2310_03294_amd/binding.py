@@ -44,6 +44,16 @@ class DfaMergeDesc(ctypes.Structure):
                 ("b_stride_h", ctypes.c_int64), ("b_stride_s", ctypes.c_int64), ("lse_b_stride_h", ctypes.c_int64)]
 
 
+class DfaFwdPair(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("q", "k", "v", "o", "lse")] + [
+        (n, ctypes.c_int64) for n in ("o_stride_h", "o_stride_s", "lse_stride_h")] + [
+        ("accumulate", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+
+
+class DfaMergePair(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("o_a", "lse_a", "o_b", "lse_b")]
+
+
 class DfaBwdPair(ctypes.Structure):
     _fields_ = [(n, ctypes.c_void_p) for n in ("q", "k", "v", "lse", "delta", "dO", "dq", "dk", "dv")] + [
         ("accumulate_dq", ctypes.c_int32), ("accumulate_dkv", ctypes.c_int32)]
@@ -56,7 +66,8 @@ class DfaStep(ctypes.Structure):
 
 Step = collections.namedtuple("Step", "t kind q_chunk kv_chunk send_to recv_from")
 
-EXPORTS = ("dfa_chunk_fwd", "dfa_chunk_fwd_acc", "dfa_merge", "dfa_delta", "dfa_chunk_bwd",
+EXPORTS = ("dfa_chunk_fwd", "dfa_chunk_fwd_acc", "dfa_chunk_fwd_batch", "dfa_merge", "dfa_merge_batch", "dfa_delta",
+           "dfa_chunk_bwd",
            "dfa_chunk_bwd_batch", "dfa_chunk_bwd_workspace", "dfa_schedule", "dfa_schedule_mode", "dfa_schedule_window", "dfa_mfma_probe", "dfa_mfma_probe_data", "dfa_status_str",
            "dfa_version")
 
@@ -82,6 +93,8 @@ def load_library():
     lib.dfa_merge.argtypes = [ctypes.POINTER(DfaMergeDesc), vp, vp, vp, vp, vp]
     lib.dfa_delta.argtypes = [shp, vp, vp, vp, vp]
     lib.dfa_chunk_bwd.argtypes = [shp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_int, vp]
+    lib.dfa_chunk_fwd_batch.argtypes = [shp, ctypes.POINTER(DfaFwdPair), i32, vp]
+    lib.dfa_merge_batch.argtypes = [ctypes.POINTER(DfaMergeDesc), ctypes.POINTER(DfaMergePair), i32, vp]
     lib.dfa_chunk_bwd_batch.argtypes = [shp, ctypes.POINTER(DfaBwdPair), i32, vp, i64, vp]
     lib.dfa_schedule.argtypes = [i32, i32, ctypes.POINTER(DfaStep), i32]
     lib.dfa_schedule_mode.argtypes = [i32, i32, i32, ctypes.POINTER(DfaStep), i32]
@@ -268,6 +281,89 @@ def dfa_chunk_bwd(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale, accumulate
     ws, n = _workspace(lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), 1, dq is not None, dk is not None), stream)
     _check(lib.dfa_chunk_bwd_batch(ctypes.byref(sh), ctypes.byref(pair), 1, _ptr(ws), n, _stream(stream)), "dfa_chunk_bwd")
     return dq, dk, dv
+
+
+class _Chunks:
+    """Addresses of the chunks (`rows` sequence positions each) of a [heads, seq, ...] tensor."""
+
+    def __init__(self, t, rows):
+        self.base, self.step = t.data_ptr(), rows * t.stride(1) * t.element_size()
+        self.n = t.shape[1] // rows if rows else 1 << 30
+
+    def __getitem__(self, i):
+        if not 0 <= i < self.n:
+            raise IndexError(f"chunk {i} of {self.n}")
+        return self.base + i * self.step
+
+
+def dfa_chunk_fwd_batch(q, k, v, rows, pairs, causal, scale, stream=None):
+    """The chunk pairs of one time step as one launch.  q, k, v: whole sequences, divided in chunks of `rows`.
+    pairs: (q_chunk, kv_chunk, o, lse, chunk, accumulate), where the result goes to chunk number `chunk` of the
+    [heads, seq, d] tensor o and of lse; accumulate: continues from the state there.  No output may overlap
+    another pair's."""
+    if not pairs:
+        return
+    lib = load_library()
+    if v.shape != k.shape or v.stride() != k.stride():
+        raise ValueError("k and v must share shape and strides")
+    sh = _make_shape(q, k, causal, scale, _dt(q), o=pairs[0][2], o_dtype=_dt(pairs[0][2]))
+    sh.s_q = sh.s_k = rows
+    cq, ck, cv = _Chunks(q, rows), _Chunks(k, rows), _Chunks(v, rows)
+    arr, dest = (DfaFwdPair * len(pairs))(), {}
+    for a, (qc, kc, o, lse, c, acc) in zip(arr, pairs):
+        d = dest.get(id(o))
+        if d is None:
+            if o.dtype != pairs[0][2].dtype or lse.stride(1) != 1:
+                raise ValueError("outputs share a dtype, lse has unit innermost stride")
+            d = dest[id(o)] = (_Chunks(o, rows), _Chunks(lse, rows), (*_hsd(o, "o"), lse.stride(0)))
+        a.q, a.k, a.v, a.o, a.lse = cq[qc], ck[kc], cv[kc], d[0][c], d[1][c]
+        a.o_stride_h, a.o_stride_s, a.lse_stride_h = d[2]
+        a.accumulate = bool(acc)
+    _check(lib.dfa_chunk_fwd_batch(ctypes.byref(sh), arr, len(pairs), _stream(stream)), "dfa_chunk_fwd_batch")
+
+
+def dfa_merge_batch(o, lse, rows, parts, stream=None):
+    """In place: chunk c of (o, lse) <- merge(chunk c, (o_b, lse_b)) for every (c, o_b, lse_b) of parts, as one
+    launch; the partials share their strides."""
+    if not parts:
+        return
+    lib = load_library()
+    md = DfaMergeDesc()
+    md.heads, md.rows, md.d, md.o_dtype = o.shape[0], rows, o.shape[2], _dt(o)
+    md.a_stride_h, md.a_stride_s = _hsd(o, "o")
+    md.b_stride_h, md.b_stride_s = _hsd(parts[0][1], "o_b")
+    md.lse_a_stride_h, md.lse_b_stride_h = lse.stride(0), parts[0][2].stride(0)
+    co, cl = _Chunks(o, rows), _Chunks(lse, rows)
+    arr = (DfaMergePair * len(parts))()
+    for a, (c, ob, lb) in zip(arr, parts):
+        if (ob.shape != (o.shape[0], rows, o.shape[2]) or ob.dtype != o.dtype or ob.stride() != parts[0][1].stride()
+                or lb.shape != (o.shape[0], rows) or lb.stride() != parts[0][2].stride()):
+            raise ValueError("merge operands must match")
+        a.o_a, a.lse_a, a.o_b, a.lse_b = co[c], cl[c], ob.data_ptr(), lb.data_ptr()
+    if lse.stride(1) != 1 or parts[0][2].stride(1) != 1:
+        raise ValueError("lse must have unit innermost stride")
+    _check(lib.dfa_merge_batch(ctypes.byref(md), arr, len(parts), _stream(stream)), "dfa_merge_batch")
+
+
+def dfa_chunk_bwd_batch(q, k, v, lse, delta, dO, dq, dk, dv, rows, pairs, causal, scale, stream=None):
+    """Gradient contributions of several chunk pairs as one launch.  Tensors: whole sequences, divided in chunks
+    of `rows`.  pairs: (q_chunk, kv_chunk, accumulate_dq, accumulate_dkv); no query chunk and no key/value chunk
+    occurs twice."""
+    if not pairs:
+        return
+    lib = load_library()
+    sh = _bwd_shape(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale)
+    sh.s_q = sh.s_k = rows
+    by_q = [_Chunks(t, rows) for t in (q, lse, delta, dO, dq)]
+    by_kv = [_Chunks(t, rows) for t in (k, v, dk, dv)]
+    arr = (DfaBwdPair * len(pairs))()
+    for a, (qc, kc, acc_q, acc_kv) in zip(arr, pairs):
+        a.q, a.lse, a.delta, a.dO, a.dq = (t[qc] for t in by_q)
+        a.k, a.v, a.dk, a.dv = (t[kc] for t in by_kv)
+        a.accumulate_dq, a.accumulate_dkv = bool(acc_q), bool(acc_kv)
+    ws, n = _workspace(lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), len(pairs), 1, 1), stream)
+    _check(lib.dfa_chunk_bwd_batch(ctypes.byref(sh), arr, len(pairs), _ptr(ws), n, _stream(stream)),
+           "dfa_chunk_bwd_batch")
 
 
 def dfa_mfma_probe(out, iters: int, stream=None) -> float:

@@ -51,26 +51,45 @@ extern "C" const char* dfa_status_str(int s) {
 
 extern "C" int dfa_version(void) { return 100; }
 
+extern "C" int dfa_chunk_fwd_batch(const dfa_shape* sh, const dfa_fwd_pair* pairs, int32_t n_pairs, void* stream) {
+  int rc = check_common(sh);
+  if (rc != DFA_OK) return rc;
+  if (n_pairs < 0) return DFA_ERR_ARG;
+  if (n_pairs == 0) return DFA_OK;
+  if (!pairs) return DFA_ERR_NULL;
+  const bool have_kv = sh->s_k > 0;   // an empty key/value chunk may come with NULL k, v
+  for (int i = 0; i < n_pairs; ++i) {
+    const dfa_fwd_pair& p = pairs[i];
+    if (!p.q || !p.o || !p.lse || (have_kv && (!p.k || !p.v))) return DFA_ERR_NULL;
+    if (!aligned16(p.q) || !aligned16(p.o) || (have_kv && (!aligned16(p.k) || !aligned16(p.v)))) return DFA_ERR_SHAPE;
+    if (!stride_ok(p.o_stride_h, p.o_stride_s, sh->d, sh->s_q) || !row_stride_ok(p.lse_stride_h, sh->s_q))
+      return DFA_ERR_SHAPE;
+  }
+  if (!stride_ok(sh->q_stride_h, sh->q_stride_s, sh->d, sh->s_q) ||
+      !stride_ok(sh->kv_stride_h, sh->kv_stride_s, sh->d, sh->s_k))
+    return DFA_ERR_SHAPE;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (sh->s_q == 0) return DFA_OK;
+  if (sh->s_k == 0) {
+    for (int i = 0; i < n_pairs; ++i) {
+      if (pairs[i].accumulate) continue;
+      dfa_shape one = *sh;
+      one.o_stride_h = pairs[i].o_stride_h; one.o_stride_s = pairs[i].o_stride_s;
+      one.lse_stride_h = pairs[i].lse_stride_h;
+      rc = dfa::launch_fill_empty_fwd(one, pairs[i].o, pairs[i].lse, st);
+      if (rc) return rc;
+    }
+    return DFA_OK;
+  }
+  return sh->dtype == DFA_F32 ? dfa::launch_fwd_f32(*sh, pairs, n_pairs, st) : dfa::launch_fwd_bf16(*sh, pairs, n_pairs, st);
+}
+
 namespace {
 int chunk_fwd(const dfa_shape* sh, const void* q, const void* k, const void* v,
               void* o, float* lse, int accumulate, void* stream) {
-  int rc = check_common(sh);
-  if (rc != DFA_OK) return rc;
-  const bool have_kv = sh->s_k > 0;   // an empty key/value chunk may come with NULL k, v
-  if (!q || !o || !lse || (have_kv && (!k || !v))) return DFA_ERR_NULL;
-  if (!aligned16(q) || !aligned16(o) || (have_kv && (!aligned16(k) || !aligned16(v)))) return DFA_ERR_SHAPE;
-  if (!stride_ok(sh->q_stride_h, sh->q_stride_s, sh->d, sh->s_q) ||
-      !stride_ok(sh->kv_stride_h, sh->kv_stride_s, sh->d, sh->s_k) ||
-      !stride_ok(sh->o_stride_h, sh->o_stride_s, sh->d, sh->s_q))
-    return DFA_ERR_SHAPE;
-  if (!row_stride_ok(sh->lse_stride_h, sh->s_q)) return DFA_ERR_SHAPE;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  if (sh->s_q == 0) return DFA_OK;
-  if (sh->s_k == 0) return accumulate ? DFA_OK : dfa::launch_fill_empty_fwd(*sh, o, lse, st);
-  if (sh->dtype == DFA_F32)
-    return dfa::launch_fwd_f32(*sh, static_cast<const float*>(q), static_cast<const float*>(k),
-                               static_cast<const float*>(v), o, lse, accumulate, st);
-  return dfa::launch_fwd_bf16(*sh, q, k, v, o, lse, accumulate, st);
+  if (!sh) return DFA_ERR_NULL;
+  const dfa_fwd_pair p{q, k, v, o, lse, sh->o_stride_h, sh->o_stride_s, sh->lse_stride_h, accumulate, 0};
+  return dfa_chunk_fwd_batch(sh, &p, 1, stream);
 }
 }  // namespace
 
@@ -84,21 +103,32 @@ extern "C" int dfa_chunk_fwd_acc(const dfa_shape* sh, const void* q, const void*
   return chunk_fwd(sh, q, k, v, o, lse, 1, stream);
 }
 
-extern "C" int dfa_merge(const dfa_merge_desc* md, void* o_a, float* lse_a,
-                         const void* o_b, const float* lse_b, void* stream) {
+extern "C" int dfa_merge_batch(const dfa_merge_desc* md, const dfa_merge_pair* pairs, int32_t n_pairs, void* stream) {
   if (!md) return DFA_ERR_NULL;
   if (md->heads < 0 || md->rows < 0 || md->heads > 65535) return DFA_ERR_SHAPE;
   if (md->d != 64 && md->d != 128) return DFA_ERR_SHAPE;
   if (md->o_dtype != DFA_BF16 && md->o_dtype != DFA_F32) return DFA_ERR_DTYPE;
-  if (!o_a || !lse_a || !o_b || !lse_b) return DFA_ERR_NULL;
-  if (!aligned16(o_a) || !aligned16(o_b)) return DFA_ERR_SHAPE;
+  if (n_pairs < 0) return DFA_ERR_ARG;
+  if (n_pairs > 0 && !pairs) return DFA_ERR_NULL;
+  for (int i = 0; i < n_pairs; ++i) {
+    const dfa_merge_pair& p = pairs[i];
+    if (!p.o_a || !p.lse_a || !p.o_b || !p.lse_b) return DFA_ERR_NULL;
+    if (!aligned16(p.o_a) || !aligned16(p.o_b)) return DFA_ERR_SHAPE;
+  }
   if (!stride_ok(md->a_stride_h, md->a_stride_s, md->d, md->rows) ||
       !stride_ok(md->b_stride_h, md->b_stride_s, md->d, md->rows))
     return DFA_ERR_SHAPE;
   if (!row_stride_ok(md->lse_a_stride_h, md->rows) || !row_stride_ok(md->lse_b_stride_h, md->rows)) return DFA_ERR_SHAPE;
-  if (o_a == o_b || lse_a == lse_b) return DFA_ERR_ARG;
-  if (md->rows == 0 || md->heads == 0) return DFA_OK;
-  return dfa::launch_merge(*md, o_a, lse_a, o_b, lse_b, static_cast<hipStream_t>(stream));
+  for (int i = 0; i < n_pairs; ++i)
+    if (pairs[i].o_a == pairs[i].o_b || pairs[i].lse_a == pairs[i].lse_b) return DFA_ERR_ARG;
+  if (md->rows == 0 || md->heads == 0 || n_pairs == 0) return DFA_OK;
+  return dfa::launch_merge(*md, pairs, n_pairs, static_cast<hipStream_t>(stream));
+}
+
+extern "C" int dfa_merge(const dfa_merge_desc* md, void* o_a, float* lse_a,
+                         const void* o_b, const float* lse_b, void* stream) {
+  const dfa_merge_pair p{o_a, lse_a, o_b, lse_b};
+  return dfa_merge_batch(md, &p, 1, stream);
 }
 
 extern "C" int dfa_delta(const dfa_shape* sh, const void* o, const void* dO, float* delta, void* stream) {

@@ -48,12 +48,31 @@ struct F32Params {
   void* o; float* lse;
   int s_q, s_k, h_q, h_kv, group, causal, o_bf16, accumulate;
   int nx_kv, n_kv;             // dk/dv: row blocks per key/value head, workgroups of a pair
-  int nx_q, n_q;               // forward, dq: row blocks per query head; dq: workgroups of a pair
+  int nx_q, n_q;               // forward, dq: row blocks per query head, workgroups of a pair
   int pairs;
   float scale;
   int64_t q_sh, q_ss, kv_sh, kv_ss, o_sh, o_ss, l_sh, dq_sh, dq_ss, dkv_sh, dkv_ss;
 };
 struct F32BwdParams : F32Params { Pair pair[MAX_PAIRS]; };
+
+struct FwdPair {
+  const float *q, *k, *v;
+  void* o; float* lse;
+  int accumulate;
+  int64_t o_sh, o_ss, l_sh;
+};
+struct F32FwdBatch : F32Params { FwdPair fpair[MAX_PAIRS]; };
+
+// The operands of an item's pair; item becomes its number within the pair.
+__device__ __forceinline__ const F32Params& pair_of(const F32Params& a, int&) { return a; }
+__device__ __forceinline__ F32Params pair_of(const F32FwdBatch& a, int& item) {
+  F32Params p = a;
+  const FwdPair& x = a.fpair[item / a.n_q];
+  item %= a.n_q;
+  p.q = x.q; p.k = x.k; p.v = x.v; p.o = x.o; p.lse = x.lse; p.accumulate = x.accumulate;
+  p.o_sh = x.o_sh; p.o_ss = x.o_ss; p.l_sh = x.l_sh;
+  return p;
+}
 
 template <int NB> struct Run;      // NB consecutive floats
 template <> struct Run<4> { typedef f32x4 type; };
@@ -190,8 +209,8 @@ constexpr size_t smem_bytes() { return sizeof(float) * (2 * ROWS * (D + 4) + 2 *
 
 // Forward.  Online softmax as in the pseudo-code of Appendix A (running row maximum m and row sum l,
 // old terms multiplied by exp(m_old - m_new)); a lane holds the scores of ONE query.
-template <int D, int NS>
-__global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(F32Params p) {
+template <int D, int NS, class Args>
+__global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(Args a) {
   constexpr int NR = 4 / NS, NB = D / 32, LD = D + 4, BK = kTile<NS>;
   typedef typename Run<NB>::type run_t;
   extern __shared__ __align__(16) float smem[];
@@ -199,8 +218,10 @@ __global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(F32Params p) {
   float* Vs = Ks + BK * LD;
   const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rb = wave % NR, part = wave / NR;
-  const int h = blockIdx.x / p.nx_q, kh = h / p.group;
-  int xq = blockIdx.x % p.nx_q;
+  int item = blockIdx.x;
+  const F32Params& p = pair_of(a, item);
+  const int h = item / p.nx_q, kh = h / p.group;
+  int xq = item % p.nx_q;
   if (p.causal) xq = p.nx_q - 1 - xq;       // longest rows first
   const int q0 = xq * NR * 32, q0w = q0 + rb * 32, qrow = q0w + r32;
   const bool qvalid = qrow < p.s_q;
@@ -523,14 +544,31 @@ int launch(const P& p, int64_t blocks, size_t smem, hipStream_t st) {
 
 int64_t blocks_of(int rows, int per) { return (static_cast<int64_t>(rows) + per - 1) / per; }
 
-template <int D, int NS>
-int fwd(F32Params p, hipStream_t st) {
+template <int D, int NS, class Args>
+int fwd(Args& p, hipStream_t st) {
   const int rows = 32 * (4 / NS);
   // tiles; the combination of the parts takes 4 results and 256 floats of row statistics
   const size_t comb = NS > 1 ? sizeof(float) * (4 * (D / 32) * 16 * 64 + 256) : 0;
   const size_t tiles = smem_bytes<D, kTile<NS>>();
   p.nx_q = static_cast<int>(blocks_of(p.s_q, rows));
-  return launch<F32Params, k_fwd_f32<D, NS>>(p, static_cast<int64_t>(p.nx_q) * p.h_q, tiles > comb ? tiles : comb, st);
+  const int64_t n_q = static_cast<int64_t>(p.nx_q) * p.h_q;
+  if (n_q * p.pairs > (1 << 30)) return DFA_ERR_SHAPE;
+  p.n_q = static_cast<int>(n_q);
+  return launch<Args, k_fwd_f32<D, NS, Args>>(p, n_q * p.pairs, tiles > comb ? tiles : comb, st);
+}
+
+template <class Args>
+int fwd_form(Args& p, const dfa_shape& sh, hipStream_t st) {
+  // Parts per tile.  A workgroup with more parts is done sooner, but stages every tile for fewer rows and
+  // runs fewer wavefronts per SIMD.  us per full pair, d = 128, with 1 / 2 / 4 parts:
+  //   8 heads x 256 rows 47 / 29 / 22, 32 x 256 49 / 31 / 28, 8 x 1024 174 / 103 / 71 (<= 256 workgroups of
+  //   4 parts: one round),  32 x 1024 190 / 183 / 271,  32 x 4096 2361 / 2501 / 3920 (116 TFLOP/s with 1);
+  //   causal, 32 x 4096: 2322 / 2043 / 2579 (64-row blocks share out the diagonal better than 128-row ones).
+  // The vector-FMA kernel this one replaced took 610 us at 8 x 1024.
+  const int64_t wg2 = blocks_of(sh.s_q, 64) * sh.h_q * p.pairs, wg4 = blocks_of(sh.s_q, 32) * sh.h_q * p.pairs;
+  const int parts = wg4 <= 256 ? 4 : wg2 <= 512 || sh.causal ? 2 : 1;
+  if (sh.d == 128) return parts == 4 ? fwd<128, 4, Args>(p, st) : parts == 2 ? fwd<128, 2, Args>(p, st) : fwd<128, 1, Args>(p, st);
+  return parts == 4 ? fwd<64, 4, Args>(p, st) : parts == 2 ? fwd<64, 2, Args>(p, st) : fwd<64, 1, Args>(p, st);
 }
 
 template <int D, int NS>
@@ -550,20 +588,25 @@ int bwd(F32BwdParams p, hipStream_t st) {
 
 }  // namespace
 
-int launch_fwd_f32(const dfa_shape& sh, const float* q, const float* k, const float* v,
-                   void* o, float* lse, int accumulate, hipStream_t st) {
-  F32Params p = make_params(sh);
-  p.q = q; p.k = k; p.v = v; p.o = o; p.lse = lse; p.accumulate = accumulate;
-  // Parts per tile.  A workgroup with more parts is done sooner, but stages every tile for fewer rows and
-  // runs fewer wavefronts per SIMD.  us per full pair, d = 128, with 1 / 2 / 4 parts:
-  //   8 heads x 256 rows 47 / 29 / 22, 32 x 256 49 / 31 / 28, 8 x 1024 174 / 103 / 71 (<= 256 workgroups of
-  //   4 parts: one round),  32 x 1024 190 / 183 / 271,  32 x 4096 2361 / 2501 / 3920 (116 TFLOP/s with 1);
-  //   causal, 32 x 4096: 2322 / 2043 / 2579 (64-row blocks share out the diagonal better than 128-row ones).
-  // The vector-FMA kernel this one replaced took 610 us at 8 x 1024.
-  const int64_t wg2 = blocks_of(sh.s_q, 64) * sh.h_q, wg4 = blocks_of(sh.s_q, 32) * sh.h_q;
-  const int parts = wg4 <= 256 ? 4 : wg2 <= 512 || sh.causal ? 2 : 1;
-  if (sh.d == 128) return parts == 4 ? fwd<128, 4>(p, st) : parts == 2 ? fwd<128, 2>(p, st) : fwd<128, 1>(p, st);
-  return parts == 4 ? fwd<64, 4>(p, st) : parts == 2 ? fwd<64, 2>(p, st) : fwd<64, 1>(p, st);
+int launch_fwd_f32(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st) {
+  for (; n > MAX_PAIRS; pairs += MAX_PAIRS, n -= MAX_PAIRS) {
+    const int rc = launch_fwd_f32(sh, pairs, MAX_PAIRS, st);
+    if (rc) return rc;
+  }
+  auto operand = [](const void* x) { return static_cast<const float*>(x); };
+  F32FwdBatch p{};
+  static_cast<F32Params&>(p) = make_params(sh);
+  const dfa_fwd_pair& x = pairs[0];
+  p.q = operand(x.q); p.k = operand(x.k); p.v = operand(x.v); p.o = x.o; p.lse = x.lse; p.accumulate = x.accumulate;
+  p.o_sh = x.o_stride_h; p.o_ss = x.o_stride_s; p.l_sh = x.lse_stride_h;
+  p.pairs = n;
+  if (n == 1) return fwd_form<F32Params>(p, sh, st);
+  for (int i = 0; i < n; ++i) {
+    const dfa_fwd_pair& y = pairs[i];
+    p.fpair[i] = FwdPair{operand(y.q), operand(y.k), operand(y.v), y.o, y.lse, y.accumulate, y.o_stride_h, y.o_stride_s,
+                         y.lse_stride_h};
+  }
+  return fwd_form<F32FwdBatch>(p, sh, st);
 }
 
 int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, hipStream_t st) {

@@ -42,10 +42,17 @@ __device__ inline void store8(void* base, int64_t elem_off, const Vec8& r) {
   }
 }
 
+constexpr int MAX_PAIRS = 16;          // per launch (blockIdx.z): the pairs travel in the kernel arguments
+template <int NP> struct MergePairs { dfa_merge_pair pair[NP]; };
+
 // (o_a, lse_a) <- merge((o_a, lse_a), (o_b, lse_b)), Section 3.2 rescale(.)
-template <int D, bool BF16>
-__global__ void __launch_bounds__(256) k_merge(dfa_merge_desc md, void* __restrict__ o_a, float* __restrict__ lse_a,
-                                               const void* __restrict__ o_b, const float* __restrict__ lse_b) {
+template <int D, bool BF16, int NP>
+__global__ void __launch_bounds__(256) k_merge(dfa_merge_desc md, MergePairs<NP> pairs) {
+  const dfa_merge_pair& pr = pairs.pair[NP == 1 ? 0 : blockIdx.z];
+  void* __restrict__ o_a = pr.o_a;
+  float* __restrict__ lse_a = pr.lse_a;
+  const void* __restrict__ o_b = pr.o_b;
+  const float* __restrict__ lse_b = pr.lse_b;
   constexpr int LPR = D / 8;           // lanes per row
   constexpr int RPB = 256 / LPR;       // rows per block iteration
   const int lane = threadIdx.x % LPR;
@@ -129,20 +136,27 @@ int grid_for(int64_t items, int per_block) {
 
 }  // namespace
 
-int launch_merge(const dfa_merge_desc& md, void* o_a, float* lse_a, const void* o_b, const float* lse_b,
-                 hipStream_t st) {
+template <int D, bool BF16>
+static void merge_form(dim3 grid, const dfa_merge_desc& md, const MergePairs<MAX_PAIRS>& all, hipStream_t st) {
+  if (grid.z > 1) k_merge<D, BF16, MAX_PAIRS><<<grid, 256, 0, st>>>(md, all);
+  else k_merge<D, BF16, 1><<<grid, 256, 0, st>>>(md, MergePairs<1>{{all.pair[0]}});
+}
+
+int launch_merge(const dfa_merge_desc& md, const dfa_merge_pair* pairs, int n, hipStream_t st) {
+  for (; n > MAX_PAIRS; pairs += MAX_PAIRS, n -= MAX_PAIRS) {
+    const int rc = launch_merge(md, pairs, MAX_PAIRS, st);
+    if (rc) return rc;
+  }
+  MergePairs<MAX_PAIRS> all{};
+  for (int i = 0; i < n; ++i) all.pair[i] = pairs[i];
   const int rpb = 256 / (md.d / 8);
   int gx = (md.rows + rpb - 1) / rpb;
   const int cap = (256 * 16 + md.heads - 1) / md.heads;   // a few blocks per CU in total; rows are grid-strided
   if (gx > cap) gx = cap;
-  dim3 grid(gx < 1 ? 1 : gx, md.heads);
-  if (md.d == 128) {
-    if (md.o_dtype == DFA_BF16) k_merge<128, true><<<grid, 256, 0, st>>>(md, o_a, lse_a, o_b, lse_b);
-    else k_merge<128, false><<<grid, 256, 0, st>>>(md, o_a, lse_a, o_b, lse_b);
-  } else {
-    if (md.o_dtype == DFA_BF16) k_merge<64, true><<<grid, 256, 0, st>>>(md, o_a, lse_a, o_b, lse_b);
-    else k_merge<64, false><<<grid, 256, 0, st>>>(md, o_a, lse_a, o_b, lse_b);
-  }
+  const dim3 grid(gx < 1 ? 1 : gx, md.heads, n);
+  const bool b = md.o_dtype == DFA_BF16;
+  if (md.d == 128) b ? merge_form<128, true>(grid, md, all, st) : merge_form<128, false>(grid, md, all, st);
+  else b ? merge_form<64, true>(grid, md, all, st) : merge_form<64, false>(grid, md, all, st);
   return last_launch_status();
 }
 

@@ -35,6 +35,31 @@ struct FwdParams {
   int64_t q_sh, q_ss, kv_sh, kv_ss, o_sh, o_ss, l_sh;
 };
 
+// Several pairs of one shape in a launch; the operands above are then not used.
+struct Pair {
+  const __bf16 *q, *k, *v;
+  void* o; float* lse;
+  int accumulate;
+  int64_t o_sh, o_ss, l_sh;
+};
+constexpr int MAX_PAIRS = 16;       // per launch: the pairs travel in the kernel arguments
+struct FwdBatch : FwdParams {
+  int per_pair;                     // (head, query tile) items of a pair
+  Pair pair[MAX_PAIRS];
+};
+
+// The operands of an item's pair; item becomes its number within the pair.  (One pair alone is no list:
+// picking it costs every workgroup another round trip to the argument memory.)
+__device__ __forceinline__ const FwdParams& pair_of(const FwdParams& a, int&) { return a; }
+__device__ __forceinline__ FwdParams pair_of(const FwdBatch& a, int& item) {
+  FwdParams p = a;
+  const Pair& x = a.pair[item / a.per_pair];
+  item %= a.per_pair;
+  p.q = x.q; p.k = x.k; p.v = x.v; p.o = x.o; p.lse = x.lse; p.accumulate = x.accumulate;
+  p.o_sh = x.o_sh; p.o_ss = x.o_ss; p.l_sh = x.l_sh;
+  return p;
+}
+
 // O^T tile of one query row per lane, read from (the state of earlier chunks) and written to memory
 __device__ __forceinline__ void load_o(f32x16 (&o)[4], const FwdParams& p, int head, int qrow, int hh) {
   const int64_t obase = head * p.o_sh + static_cast<int64_t>(qrow) * p.o_ss;
@@ -74,15 +99,16 @@ __device__ __forceinline__ void store_o(const f32x16 (&o)[4], const FwdParams& p
 
 // CAUSAL: the diagonal pair.  Its row sums are taken over the fp32 weights; those of a full pair over the
 // bf16-rounded weights that multiply V, as in the other full-pair forms.
-template <bool FULL>
-__global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(FwdParams p) {
+template <bool FULL, class Args>
+__global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
   extern __shared__ __align__(16) char smem[];   // two (K tile, V tile) buffers
 
   // XCD-aware mapping: consecutive workgroup ids go round-robin over the 8 XCDs, so give every
   // XCD a contiguous range of (head, query tile) items; its workgroups then share K/V in its L2.
   const int bid = blockIdx.x;
-  const int item = (bid & 7) * p.per_xcd + (bid >> 3);
-  if (item >= p.total) return;
+  int item = (bid & 7) * a.per_xcd + (bid >> 3);
+  if (item >= a.total) return;
+  const FwdParams& p = pair_of(a, item);
   const int head = item / p.ntq;
   int tq = item % p.ntq;
   if (p.causal) tq = p.ntq - 1 - tq;      // longest rows first
@@ -340,13 +366,14 @@ constexpr int SMEM_BYTES = OFF_ST + AL_BYTES;
 
 // RAGGED: s_k is no multiple of the 64-row tile, so the last K/V tile has rows past the end.
 // CAUSAL: the diagonal pair; its row sums are taken over the fp32 weights, as in the other causal forms.
-template <bool RAGGED, bool CAUSAL>
-__global__ void __launch_bounds__(NT, 1) k_fwd_bf16(FwdParams p) {
+template <bool RAGGED, bool CAUSAL, class Args>
+__global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
   extern __shared__ __align__(16) char smem[];
 
   const int bid = blockIdx.x;
-  const int item = (bid & 7) * p.per_xcd + (bid >> 3);   // contiguous (head, query tile) range per XCD
-  if (item >= p.total) return;
+  int item = (bid & 7) * a.per_xcd + (bid >> 3);   // contiguous (head, query tile) range per XCD
+  if (item >= a.total) return;
+  const FwdParams& p = pair_of(a, item);
   const int head = item / p.ntq;
   int tq = item % p.ntq;
   if (CAUSAL) tq = p.ntq - 1 - tq;      // longest rows first
@@ -615,14 +642,15 @@ template <int NS> constexpr int kTilesBytes = 2 * (kKeys<NS> / BN) * TILE_BYTES;
 template <int NS> constexpr int kSmem = 2 * kTilesBytes<NS>;
 constexpr int RES_BYTES = 64 * 64 * 4;         // a wavefront's O^T, 64 registers per lane
 
-template <int NS, bool CAUSAL>
-__global__ void __launch_bounds__(RB * NS * 64, NS == 2 ? 2 : 1) k_fwd_bf16(FwdParams p) {
+template <int NS, bool CAUSAL, class Args>
+__global__ void __launch_bounds__(RB * NS * 64, NS == 2 ? 2 : 1) k_fwd_bf16(Args a) {
   constexpr int SUB = kKeys<NS> / BN;          // 64-row sub-tiles of a K (or V) tile
   extern __shared__ __align__(16) char smem[]; // two buffers of (SUB K sub-tiles, SUB V sub-tiles)
 
   const int bid = blockIdx.x;
-  const int item = (bid & 7) * p.per_xcd + (bid >> 3);   // contiguous (head, query tile) range per XCD
-  if (item >= p.total) return;
+  int item = (bid & 7) * a.per_xcd + (bid >> 3);   // contiguous (head, query tile) range per XCD
+  if (item >= a.total) return;
+  const FwdParams& p = pair_of(a, item);
   const int head = item / p.ntq;
   int tq = item % p.ntq;
   if (CAUSAL) tq = p.ntq - 1 - tq;           // longest rows first
@@ -819,8 +847,8 @@ __global__ void __launch_bounds__(RB * NS * 64, NS == 2 ? 2 : 1) k_fwd_bf16(FwdP
 }  // namespace split
 
 // > 64 KB of dynamic LDS needs the opt-in, once per kernel and process (thread-safe)
-template <void (*KERNEL)(FwdParams)>
-int launch(const FwdParams& p, int threads, int smem, hipStream_t st) {
+template <class Args, void (*KERNEL)(Args)>
+int launch(const Args& p, int threads, int smem, hipStream_t st) {
   static std::once_flag once;
   static int attr_rc = DFA_OK;
   std::call_once(once, [smem] {
@@ -832,20 +860,13 @@ int launch(const FwdParams& p, int threads, int smem, hipStream_t st) {
   return last_launch_status();
 }
 
-}  // namespace
-
-int launch_fwd_bf16(const dfa_shape& sh, const void* q, const void* k, const void* v,
-                    void* o, float* lse, int accumulate, hipStream_t st) {
-  FwdParams p{};
-  p.q = static_cast<const __bf16*>(q); p.k = static_cast<const __bf16*>(k); p.v = static_cast<const __bf16*>(v);
-  p.o = o; p.lse = lse;
-  p.s_q = sh.s_q; p.s_k = sh.s_k; p.h_q = sh.h_q; p.group = sh.h_q / sh.h_kv; p.causal = sh.causal;
-  p.o_bf16 = sh.o_dtype == DFA_BF16; p.scale = sh.scale; p.accumulate = accumulate;
-  p.q_sh = sh.q_stride_h; p.q_ss = sh.q_stride_s; p.kv_sh = sh.kv_stride_h; p.kv_ss = sh.kv_stride_s;
-  p.o_sh = sh.o_stride_h; p.o_ss = sh.o_stride_s; p.l_sh = sh.lse_stride_h;
+// n pairs of one shape (n > 1: in FwdBatch)
+template <class Args>
+int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
   auto grid = [&](int rows) {
     p.ntq = (sh.s_q + rows - 1) / rows;
-    p.total = p.ntq * sh.h_q;
+    p.total = p.ntq * sh.h_q * n;
+    if constexpr (std::is_same_v<Args, FwdBatch>) p.per_pair = p.ntq * sh.h_q;
     p.per_xcd = (p.total + 7) / 8;
   };
   // Which form.  us per call on one box, d = 128, 256-row / 128-row / 64-row NS = 2 / 64-row NS = 4 workgroups:
@@ -857,7 +878,7 @@ int launch_fwd_bf16(const dfa_shape& sh, const void* q, const void* k, const voi
   //                 x 16384 492 / 564 / 720 / 800
   //                 32 heads x 1024 31.5 / 26.4 / 27.1 / 30.9   x 4096 179 / 174 / 195 / 221
   //                 x 8192 515 / 563 / 715 / 791   x 16384 1950 / 2112 / 2748 / 2985
-  auto count = [&](int rows) { return (static_cast<int64_t>(sh.s_q) + rows - 1) / rows * sh.h_q; };
+  auto count = [&](int rows) { return (static_cast<int64_t>(sh.s_q) + rows - 1) / rows * sh.h_q * n; };
   const int64_t n256 = count(256), n128 = count(128), n64 = count(64);
   bool wide;          // 256 rows
   int parts = 0;      // 64 rows with this many parts
@@ -876,26 +897,50 @@ int launch_fwd_bf16(const dfa_shape& sh, const void* q, const void* k, const voi
     wide = n128 > 256 && !(n256 > 256 && n256 < 768 && last_round > 0 && last_round <= 128);
   }
   if (parts && sh.s_k <= 256) parts = 2;      // two 128-key tiles at most: the smaller tiles start sooner
-  if (sh.causal && n128 > (1 << 30)) return DFA_ERR_SHAPE;
+  if (n128 > (1 << 30) && (sh.causal || n > 1)) return DFA_ERR_SHAPE;
   if (parts) {
     grid(split::BMS);
-    if (parts == 2) return sh.causal ? launch<split::k_fwd_bf16<2, true>>(p, 256, split::kSmem<2>, st)
-                                     : launch<split::k_fwd_bf16<2, false>>(p, 256, split::kSmem<2>, st);
-    return sh.causal ? launch<split::k_fwd_bf16<4, true>>(p, 512, split::kSmem<4>, st)
-                     : launch<split::k_fwd_bf16<4, false>>(p, 512, split::kSmem<4>, st);
+    if (parts == 2) return sh.causal ? launch<Args, split::k_fwd_bf16<2, true, Args>>(p, 256, split::kSmem<2>, st)
+                                     : launch<Args, split::k_fwd_bf16<2, false, Args>>(p, 256, split::kSmem<2>, st);
+    return sh.causal ? launch<Args, split::k_fwd_bf16<4, true, Args>>(p, 512, split::kSmem<4>, st)
+                     : launch<Args, split::k_fwd_bf16<4, false, Args>>(p, 512, split::kSmem<4>, st);
   }
   if (!wide) {
     grid(BM);
-    return sh.causal ? launch<k_fwd_bf16<false>>(p, NTHREADS, 4 * TILE_BYTES, st)
-                     : launch<k_fwd_bf16<true>>(p, NTHREADS, 4 * TILE_BYTES, st);
+    return sh.causal ? launch<Args, k_fwd_bf16<false, Args>>(p, NTHREADS, 4 * TILE_BYTES, st)
+                     : launch<Args, k_fwd_bf16<true, Args>>(p, NTHREADS, 4 * TILE_BYTES, st);
   }
   grid(full_pair::BMW);
   constexpr int nt = full_pair::NT, smem = full_pair::SMEM_BYTES;
   const bool ragged = sh.s_k % BN != 0;
-  if (sh.causal) return ragged ? launch<full_pair::k_fwd_bf16<true, true>>(p, nt, smem, st)
-                               : launch<full_pair::k_fwd_bf16<false, true>>(p, nt, smem, st);
-  return ragged ? launch<full_pair::k_fwd_bf16<true, false>>(p, nt, smem, st)
-                : launch<full_pair::k_fwd_bf16<false, false>>(p, nt, smem, st);
+  if (sh.causal) return ragged ? launch<Args, full_pair::k_fwd_bf16<true, true, Args>>(p, nt, smem, st)
+                               : launch<Args, full_pair::k_fwd_bf16<false, true, Args>>(p, nt, smem, st);
+  return ragged ? launch<Args, full_pair::k_fwd_bf16<true, false, Args>>(p, nt, smem, st)
+                : launch<Args, full_pair::k_fwd_bf16<false, false, Args>>(p, nt, smem, st);
+}
+
+}  // namespace
+
+int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st) {
+  for (; n > MAX_PAIRS; pairs += MAX_PAIRS, n -= MAX_PAIRS) {
+    const int rc = launch_fwd_bf16(sh, pairs, MAX_PAIRS, st);
+    if (rc) return rc;
+  }
+  auto operand = [](const void* x) { return static_cast<const __bf16*>(x); };
+  FwdBatch p{};
+  const dfa_fwd_pair& x = pairs[0];
+  p.q = operand(x.q); p.k = operand(x.k); p.v = operand(x.v); p.o = x.o; p.lse = x.lse; p.accumulate = x.accumulate;
+  p.o_sh = x.o_stride_h; p.o_ss = x.o_stride_s; p.l_sh = x.lse_stride_h;
+  p.s_q = sh.s_q; p.s_k = sh.s_k; p.h_q = sh.h_q; p.group = sh.h_q / sh.h_kv; p.causal = sh.causal;
+  p.o_bf16 = sh.o_dtype == DFA_BF16; p.scale = sh.scale;
+  p.q_sh = sh.q_stride_h; p.q_ss = sh.q_stride_s; p.kv_sh = sh.kv_stride_h; p.kv_ss = sh.kv_stride_s;
+  if (n == 1) return launch_form<FwdParams>(p, sh, 1, st);
+  for (int i = 0; i < n; ++i) {
+    const dfa_fwd_pair& y = pairs[i];
+    p.pair[i] = Pair{operand(y.q), operand(y.k), operand(y.v), y.o, y.lse, y.accumulate, y.o_stride_h, y.o_stride_s,
+                     y.lse_stride_h};
+  }
+  return launch_form<FwdBatch>(p, sh, n, st);
 }
 
 }  // namespace dfa

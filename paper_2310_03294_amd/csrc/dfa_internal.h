@@ -9,22 +9,18 @@
 namespace dfa {
 
 // Launch wrappers: every one validates nothing (the ABI layer did) and returns a dfa_status.
-int launch_merge(const dfa_merge_desc& md, void* o_a, float* lse_a, const void* o_b, const float* lse_b,
-                 hipStream_t st);
+int launch_merge(const dfa_merge_desc& md, const dfa_merge_pair* pairs, int n, hipStream_t st);
 int launch_delta(const dfa_shape& sh, const void* o, const void* dO, float* delta, hipStream_t st);
 int launch_fill_zero_rows(float* p, int heads, int rows, int d, int64_t stride_h, int64_t stride_s,
                           hipStream_t st);
 int launch_fill_empty_fwd(const dfa_shape& sh, void* o, float* lse, hipStream_t st);
 
-// The pairs of a backward launch share the shape, select the same outputs and write disjoint ones.
+// The pairs of a launch share the shape and write disjoint outputs (backward: all select the same ones).
 // ws: scratch of bwd_bf16_workspace() bytes (0: none is used), or null; with less the work is divided into fewer parts.
-// accumulate != 0: (o, lse) hold the state of earlier key/value chunks on entry and are updated in place
-int launch_fwd_f32(const dfa_shape& sh, const float* q, const float* k, const float* v,
-                   void* o, float* lse, int accumulate, hipStream_t st);
+int launch_fwd_f32(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st);
 int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, hipStream_t st);
 
-int launch_fwd_bf16(const dfa_shape& sh, const void* q, const void* k, const void* v,
-                    void* o, float* lse, int accumulate, hipStream_t st);
+int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st);
 int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void* ws, int64_t ws_bytes,
                     hipStream_t st);
 int64_t bwd_bf16_workspace(const dfa_shape& sh, int n, bool dq, bool dk);

@@ -15,7 +15,8 @@ from . import binding as B
 class Buffers:
     """Device buffers for one run, allocated once so that timed regions allocate nothing."""
 
-    def __init__(self, h_q, h_kv, n, d, p, device, o_dtype=torch.float32, n_partials=1, grads=True, outputs=True):
+    def __init__(self, h_q, h_kv, n, d, p, device, o_dtype=torch.float32, n_partials=1, grads=True, outputs=True,
+                 zero_grads=True):
         c = n // p
         self.c, self.p = c, p
         if outputs:     # False: the caller supplies O and L (a backward from saved tensors)
@@ -25,9 +26,10 @@ class Buffers:
             self.part_l = [torch.empty((h_q, c), dtype=torch.float32, device=device) for _ in range(n_partials)]
         if grads:
             self.delta = torch.empty((h_q, n), dtype=torch.float32, device=device)
-            self.dQ = torch.zeros((h_q, n, d), dtype=torch.float32, device=device)
-            self.dK = torch.zeros((h_kv, n, d), dtype=torch.float32, device=device)
-            self.dV = torch.zeros((h_kv, n, d), dtype=torch.float32, device=device)
+            new = torch.zeros if zero_grads else torch.empty     # False: a whole pass overwrites every chunk
+            self.dQ = new((h_q, n, d), dtype=torch.float32, device=device)
+            self.dK = new((h_kv, n, d), dtype=torch.float32, device=device)
+            self.dV = new((h_kv, n, d), dtype=torch.float32, device=device)
 
 
 def _chunk(t, i, c):
@@ -166,40 +168,74 @@ def helper_partials_for(Q, K, V, scale, P, w, bufs: Buffers):
     return out
 
 
+def _partials(bufs: Buffers, n):
+    """n partial (o, lse) buffers; kept in bufs, so that a later pass allocates nothing."""
+    while len(bufs.part_o) < n:
+        bufs.part_o.append(torch.empty_like(bufs.part_o[0]))
+        bufs.part_l.append(torch.empty_like(bufs.part_l[0]))
+    return list(zip(bufs.part_o, bufs.part_l))[:n]
+
+
+def backward_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced"):
+    """The backward of all P workers' pairs on one device, from the merged O and L and the D of every chunk, time
+    step by time step: first the pairs of the owners, then those of the helpers.  Each of the two groups has
+    every query chunk and every key/value chunk at most once, so its pairs go out as one launch."""
+    scheds = [B.dfa_schedule(P, w, mode) for w in range(P)]
+    touched = new_pass()
+    for steps in zip(*scheds):
+        for kind in (B.DFA_STEP_DIAG, B.DFA_STEP_OWN, B.DFA_STEP_HELP):
+            pairs = [(st.q_chunk, st.kv_chunk, st.q_chunk in touched["dq"], st.kv_chunk in touched["dkv"])
+                     for st in steps if st.kind == kind]
+            assert len({p[0] for p in pairs}) == len({p[1] for p in pairs}) == len(pairs)
+            B.dfa_chunk_bwd_batch(Q, K, V, bufs.L, bufs.delta, dO, bufs.dQ, bufs.dK, bufs.dV, bufs.c, pairs,
+                                  kind == B.DFA_STEP_DIAG, scale)
+            touched["dq"].update(p[0] for p in pairs)
+            touched["dkv"].update(p[1] for p in pairs)
+
+
+def _forward_step(Q, K, V, scale, steps, bufs: Buffers):
+    """What all workers compute in one time step, as one launch: the owners' pairs continue from their states, the
+    helpers' give partials, which are then "sent" and merged."""
+    diag = [st for st in steps if st.kind == B.DFA_STEP_DIAG]
+    own = [st for st in steps if st.kind == B.DFA_STEP_OWN]
+    helped = [st for st in steps if st.kind == B.DFA_STEP_HELP]
+    B.dfa_chunk_fwd_batch(Q, K, V, bufs.c, [(st.q_chunk, st.kv_chunk, bufs.O, bufs.L, st.q_chunk, False)
+                                            for st in diag], True, scale)
+    parts = _partials(bufs, len(helped))
+    B.dfa_chunk_fwd_batch(Q, K, V, bufs.c, [(st.q_chunk, st.kv_chunk, bufs.O, bufs.L, st.q_chunk, True)
+                                            for st in own] +
+                          [(st.q_chunk, st.kv_chunk, po, pl, 0, False) for st, (po, pl) in zip(helped, parts)],
+                          False, scale)
+    B.dfa_merge_batch(bufs.O, bufs.L, bufs.c, [(st.send_to, po, pl) for st, (po, pl) in zip(helped, parts)])
+
+
 def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backward=True, fused=True):
     """The whole schedule of all P workers, time step by time step, on one GPU.
-    fused: OWN pairs continue from the owner's state (dfa_chunk_fwd_acc) instead of partial + merge."""
+    fused: OWN pairs continue from the owner's state (dfa_chunk_fwd_acc) instead of partial + merge, and the
+    pairs of a time step - independent of each other, on P devices they run at the same time - go out as one
+    launch: a pair of small chunks alone leaves most of one device idle."""
     c = bufs.c
     scheds = [B.dfa_schedule(P, w, mode) for w in range(P)]
     nsteps = len(scheds[0])
     for t in range(nsteps):
-        arrivals = []
-        for w in range(P):
-            st = scheds[w][t]
+        steps = [scheds[w][t] for w in range(P)]
+        for w, st in enumerate(steps):
+            assert st.kind != B.DFA_STEP_HELP or steps[st.send_to].recv_from == w
+        if fused:
+            _forward_step(Q, K, V, scale, steps, bufs)
+            continue
+        for w, st in enumerate(steps):      # partial + merge, pair by pair
             if st.kind == B.DFA_STEP_DIAG:
                 B.dfa_chunk_fwd(_chunk(Q, w, c), _chunk(K, w, c), _chunk(V, w, c), True, scale,
                                 o=_chunk(bufs.O, w, c), lse=_chunk(bufs.L, w, c))
-            elif st.kind == B.DFA_STEP_OWN and fused:
-                B.dfa_chunk_fwd_acc(_chunk(Q, w, c), _chunk(K, st.kv_chunk, c), _chunk(V, st.kv_chunk, c), False,
-                                    scale, _chunk(bufs.O, w, c), _chunk(bufs.L, w, c))
-            elif st.kind == B.DFA_STEP_OWN:
+            elif st.kind != B.DFA_STEP_IDLE:
                 po, pl = bufs.part_o[0], bufs.part_l[0]
-                B.dfa_chunk_fwd(_chunk(Q, w, c), _chunk(K, st.kv_chunk, c), _chunk(V, st.kv_chunk, c), False,
+                B.dfa_chunk_fwd(_chunk(Q, st.q_chunk, c), _chunk(K, st.kv_chunk, c), _chunk(V, st.kv_chunk, c), False,
                                 scale, o=po, lse=pl)
-                B.dfa_merge(_chunk(bufs.O, w, c), _chunk(bufs.L, w, c), po, pl)
-            elif st.kind == B.DFA_STEP_HELP:
-                po, pl = bufs.part_o[0], bufs.part_l[0]
-                B.dfa_chunk_fwd(_chunk(Q, st.q_chunk, c), _chunk(K, w, c), _chunk(V, w, c), False, scale,
-                                o=po, lse=pl)
-                # "send": the owner merges it in this same step
-                B.dfa_merge(_chunk(bufs.O, st.send_to, c), _chunk(bufs.L, st.send_to, c), po, pl)
-                arrivals.append((st.send_to, w))
-        for owner, helper in arrivals:
-            assert scheds[owner][t].recv_from == helper
+                # HELP: "send", the owner merges it in this same step
+                B.dfa_merge(_chunk(bufs.O, st.q_chunk, c), _chunk(bufs.L, st.q_chunk, c), po, pl)
     if backward:
         # a helper's backward needs D of the chunk it helped, so all D vectors come first
-        for w in range(P):
-            B.dfa_delta(_chunk(bufs.O, w, c), _chunk(dO, w, c), delta=_chunk(bufs.delta, w, c))
-        touched = new_pass()
-        for w in range(P):
-            backward_worker(Q, K, V, dO, scale, P, w, bufs, mode, with_delta=False, touched=touched)
+        n = P * c
+        B.dfa_delta(bufs.O[:, :n], dO[:, :n], delta=bufs.delta[:, :n])
+        backward_all_workers(Q, K, V, dO, scale, P, bufs, mode)

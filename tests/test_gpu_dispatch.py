@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2310_03294_amd as dfa
-from paper_2310_03294_amd import binding as B
+from paper_2310_03294_amd import binding as B, driver
 from gpu_util import TOL, case, dev, maxerr, np64
 from oracle import attention as A
 from test_gpu_parity_small import _run_pair
@@ -177,3 +177,29 @@ def test_bf16_backward_parts(shape):
                 assert maxerr(got[i], want[i] + (0.5 if acc else 0.0)) <= bound[i]
                 # the same products, summed in another order in fp32
                 assert (got[i] - alone[i]).abs().max().item() <= 1e-5 * max(1.0, abs(want[i]).max())
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 128)])
+@pytest.mark.parametrize("p,c", [(19, 24), (5, 70), (2, 130)])
+def test_schedule_in_batches(dtype, d, p, c):
+    """All workers' pairs of a time step in one launch: more pairs than one launch takes (19 diagonal chunks), ragged
+    chunks, operands that are slices with strides of their own; a second pass over the same buffers."""
+    h_q, h_kv, n = 4, 2, p * c
+    scale = d ** -0.5
+    q, k, v, do = case(9500 + n, h_q, h_kv, n, n, d, dtype)
+    O, L = A.attention_fwd(np64(q), np64(k), np64(v), scale)
+    want = A.attention_bwd(np64(q), np64(k), np64(v), np64(do), scale)
+
+    def inside(t):      # an interior slice of a larger tensor
+        big = torch.zeros(t.shape[0] + 1, t.shape[1] + 8, d + 8, dtype=t.dtype, device=dev())
+        s = big[:t.shape[0], 8:8 + t.shape[1], :d]
+        return s.copy_(t.to(dev()))
+
+    Q, K, V, dO = (inside(t) for t in (q, k, v, do))
+    bufs = driver.Buffers(h_q, h_kv, n, d, p, dev())
+    tol = TOL[dtype]
+    for _ in range(2):
+        driver.run_all_workers(Q, K, V, dO, scale, p, bufs)
+        assert maxerr(bufs.O, O) <= tol and maxerr(bufs.L, L) <= tol
+        for got, w in zip((bufs.dQ, bufs.dK, bufs.dV), want):
+            assert maxerr(got, w) <= tol * max(1.0, abs(w).max() / 4)
