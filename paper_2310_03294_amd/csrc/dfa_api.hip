@@ -185,15 +185,17 @@ extern "C" int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pair
     }
     return DFA_OK;
   }
-  return sh->dtype == DFA_F32 ? dfa::launch_bwd_f32(*sh, pairs, n_pairs, st) : dfa::launch_bwd_bf16(*sh, pairs, n_pairs, workspace, workspace_bytes, st);
+  return sh->dtype == DFA_F32 ? dfa::launch_bwd_f32(*sh, pairs, n_pairs, workspace, workspace_bytes, st)
+                              : dfa::launch_bwd_bf16(*sh, pairs, n_pairs, workspace, workspace_bytes, st);
 }
 
 extern "C" int64_t dfa_chunk_bwd_workspace(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int32_t want_dkv) {
   const int rc = check_common(sh);
   if (rc != DFA_OK) return rc;
   if (n_pairs < 0) return DFA_ERR_ARG;
-  if (n_pairs == 0 || sh->s_q == 0 || sh->s_k == 0 || sh->dtype == DFA_F32) return 0;
-  return dfa::bwd_bf16_workspace(*sh, n_pairs, want_dq != 0, want_dkv != 0);
+  if (n_pairs == 0 || sh->s_q == 0 || sh->s_k == 0) return 0;
+  return sh->dtype == DFA_F32 ? dfa::bwd_f32_workspace(*sh, n_pairs, want_dq != 0, want_dkv != 0)
+                              : dfa::bwd_bf16_workspace(*sh, n_pairs, want_dq != 0, want_dkv != 0);
 }
 
 extern "C" int dfa_chunk_bwd(const dfa_shape* sh, const void* q, const void* k, const void* v,

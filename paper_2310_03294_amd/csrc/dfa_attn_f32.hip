@@ -18,6 +18,7 @@
 // bank conflicts).  The four wavefronts of a workgroup are NR row blocks x NS = 4 / NR parts of every
 // tile; with NS > 1 the partial results of the parts are combined through LDS at the end.  NS = 4 is
 // for calls with few rows: it gives four times the workgroups, each with a quarter of the serial work.
+#include <algorithm>
 #include <mutex>
 
 #include "dfa_internal.h"
@@ -50,6 +51,9 @@ struct F32Params {
   int nx_kv, n_kv;             // dk/dv: row blocks per key/value head, workgroups of a pair
   int nx_q, n_q;               // forward, dq: row blocks per query head, workgroups of a pair
   int pairs;
+  XcdMap map_kv, map_q;        // workgroups of all pairs; the forward's are map_q
+  int shares;                  // dk, dv: workgroups that share the query tiles of a row block
+  float* partial;              // shares > 1: their sums, 2 D floats per key row
   float scale;
   int64_t q_sh, q_ss, kv_sh, kv_ss, o_sh, o_ss, l_sh, dq_sh, dq_ss, dkv_sh, dkv_ss;
 };
@@ -218,7 +222,8 @@ __global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(Args a) {
   float* Vs = Ks + BK * LD;
   const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rb = wave % NR, part = wave / NR;
-  int item = blockIdx.x;
+  int item = xcd_item(a.map_q, blockIdx.x);
+  if (item >= a.map_q.total) return;
   const F32Params& p = pair_of(a, item);
   const int h = item / p.nx_q, kh = h / p.group;
   int xq = item % p.nx_q;
@@ -345,8 +350,9 @@ __global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(Args a) {
 // V_LDS: at d = 128 with 128-row tiles K, V, dK, dV and the tile on its way are more registers than
 // there are; V (the same 32 rows for all four wavefronts) then stays in LDS.
 template <int D, int NS> constexpr bool kVLds = D == 128 && NS == 4;
-template <int D, int NS>
-__device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int item, float* smem) {
+// SHARED: p.shares workgroups share the query tiles of a row block.
+template <int D, int NS, bool SHARED>
+__device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int item, float* partial, float* smem) {
   constexpr int NR = 4 / NS, NB = D / 32, LD = D + 4, BQ = 32 * NS;
   constexpr bool V_LDS = kVLds<D, NS>;
   float* Qs = smem;
@@ -356,7 +362,8 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
   float* Vs = Ds + BQ;
   const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rb = wave % NR, part = wave / NR;
-  const int kh = item / p.nx_kv, k0 = (item % p.nx_kv) * NR * 32, k0w = k0 + rb * 32, kvrow = k0w + r32;
+  const int share = SHARED ? item / p.nx_kv % p.shares : 0, kh = SHARED ? item / p.nx_kv / p.shares : item / p.nx_kv;
+  const int k0 = (item % p.nx_kv) * NR * 32, k0w = k0 + rb * 32, kvrow = k0w + r32;
   const bool kvalid = kvrow < p.s_k;
   const int q_begin = p.causal ? k0 : 0;
 
@@ -372,6 +379,14 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
   };
   int hq = kh * p.group, q0 = q_begin;
   const int h_end = hq + p.group;
+  int left = 0;                              // SHARED: query tiles of this workgroup's share
+  if constexpr (SHARED) {
+    const int ntq = (p.s_q - q_begin + BQ - 1) / BQ;
+    const int64_t walk = static_cast<int64_t>(ntq) * p.group;
+    const int it0 = static_cast<int>(walk * share / p.shares);
+    left = static_cast<int>(walk * (share + 1) / p.shares) - it0;
+    if (left > 0) { hq += it0 / ntq; q0 += it0 % ntq * BQ; }       // (else a tile is loaded, and not used)
+  }
   load(hq, q0);
   f32x4 k[D / 8], v[V_LDS ? 1 : D / 8];
   load_rows<D>(k, pr.k + kh * p.kv_sh, p.kv_ss, kvrow, kvalid, hh);
@@ -388,7 +403,7 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
   f32x16 dk[NB], dv[NB];
   zero(dk);
   zero(dv);
-  for (bool first = true; hq < h_end; first = false) {
+  for (bool first = true; SHARED ? left > 0 : hq < h_end; first = false) {
     if (!first) __syncthreads();
     tile.store(Qs, Gs, q0, p.s_q);
     if (tid < 2 * BQ) Ls[tid] = ld;          // Ds follows Ls
@@ -396,7 +411,7 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
     const int q0t = q0 + part * 32;          // this wavefront's 32 rows of the tile
     q0 += BQ;
     if (q0 >= p.s_q) { q0 = q_begin; ++hq; }
-    if (hq < h_end) load(hq, q0);
+    if (SHARED ? --left > 0 : hq < h_end) load(hq, q0);
     if (q0t >= p.s_q || (p.causal && k0w > q0t + 31)) continue;
     const float* Qw = Qs + part * 32 * LD;
     const float* Gw = Gs + part * 32 * LD;
@@ -433,6 +448,19 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
       add_result<NB>(x, dk, lane, 1.f);
       add_result<NB>(x + NV * 64, dv, lane, 1.f);
     }
+  }
+  if constexpr (SHARED) {       // k_reduce_f32 adds the shares up
+    typedef typename Run<NB>::type run_t;
+    run_t* x = reinterpret_cast<run_t*>(partial) + rb * 2 * 16 * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      run_t a, b;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) { a[j] = dk[j][i]; b[j] = dv[j][i]; }
+      x[i * 64] = a;
+      x[(16 + i) * 64] = b;
+    }
+    return;
   }
   if (!kvalid) return;
   const int64_t off = kh * p.dkv_sh + static_cast<int64_t>(kvrow) * p.dkv_ss;
@@ -502,18 +530,55 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int i
 }
 
 // Backward: 7 products in two kinds of workgroups of ONE launch (dk/dv first, they are the longer
-// ones), each output written once: no atomics, no zero fill, a fixed order of summation.  The fused
+// ones), no atomics, no zero fill, a fixed order of summation.  The fused
 // form (5 products, dq added with fp32 atomics) left a short chunk with as few workgroups as it has key
 // tiles.
-template <int D, int NS>
+template <int D, int NS, bool SHARED>
 __global__ void __launch_bounds__(NT, 1) k_bwd_f32(F32BwdParams p) {
   extern __shared__ __align__(16) float smem[];
-  int item = blockIdx.x;
-  if (item < p.n_kv * p.pairs) {
-    bwd_dkdv<D, NS>(p, p.pair[item / p.n_kv], item % p.n_kv, smem);
+  const int grid_kv = p.map_kv.per_xcd * 8, bid = blockIdx.x;
+  if (bid < grid_kv) {
+    const int item = xcd_item(p.map_kv, bid);
+    if (item < p.map_kv.total)
+      bwd_dkdv<D, NS, SHARED>(p, p.pair[item / p.n_kv], item % p.n_kv,
+                              p.partial + static_cast<int64_t>(item) * (4 / NS * 64 * D), smem);
   } else {
-    item -= p.n_kv * p.pairs;
-    bwd_dq<D, NS>(p, p.pair[item / p.n_q], item % p.n_q, smem);
+    const int item = xcd_item(p.map_q, bid - grid_kv);
+    if (item < p.map_q.total) bwd_dq<D, NS>(p, p.pair[item / p.n_q], item % p.n_q, smem);
+  }
+}
+
+// dk, dv of a row block of NR * 32 key rows from the sums of its shares: grid (row blocks, 2 NR), 256 threads, each
+// four of a lane's sixteen runs.  The order of the sum is that of the shares.
+template <int D, int NR>
+__global__ void __launch_bounds__(NT) k_reduce_f32(F32BwdParams p) {
+  constexpr int NB = D / 32;
+  typedef typename Run<NB>::type run_t;
+  const int xk = blockIdx.x % p.nx_kv, pk = blockIdx.x / p.nx_kv;      // pk: pair * h_kv + kv head
+  const Pair& pr = p.pair[pk / p.h_kv];
+  const int rb = blockIdx.y >> 1, is_dv = blockIdx.y & 1, lane = threadIdx.x & 63, i0 = (threadIdx.x >> 6) * 4;
+  const int row = (xk * NR + rb) * 32 + (lane & 31);
+  if (row >= p.s_k) return;
+  const int64_t block = NR * 2 * 16 * 64, step = static_cast<int64_t>(p.nx_kv) * block;      // in runs
+  const run_t* src = reinterpret_cast<const run_t*>(p.partial) +
+                     (static_cast<int64_t>(pk) * p.shares * p.nx_kv + xk) * block + ((rb * 2 + is_dv) * 16 + i0) * 64 + lane;
+  run_t a[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = src[i * 64];
+  for (int s = 1; s < p.shares; ++s) {
+    src += step;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] += src[i * 64];
+  }
+  float* dst = (is_dv ? pr.dv : pr.dk) + (pk % p.h_kv) * p.dkv_sh + static_cast<int64_t>(row) * p.dkv_ss +
+               NB * (i0 * 2 + 4 * (lane >> 5));
+  const float f = is_dv ? 1.f : p.scale;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    run_t* d = reinterpret_cast<run_t*>(dst + NB * i);
+    run_t x = a[i] * f;
+    if (pr.acc_kv) x += *d;
+    *d = x;
   }
 }
 
@@ -554,7 +619,8 @@ int fwd(Args& p, hipStream_t st) {
   const int64_t n_q = static_cast<int64_t>(p.nx_q) * p.h_q;
   if (n_q * p.pairs > (1 << 30)) return DFA_ERR_SHAPE;
   p.n_q = static_cast<int>(n_q);
-  return launch<Args, k_fwd_f32<D, NS, Args>>(p, n_q * p.pairs, tiles > comb ? tiles : comb, st);
+  p.map_q = xcd_map(n_q * p.pairs, p.causal, static_cast<int64_t>(p.h_q) * p.pairs);
+  return launch<Args, k_fwd_f32<D, NS, Args>>(p, xcd_blocks(p.map_q), tiles > comb ? tiles : comb, st);
 }
 
 template <class Args>
@@ -563,7 +629,7 @@ int fwd_form(Args& p, const dfa_shape& sh, hipStream_t st) {
   // runs fewer wavefronts per SIMD.  us per full pair, d = 128, with 1 / 2 / 4 parts:
   //   8 heads x 256 rows 47 / 29 / 22, 32 x 256 49 / 31 / 28, 8 x 1024 174 / 103 / 71 (<= 256 workgroups of
   //   4 parts: one round),  32 x 1024 190 / 183 / 271,  32 x 4096 2361 / 2501 / 3920 (116 TFLOP/s with 1);
-  //   causal, 32 x 4096: 2322 / 2043 / 2579 (64-row blocks share out the diagonal better than 128-row ones).
+  //   causal, 32 x 4096, 2 parts: 1402 (2043 with every eighth row block on the same XCD).
   // The vector-FMA kernel this one replaced took 610 us at 8 x 1024.
   const int64_t wg2 = blocks_of(sh.s_q, 64) * sh.h_q * p.pairs, wg4 = blocks_of(sh.s_q, 32) * sh.h_q * p.pairs;
   const int parts = wg4 <= 256 ? 4 : wg2 <= 512 || sh.causal ? 2 : 1;
@@ -578,12 +644,59 @@ int bwd(F32BwdParams p, hipStream_t st) {
   const size_t tiles = smem_bytes<D, 32 * NS>() + (kVLds<D, NS> ? sizeof(float) * 32 * (D + 4) : 0);
   p.nx_kv = static_cast<int>(blocks_of(p.s_k, rows));
   p.nx_q = static_cast<int>(blocks_of(p.s_q, rows));
-  const int64_t n_kv = p.pair[0].dk ? static_cast<int64_t>(p.nx_kv) * p.h_kv : 0;
+  const int64_t n_kv = p.pair[0].dk ? static_cast<int64_t>(p.nx_kv) * p.h_kv * p.shares : 0;
   const int64_t n_q = p.pair[0].dq ? static_cast<int64_t>(p.nx_q) * p.h_q : 0;
-  if (n_kv * p.pairs > (1 << 30)) return DFA_ERR_SHAPE;
+  if ((n_kv + n_q) * p.pairs > (1 << 30)) return DFA_ERR_SHAPE;
   p.n_kv = static_cast<int>(n_kv);
   p.n_q = static_cast<int>(n_q);
-  return launch<F32BwdParams, k_bwd_f32<D, NS>>(p, (n_kv + n_q) * p.pairs, tiles > comb ? tiles : comb, st);
+  p.map_kv = xcd_map(n_kv * p.pairs, p.causal, static_cast<int64_t>(p.h_kv) * p.shares * p.pairs);
+  p.map_q = xcd_map(n_q * p.pairs, p.causal, static_cast<int64_t>(p.h_q) * p.pairs);
+  const int64_t blocks = xcd_blocks(p.map_kv) + xcd_blocks(p.map_q);
+  const size_t smem = tiles > comb ? tiles : comb;
+  const int rc = p.shares > 1 ? launch<F32BwdParams, k_bwd_f32<D, NS, true>>(p, blocks, smem, st)
+                              : launch<F32BwdParams, k_bwd_f32<D, NS, false>>(p, blocks, smem, st);
+  if (rc || p.shares == 1) return rc;
+  const dim3 grid(static_cast<unsigned>(n_kv * p.pairs / p.shares), 2 * (4 / NS));
+  k_reduce_f32<D, 4 / NS><<<grid, NT, 0, st>>>(p);
+  return last_launch_status();
+}
+
+// How a backward is divided: parts of every tile inside a workgroup, and workgroups that share the query tiles of
+// a block of key rows.  A dk/dv workgroup walks over all query heads of its group, so with grouped heads a few
+// workgroups would run long after the others; sharing the walk sends their sums (2 D floats per key row)
+// through memory and a second launch.  The estimate, with what one box measured for its terms at d = 128: 6 us
+// per workgroup and, with 1 / 2 / 4 parts, 9.3 / 10.3 / 12.2 us per query tile (dk, dv) and 7 / 7.7 / 9.7 per
+// key tile (dq); calls of one round take their longest workgroup, longer ones the device's even share and about
+// half a workgroup.  us per full pair (dk, dv and dq), d = 128, with 1 / 2 / 4 parts and nothing shared:
+//   8 / 2 heads x 1024 rows 1183 / 647 / 371,  32 x 256 87 / 57 / 72,  32 x 1024 547 / 604 / 725,
+//   32 x 4096 8370 / 9210 / 11380 (82 TFLOP/s with 1);  shared, 8 / 2 x 1024 178, x 2048 1310 -> 623, four
+//   diagonal chunks of 1024 1220 -> 443.
+// The vector-FMA kernel this one replaced (dq by atomics) took 2.9 ms at 8 / 2 x 1024.
+struct Plan { int parts, shares; double us; };
+
+Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
+  const int group = sh.h_q / sh.h_kv;
+  const double width = sh.d == 128 ? 1.0 : 0.55, mean = sh.causal ? 0.5 : 1.0;
+  Plan best{0, 0, 0.};
+  for (int parts : {1, 2, 4}) {
+    const int rows = 128 / parts, tile = 32 * parts;
+    const int64_t kv1 = dk ? blocks_of(sh.s_k, rows) * sh.h_kv * pairs : 0, n_q = dq ? blocks_of(sh.s_q, rows) * sh.h_q * pairs : 0;
+    const double walk_kv = width * (parts == 1 ? 9.3 : parts == 2 ? 10.3 : 12.2) * group * blocks_of(sh.s_q, tile);
+    const double walk_q = width * (parts == 1 ? 7.0 : parts == 2 ? 7.7 : 9.7) * blocks_of(sh.s_k, tile);
+    const int64_t bytes = static_cast<int64_t>(rows) * 2 * sh.d * 4;       // of a workgroup's sums
+    for (int shares : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+      const int64_t n_kv = kv1 * shares;
+      if (shares > 1 && (!dk || shares > 4 * group || n_kv > 1024 || n_kv * bytes > ws_bytes)) break;
+      Plan x{parts, shares, std::max(dk ? 6 + walk_kv / shares : 0., dq ? 6 + walk_q : 0.)};
+      if (n_kv + n_q > 256) {
+        const double even = (n_kv * (6 + walk_kv * mean / shares) + n_q * (6 + walk_q * mean)) / 256;
+        x.us = std::max(x.us, even + 0.45 * x.us);
+      }
+      if (shares > 1) x.us = (x.us + 4 + n_kv * (2 * bytes / 2.5e6)) / 0.92;
+      if (!best.parts || x.us < best.us) best = x;
+    }
+  }
+  return best;
 }
 
 }  // namespace
@@ -609,9 +722,9 @@ int launch_fwd_f32(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStr
   return fwd_form<F32FwdBatch>(p, sh, st);
 }
 
-int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, hipStream_t st) {
+int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void* ws, int64_t ws_bytes, hipStream_t st) {
   for (; n > MAX_PAIRS; pairs += MAX_PAIRS, n -= MAX_PAIRS) {
-    const int rc = launch_bwd_f32(sh, pairs, MAX_PAIRS, st);
+    const int rc = launch_bwd_f32(sh, pairs, MAX_PAIRS, ws, ws_bytes, st);
     if (rc) return rc;
   }
   F32BwdParams p{};
@@ -623,18 +736,18 @@ int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, hipStr
                      static_cast<const float*>(x.dO), x.lse, x.delta, x.dq, x.dk, x.dv, x.accumulate_dq,
                      x.accumulate_dkv};
   }
-  // Parts per tile, as in the forward; us per full pair (dk, dv and dq), d = 128, with 1 / 2 / 4 parts:
-  //   8 / 2 heads x 1024 rows 1183 / 647 / 371 (320 workgroups of 4 parts),  32 x 256 87 / 57 / 72 (256
-  //   workgroups of 2),  32 x 1024 547 / 604 / 725,  32 x 4096 8370 / 9210 / 11380 (82 TFLOP/s with 1);
-  //   causal, 32 x 4096 8240 / 7050 / 6960, 32 x 1024 545 / 593 / 725.
-  // The vector-FMA kernel this one replaced (dq by atomics) took 2.9 ms at 8 / 2 x 1024.
-  auto workgroups = [&](int rows) {
-    return ((pairs[0].dk ? blocks_of(sh.s_k, rows) * sh.h_kv : 0) +
-            (pairs[0].dq ? blocks_of(sh.s_q, rows) * sh.h_q : 0)) * n;
-  };
-  const int parts = workgroups(32) <= 384 ? 4 : workgroups(64) <= 512 || (sh.causal && workgroups(128) >= 1024) ? 2 : 1;
-  if (sh.d == 128) return parts == 4 ? bwd<128, 4>(p, st) : parts == 2 ? bwd<128, 2>(p, st) : bwd<128, 1>(p, st);
-  return parts == 4 ? bwd<64, 4>(p, st) : parts == 2 ? bwd<64, 2>(p, st) : bwd<64, 1>(p, st);
+  const Plan pl = plan(sh, n, pairs[0].dq, pairs[0].dk, ws ? ws_bytes : 0);
+  p.shares = pl.shares;
+  p.partial = static_cast<float*>(ws);
+  if (sh.d == 128) return pl.parts == 4 ? bwd<128, 4>(p, st) : pl.parts == 2 ? bwd<128, 2>(p, st) : bwd<128, 1>(p, st);
+  return pl.parts == 4 ? bwd<64, 4>(p, st) : pl.parts == 2 ? bwd<64, 2>(p, st) : bwd<64, 1>(p, st);
+}
+
+int64_t bwd_f32_workspace(const dfa_shape& sh, int n, bool dq, bool dk) {
+  const int per = std::min(n, MAX_PAIRS);
+  const Plan pl = plan(sh, per, dq, dk, INT64_MAX);
+  const int rows = 128 / pl.parts;
+  return pl.shares > 1 ? pl.shares * blocks_of(sh.s_k, rows) * sh.h_kv * per * rows * 2 * sh.d * 4 : 0;
 }
 
 }  // namespace dfa

@@ -40,8 +40,8 @@ namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
 
-// Workgroups of one kind: tiles per head, (head, tile) items of one pair, of all pairs, and per XCD.
-struct Items { int ntile, per_pair, total, per_xcd; };
+// Workgroups of one kind: tiles per head, (head, tile) items of one pair, and those of all pairs.
+struct Items { int ntile, per_pair; XcdMap map; };
 
 // The operands of one (query chunk, key/value chunk) pair.
 struct Pair {
@@ -70,10 +70,6 @@ __device__ __forceinline__ const Pair& pair_of(const BwdPairs<NP>& p, const Item
 }
 template <int NP>
 __device__ __forceinline__ int item_in_pair(const Items& it, int item) { return NP == 1 ? item : item % it.per_pair; }
-
-// XCD-aware mapping: workgroup ids go round-robin over the 8 XCDs; every XCD gets a contiguous range of
-// (head, tile) items, so that the tiles of one head share Q/dO (or K/V) in one L2.
-__device__ __forceinline__ int item_of(const Items& it, int bid) { return (bid & 7) * it.per_xcd + (bid >> 3); }
 
 // ============================================================================================
 // dK, dV
@@ -738,15 +734,15 @@ __global__ void __launch_bounds__(kv::NT) k_reduce_dkdv(BwdPairs<MAX_PAIRS> p) {
 // The kernels: dk, dv alone, dq alone, and both kinds of workgroups in one launch; of NP pairs at most.
 template <bool RAGGED, bool PARTS, int NP>
 __device__ __forceinline__ void run_dkdv(const BwdPairs<NP>& p, int bid, char* smem) {
-  const int item = item_of(p.kv_items, bid);
-  if (item < p.kv_items.total)
+  const int item = xcd_item(p.kv_items.map, bid);
+  if (item < p.kv_items.map.total)
     kv::dkdv<RAGGED, PARTS>(p, pair_of(p, p.kv_items, item), item_in_pair<NP>(p.kv_items, item),
                             p.partial + static_cast<int64_t>(item) * kv::PART_F4, smem);
 }
 template <int NW, int NS, int NP>
 __device__ __forceinline__ void run_dq(const BwdPairs<NP>& p, int bid, char* smem) {
-  const int item = item_of(p.q_items, bid);
-  if (item < p.q_items.total)
+  const int item = xcd_item(p.q_items.map, bid);
+  if (item < p.q_items.map.total)
     qs::dq<NW, NS>(p, pair_of(p, p.q_items, item), item_in_pair<NP>(p.q_items, item), smem);
 }
 
@@ -765,7 +761,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPai
 template <bool RAGGED, int NS, bool PARTS, int NP>
 __global__ void __launch_bounds__(kv::NT, 2) k_bwd_bf16(BwdPairs<NP> p) {
   extern __shared__ __align__(16) char smem[];
-  const int n_kv = p.kv_items.per_xcd * 8, n_q = p.q_items.per_xcd * 8;
+  const int n_kv = p.kv_items.map.per_xcd * 8, n_q = p.q_items.map.per_xcd * 8;
   const int bid = blockIdx.x;
   if (p.q_first ? bid >= n_q : bid < n_kv) run_dkdv<RAGGED, PARTS, NP>(p, p.q_first ? bid - n_q : bid, smem);
   else run_dq<8, NS, NP>(p, p.q_first ? bid : bid - n_kv, smem);
@@ -793,13 +789,12 @@ template <class F>
 int with(bool b, F f) { return b ? f(std::true_type{}) : f(std::false_type{}); }
 
 // Items of `rows` rows each of `heads` heads (or heads x parts) and `pairs` pairs; false: more than a launch takes.
-bool make_items(Items& it, int s, int rows, int heads, int pairs) {
+bool make_items(Items& it, int s, int rows, int heads, int pairs, int causal) {
   const int64_t n = (static_cast<int64_t>(s) + rows - 1) / rows, total = n * heads * pairs;
   if (total > (1 << 29)) return false;
   it.ntile = static_cast<int>(n);
   it.per_pair = static_cast<int>(n * heads);
-  it.total = static_cast<int>(total);
-  it.per_xcd = (it.total + 7) / 8;
+  it.map = xcd_map(total, causal, static_cast<int64_t>(heads) * pairs);
   return true;
 }
 
@@ -879,10 +874,10 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
   const Plan pl = plan(sh, n, dq, dk, ws ? ws_bytes : 0);
   p.parts = pl.parts;
   p.partial = static_cast<f32x4*>(ws);
-  if (dk && !make_items(p.kv_items, sh.s_k, kv::BN, sh.h_kv * p.parts, n)) return DFA_ERR_SHAPE;
+  if (dk && !make_items(p.kv_items, sh.s_k, kv::BN, sh.h_kv * p.parts, n, sh.causal)) return DFA_ERR_SHAPE;
   auto reduce = [&] {
     if (p.parts == 1) return static_cast<int>(DFA_OK);
-    k_reduce_dkdv<<<dim3(4, p.kv_items.total / p.parts), kv::NT, 0, st>>>(p);
+    k_reduce_dkdv<<<dim3(4, p.kv_items.map.total / p.parts), kv::NT, 0, st>>>(p);
     return last_launch_status();
   };
   if (dk && dq) {
@@ -892,11 +887,11 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
     // (Within 2 % either way where the last round of workgroups decides, e.g. 32 x 2777 426 / 435.)
     // The longer workgroups first: a dk/dv workgroup walks over its part of the query heads of a group.
     p.q_first = p.group <= p.parts;
-    if (!make_items(p.q_items, sh.s_q, pl.split ? 128 : 256, sh.h_q, n)) return DFA_ERR_SHAPE;
-    const int64_t blocks = 8 * (static_cast<int64_t>(p.kv_items.per_xcd) + p.q_items.per_xcd);
+    if (!make_items(p.q_items, sh.s_q, pl.split ? 128 : 256, sh.h_q, n, sh.causal)) return DFA_ERR_SHAPE;
+    const int64_t blocks = xcd_blocks(p.kv_items.map) + xcd_blocks(p.q_items.map);
     // Ten rounds of workgroups and more: nothing is left to fill, and each kind alone has the better use of
     // the L2 (32 heads x 12000 6775 against 6808 us).  (Nor would a grid take more than 2^23 of them.)
-    if (p.kv_items.total >= 2560) {
+    if (p.kv_items.map.total >= 2560) {
       for (int i = 0; i < n; ++i) {
         dfa_bwd_pair a = pairs[i], b = pairs[i];
         a.dq = nullptr; b.dk = b.dv = nullptr;
@@ -920,7 +915,7 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
   return with(n > 1, [&](auto m) {
     constexpr int NP = m() ? MAX_PAIRS : 1;
     if (dk) {
-      const int64_t blocks = 8 * static_cast<int64_t>(p.kv_items.per_xcd);
+      const int64_t blocks = xcd_blocks(p.kv_items.map);
       const int rc = with(ragged, [&](auto r) {
         return with(p.parts > 1, [&](auto s) {
           return launch<NP, k_bwd_dkdv_bf16<r(), s(), NP>>(p, blocks, kv::NT, kv::SMEM_BYTES, st);
@@ -930,8 +925,8 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
     }
     // dq alone: 256-row workgroups for long unmasked chunks (at least four of them per CU), 128 rows otherwise
     const bool wide = !sh.causal && blocks_of(sh.s_q, 256) * sh.h_q * n >= 1024;
-    if (!make_items(p.q_items, sh.s_q, wide ? 256 : 128, sh.h_q, n)) return static_cast<int>(DFA_ERR_SHAPE);
-    const int64_t blocks = 8 * static_cast<int64_t>(p.q_items.per_xcd);
+    if (!make_items(p.q_items, sh.s_q, wide ? 256 : 128, sh.h_q, n, sh.causal)) return static_cast<int>(DFA_ERR_SHAPE);
+    const int64_t blocks = xcd_blocks(p.q_items.map);
     return wide ? launch<NP, k_bwd_dq_bf16<8, NP>>(p, blocks, 512, 4 * qs::TILE_BYTES, st)
                 : launch<NP, k_bwd_dq_bf16<4, NP>>(p, blocks, 256, 4 * qs::TILE_BYTES, st);
   });

@@ -30,7 +30,8 @@ constexpr float LOG2E = 1.4426950408889634f;
 struct FwdParams {
   const __bf16 *q, *k, *v;
   void* o; float* lse;
-  int s_q, s_k, h_q, group, causal, o_bf16, accumulate, ntq, total, per_xcd;
+  int s_q, s_k, h_q, group, causal, o_bf16, accumulate, ntq;
+  XcdMap map;
   float scale;
   int64_t q_sh, q_ss, kv_sh, kv_ss, o_sh, o_ss, l_sh;
 };
@@ -103,11 +104,9 @@ template <bool FULL, class Args>
 __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
   extern __shared__ __align__(16) char smem[];   // two (K tile, V tile) buffers
 
-  // XCD-aware mapping: consecutive workgroup ids go round-robin over the 8 XCDs, so give every
-  // XCD a contiguous range of (head, query tile) items; its workgroups then share K/V in its L2.
   const int bid = blockIdx.x;
-  int item = (bid & 7) * a.per_xcd + (bid >> 3);
-  if (item >= a.total) return;
+  int item = xcd_item(a.map, bid);
+  if (item >= a.map.total) return;
   const FwdParams& p = pair_of(a, item);
   const int head = item / p.ntq;
   int tq = item % p.ntq;
@@ -371,8 +370,8 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
   extern __shared__ __align__(16) char smem[];
 
   const int bid = blockIdx.x;
-  int item = (bid & 7) * a.per_xcd + (bid >> 3);   // contiguous (head, query tile) range per XCD
-  if (item >= a.total) return;
+  int item = xcd_item(a.map, bid);
+  if (item >= a.map.total) return;
   const FwdParams& p = pair_of(a, item);
   const int head = item / p.ntq;
   int tq = item % p.ntq;
@@ -648,8 +647,8 @@ __global__ void __launch_bounds__(RB * NS * 64, NS == 2 ? 2 : 1) k_fwd_bf16(Args
   extern __shared__ __align__(16) char smem[]; // two buffers of (SUB K sub-tiles, SUB V sub-tiles)
 
   const int bid = blockIdx.x;
-  int item = (bid & 7) * a.per_xcd + (bid >> 3);   // contiguous (head, query tile) range per XCD
-  if (item >= a.total) return;
+  int item = xcd_item(a.map, bid);
+  if (item >= a.map.total) return;
   const FwdParams& p = pair_of(a, item);
   const int head = item / p.ntq;
   int tq = item % p.ntq;
@@ -856,7 +855,7 @@ int launch(const Args& p, int threads, int smem, hipStream_t st) {
                                              hipFuncAttributeMaxDynamicSharedMemorySize, smem));
   });
   if (attr_rc) return attr_rc;
-  KERNEL<<<p.per_xcd * 8, threads, smem, st>>>(p);
+  KERNEL<<<static_cast<int>(xcd_blocks(p.map)), threads, smem, st>>>(p);
   return last_launch_status();
 }
 
@@ -865,9 +864,8 @@ template <class Args>
 int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
   auto grid = [&](int rows) {
     p.ntq = (sh.s_q + rows - 1) / rows;
-    p.total = p.ntq * sh.h_q * n;
+    p.map = xcd_map(static_cast<int64_t>(p.ntq) * sh.h_q * n, sh.causal, static_cast<int64_t>(sh.h_q) * n);
     if constexpr (std::is_same_v<Args, FwdBatch>) p.per_pair = p.ntq * sh.h_q;
-    p.per_xcd = (p.total + 7) / 8;
   };
   // Which form.  us per call on one box, d = 128, 256-row / 128-row / 64-row NS = 2 / 64-row NS = 4 workgroups:
   //   full pairs    8 heads x 256 rows 13.5 / 9.6 / 8.6 / 9.5    x 1024 30.5 / 24.2 / 22 / 18.4

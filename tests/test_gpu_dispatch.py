@@ -203,3 +203,38 @@ def test_schedule_in_batches(dtype, d, p, c):
         assert maxerr(bufs.O, O) <= tol and maxerr(bufs.L, L) <= tol
         for got, w in zip((bufs.dQ, bufs.dK, bufs.dV), want):
             assert maxerr(got, w) <= tol * max(1.0, abs(w).max() / 4)
+
+
+# fp32 dk, dv by several workgroups per row block: (heads, rows, keys, causal).
+F32_SHARES = [
+    (8, 2, 300, 260, False),      # remainders on both axes
+    (8, 1, 130, 70, False),
+    (12, 1, 700, 700, True),      # more shares than the last row blocks have query tiles
+    (6, 2, 1100, 150, False),     # shares that cut through heads
+]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("shape", F32_SHARES)
+def test_f32_backward_shares(shape, d):
+    """Against the oracle, overwriting and adding, with and without dq."""
+    h_q, h_kv, s_q, s_k, causal = shape
+    scale = d ** -0.5
+    q, k, v, do = case(9700 + s_q + s_k, h_q, h_kv, s_q, s_k, d, torch.float32)
+    q64, k64, v64, do64 = (np64(t) for t in (q, k, v, do))
+    O, L = A.attention_fwd(q64, k64, v64, scale, causal=causal)
+    want = A.attention_bwd(q64, k64, v64, do64, scale, causal=causal)
+    # fp32 gradients: the bound grows with their magnitude
+    bound = [TOL[torch.float32] * max(1.0, abs(w).max()) for w in want]
+    Q, K, V, dO = (t.to(dev()) for t in (q, k, v, do))
+    lse = torch.from_numpy(L).float().to(dev())
+    delta = torch.from_numpy(A.delta_rows(O, do64)).float().to(dev())
+    sh = B._bwd_shape(Q, K, V, lse, delta, dO, None, K, V, causal, scale)
+    for want_dq in (True, False):
+        assert B.load_library().dfa_chunk_bwd_workspace(ctypes.byref(sh), 1, want_dq, 1) > 0
+        for acc in (False, True):
+            got = [torch.full(w.shape, 0.5, device=dev()) for w in want]
+            dfa.dfa_chunk_bwd(Q, K, V, lse, delta, dO, got[0] if want_dq else None, got[1], got[2], causal, scale,
+                              accumulate=acc)
+            for i in (0, 1, 2) if want_dq else (1, 2):
+                assert maxerr(got[i], want[i] + (0.5 if acc else 0.0)) <= bound[i]
