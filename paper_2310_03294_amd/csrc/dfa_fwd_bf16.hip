@@ -883,9 +883,9 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
   if (sh.causal) {
     // The diagonal's longest row block sets the time of a call that does not fill the device, so long
     // chunks are split further; the 256-row form needs chunks long enough that its masked half tiles do
-    // not count.
+    // not count, and whole tiles (ragged chunks, 32 heads x 14197: 1664 us against 1608 with 128 rows).
     if (n64 <= 256 || (n64 <= 512 && sh.s_q >= 2048)) parts = 4;
-    wide = n256 >= 512 && sh.s_q >= 6144;
+    wide = n256 >= 512 && sh.s_q >= 6144 && sh.s_k % BN == 0;
   } else {
     // One round of 64-row workgroups at most: split the keys.  The 128-row form (10 % slower per row, two
     // workgroups per CU) where it needs one workgroup per CU at most, or where the last round of 256-row
@@ -911,8 +911,7 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
   grid(full_pair::BMW);
   constexpr int nt = full_pair::NT, smem = full_pair::SMEM_BYTES;
   const bool ragged = sh.s_k % BN != 0;
-  if (sh.causal) return ragged ? launch<Args, full_pair::k_fwd_bf16<true, true, Args>>(p, nt, smem, st)
-                               : launch<Args, full_pair::k_fwd_bf16<false, true, Args>>(p, nt, smem, st);
+  if (sh.causal) return launch<Args, full_pair::k_fwd_bf16<false, true, Args>>(p, nt, smem, st);
   return ragged ? launch<Args, full_pair::k_fwd_bf16<true, false, Args>>(p, nt, smem, st)
                 : launch<Args, full_pair::k_fwd_bf16<false, false, Args>>(p, nt, smem, st);
 }
