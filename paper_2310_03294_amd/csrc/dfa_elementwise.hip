@@ -1,29 +1,35 @@
 // HBM-bound row kernels: the merge (rescale) of two partial results, the D = rowsum(dO o O)
 // pre-pass of the backward, and small fill kernels.  One query row is d values wide; a row is
-// handled by d/8 adjacent lanes, each moving 8 elements (16 B of bf16 or 2 x 16 B of fp32), so
-// every global access of a wavefront is a run of full cache lines.
+// handled by adjacent lanes, so every global access of a wavefront is a run of full cache lines.
+// Operands that are not needed again soon are read past the caches (nontemporal loads), which leaves
+// them to what is: 32 heads x 16384, fp32, merge and then D 231 -> 171 us (5.5 TB/s of what both
+// cannot do without; a plain copy of the same tensor runs at 5.4).
 #include "dfa_internal.h"
 
 namespace dfa {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 struct Vec8 { float v[8]; };
 
-template <bool BF16>
+// STREAM: past the caches
+template <bool BF16, bool STREAM = false>
 __device__ inline Vec8 load8(const void* base, int64_t elem_off) {
   Vec8 r;
   if constexpr (BF16) {
-    const uint4 raw = *reinterpret_cast<const uint4*>(static_cast<const __bf16*>(base) + elem_off);
+    const u32x4* p = reinterpret_cast<const u32x4*>(static_cast<const __bf16*>(base) + elem_off);
+    const u32x4 raw = STREAM ? __builtin_nontemporal_load(p) : *p;
     bf16x8 b = __builtin_bit_cast(bf16x8, raw);
 #pragma unroll
     for (int i = 0; i < 8; ++i) r.v[i] = static_cast<float>(b[i]);
   } else {
-    const float4* p = reinterpret_cast<const float4*>(static_cast<const float*>(base) + elem_off);
-    const float4 a = p[0], b = p[1];
-    r.v[0] = a.x; r.v[1] = a.y; r.v[2] = a.z; r.v[3] = a.w;
-    r.v[4] = b.x; r.v[5] = b.y; r.v[6] = b.z; r.v[7] = b.w;
+    const f32x4* p = reinterpret_cast<const f32x4*>(static_cast<const float*>(base) + elem_off);
+    const f32x4 a = STREAM ? __builtin_nontemporal_load(p) : p[0], b = STREAM ? __builtin_nontemporal_load(p + 1) : p[1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { r.v[i] = a[i]; r.v[4 + i] = b[i]; }
   }
   return r;
 }
@@ -45,46 +51,83 @@ __device__ inline void store8(void* base, int64_t elem_off, const Vec8& r) {
 constexpr int MAX_PAIRS = 16;          // per launch (blockIdx.z): the pairs travel in the kernel arguments
 template <int NP> struct MergePairs { dfa_merge_pair pair[NP]; };
 
+// 16 bytes of a row as fp32 values
+template <bool BF16> struct Vec16 { static constexpr int N = BF16 ? 8 : 4; float v[N]; };
+template <bool BF16, bool STREAM>
+__device__ inline Vec16<BF16> load16(const void* base, int64_t elem_off) {
+  const u32x4* p = reinterpret_cast<const u32x4*>(static_cast<const char*>(base) + elem_off * (BF16 ? 2 : 4));
+  const u32x4 raw = STREAM ? __builtin_nontemporal_load(p) : *p;
+  Vec16<BF16> r;
+  if constexpr (BF16) {
+    const bf16x8 b = __builtin_bit_cast(bf16x8, raw);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r.v[i] = static_cast<float>(b[i]);
+  } else {
+    const f32x4 f = __builtin_bit_cast(f32x4, raw);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.v[i] = f[i];
+  }
+  return r;
+}
+template <bool BF16>
+__device__ inline void store16(void* base, int64_t elem_off, const Vec16<BF16>& r) {
+  if constexpr (BF16) {
+    bf16x8 b;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b[i] = static_cast<__bf16>(r.v[i]);
+    *reinterpret_cast<bf16x8*>(static_cast<__bf16*>(base) + elem_off) = b;
+  } else {
+    *reinterpret_cast<f32x4*>(static_cast<float*>(base) + elem_off) = f32x4{r.v[0], r.v[1], r.v[2], r.v[3]};
+  }
+}
+
 // (o_a, lse_a) <- merge((o_a, lse_a), (o_b, lse_b)), Section 3.2 rescale(.)
+// 16 bytes per lane and row, MERGE_ROWS rows in flight per lane; (o_b, lse_b) is read for the last time, (o_a, lse_a)
+// is what the next step continues from.  32 heads x 16384, fp32: 157 us with 32 bytes per lane and cached
+// loads, 147 with this division, 115 with o_b past the caches (7.0 TB/s; four rows in flight: 116).
+constexpr int MERGE_ROWS = 2;
+template <int D, bool BF16> constexpr int kMergeLanes = D / (BF16 ? 8 : 4);       // lanes per row
 template <int D, bool BF16, int NP>
 __global__ void __launch_bounds__(256) k_merge(dfa_merge_desc md, MergePairs<NP> pairs) {
   const dfa_merge_pair& pr = pairs.pair[NP == 1 ? 0 : blockIdx.z];
-  void* __restrict__ o_a = pr.o_a;
-  float* __restrict__ lse_a = pr.lse_a;
-  const void* __restrict__ o_b = pr.o_b;
-  const float* __restrict__ lse_b = pr.lse_b;
-  constexpr int LPR = D / 8;           // lanes per row
-  constexpr int RPB = 256 / LPR;       // rows per block iteration
-  const int lane = threadIdx.x % LPR;
-  const int rib = threadIdx.x / LPR;
-  const int h = blockIdx.y;
-  float* la_p = lse_a + h * md.lse_a_stride_h;
-  const float* lb_p = lse_b + h * md.lse_b_stride_h;
-  for (int row = blockIdx.x * RPB + rib; row < md.rows; row += gridDim.x * RPB) {
-    const float la = la_p[row], lb = lb_p[row];
-    const float m = fmaxf(la, lb);
+  constexpr int LPR = kMergeLanes<D, BF16>, RPB = 256 / LPR, VN = Vec16<BF16>::N;
+  const int lane = threadIdx.x % LPR, h = blockIdx.y;
+  const int row0 = blockIdx.x * RPB * MERGE_ROWS + threadIdx.x / LPR;
+  float* la_p = pr.lse_a + h * md.lse_a_stride_h;
+  const float* lb_p = pr.lse_b + h * md.lse_b_stride_h;
+  Vec16<BF16> a[MERGE_ROWS], b[MERGE_ROWS];
+  float la[MERGE_ROWS], lb[MERGE_ROWS];
+  auto off_a = [&](int row) { return h * md.a_stride_h + static_cast<int64_t>(row) * md.a_stride_s + lane * VN; };
+#pragma unroll
+  for (int u = 0; u < MERGE_ROWS; ++u) {
+    const int row = min(row0 + u * RPB, md.rows - 1);
+    a[u] = load16<BF16, false>(pr.o_a, off_a(row));
+    b[u] = load16<BF16, true>(pr.o_b, h * md.b_stride_h + static_cast<int64_t>(row) * md.b_stride_s + lane * VN);
+    la[u] = la_p[row];
+    lb[u] = lb_p[row];
+  }
+#pragma unroll
+  for (int u = 0; u < MERGE_ROWS; ++u) {
+    const int row = row0 + u * RPB;
+    if (row >= md.rows) break;
+    const float m = fmaxf(la[u], lb[u]);
     float wa = 0.f, wb = 0.f, l = -INFINITY;
     if (m > -INFINITY) {
-      const float ea = expf(la - m), eb = expf(lb - m);   // one of them is exactly 1
+      const float ea = expf(la[u] - m), eb = expf(lb[u] - m);   // one of them is exactly 1
       const float s = ea + eb;
       l = m + logf(s);
       const float inv = 1.f / s;
       wa = ea * inv; wb = eb * inv;
     }
-    const int64_t offa = h * md.a_stride_h + static_cast<int64_t>(row) * md.a_stride_s + lane * 8;
-    const int64_t offb = h * md.b_stride_h + static_cast<int64_t>(row) * md.b_stride_s + lane * 8;
-    const Vec8 a = load8<BF16>(o_a, offa);
-    const Vec8 b = load8<BF16>(o_b, offb);
-    Vec8 r;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) r.v[i] = wa * a.v[i] + wb * b.v[i];
-    store8<BF16>(o_a, offa, r);
+    for (int i = 0; i < VN; ++i) a[u].v[i] = wa * a[u].v[i] + wb * b[u].v[i];
+    store16<BF16>(pr.o_a, off_a(row), a[u]);
     if (lane == 0) la_p[row] = l;
   }
 }
 
-// D_i = sum_c dO_ic * O_ic  (Section 3.3: the saved output feeds the backward)
-template <int D, bool DO_BF16, bool O_BF16>
+// D_i = sum_c dO_ic * O_ic  (Section 3.3: the saved output feeds the backward).  STREAM: dO past the caches.
+template <int D, bool DO_BF16, bool O_BF16, bool STREAM>
 __global__ void __launch_bounds__(256) k_delta(int s_q, const void* __restrict__ o, int64_t o_sh, int64_t o_ss,
                                                const void* __restrict__ dO, int64_t q_sh, int64_t q_ss,
                                                float* __restrict__ delta, int64_t l_sh) {
@@ -96,7 +139,7 @@ __global__ void __launch_bounds__(256) k_delta(int s_q, const void* __restrict__
   float acc = 0.f;
   if (row < s_q) {
     const Vec8 a = load8<O_BF16>(o, h * o_sh + static_cast<int64_t>(row) * o_ss + lane * 8);
-    const Vec8 b = load8<DO_BF16>(dO, h * q_sh + static_cast<int64_t>(row) * q_ss + lane * 8);
+    const Vec8 b = load8<DO_BF16, STREAM>(dO, h * q_sh + static_cast<int64_t>(row) * q_ss + lane * 8);
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc = fmaf(a.v[i], b.v[i], acc);
   }
@@ -137,8 +180,10 @@ int grid_for(int64_t items, int per_block) {
 }  // namespace
 
 template <int D, bool BF16>
-static void merge_form(dim3 grid, const dfa_merge_desc& md, const MergePairs<MAX_PAIRS>& all, hipStream_t st) {
-  if (grid.z > 1) k_merge<D, BF16, MAX_PAIRS><<<grid, 256, 0, st>>>(md, all);
+static void merge_form(const dfa_merge_desc& md, const MergePairs<MAX_PAIRS>& all, int n, hipStream_t st) {
+  constexpr int rows = 256 / kMergeLanes<D, BF16> * MERGE_ROWS;
+  const dim3 grid((md.rows - 1) / rows + 1, md.heads, n);
+  if (n > 1) k_merge<D, BF16, MAX_PAIRS><<<grid, 256, 0, st>>>(md, all);
   else k_merge<D, BF16, 1><<<grid, 256, 0, st>>>(md, MergePairs<1>{{all.pair[0]}});
 }
 
@@ -149,14 +194,9 @@ int launch_merge(const dfa_merge_desc& md, const dfa_merge_pair* pairs, int n, h
   }
   MergePairs<MAX_PAIRS> all{};
   for (int i = 0; i < n; ++i) all.pair[i] = pairs[i];
-  const int rpb = 256 / (md.d / 8);
-  int gx = (md.rows + rpb - 1) / rpb;
-  const int cap = (256 * 16 + md.heads - 1) / md.heads;   // a few blocks per CU in total; rows are grid-strided
-  if (gx > cap) gx = cap;
-  const dim3 grid(gx < 1 ? 1 : gx, md.heads, n);
   const bool b = md.o_dtype == DFA_BF16;
-  if (md.d == 128) b ? merge_form<128, true>(grid, md, all, st) : merge_form<128, false>(grid, md, all, st);
-  else b ? merge_form<64, true>(grid, md, all, st) : merge_form<64, false>(grid, md, all, st);
+  if (md.d == 128) b ? merge_form<128, true>(md, all, n, st) : merge_form<128, false>(md, all, n, st);
+  else b ? merge_form<64, true>(md, all, n, st) : merge_form<64, false>(md, all, n, st);
   return last_launch_status();
 }
 
@@ -164,8 +204,13 @@ int launch_delta(const dfa_shape& sh, const void* o, const void* dO, float* delt
   const int rpb = 256 / (sh.d / 8);
   dim3 grid((sh.s_q + rpb - 1) / rpb, sh.h_q);
   const bool dob = sh.dtype == DFA_BF16, ob = sh.o_dtype == DFA_BF16;
-#define DFA_DELTA(DD, A, B) k_delta<DD, A, B><<<grid, 256, 0, st>>>(sh.s_q, o, sh.o_stride_h, sh.o_stride_s, dO, \
-                                sh.q_stride_h, sh.q_stride_s, delta, sh.lse_stride_h)
+  // The backward that follows reads dO again, from the caches as long as it and o fit the 256 MB that all
+  // XCDs share; a larger dO only pushes out the o that the last merge has left there (o and dO of 32 heads x
+  // 16384: 67 -> 56 us).
+  const int64_t bytes = static_cast<int64_t>(sh.h_q) * sh.s_q * sh.d * ((dob ? 2 : 4) + (ob ? 2 : 4));
+  const bool stream = bytes > (int64_t{256} << 20);
+#define DFA_DELTA(DD, A, B) (stream ? k_delta<DD, A, B, true> : k_delta<DD, A, B, false>)<<<grid, 256, 0, st>>>( \
+      sh.s_q, o, sh.o_stride_h, sh.o_stride_s, dO, sh.q_stride_h, sh.q_stride_s, delta, sh.lse_stride_h)
   if (sh.d == 128) {
     if (dob && ob) DFA_DELTA(128, true, true); else if (dob) DFA_DELTA(128, true, false);
     else if (ob) DFA_DELTA(128, false, true); else DFA_DELTA(128, false, false);
