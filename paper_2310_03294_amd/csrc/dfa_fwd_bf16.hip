@@ -621,28 +621,30 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
 }  // namespace full_pair
 
 // ============================================================================================
-// Forward for calls with few query rows, full or causal: a workgroup owns 64 rows (2 blocks of 32) and its wavefronts
-// divide the KEYS as well, NS parts of 32 keys per tile (NS = 2: 4 wavefronts, 64-key tiles, two
-// workgroups per CU; NS = 4: 8 wavefronts, 128-key tiles, one workgroup per CU).  Every wavefront runs its
+// Forward for calls that do not fill the device, full or causal: a workgroup owns RB blocks of 32 rows and its
+// wavefronts divide the KEYS as well, NS parts of 32 keys per tile (RB = 2, NS = 2: 64 rows, 4 wavefronts,
+// 64-key tiles, two workgroups per CU; RB = 2, NS = 4: 8 wavefronts, 128-key tiles, one workgroup per CU;
+// RB = 4, NS = 2: 128 rows, 8 wavefronts, 64-key tiles, one workgroup per CU, two wavefronts per SIMD).  Every wavefront runs its
 // own online softmax over its keys; the parts of a row block are combined through LDS at the end.
 // Such a call is bound by the serial walk over the key tiles with most CUs idle: this form has 2-4
 // times the workgroups and each wavefront 1/NS of the walk (8 heads x 2048 x 2048: 52 us with 256-row
 // workgroups, 43 with 128-row ones, 34 here).  Where the device is full it is the slowest form: one
 // 32-key block per wavefront and tile leaves its exponentials uncovered.
-// The matrix pipes have room here, so the weights enter the second product as two bf16 values, the
+// LO (64 rows): the matrix pipes have room, so the weights enter the second product as two bf16 values, the
 // rounded weight and its remainder (o is then off by 2^-17 of a weight instead of 2^-9, for 1 us of 18 at 8 heads x 1024), and the row sums
-// are fp32 sums of the fp32 weights.
+// are fp32 sums of the fp32 weights.  With 128 rows rounding and sums are those of the 128-row kernel.
 // ============================================================================================
 namespace split {
 
-constexpr int RB = 2, BMS = RB * 32;           // row blocks, query rows per workgroup
 template <int NS> constexpr int kKeys = 32 * NS;                          // keys per tile
 template <int NS> constexpr int kTilesBytes = 2 * (kKeys<NS> / BN) * TILE_BYTES;      // K and V of one tile
 template <int NS> constexpr int kSmem = 2 * kTilesBytes<NS>;
 constexpr int RES_BYTES = 64 * 64 * 4;         // a wavefront's O^T, 64 registers per lane
 
-template <int NS, bool CAUSAL, class Args>
-__global__ void __launch_bounds__(RB * NS * 64, NS == 2 ? 2 : 1) k_fwd_bf16(Args a) {
+template <int RB, int NS, bool CAUSAL, class Args>
+__global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16(Args a) {
+  constexpr int BMS = RB * 32;                 // query rows per workgroup
+  constexpr bool LO = RB == 2;
   constexpr int SUB = kKeys<NS> / BN;          // 64-row sub-tiles of a K (or V) tile
   extern __shared__ __align__(16) char smem[]; // two buffers of (SUB K sub-tiles, SUB V sub-tiles)
 
@@ -673,13 +675,16 @@ __global__ void __launch_bounds__(RB * NS * 64, NS == 2 ? 2 : 1) k_fwd_bf16(Args
   const int k_end = CAUSAL ? min(p.s_k, q0 + BMS) : p.s_k;
   const int ntiles = (k_end + kKeys<NS> - 1) / kKeys<NS>;
   // wavefronts 4s .. 4s + 3 copy sub-tile s of K and of V
-  const int cw = wave & 3, sub = wave >> 2;
+  // (8 wavefronts and one sub-tile: 0-3 copy K, 4-7 copy V)
+  constexpr bool ONE = RB * NS == 8 && SUB == 1;
+  const int cw = wave & 3, sub = ONE ? 0 : wave >> 2;
+  const bool v_copy = ONE && wave >= 4;
   const TileLane tl = tile_lane(cw, lane, kv_rowbytes);
   const int last = p.s_k - 1;
   const int koff = sub * TILE_BYTES, voff = (SUB + sub) * TILE_BYTES;
   // rows past the end are clamped to the last row (and masked); a sub-tile wholly past it likewise
-  tile_dma(kg, kv_rowbytes, sub * BN, last, tl, smem + koff, cw, lane);
-  tile_dma(vg, kv_rowbytes, sub * BN, last, tl, smem + voff, cw, lane);
+  tile_dma(v_copy ? vg : kg, kv_rowbytes, sub * BN, last, tl, smem + (v_copy ? voff : koff), cw, lane);
+  if (!ONE) tile_dma(vg, kv_rowbytes, sub * BN, last, tl, smem + voff, cw, lane);
 
   bf16x8 qreg[8];
   {
@@ -713,7 +718,7 @@ __global__ void __launch_bounds__(RB * NS * 64, NS == 2 ? 2 : 1) k_fwd_bf16(Args
     const char* buf = smem + (it & 1) * kTilesBytes<NS>;
     char* nbuf = smem + ((it & 1) ^ 1) * kTilesBytes<NS>;
     const int kn = (it + 1 < ntiles ? k0 + kKeys<NS> : k0) + sub * BN;
-    const TileCopy ck = tile_copy_plan(kg, kv_rowbytes, kn, last, tl, nbuf + koff, cw, lane);
+    const TileCopy ck = tile_copy_plan(v_copy ? vg : kg, kv_rowbytes, kn, last, tl, nbuf + (v_copy ? voff : koff), cw, lane);
     const TileCopy cv = tile_copy_plan(vg, kv_rowbytes, kn, last, tl, nbuf + voff, cw, lane);
     const int kb0 = k0 + part * 32;            // this wavefront's 32 keys
     const char* Ks = buf + (part >> 1) * TILE_BYTES;
@@ -737,7 +742,7 @@ __global__ void __launch_bounds__(RB * NS * 64, NS == 2 ? 2 : 1) k_fwd_bf16(Args
         if (ks == 6) tile_copy_piece<3>(ck);
         DFA_SCHED_FENCE();
       }
-      if (cw == 0) { tile_copy_piece<4>(ck); tile_copy_piece<4>(cv); }
+      if (cw == 0) { tile_copy_piece<4>(ck); if (!ONE) tile_copy_piece<4>(cv); }
 #pragma unroll
       for (int i = 0; i < 4; ++i) gv[i] = lds_gather(Vs, g_base + row + i * 64);
       if (kb0 + 32 > p.s_k || (CAUSAL && kb0 + 31 > q0w)) {
@@ -766,9 +771,8 @@ __global__ void __launch_bounds__(RB * NS * 64, NS == 2 ? 2 : 1) k_fwd_bf16(Args
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
         s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], c2, -mc));
-        sum += s[j];
+        if (LO || CAUSAL) sum += s[j];
       }
-      l_run += sum;
       if (__any(alpha != 1.f)) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -779,26 +783,33 @@ __global__ void __launch_bounds__(RB * NS * 64, NS == 2 ? 2 : 1) k_fwd_bf16(Args
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         pb[u] = pack8(s, 8 * u);
+        if constexpr (LO) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s[8 * u + e] -= static_cast<float>(pb[u][e]);
-        pl[u] = pack8(s, 8 * u);
+          for (int e = 0; e < 8; ++e) s[8 * u + e] -= static_cast<float>(pb[u][e]);
+          pl[u] = pack8(s, 8 * u);
+        }
+        if (!LO && !CAUSAL) sum = sum8(pb[u], sum);
       }
+      l_run += sum;
       DFA_SCHED_FENCE();
 #pragma unroll
       for (int i = 0; i < 8; ++i) {            // O^T += V^T P^T
         o[i & 3] = mfma32(gv[i & 3], pb[i >> 2], o[i & 3]);
-        o[i & 3] = mfma32(gv[i & 3], pl[i >> 2], o[i & 3]);
+        if constexpr (LO) o[i & 3] = mfma32(gv[i & 3], pl[i >> 2], o[i & 3]);
         if (i < 4) gv[i & 3] = lds_gather(Vs, g_base + row + 16 * kRowBytes + i * 64);
-        if (i == 0) tile_copy_piece<0>(cv);
-        if (i == 2) tile_copy_piece<1>(cv);
-        if (i == 4) tile_copy_piece<2>(cv);
-        if (i == 6) tile_copy_piece<3>(cv);
+        if (!ONE && i == 0) tile_copy_piece<0>(cv);
+        if (!ONE && i == 2) tile_copy_piece<1>(cv);
+        if (!ONE && i == 4) tile_copy_piece<2>(cv);
+        if (!ONE && i == 6) tile_copy_piece<3>(cv);
         DFA_SCHED_FENCE();
       }
     } else {                                   // nothing for this wavefront: only its share of the copies
       tile_copy_piece<0>(ck); tile_copy_piece<1>(ck); tile_copy_piece<2>(ck); tile_copy_piece<3>(ck);
-      tile_copy_piece<0>(cv); tile_copy_piece<1>(cv); tile_copy_piece<2>(cv); tile_copy_piece<3>(cv);
-      if (cw == 0) { tile_copy_piece<4>(ck); tile_copy_piece<4>(cv); }
+      if (cw == 0) tile_copy_piece<4>(ck);
+      if (!ONE) {
+        tile_copy_piece<0>(cv); tile_copy_piece<1>(cv); tile_copy_piece<2>(cv); tile_copy_piece<3>(cv);
+        if (cw == 0) tile_copy_piece<4>(cv);
+      }
     }
     lds_dma_wait();
     __syncthreads();
@@ -880,28 +891,41 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
   const int64_t n256 = count(256), n128 = count(128), n64 = count(64);
   bool wide;          // 256 rows
   int parts = 0;      // 64 rows with this many parts
+  bool two = false;   // 128 rows with two parts
   if (sh.causal) {
     // The diagonal's longest row block sets the time of a call that does not fill the device, so long
     // chunks are split further; the 256-row form needs chunks long enough that its masked half tiles do
     // not count, and whole tiles (ragged chunks, 32 heads x 14197: 1664 us against 1608 with 128 rows).
     if (n64 <= 256 || (n64 <= 512 && sh.s_q >= 2048)) parts = 4;
     wide = n256 >= 512 && sh.s_q >= 6144 && sh.s_k % BN == 0;
+    // Two parts per tile where the 128-row form's longest walk decides: 16 heads x 2500 59 -> 51 us, x 4096
+    // 117 -> 96, 8 x 6000 131 -> 112; not where short walks share the CUs anyway (32 x 1500 45 -> 49).
+    two = n128 <= 352 || (n128 <= 512 && sh.s_q > 2048);
   } else {
     // One round of 64-row workgroups at most: split the keys.  The 128-row form (10 % slower per row, two
     // workgroups per CU) where it needs one workgroup per CU at most, or where the last round of 256-row
     // workgroups would be half empty or worse.
     if (n64 <= 256) parts = 4;
+    // Two parts per tile where the 128-row form would have one wavefront per SIMD (8 heads x 2777 57 -> 46 us, x
+    // 4096 82 -> 72; 32 x 1024 27.4 -> 25.1), and up to two rounds of 256-row workgroups where that form is
+    // no better (16 x 5500 280 -> 265, 32 x 2777 151 -> 148; 32 x 5120, three rounds, 419 -> 434).
     const int64_t last_round = n256 % 256;
     wide = n128 > 256 && !(n256 > 256 && n256 < 768 && last_round > 0 && last_round <= 128);
+    two = n256 < 512;
   }
   if (parts && sh.s_k <= 256) parts = 2;      // two 128-key tiles at most: the smaller tiles start sooner
   if (n128 > (1 << 30) && (sh.causal || n > 1)) return DFA_ERR_SHAPE;
   if (parts) {
-    grid(split::BMS);
-    if (parts == 2) return sh.causal ? launch<Args, split::k_fwd_bf16<2, true, Args>>(p, 256, split::kSmem<2>, st)
-                                     : launch<Args, split::k_fwd_bf16<2, false, Args>>(p, 256, split::kSmem<2>, st);
-    return sh.causal ? launch<Args, split::k_fwd_bf16<4, true, Args>>(p, 512, split::kSmem<4>, st)
-                     : launch<Args, split::k_fwd_bf16<4, false, Args>>(p, 512, split::kSmem<4>, st);
+    grid(64);
+    if (parts == 2) return sh.causal ? launch<Args, split::k_fwd_bf16<2, 2, true, Args>>(p, 256, split::kSmem<2>, st)
+                                     : launch<Args, split::k_fwd_bf16<2, 2, false, Args>>(p, 256, split::kSmem<2>, st);
+    return sh.causal ? launch<Args, split::k_fwd_bf16<2, 4, true, Args>>(p, 512, split::kSmem<4>, st)
+                     : launch<Args, split::k_fwd_bf16<2, 4, false, Args>>(p, 512, split::kSmem<4>, st);
+  }
+  if (!wide && two) {
+    grid(128);
+    return sh.causal ? launch<Args, split::k_fwd_bf16<4, 2, true, Args>>(p, 512, split::kSmem<2>, st)
+                     : launch<Args, split::k_fwd_bf16<4, 2, false, Args>>(p, 512, split::kSmem<2>, st);
   }
   if (!wide) {
     grid(BM);

@@ -46,7 +46,12 @@ FWD_FORMS = [
     (200, 100, 300, 129, False),  # 256 rows, last round of 144
     (4, 2, 200, 200, True),       # 64 rows, 2 parts
     (4, 2, 450, 450, True),       # 64 rows, 4 parts
-    (70, 35, 260, 260, True),     # 128 rows
+    (70, 35, 260, 260, True),     # 128 rows, 2 parts: 210 workgroups
+    (130, 65, 270, 270, True),    # 128 rows: 390
+    (96, 32, 129, 33, False),     # 128 rows, 2 parts (288 64-row workgroups): a part with one key
+    (88, 44, 140, 31, False),     # the same, the second part without keys
+    (90, 45, 161, 161, True),
+    (130, 130, 515, 200, False),  # 128 rows: 390 256-row workgroups
 ]
 
 
