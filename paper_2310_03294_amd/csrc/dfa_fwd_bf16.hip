@@ -913,7 +913,7 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
     wide = n128 > 256 && !(n256 > 256 && n256 < 768 && last_round > 0 && last_round <= 128);
     two = n256 < 512;
   }
-  if (parts && sh.s_k <= 256) parts = 2;      // two 128-key tiles at most: the smaller tiles start sooner
+  if (parts && sh.s_k <= 384) parts = 2;      // three 128-key tiles at most: the smaller tiles start sooner
   if (n128 > (1 << 30) && (sh.causal || n > 1)) return DFA_ERR_SHAPE;
   if (parts) {
     grid(64);

@@ -38,7 +38,7 @@ FWD_FORMS = [
     # h_q, h_kv, s_q, s_k, causal
     (4, 2, 129, 256, False),      # 64 rows, 2 parts; one row past a block
     (4, 2, 257, 97, False),       # the same, fewer keys than two tiles
-    (4, 2, 200, 257, False),      # 64 rows, 4 parts: one key past two tiles
+    (4, 2, 200, 385, False),      # 64 rows, 4 parts: one key past three tiles
     (2, 2, 65, 31, False),        # fewer keys than one part's block: parts without keys
     (3, 3, 70, 1153, False),
     (96, 32, 190, 300, False),    # 128 rows (288 64-row workgroups)
