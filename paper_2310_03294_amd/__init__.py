@@ -5,13 +5,13 @@ marshals arguments (device pointers, sizes, strides, the current HIP stream).  T
 no CPU or PyTorch fallback: if the library has not been built, loading fails loudly.
 """
 from .binding import (  # noqa: F401
+    BackwardChunks,
     DfaError,
+    ForwardChunks,
     Step,
     dfa_chunk_bwd,
-    dfa_chunk_bwd_batch,
     dfa_chunk_fwd,
     dfa_chunk_fwd_acc,
-    dfa_chunk_fwd_batch,
     dfa_delta,
     dfa_merge,
     dfa_merge_batch,

@@ -131,9 +131,18 @@ def _dt(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
+def _current_stream() -> int:
+    return torch.cuda.current_stream().cuda_stream
+
+
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):      # the same without a Stream object for every launch
+    def _current_stream() -> int:  # noqa: F811
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     return getattr(stream, "cuda_stream", stream)
 
 
@@ -260,7 +269,7 @@ def _workspace(n, stream):
     stream known by its handle alone gets none, unless it is the current one."""
     if n <= 0:
         return None, 0
-    if stream is None or _stream(stream) == torch.cuda.current_stream().cuda_stream:
+    if stream is None or _stream(stream) == _current_stream():
         return torch.empty(n, dtype=torch.uint8, device="cuda"), n
     if isinstance(stream, torch.cuda.Stream):
         with torch.cuda.stream(stream):
@@ -296,30 +305,40 @@ class _Chunks:
         return self.base + i * self.step
 
 
-def dfa_chunk_fwd_batch(q, k, v, rows, pairs, causal, scale, stream=None):
-    """The chunk pairs of one time step as one launch.  q, k, v: whole sequences, divided in chunks of `rows`.
-    pairs: (q_chunk, kv_chunk, o, lse, chunk, accumulate), where the result goes to chunk number `chunk` of the
-    [heads, seq, d] tensor o and of lse; accumulate: continues from the state there.  No output may overlap
-    another pair's."""
-    if not pairs:
-        return
-    lib = load_library()
-    if v.shape != k.shape or v.stride() != k.stride():
-        raise ValueError("k and v must share shape and strides")
-    sh = _make_shape(q, k, causal, scale, _dt(q), o=pairs[0][2], o_dtype=_dt(pairs[0][2]))
-    sh.s_q = sh.s_k = rows
-    cq, ck, cv = _Chunks(q, rows), _Chunks(k, rows), _Chunks(v, rows)
-    arr, dest = (DfaFwdPair * len(pairs))(), {}
-    for a, (qc, kc, o, lse, c, acc) in zip(arr, pairs):
-        d = dest.get(id(o))
-        if d is None:
-            if o.dtype != pairs[0][2].dtype or lse.stride(1) != 1:
-                raise ValueError("outputs share a dtype, lse has unit innermost stride")
-            d = dest[id(o)] = (_Chunks(o, rows), _Chunks(lse, rows), (*_hsd(o, "o"), lse.stride(0)))
-        a.q, a.k, a.v, a.o, a.lse = cq[qc], ck[kc], cv[kc], d[0][c], d[1][c]
-        a.o_stride_h, a.o_stride_s, a.lse_stride_h = d[2]
-        a.accumulate = bool(acc)
-    _check(lib.dfa_chunk_fwd_batch(ctypes.byref(sh), arr, len(pairs), _stream(stream)), "dfa_chunk_fwd_batch")
+class ForwardChunks:
+    """Forward calls (dfa_chunk_fwd_batch) on the chunk pairs of whole sequences q, k, v, divided in chunks of `rows`.
+    The operands are checked and described once; a launch then costs the host little more than its pointers."""
+
+    def __init__(self, q, k, v, rows, scale):
+        if v.shape != k.shape or v.stride() != k.stride():
+            raise ValueError("k and v must share shape and strides")
+        self.tensors = (q, k, v)                     # kept: launches use their addresses
+        self.rows, self.lib = rows, load_library()
+        self.sh = _make_shape(q, k, False, scale, _dt(q))
+        self.sh.s_q = self.sh.s_k = rows
+        self.q, self.k, self.v = _Chunks(q, rows), _Chunks(k, rows), _Chunks(v, rows)
+
+    def dest(self, o, lse):
+        """[heads, seq, d] and [heads, seq] tensors that results can go to, in chunks of the same length."""
+        if lse.stride(1) != 1:
+            raise ValueError("lse must have unit innermost stride")
+        return _Chunks(o, self.rows), _Chunks(lse, self.rows), (*_hsd(o, "o"), lse.stride(0)), _dt(o), (o, lse)
+
+    def launch(self, pairs, causal, stream=None):
+        """The pairs as one launch: (q_chunk, kv_chunk, dest, chunk, accumulate), the result goes to chunk number
+        `chunk` of dest; accumulate: continues from the state there.  No output may overlap another pair's."""
+        if not pairs:
+            return
+        sh = self.sh
+        sh.causal, sh.o_dtype = int(bool(causal)), pairs[0][2][3]
+        arr = (DfaFwdPair * len(pairs))()
+        for a, (qc, kc, dest, c, acc) in zip(arr, pairs):
+            if dest[3] != sh.o_dtype:
+                raise ValueError("outputs of a launch share their dtype")
+            a.q, a.k, a.v, a.o, a.lse = self.q[qc], self.k[kc], self.v[kc], dest[0][c], dest[1][c]
+            a.o_stride_h, a.o_stride_s, a.lse_stride_h = dest[2]
+            a.accumulate = bool(acc)
+        _check(self.lib.dfa_chunk_fwd_batch(ctypes.byref(sh), arr, len(pairs), _stream(stream)), "dfa_chunk_fwd_batch")
 
 
 def dfa_merge_batch(o, lse, rows, parts, stream=None):
@@ -345,25 +364,33 @@ def dfa_merge_batch(o, lse, rows, parts, stream=None):
     _check(lib.dfa_merge_batch(ctypes.byref(md), arr, len(parts), _stream(stream)), "dfa_merge_batch")
 
 
-def dfa_chunk_bwd_batch(q, k, v, lse, delta, dO, dq, dk, dv, rows, pairs, causal, scale, stream=None):
-    """Gradient contributions of several chunk pairs as one launch.  Tensors: whole sequences, divided in chunks
-    of `rows`.  pairs: (q_chunk, kv_chunk, accumulate_dq, accumulate_dkv); no query chunk and no key/value chunk
-    occurs twice."""
-    if not pairs:
-        return
-    lib = load_library()
-    sh = _bwd_shape(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale)
-    sh.s_q = sh.s_k = rows
-    by_q = [_Chunks(t, rows) for t in (q, lse, delta, dO, dq)]
-    by_kv = [_Chunks(t, rows) for t in (k, v, dk, dv)]
-    arr = (DfaBwdPair * len(pairs))()
-    for a, (qc, kc, acc_q, acc_kv) in zip(arr, pairs):
-        a.q, a.lse, a.delta, a.dO, a.dq = (t[qc] for t in by_q)
-        a.k, a.v, a.dk, a.dv = (t[kc] for t in by_kv)
-        a.accumulate_dq, a.accumulate_dkv = bool(acc_q), bool(acc_kv)
-    ws, n = _workspace(lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), len(pairs), 1, 1), stream)
-    _check(lib.dfa_chunk_bwd_batch(ctypes.byref(sh), arr, len(pairs), _ptr(ws), n, _stream(stream)),
-           "dfa_chunk_bwd_batch")
+class BackwardChunks:
+    """Backward calls (dfa_chunk_bwd_batch) on the chunk pairs of whole sequences, divided in chunks of `rows`; as
+    ForwardChunks."""
+
+    def __init__(self, q, k, v, lse, delta, dO, dq, dk, dv, rows, scale):
+        self.tensors = (q, k, v, lse, delta, dO, dq, dk, dv)
+        self.lib = load_library()
+        self.sh = _bwd_shape(q, k, v, lse, delta, dO, dq, dk, dv, False, scale)
+        self.sh.s_q = self.sh.s_k = rows
+        self.by_q = [_Chunks(t, rows) for t in (q, lse, delta, dO, dq)]
+        self.by_kv = [_Chunks(t, rows) for t in (k, v, dk, dv)]
+
+    def launch(self, pairs, causal, stream=None):
+        """The pairs as one launch: (q_chunk, kv_chunk, accumulate_dq, accumulate_dkv); no query chunk and no
+        key/value chunk occurs twice."""
+        if not pairs:
+            return
+        sh = self.sh
+        sh.causal = int(bool(causal))
+        arr = (DfaBwdPair * len(pairs))()
+        for a, (qc, kc, acc_q, acc_kv) in zip(arr, pairs):
+            a.q, a.lse, a.delta, a.dO, a.dq = (t[qc] for t in self.by_q)
+            a.k, a.v, a.dk, a.dv = (t[kc] for t in self.by_kv)
+            a.accumulate_dq, a.accumulate_dkv = bool(acc_q), bool(acc_kv)
+        ws, n = _workspace(self.lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), len(pairs), 1, 1), stream)
+        _check(self.lib.dfa_chunk_bwd_batch(ctypes.byref(sh), arr, len(pairs), _ptr(ws), n, _stream(stream)),
+               "dfa_chunk_bwd_batch")
 
 
 def dfa_mfma_probe(out, iters: int, stream=None) -> float:

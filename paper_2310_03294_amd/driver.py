@@ -83,6 +83,8 @@ def forward_worker(Q, K, V, scale, P, w, bufs: Buffers, remote=None, mode="balan
     c = bufs.c
     sent = {}
     o_w, l_w = _chunk(bufs.O, w, c), _chunk(bufs.L, w, c)
+    fwd = B.ForwardChunks(Q, K, V, c, scale)
+    state = fwd.dest(bufs.O, bufs.L)
     sched = B.dfa_schedule(P, w, mode)
     own = _own_steps(sched) if prefetch is not None else []
     nxt, slot = 0, None
@@ -90,23 +92,21 @@ def forward_worker(Q, K, V, scale, P, w, bufs: Buffers, remote=None, mode="balan
         if st.kind == B.DFA_STEP_DIAG:
             if own:
                 slot = prefetch.fetch(own[0].kv_chunk); nxt = 1      # copy for step 1 runs under the diagonal pair
-            B.dfa_chunk_fwd(_chunk(Q, w, c), _chunk(K, w, c), _chunk(V, w, c), True, scale, o=o_w, lse=l_w)
+            fwd.launch([(w, w, state, w, False)], True)
         elif st.kind == B.DFA_STEP_OWN and fused and prefetch is not None:
             k_s, v_s = prefetch.get(slot)
             if nxt < len(own):
                 slot = prefetch.fetch(own[nxt].kv_chunk); nxt += 1   # copy for the next step runs under this pair
             B.dfa_chunk_fwd_acc(_chunk(Q, w, c), k_s, v_s, False, scale, o_w, l_w)
         elif st.kind == B.DFA_STEP_OWN and fused:
-            B.dfa_chunk_fwd_acc(_chunk(Q, w, c), _chunk(K, st.kv_chunk, c), _chunk(V, st.kv_chunk, c), False, scale,
-                                o_w, l_w)
+            fwd.launch([(w, st.kv_chunk, state, w, True)], False)
         elif st.kind == B.DFA_STEP_OWN:
             po, pl = bufs.part_o[0], bufs.part_l[0]
-            B.dfa_chunk_fwd(_chunk(Q, w, c), _chunk(K, st.kv_chunk, c), _chunk(V, st.kv_chunk, c), False, scale,
-                            o=po, lse=pl)
+            fwd.launch([(w, st.kv_chunk, fwd.dest(po, pl), 0, False)], False)
             B.dfa_merge(o_w, l_w, po, pl)
         elif st.kind == B.DFA_STEP_HELP:
             po = torch.empty_like(bufs.part_o[0]); pl = torch.empty_like(bufs.part_l[0])
-            B.dfa_chunk_fwd(_chunk(Q, st.q_chunk, c), _chunk(K, w, c), _chunk(V, w, c), False, scale, o=po, lse=pl)
+            fwd.launch([(st.q_chunk, w, fwd.dest(po, pl), 0, False)], False)
             sent[st.send_to] = (po, pl)
         if st.recv_from >= 0 and remote is not None:
             ro, rl = remote[st.recv_from]
@@ -129,19 +129,15 @@ def backward_worker(Q, K, V, dO, scale, P, w, bufs: Buffers, mode="balanced", wi
     touched: a new_pass() record shared by the calls of one pass; None = always accumulate into
     what the gradient buffers hold."""
     c = bufs.c
+    bwd = B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, bufs.dQ, bufs.dK, bufs.dV, c, scale)
     for st in B.dfa_schedule(P, w, mode):
         if st.kind == B.DFA_STEP_IDLE:
             continue
         qc, kc = st.q_chunk, st.kv_chunk
         if with_delta and st.kind == B.DFA_STEP_DIAG:
             B.dfa_delta(_chunk(bufs.O, qc, c), _chunk(dO, qc, c), delta=_chunk(bufs.delta, qc, c))
-        args = (_chunk(Q, qc, c), _chunk(K, kc, c), _chunk(V, kc, c), _chunk(bufs.L, qc, c),
-                _chunk(bufs.delta, qc, c), _chunk(dO, qc, c))
-        diag = st.kind == B.DFA_STEP_DIAG
-        acc_q = touched is None or qc in touched["dq"]
-        acc_kv = touched is None or kc in touched["dkv"]
-        B.dfa_chunk_bwd(*args, _chunk(bufs.dQ, qc, c), _chunk(bufs.dK, kc, c), _chunk(bufs.dV, kc, c), diag, scale,
-                        accumulate=acc_q, accumulate_dkv=acc_kv)
+        bwd.launch([(qc, kc, touched is None or qc in touched["dq"], touched is None or kc in touched["dkv"])],
+                   st.kind == B.DFA_STEP_DIAG)
         if touched is not None:
             touched["dq"].add(qc); touched["dkv"].add(kc)
 
@@ -182,31 +178,28 @@ def backward_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced"):
     every query chunk and every key/value chunk at most once, so its pairs go out as one launch."""
     scheds = [B.dfa_schedule(P, w, mode) for w in range(P)]
     touched = new_pass()
+    bwd = B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, bufs.dQ, bufs.dK, bufs.dV, bufs.c, scale)
     for steps in zip(*scheds):
         for kind in (B.DFA_STEP_DIAG, B.DFA_STEP_OWN, B.DFA_STEP_HELP):
             pairs = [(st.q_chunk, st.kv_chunk, st.q_chunk in touched["dq"], st.kv_chunk in touched["dkv"])
                      for st in steps if st.kind == kind]
             assert len({p[0] for p in pairs}) == len({p[1] for p in pairs}) == len(pairs)
-            B.dfa_chunk_bwd_batch(Q, K, V, bufs.L, bufs.delta, dO, bufs.dQ, bufs.dK, bufs.dV, bufs.c, pairs,
-                                  kind == B.DFA_STEP_DIAG, scale)
+            bwd.launch(pairs, kind == B.DFA_STEP_DIAG)
             touched["dq"].update(p[0] for p in pairs)
             touched["dkv"].update(p[1] for p in pairs)
 
 
-def _forward_step(Q, K, V, scale, steps, bufs: Buffers):
+def _forward_step(fwd, state, steps, bufs: Buffers):
     """What all workers compute in one time step, as one launch: the owners' pairs continue from their states, the
     helpers' give partials, which are then "sent" and merged."""
     diag = [st for st in steps if st.kind == B.DFA_STEP_DIAG]
     own = [st for st in steps if st.kind == B.DFA_STEP_OWN]
     helped = [st for st in steps if st.kind == B.DFA_STEP_HELP]
-    B.dfa_chunk_fwd_batch(Q, K, V, bufs.c, [(st.q_chunk, st.kv_chunk, bufs.O, bufs.L, st.q_chunk, False)
-                                            for st in diag], True, scale)
     parts = _partials(bufs, len(helped))
-    B.dfa_chunk_fwd_batch(Q, K, V, bufs.c, [(st.q_chunk, st.kv_chunk, bufs.O, bufs.L, st.q_chunk, True)
-                                            for st in own] +
-                          [(st.q_chunk, st.kv_chunk, po, pl, 0, False) for st, (po, pl) in zip(helped, parts)],
-                          False, scale)
-    B.dfa_merge_batch(bufs.O, bufs.L, bufs.c, [(st.send_to, po, pl) for st, (po, pl) in zip(helped, parts)])
+    fwd.launch([(st.q_chunk, st.kv_chunk, state, st.q_chunk, False) for st in diag], True)
+    fwd.launch([(st.q_chunk, st.kv_chunk, state, st.q_chunk, True) for st in own] +
+               [(st.q_chunk, st.kv_chunk, fwd.dest(*part), 0, False) for st, part in zip(helped, parts)], False)
+    B.dfa_merge_batch(bufs.O, bufs.L, bufs.c, [(st.send_to, *part) for st, part in zip(helped, parts)])
 
 
 def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backward=True, fused=True):
@@ -217,12 +210,14 @@ def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backw
     c = bufs.c
     scheds = [B.dfa_schedule(P, w, mode) for w in range(P)]
     nsteps = len(scheds[0])
+    fwd = B.ForwardChunks(Q, K, V, c, scale)
+    state = fwd.dest(bufs.O, bufs.L)
     for t in range(nsteps):
         steps = [scheds[w][t] for w in range(P)]
         for w, st in enumerate(steps):
             assert st.kind != B.DFA_STEP_HELP or steps[st.send_to].recv_from == w
         if fused:
-            _forward_step(Q, K, V, scale, steps, bufs)
+            _forward_step(fwd, state, steps, bufs)
             continue
         for w, st in enumerate(steps):      # partial + merge, pair by pair
             if st.kind == B.DFA_STEP_DIAG:
