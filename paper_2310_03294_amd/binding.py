@@ -307,7 +307,8 @@ class _Chunks:
 
 class ForwardChunks:
     """Forward calls (dfa_chunk_fwd_batch) on the chunk pairs of whole sequences q, k, v, divided in chunks of `rows`.
-    The operands are checked and described once; a launch then costs the host little more than its pointers."""
+    The operands are checked and described once; a launch then costs the host little more than its pointers.  An
+    object serves one thread at a time."""
 
     def __init__(self, q, k, v, rows, scale):
         if v.shape != k.shape or v.stride() != k.stride():
