@@ -17,7 +17,6 @@ from __future__ import annotations
 
 import torch
 
-from . import binding as B
 from . import driver
 
 # pairs computed by dfa_chunk_fwd / dfa_chunk_fwd_acc since the last reset (for tests and for
@@ -63,11 +62,10 @@ def _backward(q, k, v, o, lse, d_o, scale, P):
     tensor gradients of its own dtype, so they are rounded to it on return."""
     global last_fp32_grads
     h_q, n, d = q.shape
-    c = n // P
     d_o = d_o.to(q.dtype).contiguous()
     bufs = driver.Buffers(h_q, k.shape[0], n, d, P, q.device, grads=True, outputs=False, zero_grads=n % P != 0)
     bufs.O, bufs.L = o, lse
-    B.dfa_delta(o[:, :c * P], d_o[:, :c * P], delta=bufs.delta[:, :c * P])
+    driver.delta_all_chunks(o, d_o, bufs.delta, n // P, P)
     driver.backward_all_workers(q, k, v, d_o, scale, P, bufs)
     if keep_fp32_grads:
         last_fp32_grads = (bufs.dQ, bufs.dK, bufs.dV)

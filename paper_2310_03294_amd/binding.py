@@ -14,6 +14,8 @@ _lib = None
 DFA_BF16, DFA_F32 = 0, 1
 DFA_STEP_IDLE, DFA_STEP_DIAG, DFA_STEP_OWN, DFA_STEP_HELP = 0, 1, 2, 3
 STEP_NAMES = {0: "idle", 1: "diag", 2: "own", 3: "help"}
+# a call takes rows * row stride (elements) of one head's slice up to this (include/dfa.h: 32-bit byte offsets)
+MAX_SLICE = (1 << 29) - 1
 
 
 class DfaError(RuntimeError):

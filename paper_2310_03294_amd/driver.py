@@ -172,6 +172,15 @@ def _partials(bufs: Buffers, n):
     return list(zip(bufs.part_o, bufs.part_l))[:n]
 
 
+def delta_all_chunks(O, dO, delta, c, P):
+    """D of the P chunks of c rows.  One launch, unless the slices of all chunks together are longer than a call takes
+    (a sequence stored [N, heads, d] has heads * d elements between its rows): then as few as that makes it."""
+    per = max(1, B.MAX_SLICE // max(O.stride(1), dO.stride(1)) // max(1, c))     # chunks per launch
+    for i in range(0, P, per):
+        rows = slice(i * c, min(i + per, P) * c)
+        B.dfa_delta(O[:, rows], dO[:, rows], delta=delta[:, rows])
+
+
 def backward_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced"):
     """The backward of all P workers' pairs on one device, from the merged O and L and the D of every chunk, time
     step by time step: first the pairs of the owners, then those of the helpers.  Each of the two groups has
@@ -231,6 +240,5 @@ def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backw
                 B.dfa_merge(_chunk(bufs.O, st.q_chunk, c), _chunk(bufs.L, st.q_chunk, c), po, pl)
     if backward:
         # a helper's backward needs D of the chunk it helped, so all D vectors come first
-        n = P * c
-        B.dfa_delta(bufs.O[:, :n], dO[:, :n], delta=bufs.delta[:, :n])
+        delta_all_chunks(bufs.O, dO, bufs.delta, c, P)
         backward_all_workers(Q, K, V, dO, scale, P, bufs, mode)

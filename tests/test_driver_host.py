@@ -1,0 +1,57 @@
+"""Host side of the driver and the binding, without a GPU: which calls are made, and what is refused before any launch."""
+import ctypes
+
+import pytest
+import torch
+
+import paper_2310_03294_amd as dfa
+from paper_2310_03294_amd import binding as B, driver
+
+MAX_SLICE = (1 << 29) - 1       # rows * row stride (elements) of one head's slice that a call takes
+
+
+def _meta(heads, n, d, pitch, dtype=torch.bfloat16):
+    """A [heads, n, d] tensor with `pitch` elements between its rows, without memory."""
+    return torch.empty_strided((heads, n, d), (d if pitch > d else n * d, pitch, 1), dtype=dtype, device="meta")
+
+
+@pytest.fixture
+def no_launches(monkeypatch):
+    """The driver's calls without their launches."""
+    monkeypatch.setattr(B.ForwardChunks, "launch", lambda *a, **k: None)
+    monkeypatch.setattr(B.BackwardChunks, "launch", lambda *a, **k: None)
+    monkeypatch.setattr(B, "dfa_merge_batch", lambda *a, **k: None)
+
+
+@pytest.mark.parametrize("n,P,pitch,calls", [
+    (131071, 1, 4096, 1),            # 32 heads x 128, position-major: the longest slice one call takes
+    (131072, 8, 4096, 2),            # one row more than that
+    (524288, 8, 4096, 8),            # every chunk needs a call of its own
+    (1024, 5, 128, 1),               # 1020 rows in chunks, four left over
+])
+def test_delta_calls_stay_within_a_slice(monkeypatch, no_launches, n, P, pitch, calls):
+    """D of a sequence longer than one call takes goes out in pieces that each stay within the limit."""
+    h, c, d, seen = 2, n // P, 128, []
+
+    def record(o, dO, delta):
+        assert o.shape == dO.shape and o.shape[:2] == delta.shape
+        for t in (o, dO):
+            assert t.shape[1] * t.stride(1) <= MAX_SLICE
+        assert o.storage_offset() // d == delta.storage_offset() == dO.storage_offset() // pitch
+        seen.append((delta.storage_offset(), o.shape[1]))
+
+    monkeypatch.setattr(B, "dfa_delta", record)
+    q, k, v, dO = (_meta(h, n, d, pitch) for _ in range(4))
+    driver.run_all_workers(q, k, v, dO, d ** -0.5, P, driver.Buffers(h, h, n, d, P, "meta"))
+    assert len(seen) == calls and seen[0][0] == 0 and sum(rows for _, rows in seen) == c * P
+    assert all(a[0] + a[1] == b[0] for a, b in zip(seen, seen[1:]))
+
+
+def test_slice_limit_is_the_librarys():
+    """One row more than MAX_SLICE allows is refused (before any launch)."""
+    rows, pitch = 131072, 4096
+    assert rows * pitch == MAX_SLICE + 1
+    sh = B.DfaShape(h_q=1, h_kv=1, s_q=rows, s_k=rows, d=128, dtype=B.DFA_BF16, o_dtype=B.DFA_F32, scale=1.0, q_stride_h=128,
+                    q_stride_s=pitch, kv_stride_h=128, kv_stride_s=pitch, o_stride_h=rows * 128, o_stride_s=128,
+                    lse_stride_h=rows)
+    assert dfa.load_library().dfa_delta(ctypes.byref(sh), 4096, 4096, 4096, None) == -2

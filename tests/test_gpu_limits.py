@@ -8,7 +8,8 @@ import torch
 
 import paper_2310_03294_amd as dfa
 from oracle import attention as A
-from gpu_util import TOL, dev, maxerr, np64
+from gpu_util import TOL, case, dev, maxerr, np64
+from paper_2310_03294_amd import driver
 
 pytestmark = pytest.mark.gpu
 
@@ -74,3 +75,22 @@ def test_many_heads(dtype, d):
     # grouped heads and short causal rows: gradients reach |x| ~ 10, bound them relative to their magnitude
     mag = dict(dq=max(1.0, np.abs(rq).max()), dk=max(1.0, np.abs(rk).max()), dv=max(1.0, np.abs(rv).max()))
     assert all(errs[n] <= tol * mag.get(n, 1.0) for n in errs), (errs, mag)
+
+
+def test_sequence_longer_than_a_slice():
+    """The whole schedule on q, dO whose rows lie 2^22 elements apart (stored [N, heads, d] with many heads): 128 rows
+    span 2^29 elements, more than one call takes, each chunk of 64 half of that."""
+    n, p, h, d, pitch = 128, 2, 1, 128, 1 << 22
+    scale = d ** -0.5
+    q, k, v, do = case(23, h, h, n, n, d, torch.bfloat16)
+    big = torch.empty(n * pitch, dtype=torch.bfloat16, device=dev())         # 1 GiB: q and, d elements further on, dO
+    Q, dO = (torch.as_strided(big, (h, n, d), (d, pitch, 1), at) for at in (0, d))
+    Q.copy_(q.to(dev())), dO.copy_(do.to(dev()))
+    bufs = driver.Buffers(h, h, n, d, p, dev())
+    driver.run_all_workers(Q, k.to(dev()), v.to(dev()), dO, scale, p, bufs)
+    O, L = A.attention_fwd(np64(q), np64(k), np64(v), scale)
+    tol = TOL[torch.bfloat16]
+    assert maxerr(bufs.O, O) <= tol and maxerr(bufs.L, L) <= tol
+    assert maxerr(bufs.delta, A.delta_rows(np64(bufs.O), np64(do))) <= 1e-4
+    for got, w in zip((bufs.dQ, bufs.dK, bufs.dV), A.attention_bwd(np64(q), np64(k), np64(v), np64(do), scale)):
+        assert maxerr(got, w) <= tol * max(1.0, abs(w).max() / 4)
