@@ -12,6 +12,7 @@ _LIB_PATH = os.path.join(_PKG_DIR, "libdfa.so")
 _lib = None
 
 DFA_BF16, DFA_F32 = 0, 1
+DFA_ERR_NULL = -1
 DFA_STEP_IDLE, DFA_STEP_DIAG, DFA_STEP_OWN, DFA_STEP_HELP = 0, 1, 2, 3
 STEP_NAMES = {0: "idle", 1: "diag", 2: "own", 3: "help"}
 # a call takes rows * row stride (elements) of one head's slice up to this (include/dfa.h: 32-bit byte offsets)
@@ -295,11 +296,14 @@ def dfa_chunk_bwd(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale, accumulate
 
 
 class _Chunks:
-    """Addresses of the chunks (`rows` sequence positions each) of a [heads, seq, ...] tensor."""
+    """Addresses of the chunks (`rows` sequence positions each) of a [heads, seq, ...] tensor.  Chunks without rows (a
+    sequence shorter than its number of chunks) have none, as the empty slices of a tensor."""
 
     def __init__(self, t, rows):
+        if rows < 1:
+            raise DfaError(DFA_ERR_NULL, f"chunks of {rows} rows")
         self.base, self.step = t.data_ptr(), rows * t.stride(1) * t.element_size()
-        self.n = t.shape[1] // rows if rows else 1 << 30
+        self.n = t.shape[1] // rows
 
     def __getitem__(self, i):
         if not 0 <= i < self.n:

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import paper_2310_03294_amd as dfa
-from paper_2310_03294_amd import binding as B, driver
+from paper_2310_03294_amd import autograd, binding as B, driver
 
 MAX_SLICE = (1 << 29) - 1       # rows * row stride (elements) of one head's slice that a call takes
 
@@ -55,3 +55,20 @@ def test_slice_limit_is_the_librarys():
                     q_stride_s=pitch, kv_stride_h=128, kv_stride_s=pitch, o_stride_h=rows * 128, o_stride_s=128,
                     lse_stride_h=rows)
     assert dfa.load_library().dfa_delta(ctypes.byref(sh), 4096, 4096, 4096, None) == -2
+
+
+@pytest.mark.parametrize("mode", ["balanced", "ring"])
+def test_sequence_shorter_than_its_chunks_is_refused(mode):
+    """Chunks without rows: no pass may return as if it had written its outputs."""
+    n, P, h, d = 3, 4, 2, 64
+    q, k, v, do = (torch.zeros(h, n, d) for _ in range(4))
+    bufs = driver.Buffers(h, h, n, d, P, "cpu")
+    calls = [lambda: driver.run_all_workers(q, k, v, do, 1.0, P, bufs, mode, backward=False),
+             lambda: driver.forward_worker(q, k, v, 1.0, P, P - 1, bufs, mode=mode),
+             lambda: driver.backward_all_workers(q, k, v, do, 1.0, P, bufs, mode),
+             lambda: driver.backward_worker(q, k, v, do, 1.0, P, P - 1, bufs, mode),
+             lambda: autograd.dist_flash_attn(q, k, v, 1.0, P)]
+    for call in calls:
+        with pytest.raises(dfa.DfaError) as e:
+            call()
+        assert e.value.status == -1
