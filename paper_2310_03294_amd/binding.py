@@ -242,19 +242,25 @@ def dfa_delta(o, dO, delta=None, stream=None):
     return delta
 
 
+def _same_strides(a, b) -> bool:
+    """Whether the elements of a and b lie the same way (the stride of an axis of one element says nothing)."""
+    return all(n == 1 or x == y for n, x, y in zip(a.shape, a.stride(), b.stride()))
+
+
+def _alike(a, b) -> bool:
+    return a.shape == b.shape and _same_strides(a, b)
+
+
 def _bwd_shape(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale):
-    """Checks one pair's operands and describes them."""
-    if v.shape != k.shape or v.stride() != k.stride():
+    """Checks that operands which share a description are alike, and describes them.  (Which outputs may be left out
+    is the library's check.)"""
+    if not _alike(v, k):
         raise ValueError("k and v must share shape and strides")
-    if dO.shape != q.shape or dO.stride() != q.stride():
+    if not _alike(dO, q):
         raise ValueError("dO and q must share shape and strides")
-    if (dk is None) != (dv is None):
-        raise ValueError("dk and dv are given together or not at all")
-    if dq is None and dk is None:
-        raise ValueError("nothing to compute: dq, dk, dv are all None")
-    if dk is not None and (dv.shape != dk.shape or dv.stride() != dk.stride()):
+    if dk is not None and dv is not None and not _alike(dv, dk):
         raise ValueError("dk and dv must share shape and strides")
-    if lse.stride() != delta.stride():
+    if not _same_strides(lse, delta):
         raise ValueError("lse and delta must share strides")
     for t in (dq, dk, dv, lse, delta):
         if t is not None and t.dtype != torch.float32:

@@ -72,3 +72,42 @@ def test_sequence_shorter_than_its_chunks_is_refused(mode):
         with pytest.raises(dfa.DfaError) as e:
             call()
         assert e.value.status == -1
+
+
+def _bwd_operands(h, n, d=64):
+    """q, k, v, lse, delta, dO, dq, dk, dv, all contiguous."""
+    x = {t: torch.zeros(h, n, d) for t in ("q", "k", "v", "dO", "dq", "dk", "dv")}
+    return {**x, "lse": torch.zeros(h, n), "delta": torch.zeros(h, n)}
+
+
+def _shape_of(x):
+    return B._bwd_shape(*(x[t] for t in ("q", "k", "v", "lse", "delta", "dO", "dq", "dk", "dv")), False, 1.0)
+
+
+@pytest.mark.parametrize("name", ["dO", "v", "dv", "delta"])
+def test_strides_of_one_head_do_not_matter(name):
+    """With one head the head stride is never used: slices of larger tensors next to contiguous ones.  With two it is,
+    and operands that share a description have to share it."""
+    for h in (1, 2):
+        x = _bwd_operands(h, 8)
+        x[name] = torch.zeros(h, 16, *x[name].shape[2:])[:, :8]
+        if h == 1:
+            assert _shape_of(x).h_q == 1
+            B.BackwardChunks(*(x[t] for t in ("q", "k", "v", "lse", "delta", "dO", "dq", "dk", "dv")), 4, 1.0)
+        else:
+            with pytest.raises(ValueError):
+                _shape_of(x)
+    x = _bwd_operands(1, 8)
+    x["q"] = torch.zeros(8, 1, 64).transpose(0, 1)        # position-major: contiguous all the same
+    assert x["q"].is_contiguous() and x["q"].stride() != x["dO"].stride()
+    assert _shape_of(x).s_q == 8
+
+
+@pytest.mark.parametrize("missing", [("dq", "dk", "dv"), ("dk",), ("dv",), ("dq", "dv")])
+def test_missing_outputs_are_refused_by_the_library(missing):
+    x = _bwd_operands(2, 8)
+    for t in missing:
+        x[t] = None
+    with pytest.raises(dfa.DfaError) as e:
+        dfa.dfa_chunk_bwd(*(x[t] for t in ("q", "k", "v", "lse", "delta", "dO", "dq", "dk", "dv")), False, 1.0, stream=0)
+    assert e.value.status == -1
