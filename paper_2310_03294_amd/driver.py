@@ -204,7 +204,7 @@ def _forward_step(fwd, state, steps, bufs: Buffers):
     diag = [st for st in steps if st.kind == B.DFA_STEP_DIAG]
     own = [st for st in steps if st.kind == B.DFA_STEP_OWN]
     helped = [st for st in steps if st.kind == B.DFA_STEP_HELP]
-    parts = _partials(bufs, len(helped))
+    parts = _partials(bufs, len(helped)) if helped else []
     fwd.launch([(st.q_chunk, st.kv_chunk, state, st.q_chunk, False) for st in diag], True)
     fwd.launch([(st.q_chunk, st.kv_chunk, state, st.q_chunk, True) for st in own] +
                [(st.q_chunk, st.kv_chunk, fwd.dest(*part), 0, False) for st, part in zip(helped, parts)], False)

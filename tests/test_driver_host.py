@@ -111,3 +111,14 @@ def test_missing_outputs_are_refused_by_the_library(missing):
     with pytest.raises(dfa.DfaError) as e:
         dfa.dfa_chunk_bwd(*(x[t] for t in ("q", "k", "v", "lse", "delta", "dO", "dq", "dk", "dv")), False, 1.0, stream=0)
     assert e.value.status == -1
+
+
+@pytest.mark.parametrize("mode,P", [("ring", 4), (("window", 2), 4), ("balanced", 2)])
+def test_buffers_of_the_caller_without_partials(monkeypatch, no_launches, mode, P):
+    """A schedule without helpers needs no partial buffers: O and L of the caller's own are enough."""
+    monkeypatch.setattr(B, "dfa_delta", lambda *a, **k: None)
+    h, n, d = 2, 64, 64
+    q, k, v, do = (torch.zeros(h, n, d) for _ in range(4))
+    bufs = driver.Buffers(h, h, n, d, P, "cpu", outputs=False)
+    bufs.O, bufs.L = torch.zeros(h, n, d), torch.zeros(h, n)
+    driver.run_all_workers(q, k, v, do, 1.0, P, bufs, mode)
