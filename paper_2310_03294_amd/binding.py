@@ -272,18 +272,25 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+def _scratch(n):
+    """n bytes of device memory, or None where there are not as many: scratch makes a call faster, no call needs it."""
+    try:
+        return torch.empty(n, dtype=torch.uint8, device="cuda")
+    except torch.OutOfMemoryError:
+        return None
+
+
 def _workspace(n, stream):
     """Scratch of n bytes for one call on `stream`: (tensor or None, bytes).  It comes from the caching
     allocator of that stream, so that the stream's order protects it when it is let go after the call; a
     stream known by its handle alone gets none, unless it is the current one."""
-    if n <= 0:
-        return None, 0
-    if stream is None or _stream(stream) == _current_stream():
-        return torch.empty(n, dtype=torch.uint8, device="cuda"), n
-    if isinstance(stream, torch.cuda.Stream):
+    ws = None
+    if n > 0 and (stream is None or _stream(stream) == _current_stream()):
+        ws = _scratch(n)
+    elif n > 0 and isinstance(stream, torch.cuda.Stream):
         with torch.cuda.stream(stream):
-            return torch.empty(n, dtype=torch.uint8, device="cuda"), n
-    return None, 0
+            ws = _scratch(n)
+    return ws, 0 if ws is None else n
 
 
 def dfa_chunk_bwd(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale, accumulate=False, stream=None,

@@ -165,10 +165,14 @@ def helper_partials_for(Q, K, V, scale, P, w, bufs: Buffers):
 
 
 def _partials(bufs: Buffers, n):
-    """n partial (o, lse) buffers; kept in bufs, so that a later pass allocates nothing."""
-    while len(bufs.part_o) < n:
-        bufs.part_o.append(torch.empty_like(bufs.part_o[0]))
-        bufs.part_l.append(torch.empty_like(bufs.part_l[0]))
+    """n partial (o, lse) buffers, or as many as there is memory for (at least the first); kept in bufs, so that a later
+    pass allocates nothing.  A pass of all workers holds up to (P - 1) / 2 of them, half as much as O."""
+    try:
+        while len(bufs.part_o) < n:
+            part = torch.empty_like(bufs.part_o[0]), torch.empty_like(bufs.part_l[0])
+            bufs.part_o.append(part[0]); bufs.part_l.append(part[1])
+    except torch.OutOfMemoryError:
+        pass
     return list(zip(bufs.part_o, bufs.part_l))[:n]
 
 
@@ -204,11 +208,14 @@ def _forward_step(fwd, state, steps, bufs: Buffers):
     diag = [st for st in steps if st.kind == B.DFA_STEP_DIAG]
     own = [st for st in steps if st.kind == B.DFA_STEP_OWN]
     helped = [st for st in steps if st.kind == B.DFA_STEP_HELP]
-    parts = _partials(bufs, len(helped)) if helped else []
     fwd.launch([(st.q_chunk, st.kv_chunk, state, st.q_chunk, False) for st in diag], True)
-    fwd.launch([(st.q_chunk, st.kv_chunk, state, st.q_chunk, True) for st in own] +
-               [(st.q_chunk, st.kv_chunk, fwd.dest(*part), 0, False) for st, part in zip(helped, parts)], False)
-    B.dfa_merge_batch(bufs.O, bufs.L, bufs.c, [(st.send_to, *part) for st, part in zip(helped, parts)])
+    own = [(st.q_chunk, st.kv_chunk, state, st.q_chunk, True) for st in own]
+    parts = _partials(bufs, len(helped)) if helped else []
+    while own or helped:        # once, unless there are fewer partial buffers than helpers
+        now = list(zip(helped, parts))
+        fwd.launch(own + [(st.q_chunk, st.kv_chunk, fwd.dest(*part), 0, False) for st, part in now], False)
+        B.dfa_merge_batch(bufs.O, bufs.L, bufs.c, [(st.send_to, *part) for st, part in now])
+        own, helped = [], helped[len(now):]
 
 
 def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backward=True, fused=True):

@@ -122,3 +122,50 @@ def test_buffers_of_the_caller_without_partials(monkeypatch, no_launches, mode, 
     bufs = driver.Buffers(h, h, n, d, P, "cpu", outputs=False)
     bufs.O, bufs.L = torch.zeros(h, n, d), torch.zeros(h, n)
     driver.run_all_workers(q, k, v, do, 1.0, P, bufs, mode)
+
+
+def test_backward_without_memory_for_scratch(monkeypatch):
+    """Scratch that cannot be had is done without."""
+    def empty(*a, **k):
+        raise torch.OutOfMemoryError
+
+    monkeypatch.setattr(B, "_current_stream", lambda: 0)
+    monkeypatch.setattr(torch, "empty", empty)
+    assert B._workspace(1 << 20, None) == B._workspace(1 << 20, 0) == (None, 0)
+
+
+@pytest.mark.parametrize("extra", [0, 1, 100])
+@pytest.mark.parametrize("P", [3, 8, 11])
+def test_fewer_partials_than_helpers(monkeypatch, P, extra):
+    """Memory for `extra` more partial buffers than the first: every pair is still computed once, and no buffer is
+    written again before it is merged."""
+    h, c, d = 2, 4, 64
+    bufs = driver.Buffers(h, h, P * c, d, P, "cpu", grads=False)
+    like, left = torch.empty_like, [2 * extra]
+
+    def empty_like(t):
+        left[0] -= 1
+        if left[0] < 0:
+            raise torch.OutOfMemoryError
+        return like(t)
+
+    pairs, waiting = [], set()
+
+    def launch(self, items, causal, stream=None):
+        for q, kv, dest, _, _ in items:
+            pairs.append((q, kv))
+            if dest[4][0] is not bufs.O:
+                assert id(dest[4][0]) not in waiting
+                waiting.add(id(dest[4][0]))
+
+    def merge(o, lse, rows, parts, stream=None):
+        assert {id(ob) for _, ob, _ in parts} == waiting and len(waiting) == len(parts)
+        waiting.clear()
+
+    monkeypatch.setattr(torch, "empty_like", empty_like)
+    monkeypatch.setattr(B.ForwardChunks, "launch", launch)
+    monkeypatch.setattr(B, "dfa_merge_batch", merge)
+    q, k, v = (torch.zeros(h, P * c, d) for _ in range(3))
+    driver.run_all_workers(q, k, v, None, 1.0, P, bufs, backward=False)
+    assert sorted(pairs) == [(i, j) for i in range(P) for j in range(i + 1)] and not waiting
+    assert len(bufs.part_o) == len(bufs.part_l) == min(1 + extra, max(1, (P - 1) // 2))
