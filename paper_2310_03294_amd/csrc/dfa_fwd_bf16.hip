@@ -633,6 +633,10 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
 // LO (64 rows): the matrix pipes have room, so the weights enter the second product as two bf16 values, the
 // rounded weight and its remainder (o is then off by 2^-17 of a weight instead of 2^-9, for 1 us of 18 at 8 heads x 1024), and the row sums
 // are fp32 sums of the fp32 weights.  With 128 rows rounding and sums are those of the 128-row kernel.
+// A remainder is zero or negative as often as not: against an infinite value of V the two products give NaN, where the
+// rounded weight alone gives that infinity.  A workgroup that ends with a value that is not finite therefore walks over
+// its keys once more without the remainders.  (Looking for one takes 0.15 to 0.3 us of a call: 8 heads x 256 8.7 -> 9.0 us, x 1024
+// 18.4 -> 18.55; with both walks as one loop body the causal form spilled.)
 // ============================================================================================
 namespace split {
 
@@ -658,15 +662,9 @@ __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16
   const int kh = head / p.group;
   const int q0 = tq * BMS;
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rb = wave % RB, part = wave / RB;
-  const int r32 = lane & 31, hh = lane >> 5;
   const int q0w = q0 + rb * 32;
-  const int qrow = q0w + r32;
-  const bool qvalid = qrow < p.s_q;
-  const int a_base = tile_off(r32, hh);
-  const int g_base = gather_base(lane);
   const float c2 = p.scale * LOG2E;
 
   const char* kg = reinterpret_cast<const char*>(p.k + kh * p.kv_sh);
@@ -679,158 +677,207 @@ __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16
   constexpr bool ONE = RB * NS == 8 && SUB == 1;
   const int cw = wave & 3, sub = ONE ? 0 : wave >> 2;
   const bool v_copy = ONE && wave >= 4;
-  const TileLane tl = tile_lane(cw, lane, kv_rowbytes);
   const int last = p.s_k - 1;
   const int koff = sub * TILE_BYTES, voff = (SUB + sub) * TILE_BYTES;
-  // rows past the end are clamped to the last row (and masked); a sub-tile wholly past it likewise
-  tile_dma(v_copy ? vg : kg, kv_rowbytes, sub * BN, last, tl, smem + (v_copy ? voff : koff), cw, lane);
-  if (!ONE) tile_dma(vg, kv_rowbytes, sub * BN, last, tl, smem + voff, cw, lane);
 
-  bf16x8 qreg[8];
-  {
-    const __bf16* qp = p.q + head * p.q_sh + static_cast<int64_t>(qvalid ? qrow : 0) * p.q_ss + 8 * hh;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      uint4 raw = *reinterpret_cast<const uint4*>(qp + 16 * ks);
-      if (!qvalid) raw = make_uint4(0, 0, 0, 0);
-      qreg[ks] = __builtin_bit_cast(bf16x8, raw);
-    }
-  }
   f32x16 o[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 16; ++j) o[i][j] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;        // raw-score units; l_run: this lane's half of the row sum
-  if (p.accumulate && part == 0 && qvalid) {   // the state of the earlier chunks goes into the first part
-    const float L = p.lse[head * p.l_sh + qrow];
-    if (L > -INFINITY) {
-      m_run = L / p.scale;
-      l_run = hh == 0 ? 1.f : 0.f;
-      load_o(o, p, head, qrow, hh);
-    }
-  }
-  lds_dma_wait();
-  __syncthreads();
+  float m_run, l_run;                          // raw-score units; l_run: this lane's half of the row sum
+  int lane = threadIdx.x & 63;
 
-  for (int it = 0; it < ntiles; ++it) {
-    const int k0 = it * kKeys<NS>;
-    const char* buf = smem + (it & 1) * kTilesBytes<NS>;
-    char* nbuf = smem + ((it & 1) ^ 1) * kTilesBytes<NS>;
-    const int kn = (it + 1 < ntiles ? k0 + kKeys<NS> : k0) + sub * BN;
-    const TileCopy ck = tile_copy_plan(v_copy ? vg : kg, kv_rowbytes, kn, last, tl, nbuf + (v_copy ? voff : koff), cw, lane);
-    const TileCopy cv = tile_copy_plan(vg, kv_rowbytes, kn, last, tl, nbuf + voff, cw, lane);
-    const int kb0 = k0 + part * 32;            // this wavefront's 32 keys
-    const char* Ks = buf + (part >> 1) * TILE_BYTES;
-    const char* Vs = Ks + SUB * TILE_BYTES;
-    const int row = (part & 1) * 32 * kRowBytes;
-    if (kb0 < p.s_k && !(CAUSAL && kb0 > q0w + 31)) {
-      bf16x8 ka[4], gv[4];
-      f32x16 s;
+  // The walk over the keys.  REM: the weights' remainders too.
+  auto walk = [&](auto rem) {
+    constexpr bool REM = decltype(rem)::value;
+    if constexpr (LO) lane = static_cast<int>(lds_pin(lane));      // opaque: no walk keeps registers for the other
+    const int r32 = lane & 31, hh = lane >> 5;
+    const int qrow = q0w + r32;
+    const bool qvalid = qrow < p.s_q;
+    const int a_base = tile_off(r32, hh);
+    const int g_base = gather_base(lane);
+    const TileLane tl = tile_lane(cw, lane, kv_rowbytes);
+    // rows past the end are clamped to the last row (and masked); a sub-tile wholly past it likewise
+    tile_dma(v_copy ? vg : kg, kv_rowbytes, sub * BN, last, tl, smem + (v_copy ? voff : koff), cw, lane);
+    if (!ONE) tile_dma(vg, kv_rowbytes, sub * BN, last, tl, smem + voff, cw, lane);
+
+    bf16x8 qreg[8];
+    {
+      const __bf16* qp = p.q + head * p.q_sh + static_cast<int64_t>(qvalid ? qrow : 0) * p.q_ss + 8 * hh;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) s[j] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) ka[ks] = lds_read_b128(Ks, a_base + row + ks * 32);
-      DFA_SCHED_FENCE();
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {         // S^T = K Q^T
-        s = mfma32(ka[ks & 3], qreg[ks], s);
-        if (ks < 4) ka[ks & 3] = lds_read_b128(Ks, a_base + row + (ks + 4) * 32);
-        if (ks == 0) tile_copy_piece<0>(ck);
-        if (ks == 2) tile_copy_piece<1>(ck);
-        if (ks == 4) tile_copy_piece<2>(ck);
-        if (ks == 6) tile_copy_piece<3>(ck);
-        DFA_SCHED_FENCE();
+      for (int ks = 0; ks < 8; ++ks) {
+        uint4 raw = *reinterpret_cast<const uint4*>(qp + 16 * ks);
+        if (!qvalid) raw = make_uint4(0, 0, 0, 0);
+        qreg[ks] = __builtin_bit_cast(bf16x8, raw);
       }
-      if (cw == 0) { tile_copy_piece<4>(ck); if (!ONE) tile_copy_piece<4>(cv); }
+    }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) gv[i] = lds_gather(Vs, g_base + row + i * 64);
-      if (kb0 + 32 > p.s_k || (CAUSAL && kb0 + 31 > q0w)) {
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int kvi = kb0 + (j >> 2) * 8 + hh * 4 + (j & 3);
-          if (kvi >= p.s_k || (CAUSAL && kvi > qrow)) s[j] = -INFINITY;
-        }
-      }
-      // online softmax with the lazy running maximum of the 128-row kernel
-      float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
-#pragma unroll
-      for (int j = 3; j < 15; j += 2) mx = fmaxf(fmaxf(mx, s[j]), s[j + 1]);
-      mx = fmaxf(mx, s[15]);
-      float alpha = 1.f;
-      if (__any((mx - m_run) * c2 > 8.f)) {
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m_run, mx);
-        const float mc_new = (m_new == -INFINITY) ? 0.f : m_new * c2;
-        alpha = __builtin_amdgcn_exp2f(m_run * c2 - mc_new);
-        m_run = m_new;
-        l_run *= alpha;
-      }
-      const float mc = (m_run == -INFINITY) ? 0.f : m_run * c2;
-      float sum = 0.f;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], c2, -mc));
-        if (LO || CAUSAL) sum += s[j];
-      }
-      if (__any(alpha != 1.f)) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 16; ++j) o[i][j] *= alpha;
-      }
-      bf16x8 pb[2], pl[2];                     // the weights, and what rounding them to bf16 left over
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        pb[u] = pack8(s, 8 * u);
-        if constexpr (LO) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) s[8 * u + e] -= static_cast<float>(pb[u][e]);
-          pl[u] = pack8(s, 8 * u);
-        }
-        if (!LO && !CAUSAL) sum = sum8(pb[u], sum);
-      }
-      l_run += sum;
-      DFA_SCHED_FENCE();
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {            // O^T += V^T P^T
-        o[i & 3] = mfma32(gv[i & 3], pb[i >> 2], o[i & 3]);
-        if constexpr (LO) o[i & 3] = mfma32(gv[i & 3], pl[i >> 2], o[i & 3]);
-        if (i < 4) gv[i & 3] = lds_gather(Vs, g_base + row + 16 * kRowBytes + i * 64);
-        if (!ONE && i == 0) tile_copy_piece<0>(cv);
-        if (!ONE && i == 2) tile_copy_piece<1>(cv);
-        if (!ONE && i == 4) tile_copy_piece<2>(cv);
-        if (!ONE && i == 6) tile_copy_piece<3>(cv);
-        DFA_SCHED_FENCE();
-      }
-    } else {                                   // nothing for this wavefront: only its share of the copies
-      tile_copy_piece<0>(ck); tile_copy_piece<1>(ck); tile_copy_piece<2>(ck); tile_copy_piece<3>(ck);
-      if (cw == 0) tile_copy_piece<4>(ck);
-      if (!ONE) {
-        tile_copy_piece<0>(cv); tile_copy_piece<1>(cv); tile_copy_piece<2>(cv); tile_copy_piece<3>(cv);
-        if (cw == 0) tile_copy_piece<4>(cv);
+      for (int j = 0; j < 16; ++j) o[i][j] = 0.f;
+    m_run = -INFINITY; l_run = 0.f;
+    if (p.accumulate && part == 0 && qvalid) {   // the state of the earlier chunks goes into the first part
+      const float L = p.lse[head * p.l_sh + qrow];
+      if (L > -INFINITY) {
+        m_run = L / p.scale;
+        l_run = hh == 0 ? 1.f : 0.f;
+        load_o(o, p, head, qrow, hh);
       }
     }
     lds_dma_wait();
     __syncthreads();
-  }
 
+    for (int it = 0; it < ntiles; ++it) {
+      const int k0 = it * kKeys<NS>;
+      const char* buf = smem + (it & 1) * kTilesBytes<NS>;
+      char* nbuf = smem + ((it & 1) ^ 1) * kTilesBytes<NS>;
+      const int kn = (it + 1 < ntiles ? k0 + kKeys<NS> : k0) + sub * BN;
+      const TileCopy ck = tile_copy_plan(v_copy ? vg : kg, kv_rowbytes, kn, last, tl, nbuf + (v_copy ? voff : koff), cw, lane);
+      const TileCopy cv = tile_copy_plan(vg, kv_rowbytes, kn, last, tl, nbuf + voff, cw, lane);
+      const int kb0 = k0 + part * 32;            // this wavefront's 32 keys
+      const char* Ks = buf + (part >> 1) * TILE_BYTES;
+      const char* Vs = Ks + SUB * TILE_BYTES;
+      const int row = (part & 1) * 32 * kRowBytes;
+      if (kb0 < p.s_k && !(CAUSAL && kb0 > q0w + 31)) {
+        bf16x8 ka[4], gv[4];
+        f32x16 s;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) s[j] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) ka[ks] = lds_read_b128(Ks, a_base + row + ks * 32);
+        DFA_SCHED_FENCE();
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {         // S^T = K Q^T
+          s = mfma32(ka[ks & 3], qreg[ks], s);
+          if (ks < 4) ka[ks & 3] = lds_read_b128(Ks, a_base + row + (ks + 4) * 32);
+          if (ks == 0) tile_copy_piece<0>(ck);
+          if (ks == 2) tile_copy_piece<1>(ck);
+          if (ks == 4) tile_copy_piece<2>(ck);
+          if (ks == 6) tile_copy_piece<3>(ck);
+          DFA_SCHED_FENCE();
+        }
+        if (cw == 0) { tile_copy_piece<4>(ck); if (!ONE) tile_copy_piece<4>(cv); }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) gv[i] = lds_gather(Vs, g_base + row + i * 64);
+        if (kb0 + 32 > p.s_k || (CAUSAL && kb0 + 31 > q0w)) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const int kvi = kb0 + (j >> 2) * 8 + hh * 4 + (j & 3);
+            if (kvi >= p.s_k || (CAUSAL && kvi > qrow)) s[j] = -INFINITY;
+          }
+        }
+        // online softmax with the lazy running maximum of the 128-row kernel
+        float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
+#pragma unroll
+        for (int j = 3; j < 15; j += 2) mx = fmaxf(fmaxf(mx, s[j]), s[j + 1]);
+        mx = fmaxf(mx, s[15]);
+        float alpha = 1.f;
+        if (__any((mx - m_run) * c2 > 8.f)) {
+          mx = fmaxf(mx, __shfl_xor(mx, 32));
+          const float m_new = fmaxf(m_run, mx);
+          const float mc_new = (m_new == -INFINITY) ? 0.f : m_new * c2;
+          alpha = __builtin_amdgcn_exp2f(m_run * c2 - mc_new);
+          m_run = m_new;
+          l_run *= alpha;
+        }
+        const float mc = (m_run == -INFINITY) ? 0.f : m_run * c2;
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], c2, -mc));
+          if (LO || CAUSAL) sum += s[j];
+        }
+        if (__any(alpha != 1.f)) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) o[i][j] *= alpha;
+        }
+        bf16x8 pb[2], pl[2];                     // the weights, and what rounding them to bf16 left over
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          pb[u] = pack8(s, 8 * u);
+          if constexpr (REM) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s[8 * u + e] -= static_cast<float>(pb[u][e]);
+            pl[u] = pack8(s, 8 * u);
+          }
+          if (!LO && !CAUSAL) sum = sum8(pb[u], sum);
+        }
+        l_run += sum;
+        DFA_SCHED_FENCE();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {            // O^T += V^T P^T
+          o[i & 3] = mfma32(gv[i & 3], pb[i >> 2], o[i & 3]);
+          if constexpr (REM) o[i & 3] = mfma32(gv[i & 3], pl[i >> 2], o[i & 3]);
+          if (i < 4) gv[i & 3] = lds_gather(Vs, g_base + row + 16 * kRowBytes + i * 64);
+          if (!ONE && i == 0) tile_copy_piece<0>(cv);
+          if (!ONE && i == 2) tile_copy_piece<1>(cv);
+          if (!ONE && i == 4) tile_copy_piece<2>(cv);
+          if (!ONE && i == 6) tile_copy_piece<3>(cv);
+          DFA_SCHED_FENCE();
+        }
+      } else {                                   // nothing for this wavefront: only its share of the copies
+        tile_copy_piece<0>(ck); tile_copy_piece<1>(ck); tile_copy_piece<2>(ck); tile_copy_piece<3>(ck);
+        if (cw == 0) tile_copy_piece<4>(ck);
+        if (!ONE) {
+          tile_copy_piece<0>(cv); tile_copy_piece<1>(cv); tile_copy_piece<2>(cv); tile_copy_piece<3>(cv);
+          if (cw == 0) tile_copy_piece<4>(cv);
+        }
+      }
+      lds_dma_wait();
+      __syncthreads();
+    }
+  };
   // combine the parts of a row block in part 0, against the largest of their reference maxima
-  float l_tot = l_run + __shfl_xor(l_run, 32);
   float* st = reinterpret_cast<float*>(smem + RB * (NS - 1) * RES_BYTES);      // (m, l) per part and row
-  if (part > 0) {
-    float* x = reinterpret_cast<float*>(smem + (wave - RB) * RES_BYTES) + lane;
+  float l_tot;
+  auto leave = [&] {
+    l_tot = l_run + __shfl_xor(l_run, 32);
+    if (part > 0) {
+      float* x = reinterpret_cast<float*>(smem + (wave - RB) * RES_BYTES) + lane;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) x[(i * 16 + j) * 64] = o[i][j];
-    if (hh == 0) { st[wave * 64 + r32] = m_run; st[wave * 64 + 32 + r32] = l_tot; }
+        for (int j = 0; j < 16; ++j) x[(i * 16 + j) * 64] = o[i][j];
+      if (lane < 32) { st[wave * 64 + lane] = m_run; st[wave * 64 + 32 + lane] = l_tot; }
+    }
+  };
+  float m;                                     // the largest reference
+  auto largest = [&] {
+    m = m_run;
+#pragma unroll
+    for (int s = 1; s < NS; ++s) m = fmaxf(m, st[(s * RB + rb) * 64 + (lane & 31)]);
+  };
+  walk(std::bool_constant<LO>{});
+  leave();
+  if constexpr (LO) {
+    int* odd = reinterpret_cast<int*>(st + RB * NS * 64);          // per wavefront: a value is not finite
+    float top[4] = {0.f, 0.f, 0.f, 0.f};       // of the magnitudes; maximum() hands on what is no number
+#pragma unroll
+    for (int j = 0; j < 16; j += 2)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        top[i] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(top[i], fabsf(o[i][j])), fabsf(o[i][j + 1]));
+    odd[wave] = __any(!(__builtin_elementwise_maximum(__builtin_elementwise_maximum(top[0], top[1]),
+                                                      __builtin_elementwise_maximum(top[2], top[3])) < INFINITY));
+    __syncthreads();
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < RB * NS; ++w) any |= odd[w];
+    largest();
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(any), 0)) {
+      __syncthreads();                         // the tiles go where the results are
+      walk(std::false_type{});
+      leave();
+      __syncthreads();
+      largest();
+    }
+  } else {
+    __syncthreads();
+    largest();
   }
-  __syncthreads();
   if (part > 0) return;
-  float m = m_run;
-#pragma unroll
-  for (int s = 1; s < NS; ++s) m = fmaxf(m, st[(s * RB + rb) * 64 + r32]);
+  const int r32 = lane & 31, hh = lane >> 5;
+  const int qrow = q0w + r32;
+  const bool qvalid = qrow < p.s_q;
   const float mc = (m == -INFINITY) ? 0.f : m * c2;
   const float f0 = __builtin_amdgcn_exp2f(m_run * c2 - mc);
   l_tot *= f0;

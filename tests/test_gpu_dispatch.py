@@ -101,6 +101,30 @@ def test_bf16_forward_parts_far_apart(shape):
         assert maxerr(o, O) <= 2e-2 and maxerr(lse, L) <= 2e-2 + 2.0 ** -20 * abs(L).max()
 
 
+@pytest.mark.parametrize("shape", FWD_FORMS)
+def test_bf16_forward_infinite_values(shape):
+    """A key whose value is infinite gives that infinity to every row that sees it, and NaN where two of them meet; the
+    other columns keep their values.  (The key is one that every row sees, and no last one of a ragged chunk.)"""
+    h_q, h_kv, s_q, s_k, causal = shape
+    d, tol, inf = 128, TOL[torch.bfloat16], float("inf")
+    q, k, v, _ = case(5500 + s_q + s_k, h_q, h_kv, s_q, s_k, d, torch.bfloat16)
+    scale = d ** -0.5
+    O, L = A.attention_fwd(np64(q), np64(k), np64(v), scale, causal=causal)
+    j = 0 if causal else s_k // 2
+    v[:, j, 5], v[:, j, 70], v[:, j, 100] = inf, -inf, inf
+    if not causal:
+        v[:, j + 3, 100] = -inf
+    Q, K, V = (t.to(dev()) for t in (q, k, v))
+    o, lse = dfa.dfa_chunk_fwd(Q, K, V, causal, scale)
+    for again in (False, True):
+        if again:
+            dfa.dfa_chunk_fwd_acc(Q, K, V, causal, scale, o, lse)
+        assert bool((o[..., 5] == inf).all()) and bool((o[..., 70] == -inf).all())
+        assert bool((o[..., 100] == inf).all() if causal else o[..., 100].isnan().all())
+        rest = [c for c in range(d) if c not in (5, 70, 100)]
+        assert maxerr(o[..., rest], O[..., rest]) <= tol and maxerr(lse, L + (math.log(2) if again else 0)) <= tol
+
+
 # bf16 backward: dq by 128-row workgroups with two key parts or by 256-row ones, next to the dk/dv workgroups.
 BWD_FORMS = [
     # h_q, h_kv, s_q, s_k, causal
