@@ -3,6 +3,7 @@ each form, with remainders on both axes, against the fp64 oracle (bounds as in t
 import ctypes
 import math
 
+import numpy as np
 import pytest
 import torch
 
@@ -267,3 +268,22 @@ def test_f32_backward_shares(shape, d):
                               accumulate=acc)
             for i in (0, 1, 2) if want_dq else (1, 2):
                 assert maxerr(got[i], want[i] + (0.5 if acc else 0.0)) <= bound[i]
+
+
+def test_f32_dq_of_a_long_walk():
+    """dq over 16384 keys, from the exact logsumexp and D.  A rounding is off by 2^-24 / sqrt(3) = 3.4e-8 (rms) of the partial
+    sum that it rounds, which over a chain of n steps of like size makes 3.4e-8 sqrt(n / 2) of the sum.  Scores and dP (64
+    steps each), the exponential and the factors make about 5e-7 of every term, and so of the sum; a wavefront's 4096 keys
+    in one chain of 2048 steps would add 1.1e-6, sums of 64 keys each (32 steps, then 64 more) add 2.5e-7.  The bound lies
+    between the two totals."""
+    h_q, h_kv, s_q, s_k, d = 2, 1, 300, 16384, 128
+    scale = d ** -0.5
+    q, k, v, do = case(9900, h_q, h_kv, s_q, s_k, d, torch.float32)
+    x64 = [np64(t) for t in (q, k, v, do)]
+    O, L = A.attention_fwd(*x64[:3], scale, causal=False)
+    want = A.attention_bwd(*x64, scale, causal=False)[0]
+    Q, K, V, dO = (t.to(dev()) for t in (q, k, v, do))
+    lse = torch.from_numpy(L).float().to(dev())
+    delta = torch.from_numpy(A.delta_rows(O, x64[3])).float().to(dev())
+    dq = dfa.dfa_chunk_bwd(Q, K, V, lse, delta, dO, torch.empty_like(Q), None, None, False, scale)[0]
+    assert np.linalg.norm(np64(dq) - want) <= 9e-7 * np.linalg.norm(want)
