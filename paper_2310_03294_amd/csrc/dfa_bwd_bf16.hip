@@ -890,16 +890,16 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
     if (!make_items(p.q_items, sh.s_q, pl.split ? 128 : 256, sh.h_q, n, sh.causal)) return DFA_ERR_SHAPE;
     const int64_t blocks = xcd_blocks(p.kv_items.map) + xcd_blocks(p.q_items.map);
     // Ten rounds of workgroups and more: nothing is left to fill, and each kind alone has the better use of
-    // the L2 (32 heads x 12000 6775 against 6808 us).  (Nor would a grid take more than 2^23 of them.)
+    // the L2 (32 heads x 12000 6775 against 6808 us).  (Nor would a grid take more than 2^23 of them.)  A list stays
+    // a list: eight diagonal pairs of 32 heads x 2048 take 1374 us as sixteen launches, 1171 as two, 1205 as one; sixteen of
+    // 8 heads x 4096 3066 / 1881 / 1933, full pairs 3585 / 3341 / 3338.
     if (p.kv_items.map.total >= 2560) {
-      for (int i = 0; i < n; ++i) {
-        dfa_bwd_pair a = pairs[i], b = pairs[i];
-        a.dq = nullptr; b.dk = b.dv = nullptr;
-        int rc = launch_bwd_bf16(sh, &a, 1, nullptr, 0, st);
-        if (!rc) rc = launch_bwd_bf16(sh, &b, 1, nullptr, 0, st);
-        if (rc) return rc;
-      }
-      return DFA_OK;
+      dfa_bwd_pair side[MAX_PAIRS];
+      for (int i = 0; i < n; ++i) { side[i] = pairs[i]; side[i].dq = nullptr; }
+      const int rc = launch_bwd_bf16(sh, side, n, nullptr, 0, st);
+      if (rc) return rc;
+      for (int i = 0; i < n; ++i) { side[i] = pairs[i]; side[i].dk = side[i].dv = nullptr; }
+      return launch_bwd_bf16(sh, side, n, nullptr, 0, st);
     }
     const int rc = with(n > 1, [&](auto m) {
       constexpr int NP = m() ? MAX_PAIRS : 1;
