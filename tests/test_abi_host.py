@@ -159,3 +159,61 @@ def test_empty_query_chunk_is_noop(lib):
     sh = _shape(s_q=0, lse_stride_h=0)
     assert lib.dfa_chunk_fwd(ctypes.byref(sh), FAKE, FAKE, FAKE, FAKE, FAKE, None) == 0
     assert lib.dfa_delta(ctypes.byref(sh), FAKE, FAKE, FAKE, None) == 0
+
+
+def test_list_entry_points_reject_bad_arguments_before_any_launch(lib):
+    sh = _shape()
+
+    def fwd(n=1, shape=sh, **kw):
+        p = dict(q=FAKE, k=FAKE, v=FAKE, o=FAKE, lse=FAKE, o_stride_h=64 * 64, o_stride_s=64, lse_stride_h=64)
+        pairs = (B.DfaFwdPair * 2)(B.DfaFwdPair(**p), B.DfaFwdPair(**{**p, **kw}))
+        return lib.dfa_chunk_fwd_batch(ctypes.byref(shape), pairs, n, None)
+
+    assert fwd(-1) == -4 and fwd(0) == 0
+    assert lib.dfa_chunk_fwd_batch(ctypes.byref(sh), None, 1, None) == -1
+    assert lib.dfa_chunk_fwd_batch(None, None, 1, None) == -1
+    for kw, code in ((dict(q=None), -1), (dict(lse=None), -1), (dict(k=None), -1), (dict(o=FAKE + 8), -2), (dict(v=FAKE + 2), -2),
+                     (dict(o_stride_s=60), -2), (dict(o_stride_h=-8), -2), (dict(lse_stride_h=63), -2)):
+        assert fwd(2, **kw) == code, kw                # the second pair is looked at too
+    assert fwd(2, shape=_shape(s_q=0), lse_stride_h=0) == 0
+
+    def bwd(n=1, shape=sh, ws=None, ws_bytes=0, **kw):
+        p = {t: FAKE for t in ("q", "k", "v", "lse", "delta", "dO", "dq", "dk", "dv")}
+        pairs = (B.DfaBwdPair * 2)(B.DfaBwdPair(**p), B.DfaBwdPair(**{**p, **kw}))
+        return lib.dfa_chunk_bwd_batch(ctypes.byref(shape), pairs, n, ws, ws_bytes, None)
+
+    assert bwd(-1) == -4 and bwd(0) == 0
+    assert lib.dfa_chunk_bwd_batch(ctypes.byref(sh), None, 1, None, 0, None) == -1
+    for kw, code in ((dict(dO=None), -1), (dict(delta=None), -1), (dict(dk=None), -1), (dict(dv=None), -1),
+                     (dict(dq=None, dk=None, dv=None), -1), (dict(dq=None), -4), (dict(dk=None, dv=None), -4),
+                     (dict(dq=FAKE + 4), -2), (dict(dv=FAKE + 8), -2)):
+        assert bwd(2, **kw) == code, kw
+    assert bwd(1, ws=FAKE, ws_bytes=-1) == -4 and bwd(1, ws=FAKE + 4, ws_bytes=1 << 20) == -2
+    assert bwd(2, shape=_shape(s_q=0, s_k=0, lse_stride_h=0)) == 0
+
+    m = B.DfaMergeDesc(heads=2, rows=8, d=64, o_dtype=B.DFA_F32, a_stride_h=512, a_stride_s=64, lse_a_stride_h=8,
+                       b_stride_h=512, b_stride_s=64, lse_b_stride_h=8)
+
+    def merge(n=1, **kw):
+        p = dict(o_a=FAKE, lse_a=FAKE, o_b=FAKE * 2, lse_b=FAKE * 2)
+        pairs = (B.DfaMergePair * 2)(B.DfaMergePair(**p), B.DfaMergePair(**{**p, **kw}))
+        return lib.dfa_merge_batch(ctypes.byref(m), pairs, n, None)
+
+    assert merge(-1) == -4 and merge(0) == 0 and lib.dfa_merge_batch(ctypes.byref(m), None, 1, None) == -1
+    for kw, code in ((dict(o_b=None), -1), (dict(lse_a=None), -1), (dict(o_a=FAKE + 4), -2), (dict(o_b=FAKE), -4),
+                     (dict(lse_b=FAKE), -4)):
+        assert merge(2, **kw) == code, kw
+
+
+def test_workspace_query(lib):
+    """A pure host function: refused shapes, calls that need none, and never more than 128 MiB."""
+    ask = lambda n=1, dq=1, dkv=1, **kw: lib.dfa_chunk_bwd_workspace(ctypes.byref(_shape(**kw)), n, dq, dkv)
+    assert ask(d=96) == -2 and ask(reserved=1) == -4 and ask(-1) == -4 and lib.dfa_chunk_bwd_workspace(None, 1, 1, 1) == -1
+    grouped = dict(h_q=8, h_kv=1, s_q=512, s_k=512)
+    assert ask(0, **grouped) == 0 and ask(s_q=0, **{k: v for k, v in grouped.items() if k != "s_q"}) == 0
+    assert ask(dkv=0, **grouped) == 0                  # dq alone has no sums to share
+    for dtype, d in ((B.DFA_F32, 64), (B.DFA_F32, 128), (B.DFA_BF16, 128)):
+        seen = [ask(n, dtype=dtype, d=d, h_q=h_q, h_kv=h_kv, s_q=s, s_k=s, causal=causal)
+                for n in (1, 4, 16, 40) for h_q, h_kv in ((1, 1), (8, 1), (8, 2), (32, 8), (32, 32), (64, 1))
+                for s in (1, 100, 1000, 5000, 70000) for causal in (0, 1)]
+        assert max(seen) > 0 and min(seen) == 0 and max(seen) <= 128 << 20

@@ -88,6 +88,59 @@ def test_bf16_forward_forms_long_causal(h_q, s):
         assert maxerr(o[h, rows], O) <= tol and maxerr(lse[h, rows], L) <= 1e-4
 
 
+WIDE = [(120, 120, 300, 1061, False), (22, 1, 6144, 6144, True)]      # 256-row workgroups, full and diagonal
+
+
+@pytest.mark.parametrize("shape", WIDE)
+def test_bf16_forward_wide_continues(shape):
+    """256-row workgroups from a state that another chunk left, with fp32 and bf16 output, by sampled rows."""
+    h_q, h_kv, s_q, s_k, causal = shape
+    d, tol = 128, TOL[torch.bfloat16]
+    q, k, v, _ = case(6500 + s_q, h_q, h_kv, s_q, s_k, d, torch.bfloat16)
+    g = torch.Generator().manual_seed(3)
+    o0, lse0 = (0.1 * torch.randn(h_q, s_q, d, generator=g)).to(torch.bfloat16), torch.randn(h_q, s_q, generator=g) + 6
+    lse0[:, ::5] = -math.inf                 # rows that have seen nothing yet: their o counts for nothing
+    rows = sorted({0, 1, 5, 31, 32, 63, 64, 65, 255, 256, 257, s_q // 2, s_q - 44, s_q - 2, s_q - 1})
+    for o_dtype in (torch.float32, torch.bfloat16):
+        o, lse = o0.to(o_dtype).to(dev()), lse0.to(dev())
+        dfa.dfa_chunk_fwd_acc(*(t.to(dev()) for t in (q, k, v)), causal, d ** -0.5, o, lse)
+        for h in (0, h_q // 2, h_q - 1):
+            kv = h * h_kv // h_q
+            want = _sampled(q, k, v, h, kv, rows, d ** -0.5, causal)
+            want = A.merge(np64(o0[h, rows]), np64(lse0[h, rows]), *want)
+            assert maxerr(o[h, rows], want[0]) <= tol and maxerr(lse[h, rows], want[1]) <= tol
+
+
+def _sampled(q, k, v, h, kv, rows, scale, causal):
+    if causal:
+        return A.rows_fwd(np64(q[h, rows]), rows, np64(k[kv]), np64(v[kv]), scale)
+    O, L = A.attention_fwd(np64(q[h:h + 1, rows]), np64(k[kv:kv + 1]), np64(v[kv:kv + 1]), scale, causal=False)
+    return O[0], L[0]
+
+
+@pytest.mark.parametrize("top", [150.0, 4000.0])
+@pytest.mark.parametrize("shape", WIDE)
+def test_bf16_forward_wide_reference_jumps(shape, top):
+    """256-row workgroups on scores that jump from one 64-key tile to the next by more than the reference may lag behind
+    (2^14 in the exp2 domain): tiles are redone against a moved reference.  Tiles in random order, so that some tower
+    over all before them and others lie far below."""
+    h_q, h_kv, s_q, s_k, causal = shape
+    d, tol, scale = 128, TOL[torch.bfloat16], 128 ** -0.5
+    q, k, v, _ = case(6600 + s_q, h_q, h_kv, s_q, s_k, d, torch.bfloat16)
+    g = torch.Generator().manual_seed(11)
+    u = torch.ones(d) / d ** 0.5
+    ramp = torch.linspace(0.0, top, s_k)
+    order = torch.randperm((s_k + 63) // 64, generator=g)
+    ramp = torch.cat([ramp[i * 64:(i + 1) * 64] for i in order.tolist()]).view(1, s_k, 1)
+    q, k = (q + 4.0 * u).to(torch.bfloat16), (0.3 * k + ramp * u).to(torch.bfloat16)
+    o, lse = dfa.dfa_chunk_fwd(*(t.to(dev()) for t in (q, k, v)), causal, scale)
+    rows = sorted({0, 63, 64, 127, 128, 255, 256, 299, s_q // 3, s_q // 2, s_q - 65, s_q - 1})
+    for h in (0, h_q // 2, h_q - 1):
+        O, L = _sampled(q, k, v, h, h * h_kv // h_q, rows, scale, causal)
+        # lse is formed in fp32 from scores of its own size: 2^-17 of it
+        assert maxerr(o[h, rows], O) <= tol and maxerr(lse[h, rows], L) <= max(tol, abs(L).max() * 2.0 ** -17)
+
+
 @pytest.mark.parametrize("shape", [(4, 4, 64, 640, False), (4, 4, 640, 640, True)])
 def test_bf16_forward_parts_far_apart(shape):
     """Parts of the keys whose scores differ by hundreds: the other parts' weights underflow."""
