@@ -682,6 +682,9 @@ int bwd(F32BwdParams p, hipStream_t st) {
 //   8 / 2 heads x 1024 rows 1183 / 647 / 371,  32 x 256 87 / 57 / 72,  32 x 1024 547 / 604 / 725,
 //   32 x 4096 8370 / 9210 / 11380 (82 TFLOP/s with 1);  shared, 8 / 2 x 1024 178, x 2048 1310 -> 623, four
 //   diagonal chunks of 1024 1220 -> 443.
+// At d = 128 the 4-part form with a shared walk spills 53 registers and takes longer than estimated (8 / 2 x 256 44 us
+// for 35).  Where it is chosen it is the better form all the same: 4 against 2 parts 44 / 45 there, 8 / 2 x 512 diagonal
+// 58 / 78, 4 / 1 x 768 75 / 109, x 1024 129 / 141, x 1536 diagonal 206 / 205.
 // The vector-FMA kernel this one replaced (dq by atomics) took 2.9 ms at 8 / 2 x 1024.
 struct Plan { int parts, shares; double us; };
 

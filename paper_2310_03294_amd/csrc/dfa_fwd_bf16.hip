@@ -98,8 +98,8 @@ __device__ __forceinline__ void store_o(const f32x16 (&o)[4], const FwdParams& p
     }
 }
 
-// CAUSAL: the diagonal pair.  Its row sums are taken over the fp32 weights; those of a full pair over the
-// bf16-rounded weights that multiply V, as in the other full-pair forms.
+// FULL: a full pair.  Its row sums are taken over the bf16-rounded weights that multiply V, those of the diagonal pair
+// over the fp32 weights (the same in the other forms of 128 and 256 rows).
 template <bool FULL, class Args>
 __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
   extern __shared__ __align__(16) char smem[];   // two (K tile, V tile) buffers

@@ -34,7 +34,10 @@ int64_t bwd_bf16_workspace(const dfa_shape& sh, int n, bool dq, bool dk);
 // one: fp32 backward of 32 heads x 4096, d = 128, 7.2 ms against 4.8.)
 // snake: causal calls of one or two heads, where a range would hold long or short tiles only: ids in rows of
 // eight, every second row backwards, give each XCD the same mix (fp32 backward of one head x 4096 495 -> 387 us,
-// 2 over 1 heads 743 -> 675; from four heads on ranges are the better ones: 4 heads 938 against 1162).
+// 2 over 1 heads 743 -> 675; from four heads on ranges are the better ones: 4 heads 938 against 1162).  bf16, ranges
+// against this: forward of one head x 16384 221 / 215 us, x 32768 800 / 515, of two heads x 4096 54 / 58, x 16384 383 / 282, x
+// 32768 956 / 704; backward of one head x 16384 348 / 354, x 32768 1225 / 927, of two x 16384 553 / 592, x 32768 2270 / 1890;
+// no difference below 4096 rows.
 struct XcdMap { int total, per_xcd, snake; };
 inline XcdMap xcd_map(int64_t total, int causal, int64_t groups) {
   return XcdMap{static_cast<int>(total), static_cast<int>((total + 7) / 8), causal && groups <= 2};
