@@ -946,19 +946,24 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
     if (n64 <= 256 || (n64 <= 512 && sh.s_q >= 2048)) parts = 4;
     wide = n256 >= 512 && sh.s_q >= 6144 && sh.s_k % BN == 0;
     // Two parts per tile where the 128-row form's longest walk decides: 16 heads x 2500 59 -> 51 us, x 4096
-    // 117 -> 96, 8 x 6000 131 -> 112; not where short walks share the CUs anyway (32 x 1500 45 -> 49).
-    two = n128 <= 352 || (n128 <= 512 && sh.s_q > 2048);
+    // 117 -> 96, 8 x 6000 131 -> 112; not where short walks share the CUs anyway (32 x 1500 45 -> 49).  It is one workgroup
+    // per CU, so more than 256 of them need the longer walks: 24 x 1500 (288) 37.5 -> 33.7, 32 x 1300 (352) 43 -> 41, but
+    // 40 x 1024 (320) 36.8 -> 40.4, 64 x 566 (320) 21.2 -> 25.8; and fewer than that gain nothing below 1024 rows: 32 x 1024
+    // 26.3 -> 26.2, x 700 18.8 -> 19.3, 64 x 384 14.8 -> 15.5.
+    two = sh.s_q >= 1024 && n128 <= (sh.s_q > 2048 ? 512 : sh.s_q >= 1280 ? 352 : 256);
   } else {
     // One round of 64-row workgroups at most: split the keys.  The 128-row form (10 % slower per row, two
     // workgroups per CU) where it needs one workgroup per CU at most, or where the last round of 256-row
     // workgroups would be half empty or worse.
     if (n64 <= 256) parts = 4;
     // Two parts per tile where the 128-row form would have one wavefront per SIMD (8 heads x 2777 57 -> 46 us, x
-    // 4096 82 -> 72; 32 x 1024 27.4 -> 25.1), and up to two rounds of 256-row workgroups where that form is
-    // no better (16 x 5500 280 -> 265, 32 x 2777 151 -> 148; 32 x 5120, three rounds, 419 -> 434).
+    // 4096 82 -> 72; 32 x 1024 27.4 -> 25.1), and for long walks up to two rounds of 256-row workgroups where that form is
+    // no better (16 x 5500 282 -> 265, 24 x 3300 171 -> 165, 32 x 2777 156.5 -> 155.5; 32 x 5120, three rounds, 419 -> 434).  Up to
+    // 2048 keys one part is the better: 64 x 1300 76 against 80 (256 rows: 81.5), 32 x 2700 x 2000 109 against 111 (116),
+    // 128 x 700 x 500 41 against 46 (43).
     const int64_t last_round = n256 % 256;
     wide = n128 > 256 && !(n256 > 256 && n256 < 768 && last_round > 0 && last_round <= 128);
-    two = n256 < 512;
+    two = n128 <= 256 || (n256 < 512 && sh.s_k > 2048);
   }
   if (parts && sh.s_k <= 384) parts = 2;      // three 128-key tiles at most: the smaller tiles start sooner
   if (n128 > (1 << 30) && (sh.causal || n > 1)) return DFA_ERR_SHAPE;

@@ -44,10 +44,12 @@ FWD_FORMS = [
     (3, 3, 70, 1153, False),
     (96, 32, 190, 300, False),    # 128 rows (288 64-row workgroups)
     (130, 130, 300, 333, False),  # 128 rows: 260 256-row workgroups would leave a last round of 4
+    (130, 65, 300, 2111, False),  # the same with 2 parts: more than 2048 keys
     (200, 100, 300, 129, False),  # 256 rows, last round of 144
     (4, 2, 200, 200, True),       # 64 rows, 2 parts
     (4, 2, 450, 450, True),       # 64 rows, 4 parts
-    (70, 35, 260, 260, True),     # 128 rows, 2 parts: 210 workgroups
+    (70, 35, 260, 260, True),     # 128 rows: 210 short workgroups
+    (16, 4, 1090, 1090, True),    # 128 rows, 2 parts: 144 workgroups
     (130, 65, 270, 270, True),    # 128 rows: 390
     (96, 32, 129, 33, False),     # 128 rows, 2 parts (288 64-row workgroups): a part with one key
     (88, 44, 140, 31, False),     # the same, the second part without keys

@@ -33,7 +33,8 @@ FWD = [
     (BF16, 32, 32, 300, 4, False),    # 256 rows, ragged
     (BF16, 32, 8, 320, 4, False),     # 256 rows, whole tiles
     (BF16, 4, 2, 450, 4, True),       # 64 rows, 4 key parts
-    (BF16, 16, 4, 300, 4, True),      # 128 rows, 2 key parts
+    (BF16, 16, 4, 300, 4, True),      # 128 rows
+    (BF16, 8, 2, 1100, 3, True),      # 128 rows, 2 key parts: 216 workgroups
     (BF16, 32, 32, 300, 4, True),     # 128 rows: 384 workgroups
     (BF16, 3, 1, 70, 19, True),       # more pairs than a launch takes
     (F32, 40, 20, 150, 4, False),     # 2 parts
