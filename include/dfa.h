@@ -167,8 +167,9 @@ int dfa_delta(const dfa_shape* sh, const void* o, const void* dO, float* delta, 
  *   gives dq only (so a worker can send one while the other is still being computed); dk
  *   and dv are given together; all three NULL is DFA_ERR_NULL.
  * No path uses atomics: the summation order is fixed and repeated calls agree bit for bit.
- * This call has no scratch.  With grouped heads and few key tiles, dfa_chunk_bwd_batch of one pair with
- * a workspace divides the work further and is up to 2.5 times as fast.
+ * This call has no scratch.  With grouped heads and few key tiles, and in fp32 with a few query rows
+ * against many keys, dfa_chunk_bwd_batch of one pair with a workspace divides the work further and is
+ * several times as fast.
  */
 int dfa_chunk_bwd(const dfa_shape* sh, const void* q, const void* k, const void* v,
                   const float* lse, const float* delta, const void* dO,

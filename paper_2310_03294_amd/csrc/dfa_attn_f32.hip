@@ -54,6 +54,8 @@ struct F32Params {
   XcdMap map_kv, map_q;        // workgroups of all pairs; the forward's are map_q
   int shares;                  // dk, dv: workgroups that share the query tiles of a row block
   float* partial;              // shares > 1: their sums, 2 D floats per key row
+  int q_shares;                // dq: workgroups that share the key tiles of a row block
+  float* q_partial;            // q_shares > 1: their sums, D floats per query row
   float scale;
   int64_t q_sh, q_ss, kv_sh, kv_ss, o_sh, o_ss, l_sh, dq_sh, dq_ss, dkv_sh, dkv_ss;
 };
@@ -469,24 +471,30 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
 }
 
 // dq of one workgroup's query rows: Q and dO rows in registers, K / V tiles in LDS.
+// q_shares > 1: its share of the key tiles only, k_reduce_f32 adds the shares up.
 template <int D, int NS>
-__device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int item, float* smem) {
+__device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int item, float* partial, float* smem) {
   constexpr int NR = 4 / NS, NB = D / 32, LD = D + 4, BK = 32 * NS;
   float* Ks = smem;
   float* Vs = Ks + BK * LD;
   const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rb = wave % NR, part = wave / NR;
-  const int h = item / p.nx_q, kh = h / p.group;
+  const int share = item / p.nx_q % p.q_shares, h = item / p.nx_q / p.q_shares, kh = h / p.group;
   int xq = item % p.nx_q;
   if (p.causal) xq = p.nx_q - 1 - xq;
   const int q0 = xq * NR * 32, q0w = q0 + rb * 32, qrow = q0w + r32;
   const bool qvalid = qrow < p.s_q;
   const float* kg = pr.k + kh * p.kv_sh;
   const float* vg = pr.v + kh * p.kv_sh;
-  const int k_end = p.causal ? min(p.s_k, q0 + NR * 32) : p.s_k;
+  int k_end = p.causal ? min(p.s_k, q0 + NR * 32) : p.s_k, k_begin = 0;
+  if (p.q_shares > 1) {
+    const int64_t ntk = (k_end + BK - 1) / BK;
+    k_begin = static_cast<int>(ntk * share / p.q_shares) * BK;
+    k_end = min(k_end, static_cast<int>(ntk * (share + 1) / p.q_shares) * BK);
+  }
 
   TilePair<D, BK> tile;
-  tile.load(kg, vg, p.kv_ss, 0, p.s_k);
+  tile.load(kg, vg, p.kv_ss, k_begin, p.s_k);
   f32x4 q[D / 8], g[D / 8];
   load_rows<D>(q, pr.q + h * p.q_sh, p.q_ss, qrow, qvalid, hh);
   load_rows<D>(g, pr.dO + h * p.q_sh, p.q_ss, qrow, qvalid, hh);
@@ -498,10 +506,10 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int i
   constexpr int RUN = 2;
   f32x16 dq[NB], run[NB];
   zero(dq);
-  for (int k0 = 0; k0 < k_end;) {
+  for (int k0 = k_begin; k0 < k_end;) {
     zero(run);
     for (int n = 0; n < RUN && k0 < k_end; ++n, k0 += BK) {
-      if (k0) __syncthreads();
+      if (k0 > k_begin) __syncthreads();
       tile.store(Ks, Vs, k0, p.s_k);
       __syncthreads();
       if (k0 + BK < k_end) tile.load(kg, vg, p.kv_ss, k0 + BK, p.s_k);
@@ -536,6 +544,18 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int i
 #pragma unroll
     for (int s = 1; s < NS; ++s) add_result<NB>(smem + (s * NR + rb) * NV * 64, dq, lane, 1.f);
   }
+  if (p.q_shares > 1) {
+    typedef typename Run<NB>::type run_t;
+    run_t* x = reinterpret_cast<run_t*>(partial) + rb * 16 * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      run_t a;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) a[j] = dq[j][i];
+      x[i * 64] = a;
+    }
+    return;
+  }
   if (!qvalid) return;
   write_grad<D>(pr.dq + h * p.dq_sh + static_cast<int64_t>(qrow) * p.dq_ss, dq, p.scale, pr.acc_q, hh);
 }
@@ -555,40 +575,46 @@ __global__ void __launch_bounds__(NT, 1) k_bwd_f32(F32BwdParams p) {
                               p.partial + static_cast<int64_t>(item) * (4 / NS * 64 * D), smem);
   } else {
     const int item = xcd_item(p.map_q, bid - grid_kv);
-    if (item < p.map_q.total) bwd_dq<D, NS>(p, p.pair[item / p.n_q], item % p.n_q, smem);
+    if (item < p.map_q.total)
+      bwd_dq<D, NS>(p, p.pair[item / p.n_q], item % p.n_q, p.q_partial + static_cast<int64_t>(item) * (4 / NS * 32 * D), smem);
   }
 }
 
-// dk, dv of a row block of NR * 32 key rows from the sums of its shares: grid (row blocks, 2 NR), 256 threads, each
-// four of a lane's sixteen runs.  The order of the sum is that of the shares.
-template <int D, int NR>
+// dk, dv (KV: blockIdx.y = 2 * 32-row block + dv) or dq (blockIdx.y = 32-row block) of a block of NR * 32 rows from the sums of
+// its shares: blockIdx.x = row block, 256 threads, each four of a lane's sixteen runs.  The order of the sum is that of the shares.
+template <int D, int NR, bool KV>
 __global__ void __launch_bounds__(NT) k_reduce_f32(F32BwdParams p) {
   constexpr int NB = D / 32;
   typedef typename Run<NB>::type run_t;
-  const int xk = blockIdx.x % p.nx_kv, pk = blockIdx.x / p.nx_kv;      // pk: pair * h_kv + kv head
-  const Pair& pr = p.pair[pk / p.h_kv];
-  const int rb = blockIdx.y >> 1, is_dv = blockIdx.y & 1, lane = threadIdx.x & 63, i0 = (threadIdx.x >> 6) * 4;
-  const int row = (xk * NR + rb) * 32 + (lane & 31);
-  if (row >= p.s_k) return;
-  const int64_t block = NR * 2 * 16 * 64, step = static_cast<int64_t>(p.nx_kv) * block;      // in runs
-  const run_t* src = reinterpret_cast<const run_t*>(p.partial) +
-                     (static_cast<int64_t>(pk) * p.shares * p.nx_kv + xk) * block + ((rb * 2 + is_dv) * 16 + i0) * 64 + lane;
+  const int nx = KV ? p.nx_kv : p.nx_q, heads = KV ? p.h_kv : p.h_q, shares = KV ? p.shares : p.q_shares;
+  const int xr = blockIdx.x % nx, ph = blockIdx.x / nx;                // ph: pair * heads + head
+  const Pair& pr = p.pair[ph / heads];
+  const int rb = KV ? blockIdx.y >> 1 : blockIdx.y, is_dv = KV ? blockIdx.y & 1 : 0;
+  const int lane = threadIdx.x & 63, i0 = (threadIdx.x >> 6) * 4;
+  const int row = (xr * NR + rb) * 32 + (lane & 31);
+  if (row >= (KV ? p.s_k : p.s_q)) return;
+  const int64_t block = NR * (KV ? 2 : 1) * 16 * 64, step = static_cast<int64_t>(nx) * block;      // in runs
+  const run_t* src = reinterpret_cast<const run_t*>(KV ? p.partial : p.q_partial) +
+                     (static_cast<int64_t>(ph) * shares * nx + xr) * block + (blockIdx.y * 16 + i0) * 64 + lane;
   run_t a[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) a[i] = src[i * 64];
-  for (int s = 1; s < p.shares; ++s) {
+#pragma unroll 4      // (the reads of four shares on their way)
+  for (int s = 1; s < shares; ++s) {
     src += step;
 #pragma unroll
     for (int i = 0; i < 4; ++i) a[i] += src[i * 64];
   }
-  float* dst = (is_dv ? pr.dv : pr.dk) + (pk % p.h_kv) * p.dkv_sh + static_cast<int64_t>(row) * p.dkv_ss +
+  float* out = KV ? (is_dv ? pr.dv : pr.dk) : pr.dq;
+  float* dst = out + (ph % heads) * (KV ? p.dkv_sh : p.dq_sh) + static_cast<int64_t>(row) * (KV ? p.dkv_ss : p.dq_ss) +
                NB * (i0 * 2 + 4 * (lane >> 5));
   const float f = is_dv ? 1.f : p.scale;
+  const int add = KV ? pr.acc_kv : pr.acc_q;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     run_t* d = reinterpret_cast<run_t*>(dst + NB * i);
     run_t x = a[i] * f;
-    if (pr.acc_kv) x += *d;
+    if (add) x += *d;
     *d = x;
   }
 }
@@ -656,19 +682,22 @@ int bwd(F32BwdParams p, hipStream_t st) {
   p.nx_kv = static_cast<int>(blocks_of(p.s_k, rows));
   p.nx_q = static_cast<int>(blocks_of(p.s_q, rows));
   const int64_t n_kv = p.pair[0].dk ? static_cast<int64_t>(p.nx_kv) * p.h_kv * p.shares : 0;
-  const int64_t n_q = p.pair[0].dq ? static_cast<int64_t>(p.nx_q) * p.h_q : 0;
+  const int64_t n_q = p.pair[0].dq ? static_cast<int64_t>(p.nx_q) * p.h_q * p.q_shares : 0;
   if ((n_kv + n_q) * p.pairs > (1 << 30)) return DFA_ERR_SHAPE;
   p.n_kv = static_cast<int>(n_kv);
   p.n_q = static_cast<int>(n_q);
   p.map_kv = xcd_map(n_kv * p.pairs, p.causal, static_cast<int64_t>(p.h_kv) * p.shares * p.pairs);
-  p.map_q = xcd_map(n_q * p.pairs, p.causal, static_cast<int64_t>(p.h_q) * p.pairs);
+  p.map_q = xcd_map(n_q * p.pairs, p.causal, static_cast<int64_t>(p.h_q) * p.q_shares * p.pairs);
+  if (p.shares > 1) p.q_partial += n_kv * p.pairs * (rows * 2 * D);      // after the sums of dk, dv
   const int64_t blocks = xcd_blocks(p.map_kv) + xcd_blocks(p.map_q);
   const size_t smem = tiles > comb ? tiles : comb;
   const int rc = p.shares > 1 ? launch<F32BwdParams, k_bwd_f32<D, NS, true>>(p, blocks, smem, st)
                               : launch<F32BwdParams, k_bwd_f32<D, NS, false>>(p, blocks, smem, st);
-  if (rc || p.shares == 1) return rc;
-  const dim3 grid(static_cast<unsigned>(n_kv * p.pairs / p.shares), 2 * (4 / NS));
-  k_reduce_f32<D, 4 / NS><<<grid, NT, 0, st>>>(p);
+  if (rc) return rc;
+  if (p.shares > 1)
+    k_reduce_f32<D, 4 / NS, true><<<dim3(static_cast<unsigned>(n_kv * p.pairs / p.shares), 2 * (4 / NS)), NT, 0, st>>>(p);
+  if (p.q_shares > 1)
+    k_reduce_f32<D, 4 / NS, false><<<dim3(static_cast<unsigned>(n_q * p.pairs / p.q_shares), 4 / NS), NT, 0, st>>>(p);
   return last_launch_status();
 }
 
@@ -686,28 +715,38 @@ int bwd(F32BwdParams p, hipStream_t st) {
 // for 35).  Where it is chosen it is the better form all the same: 4 against 2 parts 44 / 45 there, 8 / 2 x 512 diagonal
 // 58 / 78, 4 / 1 x 768 75 / 109, x 1024 129 / 141, x 1536 diagonal 206 / 205.
 // The vector-FMA kernel this one replaced (dq by atomics) took 2.9 ms at 8 / 2 x 1024.
-struct Plan { int parts, shares; double us; };
+// dq by several workgroups per row block: a few query rows against many keys, where a row block's walk over all of them would be
+// the whole call (us with one walk / shared, d = 128; dq by atomics took the third): 1 head x 32 x 16384 1278 / 76 / 47,
+// x 256 x 32768 2615 / 195 / 430, 8 x 64 x 16384 1573 / 260 / 525, 2 over 1 x 47 x 2011 161 / 34 / 103.  From eight keys per row
+// on: below, the row blocks are enough (4 heads x 500 x 1000 88, and 393 with atomics).
+struct Plan { int parts, shares, q_shares; double us; int64_t bytes; };
 
 Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
   const int group = sh.h_q / sh.h_kv;
   const double width = sh.d == 128 ? 1.0 : 0.55, mean = sh.causal ? 0.5 : 1.0;
-  Plan best{0, 0, 0.};
+  ws_bytes = std::min(ws_bytes, int64_t{128} << 20);
+  const int max_q = dq && sh.s_k / 8 >= sh.s_q ? 64 : 1;
+  Plan best{0, 0, 0, 0., 0};
   for (int parts : {1, 2, 4}) {
     const int rows = 128 / parts, tile = 32 * parts;
-    const int64_t kv1 = dk ? blocks_of(sh.s_k, rows) * sh.h_kv * pairs : 0, n_q = dq ? blocks_of(sh.s_q, rows) * sh.h_q * pairs : 0;
+    const int64_t kv1 = dk ? blocks_of(sh.s_k, rows) * sh.h_kv * pairs : 0, q1 = dq ? blocks_of(sh.s_q, rows) * sh.h_q * pairs : 0;
     const double walk_kv = width * (parts == 1 ? 9.3 : parts == 2 ? 10.3 : 12.2) * group * blocks_of(sh.s_q, tile);
     const double walk_q = width * (parts == 1 ? 7.0 : parts == 2 ? 7.7 : 9.7) * blocks_of(sh.s_k, tile);
-    const int64_t bytes = static_cast<int64_t>(rows) * 2 * sh.d * 4;       // of a workgroup's sums
-    for (int shares : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-      const int64_t n_kv = kv1 * shares;
-      if (shares > 1 && (!dk || shares > 4 * group || n_kv > 1024 || n_kv * bytes > ws_bytes)) break;
-      Plan x{parts, shares, std::max(dk ? 6 + walk_kv / shares : 0., dq ? 6 + walk_q : 0.)};
-      if (n_kv + n_q > 256) {
-        const double even = (n_kv * (6 + walk_kv * mean / shares) + n_q * (6 + walk_q * mean)) / 256;
-        x.us = std::max(x.us, even + 0.45 * x.us);
+    const int64_t bytes = static_cast<int64_t>(rows) * 2 * sh.d * 4;       // of a dk/dv workgroup's sums; dq: half
+    for (int q_shares = 1; q_shares <= max_q; q_shares *= 2) {
+      const int64_t n_q = q1 * q_shares, q_bytes = q_shares > 1 ? n_q * (bytes / 2) : 0;
+      if (q_shares > 1 && (n_q > 1024 || q_shares > blocks_of(sh.s_k, tile) || q_bytes > ws_bytes)) break;
+      for (int shares : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+        const int64_t n_kv = kv1 * shares, sums = (shares > 1 ? n_kv * bytes : 0) + q_bytes;
+        if (shares > 1 && (!dk || shares > 4 * group || n_kv > 1024 || sums > ws_bytes)) break;
+        Plan x{parts, shares, q_shares, std::max(dk ? 6 + walk_kv / shares : 0., dq ? 6 + walk_q / q_shares : 0.), sums};
+        if (n_kv + n_q > 256) {
+          const double even = (n_kv * (6 + walk_kv * mean / shares) + n_q * (6 + walk_q * mean / q_shares)) / 256;
+          x.us = std::max(x.us, even + 0.45 * x.us);
+        }
+        if (sums > 0) x.us = (x.us + 4 * ((shares > 1) + (q_shares > 1)) + 2 * sums / 2.5e6) / 0.92;
+        if (!best.parts || x.us < best.us) best = x;
       }
-      if (shares > 1) x.us = (x.us + 4 + n_kv * (2 * bytes / 2.5e6)) / 0.92;
-      if (!best.parts || x.us < best.us) best = x;
     }
   }
   return best;
@@ -752,16 +791,15 @@ int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void* 
   }
   const Plan pl = plan(sh, n, pairs[0].dq, pairs[0].dk, ws ? ws_bytes : 0);
   p.shares = pl.shares;
-  p.partial = static_cast<float*>(ws);
+  p.q_shares = pl.q_shares;
+  p.partial = p.q_partial = static_cast<float*>(ws);
   if (sh.d == 128) return pl.parts == 4 ? bwd<128, 4>(p, st) : pl.parts == 2 ? bwd<128, 2>(p, st) : bwd<128, 1>(p, st);
   return pl.parts == 4 ? bwd<64, 4>(p, st) : pl.parts == 2 ? bwd<64, 2>(p, st) : bwd<64, 1>(p, st);
 }
 
 int64_t bwd_f32_workspace(const dfa_shape& sh, int n, bool dq, bool dk) {
   const int per = std::min(n, MAX_PAIRS);
-  const Plan pl = plan(sh, per, dq, dk, INT64_MAX);
-  const int rows = 128 / pl.parts;
-  return pl.shares > 1 ? pl.shares * blocks_of(sh.s_k, rows) * sh.h_kv * per * rows * 2 * sh.d * 4 : 0;
+  return plan(sh, per, dq, dk, INT64_MAX).bytes;
 }
 
 }  // namespace dfa

@@ -325,6 +325,53 @@ def test_f32_backward_shares(shape, d):
                 assert maxerr(got[i], want[i] + (0.5 if acc else 0.0)) <= bound[i]
 
 
+# fp32 dq by several workgroups per row block, from eight keys per query row on: (heads, rows, keys, pairs)
+F32_Q_SHARES = [
+    (2, 1, 20, 1000, 1),
+    (8, 2, 33, 2500, 1),          # two row blocks
+    (16, 1, 60, 1500, 1),         # dk, dv shared too
+    (1, 1, 5, 400, 18),           # more pairs than a launch takes
+    (4, 4, 100, 801, 2),
+    (1, 1, 31, 16384, 1),
+]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("shape", F32_Q_SHARES)
+def test_f32_backward_query_shares(shape, d):
+    """A list of pairs with all the scratch asked for, half of it and none: against the oracle, overwriting and adding, with
+    all gradients and dq alone; nothing is written behind the scratch."""
+    h_q, h_kv, s_q, s_k, n = shape
+    scale, lib = d ** -0.5, B.load_library()
+    ops, want, pairs = [], [], (B.DfaBwdPair * n)()
+    for i in range(n):
+        x = case(9800 + 31 * i + s_k, h_q, h_kv, s_q, s_k, d, torch.float32)
+        x64 = [np64(t) for t in x]
+        O, L = A.attention_fwd(*x64[:3], scale, causal=False)
+        want.append(A.attention_bwd(*x64, scale, causal=False))
+        q, k, v, do = (t.to(dev()) for t in x)
+        ops.append((q, k, v, torch.from_numpy(L).float().to(dev()), torch.from_numpy(A.delta_rows(O, x64[3])).float().to(dev()), do))
+    sh = B._make_shape(ops[0][0], ops[0][1], False, scale, B.DFA_F32, lse=ops[0][3], dq=ops[0][0], dkv=ops[0][1])
+    stream = torch.cuda.current_stream().cuda_stream
+    for want_kv in (True, False):
+        full = lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), n, 1, want_kv)
+        assert full > 0
+        for n_bytes, acc in ((full, False), (full, True), (full // 2 & ~15, False), (0, True)):
+            ws = torch.full((n_bytes // 4 + 256,), 7.0, device=dev())
+            outs = [[torch.full(w.shape, 0.5, device=dev()) for w in ws_i] for ws_i in want]
+            for p, o, g in zip(pairs, ops, outs):
+                p.q, p.k, p.v, p.lse, p.delta, p.dO = (t.data_ptr() for t in o)
+                p.dq, p.dk, p.dv = g[0].data_ptr(), *(t.data_ptr() if want_kv else None for t in g[1:])
+                p.accumulate_dq = p.accumulate_dkv = acc
+            assert lib.dfa_chunk_bwd_batch(ctypes.byref(sh), pairs, n, ws.data_ptr() if n_bytes else None, n_bytes, stream) == 0
+            assert bool((ws[n_bytes // 4:] == 7.0).all())
+            for g, w in zip(outs, want):
+                for j in range(3 if want_kv else 1):
+                    bound = TOL[torch.float32] * max(1.0, abs(w[j]).max())      # grows with the magnitude of the sums
+                    assert maxerr(g[j], w[j] + (0.5 if acc else 0.0)) <= bound
+                assert want_kv or all(bool((t == 0.5).all()) for t in g[1:])
+
+
 def test_f32_dq_of_a_long_walk():
     """dq over 16384 keys, from the exact logsumexp and D.  A rounding is off by 2^-24 / sqrt(3) = 3.4e-8 (rms) of the partial
     sum that it rounds, which over a chain of n steps of like size makes 3.4e-8 sqrt(n / 2) of the sum.  Scores and dP (64
