@@ -82,24 +82,23 @@ __device__ inline void store16(void* base, int64_t elem_off, const Vec16<BF16>& 
 }
 
 // (o_a, lse_a) <- merge((o_a, lse_a), (o_b, lse_b)), Section 3.2 rescale(.)
-// 16 bytes per lane and row, MERGE_ROWS rows in flight per lane; (o_b, lse_b) is read for the last time, (o_a, lse_a)
+// 16 bytes per lane and row, ROWS rows in flight per lane; (o_b, lse_b) is read for the last time, (o_a, lse_a)
 // is what the next step continues from.  32 heads x 16384, fp32: 157 us with 32 bytes per lane and cached
 // loads, 147 with this division, 115 with o_b past the caches (7.0 TB/s; four rows in flight: 116).
-constexpr int MERGE_ROWS = 2;
 template <int D, bool BF16> constexpr int kMergeLanes = D / (BF16 ? 8 : 4);       // lanes per row
-template <int D, bool BF16, int NP>
+template <int D, bool BF16, int NP, int ROWS>
 __global__ void __launch_bounds__(256) k_merge(dfa_merge_desc md, MergePairs<NP> pairs) {
   const dfa_merge_pair& pr = pairs.pair[NP == 1 ? 0 : blockIdx.z];
   constexpr int LPR = kMergeLanes<D, BF16>, RPB = 256 / LPR, VN = Vec16<BF16>::N;
   const int lane = threadIdx.x % LPR, h = blockIdx.y;
-  const int row0 = blockIdx.x * RPB * MERGE_ROWS + threadIdx.x / LPR;
+  const int row0 = blockIdx.x * RPB * ROWS + threadIdx.x / LPR;
   float* la_p = pr.lse_a + h * md.lse_a_stride_h;
   const float* lb_p = pr.lse_b + h * md.lse_b_stride_h;
-  Vec16<BF16> a[MERGE_ROWS], b[MERGE_ROWS];
-  float la[MERGE_ROWS], lb[MERGE_ROWS];
+  Vec16<BF16> a[ROWS], b[ROWS];
+  float la[ROWS], lb[ROWS];
   auto off_a = [&](int row) { return h * md.a_stride_h + static_cast<int64_t>(row) * md.a_stride_s + lane * VN; };
 #pragma unroll
-  for (int u = 0; u < MERGE_ROWS; ++u) {
+  for (int u = 0; u < ROWS; ++u) {
     const int row = min(row0 + u * RPB, md.rows - 1);
     a[u] = load16<BF16, false>(pr.o_a, off_a(row));
     b[u] = load16<BF16, true>(pr.o_b, h * md.b_stride_h + static_cast<int64_t>(row) * md.b_stride_s + lane * VN);
@@ -107,7 +106,7 @@ __global__ void __launch_bounds__(256) k_merge(dfa_merge_desc md, MergePairs<NP>
     lb[u] = lb_p[row];
   }
 #pragma unroll
-  for (int u = 0; u < MERGE_ROWS; ++u) {
+  for (int u = 0; u < ROWS; ++u) {
     const int row = row0 + u * RPB;
     if (row >= md.rows) break;
     const float m = fmaxf(la[u], lb[u]);
@@ -179,12 +178,21 @@ int grid_for(int64_t items, int per_block) {
 
 }  // namespace
 
+template <int D, bool BF16, int ROWS>
+static void merge_rows(const dfa_merge_desc& md, const MergePairs<MAX_PAIRS>& all, int n, hipStream_t st) {
+  constexpr int rows = 256 / kMergeLanes<D, BF16> * ROWS;
+  const dim3 grid((md.rows - 1) / rows + 1, md.heads, n);
+  if (n > 1) k_merge<D, BF16, MAX_PAIRS, ROWS><<<grid, 256, 0, st>>>(md, all);
+  else k_merge<D, BF16, 1, ROWS><<<grid, 256, 0, st>>>(md, MergePairs<1>{{all.pair[0]}});
+}
+
 template <int D, bool BF16>
 static void merge_form(const dfa_merge_desc& md, const MergePairs<MAX_PAIRS>& all, int n, hipStream_t st) {
-  constexpr int rows = 256 / kMergeLanes<D, BF16> * MERGE_ROWS;
-  const dim3 grid((md.rows - 1) / rows + 1, md.heads, n);
-  if (n > 1) k_merge<D, BF16, MAX_PAIRS><<<grid, 256, 0, st>>>(md, all);
-  else k_merge<D, BF16, 1><<<grid, 256, 0, st>>>(md, MergePairs<1>{{all.pair[0]}});
+  // One row per lane while all workgroups are resident at once (eight per CU) that way: 8 heads x 112, fp32, 2.87 -> 2.65 us,
+  // 32 x 300 3.95 -> 3.65; two rows beyond (32 x 1024, o_b just written, 10.4 against 11.0).
+  const int64_t blocks = (static_cast<int64_t>(md.rows) * kMergeLanes<D, BF16> + 255) / 256 * md.heads * n;
+  if (blocks <= 2048) merge_rows<D, BF16, 1>(md, all, n, st);
+  else merge_rows<D, BF16, 2>(md, all, n, st);
 }
 
 int launch_merge(const dfa_merge_desc& md, const dfa_merge_pair* pairs, int n, hipStream_t st) {

@@ -389,3 +389,22 @@ def test_f32_dq_of_a_long_walk():
     delta = torch.from_numpy(A.delta_rows(O, x64[3])).float().to(dev())
     dq = dfa.dfa_chunk_bwd(Q, K, V, lse, delta, dO, torch.empty_like(Q), None, None, False, scale)[0]
     assert np.linalg.norm(np64(dq) - want) <= 9e-7 * np.linalg.norm(want)
+
+
+# One row per lane, and two (from 2049 workgroups of one row per lane on), with remainders.
+@pytest.mark.parametrize("o_dtype,heads,rows,d", [
+    (torch.float32, 3, 37, 128), (torch.float32, 40, 515, 128), (torch.float32, 64, 1031, 64),
+    (torch.bfloat16, 5, 70, 64), (torch.bfloat16, 64, 529, 128), (torch.bfloat16, 20, 4101, 64),
+])
+def test_merge_rows(o_dtype, heads, rows, d):
+    g = torch.Generator().manual_seed(rows)
+    oa, ob = (torch.randn(heads, rows, d, generator=g).to(o_dtype) for _ in range(2))
+    la, lb = (torch.randn(heads, rows, generator=g) for _ in range(2))
+    la[:, ::7], lb[:, ::5] = -math.inf, -math.inf
+    O, L = A.merge(np64(oa), np64(la), np64(ob), np64(lb))
+    o, lse = oa.to(dev()), la.to(dev())
+    dfa.dfa_merge(o, lse, ob.to(dev()), lb.to(dev()))
+    # one rounding of a value below 8 to bf16 (2^-6), or a few of fp32
+    assert maxerr(o, O) <= (2.0 ** -6 if o_dtype == torch.bfloat16 else 4e-6)
+    both = np.isfinite(L)
+    assert maxerr(lse[torch.from_numpy(both).to(dev())], L[both]) <= 1e-6 and bool((lse.cpu()[torch.from_numpy(~both)] == -math.inf).all())
