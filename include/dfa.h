@@ -117,6 +117,28 @@ typedef struct {
 int dfa_chunk_fwd_batch(const dfa_shape* sh, const dfa_fwd_pair* pairs, int32_t n_pairs, void* stream);
 
 /*
+ * dfa_span_fwd - forward of query chunks against SPANS of consecutive key/value rows, n_spans of them as one piece
+ * of work: what a worker computes with the key/value chunks it has at hand, without a trip of its state through
+ * memory for each of them.  A span's n_keys rows begin at k, v (of which the strides are those of `sh`; its s_k and
+ * causal are not looked at).  own != 0: the last s_q of them (n_keys >= s_q) are the query chunk's own rows, key j is visible to
+ * query i iff j <= i + n_keys - s_q; own == 0: every key is visible.  accumulate, o, lse and the rules for lists as
+ * for dfa_chunk_fwd_batch; the result is that of the span's pairs one after the other, up to rounding.
+ * `workspace`: as for dfa_chunk_bwd_batch; dfa_span_fwd_workspace() bytes (at most 128 MiB, 0 where it needs none) let it
+ * divide the keys of few query rows among more workgroups.
+ */
+typedef struct {
+  const void *q, *k, *v;
+  void* o;
+  float* lse;
+  int64_t o_stride_h, o_stride_s, lse_stride_h;
+  int32_t n_keys, own, accumulate, reserved;
+} dfa_fwd_span;
+
+int dfa_span_fwd(const dfa_shape* sh, const dfa_fwd_span* spans, int32_t n_spans, void* workspace,
+                 int64_t workspace_bytes, void* stream);
+int64_t dfa_span_fwd_workspace(const dfa_shape* sh, const dfa_fwd_span* spans, int32_t n_spans);
+
+/*
  * dfa_merge - the rescale(o, s, o', s') update of the balanced schedule (Section 3.2,
  * Algorithm 2): exact combination of two partial results for the same query rows,
  *   lse = log(e^lse_a + e^lse_b),  o = e^(lse_a-lse) o_a + e^(lse_b-lse) o_b,
@@ -134,7 +156,8 @@ int dfa_merge(const dfa_merge_desc* md, void* o_a, float* lse_a,
               const void* o_b, const float* lse_b, void* stream);
 
 /* dfa_merge_batch - n_pairs merges of one shape and one set of strides at once; the operands of the
- * pairs must not overlap.  `pairs` is a HOST array, read before the call returns. */
+ * pairs must not overlap, but for pairs next to each other in the list with the same (o_a, lse_a): these are
+ * merged into it in one pass.  `pairs` is a HOST array, read before the call returns. */
 typedef struct {
   void* o_a;
   float* lse_a;
@@ -201,6 +224,15 @@ int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t 
  * dk, dv are wanted (0 where it needs none), or a negative dfa_status.  Pure host function; strides
  * are not looked at.  At most 128 MiB. */
 int64_t dfa_chunk_bwd_workspace(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int32_t want_dkv);
+
+/*
+ * dfa_span_bwd - dfa_chunk_bwd_batch of one query chunk against a span of consecutive key/value rows, s_k of them: with
+ * causal = 1 (s_k >= s_q) the last s_q are the chunk's own, key j is visible to query i iff j <= i + s_k - s_q.  dk, dv are
+ * those of all s_k rows; accumulate_dkv goes for all of them.  The gradients are those of the span's pairs one after
+ * the other, up to the order of summation.  Workspace as there.
+ */
+int dfa_span_bwd(const dfa_shape* sh, const dfa_bwd_pair* span, void* workspace, int64_t workspace_bytes, void* stream);
+int64_t dfa_span_bwd_workspace(const dfa_shape* sh, int32_t want_dq, int32_t want_dkv);
 
 /* Step kinds of the balanced schedule. */
 typedef enum { DFA_STEP_IDLE = 0, DFA_STEP_DIAG = 1, DFA_STEP_OWN = 2, DFA_STEP_HELP = 3 } dfa_step_kind;

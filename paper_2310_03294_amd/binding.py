@@ -57,6 +57,12 @@ class DfaMergePair(ctypes.Structure):
     _fields_ = [(n, ctypes.c_void_p) for n in ("o_a", "lse_a", "o_b", "lse_b")]
 
 
+class DfaFwdSpan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("q", "k", "v", "o", "lse")] + [
+        (n, ctypes.c_int64) for n in ("o_stride_h", "o_stride_s", "lse_stride_h")] + [
+        (n, ctypes.c_int32) for n in ("n_keys", "own", "accumulate", "reserved")]
+
+
 class DfaBwdPair(ctypes.Structure):
     _fields_ = [(n, ctypes.c_void_p) for n in ("q", "k", "v", "lse", "delta", "dO", "dq", "dk", "dv")] + [
         ("accumulate_dq", ctypes.c_int32), ("accumulate_dkv", ctypes.c_int32)]
@@ -69,9 +75,9 @@ class DfaStep(ctypes.Structure):
 
 Step = collections.namedtuple("Step", "t kind q_chunk kv_chunk send_to recv_from")
 
-EXPORTS = ("dfa_chunk_fwd", "dfa_chunk_fwd_acc", "dfa_chunk_fwd_batch", "dfa_merge", "dfa_merge_batch", "dfa_delta",
+EXPORTS = ("dfa_chunk_fwd", "dfa_chunk_fwd_acc", "dfa_chunk_fwd_batch", "dfa_span_fwd", "dfa_span_fwd_workspace", "dfa_merge", "dfa_merge_batch", "dfa_delta",
            "dfa_chunk_bwd",
-           "dfa_chunk_bwd_batch", "dfa_chunk_bwd_workspace", "dfa_schedule", "dfa_schedule_mode", "dfa_schedule_window", "dfa_mfma_probe", "dfa_mfma_probe_data", "dfa_status_str",
+           "dfa_chunk_bwd_batch", "dfa_chunk_bwd_workspace", "dfa_span_bwd", "dfa_span_bwd_workspace", "dfa_schedule", "dfa_schedule_mode", "dfa_schedule_window", "dfa_mfma_probe", "dfa_mfma_probe_data", "dfa_status_str",
            "dfa_version")
 
 
@@ -97,6 +103,8 @@ def load_library():
     lib.dfa_delta.argtypes = [shp, vp, vp, vp, vp]
     lib.dfa_chunk_bwd.argtypes = [shp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_int, vp]
     lib.dfa_chunk_fwd_batch.argtypes = [shp, ctypes.POINTER(DfaFwdPair), i32, vp]
+    lib.dfa_span_fwd.argtypes = [shp, ctypes.POINTER(DfaFwdSpan), i32, vp, i64, vp]
+    lib.dfa_span_fwd_workspace.argtypes = [shp, ctypes.POINTER(DfaFwdSpan), i32]
     lib.dfa_merge_batch.argtypes = [ctypes.POINTER(DfaMergeDesc), ctypes.POINTER(DfaMergePair), i32, vp]
     lib.dfa_chunk_bwd_batch.argtypes = [shp, ctypes.POINTER(DfaBwdPair), i32, vp, i64, vp]
     lib.dfa_schedule.argtypes = [i32, i32, ctypes.POINTER(DfaStep), i32]
@@ -109,11 +117,13 @@ def load_library():
     lib.dfa_status_str.argtypes = [ctypes.c_int]
     lib.dfa_status_str.restype = ctypes.c_char_p
     lib.dfa_version.argtypes = []
+    lib.dfa_span_bwd.argtypes = [shp, ctypes.POINTER(DfaBwdPair), vp, i64, vp]
+    lib.dfa_span_bwd_workspace.argtypes = [shp, i32, i32]
     lib.dfa_chunk_bwd_workspace.argtypes = [shp, i32, i32, i32]
     for name in EXPORTS:
         if name not in ("dfa_status_str",):
             getattr(lib, name).restype = ctypes.c_int
-    lib.dfa_chunk_bwd_workspace.restype = i64
+    lib.dfa_chunk_bwd_workspace.restype = lib.dfa_span_fwd_workspace.restype = lib.dfa_span_bwd_workspace.restype = i64
     _lib = lib
     return lib
 
@@ -346,10 +356,15 @@ class ForwardChunks:
 
     def launch(self, pairs, causal, stream=None):
         """The pairs as one launch: (q_chunk, kv_chunk, dest, chunk, accumulate), the result goes to chunk number
-        `chunk` of dest; accumulate: continues from the state there.  No output may overlap another pair's."""
+        `chunk` of dest; accumulate: continues from the state there.  No output may overlap another pair's.
+        causal None: a chunk's pair with itself is causal, no other is; pairs next to each other in the list with one
+        destination, each after the first accumulating, are one walk over their key/value chunks, which
+        have to be consecutive (dfa_span_fwd)."""
         if not pairs:
             return
         sh = self.sh
+        if causal is None:
+            return self._launch_spans(pairs, stream)
         sh.causal, sh.o_dtype = int(bool(causal)), pairs[0][2][3]
         arr = (DfaFwdPair * len(pairs))()
         for a, (qc, kc, dest, c, acc) in zip(arr, pairs):
@@ -361,9 +376,33 @@ class ForwardChunks:
         _check(self.lib.dfa_chunk_fwd_batch(ctypes.byref(sh), arr, len(pairs), _stream(stream)), "dfa_chunk_fwd_batch")
 
 
+    def _launch_spans(self, pairs, stream):
+        sh = self.sh
+        sh.o_dtype = pairs[0][2][3]
+        runs = []                                    # [q_chunk, dest, chunk, accumulate, key/value chunks]
+        for qc, kc, dest, c, acc in pairs:
+            if dest[3] != sh.o_dtype:
+                raise ValueError("outputs of a launch share their dtype")
+            if acc and runs and runs[-1][0] == qc and runs[-1][1] is dest and runs[-1][2] == c:
+                runs[-1][4].append(kc)
+            else:
+                runs.append([qc, dest, c, acc, [kc]])
+        arr = (DfaFwdSpan * len(runs))()
+        for a, (qc, dest, c, acc, kv) in zip(arr, runs):
+            lo, hi = min(kv), max(kv)
+            if sorted(kv) != list(range(lo, hi + 1)) or (qc in kv and qc != hi):
+                raise ValueError("the key/value chunks of a walk are consecutive, the query chunk's own the last")
+            a.q, a.k, a.v, a.o, a.lse = self.q[qc], self.k[lo], self.v[lo], dest[0][c], dest[1][c]
+            self.k[hi]                               # (in range)
+            a.o_stride_h, a.o_stride_s, a.lse_stride_h = dest[2]
+            a.n_keys, a.own, a.accumulate = len(kv) * self.rows, qc == hi, bool(acc)
+        ws, n = _workspace(self.lib.dfa_span_fwd_workspace(ctypes.byref(sh), arr, len(runs)), stream)
+        _check(self.lib.dfa_span_fwd(ctypes.byref(sh), arr, len(runs), _ptr(ws), n, _stream(stream)), "dfa_span_fwd")
+
+
 def dfa_merge_batch(o, lse, rows, parts, stream=None):
     """In place: chunk c of (o, lse) <- merge(chunk c, (o_b, lse_b)) for every (c, o_b, lse_b) of parts, as one
-    launch; the partials share their strides."""
+    launch; the partials share their strides.  Partials of one chunk are next to each other in the list."""
     if not parts:
         return
     lib = load_library()
@@ -411,6 +450,22 @@ class BackwardChunks:
         ws, n = _workspace(self.lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), len(pairs), 1, 1), stream)
         _check(self.lib.dfa_chunk_bwd_batch(ctypes.byref(sh), arr, len(pairs), _ptr(ws), n, _stream(stream)),
                "dfa_chunk_bwd_batch")
+
+
+    def launch_span(self, qc, lo, hi, acc_q, acc_kv, stream=None):
+        """Query chunk qc against the key/value chunks lo .. hi, the last of which may be its own (dfa_span_bwd)."""
+        sh, rows = self.sh, self.sh.s_q
+        sh.s_k, sh.causal = (hi - lo + 1) * rows, int(qc == hi)
+        try:
+            a = DfaBwdPair()
+            a.q, a.lse, a.delta, a.dO, a.dq = (t[qc] for t in self.by_q)
+            a.k, a.v, a.dk, a.dv = (t[lo] for t in self.by_kv)
+            self.by_kv[0][hi]                        # (in range)
+            a.accumulate_dq, a.accumulate_dkv = bool(acc_q), bool(acc_kv)
+            ws, n = _workspace(self.lib.dfa_span_bwd_workspace(ctypes.byref(sh), 1, 1), stream)
+            _check(self.lib.dfa_span_bwd(ctypes.byref(sh), ctypes.byref(a), _ptr(ws), n, _stream(stream)), "dfa_span_bwd")
+        finally:
+            sh.s_k = rows
 
 
 def dfa_mfma_probe(out, iters: int, stream=None) -> float:

@@ -6,7 +6,8 @@ namespace {
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 bool mult8(int64_t x) { return (x & 7) == 0; }
 
-int check_common(const dfa_shape* sh) {
+// spans: a query chunk's own keys may have others before them
+int check_common(const dfa_shape* sh, bool spans = false) {
   if (!sh) return DFA_ERR_NULL;
   if (sh->reserved != 0) return DFA_ERR_ARG;
   if (sh->dtype != DFA_BF16 && sh->dtype != DFA_F32) return DFA_ERR_DTYPE;
@@ -17,7 +18,7 @@ int check_common(const dfa_shape* sh) {
   if (sh->d != 64 && sh->d != 128) return DFA_ERR_SHAPE;
   if (sh->dtype == DFA_BF16 && sh->d != 128) return DFA_ERR_SHAPE;
   if (sh->causal != 0 && sh->causal != 1) return DFA_ERR_ARG;
-  if (sh->causal && sh->s_q != sh->s_k) return DFA_ERR_ARG;
+  if (sh->causal && (spans ? sh->s_k < sh->s_q : sh->s_q != sh->s_k)) return DFA_ERR_ARG;
   if (!(sh->scale == sh->scale) || sh->scale <= 0.f) return DFA_ERR_ARG;
   return DFA_OK;
 }
@@ -85,6 +86,52 @@ extern "C" int dfa_chunk_fwd_batch(const dfa_shape* sh, const dfa_fwd_pair* pair
 }
 
 namespace {
+int check_spans(const dfa_shape* sh, const dfa_fwd_span* spans, int32_t n) {
+  dfa_shape s = *sh;
+  s.causal = 0; s.s_k = 0;
+  int rc = check_common(&s);
+  if (rc != DFA_OK) return rc;
+  if (n < 0) return DFA_ERR_ARG;
+  if (n > 0 && !spans) return DFA_ERR_NULL;
+  for (int i = 0; i < n; ++i) {
+    const dfa_fwd_span& x = spans[i];
+    if (x.n_keys < 1) return DFA_ERR_SHAPE;
+    if (x.reserved != 0 || (x.own && x.n_keys < sh->s_q)) return DFA_ERR_ARG;
+    if (!stride_ok(sh->kv_stride_h, sh->kv_stride_s, sh->d, x.n_keys)) return DFA_ERR_SHAPE;
+  }
+  return DFA_OK;
+}
+}  // namespace
+
+extern "C" int dfa_span_fwd(const dfa_shape* sh, const dfa_fwd_span* spans, int32_t n_spans, void* workspace,
+                            int64_t workspace_bytes, void* stream) {
+  if (!sh) return DFA_ERR_NULL;
+  const int rc = check_spans(sh, spans, n_spans);
+  if (rc != DFA_OK) return rc;
+  for (int i = 0; i < n_spans; ++i) {
+    const dfa_fwd_span& p = spans[i];
+    if (!p.q || !p.k || !p.v || !p.o || !p.lse) return DFA_ERR_NULL;
+    if (!aligned16(p.q) || !aligned16(p.k) || !aligned16(p.v) || !aligned16(p.o)) return DFA_ERR_SHAPE;
+    if (!stride_ok(p.o_stride_h, p.o_stride_s, sh->d, sh->s_q) || !row_stride_ok(p.lse_stride_h, sh->s_q)) return DFA_ERR_SHAPE;
+  }
+  if (!stride_ok(sh->q_stride_h, sh->q_stride_s, sh->d, sh->s_q)) return DFA_ERR_SHAPE;
+  if (workspace_bytes < 0) return DFA_ERR_ARG;
+  if (!aligned16(workspace)) return DFA_ERR_SHAPE;
+  if (sh->s_q == 0 || n_spans == 0) return DFA_OK;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  return sh->dtype == DFA_F32 ? dfa::launch_span_f32(*sh, spans, n_spans, workspace, workspace_bytes, st)
+                              : dfa::launch_span_bf16(*sh, spans, n_spans, workspace, workspace_bytes, st);
+}
+
+extern "C" int64_t dfa_span_fwd_workspace(const dfa_shape* sh, const dfa_fwd_span* spans, int32_t n_spans) {
+  if (!sh) return DFA_ERR_NULL;
+  const int rc = check_spans(sh, spans, n_spans);
+  if (rc != DFA_OK) return rc;
+  if (sh->s_q == 0 || n_spans == 0) return 0;
+  return sh->dtype == DFA_F32 ? dfa::span_f32_workspace(*sh, spans, n_spans) : dfa::span_bf16_workspace(*sh, spans, n_spans);
+}
+
+namespace {
 int chunk_fwd(const dfa_shape* sh, const void* q, const void* k, const void* v,
               void* o, float* lse, int accumulate, void* stream) {
   if (!sh) return DFA_ERR_NULL;
@@ -144,9 +191,10 @@ extern "C" int dfa_delta(const dfa_shape* sh, const void* o, const void* dO, flo
   return dfa::launch_delta(*sh, o, dO, delta, static_cast<hipStream_t>(stream));
 }
 
-extern "C" int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t n_pairs, void* workspace,
-                                   int64_t workspace_bytes, void* stream) {
-  int rc = check_common(sh);
+namespace {
+int bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t n_pairs, void* workspace, int64_t workspace_bytes,
+              void* stream, bool spans) {
+  int rc = check_common(sh, spans);
   if (rc != DFA_OK) return rc;
   if (n_pairs < 0) return DFA_ERR_ARG;
   if (n_pairs == 0) return DFA_OK;
@@ -189,13 +237,30 @@ extern "C" int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pair
                               : dfa::launch_bwd_bf16(*sh, pairs, n_pairs, workspace, workspace_bytes, st);
 }
 
-extern "C" int64_t dfa_chunk_bwd_workspace(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int32_t want_dkv) {
-  const int rc = check_common(sh);
+int64_t bwd_workspace(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int32_t want_dkv, bool spans) {
+  const int rc = check_common(sh, spans);
   if (rc != DFA_OK) return rc;
   if (n_pairs < 0) return DFA_ERR_ARG;
   if (n_pairs == 0 || sh->s_q == 0 || sh->s_k == 0) return 0;
   return sh->dtype == DFA_F32 ? dfa::bwd_f32_workspace(*sh, n_pairs, want_dq != 0, want_dkv != 0)
                               : dfa::bwd_bf16_workspace(*sh, n_pairs, want_dq != 0, want_dkv != 0);
+}
+
+}  // namespace
+
+extern "C" int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t n_pairs, void* workspace,
+                                   int64_t workspace_bytes, void* stream) {
+  return bwd_batch(sh, pairs, n_pairs, workspace, workspace_bytes, stream, false);
+}
+extern "C" int64_t dfa_chunk_bwd_workspace(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int32_t want_dkv) {
+  return bwd_workspace(sh, n_pairs, want_dq, want_dkv, false);
+}
+
+extern "C" int dfa_span_bwd(const dfa_shape* sh, const dfa_bwd_pair* span, void* workspace, int64_t workspace_bytes, void* stream) {
+  return bwd_batch(sh, span, 1, workspace, workspace_bytes, stream, true);
+}
+extern "C" int64_t dfa_span_bwd_workspace(const dfa_shape* sh, int32_t want_dq, int32_t want_dkv) {
+  return bwd_workspace(sh, 1, want_dq, want_dkv, true);
 }
 
 extern "C" int dfa_chunk_bwd(const dfa_shape* sh, const void* q, const void* k, const void* v,

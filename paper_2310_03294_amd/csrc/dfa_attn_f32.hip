@@ -22,6 +22,7 @@
 #include <mutex>
 
 #include "dfa_internal.h"
+#include "dfa_span.h"
 
 namespace dfa {
 namespace {
@@ -68,6 +69,12 @@ struct FwdPair {
   int64_t o_sh, o_ss, l_sh;
 };
 struct F32FwdBatch : F32Params { FwdPair fpair[MAX_PAIRS]; };
+// Query chunks against spans of keys, each with its own number of them; off: key kv is visible to query row i if kv <= i + off.
+struct Span : FwdPair { int s_k, off, o_bf16; };
+struct F32FwdSpans : F32Params { int heads; Span span[MAX_PAIRS]; };
+struct F32SpanParams : F32Params { int off; };
+template <class P> __device__ __forceinline__ int off_of(const P&) { return 0; }
+__device__ __forceinline__ int off_of(const F32SpanParams& p) { return p.off; }
 
 // The operands of an item's pair; item becomes its number within the pair.
 __device__ __forceinline__ const F32Params& pair_of(const F32Params& a, int&) { return a; }
@@ -77,6 +84,22 @@ __device__ __forceinline__ F32Params pair_of(const F32FwdBatch& a, int& item) {
   item %= a.n_q;
   p.q = x.q; p.k = x.k; p.v = x.v; p.o = x.o; p.lse = x.lse; p.accumulate = x.accumulate;
   p.o_sh = x.o_sh; p.o_ss = x.o_ss; p.l_sh = x.l_sh;
+  return p;
+}
+
+// (as in the bf16 forward: an XCD takes its heads of all spans, span by span, the longest first)
+__device__ __forceinline__ F32SpanParams pair_of(const F32FwdSpans& a, int& item) {
+  int i = item / a.n_q, r = item % a.n_q;
+  if (a.heads) {
+    const int x = item / a.map_q.per_xcd, y = item % a.map_q.per_xcd, run = a.heads * a.nx_q;
+    i = y / run; r = x * run + y % run;
+  }
+  item = r;
+  F32SpanParams p;
+  static_cast<F32Params&>(p) = a;
+  const Span& s = a.span[i];
+  p.q = s.q; p.k = s.k; p.v = s.v; p.o = s.o; p.lse = s.lse; p.accumulate = s.accumulate;
+  p.o_sh = s.o_sh; p.o_ss = s.o_ss; p.l_sh = s.l_sh; p.s_k = s.s_k; p.o_bf16 = s.o_bf16; p.off = s.off;
   return p;
 }
 
@@ -226,7 +249,8 @@ __global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(Args a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rb = wave % NR, part = wave / NR;
   int item = xcd_item(a.map_q, blockIdx.x);
   if (item >= a.map_q.total) return;
-  const F32Params& p = pair_of(a, item);
+  const auto& p = pair_of(a, item);
+  const int off = off_of(p);
   const int h = item / p.nx_q, kh = h / p.group;
   int xq = item % p.nx_q;
   if (p.causal) xq = p.nx_q - 1 - xq;       // longest rows first
@@ -234,7 +258,7 @@ __global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(Args a) {
   const bool qvalid = qrow < p.s_q;
   const float* kg = p.k + kh * p.kv_sh;
   const float* vg = p.v + kh * p.kv_sh;
-  const int k_end = p.causal ? min(p.s_k, q0 + NR * 32) : p.s_k;
+  const int k_end = p.causal ? min(p.s_k, q0 + NR * 32 + off) : p.s_k;
 
   TilePair<D, BK> tile;
   tile.load(kg, vg, p.kv_ss, 0, p.s_k);
@@ -270,7 +294,7 @@ __global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(Args a) {
 #pragma unroll
     for (int kb = part * 32; kb < BK; kb += NS * 32) {
       const int kb0 = k0 + kb;
-      if (kb0 >= p.s_k || (p.causal && kb0 > q0w + 31)) break;
+      if (kb0 >= p.s_k || (p.causal && kb0 > q0w + 31 + off)) break;
       f32x16 s;
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[i] = 0.f;
@@ -279,7 +303,7 @@ __global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(Args a) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int kvi = kb0 + (i >> 2) * 8 + 4 * hh + (i & 3);
-        s[i] = kvi < p.s_k && !(p.causal && kvi > qrow) ? s[i] * p.scale : -INFINITY;
+        s[i] = kvi < p.s_k && !(p.causal && kvi > qrow + off) ? s[i] * p.scale : -INFINITY;
         mx = fmaxf(mx, s[i]);
       }
       mx = fmaxf(mx, __shfl_xor(mx, 32));
@@ -367,7 +391,8 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
   const int share = SHARED ? item / p.nx_kv % p.shares : 0, kh = SHARED ? item / p.nx_kv / p.shares : item / p.nx_kv;
   const int k0 = (item % p.nx_kv) * NR * 32, k0w = k0 + rb * 32, kvrow = k0w + r32;
   const bool kvalid = kvrow < p.s_k;
-  const int q_begin = p.causal ? k0 : 0;
+  const int off = p.s_k - p.s_q;             // causal: key kv is visible to query row i if kv <= i + off
+  const int q_begin = p.causal ? max(0, k0 - off) : 0;
 
   TilePair<D, BQ> tile;
   float ld = 0.f;                            // lse (first BQ threads) or D (next BQ) of the tile on its way
@@ -414,7 +439,7 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
     q0 += BQ;
     if (q0 >= p.s_q) { q0 = q_begin; ++hq; }
     if (SHARED ? --left > 0 : hq < h_end) load(hq, q0);
-    if (q0t >= p.s_q || (p.causal && k0w > q0t + 31)) continue;
+    if (q0t >= p.s_q || (p.causal && k0w > q0t + 31 + off)) continue;
     const float* Qw = Qs + part * 32 * LD;
     const float* Gw = Gs + part * 32 * LD;
     f32x16 s, dp;
@@ -427,7 +452,7 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
     for (int i = 0; i < 16; ++i) {
       const int r = (i >> 2) * 8 + 4 * hh + (i & 3);
       const float L = Ls[part * 32 + r];      // -inf for rows past the end and empty rows
-      const bool vis = L > -INFINITY && !(p.causal && kvrow > q0t + r);
+      const bool vis = L > -INFINITY && !(p.causal && kvrow > q0t + r + off);
       s[i] = vis ? expf(s[i] * p.scale - L) : 0.f;
       dp[i] = s[i] * (dp[i] - Ds[part * 32 + r]);
     }
@@ -465,9 +490,9 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
     return;
   }
   if (!kvalid) return;
-  const int64_t off = kh * p.dkv_sh + static_cast<int64_t>(kvrow) * p.dkv_ss;
-  write_grad<D>(pr.dk + off, dk, p.scale, pr.acc_kv, hh);
-  write_grad<D>(pr.dv + off, dv, 1.f, pr.acc_kv, hh);
+  const int64_t dst = kh * p.dkv_sh + static_cast<int64_t>(kvrow) * p.dkv_ss;
+  write_grad<D>(pr.dk + dst, dk, p.scale, pr.acc_kv, hh);
+  write_grad<D>(pr.dv + dst, dv, 1.f, pr.acc_kv, hh);
 }
 
 // dq of one workgroup's query rows: Q and dO rows in registers, K / V tiles in LDS.
@@ -486,7 +511,8 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int i
   const bool qvalid = qrow < p.s_q;
   const float* kg = pr.k + kh * p.kv_sh;
   const float* vg = pr.v + kh * p.kv_sh;
-  int k_end = p.causal ? min(p.s_k, q0 + NR * 32) : p.s_k, k_begin = 0;
+  const int off = p.s_k - p.s_q;
+  int k_end = p.causal ? min(p.s_k, q0 + NR * 32 + off) : p.s_k, k_begin = 0;
   if (p.q_shares > 1) {
     const int64_t ntk = (k_end + BK - 1) / BK;
     k_begin = static_cast<int>(ntk * share / p.q_shares) * BK;
@@ -514,7 +540,7 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int i
       __syncthreads();
       if (k0 + BK < k_end) tile.load(kg, vg, p.kv_ss, k0 + BK, p.s_k);
       const int kb0 = k0 + part * 32;
-      if (kb0 >= p.s_k || (p.causal && kb0 > q0w + 31)) continue;
+      if (kb0 >= p.s_k || (p.causal && kb0 > q0w + 31 + off)) continue;
       const float* Kw = Ks + part * 32 * LD;
       f32x16 s, dp;
 #pragma unroll
@@ -524,7 +550,7 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int i
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int kvi = kb0 + (i >> 2) * 8 + 4 * hh + (i & 3);
-        const bool vis = kvi < p.s_k && L > -INFINITY && !(p.causal && kvi > qrow);
+        const bool vis = kvi < p.s_k && L > -INFINITY && !(p.causal && kvi > qrow + off);
         const float pr = vis ? expf(s[i] * p.scale - L) : 0.f;
         dp[i] = pr * (dp[i] - Dr);
       }
@@ -591,7 +617,8 @@ __global__ void __launch_bounds__(NT) k_reduce_f32(F32BwdParams p) {
   const Pair& pr = p.pair[ph / heads];
   const int rb = KV ? blockIdx.y >> 1 : blockIdx.y, is_dv = KV ? blockIdx.y & 1 : 0;
   const int lane = threadIdx.x & 63, i0 = (threadIdx.x >> 6) * 4;
-  const int row = (xr * NR + rb) * 32 + (lane & 31);
+  const int xrow = !KV && p.causal ? nx - 1 - xr : xr;      // (dq: the longest rows come first)
+  const int row = (xrow * NR + rb) * 32 + (lane & 31);
   if (row >= (KV ? p.s_k : p.s_q)) return;
   const int64_t block = NR * (KV ? 2 : 1) * 16 * 64, step = static_cast<int64_t>(nx) * block;      // in runs
   const run_t* src = reinterpret_cast<const run_t*>(KV ? p.partial : p.q_partial) +
@@ -674,6 +701,45 @@ int fwd_form(Args& p, const dfa_shape& sh, hipStream_t st) {
   return parts == 4 ? fwd<64, 4, Args>(p, st) : parts == 2 ? fwd<64, 2, Args>(p, st) : fwd<64, 1, Args>(p, st);
 }
 
+// Spans.  Parts per tile (NS) and parts that the keys of a span are cut in, by an estimate with what one box measured at d =
+// 128: 6 us per workgroup and, per tile of a walk, 8 us with 4 parts of 32 keys, 6.1 with 2 (11.4 where two workgroups share a
+// CU); a launch that runs in one round takes its longest walk, a longer one the device's even share and half a walk; the
+// merge 5 us and 3 TB/s.
+struct SpanPlan { int ns, parts; double us; };
+SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_t ws_bytes) {
+  SpanPlan best{0, 1, 0.};
+  const double width = sh.d == 128 ? 1.0 : 0.55;
+  for (int ns : {4, 2}) {
+    const int64_t blocks = blocks_of(sh.s_q, 128 / ns) * sh.h_q;
+    for (int parts = 1; parts <= MAX_SPAN_PARTS; ++parts) {
+      const SpanWork w = span_work(sh, spans, n, parts, blocks);
+      if (parts > 1 && (!w.cut || w.part_bytes > ws_bytes)) break;
+      const bool shared = ns == 2 && w.workgroups > 256;
+      const double tile = width * (ns == 4 ? 8.0 : shared ? 11.4 : 6.1) / (32 * ns);      // per key
+      SpanPlan x{ns, parts, 6 + w.longest * tile};
+      if (w.workgroups > (ns == 4 ? 256 : 512))
+        x.us = std::max(x.us, 6 + w.keys * tile / (shared ? 512 : 256) + 0.45 * w.longest * tile);
+      if (w.cut) x.us += 5 + 2 * w.part_bytes / 3e6;
+      if (!best.ns || x.us < best.us) best = x;
+    }
+  }
+  return best;
+}
+
+template <int D, int NS>
+int fwd_spans(F32FwdSpans& p, int n, hipStream_t st) {
+  const int rows = 32 * (4 / NS);
+  const size_t comb = sizeof(float) * (4 * (D / 32) * 16 * 64 + 256), tiles = smem_bytes<D, kTile<NS>>();
+  p.nx_q = static_cast<int>(blocks_of(p.s_q, rows));
+  const int64_t n_q = static_cast<int64_t>(p.nx_q) * p.h_q;
+  if (n_q * n > (1 << 30)) return DFA_ERR_SHAPE;
+  p.n_q = static_cast<int>(n_q);
+  p.heads = p.h_q % 8 == 0 ? p.h_q / 8 : 0;
+  p.map_q = xcd_map(n_q * n, 1, p.heads ? 8 : 1);
+  std::stable_sort(p.span, p.span + n, [](const Span& x, const Span& y) { return x.s_k > y.s_k; });
+  return launch<F32FwdSpans, k_fwd_f32<D, NS, F32FwdSpans>>(p, xcd_blocks(p.map_q), tiles > comb ? tiles : comb, st);
+}
+
 template <int D, int NS>
 int bwd(F32BwdParams p, hipStream_t st) {
   const int rows = 32 * (4 / NS);
@@ -723,7 +789,7 @@ struct Plan { int parts, shares, q_shares; double us; int64_t bytes; };
 
 Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
   const int group = sh.h_q / sh.h_kv;
-  const double width = sh.d == 128 ? 1.0 : 0.55, mean = sh.causal ? 0.5 : 1.0;
+  const double width = sh.d == 128 ? 1.0 : 0.55, mean = sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0;
   ws_bytes = std::min(ws_bytes, int64_t{128} << 20);
   const int max_q = dq && sh.s_k / 8 >= sh.s_q ? 64 : 1;
   Plan best{0, 0, 0, 0., 0};
@@ -800,6 +866,28 @@ int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void* 
 int64_t bwd_f32_workspace(const dfa_shape& sh, int n, bool dq, bool dk) {
   const int per = std::min(n, MAX_PAIRS);
   return plan(sh, per, dq, dk, INT64_MAX).bytes;
+}
+
+int launch_span_f32(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void* ws, int64_t ws_bytes, hipStream_t st) {
+  const SpanPlan pl = span_plan(sh, spans, n, ws ? ws_bytes : 0);
+  F32FwdSpans p{};
+  static_cast<F32Params&>(p) = make_params(sh);
+  p.causal = 1; p.pairs = 1;
+  return run_spans<MAX_PAIRS>(sh, spans, n, pl.parts, ws, st, [&](const SpanPart* part, int count) {
+    for (int i = 0; i < count; ++i) {
+      const SpanPart& x = part[i];
+      Span& y = p.span[i];
+      y.q = static_cast<const float*>(x.q); y.k = static_cast<const float*>(x.k); y.v = static_cast<const float*>(x.v);
+      y.o = x.o; y.lse = x.lse; y.accumulate = x.accumulate; y.o_sh = x.o_sh; y.o_ss = x.o_ss; y.l_sh = x.l_sh;
+      y.s_k = x.n_keys; y.off = x.off; y.o_bf16 = x.o_bf16;
+    }
+    if (sh.d == 128) return pl.ns == 4 ? fwd_spans<128, 4>(p, count, st) : fwd_spans<128, 2>(p, count, st);
+    return pl.ns == 4 ? fwd_spans<64, 4>(p, count, st) : fwd_spans<64, 2>(p, count, st);
+  });
+}
+
+int64_t span_f32_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
+  return span_work(sh, spans, n, span_plan(sh, spans, n, MAX_SPAN_BYTES).parts, 1).part_bytes;
 }
 
 }  // namespace dfa

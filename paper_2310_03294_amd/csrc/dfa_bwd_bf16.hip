@@ -54,8 +54,11 @@ constexpr int MAX_PAIRS = 16;       // per launch: the pairs travel in the kerne
 
 struct BwdParams {
   int s_q, s_k, h_q, h_kv, group, causal, q_first;
+  int off;                   // causal: key kv is visible to query row i if kv <= i + off (keys before the chunk's own)
   int parts;                 // dk, dv: workgroups that share the query tiles of a key tile
   f32x4* partial;            // parts > 1: their sums, PART_F4 per workgroup
+  int q_parts;               // dq: workgroups that share the key tiles of a row block
+  f32x4* q_partial;          // q_parts > 1: their sums
   Items kv_items, q_items;
   float scale;
   int64_t q_sh, q_ss, kv_sh, kv_ss, l_sh, dq_sh, dq_ss, dkv_sh, dkv_ss;
@@ -259,7 +262,8 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
     for (int j = 0; j < 16; ++j) acc[i][j] = 0.f;
 
   const float c2 = p.scale * LOG2E;
-  const int q_begin = p.causal ? k0 : 0;            // k0 is a multiple of BM
+  const int off = p.off;
+  const int q_begin = p.causal ? max(0, k0 - off) & ~(BM - 1) : 0;
   const int ntq = (p.s_q - q_begin + BM - 1) / BM;  // query tiles per head for this key tile
   // this workgroup's share of the group's ntq * group query tiles
   const int walk = ntq * p.group;
@@ -344,10 +348,10 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
       __builtin_amdgcn_s_setprio(0);
       // Only the causal diagonal needs a mask: query rows past s_q carry lse' = +inf (P = 0)
       // and key rows past s_k only feed dk/dv rows that are never written.
-      if (p.causal && q0 < k0 + BN - 1) {
+      if (p.causal && q0 + off < k0 + BN - 1) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-          const int qrow = q0 + (j >> 2) * 8 + hh * 4 + (j & 3);
+          const int qrow = q0 + off + (j >> 2) * 8 + hh * 4 + (j & 3);
           c0[j] = kvrow > qrow ? -INFINITY : c0[j];
           c1[j] = kvrow > qrow + 32 ? -INFINITY : c1[j];
         }
@@ -502,10 +506,12 @@ constexpr int TILE_BYTES = BN * kRowBytes;
 // used to hide, and no faster on short ones and on the causal diagonal pair, which keep the 128-row form).
 // NW = 8, NS = 2 (128 rows, one workgroup per CU, half the serial walk each) is for calls that do not fill
 // the device; the sums of the two parts are added through LDS at the end.
-template <int NW, int NS>
-__device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item, char* smem) {   // smem: two (K tile, V tile) buffers
+// PARTS: q_parts workgroups share the key tiles of a row block; k_reduce_dq adds their sums up.
+template <int NW, int NS, bool PARTS>
+__device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item, f32x4* partial, char* smem) {   // smem: two (K tile, V tile) buffers
   constexpr int BM = NW / NS * 32;     // query rows per workgroup
-  const int head = item / p.q_items.ntile;
+  const int share = PARTS ? item / p.q_items.ntile % p.q_parts : 0;
+  const int head = PARTS ? item / p.q_items.ntile / p.q_parts : item / p.q_items.ntile;
   int tq = item % p.q_items.ntile;
   if (p.causal) tq = p.q_items.ntile - 1 - tq;      // longest rows first
   const int kh = head / p.group;
@@ -561,17 +567,20 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
     for (int j = 0; j < 16; ++j) dqT[i][j] = 0.f;
   const float c2 = p.scale * LOG2E;
 
-  const int k_end = p.causal ? min(p.s_k, q0 + BM) : p.s_k;
-  const int ntiles = (k_end + BN - 1) / BN;
+  const int off = p.off;
+  const int k_end = p.causal ? min(p.s_k, q0 + BM + off) : p.s_k;
+  const int all = (k_end + BN - 1) / BN;
+  const int it0 = PARTS ? all * share / p.q_parts : 0, ntiles = PARTS ? all * (share + 1) / p.q_parts : all;
 
   // K/V tiles go from global memory straight into LDS; key rows past s_k are clamped to the last
   // row and masked below.  Tile t + 1 is on its way while tile t is computed on.
-  if (NW == 4 || wave < 4) tile_dma(kg, kv_rowbytes, 0, p.s_k - 1, tl, smem, cw, lane);
-  if (NW == 4 || wave >= 4) tile_dma(vg, kv_rowbytes, 0, p.s_k - 1, tl, smem + TILE_BYTES, cw, lane);
+  const char* first = smem + (PARTS ? (it0 & 1) * 2 * TILE_BYTES : 0);
+  if (NW == 4 || wave < 4) tile_dma(kg, kv_rowbytes, it0 * BN, p.s_k - 1, tl, first, cw, lane);
+  if (NW == 4 || wave >= 4) tile_dma(vg, kv_rowbytes, it0 * BN, p.s_k - 1, tl, first + TILE_BYTES, cw, lane);
   lds_dma_wait();
   __syncthreads();
 
-  for (int it = 0; it < ntiles; ++it) {
+  for (int it = it0; it < ntiles; ++it) {
     const int k0 = it * BN;
     const char* Ks = smem + (it & 1) * 2 * TILE_BYTES;
     const char* Vs = Ks + TILE_BYTES;
@@ -588,7 +597,7 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
                                        v_wave ? Kn + TILE_BYTES : Kn, cw, lane);
     const TileCopy cv = tile_copy_plan(vg, kv_rowbytes, kn0, p.s_k - 1, tl, Kn + TILE_BYTES, cw, lane);
 
-    const bool active = !(p.causal && k0 + (NS == 2 ? part * 32 : 0) > q0w + 31);
+    const bool active = !(p.causal && k0 + (NS == 2 ? part * 32 : 0) > q0w + 31 + off);
     if (!active) {      // nothing to compute for this wavefront's rows: only its share of the copies
       tile_copy_piece<0>(ck); tile_copy_piece<1>(ck); tile_copy_piece<2>(ck); tile_copy_piece<3>(ck);
       if (cw == 0) tile_copy_piece<4>(ck);
@@ -598,7 +607,7 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
       }
     }
     if (active) {
-      const bool need_mask = (k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w);
+      const bool need_mask = (k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w + off);
 #pragma unroll
       for (int n = 0; n < 2 / NS; ++n) {
         const int nb = NS == 2 ? part : n;       // 32-key block of the tile
@@ -642,7 +651,7 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             const int kvi = k0 + nb * 32 + (j >> 2) * 8 + hh * 4 + (j & 3);
-            if (kvi >= p.s_k || (p.causal && kvi > qrow)) dp[j] = 0.f;
+            if (kvi >= p.s_k || (p.causal && kvi > qrow + off)) dp[j] = 0.f;
           }
         }
         if (cw == 0 && (NW == 4 || n == 0)) tile_copy_piece<4>(n == 0 ? ck : cv);
@@ -680,6 +689,16 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 16; ++j) dqT[i][j] += x[(i * 16 + j) * 64];
+  }
+  if constexpr (PARTS) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      f32x4 a;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = dqT[i >> 2][(i & 3) * 4 + e];
+      partial[(rb * 16 + i) * 64 + lane] = a;
+    }
+    return;
   }
   if (qvalid) {
     float* dst = pr.dq + head * p.dq_sh + static_cast<int64_t>(qrow) * p.dq_ss;
@@ -733,6 +752,33 @@ __global__ void __launch_bounds__(kv::NT) k_reduce_dkdv(BwdPairs<MAX_PAIRS> p) {
   }
 }
 
+// dq of a row block of 128 rows from the sums of its parts: grid (4 column blocks, row blocks of all heads), 256 threads.
+constexpr int QPART_F4 = 4 * 16 * 64;
+__global__ void __launch_bounds__(256) k_reduce_dq(BwdPairs<1> p) {
+  const int ntile = p.q_items.ntile, tid = threadIdx.x, lane = tid & 63, rb = tid >> 6;
+  const int head = blockIdx.y / ntile, slot = blockIdx.y % ntile, tq = p.causal ? ntile - 1 - slot : slot;
+  const int row = tq * 128 + rb * 32 + (lane & 31);
+  if (row >= p.s_q) return;
+  const f32x4* src = p.q_partial + (static_cast<int64_t>(head) * p.q_parts * ntile + slot) * QPART_F4 + (rb * 16 + blockIdx.x * 4) * 64 + lane;
+  f32x4 a[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = src[i * 64];
+#pragma unroll 4      // (the reads of four parts on their way)
+  for (int s = 1; s < p.q_parts; ++s) {
+    src += static_cast<int64_t>(ntile) * QPART_F4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] += src[i * 64];
+  }
+  float* dst = p.pair[0].dq + head * p.dq_sh + static_cast<int64_t>(row) * p.dq_ss + blockIdx.x * 32 + (lane >> 5) * 4;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f32x4* d = reinterpret_cast<f32x4*>(dst + i * 8);
+    f32x4 x = a[i] * p.scale;
+    if (p.pair[0].acc_q) x += *d;
+    *d = x;
+  }
+}
+
 // The kernels: dk, dv alone, dq alone, and both kinds of workgroups in one launch; of NP pairs at most.
 template <bool RAGGED, bool PARTS, int NP>
 __device__ __forceinline__ void run_dkdv(const BwdPairs<NP>& p, int bid, char* smem) {
@@ -741,11 +787,12 @@ __device__ __forceinline__ void run_dkdv(const BwdPairs<NP>& p, int bid, char* s
     kv::dkdv<RAGGED, PARTS>(p, pair_of(p, p.kv_items, item), item_in_pair<NP>(p.kv_items, item),
                             p.partial + static_cast<int64_t>(item) * kv::PART_F4, smem);
 }
-template <int NW, int NS, int NP>
+template <int NW, int NS, bool PARTS, int NP>
 __device__ __forceinline__ void run_dq(const BwdPairs<NP>& p, int bid, char* smem) {
   const int item = xcd_item(p.q_items.map, bid);
   if (item < p.q_items.map.total)
-    qs::dq<NW, NS>(p, pair_of(p, p.q_items, item), item_in_pair<NP>(p.q_items, item), smem);
+    qs::dq<NW, NS, PARTS>(p, pair_of(p, p.q_items, item), item_in_pair<NP>(p.q_items, item),
+                          p.q_partial + static_cast<int64_t>(item) * QPART_F4, smem);
 }
 
 template <bool RAGGED, bool PARTS, int NP>
@@ -757,16 +804,16 @@ __global__ void __launch_bounds__(kv::NT, 2) k_bwd_dkdv_bf16(BwdPairs<NP> p) {
 template <int NW, int NP>
 __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPairs<NP> p) {
   extern __shared__ __align__(16) char smem[];
-  run_dq<NW, 1, NP>(p, blockIdx.x, smem);
+  run_dq<NW, 1, false, NP>(p, blockIdx.x, smem);
 }
 
-template <bool RAGGED, int NS, bool PARTS, int NP>
+template <bool RAGGED, int NS, bool PARTS, int NP, bool Q_PARTS = false>
 __global__ void __launch_bounds__(kv::NT, 2) k_bwd_bf16(BwdPairs<NP> p) {
   extern __shared__ __align__(16) char smem[];
   const int n_kv = p.kv_items.map.per_xcd * 8, n_q = p.q_items.map.per_xcd * 8;
   const int bid = blockIdx.x;
   if (p.q_first ? bid >= n_q : bid < n_kv) run_dkdv<RAGGED, PARTS, NP>(p, p.q_first ? bid - n_q : bid, smem);
-  else run_dq<8, NS, NP>(p, p.q_first ? bid : bid - n_kv, smem);
+  else run_dq<8, NS, Q_PARTS, NP>(p, p.q_first ? bid : bid - n_kv, smem);
 }
 
 // > 64 KB of dynamic LDS needs the opt-in, once per kernel and process (thread-safe)
@@ -806,7 +853,7 @@ constexpr int64_t PART_BYTES = kv::PART_F4 * 16;
 
 // How a call's work is divided: dq by 128-row workgroups with two key parts (split) or 256-row ones, and
 // `parts` workgroups per key tile for dk, dv.
-struct Plan { bool split; int parts; double us; };
+struct Plan { bool split; int parts; double us; int q_parts; int64_t bytes; bool q_first; };
 
 // dq by 128-row workgroups with two key parts while all workgroups still run at once (8 heads x 2048: 60
 // us, with 256 rows 72), by 256-row ones if that makes them (8 x 2304: 84, with 128 rows 108), then by
@@ -826,27 +873,40 @@ bool split_dq(int64_t n_kv, int64_t n256, int64_t n128) {
 // parts: 8 over 2 heads x 1024 87 / 51 / 35, x 4096 341 / 217 / 212, x 8192 814 / 761 / 767; 32 over 8 x
 // 1024 91 / 66 / 73, x 1500 diagonal 135 / 101 / 103, x 4096 756 / 779 / 810; 8 heads of their own x 1024
 // 31 / 36 / 38.
+// Parts of dq, for a few query rows against many keys (a span of chunks), where a row block's walk over all of them would be the
+// whole call: `q_parts` workgroups of 128 rows share it, from two keys per row on.
 Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
   const int group = sh.h_q / sh.h_kv;
   const int64_t kv1 = dk ? blocks_of(sh.s_k, kv::BN) * sh.h_kv * pairs : 0;
   const int64_t n256 = dq ? blocks_of(sh.s_q, 256) * sh.h_q * pairs : 0;
   const int64_t n128 = dq ? blocks_of(sh.s_q, 128) * sh.h_q * pairs : 0;
   const double walk_kv = 1.35 * group * blocks_of(sh.s_q, kv::BM), walk_q = 1.9 * blocks_of(sh.s_k, qs::BN);
-  const double mean = sh.causal ? 0.5 : 1.0;           // of a walk
+  // of a walk: the query chunk's own keys are half visible
+  const double mean_kv = sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0, mean_q = mean_kv;
+  ws_bytes = std::min(ws_bytes, int64_t{128} << 20);
+  const int most_q = dq && dk && pairs == 1 && sh.s_k / 2 >= sh.s_q ? 16 : 1;
   Plan best{};
-  for (int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-    const int64_t n_kv = kv1 * parts;
-    if (parts > 1 && (!dk || parts > 4 * group || n_kv > 1024 || n_kv * PART_BYTES > ws_bytes)) break;
-    Plan x{dq && split_dq(n_kv, n256, n128), parts, 0.};
-    const int64_t n_q = x.split ? n128 : n256;
-    const double t_kv = dk ? 8 + walk_kv / parts : 0, w_q = x.split ? walk_q / 2 : walk_q, t_q = dq ? 8 + w_q : 0;
-    x.us = std::max(t_kv, t_q);
-    if (n_kv + n_q > 256) {
-      const double share = (n_kv * (8 + walk_kv * mean / parts) + n_q * (8 + w_q * mean)) / 256;
-      x.us = std::max(x.us, share + 0.45 * x.us);
+  for (int q_parts = 1; q_parts <= most_q; ++q_parts) {
+    const int64_t q_bytes = q_parts > 1 ? n128 * q_parts * QPART_F4 * 16 : 0;
+    if (q_parts > 1 && (n128 * q_parts > 1024 || q_bytes > ws_bytes)) break;
+    for (int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+      const int64_t n_kv = kv1 * parts, bytes = q_bytes + (parts > 1 ? n_kv * PART_BYTES : 0);
+      if (parts > 1 && (!dk || parts > 4 * group || n_kv > 1024 || bytes > ws_bytes)) break;
+      Plan x{dq && (q_parts > 1 || split_dq(n_kv, n256, n128)), parts, 0., q_parts, bytes};
+      const int64_t n_q = x.split ? n128 * q_parts : n256;
+      const double t_kv = dk ? 8 + walk_kv / parts : 0, w_q = x.split ? walk_q / 2 / q_parts : walk_q, t_q = dq ? 8 + w_q : 0;
+      x.us = std::max(t_kv, t_q);
+      if (n_kv + n_q > 256) {
+        // (of a span, the longer kind goes first and the shorter fills the end; two key parts copy every tile for half the rows)
+        const double q_us = n_q * (8 + w_q * mean_q) * (most_q > 1 && x.split ? 1.15 : 1.0);
+        const double share = (n_kv * (8 + walk_kv * mean_kv / parts) + q_us) / 256;
+        x.us = std::max(x.us, share + 0.45 * (most_q > 1 ? std::min(t_kv, t_q) : x.us));
+      }
+      x.q_first = most_q > 1 ? t_q > t_kv : group <= parts;
+      if (parts > 1) x.us = (x.us + 4 + n_kv * (2 * PART_BYTES / 2.5e6)) * (group % parts ? 1.15 : 1.0);
+      if (q_parts > 1) x.us += 4 + 2 * q_bytes / 2.5e6;
+      if ((parts == 1 && q_parts == 1) || x.us < (best.parts == 1 && best.q_parts == 1 ? 0.92 : 1.0) * best.us) best = x;
     }
-    if (parts > 1) x.us = (x.us + 4 + n_kv * (2 * PART_BYTES / 2.5e6)) * (group % parts ? 1.15 : 1.0);
-    if (parts == 1 || x.us < (best.parts == 1 ? 0.92 : 1.0) * best.us) best = x;
   }
   return best;
 }
@@ -867,7 +927,7 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
                      x.accumulate_dkv};
   }
   p.s_q = sh.s_q; p.s_k = sh.s_k; p.h_q = sh.h_q; p.h_kv = sh.h_kv; p.group = sh.h_q / sh.h_kv;
-  p.causal = sh.causal; p.scale = sh.scale;
+  p.causal = sh.causal; p.off = sh.s_k - sh.s_q; p.scale = sh.scale;
   p.q_sh = sh.q_stride_h; p.q_ss = sh.q_stride_s; p.kv_sh = sh.kv_stride_h; p.kv_ss = sh.kv_stride_s;
   p.l_sh = sh.lse_stride_h; p.dq_sh = sh.dq_stride_h; p.dq_ss = sh.dq_stride_s;
   p.dkv_sh = sh.dkv_stride_h; p.dkv_ss = sh.dkv_stride_s;
@@ -875,11 +935,18 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
   const bool ragged = sh.s_q % kv::BM != 0, dq = pairs[0].dq, dk = pairs[0].dk;
   const Plan pl = plan(sh, n, dq, dk, ws ? ws_bytes : 0);
   p.parts = pl.parts;
-  p.partial = static_cast<f32x4*>(ws);
+  p.q_parts = pl.q_parts;
+  p.partial = p.q_partial = static_cast<f32x4*>(ws);
+  if (p.parts > 1) p.q_partial += p.parts * blocks_of(sh.s_k, kv::BN) * sh.h_kv * n * kv::PART_F4;
   if (dk && !make_items(p.kv_items, sh.s_k, kv::BN, sh.h_kv * p.parts, n, sh.causal)) return DFA_ERR_SHAPE;
   auto reduce = [&] {
-    if (p.parts == 1) return static_cast<int>(DFA_OK);
-    k_reduce_dkdv<<<dim3(4, p.kv_items.map.total / p.parts), kv::NT, 0, st>>>(p);
+    if (p.parts > 1) k_reduce_dkdv<<<dim3(4, p.kv_items.map.total / p.parts), kv::NT, 0, st>>>(p);
+    if (p.q_parts > 1) {
+      BwdPairs<1> one;
+      static_cast<BwdParams&>(one) = p;
+      one.pair[0] = p.pair[0];
+      k_reduce_dq<<<dim3(4, p.q_items.map.total / p.q_parts), 256, 0, st>>>(one);
+    }
     return last_launch_status();
   };
   if (dk && dq) {
@@ -888,8 +955,8 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
     // 823 / 804, x 16384 12364 / 12350;  32 over 8 heads x 1024 119 / 91, x 4096 802 / 783, causal 560 / 475.
     // (Within 2 % either way where the last round of workgroups decides, e.g. 32 x 2777 426 / 435.)
     // The longer workgroups first: a dk/dv workgroup walks over its part of the query heads of a group.
-    p.q_first = p.group <= p.parts;
-    if (!make_items(p.q_items, sh.s_q, pl.split ? 128 : 256, sh.h_q, n, sh.causal)) return DFA_ERR_SHAPE;
+    p.q_first = pl.q_first;
+    if (!make_items(p.q_items, sh.s_q, pl.split ? 128 : 256, sh.h_q * p.q_parts, n, sh.causal)) return DFA_ERR_SHAPE;
     const int64_t blocks = xcd_blocks(p.kv_items.map) + xcd_blocks(p.q_items.map);
     // Ten rounds of workgroups and more: nothing is left to fill, and each kind alone has the better use of
     // the L2 (32 heads x 12000 6775 against 6808 us).  (Nor would a grid take more than 2^23 of them.)  A list stays
@@ -907,6 +974,8 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
       constexpr int NP = m() ? MAX_PAIRS : 1;
       return with(ragged, [&](auto r) {
         return with(p.parts > 1, [&](auto s) {
+          if constexpr (NP == 1)
+            if (p.q_parts > 1) return launch<1, k_bwd_bf16<r(), 2, s(), 1, true>>(p, blocks, kv::NT, kv::SMEM_BYTES, st);
           return pl.split ? launch<NP, k_bwd_bf16<r(), 2, s(), NP>>(p, blocks, kv::NT, kv::SMEM_BYTES, st)
                           : launch<NP, k_bwd_bf16<r(), 1, s(), NP>>(p, blocks, kv::NT, kv::SMEM_BYTES, st);
         });
@@ -926,7 +995,7 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
       return rc ? rc : reduce();
     }
     // dq alone: 256-row workgroups for long unmasked chunks (at least four of them per CU), 128 rows otherwise
-    const bool wide = !sh.causal && blocks_of(sh.s_q, 256) * sh.h_q * n >= 1024;
+    const bool wide = (!sh.causal || sh.s_k / 2 >= sh.s_q) && blocks_of(sh.s_q, 256) * sh.h_q * n >= 1024;
     if (!make_items(p.q_items, sh.s_q, wide ? 256 : 128, sh.h_q, n, sh.causal)) return static_cast<int>(DFA_ERR_SHAPE);
     const int64_t blocks = xcd_blocks(p.q_items.map);
     return wide ? launch<NP, k_bwd_dq_bf16<8, NP>>(p, blocks, 512, 4 * qs::TILE_BYTES, st)
@@ -935,9 +1004,7 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
 }
 
 int64_t bwd_bf16_workspace(const dfa_shape& sh, int n, bool dq, bool dk) {
-  const int per = std::min(n, MAX_PAIRS);
-  const Plan pl = plan(sh, per, dq, dk, INT64_MAX);
-  return pl.parts > 1 ? pl.parts * blocks_of(sh.s_k, kv::BN) * sh.h_kv * per * PART_BYTES : 0;
+  return plan(sh, std::min(n, MAX_PAIRS), dq, dk, INT64_MAX).bytes;
 }
 
 }  // namespace dfa

@@ -11,11 +11,13 @@
 // into LDS (double-buffered); K is read from LDS with ds_read_b128, V with the transposing
 // ds_read_b64_tr_b16.  The causal mask is applied only on tiles that straddle the
 // diagonal; tiles above it are skipped.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
 #include "dfa_internal.h"
 #include "dfa_mfma.h"
+#include "dfa_span.h"
 
 namespace dfa {
 namespace {
@@ -49,9 +51,37 @@ struct FwdBatch : FwdParams {
   Pair pair[MAX_PAIRS];
 };
 
+// Spans: query chunks against consecutive keys, each span with a number of keys of its own, the last of which may be the
+// chunk's own.  The longest walks come first: an XCD takes its heads of all spans, span by span (`heads` of them; 0: the
+// heads do not divide into XCDs, and the items of a span go over all XCDs in turn).
+struct Span : Pair { int s_k, off, o_bf16; };       // off: key kv is visible to query row i if kv <= i + off
+struct FwdSpans : FwdParams {
+  int per_pair, heads;
+  Span span[MAX_PAIRS];
+};
+struct SpanParams : FwdParams { int off; };
+
+// Keys up to which query row 0 sees (a single pair or a list of pairs of equal chunks: its own).
+template <class P> __device__ __forceinline__ int off_of(const P&) { return 0; }
+__device__ __forceinline__ int off_of(const SpanParams& p) { return p.off; }
+
 // The operands of an item's pair; item becomes its number within the pair.  (One pair alone is no list:
 // picking it costs every workgroup another round trip to the argument memory.)
 __device__ __forceinline__ const FwdParams& pair_of(const FwdParams& a, int&) { return a; }
+__device__ __forceinline__ SpanParams pair_of(const FwdSpans& a, int& item) {
+  int i = item / a.per_pair, r = item % a.per_pair;
+  if (a.heads) {
+    const int x = item / a.map.per_xcd, y = item % a.map.per_xcd, run = a.heads * a.ntq;      // items of a span on an XCD
+    i = y / run; r = x * run + y % run;
+  }
+  item = r;
+  SpanParams p;
+  static_cast<FwdParams&>(p) = a;
+  const Span& s = a.span[i];
+  p.q = s.q; p.k = s.k; p.v = s.v; p.o = s.o; p.lse = s.lse; p.accumulate = s.accumulate;
+  p.o_sh = s.o_sh; p.o_ss = s.o_ss; p.l_sh = s.l_sh; p.s_k = s.s_k; p.o_bf16 = s.o_bf16; p.off = s.off;
+  return p;
+}
 __device__ __forceinline__ FwdParams pair_of(const FwdBatch& a, int& item) {
   FwdParams p = a;
   const Pair& x = a.pair[item / a.per_pair];
@@ -107,7 +137,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
   const int bid = blockIdx.x;
   int item = xcd_item(a.map, bid);
   if (item >= a.map.total) return;
-  const FwdParams& p = pair_of(a, item);
+  const auto& p = pair_of(a, item);
   const int head = item / p.ntq;
   int tq = item % p.ntq;
   if (p.causal) tq = p.ntq - 1 - tq;      // longest rows first
@@ -159,7 +189,8 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
     }
   }
 
-  const int k_end = p.causal ? min(p.s_k, q0 + BM) : p.s_k;
+  const int off = off_of(p);
+  const int k_end = p.causal ? min(p.s_k, q0 + BM + off) : p.s_k;
   const int ntiles = (k_end + BN - 1) / BN;
 
   // K/V tiles go from global memory straight into LDS; key rows past s_k are clamped to the last
@@ -213,7 +244,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const int kvi = kbase + (j >> 2) * 8 + hh * 4 + (j & 3);
-      if (kvi >= p.s_k || (p.causal && kvi > qrow)) s[j] = -INFINITY;
+      if (kvi >= p.s_k || (p.causal && kvi > qrow + off)) s[j] = -INFINITY;
     }
   };
 
@@ -232,14 +263,14 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
     const TileCopy ck = tile_copy_plan(kg, kv_rowbytes, kn0, p.s_k - 1, tl, Kn, wave, lane);
     const TileCopy cv = tile_copy_plan(vg, kv_rowbytes, kn0, p.s_k - 1, tl, Kn + TILE_BYTES, wave, lane);
 
-    const bool active = !(p.causal && k0 > q0w + 31);
+    const bool active = !(p.causal && k0 > q0w + 31 + off);
     if (!active) {      // nothing to compute for this wavefront's rows: only its share of the copies
       tile_copy_piece<0>(ck); tile_copy_piece<1>(ck); tile_copy_piece<2>(ck); tile_copy_piece<3>(ck);
       tile_copy_piece<0>(cv); tile_copy_piece<1>(cv); tile_copy_piece<2>(cv); tile_copy_piece<3>(cv);
       if (wave == 0) { tile_copy_piece<4>(ck); tile_copy_piece<4>(cv); }
     }
     if (active) {
-      const bool need_mask = (k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w);
+      const bool need_mask = (k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w + off);
       // Software pipeline over the two 32-key blocks of the tile: the MFMAs of one block run
       // under the softmax arithmetic of the other; LDS operand reads run ahead of their MFMAs.
       bf16x8 ka[4], gv[2], pb0[2], pb1[2];
@@ -364,15 +395,16 @@ constexpr int OFF_ST = OFF_AL + 2 * AL_BYTES;  // 1 / row sum, written once by t
 constexpr int SMEM_BYTES = OFF_ST + AL_BYTES;
 
 // RAGGED: s_k is no multiple of the 64-row tile, so the last K/V tile has rows past the end.
-// CAUSAL: the diagonal pair; its row sums are taken over the fp32 weights, as in the other causal forms.
-template <bool RAGGED, bool CAUSAL, class Args>
+// CAUSAL: the diagonal pair; its row sums are taken over the fp32 weights, as in the other causal forms (ROUNDED: a chunk of
+// keys and more before the diagonal; over the rounded weights, as for full pairs).
+template <bool RAGGED, bool CAUSAL, class Args, bool ROUNDED = !CAUSAL>
 __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
   extern __shared__ __align__(16) char smem[];
 
   const int bid = blockIdx.x;
   int item = xcd_item(a.map, bid);
   if (item >= a.map.total) return;
-  const FwdParams& p = pair_of(a, item);
+  const auto& p = pair_of(a, item);
   const int head = item / p.ntq;
   int tq = item % p.ntq;
   if (CAUSAL) tq = p.ntq - 1 - tq;      // longest rows first
@@ -385,7 +417,8 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
   const int r32 = lane & 31, hh = lane >> 5;
   const float c2 = p.scale * LOG2E;
 
-  const int k_end = CAUSAL ? min(p.s_k, q0 + BMW) : p.s_k;
+  const int off = off_of(p);
+  const int k_end = CAUSAL ? min(p.s_k, q0 + BMW + off) : p.s_k;
   const int ntiles = (k_end + BN - 1) / BN;
 
   if (!pv_wave) {
@@ -432,7 +465,7 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
                                          wave < 4 ? smem + OFF_K + ((it + 1) & 1) * TILE_BYTES
                                                   : smem + OFF_V + ((it + 1) % 3) * TILE_BYTES,
                                          wave & 3, lane);
-      const bool active = !(CAUSAL && k0 > q0w + 31);   // else: the whole tile lies above this block's diagonal
+      const bool active = !(CAUSAL && k0 > q0w + 31 + off);   // else: the whole tile lies above this block's diagonal
       if (!active) {
         tile_copy_piece<0>(cn); tile_copy_piece<1>(cn); tile_copy_piece<2>(cn); tile_copy_piece<3>(cn);
         if ((wave & 3) == 0) tile_copy_piece<4>(cn);
@@ -472,12 +505,12 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
           }
           __builtin_amdgcn_s_setprio(0);
           if (COPIES && (wave & 3) == 0) tile_copy_piece<4>(cn);
-          if ((k0 + BN > p.s_k) || (CAUSAL && k0 + BN - 1 > q0w)) {
+          if ((k0 + BN > p.s_k) || (CAUSAL && k0 + BN - 1 > q0w + off)) {
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
               const int kvi = k0 + (j >> 2) * 8 + hh * 4 + (j & 3);
-              if (kvi >= p.s_k || (CAUSAL && kvi > qrow)) s0[j] = -INFINITY;
-              if (kvi + 32 >= p.s_k || (CAUSAL && kvi + 32 > qrow)) s1[j] = -INFINITY;
+              if (kvi >= p.s_k || (CAUSAL && kvi > qrow + off)) s0[j] = -INFINITY;
+              if (kvi + 32 >= p.s_k || (CAUSAL && kvi + 32 > qrow + off)) s1[j] = -INFINITY;
             }
           }
         };
@@ -508,7 +541,7 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
           }
           p0 = pack8(s0, 0); p1 = pack8(s0, 8); p2 = pack8(s1, 0); p3 = pack8(s1, 8);
           // independent chains, so that the adds do not wait for one another
-          if constexpr (CAUSAL) {
+          if constexpr (!ROUNDED) {
             float a[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < 16; ++j) { a[j & 1] += s0[j]; a[2 + (j & 1)] += s1[j]; }
@@ -572,7 +605,7 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
     // O^T = O^T * factor + V^T P^T for tile t (skipped when the tile lies above the block's diagonal)
     auto pv_tile = [&](int t) {
       const int k0 = t * BN;
-      if (CAUSAL && k0 > q0w + 31) return;
+      if (CAUSAL && k0 > q0w + 31 + off) return;
       const char* Vs = smem + OFF_V + (t % 3) * TILE_BYTES;
       const char* px = smem + OFF_PX + (t & 1) * PX_BYTES + sw * 4096 + lane * 16;
       const float a = reinterpret_cast<const float*>(smem + OFF_AL)[(t & 1) * (AL_BYTES / 4) + sw * 32 + r32];
@@ -645,7 +678,7 @@ template <int NS> constexpr int kTilesBytes = 2 * (kKeys<NS> / BN) * TILE_BYTES;
 template <int NS> constexpr int kSmem = 2 * kTilesBytes<NS>;
 constexpr int RES_BYTES = 64 * 64 * 4;         // a wavefront's O^T, 64 registers per lane
 
-template <int RB, int NS, bool CAUSAL, class Args>
+template <int RB, int NS, bool CAUSAL, class Args, bool ROUNDED = !CAUSAL>
 __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16(Args a) {
   constexpr int BMS = RB * 32;                 // query rows per workgroup
   constexpr bool LO = RB == 2;
@@ -655,7 +688,7 @@ __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16
   const int bid = blockIdx.x;
   int item = xcd_item(a.map, bid);
   if (item >= a.map.total) return;
-  const FwdParams& p = pair_of(a, item);
+  const auto& p = pair_of(a, item);
   const int head = item / p.ntq;
   int tq = item % p.ntq;
   if (CAUSAL) tq = p.ntq - 1 - tq;           // longest rows first
@@ -670,7 +703,8 @@ __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16
   const char* kg = reinterpret_cast<const char*>(p.k + kh * p.kv_sh);
   const char* vg = reinterpret_cast<const char*>(p.v + kh * p.kv_sh);
   const uint32_t kv_rowbytes = static_cast<uint32_t>(p.kv_ss) * 2;
-  const int k_end = CAUSAL ? min(p.s_k, q0 + BMS) : p.s_k;
+  const int off = off_of(p);
+  const int k_end = CAUSAL ? min(p.s_k, q0 + BMS + off) : p.s_k;
   const int ntiles = (k_end + kKeys<NS> - 1) / kKeys<NS>;
   // wavefronts 4s .. 4s + 3 copy sub-tile s of K and of V
   // (8 wavefronts and one sub-tile: 0-3 copy K, 4-7 copy V)
@@ -735,7 +769,7 @@ __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16
       const char* Ks = buf + (part >> 1) * TILE_BYTES;
       const char* Vs = Ks + SUB * TILE_BYTES;
       const int row = (part & 1) * 32 * kRowBytes;
-      if (kb0 < p.s_k && !(CAUSAL && kb0 > q0w + 31)) {
+      if (kb0 < p.s_k && !(CAUSAL && kb0 > q0w + 31 + off)) {
         bf16x8 ka[4], gv[4];
         f32x16 s;
 #pragma unroll
@@ -756,11 +790,11 @@ __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16
         if (cw == 0) { tile_copy_piece<4>(ck); if (!ONE) tile_copy_piece<4>(cv); }
 #pragma unroll
         for (int i = 0; i < 4; ++i) gv[i] = lds_gather(Vs, g_base + row + i * 64);
-        if (kb0 + 32 > p.s_k || (CAUSAL && kb0 + 31 > q0w)) {
+        if (kb0 + 32 > p.s_k || (CAUSAL && kb0 + 31 > q0w + off)) {
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             const int kvi = kb0 + (j >> 2) * 8 + hh * 4 + (j & 3);
-            if (kvi >= p.s_k || (CAUSAL && kvi > qrow)) s[j] = -INFINITY;
+            if (kvi >= p.s_k || (CAUSAL && kvi > qrow + off)) s[j] = -INFINITY;
           }
         }
         // online softmax with the lazy running maximum of the 128-row kernel
@@ -782,7 +816,7 @@ __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
           s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], c2, -mc));
-          if (LO || CAUSAL) sum += s[j];
+          if (LO || !ROUNDED) sum += s[j];
         }
         if (__any(alpha != 1.f)) {
 #pragma unroll
@@ -799,7 +833,7 @@ __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16
             for (int e = 0; e < 8; ++e) s[8 * u + e] -= static_cast<float>(pb[u][e]);
             pl[u] = pack8(s, 8 * u);
           }
-          if (!LO && !CAUSAL) sum = sum8(pb[u], sum);
+          if (!LO && ROUNDED) sum = sum8(pb[u], sum);
         }
         l_run += sum;
         DFA_SCHED_FENCE();
@@ -992,6 +1026,55 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
                 : launch<Args, full_pair::k_fwd_bf16<false, false, Args>>(p, nt, smem, st);
 }
 
+// The spans of a launch.  Which form, and in how many parts the keys of a span are cut (the parts are merged afterwards):
+// by an estimate, with what one box measured for its terms: 8 us per workgroup and, per 64 keys, 0.95 us with 64-row
+// workgroups (four key parts), 1.1 with 128-row ones (two) and 1.9 with 256-row ones; a launch that runs in one round takes its
+// longest walk, a longer one the device's even share and about half a walk; the merge 5 us and 3 TB/s.
+struct SpanPlan { int rows, parts; double us; bool rounded; };
+
+SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_t ws_bytes) {
+  SpanPlan best{};
+  bool whole = true, rounded = true;      // (launch_spans)
+  for (int i = 0; i < n; ++i) {
+    whole &= spans[i].n_keys % BN == 0;
+    rounded &= !spans[i].own || spans[i].n_keys >= 2 * static_cast<int64_t>(sh.s_q);
+  }
+  for (int rows : {64, 128, 256}) {
+    if (rows == 256 && !whole && !rounded) break;
+    const double tile = rows == 64 ? 0.95 : rows == 128 ? 1.1 : 1.9;
+    const int64_t blocks = (static_cast<int64_t>(sh.s_q) + rows - 1) / rows * sh.h_q;
+    for (int parts = 1; parts <= MAX_SPAN_PARTS; ++parts) {
+      const SpanWork w = span_work(sh, spans, n, parts, blocks);
+      if (parts > 1 && (!w.cut || w.part_bytes > ws_bytes)) break;
+      SpanPlan x{rows, parts, 8 + w.longest / 64 * tile, rounded};
+      if (w.workgroups > 256) x.us = std::max(x.us, 8 + w.keys / 64 * tile / 256 + 0.45 * w.longest / 64 * tile);
+      if (w.cut) x.us += 5 + 2 * w.part_bytes / 3e6;
+      if (!best.rows || x.us < best.us) best = x;
+    }
+  }
+  return best;
+}
+
+// Where every span has a chunk and more of keys before its own, row sums are taken over the rounded weights, as for full pairs;
+// over the fp32 weights otherwise (256 rows: of whole tiles only, the ragged form spills).
+int launch_spans(FwdSpans& p, const dfa_shape& sh, int n, int rows, bool rounded, hipStream_t st) {
+  p.ntq = (sh.s_q + rows - 1) / rows;
+  p.per_pair = p.ntq * sh.h_q;
+  p.heads = sh.h_q % 8 == 0 ? sh.h_q / 8 : 0;
+  if (static_cast<int64_t>(p.per_pair) * n > (1 << 30)) return DFA_ERR_SHAPE;
+  p.map = xcd_map(static_cast<int64_t>(p.per_pair) * n, 1, p.heads ? 8 : 1);      // (1: every second row of items backwards)
+  std::stable_sort(p.span, p.span + n, [](const Span& x, const Span& y) { return x.s_k > y.s_k; });
+  if (rows == 64) return launch<FwdSpans, split::k_fwd_bf16<2, 4, true, FwdSpans>>(p, 512, split::kSmem<4>, st);
+  if (rows == 128) return rounded ? launch<FwdSpans, split::k_fwd_bf16<4, 2, true, FwdSpans, true>>(p, 512, split::kSmem<2>, st)
+                                  : launch<FwdSpans, split::k_fwd_bf16<4, 2, true, FwdSpans>>(p, 512, split::kSmem<2>, st);
+  constexpr int nt = full_pair::NT, smem = full_pair::SMEM_BYTES;
+  bool whole = true;
+  for (int i = 0; i < n; ++i) whole &= p.span[i].s_k % BN == 0;
+  if (!rounded) return launch<FwdSpans, full_pair::k_fwd_bf16<false, true, FwdSpans>>(p, nt, smem, st);
+  return whole ? launch<FwdSpans, full_pair::k_fwd_bf16<false, true, FwdSpans, true>>(p, nt, smem, st)
+               : launch<FwdSpans, full_pair::k_fwd_bf16<true, true, FwdSpans, true>>(p, nt, smem, st);
+}
+
 }  // namespace
 
 int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st) {
@@ -1014,6 +1097,27 @@ int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipSt
                      y.lse_stride_h};
   }
   return launch_form<FwdBatch>(p, sh, n, st);
+}
+
+int launch_span_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void* ws, int64_t ws_bytes, hipStream_t st) {
+  const SpanPlan pl = span_plan(sh, spans, n, ws ? ws_bytes : 0);
+  FwdSpans p{};
+  p.s_q = sh.s_q; p.s_k = sh.s_k; p.h_q = sh.h_q; p.group = sh.h_q / sh.h_kv; p.causal = 1; p.scale = sh.scale;
+  p.q_sh = sh.q_stride_h; p.q_ss = sh.q_stride_s; p.kv_sh = sh.kv_stride_h; p.kv_ss = sh.kv_stride_s;
+  return run_spans<MAX_PAIRS>(sh, spans, n, pl.parts, ws, st, [&](const SpanPart* part, int count) {
+    for (int i = 0; i < count; ++i) {
+      const SpanPart& x = part[i];
+      Span& y = p.span[i];
+      y.q = static_cast<const __bf16*>(x.q); y.k = static_cast<const __bf16*>(x.k); y.v = static_cast<const __bf16*>(x.v);
+      y.o = x.o; y.lse = x.lse; y.accumulate = x.accumulate; y.o_sh = x.o_sh; y.o_ss = x.o_ss; y.l_sh = x.l_sh;
+      y.s_k = x.n_keys; y.off = x.off; y.o_bf16 = x.o_bf16;
+    }
+    return launch_spans(p, sh, count, pl.rows, pl.rounded, st);
+  });
+}
+
+int64_t span_bf16_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
+  return span_work(sh, spans, n, span_plan(sh, spans, n, MAX_SPAN_BYTES).parts, 1).part_bytes;
 }
 
 }  // namespace dfa

@@ -10,6 +10,11 @@ namespace dfa {
 
 // Launch wrappers: every one validates nothing (the ABI layer did) and returns a dfa_status.
 int launch_merge(const dfa_merge_desc& md, const dfa_merge_pair* pairs, int n, hipStream_t st);
+// Several partials (o_b, lse_b) into one (o, lse) each, which takes part (accumulate) or is only written.
+struct MergeShape { int heads, rows, d; bool b_bf16; int64_t b_sh, b_ss, lb_sh; };
+struct MergeGroup { void* o; float* lse; int64_t o_sh, o_ss, l_sh; int first, n, accumulate, o_bf16; };
+struct MergePart { const void* o; const float* lse; };
+int launch_merge_parts(const MergeShape& sh, const MergeGroup* groups, int n, const MergePart* parts, hipStream_t st);
 int launch_delta(const dfa_shape& sh, const void* o, const void* dO, float* delta, hipStream_t st);
 int launch_fill_zero_rows(float* p, int heads, int rows, int d, int64_t stride_h, int64_t stride_s,
                           hipStream_t st);
@@ -23,6 +28,12 @@ int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void* 
 int64_t bwd_f32_workspace(const dfa_shape& sh, int n, bool dq, bool dk);
 
 int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st);
+
+// Spans.  Their keys are cut in parts where that pays; the parts' results take ws (span_part_bytes() each) and are merged.
+int launch_span_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void* ws, int64_t ws_bytes, hipStream_t st);
+int launch_span_f32(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void* ws, int64_t ws_bytes, hipStream_t st);
+int64_t span_bf16_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int n);
+int64_t span_f32_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int n);
 int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void* ws, int64_t ws_bytes,
                     hipStream_t st);
 int64_t bwd_bf16_workspace(const dfa_shape& sh, int n, bool dq, bool dk);

@@ -114,6 +114,34 @@ def forward_worker(Q, K, V, scale, P, w, bufs: Buffers, remote=None, mode="balan
     return sent
 
 
+def _walk(sched, w, state):
+    """The pairs of a worker's own chunk, in the order of its steps, as one walk from the empty state."""
+    return [(w, st.kv_chunk, state, w, st.kind == B.DFA_STEP_OWN) for st in sched
+            if st.kind in (B.DFA_STEP_DIAG, B.DFA_STEP_OWN)]
+
+
+def _forward_at_hand(Q, K, V, scale, sched, w, bufs: Buffers, remote):
+    """forward_worker for a worker that has all its key/value chunks and all partials at hand: one walk over its own and its
+    earlier chunks and its HELP pairs as one launch, the partials merged in one pass.  (Step by step, a
+    short chunk's pairs are a chain of launches that each leave most of the device idle.)"""
+    fwd = B.ForwardChunks(Q, K, V, bufs.c, scale)
+    sent, pairs = {}, _walk(sched, w, fwd.dest(bufs.O, bufs.L))
+    for st in sched:
+        if st.kind == B.DFA_STEP_HELP:
+            po = torch.empty_like(bufs.part_o[0]); pl = torch.empty_like(bufs.part_l[0])
+            pairs.append((st.q_chunk, w, fwd.dest(po, pl), 0, False))
+            sent[st.send_to] = (po, pl)
+    fwd.launch(pairs, None)
+    if remote is not None:
+        parts = [remote[st.recv_from] for st in sched if st.recv_from >= 0]
+        if all(o.stride() == parts[0][0].stride() and l.stride() == parts[0][1].stride() for o, l in parts):
+            B.dfa_merge_batch(bufs.O, bufs.L, bufs.c, [(w, o, l) for o, l in parts])
+        else:
+            for o, l in parts:
+                B.dfa_merge(_chunk(bufs.O, w, bufs.c), _chunk(bufs.L, w, bufs.c), o, l)
+    return sent
+
+
 def new_pass():
     """Bookkeeping of one backward pass: which dQ / dK,dV chunks already hold a contribution.
     The first contribution to a chunk overwrites it (no zero-fill, no read of stale values), the
@@ -142,10 +170,29 @@ def backward_worker(Q, K, V, dO, scale, P, w, bufs: Buffers, mode="balanced", wi
             touched["dq"].add(qc); touched["dkv"].add(kc)
 
 
+def _backward_at_hand(Q, K, V, dO, scale, sched, w, bufs: Buffers):
+    """backward_worker for a worker that has all its key/value chunks at hand, into gradient chunks that hold nothing yet: its
+    own and its earlier chunks as one call, then its HELP pairs, all with its own key/value chunk."""
+    c = bufs.c
+    B.dfa_delta(_chunk(bufs.O, w, c), _chunk(dO, w, c), delta=_chunk(bufs.delta, w, c))
+    bwd = B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, bufs.dQ, bufs.dK, bufs.dV, c, scale)
+    bwd.launch_span(w, min(st.kv_chunk for st in sched if st.kind in (B.DFA_STEP_DIAG, B.DFA_STEP_OWN)), w, False, False)
+    for st in sched:
+        if st.kind == B.DFA_STEP_HELP:
+            bwd.launch([(st.q_chunk, w, False, True)], False)
+
+
 def run_worker_share(Q, K, V, dO, scale, P, w, bufs: Buffers, remote, fused=True):
     """One pass of worker w's whole share: forward (incl. merges of the helpers' partials),
     the D pre-pass and the backward of the same pairs.  The gradient chunks the share touches are
-    overwritten with the share's own sums (first contribution overwrites, the rest accumulate)."""
+    overwritten with the share's own sums (first contribution overwrites, the rest accumulate).
+    fused: all chunks and partials being there, the worker's pairs are one walk each way (a short chunk's step by step: 8 heads x 512,
+    P = 8, 183 us, as one walk 84); otherwise step by step."""
+    sched = B.dfa_schedule(P, w)
+    if fused and _fits_a_call(len(sched) * bufs.c, K, bufs.dK):
+        _forward_at_hand(Q, K, V, scale, sched, w, bufs, remote)
+        _backward_at_hand(Q, K, V, dO, scale, sched, w, bufs)
+        return
     forward_worker(Q, K, V, scale, P, w, bufs, remote=remote, fused=fused)
     backward_worker(Q, K, V, dO, scale, P, w, bufs, touched=new_pass())
 
@@ -185,6 +232,11 @@ def delta_all_chunks(O, dO, delta, c, P):
         B.dfa_delta(O[:, rows], dO[:, rows], delta=delta[:, rows])
 
 
+def _fits_a_call(rows, *tensors):
+    """Whether the first `rows` positions of [heads, seq, d] tensors are no longer a slice than a call takes."""
+    return all(rows * t.stride(1) <= B.MAX_SLICE for t in tensors)
+
+
 def backward_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced"):
     """The backward of all P workers' pairs on one device, from the merged O and L and the D of every chunk, time
     step by time step: first the pairs of the owners, then those of the helpers.  Each of the two groups has
@@ -218,17 +270,35 @@ def _forward_step(fwd, state, steps, bufs: Buffers):
         own, helped = [], helped[len(now):]
 
 
+def _forward_at_once(fwd, state, scheds, bufs: Buffers):
+    """The forward of all workers: every owner's walk over its own and earlier chunks and, as far as there are partial
+    buffers (as many as helpers in a time step), the helpers' pairs as one launch, the partials merged; then the helpers'
+    pairs that are left."""
+    walks = [pair for w, sched in enumerate(scheds) for pair in _walk(sched, w, state)]
+    helped = [st for steps in zip(*scheds) for st in steps if st.kind == B.DFA_STEP_HELP]
+    most = max(sum(st.kind == B.DFA_STEP_HELP for st in steps) for steps in zip(*scheds))
+    parts = _partials(bufs, most) if helped else []
+    while walks or helped:
+        now = sorted(zip(helped, parts), key=lambda x: x[0].send_to)      # (the partials of a chunk next to each other)
+        fwd.launch(walks + [(st.q_chunk, st.kv_chunk, fwd.dest(*part), 0, False) for st, part in now], None)
+        B.dfa_merge_batch(bufs.O, bufs.L, bufs.c, [(st.send_to, *part) for st, part in now])
+        walks, helped = [], helped[len(now):]
+
+
 def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backward=True, fused=True):
-    """The whole schedule of all P workers, time step by time step, on one GPU.
-    fused: OWN pairs continue from the owner's state (dfa_chunk_fwd_acc) instead of partial + merge, and the
-    pairs of a time step - independent of each other, on P devices they run at the same time - go out as one
-    launch: a pair of small chunks alone leaves most of one device idle."""
+    """The whole schedule of all P workers on one GPU.
+    fused: OWN pairs continue from the owner's state instead of partial + merge, and pairs that do not wait for each other go
+    out as one launch (a pair of small chunks alone leaves most of one device idle): all of the owners' as one walk
+    per owner; otherwise time step by time step, pair by pair."""
     c = bufs.c
     scheds = [B.dfa_schedule(P, w, mode) for w in range(P)]
     nsteps = len(scheds[0])
     fwd = B.ForwardChunks(Q, K, V, c, scale)
     state = fwd.dest(bufs.O, bufs.L)
-    for t in range(nsteps):
+    at_once = fused and _fits_a_call(nsteps * c, K)
+    if at_once:
+        _forward_at_once(fwd, state, scheds, bufs)
+    for t in range(0 if at_once else nsteps):
         steps = [scheds[w][t] for w in range(P)]
         for w, st in enumerate(steps):
             assert st.kind != B.DFA_STEP_HELP or steps[st.send_to].recv_from == w

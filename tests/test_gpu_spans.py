@@ -1,0 +1,191 @@
+"""GPU parity of walks over several key/value chunks (dfa_span_fwd, dfa_span_bwd) and of merges of several partials in one pass, in
+every kernel form they reach; against the fp64 oracle (bounds as in the parity tests)."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2310_03294_amd as dfa
+from paper_2310_03294_amd import binding as B, driver
+from gpu_util import TOL, case, dev, maxerr, np64
+from oracle import attention as A
+
+pytestmark = pytest.mark.gpu
+
+BF16, F32 = torch.bfloat16, torch.float32
+
+
+def _visible(lo, hi, qc, c):
+    """Global index of the last key that each query row of chunk qc sees of the chunks lo .. hi."""
+    return qc * c + np.arange(c) if qc == hi else np.full(c, (hi + 1) * c - 1)
+
+
+# dtype, d, heads, chunk, walks (query chunk, first and last key/value chunk); which of them continue from a state
+FWD = [
+    (BF16, 128, 4, 2, 200, [(5, 0, 5), (4, 4, 4), (3, 0, 2), (2, 1, 2)], (1, 3)),      # 64 rows, the longer ones cut in parts
+    (BF16, 128, 3, 1, 70, [(1, 0, 1), (0, 0, 0), (2, 0, 0)], ()),                      # 64 rows, heads that do not divide into XCDs
+    (BF16, 128, 8, 8, 512, [(4, 0, 4)], ()),                                           # cut at chunk ends
+    (BF16, 128, 8, 2, 128, [(i, max(0, i - 2), i) for i in range(18)], (0, 7)),        # more walks than a launch takes
+    (BF16, 128, 64, 16, 300, [(2, 0, 2)], (0,)),                                       # 128 rows, sums of the rounded weights
+    (BF16, 128, 40, 8, 300, [(2, 0, 2), (0, 0, 0), (1, 0, 0)], (2,)),                  # 128 rows, fp32 sums
+    (BF16, 128, 64, 64, 1024, [(3, 0, 3)], (0,)),                                      # 256 rows, whole tiles
+    (BF16, 128, 64, 16, 1000, [(3, 0, 3)], ()),                                        # 256 rows, ragged
+    (BF16, 128, 64, 64, 1024, [(3, 0, 3), (0, 0, 0)], (1,)),                           # 256 rows, fp32 sums
+    (F32, 128, 2, 1, 100, [(4, 0, 4), (1, 1, 1), (3, 0, 2)], (0,)),                    # 4 parts, cut
+    (F32, 64, 3, 3, 70, [(2, 0, 2), (0, 0, 0)], (1,)),
+    (F32, 128, 40, 20, 200, [(2, 0, 2), (1, 0, 0), (0, 0, 0)], (1,)),                  # 2 parts
+    (F32, 64, 48, 16, 300, [(2, 0, 2)], ()),
+]
+
+
+@pytest.mark.parametrize("o_dtype", [F32, BF16])
+@pytest.mark.parametrize("dtype,d,h_q,h_kv,c,walks,acc", FWD)
+def test_forward_walks(dtype, d, h_q, h_kv, c, walks, acc, o_dtype):
+    """Every second walk's result goes to a buffer of its own; two heads against the oracle."""
+    n, scale, tol = max(w[0] for w in walks) + 1, d ** -0.5, 2e-2 if o_dtype == BF16 else TOL[dtype]
+    q, k, v, _ = case(700 + c + h_q, h_q, h_kv, n * c, n * c, d, dtype)
+    o0, lse0 = (torch.randn(h_q, n * c, d) * 0.1).to(o_dtype), torch.randn(h_q, n * c) + 5
+    O, L = o0.to(dev()), lse0.to(dev())
+    fwd = B.ForwardChunks(*(t.to(dev()) for t in (q, k, v)), c, scale)
+    state, own, pairs = fwd.dest(O, L), {}, []
+    for i, (qc, lo, hi) in enumerate(walks):
+        dest, chunk = state, qc
+        if i % 2 and i not in acc:
+            own[i] = (torch.empty(h_q, c, d, dtype=o_dtype, device=dev()), torch.empty(h_q, c, device=dev()))
+            dest, chunk = fwd.dest(*own[i]), 0
+        pairs += [(qc, kc, dest, chunk, kc != hi or i in acc) for kc in range(hi, lo - 1, -1)]
+    fwd.launch(pairs, None)
+    for i, (qc, lo, hi) in enumerate(walks):
+        rows, keys = slice(qc * c, (qc + 1) * c), slice(lo * c, (hi + 1) * c)
+        got_o, got_l = own[i] if i in own else (O[:, rows], L[:, rows])
+        for h in (0, h_q - 1):
+            kh = h * h_kv // h_q
+            want = A.rows_fwd(np64(q[h, rows]), _visible(lo, hi, qc, c), np64(k[kh, keys]), np64(v[kh, keys]), scale, lo * c)
+            if i in acc:
+                want = A.merge(np64(o0[h, rows])[None], np64(lse0[h, rows])[None], want[0][None], want[1][None])
+                want = want[0][0], want[1][0]
+            assert maxerr(got_o[h], want[0]) <= tol and maxerr(got_l[h], want[1]) <= TOL[dtype], (i, h)
+    used = {w[0] for i, w in enumerate(walks) if i not in own}
+    for j in set(range(n)) - used:      # untouched
+        assert torch.equal(O[:, j * c:(j + 1) * c].cpu(), o0[:, j * c:(j + 1) * c])
+
+
+@pytest.mark.parametrize("ws", [0, 1, 2])
+def test_forward_walk_with_any_scratch(ws):
+    """None, half and all of the scratch asked for: nothing is written behind it."""
+    h, c, d, n = 4, 200, 128, 6
+    q, k, v, _ = case(801, h, h, n * c, n * c, d, BF16)
+    Q, K, V = (t.to(dev()) for t in (q, k, v))
+    O, L = torch.empty(h, c, d, device=dev()), torch.empty(h, c, device=dev())
+    lib, sh = dfa.load_library(), B._make_shape(Q[:, :c], K, False, d ** -0.5, B.DFA_BF16)
+    span = B.DfaFwdSpan(Q[:, (n - 1) * c:].data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), L.data_ptr(), c * d, d, c,
+                        n * c, 1, 0, 0)
+    sh.q_stride_h = n * c * d
+    full = lib.dfa_span_fwd_workspace(ctypes.byref(sh), ctypes.byref(span), 1)
+    assert full > 0
+    size = (0, full // 2 & ~15, full)[ws]
+    buf = torch.full((size // 4 + 1024,), 7.0, device=dev())
+    assert lib.dfa_span_fwd(ctypes.byref(sh), ctypes.byref(span), 1, buf.data_ptr() if size else None, size,
+                            torch.cuda.current_stream().cuda_stream) == 0
+    assert bool((buf[size // 4:] == 7.0).all())
+    for h_ in (0, h - 1):
+        want = A.rows_fwd(np64(q[h_, (n - 1) * c:]), (n - 1) * c + np.arange(c), np64(k[h_]), np64(v[h_]), d ** -0.5)
+        assert maxerr(O[h_], want[0]) <= TOL[BF16] and maxerr(L[h_], want[1]) <= TOL[BF16]
+
+
+@pytest.mark.parametrize("d,dtype", [(64, F32), (128, F32), (128, BF16)])
+@pytest.mark.parametrize("parts", [(2,), (1, 3), (8, 1, 9), (17,), (2,) * 18])
+def test_merges_of_several_partials(d, dtype, parts):
+    """parts[i] partials into chunk i, in one pass each (more than a launch takes: in several); empty ones among them."""
+    h, c = 3, 37
+    g = torch.Generator().manual_seed(sum(parts) + d)
+    o, lse = torch.randn(h, len(parts) * c, d, generator=g).to(dtype), 3 * torch.randn(h, len(parts) * c, generator=g)
+    lse[:, 5] = -np.inf
+    O, L, todo, want = o.to(dev()), lse.to(dev()), [], []
+    for i, m in enumerate(parts):
+        wo, wl = np64(o[:, i * c:(i + 1) * c]), np64(lse[:, i * c:(i + 1) * c])
+        for j in range(m):
+            po, pl = torch.randn(h, c, d, generator=g).to(dtype), 3 * torch.randn(h, c, generator=g)
+            if j == 1:
+                po[:, :9], pl[:, :9] = 0, -np.inf
+            todo.append((i, po.to(dev()), pl.to(dev())))
+            wo, wl = A.merge(wo, wl, np64(po), np64(pl))
+        want.append((wo, wl))
+    B.dfa_merge_batch(O, L, c, todo)
+    for i, (wo, wl) in enumerate(want):
+        assert maxerr(O[:, i * c:(i + 1) * c], wo) <= (1e-5 if dtype == F32 else 2e-2)
+        assert maxerr(L[:, i * c:(i + 1) * c], wl) <= 1e-5
+
+
+# dtype, d, heads, chunk, query chunk, first and last key/value chunk, heads that are checked
+BWD = [
+    (BF16, 128, 8, 8, 130, 6, 0, 6, (0, 7)),        # dq by several workgroups per row block, ragged
+    (BF16, 128, 8, 2, 200, 4, 1, 4, (0, 7)),        # key tiles shared, too
+    (BF16, 128, 4, 4, 128, 5, 0, 3, (0, 3)),        # none of the chunk's own keys
+    (BF16, 128, 2, 1, 64, 8, 0, 8, (0, 1)),
+    (BF16, 128, 16, 16, 320, 2, 1, 2, (0, 15)),
+    (BF16, 128, 32, 32, 256, 40, 0, 40, (0, 31)),   # more than 2560 key tiles: two launches
+    (F32, 64, 4, 2, 100, 4, 0, 4, (0, 3)),
+    (F32, 128, 4, 2, 100, 4, 0, 4, (0, 3)),
+    (F32, 128, 2, 2, 33, 20, 0, 20, (0, 1)),        # dq's walk shared
+    (F32, 64, 8, 1, 150, 3, 1, 2, (0, 7)),
+]
+
+
+@pytest.mark.parametrize("acc", [(False, False), (True, False), (True, True)])
+@pytest.mark.parametrize("dtype,d,h_q,h_kv,c,qc,lo,hi,heads", BWD)
+def test_backward_span(dtype, d, h_q, h_kv, c, qc, lo, hi, heads, acc):
+    """Gradients of one query chunk against the chunks lo .. hi, with the logsumexp and D that these give; neighbours untouched."""
+    n, scale, g = qc + 1, d ** -0.5, h_q // h_kv
+    q, k, v, do = case(900 + c + h_q, h_q, h_kv, n * c, n * c, d, dtype)
+    rows, keys = slice(qc * c, (qc + 1) * c), slice(lo * c, (hi + 1) * c)
+    vis = _visible(lo, hi, qc, c)
+    lse, delta = torch.full((h_q, n * c), 8.0), torch.zeros(h_q, n * c)
+    checked = sorted({h for x in heads for h in range(x // g * g, x // g * g + g)})      # whole groups
+    for h in checked:
+        o, l = A.rows_fwd(np64(q[h, rows]), vis, np64(k[h // g, keys]), np64(v[h // g, keys]), scale, lo * c)
+        lse[h, rows] = torch.from_numpy(l).float()
+        delta[h, rows] = torch.from_numpy(A.delta_rows(o, np64(do[h, rows]))).float()
+    out = [torch.full((x, n * c, d), 0.5, device=dev()) for x in (h_q, h_kv, h_kv)]
+    x = [t.to(dev()) for t in (q, k, v, lse, delta, do)]
+    bwd = B.BackwardChunks(*x[:3], *x[3:], *out, c, scale)
+    bwd.launch_span(qc, lo, hi, *acc)
+    per = 4 if dtype == BF16 else 1
+
+    def check(got, want, add):
+        assert maxerr(got, want + (0.5 if add else 0.0)) <= TOL[dtype] * max(1.0, abs(want).max() / per)
+
+    for h in heads:
+        args = np64(k[h // g, keys]), np64(v[h // g, keys])
+        check(out[0][h, rows], A.rows_dq(np64(q[h, rows]), vis, np64(do[h, rows]), np64(lse[h, rows]), np64(delta[h, rows]), *args,
+                                         scale, lo * c), acc[0])
+        grads = [A.cols_dkdv(*args, np.arange(lo * c, (hi + 1) * c), np64(q[i, rows]), np64(do[i, rows]), np64(lse[i, rows]),
+                             np64(delta[i, rows]), scale, qc * c if qc == hi else n * c) for i in range(h // g * g, h // g * g + g)]
+        check(out[1][h // g, keys], sum(a for a, _ in grads), acc[1])
+        check(out[2][h // g, keys], sum(b for _, b in grads), acc[1])
+    for t, own in zip(out, (rows, keys, keys)):
+        rest = torch.ones(n * c, dtype=torch.bool)
+        rest[own] = False
+        assert bool((t[:, rest] == 0.5).all())
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("P,c", [(1, 64), (5, 70), (8, 96)])
+def test_share_at_hand_equals_step_by_step(dtype, P, c):
+    """A worker's share in one walk each way, for every worker (helpers among them), against the same share step by step."""
+    h_q, h_kv, n, d = 4, 2, P * c, 128
+    q, k, v, do = (t.to(dev()) for t in case(950 + n, h_q, h_kv, n, n, d, dtype))
+    scale = d ** -0.5
+    whole = driver.Buffers(h_q, h_kv, n, d, P, dev())
+    driver.run_all_workers(q, k, v, do, scale, P, whole)
+    for w in range(P):
+        got = []
+        for fused in (True, False):
+            bufs = driver.Buffers(h_q, h_kv, n, d, P, dev())
+            bufs.O.copy_(whole.O); bufs.L.copy_(whole.L); bufs.delta.copy_(whole.delta)      # of the chunks it helps
+            remote = driver.helper_partials_for(q, k, v, scale, P, w, bufs)
+            driver.run_worker_share(q, k, v, do, scale, P, w, bufs, remote, fused=fused)
+            got.append((bufs.O, bufs.L, bufs.dQ, bufs.dK, bufs.dV))
+        for a, b in zip(*got):
+            assert (a - b).abs().max().item() <= TOL[dtype] * max(1.0, b.abs().max().item() / 4)

@@ -1,0 +1,116 @@
+"""Host side of walks over several key/value chunks, without a GPU: which pairs the driver computes, and what is refused."""
+import ctypes
+
+import pytest
+import torch
+
+import paper_2310_03294_amd as dfa
+from paper_2310_03294_amd import binding as B, driver
+
+
+def _tensors(h, n, d=64):
+    return [torch.zeros(h, n, d) for _ in range(4)]
+
+
+@pytest.mark.parametrize("P", [1, 2, 3, 4, 7, 8, 16])
+def test_share_computes_the_schedules_pairs(monkeypatch, P):
+    """Forward and backward of a share: every pair of the worker's schedule once, every partial merged, D before the backward."""
+    h, c, d = 2, 4, 64
+    q, k, v, do = _tensors(h, P * c)
+    log = []
+
+    def span(self, qc, lo, hi, acc_q, acc_kv, stream=None):
+        assert not acc_q and not acc_kv
+        log.extend(("bwd", qc, kc) for kc in range(lo, hi + 1))
+
+    def pairs(self, items, causal, stream=None):
+        assert not causal and all(acc_kv and not acc_q for _, _, acc_q, acc_kv in items)
+        log.extend(("bwd", qc, kc) for qc, kc, _, _ in items)
+
+    monkeypatch.setattr(B.ForwardChunks, "launch", lambda self, items, causal, stream=None: log.extend(
+        ("fwd", qc, kc, dest[4][0] is bufs.O, acc) for qc, kc, dest, _, acc in items))
+    monkeypatch.setattr(B.BackwardChunks, "launch_span", span)
+    monkeypatch.setattr(B.BackwardChunks, "launch", pairs)
+    monkeypatch.setattr(B, "dfa_merge_batch", lambda o, lse, rows, parts: log.extend(("merge", i) for i, _, _ in parts))
+    monkeypatch.setattr(B, "dfa_delta", lambda *a, **kw: log.append("delta"))
+    for w in range(P):
+        bufs = driver.Buffers(h, h, P * c, d, P, "cpu")
+        sched = dfa.dfa_schedule(P, w)
+        remote = {st.recv_from: (bufs.part_o[0], bufs.part_l[0]) for st in sched if st.recv_from >= 0}
+        log.clear()
+        driver.run_worker_share(q, k, v, do, 1.0, P, w, bufs, remote)
+        mine = sorted((st.q_chunk, st.kv_chunk) for st in sched if st.kind != B.DFA_STEP_IDLE)
+        fwd = [x for x in log if x[0] == "fwd"]
+        assert sorted(x[1:3] for x in fwd) == mine and sorted(x[1:] for x in log if x[0] == "bwd") == mine
+        assert all(x[3] == (x[1] == w) and x[4] == (x[1] == w != x[2]) for x in fwd)
+        assert log.count(("merge", w)) == len(remote) and log.count("delta") == 1
+        assert log.index("delta") == len(fwd) + len(remote)
+
+
+def test_long_sequences_stay_step_by_step(monkeypatch):
+    """A walk longer than a call's slice is not one call."""
+    h, d, P, c = 2, 128, 4, 40000
+    t = torch.empty_strided((h, P * c, d), (d, 4096, 1), dtype=torch.bfloat16, device="meta")
+    assert P * c * 4096 > B.MAX_SLICE >= c * 4096
+    calls = []
+    monkeypatch.setattr(B.ForwardChunks, "launch", lambda self, items, causal, stream=None: calls.append(("fwd", causal, len(items))))
+    monkeypatch.setattr(B.BackwardChunks, "launch", lambda self, items, causal, stream=None: calls.append(("bwd", causal, len(items))))
+    monkeypatch.setattr(B, "dfa_merge_batch", lambda *a, **kw: None)
+    monkeypatch.setattr(B, "dfa_delta", lambda *a, **kw: None)
+    bufs = driver.Buffers(h, h, P * c, d, P, "meta")
+    driver.run_all_workers(t, t, t, t, 1.0, P, bufs)
+    assert [x[1] for x in calls if x[0] == "bwd"][0] is True and len([x for x in calls if x[0] == "bwd"]) > 1
+
+
+@pytest.mark.parametrize("pairs", [
+    [(2, 2, False), (2, 0, True)],                 # a chunk is left out
+    [(1, 1, False), (1, 2, True)],                 # keys behind the query chunk's own
+])
+def test_walks_of_other_chunks_are_refused(pairs):
+    q, k, v, _ = _tensors(2, 16)
+    fwd = B.ForwardChunks(q, k, v, 4, 1.0)
+    dest = fwd.dest(torch.zeros(2, 16, 64), torch.zeros(2, 16))
+    with pytest.raises(ValueError):
+        fwd.launch([(qc, kc, dest, qc, acc) for qc, kc, acc in pairs], None)
+
+
+def test_span_arguments():
+    """Refused before any launch: status codes of dfa_span_fwd and dfa_span_bwd."""
+    lib = dfa.load_library()
+
+    def shape(**kw):
+        sh = B.DfaShape(h_q=2, h_kv=2, s_q=64, s_k=64, d=64, dtype=B.DFA_F32, o_dtype=B.DFA_F32, scale=1.0, q_stride_h=4096,
+                        q_stride_s=64, kv_stride_h=1 << 20, kv_stride_s=64, o_stride_h=4096, o_stride_s=64, lse_stride_h=64,
+                        dq_stride_h=4096, dq_stride_s=64, dkv_stride_h=1 << 20, dkv_stride_s=64)
+        for a, b in kw.items():
+            setattr(sh, a, b)
+        return sh
+
+    def fwd(sh=None, n=1, ws=None, ws_bytes=0, **kw):
+        x = B.DfaFwdSpan(4096, 4096, 4096, 4096, 4096, 4096, 64, 64, 128, 1, 0, 0)
+        for a, b in kw.items():
+            setattr(x, a, b)
+        return lib.dfa_span_fwd(ctypes.byref(sh or shape()), ctypes.byref(x), n, ws, ws_bytes, None)
+
+    assert fwd(n=0) == 0 and fwd(n=-1) == -4 and fwd(sh=shape(s_q=0)) == 0
+    for f in ("q", "k", "v", "o", "lse"):
+        assert fwd(**{f: None}) == -1
+    assert fwd(q=4100) == -2 and fwd(n_keys=0) == -2 and fwd(n_keys=1 << 24) == -2 and fwd(sh=shape(q_stride_s=63)) == -2
+    assert fwd(n_keys=63) == -4 and fwd(reserved=1) == -4 and fwd(ws_bytes=-1) == -4 and fwd(ws=8, ws_bytes=64) == -2
+    assert fwd(sh=shape(dtype=7)) == -3 and fwd(sh=shape(d=96)) == -2 and fwd(o_stride_s=60) == -2
+    x = B.DfaFwdSpan(4096, 4096, 4096, 4096, 4096, 4096, 64, 64, 1280, 1, 0, 0)
+    assert lib.dfa_span_fwd_workspace(ctypes.byref(shape()), ctypes.byref(x), 1) > 0
+    assert lib.dfa_span_fwd_workspace(ctypes.byref(shape(scale=-1.0)), ctypes.byref(x), 1) == -4
+
+    def bwd(sh, **kw):
+        y = B.DfaBwdPair(*[4096] * 9, 0, 0)
+        for a, b in kw.items():
+            setattr(y, a, b)
+        return lib.dfa_span_bwd(ctypes.byref(sh), ctypes.byref(y), None, 0, None)
+
+    assert bwd(shape(s_k=63, causal=1)) == -4 and bwd(shape(s_k=128, causal=1), dk=None) == -1
+    assert bwd(shape(s_k=128, causal=1), q=None) == -1 and bwd(shape(s_k=128, causal=2)) == -4
+    assert lib.dfa_span_bwd_workspace(ctypes.byref(shape(s_k=4096, causal=1)), 1, 1) > 0
+    # what a pair's backward refused it still refuses
+    y = B.DfaBwdPair(*[4096] * 9, 0, 0)
+    assert lib.dfa_chunk_bwd_batch(ctypes.byref(shape(s_k=128, causal=1)), ctypes.byref(y), 1, None, 0, None) == -4
