@@ -196,6 +196,26 @@ __device__ __forceinline__ void col_product(f32x16 (&acc)[D / 32], const float* 
   }
 }
 
+// The same with the 32 rows' products as a sum of their own, added to acc; two column blocks at a time, which keeps it to 32 registers.
+template <int D>
+__device__ __forceinline__ void col_sum(f32x16 (&acc)[D / 32], const float* Xs, const f32x16& w, int r32, int hh) {
+  constexpr int NB = D / 32;
+#pragma unroll
+  for (int j = 0; j < NB; j += 2) {
+    f32x16 t[2];
+    zero(t);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const f32x2 a = *reinterpret_cast<const f32x2*>(Xs + ((i >> 2) * 8 + 4 * hh + (i & 3)) * (D + 4) + NB * r32 + j);
+      t[0] = mfma_f32(a.x, w[i], t[0]);
+      t[1] = mfma_f32(a.y, w[i], t[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { acc[j][i] += t[0][i]; acc[j + 1][i] += t[1][i]; }
+    __builtin_amdgcn_sched_barrier(0);      // (else the reads of what follows are hoisted above it and registers spill: 5 % at d = 128)
+  }
+}
+
 // Sum of a result over the NS parts of a row block, left in part 0: `x` is LDS space for
 // 4 * NV * 64 floats (NV registers of the result per lane).
 template <int NB>
@@ -427,6 +447,9 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
   } else {
     load_rows<D>(v, pr.v + kh * p.kv_sh, p.kv_ss, kvrow, kvalid, hh);
   }
+  // Sums of 32 query rows each, added up: the rounding errors of one chain over all rows grow with its length.  Relative error of dk,
+  // dv in a schedule of 4 heads x 8000, d = 128: one chain 1.6e-6, this 5.8e-7 and 5.1e-7 (pair by pair, 1000 rows each, 7.0e-7 and
+  // 6.6e-7); it takes 2 to 3 % of the time.
   f32x16 dk[NB], dv[NB];
   zero(dk);
   zero(dv);
@@ -456,8 +479,13 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
       s[i] = vis ? expf(s[i] * p.scale - L) : 0.f;
       dp[i] = s[i] * (dp[i] - Ds[part * 32 + r]);
     }
-    col_product<D>(dv, Gw, s, r32, hh);
-    col_product<D>(dk, Qw, dp, r32, hh);
+    if constexpr (V_LDS) {      // (no registers left for the sums)
+      col_product<D>(dv, Gw, s, r32, hh);
+      col_product<D>(dk, Qw, dp, r32, hh);
+    } else {
+      col_sum<D>(dv, Gw, s, r32, hh);
+      col_sum<D>(dk, Qw, dp, r32, hh);
+    }
   }
   if constexpr (NS > 1) {
     constexpr int NV = NB * 16;
@@ -784,16 +812,26 @@ int bwd(F32BwdParams p, hipStream_t st) {
 // dq by several workgroups per row block: a few query rows against many keys, where a row block's walk over all of them would be
 // the whole call (us with one walk / shared, d = 128; dq by atomics took the third): 1 head x 32 x 16384 1278 / 76 / 47,
 // x 256 x 32768 2615 / 195 / 430, 8 x 64 x 16384 1573 / 260 / 525, 2 over 1 x 47 x 2011 161 / 34 / 103.  From eight keys per row
-// on: below, the row blocks are enough (4 heads x 500 x 1000 88, and 393 with atomics).
+// on: below, the row blocks are enough (4 heads x 500 x 1000 88, and 393 with atomics), but for diagonal chunks, whose last row
+// blocks have the whole chunk to walk over (one head x 1024, d = 64: 45 + 4 us with
+// one walk, 22 + 8 with four workgroups per row block).
 struct Plan { int parts, shares, q_shares; double us; int64_t bytes; };
+
+// A causal call's (head, share) groups go to the XCDs in ranges, longest row blocks first: with a part of a group left over, an
+// XCD that gets its first blocks has so much more than an even share.
+double uneven(int64_t groups) {
+  const double g = groups / 8., whole = static_cast<double>(groups / 8), rest = g - whole;
+  return groups <= 2 ? 1.0 : (whole + rest * (2 - rest)) / g;
+}
 
 Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
   const int group = sh.h_q / sh.h_kv;
   const double width = sh.d == 128 ? 1.0 : 0.55, mean = sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0;
   ws_bytes = std::min(ws_bytes, int64_t{128} << 20);
-  const int max_q = dq && sh.s_k / 8 >= sh.s_q ? 64 : 1;
+  const int max_q = !dq ? 1 : sh.s_k / 8 >= sh.s_q ? 64 : dk && pairs == 1 && sh.causal ? 8 : 1;
   Plan best{0, 0, 0, 0., 0};
   for (int parts : {1, 2, 4}) {
+    if (parts == 4 && max_q == 8 && sh.d == 128) break;      // (its dk, dv are one chain)
     const int rows = 128 / parts, tile = 32 * parts;
     const int64_t kv1 = dk ? blocks_of(sh.s_k, rows) * sh.h_kv * pairs : 0, q1 = dq ? blocks_of(sh.s_q, rows) * sh.h_q * pairs : 0;
     const double walk_kv = width * (parts == 1 ? 9.3 : parts == 2 ? 10.3 : 12.2) * group * blocks_of(sh.s_q, tile);
@@ -807,8 +845,11 @@ Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
         if (shares > 1 && (!dk || shares > 4 * group || n_kv > 1024 || sums > ws_bytes)) break;
         Plan x{parts, shares, q_shares, std::max(dk ? 6 + walk_kv / shares : 0., dq ? 6 + walk_q / q_shares : 0.), sums};
         if (n_kv + n_q > 256) {
-          const double even = (n_kv * (6 + walk_kv * mean / shares) + n_q * (6 + walk_q * mean / q_shares)) / 256;
-          x.us = std::max(x.us, even + 0.45 * x.us);
+          double even_kv = n_kv * (6 + walk_kv * mean / shares) / 256, even_q = n_q * (6 + walk_q * mean / q_shares) / 256;
+          if (max_q == 8) { even_kv *= uneven(sh.h_kv * shares); even_q *= uneven(sh.h_q * q_shares); }
+          // (dq's workgroups come after those of dk, dv: the first of them, the longest of a causal call, ends as late as that)
+          if (max_q == 8) x.us = std::max(x.us, even_kv + std::max(6 + walk_q / q_shares, even_q + 0.3 * (6 + walk_q / q_shares)));
+          else x.us = std::max(x.us, even_kv + even_q + 0.45 * x.us);
         }
         if (sums > 0) x.us = (x.us + 4 * ((shares > 1) + (q_shares > 1)) + 2 * sums / 2.5e6) / 0.92;
         if (!best.parts || x.us < best.us) best = x;

@@ -189,3 +189,25 @@ def test_share_at_hand_equals_step_by_step(dtype, P, c):
             got.append((bufs.O, bufs.L, bufs.dQ, bufs.dK, bufs.dV))
         for a, b in zip(*got):
             assert (a - b).abs().max().item() <= TOL[dtype] * max(1.0, b.abs().max().item() / 4)
+
+
+@pytest.mark.parametrize("h_q,h_kv,n,d", [(1, 1, 1000, 64), (4, 4, 800, 128), (2, 1, 1090, 64), (3, 1, 130, 128)])
+def test_f32_diagonal_by_several_workgroups_per_row_block(h_q, h_kv, n, d):
+    """dq's walks over a diagonal chunk shared by several workgroups; with all the scratch, half of it and none."""
+    q, k, v, do = case(970 + n, h_q, h_kv, n, n, d, F32)
+    x64, scale = [np64(t) for t in (q, k, v, do)], d ** -0.5
+    O, L = A.attention_fwd(*x64[:3], scale)
+    want = A.attention_bwd(*x64, scale)
+    x = [t.to(dev()) for t in (q, k, v, torch.from_numpy(L).float(), torch.from_numpy(A.delta_rows(O, x64[3])).float(), do)]
+    lib, sh = dfa.load_library(), B._bwd_shape(*x, torch.empty_like(x[0]), torch.empty_like(x[1]), torch.empty_like(x[1]), True, scale)
+    full = lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), 1, 1, 1)
+    assert full > 0
+    for size in (full, full // 2 & ~15, 0):
+        got = [torch.full(w.shape, 0.5, device=dev()) for w in want]
+        ws = torch.full((size // 4 + 1024,), 7.0, device=dev())
+        pair = B.DfaBwdPair(*(t.data_ptr() for t in x), *(t.data_ptr() for t in got), 1, 0)
+        assert lib.dfa_chunk_bwd_batch(ctypes.byref(sh), ctypes.byref(pair), 1, ws.data_ptr() if size else None, size,
+                                       torch.cuda.current_stream().cuda_stream) == 0
+        assert bool((ws[size // 4:] == 7.0).all())
+        for g, w, add in zip(got, want, (0.5, 0.0, 0.0)):
+            assert maxerr(g, w + add) <= TOL[F32] * max(1.0, abs(w).max())
