@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import collections
 import ctypes
+import functools
 import os
 
 import torch
@@ -160,33 +161,19 @@ def _stream(stream) -> int:
 
 
 def _hsd(t: torch.Tensor, name: str):
-    if t.dim() != 3 or t.stride(2) != 1:
+    strides = t.stride()
+    if len(strides) != 3 or strides[2] != 1:
         raise ValueError(f"{name} must be [heads, seq, d] with unit innermost stride")
-    return t.stride(0), t.stride(1)
+    return strides[:2]
 
 
 def _make_shape(q, k, causal, scale, in_dtype, o=None, o_dtype=DFA_F32, lse=None, dq=None, dkv=None) -> DfaShape:
-    sh = DfaShape()
-    sh.h_q, sh.s_q, sh.d = q.shape
-    sh.h_kv, sh.s_k = k.shape[0], k.shape[1]
-    sh.dtype, sh.o_dtype = in_dtype, o_dtype
-    sh.causal, sh.scale, sh.reserved = int(bool(causal)), float(scale), 0
-    sh.q_stride_h, sh.q_stride_s = _hsd(q, "q")
-    sh.kv_stride_h, sh.kv_stride_s = _hsd(k, "k")
-    if o is not None:
-        sh.o_stride_h, sh.o_stride_s = _hsd(o, "o")
-    else:
-        sh.o_stride_h, sh.o_stride_s = sh.s_q * sh.d, sh.d
-    sh.lse_stride_h = lse.stride(0) if lse is not None else sh.s_q
-    if dq is not None:
-        sh.dq_stride_h, sh.dq_stride_s = _hsd(dq, "dq")
-    else:
-        sh.dq_stride_h, sh.dq_stride_s = sh.s_q * sh.d, sh.d
-    if dkv is not None:
-        sh.dkv_stride_h, sh.dkv_stride_s = _hsd(dkv, "dk")
-    else:
-        sh.dkv_stride_h, sh.dkv_stride_s = sh.s_k * sh.d, sh.d
-    return sh
+    h_q, s_q, d = q.shape
+    h_kv, s_k = k.shape[:2]
+    return DfaShape(h_q, h_kv, s_q, s_k, d, in_dtype, o_dtype, bool(causal), float(scale), 0, *_hsd(q, "q"), *_hsd(k, "k"),
+                    *(_hsd(o, "o") if o is not None else (s_q * d, d)), lse.stride(0) if lse is not None else s_q,
+                    *(_hsd(dq, "dq") if dq is not None else (s_q * d, d)),
+                    *(_hsd(dkv, "dk") if dkv is not None else (s_k * d, d)))
 
 
 def _check(rc: int, where: str):
@@ -229,14 +216,9 @@ def dfa_merge(o_a, lse_a, o_b, lse_b, stream=None):
     lib = load_library()
     if o_a.shape != o_b.shape or lse_a.shape != lse_b.shape or o_a.dtype != o_b.dtype:
         raise ValueError("merge operands must match")
-    md = DfaMergeDesc()
-    md.heads, md.rows, md.d = o_a.shape
-    md.o_dtype = _dt(o_a)
-    md.a_stride_h, md.a_stride_s = _hsd(o_a, "o_a")
-    md.b_stride_h, md.b_stride_s = _hsd(o_b, "o_b")
+    md = DfaMergeDesc(*o_a.shape, _dt(o_a), *_hsd(o_a, "o_a"), lse_a.stride(0), *_hsd(o_b, "o_b"), lse_b.stride(0))
     if lse_a.stride(1) != 1 or lse_b.stride(1) != 1:
         raise ValueError("lse must have unit innermost stride")
-    md.lse_a_stride_h, md.lse_b_stride_h = lse_a.stride(0), lse_b.stride(0)
     _check(lib.dfa_merge(ctypes.byref(md), o_a.data_ptr(), lse_a.data_ptr(), o_b.data_ptr(), lse_b.data_ptr(),
                          _stream(stream)), "dfa_merge")
 
@@ -254,7 +236,8 @@ def dfa_delta(o, dO, delta=None, stream=None):
 
 def _same_strides(a, b) -> bool:
     """Whether the elements of a and b lie the same way (the stride of an axis of one element says nothing)."""
-    return all(n == 1 or x == y for n, x, y in zip(a.shape, a.stride(), b.stride()))
+    x, y = a.stride(), b.stride()
+    return x == y or all(n == 1 or i == j for n, i, j in zip(a.shape, x, y))
 
 
 def _alike(a, b) -> bool:
@@ -322,11 +305,19 @@ class _Chunks:
     """Addresses of the chunks (`rows` sequence positions each) of a [heads, seq, ...] tensor.  Chunks without rows (a
     sequence shorter than its number of chunks) have none, as the empty slices of a tensor."""
 
+    __slots__ = ("base", "step", "n")
+
     def __init__(self, t, rows):
         if rows < 1:
             raise DfaError(DFA_ERR_NULL, f"chunks of {rows} rows")
         self.base, self.step = t.data_ptr(), rows * t.stride(1) * t.element_size()
         self.n = t.shape[1] // rows
+
+    def of(self, t):
+        """Those of a tensor of the same shape and strides."""
+        other = _Chunks.__new__(_Chunks)
+        other.base, other.step, other.n = t.data_ptr(), self.step, self.n
+        return other
 
     def __getitem__(self, i):
         if not 0 <= i < self.n:
@@ -346,7 +337,8 @@ class ForwardChunks:
         self.rows, self.lib = rows, load_library()
         self.sh = _make_shape(q, k, False, scale, _dt(q))
         self.sh.s_q = self.sh.s_k = rows
-        self.q, self.k, self.v = _Chunks(q, rows), _Chunks(k, rows), _Chunks(v, rows)
+        self.q, self.k = _Chunks(q, rows), _Chunks(k, rows)
+        self.v = self.k.of(v)
 
     def dest(self, o, lse):
         """[heads, seq, d] and [heads, seq] tensors that results can go to, in chunks of the same length."""
@@ -366,38 +358,35 @@ class ForwardChunks:
         if causal is None:
             return self._launch_spans(pairs, stream)
         sh.causal, sh.o_dtype = int(bool(causal)), pairs[0][2][3]
-        arr = (DfaFwdPair * len(pairs))()
-        for a, (qc, kc, dest, c, acc) in zip(arr, pairs):
-            if dest[3] != sh.o_dtype:
-                raise ValueError("outputs of a launch share their dtype")
-            a.q, a.k, a.v, a.o, a.lse = self.q[qc], self.k[kc], self.v[kc], dest[0][c], dest[1][c]
-            a.o_stride_h, a.o_stride_s, a.lse_stride_h = dest[2]
-            a.accumulate = bool(acc)
+        if any(dest[3] != sh.o_dtype for _, _, dest, _, _ in pairs):
+            raise ValueError("outputs of a launch share their dtype")
+        arr = (DfaFwdPair * len(pairs))(*[
+            (self.q[qc], self.k[kc], self.v[kc], dest[0][c], dest[1][c], *dest[2], bool(acc)) for qc, kc, dest, c, acc in pairs])
         _check(self.lib.dfa_chunk_fwd_batch(ctypes.byref(sh), arr, len(pairs), _stream(stream)), "dfa_chunk_fwd_batch")
-
 
     def _launch_spans(self, pairs, stream):
         sh = self.sh
         sh.o_dtype = pairs[0][2][3]
-        runs = []                                    # [q_chunk, dest, chunk, accumulate, key/value chunks]
+        runs, kv = [], None                          # (q_chunk, dest, chunk, accumulate, key/value chunks)
         for qc, kc, dest, c, acc in pairs:
             if dest[3] != sh.o_dtype:
                 raise ValueError("outputs of a launch share their dtype")
-            if acc and runs and runs[-1][0] == qc and runs[-1][1] is dest and runs[-1][2] == c:
-                runs[-1][4].append(kc)
+            if acc and kv is not None and (qc, c) == at and runs[-1][1] is dest:
+                kv.append(kc)
             else:
-                runs.append([qc, dest, c, acc, [kc]])
-        arr = (DfaFwdSpan * len(runs))()
-        for a, (qc, dest, c, acc, kv) in zip(arr, runs):
+                kv, at = [kc], (qc, c)
+                runs.append((qc, dest, c, acc, kv))
+        spans = []
+        for qc, dest, c, acc, kv in runs:
             lo, hi = min(kv), max(kv)
-            if sorted(kv) != list(range(lo, hi + 1)) or (qc in kv and qc != hi):
+            if hi - lo + 1 != len(kv) or len(set(kv)) != len(kv) or (qc in kv and qc != hi):
                 raise ValueError("the key/value chunks of a walk are consecutive, the query chunk's own the last")
-            a.q, a.k, a.v, a.o, a.lse = self.q[qc], self.k[lo], self.v[lo], dest[0][c], dest[1][c]
             self.k[hi]                               # (in range)
-            a.o_stride_h, a.o_stride_s, a.lse_stride_h = dest[2]
-            a.n_keys, a.own, a.accumulate = len(kv) * self.rows, qc == hi, bool(acc)
-        ws, n = _workspace(self.lib.dfa_span_fwd_workspace(ctypes.byref(sh), arr, len(runs)), stream)
-        _check(self.lib.dfa_span_fwd(ctypes.byref(sh), arr, len(runs), _ptr(ws), n, _stream(stream)), "dfa_span_fwd")
+            spans.append((self.q[qc], self.k[lo], self.v[lo], dest[0][c], dest[1][c], *dest[2],
+                          len(kv) * self.rows, qc == hi, bool(acc)))
+        arr = (DfaFwdSpan * len(spans))(*spans)
+        ws, n = _workspace(self.lib.dfa_span_fwd_workspace(ctypes.byref(sh), arr, len(spans)), stream)
+        _check(self.lib.dfa_span_fwd(ctypes.byref(sh), arr, len(spans), _ptr(ws), n, _stream(stream)), "dfa_span_fwd")
 
 
 def dfa_merge_batch(o, lse, rows, parts, stream=None):
@@ -406,20 +395,18 @@ def dfa_merge_batch(o, lse, rows, parts, stream=None):
     if not parts:
         return
     lib = load_library()
-    md = DfaMergeDesc()
-    md.heads, md.rows, md.d, md.o_dtype = o.shape[0], rows, o.shape[2], _dt(o)
-    md.a_stride_h, md.a_stride_s = _hsd(o, "o")
-    md.b_stride_h, md.b_stride_s = _hsd(parts[0][1], "o_b")
-    md.lse_a_stride_h, md.lse_b_stride_h = lse.stride(0), parts[0][2].stride(0)
+    shape, lse_shape = (o.shape[0], rows, o.shape[2]), (o.shape[0], rows)
+    like, lse_like = parts[0][1].stride(), parts[0][2].stride()
+    md = DfaMergeDesc(*shape, _dt(o), *_hsd(o, "o"), lse.stride(0), *_hsd(parts[0][1], "o_b"), lse_like[0])
     co, cl = _Chunks(o, rows), _Chunks(lse, rows)
-    arr = (DfaMergePair * len(parts))()
-    for a, (c, ob, lb) in zip(arr, parts):
-        if (ob.shape != (o.shape[0], rows, o.shape[2]) or ob.dtype != o.dtype or ob.stride() != parts[0][1].stride()
-                or lb.shape != (o.shape[0], rows) or lb.stride() != parts[0][2].stride()):
+    pairs = []
+    for c, ob, lb in parts:
+        if ob.shape != shape or ob.dtype != o.dtype or ob.stride() != like or lb.shape != lse_shape or lb.stride() != lse_like:
             raise ValueError("merge operands must match")
-        a.o_a, a.lse_a, a.o_b, a.lse_b = co[c], cl[c], ob.data_ptr(), lb.data_ptr()
-    if lse.stride(1) != 1 or parts[0][2].stride(1) != 1:
+        pairs.append((co[c], cl[c], ob.data_ptr(), lb.data_ptr()))
+    if lse.stride(1) != 1 or lse_like[1] != 1:
         raise ValueError("lse must have unit innermost stride")
+    arr = (DfaMergePair * len(pairs))(*pairs)
     _check(lib.dfa_merge_batch(ctypes.byref(md), arr, len(parts), _stream(stream)), "dfa_merge_batch")
 
 
@@ -432,8 +419,15 @@ class BackwardChunks:
         self.lib = load_library()
         self.sh = _bwd_shape(q, k, v, lse, delta, dO, dq, dk, dv, False, scale)
         self.sh.s_q = self.sh.s_k = rows
-        self.by_q = [_Chunks(t, rows) for t in (q, lse, delta, dO, dq)]
-        self.by_kv = [_Chunks(t, rows) for t in (k, v, dk, dv)]
+        by_q, by_k, by_dk = _Chunks(q, rows), _Chunks(k, rows), _Chunks(dk, rows)
+        self.by_q = [by_q, _Chunks(lse, rows), _Chunks(delta, rows), by_q.of(dO), _Chunks(dq, rows)]
+        self.by_kv = [by_k, by_k.of(v), by_dk, by_dk.of(dv)]
+
+    def _pair(self, qc, kc, acc_q, acc_kv):
+        """The members of a DfaBwdPair."""
+        q, lse, delta, dO, dq = (t[qc] for t in self.by_q)
+        k, v, dk, dv = (t[kc] for t in self.by_kv)
+        return q, k, v, lse, delta, dO, dq, dk, dv, bool(acc_q), bool(acc_kv)
 
     def launch(self, pairs, causal, stream=None):
         """The pairs as one launch: (q_chunk, kv_chunk, accumulate_dq, accumulate_dkv); no query chunk and no
@@ -442,26 +436,18 @@ class BackwardChunks:
             return
         sh = self.sh
         sh.causal = int(bool(causal))
-        arr = (DfaBwdPair * len(pairs))()
-        for a, (qc, kc, acc_q, acc_kv) in zip(arr, pairs):
-            a.q, a.lse, a.delta, a.dO, a.dq = (t[qc] for t in self.by_q)
-            a.k, a.v, a.dk, a.dv = (t[kc] for t in self.by_kv)
-            a.accumulate_dq, a.accumulate_dkv = bool(acc_q), bool(acc_kv)
+        arr = (DfaBwdPair * len(pairs))(*[self._pair(*pair) for pair in pairs])
         ws, n = _workspace(self.lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), len(pairs), 1, 1), stream)
         _check(self.lib.dfa_chunk_bwd_batch(ctypes.byref(sh), arr, len(pairs), _ptr(ws), n, _stream(stream)),
                "dfa_chunk_bwd_batch")
-
 
     def launch_span(self, qc, lo, hi, acc_q, acc_kv, stream=None):
         """Query chunk qc against the key/value chunks lo .. hi, the last of which may be its own (dfa_span_bwd)."""
         sh, rows = self.sh, self.sh.s_q
         sh.s_k, sh.causal = (hi - lo + 1) * rows, int(qc == hi)
         try:
-            a = DfaBwdPair()
-            a.q, a.lse, a.delta, a.dO, a.dq = (t[qc] for t in self.by_q)
-            a.k, a.v, a.dk, a.dv = (t[lo] for t in self.by_kv)
+            a = DfaBwdPair(*self._pair(qc, lo, acc_q, acc_kv))
             self.by_kv[0][hi]                        # (in range)
-            a.accumulate_dq, a.accumulate_dkv = bool(acc_q), bool(acc_kv)
             ws, n = _workspace(self.lib.dfa_span_bwd_workspace(ctypes.byref(sh), 1, 1), stream)
             _check(self.lib.dfa_span_bwd(ctypes.byref(sh), ctypes.byref(a), _ptr(ws), n, _stream(stream)), "dfa_span_bwd")
         finally:
@@ -492,6 +478,11 @@ def dfa_mfma_probe_data(operands, out, iters: int, stream=None) -> float:
 def dfa_schedule(P: int, worker_id: int, mode="balanced"):
     """Step list of one worker (host integers only).  mode: "balanced", "ring", or
     ("window", window_chunks) for the local sliding window (dfa_schedule_window)."""
+    # (the schedules of up to 64 workers are kept: a pass of all workers asks for each of them twice, 3 to 4 us each time)
+    return list((_kept_steps if type(P) is int and P <= 64 else _steps)(P, worker_id, mode))
+
+
+def _steps(P, worker_id, mode):
     lib = load_library()
     cap = max(1, P + 1)
     buf = (DfaStep * cap)()
@@ -504,3 +495,6 @@ def dfa_schedule(P: int, worker_id: int, mode="balanced"):
     if n < 0:
         raise DfaError(n, "dfa_schedule")
     return [Step(b.t, b.kind, b.q_chunk, b.kv_chunk, b.send_to, b.recv_from) for b in buf[:n]]
+
+
+_kept_steps = functools.lru_cache(maxsize=256, typed=True)(_steps)

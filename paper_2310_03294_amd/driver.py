@@ -7,6 +7,9 @@ on the same device here.
 """
 from __future__ import annotations
 
+import collections
+import functools
+
 import torch
 
 from . import binding as B
@@ -134,7 +137,7 @@ def _forward_at_hand(Q, K, V, scale, sched, w, bufs: Buffers, remote):
     fwd.launch(pairs, None)
     if remote is not None:
         parts = [remote[st.recv_from] for st in sched if st.recv_from >= 0]
-        if all(o.stride() == parts[0][0].stride() and l.stride() == parts[0][1].stride() for o, l in parts):
+        if len({(o.stride(), l.stride()) for o, l in parts}) == 1:
             B.dfa_merge_batch(bufs.O, bufs.L, bufs.c, [(w, o, l) for o, l in parts])
         else:
             for o, l in parts:
@@ -187,7 +190,7 @@ def run_worker_share(Q, K, V, dO, scale, P, w, bufs: Buffers, remote, fused=True
     the D pre-pass and the backward of the same pairs.  The gradient chunks the share touches are
     overwritten with the share's own sums (first contribution overwrites, the rest accumulate).
     fused: all chunks and partials being there, the worker's pairs are one walk each way (a short chunk's step by step: 8 heads x 512,
-    P = 8, 183 us, as one walk 84); otherwise step by step."""
+    P = 8, 183 us, as one walk 72); otherwise step by step."""
     sched = B.dfa_schedule(P, w)
     if fused and _fits_a_call(len(sched) * bufs.c, K, bufs.dK):
         _forward_at_hand(Q, K, V, scale, sched, w, bufs, remote)
@@ -227,6 +230,9 @@ def delta_all_chunks(O, dO, delta, c, P):
     """D of the P chunks of c rows.  One launch, unless the slices of all chunks together are longer than a call takes
     (a sequence stored [N, heads, d] has heads * d elements between its rows): then as few as that makes it."""
     per = max(1, B.MAX_SLICE // max(O.stride(1), dO.stride(1)) // max(1, c))     # chunks per launch
+    if per >= P and P * c == O.shape[1] == delta.shape[1] == dO.shape[1]:
+        B.dfa_delta(O, dO, delta=delta)       # (without the slices: 4 us of the host's time)
+        return
     for i in range(0, P, per):
         rows = slice(i * c, min(i + per, P) * c)
         B.dfa_delta(O[:, rows], dO[:, rows], delta=delta[:, rows])
@@ -235,6 +241,13 @@ def delta_all_chunks(O, dO, delta, c, P):
 def _fits_a_call(rows, *tensors):
     """Whether the first `rows` positions of [heads, seq, d] tensors are no longer a slice than a call takes."""
     return all(rows * t.stride(1) <= B.MAX_SLICE for t in tensors)
+
+
+@functools.lru_cache(maxsize=64, typed=True)
+def _whole_triangle(P, mode):
+    """Whether a schedule's pairs are those of every chunk with itself and all earlier ones."""
+    return ({(st.q_chunk, st.kv_chunk) for w in range(P) for st in B.dfa_schedule(P, w, mode) if st.kind != B.DFA_STEP_IDLE}
+            == {(q, k) for q in range(P) for k in range(q + 1)})
 
 
 def backward_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced"):
@@ -246,15 +259,13 @@ def backward_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced"):
     99 / 30.
     Otherwise time step by time step: first the pairs of the owners, then those of the helpers.  Each of the two
     groups has every query chunk and every key/value chunk at most once, so its pairs go out as one launch."""
-    scheds = [B.dfa_schedule(P, w, mode) for w in range(P)]
     grads = (bufs.dQ, bufs.dK, bufs.dV)
-    if ({(st.q_chunk, st.kv_chunk) for s in scheds for st in s if st.kind != B.DFA_STEP_IDLE}
-            == {(q, k) for q in range(P) for k in range(q + 1)} and _fits_a_call(P * bufs.c, Q, K, *grads)):
+    if _whole_triangle(P, mode) and _fits_a_call(P * bufs.c, Q, K, *grads):
         B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, *grads, P * bufs.c, scale).launch([(0, 0, False, False)], True)
         return
     touched = new_pass()
     bwd = B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, *grads, bufs.c, scale)
-    for steps in zip(*scheds):
+    for steps in zip(*(B.dfa_schedule(P, w, mode) for w in range(P))):
         for kind in (B.DFA_STEP_DIAG, B.DFA_STEP_OWN, B.DFA_STEP_HELP):
             pairs = [(st.q_chunk, st.kv_chunk, st.q_chunk in touched["dq"], st.kv_chunk in touched["dkv"])
                      for st in steps if st.kind == kind]
@@ -286,8 +297,7 @@ def _forward_at_once(fwd, state, scheds, bufs: Buffers):
     pairs that are left."""
     walks = [pair for w, sched in enumerate(scheds) for pair in _walk(sched, w, state)]
     helped = [st for steps in zip(*scheds) for st in steps if st.kind == B.DFA_STEP_HELP]
-    most = max(sum(st.kind == B.DFA_STEP_HELP for st in steps) for steps in zip(*scheds))
-    parts = _partials(bufs, most) if helped else []
+    parts = _partials(bufs, max(collections.Counter(st.t for st in helped).values())) if helped else []
     while walks or helped:
         now = sorted(zip(helped, parts), key=lambda x: x[0].send_to)      # (the partials of a chunk next to each other)
         fwd.launch(walks + [(st.q_chunk, st.kv_chunk, fwd.dest(*part), 0, False) for st, part in now], None)

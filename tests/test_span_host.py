@@ -114,3 +114,12 @@ def test_span_arguments():
     # what a pair's backward refused it still refuses
     y = B.DfaBwdPair(*[4096] * 9, 0, 0)
     assert lib.dfa_chunk_bwd_batch(ctypes.byref(shape(s_k=128, causal=1)), ctypes.byref(y), 1, None, 0, None) == -4
+
+
+def test_a_schedule_is_the_callers_own():
+    want = [tuple(st) for st in dfa.dfa_schedule(8, 3)]
+    dfa.dfa_schedule(8, 3).clear()
+    assert [tuple(st) for st in dfa.dfa_schedule(8, 3)] == want
+    for bad in ((8.0, 3), (8, 3.0), (8, 8), (0, 0), (8, -1)):      # refused, also where an equal number has been asked for
+        with pytest.raises((ctypes.ArgumentError, TypeError, dfa.DfaError)):
+            dfa.dfa_schedule(*bad)
