@@ -1026,27 +1026,49 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
                 : launch<Args, full_pair::k_fwd_bf16<false, false, Args>>(p, nt, smem, st);
 }
 
+// What a walk's weights and row sums are taken in: no less than in the pairs that it stands for, each as a call of its own
+// (launch_form) or, with several walks, as those of all owners in one.
+//   REMAINDERS  where those are in the 64-row form: the remainders of the weights too, and fp32 sums.  (That form with 128
+//               rows was tried: walk of 3 chunks of 8 heads x 1000 38.5 -> 43.4 us, of 5 x 2048 143.5 -> 145, of 9 x 2048
+//               258 -> 245.  Without the remainders the latter two are 15 % faster, and o 200 times as far off.)
+//   FP32        rounded weights, fp32 sums: where a walk is little more than a diagonal
+//   ROUNDED     rounded weights and their sums, as in full pairs
+enum class SpanSums { REMAINDERS, FP32, ROUNDED };
+
+SpanSums span_sums(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
+  int64_t owners = 0, longest = 0;
+  bool rounded = true;
+  for (int i = 0; i < n; ++i) {
+    owners += spans[i].own != 0;
+    longest = std::max<int64_t>(longest, spans[i].n_keys);
+    rounded &= !spans[i].own || spans[i].n_keys >= 2 * static_cast<int64_t>(sh.s_q);
+  }
+  const int64_t n64 = (static_cast<int64_t>(sh.s_q) + 63) / 64 * sh.h_q * std::max<int64_t>(owners, 1);
+  // (up to 512 workgroups: diagonals of 2048 rows and more, and the one full pair of two workers)
+  const bool two_rounds = longest <= sh.s_q ? sh.s_q >= 2048 : longest <= 2 * static_cast<int64_t>(sh.s_q);
+  if (n64 <= 256 || (n64 <= 512 && two_rounds)) return SpanSums::REMAINDERS;
+  return rounded ? SpanSums::ROUNDED : SpanSums::FP32;
+}
+
 // The spans of a launch.  Which form, and in how many parts the keys of a span are cut (the parts are merged afterwards):
 // by an estimate, with what one box measured for its terms: 8 us per workgroup and, per 64 keys, 0.95 us with 64-row
 // workgroups (four key parts), 1.1 with 128-row ones (two) and 1.9 with 256-row ones; a launch that runs in one round takes its
 // longest walk, a longer one the device's even share and about half a walk; the merge 5 us and 3 TB/s.
-struct SpanPlan { int rows, parts; double us; bool rounded; };
+struct SpanPlan { int rows, parts; double us; SpanSums sums; };
 
 SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_t ws_bytes) {
   SpanPlan best{};
-  bool whole = true, rounded = true;      // (launch_spans)
-  for (int i = 0; i < n; ++i) {
-    whole &= spans[i].n_keys % BN == 0;
-    rounded &= !spans[i].own || spans[i].n_keys >= 2 * static_cast<int64_t>(sh.s_q);
-  }
+  const SpanSums sums = span_sums(sh, spans, n);
+  bool whole = true;      // (launch_spans)
+  for (int i = 0; i < n; ++i) whole &= spans[i].n_keys % BN == 0;
   for (int rows : {64, 128, 256}) {
-    if (rows == 256 && !whole && !rounded) break;
+    if ((rows > 64 && sums == SpanSums::REMAINDERS) || (rows == 256 && !whole && sums == SpanSums::FP32)) break;
     const double tile = rows == 64 ? 0.95 : rows == 128 ? 1.1 : 1.9;
     const int64_t blocks = (static_cast<int64_t>(sh.s_q) + rows - 1) / rows * sh.h_q;
     for (int parts = 1; parts <= MAX_SPAN_PARTS; ++parts) {
       const SpanWork w = span_work(sh, spans, n, parts, blocks);
       if (parts > 1 && (!w.cut || w.part_bytes > ws_bytes)) break;
-      SpanPlan x{rows, parts, 8 + w.longest / 64 * tile, rounded};
+      SpanPlan x{rows, parts, 8 + w.longest / 64 * tile, sums};
       if (w.workgroups > 256) x.us = std::max(x.us, 8 + w.keys / 64 * tile / 256 + 0.45 * w.longest / 64 * tile);
       if (w.cut) x.us += 5 + 2 * w.part_bytes / 3e6;
       if (!best.rows || x.us < best.us) best = x;
@@ -1055,9 +1077,8 @@ SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_
   return best;
 }
 
-// Where every span has a chunk and more of keys before its own, row sums are taken over the rounded weights, as for full pairs;
-// over the fp32 weights otherwise (256 rows: of whole tiles only, the ragged form spills).
-int launch_spans(FwdSpans& p, const dfa_shape& sh, int n, int rows, bool rounded, hipStream_t st) {
+// (FP32 with 256 rows: whole tiles only, the ragged form spills)
+int launch_spans(FwdSpans& p, const dfa_shape& sh, int n, int rows, SpanSums sums, hipStream_t st) {
   p.ntq = (sh.s_q + rows - 1) / rows;
   p.per_pair = p.ntq * sh.h_q;
   p.heads = sh.h_q % 8 == 0 ? sh.h_q / 8 : 0;
@@ -1065,6 +1086,7 @@ int launch_spans(FwdSpans& p, const dfa_shape& sh, int n, int rows, bool rounded
   p.map = xcd_map(static_cast<int64_t>(p.per_pair) * n, 1, p.heads ? 8 : 1);      // (1: every second row of items backwards)
   std::stable_sort(p.span, p.span + n, [](const Span& x, const Span& y) { return x.s_k > y.s_k; });
   if (rows == 64) return launch<FwdSpans, split::k_fwd_bf16<2, 4, true, FwdSpans>>(p, 512, split::kSmem<4>, st);
+  const bool rounded = sums == SpanSums::ROUNDED;
   if (rows == 128) return rounded ? launch<FwdSpans, split::k_fwd_bf16<4, 2, true, FwdSpans, true>>(p, 512, split::kSmem<2>, st)
                                   : launch<FwdSpans, split::k_fwd_bf16<4, 2, true, FwdSpans>>(p, 512, split::kSmem<2>, st);
   constexpr int nt = full_pair::NT, smem = full_pair::SMEM_BYTES;
@@ -1112,7 +1134,7 @@ int launch_span_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void
       y.o = x.o; y.lse = x.lse; y.accumulate = x.accumulate; y.o_sh = x.o_sh; y.o_ss = x.o_ss; y.l_sh = x.l_sh;
       y.s_k = x.n_keys; y.off = x.off; y.o_bf16 = x.o_bf16;
     }
-    return launch_spans(p, sh, count, pl.rows, pl.rounded, st);
+    return launch_spans(p, sh, count, pl.rows, pl.sums, st);
   });
 }
 

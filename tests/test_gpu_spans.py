@@ -71,6 +71,27 @@ def test_forward_walks(dtype, d, h_q, h_kv, c, walks, acc, o_dtype):
         assert torch.equal(O[:, j * c:(j + 1) * c].cpu(), o0[:, j * c:(j + 1) * c])
 
 
+@pytest.mark.parametrize("h_q,h_kv,c,walks", [
+    (8, 8, 1000, [(2, 0, 2)]),                     # a worker's walk whose chunk has 128 workgroups of 64 rows
+    (8, 2, 2048, [(4, 2, 4)]),                     # ... 256
+    (8, 4, 2048, [(0, 0, 0), (1, 0, 1)]),          # two workers, 512 together
+    (16, 4, 2048, [(0, 0, 0)]),                    # one worker, 512
+])
+def test_walks_keep_the_remainders_of_the_weights(h_q, h_kv, c, walks):
+    """Where the pairs as calls of their own have weights of 16 bits, so have the walks.  Bound of the relative error: 2^-17 of
+    a weight, and twice that again for scores, exponentials and sums in fp32 and the merge of parts (rounded weights: 1e-3)."""
+    n, scale = max(w[0] for w in walks) + 1, 128 ** -0.5
+    q, k, v, _ = case(900 + c + h_q, h_q, h_kv, n * c, n * c, 128, BF16)
+    O, L = torch.empty(h_q, n * c, 128, device=dev()), torch.empty(h_q, n * c, device=dev())
+    fwd = B.ForwardChunks(*(t.to(dev()) for t in (q, k, v)), c, scale)
+    state = fwd.dest(O, L)
+    fwd.launch([(qc, kc, state, qc, kc != hi) for qc, lo, hi in walks for kc in range(hi, lo - 1, -1)], None)
+    for qc, lo, hi in walks:
+        rows, keys, h = slice(qc * c, (qc + 1) * c), slice(lo * c, (hi + 1) * c), h_q - 1
+        want = A.rows_fwd(np64(q[h, rows]), _visible(lo, hi, qc, c), np64(k[h_kv - 1, keys]), np64(v[h_kv - 1, keys]), scale, lo * c)
+        assert np.linalg.norm(np64(O[h, rows]) - want[0]) <= 3 * 2 ** -17 * np.linalg.norm(want[0]), qc
+
+
 @pytest.mark.parametrize("ws", [0, 1, 2])
 def test_forward_walk_with_any_scratch(ws):
     """None, half and all of the scratch asked for: nothing is written behind it."""
