@@ -1099,10 +1099,40 @@ int launch_spans(FwdSpans& p, const dfa_shape& sh, int n, int rows, SpanSums sum
 
 }  // namespace
 
+// Query rows of full pairs that are whole rounds of 256-row workgroups, where the rows after them are better taken by a launch of
+// their own; 0: all in one launch.  All workgroups of a full pair are equally long, so a round that is not full costs as
+// much as one that is; in 128-row workgroups, one per CU at most, the rest takes 0.6 of that.  us per call, one launch /
+// two: 32 heads x 2777 x 3001 keys 156 / 146, x 3072 186 / 169, x 5120 429 / 401, x 10300 1712 / 1648, x 18500 5301 / 5051, 8 x 10000
+// 461 / 423, 16 x 5000 x 4000 196 / 181, 64 x 1300 90 / 81, 96 x 700 x 2000 125 / 99.  Not with fewer keys, where the second launch
+// and its prologue count: 32 x 2777 x 1200 keys and more gain 3 to 6 %, x 1024 60.7 / 61.0, x 512 37 / 41, 8 x 16896 x 700 78 / 81;
+// nor where 128-row workgroups alone have no more rounds (160 x 400).
+int64_t rows_of_whole_rounds(const dfa_shape& sh, int n) {
+  const int64_t heads = static_cast<int64_t>(sh.h_q) * n, n256 = (static_cast<int64_t>(sh.s_q) + 255) / 256 * heads;
+  const int64_t n128 = (static_cast<int64_t>(sh.s_q) + 127) / 128 * heads, rounds = n256 / 256;
+  if (sh.causal || sh.s_k <= 1024 || !rounds || n128 <= rounds * 512) return 0;
+  const int64_t rows = rounds * 256 / heads * 256, rest = sh.s_q - rows;
+  return rows > 0 && rest > 0 && (rest + 127) / 128 * heads <= 256 ? rows : 0;
+}
+
 int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st) {
   for (; n > MAX_PAIRS; pairs += MAX_PAIRS, n -= MAX_PAIRS) {
     const int rc = launch_fwd_bf16(sh, pairs, MAX_PAIRS, st);
     if (rc) return rc;
+  }
+  if (const int64_t rows = rows_of_whole_rounds(sh, n)) {
+    dfa_shape part = sh;
+    part.s_q = static_cast<int32_t>(rows);
+    int rc = launch_fwd_bf16(part, pairs, n, st);
+    if (rc) return rc;
+    part.s_q = static_cast<int32_t>(sh.s_q - rows);
+    dfa_fwd_pair rest[MAX_PAIRS];
+    for (int i = 0; i < n; ++i) {
+      rest[i] = pairs[i];
+      rest[i].q = static_cast<const char*>(pairs[i].q) + rows * sh.q_stride_s * 2;
+      rest[i].o = static_cast<char*>(pairs[i].o) + rows * pairs[i].o_stride_s * (sh.o_dtype == DFA_BF16 ? 2 : 4);
+      rest[i].lse = pairs[i].lse + rows;
+    }
+    return launch_fwd_bf16(part, rest, n, st);
   }
   auto operand = [](const void* x) { return static_cast<const __bf16*>(x); };
   FwdBatch p{};

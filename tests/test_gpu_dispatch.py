@@ -90,6 +90,34 @@ def test_bf16_forward_forms_long_causal(h_q, s):
         assert maxerr(o[h, rows], O) <= tol and maxerr(lse[h, rows], L) <= 1e-4
 
 
+@pytest.mark.parametrize("h_q,h_kv,s_q,s_k", [
+    (64, 32, 1025, 1100),      # a round of 256-row workgroups and one row more: 64 rows
+    (32, 8, 2400, 1025),       # ... and 352 rows of 128
+    (48, 48, 1300, 1030),      # a first launch that leaves CUs idle (5 blocks of 48 heads)
+    (128, 32, 513, 1153),      # a row of the last round
+    (64, 16, 2200, 1090),      # two rounds and the rest
+])
+def test_bf16_forward_whole_rounds_and_the_rest(h_q, h_kv, s_q, s_k):
+    """Rows on both sides of the cut, by samples; outputs with strides of their own, from the empty state and continued."""
+    d, tol, scale = 128, TOL[torch.bfloat16], 128 ** -0.5
+    q, k, v, _ = case(7000 + s_q + s_k, h_q, h_kv, s_q, s_k, d, torch.bfloat16)
+    Q, K, V = (t.to(dev()) for t in (q, k, v))
+    Q = Q.transpose(0, 1).contiguous().transpose(0, 1)            # rows of all heads side by side
+    cut = 256 // h_q * 256 * (2 if s_q > 2048 and h_q == 64 else 1)
+    rows = sorted({0, 1, 255, 256, cut - 129, cut - 1, cut, min(cut + 63, s_q - 1), min(cut + 129, s_q - 1), s_q - 1})
+    for o_dtype in (torch.float32, torch.bfloat16):
+        o = torch.full((s_q + 3, h_q, d), 7.0, dtype=o_dtype, device=dev())
+        lse = torch.full((h_q, s_q + 5), 7.0, device=dev())
+        out = o[:s_q].transpose(0, 1), lse[:, :s_q]
+        for weight, f in ((0.0, dfa.dfa_chunk_fwd), (math.log(2), dfa.dfa_chunk_fwd_acc)):
+            f(Q, K, V, False, scale, o=out[0], lse=out[1])
+            for h in (0, h_q // 2, h_q - 1):
+                kv = h * h_kv // h_q
+                O, L = A.rows_fwd(np64(q[h, rows]), np.full(len(rows), s_k - 1), np64(k[kv]), np64(v[kv]), scale)
+                assert maxerr(out[0][h, rows], O) <= tol and maxerr(out[1][h, rows], L + weight) <= tol
+        assert bool((o[s_q:] == 7).all()) and bool((lse[:, s_q:] == 7).all())
+
+
 WIDE = [(120, 120, 300, 1061, False), (22, 1, 6144, 6144, True)]      # 256-row workgroups, full and diagonal
 
 
