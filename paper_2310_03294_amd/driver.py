@@ -309,14 +309,21 @@ def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backw
     """The whole schedule of all P workers on one GPU.
     fused: OWN pairs continue from the owner's state instead of partial + merge, and pairs that do not wait for each other go
     out as one launch (a pair of small chunks alone leaves most of one device idle): all of the owners' as one walk
-    per owner; otherwise time step by time step, pair by pair."""
+    per owner, or, in bf16 and where the pairs are those of every chunk with itself and all earlier ones, all pairs as one
+    causal call, which has no partials to write, read and merge (us, forward, walks / one call: 32 over 8 heads x 8 x 1024
+    608 / 503, 8 over 2 x 8 x 2048 596 / 479, 32 x 8 x 300 141 / 72, 8 x 4 x 512 38 / 32; not in fp32, where the walks cut
+    the keys of the last rows in parts: 8 over 2 heads x 4 x 1024 385 / 478, d = 64, 2 over 1 x 3 x 700 43 / 74);
+    otherwise time step by time step, pair by pair."""
     c = bufs.c
     scheds = [B.dfa_schedule(P, w, mode) for w in range(P)]
     nsteps = len(scheds[0])
-    fwd = B.ForwardChunks(Q, K, V, c, scale)
+    one_call = fused and Q.dtype == torch.bfloat16 and _whole_triangle(P, mode) and _fits_a_call(P * c, Q, K, bufs.O)
+    fwd = B.ForwardChunks(Q, K, V, P * c if one_call else c, scale)
     state = fwd.dest(bufs.O, bufs.L)
-    at_once = fused and _fits_a_call(nsteps * c, K)
-    if at_once:
+    at_once = fused and (one_call or _fits_a_call(nsteps * c, K))
+    if one_call:
+        fwd.launch([(0, 0, state, 0, False)], True)
+    elif at_once:
         _forward_at_once(fwd, state, scheds, bufs)
     for t in range(0 if at_once else nsteps):
         steps = [scheds[w][t] for w in range(P)]
