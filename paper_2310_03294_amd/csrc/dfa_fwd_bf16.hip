@@ -986,6 +986,7 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
     // 26.3 -> 26.2, x 700 18.8 -> 19.3, 64 x 384 14.8 -> 15.5.
     two = sh.s_q >= 1024 && n128 <= (sh.s_q > 2048 ? 512 : sh.s_q >= 1280 ? 352 : 256);
   } else {
+    // (Calls whose rows are whole rounds of 256-row workgroups and a small rest come here as two: rows_of_whole_rounds.)
     // One round of 64-row workgroups at most: split the keys.  The 128-row form (10 % slower per row, two
     // workgroups per CU) where it needs one workgroup per CU at most, or where the last round of 256-row
     // workgroups would be half empty or worse.
