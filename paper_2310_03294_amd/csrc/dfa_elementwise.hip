@@ -171,35 +171,31 @@ __global__ void __launch_bounds__(256) k_merge_parts(MergeParts p) {
   float a[VN];
 #pragma unroll
   for (int i = 0; i < VN; ++i) a[i] = 0.f;
-  const float la = g.accumulate ? *la_p : -INFINITY;
-  if (la > -INFINITY) {
+  float la = g.accumulate ? *la_p : -INFINITY;
+  if (g.accumulate == MERGE_CONTINUE && !(la > -INFINITY)) la = -INFINITY;
+  if (la > -INFINITY || g.accumulate == MERGE_ALL) {
     if (g.o_bf16) load_row<VN, true>(a, g.o, off_a); else load_row<VN, false>(a, g.o, off_a);
   }
   float m = la;
 #pragma unroll
   for (int i = 0; i < GROUP_PARTS; ++i) m = i < g.n ? fmaxf(m, lb[i]) : m;
-  float l = -INFINITY;
-  if (m > -INFINITY) {
-    const float wa = expf(la - m);
-    float s = wa;
+  // Nothing to weigh against: all weights are zero, and what is no number stays that, as in k_merge.
+  const bool any = m > -INFINITY;
+  const float wa = any ? expf(la - m) : 0.f;
+  float s = wa;
 #pragma unroll
-    for (int e = 0; e < VN; ++e) a[e] *= wa;
+  for (int e = 0; e < VN; ++e) a[e] *= wa;
 #pragma unroll
-    for (int i = 0; i < GROUP_PARTS; ++i) {
-      if (i >= g.n) break;
-      const float w = expf(lb[i] - m);
-      s += w;
+  for (int i = 0; i < GROUP_PARTS; ++i) {
+    if (i >= g.n) break;
+    const float w = any ? expf(lb[i] - m) : 0.f;
+    s += w;
 #pragma unroll
-      for (int e = 0; e < VN; ++e) a[e] = fmaf(w, b[i].v[e], a[e]);
-    }
-    l = m + logf(s);
-    const float inv = 1.f / s;
-#pragma unroll
-    for (int e = 0; e < VN; ++e) a[e] *= inv;
-  } else {
-#pragma unroll
-    for (int e = 0; e < VN; ++e) a[e] = 0.f;
+    for (int e = 0; e < VN; ++e) a[e] = fmaf(w, b[i].v[e], a[e]);
   }
+  const float l = any ? m + logf(s) : -INFINITY, inv = any ? 1.f / s : 0.f;
+#pragma unroll
+  for (int e = 0; e < VN; ++e) a[e] *= inv;
 #pragma unroll
   for (int e = 0; e < VN; e += 4) {
     if (g.o_bf16) {
@@ -303,7 +299,7 @@ class MergeQueue {
       MergeGroup& x = p_.group[ng_++];
       x = g;
       x.first = np_; x.n = take;
-      if (more) x.accumulate = 1;
+      if (more) x.accumulate = MERGE_ALL;
       for (int i = 0; i < take; ++i) p_.part[np_++] = parts[done + i];
     }
     return DFA_OK;
@@ -350,7 +346,7 @@ int launch_merge(const dfa_merge_desc& md, const dfa_merge_pair* pairs, int n, h
       parts[count++] = {pairs[i].o_b, pairs[i].lse_b};
       const bool last = i + 1 == n || !same(i + 1);
       if (!last && count < GROUP_PARTS) continue;
-      const int rc = queue.add({pairs[i].o_a, pairs[i].lse_a, md.a_stride_h, md.a_stride_s, md.lse_a_stride_h, 0, 0, 1,
+      const int rc = queue.add({pairs[i].o_a, pairs[i].lse_a, md.a_stride_h, md.a_stride_s, md.lse_a_stride_h, 0, 0, MERGE_ALL,
                                 md.o_dtype == DFA_BF16}, parts, count, more);
       if (rc) return rc;
       count = 0;

@@ -10,7 +10,10 @@ namespace dfa {
 
 // Launch wrappers: every one validates nothing (the ABI layer did) and returns a dfa_status.
 int launch_merge(const dfa_merge_desc& md, const dfa_merge_pair* pairs, int n, hipStream_t st);
-// Several partials (o_b, lse_b) into one (o, lse) each, which takes part (accumulate) or is only written.
+// Several partials (o_b, lse_b) into one (o, lse) each.  What becomes of that, `accumulate`: it is only written; it takes part as
+// the state that a forward continues from (lse = -inf or no number: empty, whatever its o); or as an operand of a merge
+// (lse = -inf: weight zero, its o counts and is zero).
+enum { MERGE_WRITE, MERGE_CONTINUE, MERGE_ALL };
 struct MergeShape { int heads, rows, d; bool b_bf16; int64_t b_sh, b_ss, lb_sh; };
 struct MergeGroup { void* o; float* lse; int64_t o_sh, o_ss, l_sh; int first, n, accumulate, o_bf16; };
 struct MergePart { const void* o; const float* lse; };

@@ -88,8 +88,8 @@ int run_spans(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int parts, 
       if (rc) return rc;
     }
     if (np > 1)
-      groups[n_groups++] = {x.o, x.lse, x.o_stride_h, x.o_stride_s, x.lse_stride_h, n_results, np, x.accumulate != 0,
-                            sh.o_dtype == DFA_BF16};
+      groups[n_groups++] = {x.o, x.lse, x.o_stride_h, x.o_stride_s, x.lse_stride_h, n_results, np,
+                            x.accumulate ? MERGE_CONTINUE : MERGE_WRITE, sh.o_dtype == DFA_BF16};
     for (int j = 0; j < np; ++j) {
       const int k0 = span_cut(sh, x, np, j);
       SpanPart& y = todo[count++];

@@ -139,6 +139,73 @@ def test_merges_of_several_partials(d, dtype, parts):
         assert maxerr(L[:, i * c:(i + 1) * c], wl) <= 1e-5
 
 
+@pytest.mark.parametrize("d,dtype", [(64, F32), (128, F32), (128, BF16)])
+@pytest.mark.parametrize("m", [2, 9])
+def test_merges_hand_on_what_is_no_number(d, dtype, m):
+    """NaN and infinities come out of several partials in one pass where they come out of one merge after the other."""
+    h, c, g = 2, 12, torch.Generator().manual_seed(m)
+    nan, inf = float("nan"), float("inf")
+    o, lse = torch.randn(h, c, d, generator=g).to(dtype), torch.randn(h, c, generator=g)
+    parts = [(torch.randn(h, c, d, generator=g).to(dtype), torch.randn(h, c, generator=g)) for _ in range(m)]
+    o[:, 0], lse[:, 0] = nan, -inf                      # a state that is empty and no number
+    parts[0][0][:, 1], parts[0][1][:, 1] = nan, -inf    # such a partial
+    for x, l in [(o, lse), *parts]:                     # all of them (a query that is no number)
+        x[:, 2], l[:, 2] = nan, -inf
+    lse[:, 3], parts[1][1][:, 4] = nan, nan
+    o[:, 5], parts[0][0][:, 6] = inf, -inf
+    o[:, 7], lse[:, 7] = inf, -inf
+    for _, l in [(o, lse), *parts]:
+        l[:, 8] = -inf                                  # all empty
+    parts[m - 1][0][:, 9], parts[m - 1][1][:, 9] = nan, -inf
+    for x, l in [(o, lse), *parts[:-1]]:                # all but the last
+        x[:, 10], l[:, 10] = nan, -inf
+    one, together = ((o.to(dev()), lse.to(dev())) for _ in range(2))
+    parts = [(x.to(dev()), l.to(dev())) for x, l in parts]
+    for x, l in parts:
+        dfa.dfa_merge(*one, x, l)
+    B.dfa_merge_batch(*together, c, [(0, x, l) for x, l in parts])
+    for a, b in zip(one, together):
+        assert torch.equal(a.isnan(), b.isnan()) and torch.equal(a.isinf(), b.isinf())
+        finite = a.isfinite()
+        # (m roundings of the stored o against one)
+        assert (a[finite].float() - b[finite].float()).abs().max().item() <= (1e-5 if dtype == F32 else m * 2 ** -7)
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("acc", [False, True])
+def test_cut_walks_hand_on_what_is_no_number(dtype, acc):
+    """A query, a key and a value that are no numbers, and an empty state with any o, in a walk whose keys are cut in parts: NaN
+    in the rows in which the pairs one after the other have it."""
+    h, c, d, n = 2, 64, 128, 12
+    q, k, v, _ = case(880, h, h, n * c, n * c, d, dtype)
+    q[0, (n - 1) * c + 5] = float("nan")
+    k[1, 7, 0] = float("nan")                # (in the last pair: a forward takes the state that it leaves for an empty one)
+    v[1, 8 * c + 9, 1] = float("nan")
+    o0, lse0 = torch.randn(h, c, d), torch.randn(h, c)
+    o0[:, 20], lse0[:, 20] = float("nan"), -float("inf")        # empty: its o is not looked at
+    lse0[0, 21] = float("nan")
+    fwd = B.ForwardChunks(*(t.to(dev()) for t in (q, k, v)), c, d ** -0.5)
+    got = []
+    for at_once in (True, False):
+        o, lse = o0.to(dev()), lse0.to(dev())
+        dest = fwd.dest(o, lse)
+        pairs = [(n - 1, kc, dest, 0, acc or kc != n - 1) for kc in range(n - 1, -1, -1)]
+        if at_once:
+            sh, span = fwd.sh, B.DfaFwdSpan(fwd.q[n - 1], fwd.k[0], fwd.v[0], o.data_ptr(), lse.data_ptr(), c * d, d, c, n * c, 1, acc, 0)
+            assert fwd.lib.dfa_span_fwd_workspace(ctypes.byref(sh), ctypes.byref(span), 1) > 0      # (it is cut)
+            fwd.launch(pairs, None)
+        else:
+            for pair in pairs:
+                fwd.launch([pair], pair[1] == n - 1)
+        got.append((o, lse))
+    (o, lse), (want_o, want_lse) = got
+    assert torch.equal(o.isnan(), want_o.isnan()) and torch.equal(lse.isnan(), want_lse.isnan())
+    assert bool(o[0, 5].isnan().all()) and not bool(o[0, 20].isnan().any())
+    for a, b in zip((o, lse), (want_o, want_lse)):
+        finite = b.isfinite()
+        assert (a[finite] - b[finite]).abs().max().item() <= TOL[dtype]
+
+
 # dtype, d, heads, chunk, query chunk, first and last key/value chunk, heads that are checked
 BWD = [
     (BF16, 128, 8, 8, 130, 6, 0, 6, (0, 7)),        # dq by several workgroups per row block, ragged
