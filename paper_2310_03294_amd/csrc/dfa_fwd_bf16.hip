@@ -60,6 +60,7 @@ struct FwdSpans : FwdParams {
   Span span[MAX_PAIRS];
 };
 struct SpanParams : FwdParams { int off; };
+template <class Args> constexpr bool kSpans = std::is_same_v<Args, FwdSpans>;
 
 // Keys up to which query row 0 sees (a single pair or a list of pairs of equal chunks: its own).
 template <class P> __device__ __forceinline__ int off_of(const P&) { return 0; }
@@ -395,9 +396,9 @@ constexpr int OFF_ST = OFF_AL + 2 * AL_BYTES;  // 1 / row sum, written once by t
 constexpr int SMEM_BYTES = OFF_ST + AL_BYTES;
 
 // RAGGED: s_k is no multiple of the 64-row tile, so the last K/V tile has rows past the end.
-// CAUSAL: the diagonal pair; its row sums are taken over the fp32 weights, as in the other causal forms (ROUNDED: a chunk of
-// keys and more before the diagonal; over the rounded weights, as for full pairs).
-template <bool RAGGED, bool CAUSAL, class Args, bool ROUNDED = !CAUSAL>
+// CAUSAL: the diagonal pair; its row sums are taken over the fp32 weights, as in the other causal forms (of a span: where a tile
+// has keys of the chunk's own; before them over the rounded weights, as for full pairs).
+template <bool RAGGED, bool CAUSAL, class Args>
 __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
   extern __shared__ __align__(16) char smem[];
 
@@ -532,6 +533,7 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
         // over the ROUNDED values (v_dot2c_f32_bf16 against a pair of ones: one instruction per two
         // scores), so that the sum that normalises O is the sum of exactly the weights that multiply V.
         bf16x8 p0, p1, p2, p3;
+        const bool rounded = kSpans<Args> ? k0 + BN <= off : !CAUSAL;
         auto exponentials = [&]() {
           const float mc = (m_run == -INFINITY) ? 0.f : m_run * c2;
 #pragma unroll
@@ -541,7 +543,7 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
           }
           p0 = pack8(s0, 0); p1 = pack8(s0, 8); p2 = pack8(s1, 0); p3 = pack8(s1, 8);
           // independent chains, so that the adds do not wait for one another
-          if constexpr (!ROUNDED) {
+          if (!rounded) {
             float a[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < 16; ++j) { a[j & 1] += s0[j]; a[2 + (j & 1)] += s1[j]; }
@@ -678,7 +680,7 @@ template <int NS> constexpr int kTilesBytes = 2 * (kKeys<NS> / BN) * TILE_BYTES;
 template <int NS> constexpr int kSmem = 2 * kTilesBytes<NS>;
 constexpr int RES_BYTES = 64 * 64 * 4;         // a wavefront's O^T, 64 registers per lane
 
-template <int RB, int NS, bool CAUSAL, class Args, bool ROUNDED = !CAUSAL>
+template <int RB, int NS, bool CAUSAL, class Args>
 __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16(Args a) {
   constexpr int BMS = RB * 32;                 // query rows per workgroup
   constexpr bool LO = RB == 2;
@@ -812,11 +814,13 @@ __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16
           l_run *= alpha;
         }
         const float mc = (m_run == -INFINITY) ? 0.f : m_run * c2;
+        const bool rounded = !LO && (kSpans<Args> ? kb0 + 32 <= off : !CAUSAL);
         float sum = 0.f;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], c2, -mc));
-          if (LO || !ROUNDED) sum += s[j];
+        for (int j = 0; j < 16; ++j) s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], c2, -mc));
+        if (!rounded) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) sum += s[j];
         }
         if (__any(alpha != 1.f)) {
 #pragma unroll
@@ -833,7 +837,7 @@ __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16
             for (int e = 0; e < 8; ++e) s[8 * u + e] -= static_cast<float>(pb[u][e]);
             pl[u] = pack8(s, 8 * u);
           }
-          if (!LO && ROUNDED) sum = sum8(pb[u], sum);
+          if (rounded) sum = sum8(pb[u], sum);
         }
         l_run += sum;
         DFA_SCHED_FENCE();
@@ -1027,49 +1031,38 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
                 : launch<Args, full_pair::k_fwd_bf16<false, false, Args>>(p, nt, smem, st);
 }
 
-// What a walk's weights and row sums are taken in: no less than in the pairs that it stands for, each as a call of its own
-// (launch_form) or, with several walks, as those of all owners in one.
-//   REMAINDERS  where those are in the 64-row form: the remainders of the weights too, and fp32 sums.  (That form with 128
-//               rows was tried: walk of 3 chunks of 8 heads x 1000 38.5 -> 43.4 us, of 5 x 2048 143.5 -> 145, of 9 x 2048
-//               258 -> 245.  Without the remainders the latter two are 15 % faster, and o 200 times as far off.)
-//   FP32        rounded weights, fp32 sums: where a walk is little more than a diagonal
-//   ROUNDED     rounded weights and their sums, as in full pairs
-enum class SpanSums { REMAINDERS, FP32, ROUNDED };
-
-SpanSums span_sums(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
+// Whether the weights of a list of spans enter with their remainders (64-row form): as in the pairs that they stand for, each as a
+// call of its own (launch_form) or, with several walks, as those of all owners in one.  (That form with 128
+// rows was tried: walk of 3 chunks of 8 heads x 1000 38.5 -> 43.4 us, of 5 x 2048 143.5 -> 145, of 9 x 2048 258 -> 245.  Without
+// the remainders the latter two are 15 % faster, and o 200 times as far off.)
+bool remainders(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
   int64_t owners = 0, longest = 0;
-  bool rounded = true;
   for (int i = 0; i < n; ++i) {
     owners += spans[i].own != 0;
     longest = std::max<int64_t>(longest, spans[i].n_keys);
-    rounded &= !spans[i].own || spans[i].n_keys >= 2 * static_cast<int64_t>(sh.s_q);
   }
   const int64_t n64 = (static_cast<int64_t>(sh.s_q) + 63) / 64 * sh.h_q * std::max<int64_t>(owners, 1);
   // (up to 512 workgroups: diagonals of 2048 rows and more, and the one full pair of two workers)
   const bool two_rounds = longest <= sh.s_q ? sh.s_q >= 2048 : longest <= 2 * static_cast<int64_t>(sh.s_q);
-  if (n64 <= 256 || (n64 <= 512 && two_rounds)) return SpanSums::REMAINDERS;
-  return rounded ? SpanSums::ROUNDED : SpanSums::FP32;
+  return n64 <= 256 || (n64 <= 512 && two_rounds);
 }
 
 // The spans of a launch.  Which form, and in how many parts the keys of a span are cut (the parts are merged afterwards):
 // by an estimate, with what one box measured for its terms: 8 us per workgroup and, per 64 keys, 0.95 us with 64-row
 // workgroups (four key parts), 1.1 with 128-row ones (two) and 1.9 with 256-row ones; a launch that runs in one round takes its
 // longest walk, a longer one the device's even share and about half a walk; the merge 5 us and 3 TB/s.
-struct SpanPlan { int rows, parts; double us; SpanSums sums; };
+struct SpanPlan { int rows, parts; double us; };
 
-SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_t ws_bytes) {
+SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, bool all_remainders, int64_t ws_bytes) {
   SpanPlan best{};
-  const SpanSums sums = span_sums(sh, spans, n);
-  bool whole = true;      // (launch_spans)
-  for (int i = 0; i < n; ++i) whole &= spans[i].n_keys % BN == 0;
   for (int rows : {64, 128, 256}) {
-    if ((rows > 64 && sums == SpanSums::REMAINDERS) || (rows == 256 && !whole && sums == SpanSums::FP32)) break;
+    if (rows > 64 && all_remainders) break;
     const double tile = rows == 64 ? 0.95 : rows == 128 ? 1.1 : 1.9;
     const int64_t blocks = (static_cast<int64_t>(sh.s_q) + rows - 1) / rows * sh.h_q;
     for (int parts = 1; parts <= MAX_SPAN_PARTS; ++parts) {
       const SpanWork w = span_work(sh, spans, n, parts, blocks);
       if (parts > 1 && (!w.cut || w.part_bytes > ws_bytes)) break;
-      SpanPlan x{rows, parts, 8 + w.longest / 64 * tile, sums};
+      SpanPlan x{rows, parts, 8 + w.longest / 64 * tile};
       if (w.workgroups > 256) x.us = std::max(x.us, 8 + w.keys / 64 * tile / 256 + 0.45 * w.longest / 64 * tile);
       if (w.cut) x.us += 5 + 2 * w.part_bytes / 3e6;
       if (!best.rows || x.us < best.us) best = x;
@@ -1078,8 +1071,7 @@ SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_
   return best;
 }
 
-// (FP32 with 256 rows: whole tiles only, the ragged form spills)
-int launch_spans(FwdSpans& p, const dfa_shape& sh, int n, int rows, SpanSums sums, hipStream_t st) {
+int launch_spans(FwdSpans& p, const dfa_shape& sh, int n, int rows, hipStream_t st) {
   p.ntq = (sh.s_q + rows - 1) / rows;
   p.per_pair = p.ntq * sh.h_q;
   p.heads = sh.h_q % 8 == 0 ? sh.h_q / 8 : 0;
@@ -1087,15 +1079,12 @@ int launch_spans(FwdSpans& p, const dfa_shape& sh, int n, int rows, SpanSums sum
   p.map = xcd_map(static_cast<int64_t>(p.per_pair) * n, 1, p.heads ? 8 : 1);      // (1: every second row of items backwards)
   std::stable_sort(p.span, p.span + n, [](const Span& x, const Span& y) { return x.s_k > y.s_k; });
   if (rows == 64) return launch<FwdSpans, split::k_fwd_bf16<2, 4, true, FwdSpans>>(p, 512, split::kSmem<4>, st);
-  const bool rounded = sums == SpanSums::ROUNDED;
-  if (rows == 128) return rounded ? launch<FwdSpans, split::k_fwd_bf16<4, 2, true, FwdSpans, true>>(p, 512, split::kSmem<2>, st)
-                                  : launch<FwdSpans, split::k_fwd_bf16<4, 2, true, FwdSpans>>(p, 512, split::kSmem<2>, st);
+  if (rows == 128) return launch<FwdSpans, split::k_fwd_bf16<4, 2, true, FwdSpans>>(p, 512, split::kSmem<2>, st);
   constexpr int nt = full_pair::NT, smem = full_pair::SMEM_BYTES;
   bool whole = true;
   for (int i = 0; i < n; ++i) whole &= p.span[i].s_k % BN == 0;
-  if (!rounded) return launch<FwdSpans, full_pair::k_fwd_bf16<false, true, FwdSpans>>(p, nt, smem, st);
-  return whole ? launch<FwdSpans, full_pair::k_fwd_bf16<false, true, FwdSpans, true>>(p, nt, smem, st)
-               : launch<FwdSpans, full_pair::k_fwd_bf16<true, true, FwdSpans, true>>(p, nt, smem, st);
+  return whole ? launch<FwdSpans, full_pair::k_fwd_bf16<false, true, FwdSpans>>(p, nt, smem, st)
+               : launch<FwdSpans, full_pair::k_fwd_bf16<true, true, FwdSpans>>(p, nt, smem, st);
 }
 
 }  // namespace
@@ -1152,8 +1141,10 @@ int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipSt
   return launch_form<FwdBatch>(p, sh, n, st);
 }
 
-int launch_span_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void* ws, int64_t ws_bytes, hipStream_t st) {
-  const SpanPlan pl = span_plan(sh, spans, n, ws ? ws_bytes : 0);
+namespace {
+int run_spans_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, bool all_remainders, void* ws, int64_t ws_bytes,
+                   hipStream_t st) {
+  const SpanPlan pl = span_plan(sh, spans, n, all_remainders, ws ? ws_bytes : 0);
   FwdSpans p{};
   p.s_q = sh.s_q; p.s_k = sh.s_k; p.h_q = sh.h_q; p.group = sh.h_q / sh.h_kv; p.causal = 1; p.scale = sh.scale;
   p.q_sh = sh.q_stride_h; p.q_ss = sh.q_stride_s; p.kv_sh = sh.kv_stride_h; p.kv_ss = sh.kv_stride_s;
@@ -1165,12 +1156,21 @@ int launch_span_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void
       y.o = x.o; y.lse = x.lse; y.accumulate = x.accumulate; y.o_sh = x.o_sh; y.o_ss = x.o_ss; y.l_sh = x.l_sh;
       y.s_k = x.n_keys; y.off = x.off; y.o_bf16 = x.o_bf16;
     }
-    return launch_spans(p, sh, count, pl.rows, pl.sums, st);
+    return launch_spans(p, sh, count, pl.rows, st);
   });
 }
 
+int64_t span_bytes(const dfa_shape& sh, const dfa_fwd_span* spans, int n, bool all_remainders) {
+  return span_work(sh, spans, n, span_plan(sh, spans, n, all_remainders, MAX_SPAN_BYTES).parts, 1).part_bytes;
+}
+}  // namespace
+
+int launch_span_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void* ws, int64_t ws_bytes, hipStream_t st) {
+  return run_spans_bf16(sh, spans, n, remainders(sh, spans, n), ws, ws_bytes, st);
+}
+
 int64_t span_bf16_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
-  return span_work(sh, spans, n, span_plan(sh, spans, n, MAX_SPAN_BYTES).parts, 1).part_bytes;
+  return span_bytes(sh, spans, n, remainders(sh, spans, n));
 }
 
 }  // namespace dfa

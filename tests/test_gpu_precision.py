@@ -1,0 +1,57 @@
+"""What weights and sums are held in where one call stands in for several pairs (walks, one causal call of all workers): no less than
+in the pairs.  Keys of one chunk are made to outweigh all others (their share of a row's sum is e^-40 and less), so that a row's
+result is that of one pair, whose precision the others cannot hide."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2310_03294_amd import binding as B
+from gpu_util import case, dev, np64
+from oracle import attention as A
+
+pytestmark = pytest.mark.gpu
+
+BF16 = torch.bfloat16
+SCALE = 128 ** -0.5
+
+
+def _inputs(seed, h_q, h_kv, n, c, heavy):
+    """q, k, v of n chunks of c positions; the keys of chunk `heavy` have scores 80 above the others'."""
+    q, k, v, _ = case(seed, h_q, h_kv, n * c, n * c, 128, BF16)
+    q[..., 0], k[..., 0] = 8.0, 0.0
+    k[:, heavy * c:(heavy + 1) * c, 0] = 112.0
+    return q, k, v
+
+
+def _walks(q, k, v, c, walks):
+    h_q, n = q.shape[0], q.shape[1]
+    O, L = torch.empty(h_q, n, 128, device=dev()), torch.empty(h_q, n, device=dev())
+    fwd = B.ForwardChunks(*(t.to(dev()) for t in (q, k, v)), c, SCALE)
+    state = fwd.dest(O, L)
+    fwd.launch([(qc, kc, state, qc, kc != hi) for qc, lo, hi in walks for kc in range(hi, lo - 1, -1)], None)
+    return O, L
+
+
+def _want(q, k, v, h, rows, lo=0):
+    kh = h * k.shape[0] // q.shape[0]
+    return A.rows_fwd(np64(q[h, rows]), rows, np64(k[kh, lo:]), np64(v[kh, lo:]), SCALE, lo)
+
+
+@pytest.mark.parametrize("h_q,h_kv,c,walks", [
+    (64, 16, 300, [(2, 0, 2)]),
+    (40, 8, 300, [(2, 0, 2), (1, 0, 1)]),
+    (64, 64, 1024, [(3, 0, 3)]),
+    (64, 16, 1000, [(3, 0, 3)]),
+    (16, 4, 4096, [(1, 0, 1)]),
+    (64, 16, 1090, [(1, 0, 1), (0, 0, 0)]),
+])
+def test_row_sums_of_a_walks_own_keys_are_those_of_the_diagonal_pair(h_q, h_kv, c, walks):
+    """The diagonal pair alone sums its weights in fp32, as they are: the logsumexp of a few visible keys is off by fp32 rounding of
+    the scores (128 products: 2^-24 times 128 times a score of 80 is 6e-4 at the very worst, as a random walk 5e-5), by up to 1e-3
+    and more with the rounded weights; rows of few keys have the largest errors."""
+    qc = walks[0][0]
+    q, k, v = _inputs(310 + c + h_q, h_q, h_kv, qc + 1, c, qc)
+    O, L = _walks(q, k, v, c, walks)
+    rows = qc * c + np.array([1, 2, 3, 5, 9, 40, 70, c // 2, c - 1])
+    for h in (0, h_q // 2, h_q - 1):
+        assert np.abs(np64(L[h, rows]) - _want(q, k, v, h, rows)[1]).max() <= 6e-5, h
