@@ -955,6 +955,9 @@ int launch(const Args& p, int threads, int smem, hipStream_t st) {
   return last_launch_status();
 }
 
+// Diagonal pairs in the 64-row form, by the rows of a pair and the number of 64-row workgroups of all.
+bool causal_with_remainders(int64_t s_q, int64_t n64) { return n64 <= 256 || (n64 <= 512 && s_q >= 2048); }
+
 // n pairs of one shape (n > 1: in FwdBatch)
 template <class Args>
 int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
@@ -981,7 +984,7 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
     // The diagonal's longest row block sets the time of a call that does not fill the device, so long
     // chunks are split further; the 256-row form needs chunks long enough that its masked half tiles do
     // not count, and whole tiles (ragged chunks, 32 heads x 14197: 1664 us against 1608 with 128 rows).
-    if (n64 <= 256 || (n64 <= 512 && sh.s_q >= 2048)) parts = 4;
+    if (causal_with_remainders(sh.s_q, n64)) parts = 4;
     wide = n256 >= 512 && sh.s_q >= 6144 && sh.s_k % BN == 0;
     // Two parts per tile where the 128-row form's longest walk decides: 16 heads x 2500 59 -> 51 us, x 4096
     // 117 -> 96, 8 x 6000 131 -> 112; not where short walks share the CUs anyway (32 x 1500 45 -> 49).  It is one workgroup
@@ -1031,20 +1034,29 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
                 : launch<Args, full_pair::k_fwd_bf16<false, false, Args>>(p, nt, smem, st);
 }
 
-// Whether the weights of a list of spans enter with their remainders (64-row form): as in the pairs that they stand for, each as a
-// call of its own (launch_form) or, with several walks, as those of all owners in one.  (That form with 128
-// rows was tried: walk of 3 chunks of 8 heads x 1000 38.5 -> 43.4 us, of 5 x 2048 143.5 -> 145, of 9 x 2048 258 -> 245.  Without
-// the remainders the latter two are 15 % faster, and o 200 times as far off.)
-bool remainders(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
-  int64_t owners = 0, longest = 0;
-  for (int i = 0; i < n; ++i) {
-    owners += spans[i].own != 0;
-    longest = std::max<int64_t>(longest, spans[i].n_keys);
+// Of which keys of a list of spans the weights enter with their remainders (64-row form): no fewer than in the pairs that the spans
+// stand for, where launch_form takes each as a call of its own, or, with several owners, the pairs of a time step as one list.
+//   ALL   (The form with 128 rows and remainders was tried: walk of 3 chunks of 8 heads x 1000 38.5 -> 43.4 us, of 5 x 2048 143.5 ->
+//         145, of 9 x 2048 258 -> 245.  Without the remainders the latter two are 15 % faster, and o 200 times as far off.)
+//   OWN   of the chunks' own: those go out as diagonal pairs, the keys before them as a walk that continues from there
+//   NONE
+enum class Remainders { ALL, OWN, NONE };
+
+int64_t last_launch(int64_t pairs) { return (pairs - 1) % MAX_PAIRS + 1; }      // pairs of a list's last launch
+
+Remainders remainders(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
+  int64_t owners = 0, full = MAX_PAIRS;      // full: pairs of the smallest list of full pairs
+  for (int i = 0; i < n; ++i) owners += spans[i].own != 0;
+  if (owners < 2 || owners < n) full = 1;
+  for (int i = 0; i < n && full > 1; ++i) {
+    const int64_t step = (spans[i].n_keys - 1) / sh.s_q;      // the last one that this walk has a pair in
+    int64_t list = 0;
+    for (int j = 0; j < n; ++j) list += spans[j].n_keys > step * sh.s_q;
+    if (step > 0) full = std::min(full, last_launch(list));
   }
-  const int64_t n64 = (static_cast<int64_t>(sh.s_q) + 63) / 64 * sh.h_q * std::max<int64_t>(owners, 1);
-  // (up to 512 workgroups: diagonals of 2048 rows and more, and the one full pair of two workers)
-  const bool two_rounds = longest <= sh.s_q ? sh.s_q >= 2048 : longest <= 2 * static_cast<int64_t>(sh.s_q);
-  return n64 <= 256 || (n64 <= 512 && two_rounds);
+  const int64_t n64 = (static_cast<int64_t>(sh.s_q) + 63) / 64 * sh.h_q;
+  if (n64 * full <= 256) return Remainders::ALL;
+  return owners && causal_with_remainders(sh.s_q, n64 * last_launch(owners)) ? Remainders::OWN : Remainders::NONE;
 }
 
 // The spans of a launch.  Which form, and in how many parts the keys of a span are cut (the parts are merged afterwards):
@@ -1086,6 +1098,27 @@ int launch_spans(FwdSpans& p, const dfa_shape& sh, int n, int rows, hipStream_t 
   return whole ? launch<FwdSpans, full_pair::k_fwd_bf16<false, true, FwdSpans>>(p, nt, smem, st)
                : launch<FwdSpans, full_pair::k_fwd_bf16<true, true, FwdSpans>>(p, nt, smem, st);
 }
+
+// Spans without the keys of the chunks' own, which are diagonal pairs, of MAX_PAIRS spans at a time.
+struct WithoutOwn {
+  dfa_fwd_pair pair[MAX_PAIRS];
+  dfa_fwd_span rest[MAX_PAIRS];
+  int pairs = 0, spans = 0;
+  WithoutOwn(const dfa_shape& sh, const dfa_fwd_span* spans_, int n) {
+    for (int i = 0; i < n; ++i) {
+      dfa_fwd_span x = spans_[i];
+      if (x.own) {
+        x.n_keys -= sh.s_q;
+        const int64_t own = x.n_keys * sh.kv_stride_s * 2;
+        pair[pairs++] = {x.q, static_cast<const char*>(x.k) + own, static_cast<const char*>(x.v) + own, x.o, x.lse, x.o_stride_h,
+                         x.o_stride_s, x.lse_stride_h, x.accumulate, 0};
+        x.own = 0;
+        x.accumulate = 1;
+      }
+      if (x.n_keys > 0) rest[spans++] = x;
+    }
+  }
+};
 
 }  // namespace
 
@@ -1166,11 +1199,28 @@ int64_t span_bytes(const dfa_shape& sh, const dfa_fwd_span* spans, int n, bool a
 }  // namespace
 
 int launch_span_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void* ws, int64_t ws_bytes, hipStream_t st) {
-  return run_spans_bf16(sh, spans, n, remainders(sh, spans, n), ws, ws_bytes, st);
+  const Remainders rem = remainders(sh, spans, n);
+  if (rem != Remainders::OWN) return run_spans_bf16(sh, spans, n, rem == Remainders::ALL, ws, ws_bytes, st);
+  dfa_shape own = sh;
+  own.s_k = sh.s_q; own.causal = 1;
+  for (int i = 0; i < n; i += MAX_PAIRS) {
+    const WithoutOwn x(sh, spans + i, std::min(MAX_PAIRS, n - i));
+    int rc = x.pairs ? launch_fwd_bf16(own, x.pair, x.pairs, st) : DFA_OK;
+    if (rc == DFA_OK && x.spans) rc = run_spans_bf16(sh, x.rest, x.spans, false, ws, ws_bytes, st);
+    if (rc) return rc;
+  }
+  return DFA_OK;
 }
 
 int64_t span_bf16_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
-  return span_bytes(sh, spans, n, remainders(sh, spans, n));
+  const Remainders rem = remainders(sh, spans, n);
+  if (rem != Remainders::OWN) return span_bytes(sh, spans, n, rem == Remainders::ALL);
+  int64_t most = 0;
+  for (int i = 0; i < n; i += MAX_PAIRS) {
+    const WithoutOwn x(sh, spans + i, std::min(MAX_PAIRS, n - i));
+    if (x.spans) most = std::max(most, span_bytes(sh, x.rest, x.spans, false));
+  }
+  return most;
 }
 
 }  // namespace dfa

@@ -13,6 +13,9 @@ pytestmark = pytest.mark.gpu
 
 BF16 = torch.bfloat16
 SCALE = 128 ** -0.5
+# of o where the weights have 16 bits: 2^-17 of a weight, and twice that again for scores, exponentials and sums in fp32 and the merge
+# of parts (rounded weights: 1e-3)
+REMAINDERS = 3 * 2 ** -17
 
 
 def _inputs(seed, h_q, h_kv, n, c, heavy):
@@ -55,3 +58,21 @@ def test_row_sums_of_a_walks_own_keys_are_those_of_the_diagonal_pair(h_q, h_kv, 
     rows = qc * c + np.array([1, 2, 3, 5, 9, 40, 70, c // 2, c - 1])
     for h in (0, h_q // 2, h_q - 1):
         assert np.abs(np64(L[h, rows]) - _want(q, k, v, h, rows)[1]).max() <= 6e-5, h
+
+
+@pytest.mark.parametrize("h_q,h_kv,c,walks,heavy", [
+    (8, 8, 2049, [(3, 0, 3)], 3),                  # 264 workgroups of 64 rows: those of the diagonal pair
+    (16, 4, 2048, [(4, 2, 4)], 4),
+    (2, 1, 4096, [(i, max(0, i - 1), i) for i in range(4)], 2),
+    (32, 8, 100, [(i, max(0, i - 5), i) for i in range(8)], 2),      # the last time step's three pairs
+])
+def test_walks_keep_the_remainders_that_one_of_their_pairs_has(h_q, h_kv, c, walks, heavy):
+    """Relative error of o where a chunk of keys outweighs the others that has weights of 16 bits as a pair of its own or of its
+    time step."""
+    qc, lo, _ = walks[-1] if len(walks) == 8 else walks[heavy if len(walks) > 1 else 0]
+    q, k, v = _inputs(330 + c + h_q, h_q, h_kv, walks[-1][0] + 1, c, heavy)
+    O, _ = _walks(q, k, v, c, walks)
+    rows = np.arange(qc * c, (qc + 1) * c)
+    for h in (0, h_q - 1):
+        want = _want(q, k, v, h, rows, lo * c)[0]
+        assert np.linalg.norm(np64(O[h, rows]) - want) <= REMAINDERS * np.linalg.norm(want), h
