@@ -123,6 +123,8 @@ int dfa_chunk_fwd_batch(const dfa_shape* sh, const dfa_fwd_pair* pairs, int32_t 
  * causal are not looked at).  own != 0: the last s_q of them (n_keys >= s_q) are the query chunk's own rows, key j is visible to
  * query i iff j <= i + n_keys - s_q; own == 0: every key is visible.  accumulate, o, lse and the rules for lists as
  * for dfa_chunk_fwd_batch; the result is that of the span's pairs one after the other, up to rounding.
+ * One span of own rows alone (n_keys == s_q) is taken as a sequence of several chunks, whose pairs it stands for.
+ * Weights and sums are held in no less than in those pairs, as calls of their own or, with several owners, as the lists of time steps.
  * `workspace`: as for dfa_chunk_bwd_batch; dfa_span_fwd_workspace() bytes (at most 128 MiB, 0 where it needs none) let it
  * divide the keys of few query rows among more workgroups.
  */
@@ -137,6 +139,22 @@ typedef struct {
 int dfa_span_fwd(const dfa_shape* sh, const dfa_fwd_span* spans, int32_t n_spans, void* workspace,
                  int64_t workspace_bytes, void* stream);
 int64_t dfa_span_fwd_workspace(const dfa_shape* sh, const dfa_fwd_span* spans, int32_t n_spans);
+
+/*
+ * dfa_chunk_fwd_form, dfa_span_fwd_form - which kernel form the call of these arguments takes (of a list longer than a launch: its last
+ * launch).  Pure host functions, for tests and for programs that have to know what a call computes in: a bf16 forward in
+ * workgroups of 64 query rows multiplies V by weights of 16 bits (the rounded weight and its remainder), in larger ones by
+ * weights rounded to bf16.  Strides are not looked at.
+ */
+typedef struct {
+  int32_t rows;     /* query rows of a workgroup */
+  int32_t parts;    /* parts that a workgroup divides every tile of keys in */
+  int32_t cuts;     /* parts that the keys of a span are cut in at most */
+  int32_t reserved; /* 0 */
+} dfa_form;
+
+int dfa_chunk_fwd_form(const dfa_shape* sh, int32_t n_pairs, dfa_form* form);
+int dfa_span_fwd_form(const dfa_shape* sh, const dfa_fwd_span* spans, int32_t n_spans, int64_t workspace_bytes, dfa_form* form);
 
 /*
  * dfa_merge - the rescale(o, s, o', s') update of the balanced schedule (Section 3.2,

@@ -64,6 +64,10 @@ class DfaFwdSpan(ctypes.Structure):
         (n, ctypes.c_int32) for n in ("n_keys", "own", "accumulate", "reserved")]
 
 
+class DfaForm(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("rows", "parts", "cuts", "reserved")]
+
+
 class DfaBwdPair(ctypes.Structure):
     _fields_ = [(n, ctypes.c_void_p) for n in ("q", "k", "v", "lse", "delta", "dO", "dq", "dk", "dv")] + [
         ("accumulate_dq", ctypes.c_int32), ("accumulate_dkv", ctypes.c_int32)]
@@ -76,7 +80,8 @@ class DfaStep(ctypes.Structure):
 
 Step = collections.namedtuple("Step", "t kind q_chunk kv_chunk send_to recv_from")
 
-EXPORTS = ("dfa_chunk_fwd", "dfa_chunk_fwd_acc", "dfa_chunk_fwd_batch", "dfa_span_fwd", "dfa_span_fwd_workspace", "dfa_merge", "dfa_merge_batch", "dfa_delta",
+EXPORTS = ("dfa_chunk_fwd", "dfa_chunk_fwd_acc", "dfa_chunk_fwd_batch", "dfa_span_fwd", "dfa_span_fwd_workspace",
+           "dfa_chunk_fwd_form", "dfa_span_fwd_form", "dfa_merge", "dfa_merge_batch", "dfa_delta",
            "dfa_chunk_bwd",
            "dfa_chunk_bwd_batch", "dfa_chunk_bwd_workspace", "dfa_span_bwd", "dfa_span_bwd_workspace", "dfa_schedule", "dfa_schedule_mode", "dfa_schedule_window", "dfa_mfma_probe", "dfa_mfma_probe_data", "dfa_status_str",
            "dfa_version")
@@ -106,6 +111,8 @@ def load_library():
     lib.dfa_chunk_fwd_batch.argtypes = [shp, ctypes.POINTER(DfaFwdPair), i32, vp]
     lib.dfa_span_fwd.argtypes = [shp, ctypes.POINTER(DfaFwdSpan), i32, vp, i64, vp]
     lib.dfa_span_fwd_workspace.argtypes = [shp, ctypes.POINTER(DfaFwdSpan), i32]
+    lib.dfa_chunk_fwd_form.argtypes = [shp, i32, ctypes.POINTER(DfaForm)]
+    lib.dfa_span_fwd_form.argtypes = [shp, ctypes.POINTER(DfaFwdSpan), i32, i64, ctypes.POINTER(DfaForm)]
     lib.dfa_merge_batch.argtypes = [ctypes.POINTER(DfaMergeDesc), ctypes.POINTER(DfaMergePair), i32, vp]
     lib.dfa_chunk_bwd_batch.argtypes = [shp, ctypes.POINTER(DfaBwdPair), i32, vp, i64, vp]
     lib.dfa_schedule.argtypes = [i32, i32, ctypes.POINTER(DfaStep), i32]
@@ -301,6 +308,21 @@ def dfa_chunk_bwd(q, k, v, lse, delta, dO, dq, dk, dv, causal, scale, accumulate
     return dq, dk, dv
 
 
+def forward_form(h_q, h_kv, rows, d, dtype, causal, n_pairs):
+    """The kernel form (DfaForm) of n_pairs pairs of chunks of `rows` positions as one list."""
+    form, sh = DfaForm(), DfaShape(h_q, h_kv, rows, rows, d, dtype, DFA_F32, bool(causal), 1.0)
+    _check(load_library().dfa_chunk_fwd_form(ctypes.byref(sh), n_pairs, ctypes.byref(form)), "dfa_chunk_fwd_form")
+    return form
+
+
+def sequence_form(h_q, h_kv, n, d, dtype):
+    """That of a sequence of n positions as one causal call (ForwardChunks.launch, causal None)."""
+    form, span = DfaForm(), DfaFwdSpan(n_keys=n, own=1)
+    sh = DfaShape(h_q, h_kv, n, n, d, dtype, DFA_F32, 0, 1.0, 0, n * d, d, n * d, d)
+    _check(load_library().dfa_span_fwd_form(ctypes.byref(sh), ctypes.byref(span), 1, 0, ctypes.byref(form)), "dfa_span_fwd_form")
+    return form
+
+
 class _Chunks:
     """Addresses of the chunks (`rows` sequence positions each) of a [heads, seq, ...] tensor.  Chunks without rows (a
     sequence shorter than its number of chunks) have none, as the empty slices of a tensor."""
@@ -351,7 +373,7 @@ class ForwardChunks:
         `chunk` of dest; accumulate: continues from the state there.  No output may overlap another pair's.
         causal None: a chunk's pair with itself is causal, no other is; pairs next to each other in the list with one
         destination, each after the first accumulating, are one walk over their key/value chunks, which
-        have to be consecutive (dfa_span_fwd)."""
+        have to be consecutive (dfa_span_fwd); one causal pair alone is a sequence that stands for the pairs of several chunks."""
         if not pairs:
             return
         sh = self.sh

@@ -131,6 +131,28 @@ extern "C" int64_t dfa_span_fwd_workspace(const dfa_shape* sh, const dfa_fwd_spa
   return sh->dtype == DFA_F32 ? dfa::span_f32_workspace(*sh, spans, n_spans) : dfa::span_bf16_workspace(*sh, spans, n_spans);
 }
 
+extern "C" int dfa_chunk_fwd_form(const dfa_shape* sh, int32_t n_pairs, dfa_form* form) {
+  const int rc = check_common(sh);
+  if (rc != DFA_OK) return rc;
+  if (!form) return DFA_ERR_NULL;
+  if (n_pairs < 1) return DFA_ERR_ARG;
+  if (sh->s_q == 0 || sh->s_k == 0) return DFA_ERR_SHAPE;
+  *form = sh->dtype == DFA_F32 ? dfa::fwd_f32_form(*sh, n_pairs) : dfa::fwd_bf16_form(*sh, n_pairs);
+  return DFA_OK;
+}
+
+extern "C" int dfa_span_fwd_form(const dfa_shape* sh, const dfa_fwd_span* spans, int32_t n_spans, int64_t workspace_bytes,
+                                 dfa_form* form) {
+  if (!sh || !form) return DFA_ERR_NULL;
+  const int rc = check_spans(sh, spans, n_spans);
+  if (rc != DFA_OK) return rc;
+  if (n_spans < 1 || workspace_bytes < 0) return DFA_ERR_ARG;
+  if (sh->s_q == 0) return DFA_ERR_SHAPE;
+  *form = sh->dtype == DFA_F32 ? dfa::span_f32_form(*sh, spans, n_spans, workspace_bytes)
+                               : dfa::span_bf16_form(*sh, spans, n_spans, workspace_bytes);
+  return DFA_OK;
+}
+
 namespace {
 int chunk_fwd(const dfa_shape* sh, const void* q, const void* k, const void* v,
               void* o, float* lse, int accumulate, void* stream) {

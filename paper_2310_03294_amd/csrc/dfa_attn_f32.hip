@@ -715,16 +715,20 @@ int fwd(Args& p, hipStream_t st) {
   return launch<Args, k_fwd_f32<D, NS, Args>>(p, xcd_blocks(p.map_q), tiles > comb ? tiles : comb, st);
 }
 
-template <class Args>
-int fwd_form(Args& p, const dfa_shape& sh, hipStream_t st) {
+int fwd_parts(const dfa_shape& sh, int pairs) {
   // Parts per tile.  A workgroup with more parts is done sooner, but stages every tile for fewer rows and
   // runs fewer wavefronts per SIMD.  us per full pair, d = 128, with 1 / 2 / 4 parts:
   //   8 heads x 256 rows 47 / 29 / 22, 32 x 256 49 / 31 / 28, 8 x 1024 174 / 103 / 71 (<= 256 workgroups of
   //   4 parts: one round),  32 x 1024 190 / 183 / 271,  32 x 4096 2361 / 2501 / 3920 (116 TFLOP/s with 1);
   //   causal, 32 x 4096, 2 parts: 1402 (2043 with every eighth row block on the same XCD).
   // The vector-FMA kernel this one replaced took 610 us at 8 x 1024.
-  const int64_t wg2 = blocks_of(sh.s_q, 64) * sh.h_q * p.pairs, wg4 = blocks_of(sh.s_q, 32) * sh.h_q * p.pairs;
-  const int parts = wg4 <= 256 ? 4 : wg2 <= 512 || sh.causal ? 2 : 1;
+  const int64_t wg2 = blocks_of(sh.s_q, 64) * sh.h_q * pairs, wg4 = blocks_of(sh.s_q, 32) * sh.h_q * pairs;
+  return wg4 <= 256 ? 4 : wg2 <= 512 || sh.causal ? 2 : 1;
+}
+
+template <class Args>
+int fwd_form(Args& p, const dfa_shape& sh, hipStream_t st) {
+  const int parts = fwd_parts(sh, p.pairs);
   if (sh.d == 128) return parts == 4 ? fwd<128, 4, Args>(p, st) : parts == 2 ? fwd<128, 2, Args>(p, st) : fwd<128, 1, Args>(p, st);
   return parts == 4 ? fwd<64, 4, Args>(p, st) : parts == 2 ? fwd<64, 2, Args>(p, st) : fwd<64, 1, Args>(p, st);
 }
@@ -929,6 +933,16 @@ int launch_span_f32(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void*
 
 int64_t span_f32_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
   return span_work(sh, spans, n, span_plan(sh, spans, n, MAX_SPAN_BYTES).parts, 1).part_bytes;
+}
+
+dfa_form fwd_f32_form(const dfa_shape& sh, int n) {
+  const int parts = fwd_parts(sh, (n - 1) % MAX_PAIRS + 1);
+  return {128 / parts, parts, 1, 0};
+}
+
+dfa_form span_f32_form(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_t ws_bytes) {
+  const SpanPlan pl = span_plan(sh, spans, n, ws_bytes);
+  return {128 / pl.ns, pl.ns, pl.parts, 0};
 }
 
 }  // namespace dfa

@@ -958,14 +958,9 @@ int launch(const Args& p, int threads, int smem, hipStream_t st) {
 // Diagonal pairs in the 64-row form, by the rows of a pair and the number of 64-row workgroups of all.
 bool causal_with_remainders(int64_t s_q, int64_t n64) { return n64 <= 256 || (n64 <= 512 && s_q >= 2048); }
 
-// n pairs of one shape (n > 1: in FwdBatch)
-template <class Args>
-int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
-  auto grid = [&](int rows) {
-    p.ntq = (sh.s_q + rows - 1) / rows;
-    p.map = xcd_map(static_cast<int64_t>(p.ntq) * sh.h_q * n, sh.causal, static_cast<int64_t>(sh.h_q) * n);
-    if constexpr (std::is_same_v<Args, FwdBatch>) p.per_pair = p.ntq * sh.h_q;
-  };
+// The form of n pairs of one shape.  sequence: a causal call that stands for the pairs of several workers' chunks.
+struct FwdForm { int rows, parts; };      // query rows of a workgroup, parts that it divides the keys of a tile in
+FwdForm form_of(const dfa_shape& sh, int n, bool sequence) {
   // Which form.  us per call on one box, d = 128, 256-row / 128-row / 64-row NS = 2 / 64-row NS = 4 workgroups:
   //   full pairs    8 heads x 256 rows 13.5 / 9.6 / 8.6 / 9.5    x 1024 30.5 / 24.2 / 22 / 18.4
   //                 x 2048 52.5 / 42.7 / 40 / 34.2 (256 64-row workgroups)   x 4096 97 / 82 / 100 / 105
@@ -985,6 +980,9 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
     // chunks are split further; the 256-row form needs chunks long enough that its masked half tiles do
     // not count, and whole tiles (ragged chunks, 32 heads x 14197: 1664 us against 1608 with 128 rows).
     if (causal_with_remainders(sh.s_q, n64)) parts = 4;
+    // A sequence of several chunks, whose shortest lists of pairs have half as many workgroups at least.  us with 2 / 4 parts: 32
+    // heads x 600 20.2 / 23.1, x 1024 32.7 / 35.4, 24 x 800 21.4 / 22.2, 16 x 1200 28.4 / 23.0, x 1400 31.9 / 26.3, x 2000 56 / 43.
+    else if (sequence && n64 <= 512) parts = sh.s_q <= 1024 ? 2 : 4;
     wide = n256 >= 512 && sh.s_q >= 6144 && sh.s_k % BN == 0;
     // Two parts per tile where the 128-row form's longest walk decides: 16 heads x 2500 59 -> 51 us, x 4096
     // 117 -> 96, 8 x 6000 131 -> 112; not where short walks share the CUs anyway (32 x 1500 45 -> 49).  It is one workgroup
@@ -1007,26 +1005,33 @@ int launch_form(Args& p, const dfa_shape& sh, int n, hipStream_t st) {
     wide = n128 > 256 && !(n256 > 256 && n256 < 768 && last_round > 0 && last_round <= 128);
     two = n128 <= 256 || (n256 < 512 && sh.s_k > 2048);
   }
-  if (parts && sh.s_k <= 384) parts = 2;      // three 128-key tiles at most: the smaller tiles start sooner
-  if (n128 > (1 << 30) && (sh.causal || n > 1)) return DFA_ERR_SHAPE;
-  if (parts) {
-    grid(64);
-    if (parts == 2) return sh.causal ? launch<Args, split::k_fwd_bf16<2, 2, true, Args>>(p, 256, split::kSmem<2>, st)
+  if (parts) return {64, sh.s_k <= 384 ? 2 : parts};      // (three 128-key tiles at most: the smaller tiles start sooner)
+  return wide ? FwdForm{256, 1} : FwdForm{128, two ? 2 : 1};
+}
+
+// n pairs of one shape (n > 1: in FwdBatch)
+template <class Args>
+int launch_form(Args& p, const dfa_shape& sh, int n, bool sequence, hipStream_t st) {
+  const FwdForm form = form_of(sh, n, sequence);
+  const int64_t heads = static_cast<int64_t>(sh.h_q) * n;
+  if ((static_cast<int64_t>(sh.s_q) + 127) / 128 * heads > (1 << 30) && (sh.causal || n > 1)) return DFA_ERR_SHAPE;
+  p.ntq = (sh.s_q + form.rows - 1) / form.rows;
+  p.map = xcd_map(p.ntq * heads, sh.causal, heads);
+  if constexpr (std::is_same_v<Args, FwdBatch>) p.per_pair = p.ntq * sh.h_q;
+  if (form.rows == 64) {
+    if (form.parts == 2) return sh.causal ? launch<Args, split::k_fwd_bf16<2, 2, true, Args>>(p, 256, split::kSmem<2>, st)
                                      : launch<Args, split::k_fwd_bf16<2, 2, false, Args>>(p, 256, split::kSmem<2>, st);
     return sh.causal ? launch<Args, split::k_fwd_bf16<2, 4, true, Args>>(p, 512, split::kSmem<4>, st)
                      : launch<Args, split::k_fwd_bf16<2, 4, false, Args>>(p, 512, split::kSmem<4>, st);
   }
-  if (!wide && two) {
-    grid(128);
+  if (form.rows == 128 && form.parts == 2) {
     return sh.causal ? launch<Args, split::k_fwd_bf16<4, 2, true, Args>>(p, 512, split::kSmem<2>, st)
                      : launch<Args, split::k_fwd_bf16<4, 2, false, Args>>(p, 512, split::kSmem<2>, st);
   }
-  if (!wide) {
-    grid(BM);
+  if (form.rows == 128) {
     return sh.causal ? launch<Args, k_fwd_bf16<false, Args>>(p, NTHREADS, 4 * TILE_BYTES, st)
                      : launch<Args, k_fwd_bf16<true, Args>>(p, NTHREADS, 4 * TILE_BYTES, st);
   }
-  grid(full_pair::BMW);
   constexpr int nt = full_pair::NT, smem = full_pair::SMEM_BYTES;
   const bool ragged = sh.s_k % BN != 0;
   if (sh.causal) return launch<Args, full_pair::k_fwd_bf16<false, true, Args>>(p, nt, smem, st);
@@ -1137,15 +1142,16 @@ int64_t rows_of_whole_rounds(const dfa_shape& sh, int n) {
   return rows > 0 && rest > 0 && (rest + 127) / 128 * heads <= 256 ? rows : 0;
 }
 
-int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st) {
+namespace {
+int launch_pairs(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, bool sequence, hipStream_t st) {
   for (; n > MAX_PAIRS; pairs += MAX_PAIRS, n -= MAX_PAIRS) {
-    const int rc = launch_fwd_bf16(sh, pairs, MAX_PAIRS, st);
+    const int rc = launch_pairs(sh, pairs, MAX_PAIRS, sequence, st);
     if (rc) return rc;
   }
   if (const int64_t rows = rows_of_whole_rounds(sh, n)) {
     dfa_shape part = sh;
     part.s_q = static_cast<int32_t>(rows);
-    int rc = launch_fwd_bf16(part, pairs, n, st);
+    int rc = launch_pairs(part, pairs, n, sequence, st);
     if (rc) return rc;
     part.s_q = static_cast<int32_t>(sh.s_q - rows);
     dfa_fwd_pair rest[MAX_PAIRS];
@@ -1155,7 +1161,7 @@ int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipSt
       rest[i].o = static_cast<char*>(pairs[i].o) + rows * pairs[i].o_stride_s * (sh.o_dtype == DFA_BF16 ? 2 : 4);
       rest[i].lse = pairs[i].lse + rows;
     }
-    return launch_fwd_bf16(part, rest, n, st);
+    return launch_pairs(part, rest, n, sequence, st);
   }
   auto operand = [](const void* x) { return static_cast<const __bf16*>(x); };
   FwdBatch p{};
@@ -1165,16 +1171,15 @@ int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipSt
   p.s_q = sh.s_q; p.s_k = sh.s_k; p.h_q = sh.h_q; p.group = sh.h_q / sh.h_kv; p.causal = sh.causal;
   p.o_bf16 = sh.o_dtype == DFA_BF16; p.scale = sh.scale;
   p.q_sh = sh.q_stride_h; p.q_ss = sh.q_stride_s; p.kv_sh = sh.kv_stride_h; p.kv_ss = sh.kv_stride_s;
-  if (n == 1) return launch_form<FwdParams>(p, sh, 1, st);
+  if (n == 1) return launch_form<FwdParams>(p, sh, 1, sequence, st);
   for (int i = 0; i < n; ++i) {
     const dfa_fwd_pair& y = pairs[i];
     p.pair[i] = Pair{operand(y.q), operand(y.k), operand(y.v), y.o, y.lse, y.accumulate, y.o_stride_h, y.o_stride_s,
                      y.lse_stride_h};
   }
-  return launch_form<FwdBatch>(p, sh, n, st);
+  return launch_form<FwdBatch>(p, sh, n, sequence, st);
 }
 
-namespace {
 int run_spans_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, bool all_remainders, void* ws, int64_t ws_bytes,
                    hipStream_t st) {
   const SpanPlan pl = span_plan(sh, spans, n, all_remainders, ws ? ws_bytes : 0);
@@ -1196,16 +1201,25 @@ int run_spans_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, bool a
 int64_t span_bytes(const dfa_shape& sh, const dfa_fwd_span* spans, int n, bool all_remainders) {
   return span_work(sh, spans, n, span_plan(sh, spans, n, all_remainders, MAX_SPAN_BYTES).parts, 1).part_bytes;
 }
+
+dfa_shape own_pair(dfa_shape sh) {
+  sh.s_k = sh.s_q; sh.causal = 1;
+  return sh;
+}
 }  // namespace
 
+int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st) {
+  return launch_pairs(sh, pairs, n, false, st);
+}
+
 int launch_span_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void* ws, int64_t ws_bytes, hipStream_t st) {
+  const dfa_shape own = own_pair(sh);
+  if (is_sequence(sh, spans, n)) return launch_pairs(own, WithoutOwn(sh, spans, 1).pair, 1, true, st);
   const Remainders rem = remainders(sh, spans, n);
   if (rem != Remainders::OWN) return run_spans_bf16(sh, spans, n, rem == Remainders::ALL, ws, ws_bytes, st);
-  dfa_shape own = sh;
-  own.s_k = sh.s_q; own.causal = 1;
   for (int i = 0; i < n; i += MAX_PAIRS) {
     const WithoutOwn x(sh, spans + i, std::min(MAX_PAIRS, n - i));
-    int rc = x.pairs ? launch_fwd_bf16(own, x.pair, x.pairs, st) : DFA_OK;
+    int rc = x.pairs ? launch_pairs(own, x.pair, x.pairs, false, st) : DFA_OK;
     if (rc == DFA_OK && x.spans) rc = run_spans_bf16(sh, x.rest, x.spans, false, ws, ws_bytes, st);
     if (rc) return rc;
   }
@@ -1213,6 +1227,7 @@ int launch_span_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void
 }
 
 int64_t span_bf16_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
+  if (is_sequence(sh, spans, n)) return 0;
   const Remainders rem = remainders(sh, spans, n);
   if (rem != Remainders::OWN) return span_bytes(sh, spans, n, rem == Remainders::ALL);
   int64_t most = 0;
@@ -1221,6 +1236,28 @@ int64_t span_bf16_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int 
     if (x.spans) most = std::max(most, span_bytes(sh, x.rest, x.spans, false));
   }
   return most;
+}
+
+dfa_form fwd_bf16_form(const dfa_shape& sh, int n) {
+  n = static_cast<int>(last_launch(n));
+  if (rows_of_whole_rounds(sh, n)) return {256, 1, 1, 0};
+  const FwdForm f = form_of(sh, n, false);
+  return {f.rows, f.parts, 1, 0};
+}
+
+dfa_form span_bf16_form(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_t ws_bytes) {
+  if (is_sequence(sh, spans, n)) {
+    const FwdForm f = form_of(own_pair(sh), 1, true);
+    return {f.rows, f.parts, 1, 0};
+  }
+  const Remainders rem = remainders(sh, spans, n);
+  auto of = [&](const dfa_fwd_span* x, int count) {
+    const SpanPlan pl = span_plan(sh, x, count, rem == Remainders::ALL, ws_bytes);
+    return dfa_form{pl.rows, 256 / pl.rows, pl.parts, 0};
+  };
+  if (rem != Remainders::OWN) return of(spans, n);
+  const WithoutOwn x(sh, spans, std::min(MAX_PAIRS, n));
+  return x.spans ? of(x.rest, x.spans) : fwd_bf16_form(own_pair(sh), x.pairs);
 }
 
 }  // namespace dfa

@@ -32,7 +32,7 @@ int64_t bwd_f32_workspace(const dfa_shape& sh, int n, bool dq, bool dk);
 
 int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st);
 
-// Spans.  Their keys are cut in parts where that pays; the parts' results take ws (span_part_bytes() each) and are merged.
+// Spans.  Their keys are cut in parts where that pays; the parts' results take ws (part_floats() each) and are merged.
 int launch_span_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void* ws, int64_t ws_bytes, hipStream_t st);
 int launch_span_f32(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void* ws, int64_t ws_bytes, hipStream_t st);
 int64_t span_bf16_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int n);
@@ -40,6 +40,12 @@ int64_t span_f32_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int n
 int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void* ws, int64_t ws_bytes,
                     hipStream_t st);
 int64_t bwd_bf16_workspace(const dfa_shape& sh, int n, bool dq, bool dk);
+
+// The forms that these calls take (dfa_form).
+dfa_form fwd_bf16_form(const dfa_shape& sh, int n);
+dfa_form fwd_f32_form(const dfa_shape& sh, int n);
+dfa_form span_bf16_form(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_t ws_bytes);
+dfa_form span_f32_form(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_t ws_bytes);
 
 // Which item a workgroup takes.  Workgroup ids go round-robin over the 8 XCDs, and in order: a workgroup waits for
 // its XCD even if another is free.  Every XCD gets a contiguous range of (head, tile) items, so that the tiles of a

@@ -19,6 +19,11 @@ struct SpanPart {
   int n_keys, off, accumulate, o_bf16;
 };
 
+// One chunk and its own keys alone: a sequence, which stands for the pairs of several workers' chunks.
+inline bool is_sequence(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
+  return n == 1 && spans[0].own && spans[0].n_keys == sh.s_q;
+}
+
 // Keys of a span before the query chunk's own.
 inline int64_t keys_before(const dfa_shape& sh, const dfa_fwd_span& x) { return x.own ? x.n_keys - sh.s_q : x.n_keys; }
 // Parts that a span is cut in, at most `parts`: of 128 keys at least, and none begins among the chunk's own keys (a workgroup

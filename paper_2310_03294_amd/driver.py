@@ -250,6 +250,29 @@ def _whole_triangle(P, mode):
             == {(q, k) for q in range(P) for k in range(q + 1)})
 
 
+@functools.lru_cache(maxsize=64, typed=True)
+def _lists_with_remainders(h_q, h_kv, c, P, mode):
+    """Whether the bf16 forward's lists of pairs, time step by time step, multiply V by weights of 16 bits (64-row form): the set of
+    what the lists say.  (They get shorter with the steps: to P / 2 pairs, in the ring schedule to one.)"""
+    lists = {(kind == B.DFA_STEP_DIAG, n) for steps in zip(*(B.dfa_schedule(P, w, mode) for w in range(P)))
+             for kind, n in collections.Counter(min(st.kind, B.DFA_STEP_OWN) for st in steps if st.kind != B.DFA_STEP_IDLE).items()}
+    return {B.forward_form(h_q, h_kv, c, 128, B.DFA_BF16, causal, n).rows == 64 for causal, n in lists}
+
+
+def _how_at_once(Q, K, bufs: Buffers, P, mode):
+    """(as one causal call, as walks): how the forward of all workers goes out.  In bf16 neither may hold less of the weights than the
+    lists of pairs do; walks take all in the form of the shortest list, which is the slower one for the others of
+    long chunks (ring, us, steps / walks: 32 over 8 heads x 8 x 512 292 / 288, 16 over 4 x 8 x 700 292 / 263, 8 over 2 x 16 x
+    1000 879 / 968)."""
+    c = bufs.c
+    if Q.dtype != torch.bfloat16 or c < 1:
+        return False, True
+    lists = _lists_with_remainders(Q.shape[0], K.shape[0], c, P, mode)
+    one = (_whole_triangle(P, mode) and _fits_a_call(P * c, Q, K, bufs.O)
+           and (True not in lists or B.sequence_form(Q.shape[0], K.shape[0], P * c, 128, B.DFA_BF16).rows == 64))
+    return one, c <= 768 or len(lists) == 1
+
+
 def backward_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced"):
     """The backward of all P workers' pairs on one device, from the merged O and L and the D of every chunk.
     Where the pairs are those of every chunk with itself and all earlier ones, they are one causal call over the P
@@ -310,19 +333,19 @@ def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backw
     fused: OWN pairs continue from the owner's state instead of partial + merge, and pairs that do not wait for each other go
     out as one launch (a pair of small chunks alone leaves most of one device idle): all of the owners' as one walk
     per owner, or, in bf16 and where the pairs are those of every chunk with itself and all earlier ones, all pairs as one
-    causal call, which has no partials to write, read and merge (us, forward, walks / one call: 32 over 8 heads x 8 x 1024
+    causal call (where that is as precise: _how_at_once), which has no partials to write, read and merge (us, forward, walks / one call: 32 over 8 heads x 8 x 1024
     608 / 503, 8 over 2 x 8 x 2048 596 / 479, 32 x 8 x 300 141 / 72, 8 x 4 x 512 38 / 32; not in fp32, where the walks cut
     the keys of the last rows in parts: 8 over 2 heads x 4 x 1024 385 / 478, d = 64, 2 over 1 x 3 x 700 43 / 74);
     otherwise time step by time step, pair by pair."""
     c = bufs.c
     scheds = [B.dfa_schedule(P, w, mode) for w in range(P)]
     nsteps = len(scheds[0])
-    one_call = fused and Q.dtype == torch.bfloat16 and _whole_triangle(P, mode) and _fits_a_call(P * c, Q, K, bufs.O)
+    one_call, walks = _how_at_once(Q, K, bufs, P, mode) if fused else (False, False)
     fwd = B.ForwardChunks(Q, K, V, P * c if one_call else c, scale)
     state = fwd.dest(bufs.O, bufs.L)
-    at_once = fused and (one_call or _fits_a_call(nsteps * c, K))
+    at_once = one_call or (walks and _fits_a_call(nsteps * c, K))
     if one_call:
-        fwd.launch([(0, 0, state, 0, False)], True)
+        fwd.launch([(0, 0, state, 0, False)], True if P == 1 else None)
     elif at_once:
         _forward_at_once(fwd, state, scheds, bufs)
     for t in range(0 if at_once else nsteps):

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2310_03294_amd import binding as B
+from paper_2310_03294_amd import binding as B, driver
 from gpu_util import case, dev, np64
 from oracle import attention as A
 
@@ -76,3 +76,21 @@ def test_walks_keep_the_remainders_that_one_of_their_pairs_has(h_q, h_kv, c, wal
     for h in (0, h_q - 1):
         want = _want(q, k, v, h, rows, lo * c)[0]
         assert np.linalg.norm(np64(O[h, rows]) - want) <= REMAINDERS * np.linalg.norm(want), h
+
+
+@pytest.mark.parametrize("h_q,h_kv,P,c,mode,qc,heavy", [
+    (32, 32, 2, 300, "balanced", 1, 0),            # the one full pair of two workers
+    (16, 4, 2, 700, "balanced", 1, 0),
+    (16, 4, 4, 300, "balanced", 3, 1),             # the last time step's two pairs
+    (32, 8, 8, 100, "balanced", 7, 3),             # ... four
+    (32, 8, 8, 500, "ring", 7, 0),                 # ... one
+    (32, 8, 8, 100, ("window", 5), 7, 2),          # ... three
+])
+def test_all_workers_keep_the_remainders_that_a_time_step_has(h_q, h_kv, P, c, mode, qc, heavy):
+    q, k, v = _inputs(350 + c + h_q, h_q, h_kv, P, c, heavy)
+    bufs = driver.Buffers(h_q, h_kv, P * c, 128, P, dev(), grads=False)
+    driver.run_all_workers(*(t.to(dev()) for t in (q, k, v)), None, SCALE, P, bufs, mode=mode, backward=False)
+    rows, lo = np.arange(qc * c, (qc + 1) * c), max(0, qc - mode[1]) * c if isinstance(mode, tuple) else 0
+    for h in (0, h_q - 1):
+        want = _want(q, k, v, h, rows, lo)[0]
+        assert np.linalg.norm(np64(bufs.O[h, rows]) - want) <= REMAINDERS * np.linalg.norm(want), h

@@ -62,6 +62,36 @@ def test_long_sequences_stay_step_by_step(monkeypatch):
     assert [x[1] for x in calls if x[0] == "bwd"][0] is True and len([x for x in calls if x[0] == "bwd"]) > 1
 
 
+@pytest.mark.parametrize("mode", ["balanced", "ring", ("window", 1), ("window", 3)])
+@pytest.mark.parametrize("P", [1, 2, 3, 4, 8, 16])
+def test_no_way_of_all_workers_drops_remainders(P, mode):
+    """bf16: where a list of pairs of a time step is in the 64-row form (weights of 16 bits), the one call or the walks that stand for it
+    are; the time steps are what they are."""
+    lib, seen = dfa.load_library(), set()
+    for h_q, h_kv in ((1, 1), (2, 1), (8, 8), (16, 4), (32, 8), (48, 16), (64, 64)):
+        for c in (1, 64, 65, 100, 128, 257, 300, 512, 513, 700, 1000, 1023, 2047, 2048, 2049, 4096, 9000):
+            scheds = [dfa.dfa_schedule(P, w, mode) for w in range(P)]
+            rows = {}
+            for t, steps in enumerate(zip(*scheds)):
+                n = sum(st.kind != B.DFA_STEP_IDLE for st in steps)
+                rows[t] = B.forward_form(h_q, h_kv, c, 128, B.DFA_BF16, t == 0, n).rows if n else 0
+            bufs = driver.Buffers(h_q, h_kv, P * c, 128, P, "meta")
+            q, k = (torch.empty(h, P * c, 128, dtype=torch.bfloat16, device="meta") for h in (h_q, h_kv))
+            one, walks = driver._how_at_once(q, k, bufs, P, mode)
+            seen.add((one, walks))
+            full = any(r == 64 for t, r in rows.items() if t)
+            if one and P > 1:
+                assert 64 not in rows.values() or B.sequence_form(h_q, h_kv, P * c, 128, B.DFA_BF16).rows == 64, (h_q, c)
+            elif not one and walks:
+                spans = [(sum(st.kind in (B.DFA_STEP_DIAG, B.DFA_STEP_OWN) for st in s) * c, 1) for s in scheds]
+                spans += [(c, 0) for s in scheds for st in s if st.kind == B.DFA_STEP_HELP]
+                arr = (B.DfaFwdSpan * len(spans))(*[B.DfaFwdSpan(n_keys=n, own=own) for n, own in spans])
+                sh, form = B.DfaShape(h_q, h_kv, c, c, 128, B.DFA_BF16, B.DFA_F32, 0, 1.0, 0, P * c * 128, 128, P * c * 128, 128), B.DfaForm()
+                assert lib.dfa_span_fwd_form(ctypes.byref(sh), arr, len(spans), 0, ctypes.byref(form)) == 0
+                assert not full or form.rows == 64, (h_q, c)
+    assert (True, True) in seen or isinstance(mode, tuple)
+
+
 @pytest.mark.parametrize("pairs", [
     [(2, 2, False), (2, 0, True)],                 # a chunk is left out
     [(1, 1, False), (1, 2, True)],                 # keys behind the query chunk's own
