@@ -876,42 +876,68 @@ bool split_dq(int64_t n_kv, int64_t n256, int64_t n128) {
 // parts: 8 over 2 heads x 1024 87 / 51 / 35, x 4096 341 / 217 / 212, x 8192 814 / 761 / 767; 32 over 8 x
 // 1024 91 / 66 / 73, x 1500 diagonal 135 / 101 / 103, x 4096 756 / 779 / 810; 8 heads of their own x 1024
 // 31 / 36 / 38.
-// Parts of dq, for a few query rows against many keys (a span of chunks), where a row block's walk over all of them would be the
-// whole call: `q_parts` workgroups of 128 rows share it, from two keys per row on.
-Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
-  const int group = sh.h_q / sh.h_kv;
-  const int64_t kv1 = dk ? blocks_of(sh.s_k, kv::BN) * sh.h_kv * pairs : 0;
-  const int64_t n256 = dq ? blocks_of(sh.s_q, 256) * sh.h_q * pairs : 0;
-  const int64_t n128 = dq ? blocks_of(sh.s_q, 128) * sh.h_q * pairs : 0;
-  const double walk_kv = 1.35 * group * blocks_of(sh.s_q, kv::BM), walk_q = 1.9 * blocks_of(sh.s_k, qs::BN);
-  // of a walk: the query chunk's own keys are half visible
-  const double mean_kv = sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0, mean_q = mean_kv;
-  ws_bytes = std::min(ws_bytes, int64_t{128} << 20);
-  const int most_q = dq && dk && pairs == 1 && sh.s_k / 2 >= sh.s_q ? 16 : 1;
-  Plan best{};
-  for (int q_parts = 1; q_parts <= most_q; ++q_parts) {
-    const int64_t q_bytes = q_parts > 1 ? n128 * q_parts * QPART_F4 * 16 : 0;
-    if (q_parts > 1 && (n128 * q_parts > 1024 || q_bytes > ws_bytes)) break;
-    for (int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-      const int64_t n_kv = kv1 * parts, bytes = q_bytes + (parts > 1 ? n_kv * PART_BYTES : 0);
-      if (parts > 1 && (!dk || parts > 4 * group || n_kv > 1024 || bytes > ws_bytes)) break;
-      Plan x{dq && (q_parts > 1 || split_dq(n_kv, n256, n128)), parts, 0., q_parts, bytes};
-      const int64_t n_q = x.split ? n128 * q_parts : n256;
-      const double t_kv = dk ? 8 + walk_kv / parts : 0, w_q = x.split ? walk_q / 2 / q_parts : walk_q, t_q = dq ? 8 + w_q : 0;
-      x.us = std::max(t_kv, t_q);
-      if (n_kv + n_q > 256) {
-        // (of a span, the longer kind goes first and the shorter fills the end; two key parts copy every tile for half the rows)
-        const double q_us = n_q * (8 + w_q * mean_q) * (most_q > 1 && x.split ? 1.15 : 1.0);
-        const double share = (n_kv * (8 + walk_kv * mean_kv / parts) + q_us) / 256;
-        x.us = std::max(x.us, share + 0.45 * (most_q > 1 ? std::min(t_kv, t_q) : x.us));
-      }
-      x.q_first = most_q > 1 ? t_q > t_kv : group <= parts;
-      if (parts > 1) x.us = (x.us + 4 + n_kv * (2 * PART_BYTES / 2.5e6)) * (group % parts ? 1.15 : 1.0);
-      if (q_parts > 1) x.us += 4 + 2 * q_bytes / 2.5e6;
-      if ((parts == 1 && q_parts == 1) || x.us < (best.parts == 1 && best.q_parts == 1 ? 0.92 : 1.0) * best.us) best = x;
-    }
+// Few query rows against many keys, from two keys per row on (a span of chunks): the walk of a row block of dq over all of them
+// may be the whole call, and `q_parts` workgroups of 128 rows share it.  Such calls run in many rounds, the longer kind of
+// workgroups first and the shorter filling the end, so they have an estimate of their own, with constants fitted to 40 spans of 2
+// to 9 chunks of 256 to 8192 rows with every division timed (chosen / best 1.025 in the mean).  us, pairs one by one / span: 4
+// over 1 heads, 5 x 8192 1928 / 1781, 16 over 4, 5 x 2048 545 / 484, 8 over 2, 5 x 700 136 / 50, 8 heads, 5 x 2777 588 / 450, 32 heads,
+// 5 x 1024 338 / 268.
+struct Call {
+  int group, s_k;
+  int64_t kv1, n256, n128;      // workgroups of dk, dv undivided, of dq by 256 and by 128 rows
+  double mean;                  // of a walk: the query chunk's own keys are half visible
+  int64_t ws_bytes;
+  int tiles_q;
+};
+bool feasible(const Call& c, int parts, int q_parts, int64_t bytes) {
+  return (parts == 1 || (c.kv1 && parts <= 4 * c.group && c.kv1 * parts <= 1024)) && (q_parts == 1 || c.n128 * q_parts <= 1024) &&
+         bytes <= c.ws_bytes;
+}
+Plan estimate(const Call& c, int parts, int q_parts, bool split, bool span) {
+  const int64_t n_kv = c.kv1 * parts, n_q = split ? c.n128 * q_parts : c.n256;
+  const int64_t q_bytes = q_parts > 1 ? n_q * QPART_F4 * 16 : 0, kv_bytes = parts > 1 ? n_kv * PART_BYTES : 0;
+  Plan x{split, parts, 0., q_parts, kv_bytes + q_bytes, false};
+  const double walk_kv = 1.35 * c.group * c.tiles_q, walk_q = (span ? 2.1 : 1.9) * blocks_of(c.s_k, qs::BN);
+  const double w_q = split ? walk_q / 2 / q_parts * (span ? 1.1 : 1.0) : walk_q;
+  const double t_kv = n_kv ? 8 + walk_kv / parts : 0, t_q = n_q ? 8 + w_q : 0;
+  x.us = std::max(t_kv, t_q);
+  if (n_kv + n_q > 256) {
+    const double share = (n_kv * (8 + walk_kv * c.mean / parts) + n_q * (8 + w_q * c.mean)) / 256;
+    x.us = std::max(x.us, share + (span ? 0.8 * std::min(t_kv, t_q) : 0.45 * x.us));
   }
-  return best;
+  if (parts > 1) x.us = (x.us + 4 + 2 * kv_bytes / 2.5e6) * (c.group % parts && !span ? 1.15 : 1.0);
+  if (q_parts > 1) x.us += 4 + 2 * q_bytes / 2.5e6;
+  x.q_first = span ? t_q > t_kv : c.group <= parts;      // (the longer workgroups first)
+  return x;
+}
+constexpr int PARTS[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+
+Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
+  Call c{sh.h_q / sh.h_kv, sh.s_k, dk ? blocks_of(sh.s_k, kv::BN) * sh.h_kv * pairs : 0, dq ? blocks_of(sh.s_q, 256) * sh.h_q * pairs : 0,
+         dq ? blocks_of(sh.s_q, 128) * sh.h_q * pairs : 0, sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0,
+         std::min(ws_bytes, int64_t{128} << 20), static_cast<int>(blocks_of(sh.s_q, kv::BM))};
+  Plan best{};
+  for (int parts : PARTS) {
+    const Plan x = estimate(c, parts, 1, dq && split_dq(c.kv1 * parts, c.n256, c.n128), false);
+    if (!feasible(c, parts, 1, x.bytes)) break;
+    if (parts == 1 || x.us < (best.parts == 1 ? 0.92 : 1.0) * best.us) best = x;
+  }
+  if (!dq || !dk || pairs > 1 || sh.s_k / 2 < sh.s_q) return best;
+  Plan span = estimate(c, 1, 1, false, true);
+  for (int q_parts = 1; q_parts <= 16; ++q_parts)
+    for (int parts : PARTS) {
+      Plan x = estimate(c, parts, q_parts, true, true);
+      if (!feasible(c, parts, q_parts, x.bytes)) break;
+      if (q_parts == 1) {
+        const Plan y = estimate(c, parts, 1, false, true);
+        if (y.us <= x.us || c.n256 > 256) x = y;      // (many rounds of 256-row workgroups: 32 over 8 heads, 3 x 5000 2 % slower split)
+      }
+      const bool whole = span.parts == 1 && span.q_parts == 1;
+      if (x.us < span.us * (whole && (parts > 1 || q_parts > 1) ? 0.97 : 1.0)) span = x;
+    }
+  // A pair of chunks: only where the gain is beyond what the estimate errs (8 over 2 heads x 4096 x 16384, 0.89 of it: 770 -> 795).
+  if (!sh.causal && span.us >= 0.88 * estimate(c, best.parts, 1, best.split, true).us) return best;
+  return span;
 }
 
 }  // namespace

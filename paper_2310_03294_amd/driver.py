@@ -175,11 +175,20 @@ def backward_worker(Q, K, V, dO, scale, P, w, bufs: Buffers, mode="balanced", wi
 
 def _backward_at_hand(Q, K, V, dO, scale, sched, w, bufs: Buffers):
     """backward_worker for a worker that has all its key/value chunks at hand, into gradient chunks that hold nothing yet: its
-    own and its earlier chunks as one call, then its HELP pairs, all with its own key/value chunk."""
+    own and its earlier chunks as one call, then its HELP pairs, all with its own key/value chunk.
+    (bf16, long chunks of heads that do not divide into XCDs: pair by pair, each of which fills the device, as the XCD with the
+    last key tiles of a walk, half of them behind the diagonal, is done before the others.  us, pairs / walk: 8 over 2 heads, 3 x
+    8192 1950 / 2130, 16 over 4, 5 x 6000 3912 / 4065, 4 heads, 3 x 16384 3950 / 4108; 8 over 2, 5 x 6000 2148 / 1971; 8 heads, 5 x 8192
+    3464 / 3459, 32 over 8, 5 x 4096 3519 / 3451.)"""
     c = bufs.c
     B.dfa_delta(_chunk(bufs.O, w, c), _chunk(dO, w, c), delta=_chunk(bufs.delta, w, c))
     bwd = B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, bufs.dQ, bufs.dK, bufs.dV, c, scale)
-    bwd.launch_span(w, min(st.kv_chunk for st in sched if st.kind in (B.DFA_STEP_DIAG, B.DFA_STEP_OWN)), w, False, False)
+    own = [st.kv_chunk for st in sched if st.kind in (B.DFA_STEP_DIAG, B.DFA_STEP_OWN)]
+    if Q.dtype == torch.bfloat16 and K.shape[0] % 8 and Q.shape[0] * c * c > 3 << 27:
+        for kc in own:
+            bwd.launch([(w, kc, kc != w, False)], kc == w)
+    else:
+        bwd.launch_span(w, min(own), w, False, False)
     for st in sched:
         if st.kind == B.DFA_STEP_HELP:
             bwd.launch([(st.q_chunk, w, False, True)], False)

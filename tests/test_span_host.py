@@ -47,6 +47,39 @@ def test_share_computes_the_schedules_pairs(monkeypatch, P):
         assert log.index("delta") == len(fwd) + len(remote)
 
 
+@pytest.mark.parametrize("h_q,h_kv,c,span", [(16, 4, 6000, False), (8, 2, 8192, False), (4, 4, 16384, False), (16, 4, 4096, True), (32, 8, 8192, True),
+                                             (2, 1, 8192, True)])
+def test_backward_of_long_chunks_of_few_heads_goes_pair_by_pair(monkeypatch, h_q, h_kv, c, span):
+    """(Its walk leaves the XCDs unequal shares, and the pairs fill the device.)  Every pair once, dq of the first overwritten."""
+    P, log = 4, []
+    q, k = (torch.empty(h, P * c, 128, dtype=torch.bfloat16, device="meta") for h in (h_q, h_kv))
+    bufs = driver.Buffers(h_q, h_kv, P * c, 128, P, "meta")
+    monkeypatch.setattr(B, "dfa_delta", lambda *a, **kw: None)
+    monkeypatch.setattr(B.BackwardChunks, "launch_span", lambda self, qc, lo, hi, acc_q, acc_kv, stream=None: log.append("span"))
+    monkeypatch.setattr(B.BackwardChunks, "launch", lambda self, items, causal, stream=None: log.extend((*x, causal) for x in items))
+    driver._backward_at_hand(q, k, k, q, 1.0, dfa.dfa_schedule(P, P - 1), P - 1, bufs)
+    assert log == (["span"] if span else [(3, 3, False, False, True), (3, 2, True, False, False), (3, 1, True, False, False)])
+
+
+def test_divisions_of_the_backward():
+    """What a pair of chunks asks for in scratch: as before there were spans where sharing dq's walk gains little (its 128-row form
+    has no scratch), its sums where it gains much; spans divide more."""
+    lib = dfa.load_library()
+
+    def ask(h_q, h_kv, s_q, s_k, span):
+        sh = B.DfaShape(h_q=h_q, h_kv=h_kv, s_q=s_q, s_k=s_k, d=128, dtype=B.DFA_BF16, scale=1.0, causal=span)
+        if span:
+            return lib.dfa_span_bwd_workspace(ctypes.byref(sh), 1, 1)
+        return lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), 1, 1, 1)
+
+    for shape in ((8, 8, 1000, 2500), (16, 4, 1024, 4096), (16, 4, 2048, 8192), (8, 2, 4096, 16384), (32, 8, 1024, 4096)):
+        assert ask(*shape, 0) == 0, shape
+    for shape in ((1, 1, 1000, 30000), (8, 8, 128, 8000), (32, 32, 128, 20000)):
+        assert ask(*shape, 0) > 0, shape
+    for shape in ((4, 1, 8192, 40960), (8, 2, 4096, 20480), (8, 2, 700, 3500)):
+        assert ask(*shape, 1) > 0, shape
+
+
 def test_long_sequences_stay_step_by_step(monkeypatch):
     """A walk longer than a call's slice is not one call."""
     h, d, P, c = 2, 128, 4, 40000
