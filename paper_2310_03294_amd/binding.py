@@ -453,10 +453,14 @@ class BackwardChunks:
 
     def launch(self, pairs, causal, stream=None):
         """The pairs as one launch: (q_chunk, kv_chunk, accumulate_dq, accumulate_dkv); no query chunk and no
-        key/value chunk occurs twice."""
+        key/value chunk occurs twice.  causal None: one chunk with itself, a sequence that stands for the pairs of several
+        chunks (dfa_span_bwd)."""
         if not pairs:
             return
         sh = self.sh
+        if causal is None:
+            (qc, kc, acc_q, acc_kv), = pairs
+            return self.launch_span(qc, kc, qc, acc_q, acc_kv, stream)
         sh.causal = int(bool(causal))
         arr = (DfaBwdPair * len(pairs))(*[self._pair(*pair) for pair in pairs])
         ws, n = _workspace(self.lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), len(pairs), 1, 1), stream)

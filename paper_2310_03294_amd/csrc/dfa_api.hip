@@ -255,7 +255,8 @@ int bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t n_pairs, v
     }
     return DFA_OK;
   }
-  return sh->dtype == DFA_F32 ? dfa::launch_bwd_f32(*sh, pairs, n_pairs, workspace, workspace_bytes, st)
+  const bool sequence = spans && sh->causal && sh->s_q == sh->s_k;
+  return sh->dtype == DFA_F32 ? dfa::launch_bwd_f32(*sh, pairs, n_pairs, sequence, workspace, workspace_bytes, st)
                               : dfa::launch_bwd_bf16(*sh, pairs, n_pairs, workspace, workspace_bytes, st);
 }
 
@@ -264,7 +265,8 @@ int64_t bwd_workspace(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int
   if (rc != DFA_OK) return rc;
   if (n_pairs < 0) return DFA_ERR_ARG;
   if (n_pairs == 0 || sh->s_q == 0 || sh->s_k == 0) return 0;
-  return sh->dtype == DFA_F32 ? dfa::bwd_f32_workspace(*sh, n_pairs, want_dq != 0, want_dkv != 0)
+  const bool sequence = spans && sh->causal && sh->s_q == sh->s_k;
+  return sh->dtype == DFA_F32 ? dfa::bwd_f32_workspace(*sh, n_pairs, want_dq != 0, want_dkv != 0, sequence)
                               : dfa::bwd_bf16_workspace(*sh, n_pairs, want_dq != 0, want_dkv != 0);
 }
 

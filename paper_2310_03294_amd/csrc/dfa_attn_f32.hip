@@ -397,7 +397,12 @@ __global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(Args a) {
 // there are; V (the same 32 rows for all four wavefronts) then stays in LDS.
 template <int D, int NS> constexpr bool kVLds = D == 128 && NS == 4;
 // SHARED: p.shares workgroups share the query tiles of a row block.
-template <int D, int NS, bool SHARED>
+// SUMS (a sequence that stands for the pairs of several chunks): dk, dv as sums of 32 query rows each, added up.  The rounding
+// errors of one chain over all rows grow with its length.  Relative error of dk, dv in a schedule of 4 heads x 8000, d = 128: one chain
+// 1.6e-6, sums 5.8e-7 and 5.1e-7 (pair by pair, 1000 rows each in one chain, 7.0e-7 and 6.6e-7).  They take 7 to 8 % of a
+// backward at d = 128 (full pair of 32 heads x 4096 8766 / 9421 us) and 1 to 2 % at d = 64, so a pair, whose chain is no longer
+// than it ever was, goes without.
+template <int D, int NS, bool SHARED, bool SUMS>
 __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int item, float* partial, float* smem) {
   constexpr int NR = 4 / NS, NB = D / 32, LD = D + 4, BQ = 32 * NS;
   constexpr bool V_LDS = kVLds<D, NS>;
@@ -447,9 +452,6 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
   } else {
     load_rows<D>(v, pr.v + kh * p.kv_sh, p.kv_ss, kvrow, kvalid, hh);
   }
-  // Sums of 32 query rows each, added up: the rounding errors of one chain over all rows grow with its length.  Relative error of dk,
-  // dv in a schedule of 4 heads x 8000, d = 128: one chain 1.6e-6, this 5.8e-7 and 5.1e-7 (pair by pair, 1000 rows each, 7.0e-7 and
-  // 6.6e-7); it takes 2 to 3 % of the time.
   f32x16 dk[NB], dv[NB];
   zero(dk);
   zero(dv);
@@ -479,12 +481,13 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
       s[i] = vis ? expf(s[i] * p.scale - L) : 0.f;
       dp[i] = s[i] * (dp[i] - Ds[part * 32 + r]);
     }
-    if constexpr (V_LDS) {      // (no registers left for the sums)
-      col_product<D>(dv, Gw, s, r32, hh);
-      col_product<D>(dk, Qw, dp, r32, hh);
-    } else {
+    if constexpr (SUMS) {
+      static_assert(!V_LDS, "no registers left for the sums");
       col_sum<D>(dv, Gw, s, r32, hh);
       col_sum<D>(dk, Qw, dp, r32, hh);
+    } else {
+      col_product<D>(dv, Gw, s, r32, hh);
+      col_product<D>(dk, Qw, dp, r32, hh);
     }
   }
   if constexpr (NS > 1) {
@@ -618,14 +621,14 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int i
 // ones), no atomics, no zero fill, a fixed order of summation.  The fused
 // form (5 products, dq added with fp32 atomics) left a short chunk with as few workgroups as it has key
 // tiles.
-template <int D, int NS, bool SHARED>
+template <int D, int NS, bool SHARED, bool SUMS>
 __global__ void __launch_bounds__(NT, 1) k_bwd_f32(F32BwdParams p) {
   extern __shared__ __align__(16) float smem[];
   const int grid_kv = p.map_kv.per_xcd * 8, bid = blockIdx.x;
   if (bid < grid_kv) {
     const int item = xcd_item(p.map_kv, bid);
     if (item < p.map_kv.total)
-      bwd_dkdv<D, NS, SHARED>(p, p.pair[item / p.n_kv], item % p.n_kv,
+      bwd_dkdv<D, NS, SHARED, SUMS>(p, p.pair[item / p.n_kv], item % p.n_kv,
                               p.partial + static_cast<int64_t>(item) * (4 / NS * 64 * D), smem);
   } else {
     const int item = xcd_item(p.map_q, bid - grid_kv);
@@ -772,7 +775,7 @@ int fwd_spans(F32FwdSpans& p, int n, hipStream_t st) {
   return launch<F32FwdSpans, k_fwd_f32<D, NS, F32FwdSpans>>(p, xcd_blocks(p.map_q), tiles > comb ? tiles : comb, st);
 }
 
-template <int D, int NS>
+template <int D, int NS, bool SUMS>
 int bwd(F32BwdParams p, hipStream_t st) {
   const int rows = 32 * (4 / NS);
   const size_t comb = NS > 1 ? sizeof(float) * (4 - 4 / NS) * 2 * (D / 32) * 16 * 64 : 0;
@@ -789,8 +792,8 @@ int bwd(F32BwdParams p, hipStream_t st) {
   if (p.shares > 1) p.q_partial += n_kv * p.pairs * (rows * 2 * D);      // after the sums of dk, dv
   const int64_t blocks = xcd_blocks(p.map_kv) + xcd_blocks(p.map_q);
   const size_t smem = tiles > comb ? tiles : comb;
-  const int rc = p.shares > 1 ? launch<F32BwdParams, k_bwd_f32<D, NS, true>>(p, blocks, smem, st)
-                              : launch<F32BwdParams, k_bwd_f32<D, NS, false>>(p, blocks, smem, st);
+  const int rc = p.shares > 1 ? launch<F32BwdParams, k_bwd_f32<D, NS, true, SUMS>>(p, blocks, smem, st)
+                              : launch<F32BwdParams, k_bwd_f32<D, NS, false, SUMS>>(p, blocks, smem, st);
   if (rc) return rc;
   if (p.shares > 1)
     k_reduce_f32<D, 4 / NS, true><<<dim3(static_cast<unsigned>(n_kv * p.pairs / p.shares), 2 * (4 / NS)), NT, 0, st>>>(p);
@@ -828,14 +831,15 @@ double uneven(int64_t groups) {
   return groups <= 2 ? 1.0 : (whole + rest * (2 - rest)) / g;
 }
 
-Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
+Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes, bool sequence) {
+  (void)sequence;
   const int group = sh.h_q / sh.h_kv;
   const double width = sh.d == 128 ? 1.0 : 0.55, mean = sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0;
   ws_bytes = std::min(ws_bytes, int64_t{128} << 20);
   const int max_q = !dq ? 1 : sh.s_k / 8 >= sh.s_q ? 64 : dk && pairs == 1 && sh.causal ? 8 : 1;
   Plan best{0, 0, 0, 0., 0};
   for (int parts : {1, 2, 4}) {
-    if (parts == 4 && max_q == 8 && sh.d == 128) break;      // (its dk, dv are one chain)
+    if (parts == 4 && max_q == 8 && sh.d == 128) break;      // (no registers for the sums)
     const int rows = 128 / parts, tile = 32 * parts;
     const int64_t kv1 = dk ? blocks_of(sh.s_k, rows) * sh.h_kv * pairs : 0, q1 = dq ? blocks_of(sh.s_q, rows) * sh.h_q * pairs : 0;
     const double walk_kv = width * (parts == 1 ? 9.3 : parts == 2 ? 10.3 : 12.2) * group * blocks_of(sh.s_q, tile);
@@ -886,9 +890,9 @@ int launch_fwd_f32(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStr
   return fwd_form<F32FwdBatch>(p, sh, st);
 }
 
-int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void* ws, int64_t ws_bytes, hipStream_t st) {
+int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, bool sequence, void* ws, int64_t ws_bytes, hipStream_t st) {
   for (; n > MAX_PAIRS; pairs += MAX_PAIRS, n -= MAX_PAIRS) {
-    const int rc = launch_bwd_f32(sh, pairs, MAX_PAIRS, ws, ws_bytes, st);
+    const int rc = launch_bwd_f32(sh, pairs, MAX_PAIRS, sequence, ws, ws_bytes, st);
     if (rc) return rc;
   }
   F32BwdParams p{};
@@ -900,17 +904,21 @@ int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void* 
                      static_cast<const float*>(x.dO), x.lse, x.delta, x.dq, x.dk, x.dv, x.accumulate_dq,
                      x.accumulate_dkv};
   }
-  const Plan pl = plan(sh, n, pairs[0].dq, pairs[0].dk, ws ? ws_bytes : 0);
+  const Plan pl = plan(sh, n, pairs[0].dq, pairs[0].dk, ws ? ws_bytes : 0, sequence);
   p.shares = pl.shares;
   p.q_shares = pl.q_shares;
   p.partial = p.q_partial = static_cast<float*>(ws);
-  if (sh.d == 128) return pl.parts == 4 ? bwd<128, 4>(p, st) : pl.parts == 2 ? bwd<128, 2>(p, st) : bwd<128, 1>(p, st);
-  return pl.parts == 4 ? bwd<64, 4>(p, st) : pl.parts == 2 ? bwd<64, 2>(p, st) : bwd<64, 1>(p, st);
+  if (sequence) {
+    if (sh.d == 128) return pl.parts == 2 ? bwd<128, 2, true>(p, st) : bwd<128, 1, true>(p, st);
+    return pl.parts == 4 ? bwd<64, 4, true>(p, st) : pl.parts == 2 ? bwd<64, 2, true>(p, st) : bwd<64, 1, true>(p, st);
+  }
+  if (sh.d == 128)
+    return pl.parts == 4 ? bwd<128, 4, false>(p, st) : pl.parts == 2 ? bwd<128, 2, false>(p, st) : bwd<128, 1, false>(p, st);
+  return pl.parts == 4 ? bwd<64, 4, false>(p, st) : pl.parts == 2 ? bwd<64, 2, false>(p, st) : bwd<64, 1, false>(p, st);
 }
 
-int64_t bwd_f32_workspace(const dfa_shape& sh, int n, bool dq, bool dk) {
-  const int per = std::min(n, MAX_PAIRS);
-  return plan(sh, per, dq, dk, INT64_MAX).bytes;
+int64_t bwd_f32_workspace(const dfa_shape& sh, int n, bool dq, bool dk, bool sequence) {
+  return plan(sh, std::min(n, MAX_PAIRS), dq, dk, INT64_MAX, sequence).bytes;
 }
 
 int launch_span_f32(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void* ws, int64_t ws_bytes, hipStream_t st) {

@@ -26,9 +26,10 @@ int launch_fill_empty_fwd(const dfa_shape& sh, void* o, float* lse, hipStream_t 
 // The pairs of a launch share the shape and write disjoint outputs (backward: all select the same ones).
 // ws: scratch of bwd_*_workspace() bytes (0: none is used), or null; with less the work is divided into fewer parts.
 int launch_fwd_f32(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st);
-int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void* ws, int64_t ws_bytes,
+// sequence: one causal call of all chunks, which stands for their pairs.
+int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, bool sequence, void* ws, int64_t ws_bytes,
                    hipStream_t st);
-int64_t bwd_f32_workspace(const dfa_shape& sh, int n, bool dq, bool dk);
+int64_t bwd_f32_workspace(const dfa_shape& sh, int n, bool dq, bool dk, bool sequence);
 
 int launch_fwd_bf16(const dfa_shape& sh, const dfa_fwd_pair* pairs, int n, hipStream_t st);
 

@@ -293,7 +293,8 @@ def backward_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced"):
     groups has every query chunk and every key/value chunk at most once, so its pairs go out as one launch."""
     grads = (bufs.dQ, bufs.dK, bufs.dV)
     if _whole_triangle(P, mode) and _fits_a_call(P * bufs.c, Q, K, *grads):
-        B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, *grads, P * bufs.c, scale).launch([(0, 0, False, False)], True)
+        bwd = B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, *grads, P * bufs.c, scale)
+        bwd.launch([(0, 0, False, False)], None if P > 1 else True)
         return
     touched = new_pass()
     bwd = B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, *grads, bufs.c, scale)

@@ -25,3 +25,11 @@ def _spills(source, tmp_path):
 
 def test_bf16_backward_spills_nothing(tmp_path):
     assert {k: n for k, n in _spills("dfa_bwd_bf16.hip", tmp_path).items() if n} == {}
+
+
+def test_f32_sums_are_for_sequences_alone(tmp_path):
+    """dk, dv as sums of 32 rows (7 % of a backward at d = 128) in kernels of their own, and no form of theirs spills."""
+    spills = {k: n for k, n in _spills("dfa_attn_f32.hip", tmp_path).items() if "k_bwd_f32" in k}
+    flags = {k: tuple(re.findall(r"Lb([01])E", k)) for k in spills}          # (SHARED, SUMS) of the mangled name
+    assert {f[1] for f in flags.values()} == {"0", "1"}
+    assert all(n == 0 for k, n in spills.items() if flags[k][1] == "1")
