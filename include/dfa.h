@@ -141,16 +141,16 @@ int dfa_span_fwd(const dfa_shape* sh, const dfa_fwd_span* spans, int32_t n_spans
 int64_t dfa_span_fwd_workspace(const dfa_shape* sh, const dfa_fwd_span* spans, int32_t n_spans);
 
 /*
- * dfa_chunk_fwd_form, dfa_span_fwd_form - which kernel form the call of these arguments takes (of a list longer than a launch: its last
- * launch).  Pure host functions, for tests and for programs that have to know what a call computes in: a bf16 forward in
- * workgroups of 64 query rows multiplies V by weights of 16 bits (the rounded weight and its remainder), in larger ones by
- * weights rounded to bf16.  Strides are not looked at.
+ * dfa_chunk_fwd_form, dfa_span_fwd_form, dfa_chunk_bwd_form, dfa_span_bwd_form - which kernel form the call of these arguments takes
+ * (of a list longer than a launch: its last launch).  Pure host functions, for tests and for programs that have to know what a
+ * call computes in: a bf16 forward in workgroups of 64 query rows multiplies V by weights of 16 bits (the rounded weight and
+ * its remainder), in larger ones by weights rounded to bf16.
  */
 typedef struct {
-  int32_t rows;     /* query rows of a workgroup */
+  int32_t rows;     /* query rows of a workgroup (backward: of dq) */
   int32_t parts;    /* parts that a workgroup divides every tile of keys in */
-  int32_t cuts;     /* parts that the keys of a span are cut in at most */
-  int32_t reserved; /* 0 */
+  int32_t cuts;     /* parts that the keys of a span are cut in at most; backward: workgroups that share the walk of a dk, dv tile */
+  int32_t q_cuts;   /* backward: workgroups that share the walk of a dq row block; forward: 0 */
 } dfa_form;
 
 int dfa_chunk_fwd_form(const dfa_shape* sh, int32_t n_pairs, dfa_form* form);
@@ -247,10 +247,15 @@ int64_t dfa_chunk_bwd_workspace(const dfa_shape* sh, int32_t n_pairs, int32_t wa
  * dfa_span_bwd - dfa_chunk_bwd_batch of one query chunk against a span of consecutive key/value rows, s_k of them: with
  * causal = 1 (s_k >= s_q) the last s_q are the chunk's own, key j is visible to query i iff j <= i + s_k - s_q.  dk, dv are
  * those of all s_k rows; accumulate_dkv goes for all of them.  The gradients are those of the span's pairs one after
- * the other, up to the order of summation.  Workspace as there.
+ * the other, up to the order of summation.  Workspace as there.  With causal = 1 and s_k == s_q it is a sequence that stands for the
+ * pairs of several chunks: in fp32, dk, dv are then sums of 32 rows each, no further off than those pairs' chains.
  */
 int dfa_span_bwd(const dfa_shape* sh, const dfa_bwd_pair* span, void* workspace, int64_t workspace_bytes, void* stream);
 int64_t dfa_span_bwd_workspace(const dfa_shape* sh, int32_t want_dq, int32_t want_dkv);
+
+int dfa_chunk_bwd_form(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int32_t want_dkv, int64_t workspace_bytes,
+                       dfa_form* form);
+int dfa_span_bwd_form(const dfa_shape* sh, int32_t want_dq, int32_t want_dkv, int64_t workspace_bytes, dfa_form* form);
 
 /* Step kinds of the balanced schedule. */
 typedef enum { DFA_STEP_IDLE = 0, DFA_STEP_DIAG = 1, DFA_STEP_OWN = 2, DFA_STEP_HELP = 3 } dfa_step_kind;

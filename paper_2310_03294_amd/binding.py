@@ -65,7 +65,7 @@ class DfaFwdSpan(ctypes.Structure):
 
 
 class DfaForm(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int32) for n in ("rows", "parts", "cuts", "reserved")]
+    _fields_ = [(n, ctypes.c_int32) for n in ("rows", "parts", "cuts", "q_cuts")]
 
 
 class DfaBwdPair(ctypes.Structure):
@@ -81,7 +81,7 @@ class DfaStep(ctypes.Structure):
 Step = collections.namedtuple("Step", "t kind q_chunk kv_chunk send_to recv_from")
 
 EXPORTS = ("dfa_chunk_fwd", "dfa_chunk_fwd_acc", "dfa_chunk_fwd_batch", "dfa_span_fwd", "dfa_span_fwd_workspace",
-           "dfa_chunk_fwd_form", "dfa_span_fwd_form", "dfa_merge", "dfa_merge_batch", "dfa_delta",
+           "dfa_chunk_fwd_form", "dfa_span_fwd_form", "dfa_chunk_bwd_form", "dfa_span_bwd_form", "dfa_merge", "dfa_merge_batch", "dfa_delta",
            "dfa_chunk_bwd",
            "dfa_chunk_bwd_batch", "dfa_chunk_bwd_workspace", "dfa_span_bwd", "dfa_span_bwd_workspace", "dfa_schedule", "dfa_schedule_mode", "dfa_schedule_window", "dfa_mfma_probe", "dfa_mfma_probe_data", "dfa_status_str",
            "dfa_version")
@@ -112,6 +112,8 @@ def load_library():
     lib.dfa_span_fwd.argtypes = [shp, ctypes.POINTER(DfaFwdSpan), i32, vp, i64, vp]
     lib.dfa_span_fwd_workspace.argtypes = [shp, ctypes.POINTER(DfaFwdSpan), i32]
     lib.dfa_chunk_fwd_form.argtypes = [shp, i32, ctypes.POINTER(DfaForm)]
+    lib.dfa_chunk_bwd_form.argtypes = [shp, i32, i32, i32, i64, ctypes.POINTER(DfaForm)]
+    lib.dfa_span_bwd_form.argtypes = [shp, i32, i32, i64, ctypes.POINTER(DfaForm)]
     lib.dfa_span_fwd_form.argtypes = [shp, ctypes.POINTER(DfaFwdSpan), i32, i64, ctypes.POINTER(DfaForm)]
     lib.dfa_merge_batch.argtypes = [ctypes.POINTER(DfaMergeDesc), ctypes.POINTER(DfaMergePair), i32, vp]
     lib.dfa_chunk_bwd_batch.argtypes = [shp, ctypes.POINTER(DfaBwdPair), i32, vp, i64, vp]

@@ -270,7 +270,28 @@ int64_t bwd_workspace(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int
                               : dfa::bwd_bf16_workspace(*sh, n_pairs, want_dq != 0, want_dkv != 0);
 }
 
+int bwd_form(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int32_t want_dkv, int64_t workspace_bytes, dfa_form* form,
+             bool spans) {
+  const int rc = check_common(sh, spans);
+  if (rc != DFA_OK) return rc;
+  if (!form) return DFA_ERR_NULL;
+  if (n_pairs < 1 || workspace_bytes < 0 || (!want_dq && !want_dkv)) return DFA_ERR_ARG;
+  if (sh->s_q == 0 || sh->s_k == 0) return DFA_ERR_SHAPE;
+  const bool sequence = spans && sh->causal && sh->s_q == sh->s_k;
+  *form = sh->dtype == DFA_F32 ? dfa::bwd_f32_form(*sh, n_pairs, want_dq != 0, want_dkv != 0, workspace_bytes, sequence)
+                               : dfa::bwd_bf16_form(*sh, n_pairs, want_dq != 0, want_dkv != 0, workspace_bytes);
+  return DFA_OK;
+}
+
 }  // namespace
+
+extern "C" int dfa_chunk_bwd_form(const dfa_shape* sh, int32_t n_pairs, int32_t want_dq, int32_t want_dkv, int64_t workspace_bytes,
+                                  dfa_form* form) {
+  return bwd_form(sh, n_pairs, want_dq, want_dkv, workspace_bytes, form, false);
+}
+extern "C" int dfa_span_bwd_form(const dfa_shape* sh, int32_t want_dq, int32_t want_dkv, int64_t workspace_bytes, dfa_form* form) {
+  return bwd_form(sh, 1, want_dq, want_dkv, workspace_bytes, form, true);
+}
 
 extern "C" int dfa_chunk_bwd_batch(const dfa_shape* sh, const dfa_bwd_pair* pairs, int32_t n_pairs, void* workspace,
                                    int64_t workspace_bytes, void* stream) {

@@ -812,16 +812,16 @@ int bwd(F32BwdParams p, hipStream_t st) {
 //   8 / 2 heads x 1024 rows 1183 / 647 / 371,  32 x 256 87 / 57 / 72,  32 x 1024 547 / 604 / 725,
 //   32 x 4096 8370 / 9210 / 11380 (82 TFLOP/s with 1);  shared, 8 / 2 x 1024 178, x 2048 1310 -> 623, four
 //   diagonal chunks of 1024 1220 -> 443.
-// At d = 128 the 4-part form with a shared walk spills 53 registers and takes longer than estimated (8 / 2 x 256 44 us
+// At d = 128 the 4-part form with a shared walk spills 52 registers and takes longer than estimated (8 / 2 x 256 44 us
 // for 35).  Where it is chosen it is the better form all the same: 4 against 2 parts 44 / 45 there, 8 / 2 x 512 diagonal
-// 58 / 78, 4 / 1 x 768 75 / 109, x 1024 129 / 141, x 1536 diagonal 206 / 205.
+// 57 / 65, 8 x 512 diagonal 56 / 66, 4 / 1 x 768 75 / 109, x 1024 129 / 141; without scratch 8 / 2 x 1024 diagonal 375 / 649, one head
+// x 1024 99 / 171.
 // The vector-FMA kernel this one replaced (dq by atomics) took 2.9 ms at 8 / 2 x 1024.
 // dq by several workgroups per row block: a few query rows against many keys, where a row block's walk over all of them would be
 // the whole call (us with one walk / shared, d = 128; dq by atomics took the third): 1 head x 32 x 16384 1278 / 76 / 47,
 // x 256 x 32768 2615 / 195 / 430, 8 x 64 x 16384 1573 / 260 / 525, 2 over 1 x 47 x 2011 161 / 34 / 103.  From eight keys per row
-// on: below, the row blocks are enough (4 heads x 500 x 1000 88, and 393 with atomics), but for diagonal chunks, whose last row
-// blocks have the whole chunk to walk over (one head x 1024, d = 64: 45 + 4 us with
-// one walk, 22 + 8 with four workgroups per row block).
+// on: below, the row blocks are enough (4 heads x 500 x 1000 88, and 393 with atomics), but for diagonal chunks of few heads, whose
+// last row blocks have the whole chunk to walk over (one head x 1024 86 / 47, d = 64 47 / 28; 4 / 1 x 1536 202 / 136).
 struct Plan { int parts, shares, q_shares; double us; int64_t bytes; };
 
 // A causal call's (head, share) groups go to the XCDs in ranges, longest row blocks first: with a part of a group left over, an
@@ -831,40 +831,63 @@ double uneven(int64_t groups) {
   return groups <= 2 ? 1.0 : (whole + rest * (2 - rest)) / g;
 }
 
-Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes, bool sequence) {
-  (void)sequence;
-  const int group = sh.h_q / sh.h_kv;
-  const double width = sh.d == 128 ? 1.0 : 0.55, mean = sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0;
-  ws_bytes = std::min(ws_bytes, int64_t{128} << 20);
-  const int max_q = !dq ? 1 : sh.s_k / 8 >= sh.s_q ? 64 : dk && pairs == 1 && sh.causal ? 8 : 1;
+struct Call {
+  int d, group, s_q, s_k, h_q, h_kv, pairs;
+  bool dq, dk;
+  double mean;            // of a walk: the query chunk's own keys are half visible
+  int64_t ws_bytes;
+};
+// diagonal: a causal call of all gradients, of which dq's workgroups come after those of dk, dv, the longest of them first.
+Plan estimate(const Call& c, int parts, int shares, int q_shares, bool diagonal) {
+  const int rows = 128 / parts, tile = 32 * parts;
+  const double width = c.d == 128 ? 1.0 : 0.55;
+  const double walk_kv = width * (parts == 1 ? 9.3 : parts == 2 ? 10.3 : 12.2) * c.group * blocks_of(c.s_q, tile);
+  const double walk_q = width * (parts == 1 ? 7.0 : parts == 2 ? 7.7 : 9.7) * blocks_of(c.s_k, tile);
+  const int64_t n_kv = c.dk ? blocks_of(c.s_k, rows) * c.h_kv * c.pairs * shares : 0;
+  const int64_t n_q = c.dq ? blocks_of(c.s_q, rows) * c.h_q * c.pairs * q_shares : 0;
+  const int64_t bytes = static_cast<int64_t>(rows) * 2 * c.d * 4;       // of a dk/dv workgroup's sums; dq: half
+  const int64_t sums = (shares > 1 ? n_kv * bytes : 0) + (q_shares > 1 ? n_q * (bytes / 2) : 0);
+  const double t_kv = c.dk ? 6 + walk_kv / shares : 0., t_q = c.dq ? 6 + walk_q / q_shares : 0.;
+  Plan x{parts, shares, q_shares, std::max(t_kv, t_q), sums};
+  if (n_kv + n_q > 256) {
+    const double even_kv = n_kv * (6 + walk_kv * c.mean / shares) / 256, even_q = n_q * (6 + walk_q * c.mean / q_shares) / 256;
+    const double last = diagonal ? even_kv * uneven(c.h_kv * shares) + std::max(t_q, even_q * uneven(c.h_q * q_shares) + 0.3 * t_q)
+                                 : even_kv + even_q + 0.45 * x.us;
+    x.us = std::max(x.us, last);
+  }
+  if (sums > 0) x.us = (x.us + 4 * ((shares > 1) + (q_shares > 1)) + 2 * sums / 2.5e6) / 0.92;
+  return x;
+}
+bool feasible(const Call& c, const Plan& x) {
+  const int rows = 128 / x.parts, tile = 32 * x.parts;
+  if (x.shares > 1 && (!c.dk || x.shares > 4 * c.group || blocks_of(c.s_k, rows) * c.h_kv * c.pairs * x.shares > 1024)) return false;
+  if (x.q_shares > 1 && (blocks_of(c.s_q, rows) * c.h_q * c.pairs * x.q_shares > 1024 || x.q_shares > blocks_of(c.s_k, tile))) return false;
+  return x.bytes <= c.ws_bytes;
+}
+Plan best_of(const Call& c, int most_parts, int most_q, bool diagonal) {
   Plan best{0, 0, 0, 0., 0};
-  for (int parts : {1, 2, 4}) {
-    if (parts == 4 && max_q == 8 && sh.d == 128) break;      // (no registers for the sums)
-    const int rows = 128 / parts, tile = 32 * parts;
-    const int64_t kv1 = dk ? blocks_of(sh.s_k, rows) * sh.h_kv * pairs : 0, q1 = dq ? blocks_of(sh.s_q, rows) * sh.h_q * pairs : 0;
-    const double walk_kv = width * (parts == 1 ? 9.3 : parts == 2 ? 10.3 : 12.2) * group * blocks_of(sh.s_q, tile);
-    const double walk_q = width * (parts == 1 ? 7.0 : parts == 2 ? 7.7 : 9.7) * blocks_of(sh.s_k, tile);
-    const int64_t bytes = static_cast<int64_t>(rows) * 2 * sh.d * 4;       // of a dk/dv workgroup's sums; dq: half
-    for (int q_shares = 1; q_shares <= max_q; q_shares *= 2) {
-      const int64_t n_q = q1 * q_shares, q_bytes = q_shares > 1 ? n_q * (bytes / 2) : 0;
-      if (q_shares > 1 && (n_q > 1024 || q_shares > blocks_of(sh.s_k, tile) || q_bytes > ws_bytes)) break;
+  for (int parts = 1; parts <= most_parts; parts *= 2)
+    for (int q_shares = 1; q_shares <= most_q; q_shares *= 2)
       for (int shares : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-        const int64_t n_kv = kv1 * shares, sums = (shares > 1 ? n_kv * bytes : 0) + q_bytes;
-        if (shares > 1 && (!dk || shares > 4 * group || n_kv > 1024 || sums > ws_bytes)) break;
-        Plan x{parts, shares, q_shares, std::max(dk ? 6 + walk_kv / shares : 0., dq ? 6 + walk_q / q_shares : 0.), sums};
-        if (n_kv + n_q > 256) {
-          double even_kv = n_kv * (6 + walk_kv * mean / shares) / 256, even_q = n_q * (6 + walk_q * mean / q_shares) / 256;
-          if (max_q == 8) { even_kv *= uneven(sh.h_kv * shares); even_q *= uneven(sh.h_q * q_shares); }
-          // (dq's workgroups come after those of dk, dv: the first of them, the longest of a causal call, ends as late as that)
-          if (max_q == 8) x.us = std::max(x.us, even_kv + std::max(6 + walk_q / q_shares, even_q + 0.3 * (6 + walk_q / q_shares)));
-          else x.us = std::max(x.us, even_kv + even_q + 0.45 * x.us);
-        }
-        if (sums > 0) x.us = (x.us + 4 * ((shares > 1) + (q_shares > 1)) + 2 * sums / 2.5e6) / 0.92;
+        const Plan x = estimate(c, parts, shares, q_shares, diagonal);
+        if (!feasible(c, x)) break;
         if (!best.parts || x.us < best.us) best = x;
       }
-    }
-  }
   return best;
+}
+
+// sequence: a causal call that stands for the pairs of several chunks; dk, dv as sums (no 4 parts at d = 128).
+Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes, bool sequence) {
+  const Call c{sh.d, sh.h_q / sh.h_kv, sh.s_q, sh.s_k, sh.h_q, sh.h_kv, pairs, dq, dk, sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0,
+               std::min(ws_bytes, int64_t{128} << 20)};
+  const bool few = dq && sh.s_k / 8 >= sh.s_q, diagonal = sh.causal && dq && dk && pairs == 1 && !few;
+  if (sequence) return best_of(c, sh.d == 128 ? 2 : 4, diagonal ? 8 : few ? 64 : 1, diagonal);
+  const Plan best = best_of(c, 4, few ? 64 : 1, false);
+  if (!diagonal) return best;
+  // A diagonal pair: only where the gain is beyond what the estimate errs (0.78 of it: 8 over 2 heads x 2048 412 -> 425 us); a
+  // span: always (32 over 8 heads, 5 x 512 918 -> 771, one by one 825).
+  const Plan shared = best_of(c, 4, 8, true);
+  return sh.s_k > sh.s_q || shared.us < 0.77 * estimate(c, best.parts, best.shares, 1, true).us ? shared : best;
 }
 
 }  // namespace
@@ -915,6 +938,11 @@ int launch_bwd_f32(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, bool s
   if (sh.d == 128)
     return pl.parts == 4 ? bwd<128, 4, false>(p, st) : pl.parts == 2 ? bwd<128, 2, false>(p, st) : bwd<128, 1, false>(p, st);
   return pl.parts == 4 ? bwd<64, 4, false>(p, st) : pl.parts == 2 ? bwd<64, 2, false>(p, st) : bwd<64, 1, false>(p, st);
+}
+
+dfa_form bwd_f32_form(const dfa_shape& sh, int n, bool dq, bool dk, int64_t ws_bytes, bool sequence) {
+  const Plan x = plan(sh, (n - 1) % MAX_PAIRS + 1, dq, dk, ws_bytes, sequence);
+  return {128 / x.parts, x.parts, x.shares, x.q_shares};
 }
 
 int64_t bwd_f32_workspace(const dfa_shape& sh, int n, bool dq, bool dk, bool sequence) {

@@ -1032,6 +1032,11 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
   });
 }
 
+dfa_form bwd_bf16_form(const dfa_shape& sh, int n, bool dq, bool dk, int64_t ws_bytes) {
+  const Plan x = plan(sh, (n - 1) % MAX_PAIRS + 1, dq, dk, ws_bytes);
+  return {x.split ? 128 : 256, x.split ? 2 : 1, x.parts, x.q_parts};
+}
+
 int64_t bwd_bf16_workspace(const dfa_shape& sh, int n, bool dq, bool dk) {
   return plan(sh, std::min(n, MAX_PAIRS), dq, dk, INT64_MAX).bytes;
 }

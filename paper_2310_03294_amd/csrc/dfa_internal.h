@@ -45,6 +45,8 @@ int64_t bwd_bf16_workspace(const dfa_shape& sh, int n, bool dq, bool dk);
 // The forms that these calls take (dfa_form).
 dfa_form fwd_bf16_form(const dfa_shape& sh, int n);
 dfa_form fwd_f32_form(const dfa_shape& sh, int n);
+dfa_form bwd_bf16_form(const dfa_shape& sh, int n, bool dq, bool dk, int64_t ws_bytes);
+dfa_form bwd_f32_form(const dfa_shape& sh, int n, bool dq, bool dk, int64_t ws_bytes, bool sequence);
 dfa_form span_bf16_form(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_t ws_bytes);
 dfa_form span_f32_form(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_t ws_bytes);
 

@@ -80,6 +80,26 @@ def test_divisions_of_the_backward():
         assert ask(*shape, 1) > 0, shape
 
 
+def test_forms_of_the_f32_diagonal():
+    """Short diagonals of few heads are in the 4-part form, with scratch and above all without; sharing dq's walk only where it gains."""
+    lib, form = dfa.load_library(), B.DfaForm()
+
+    def of(h_q, h_kv, s, d, ws):
+        sh = B.DfaShape(h_q=h_q, h_kv=h_kv, s_q=s, s_k=s, d=d, dtype=B.DFA_F32, scale=1.0, causal=1)
+        assert lib.dfa_chunk_bwd_form(ctypes.byref(sh), 1, 1, 1, ws, ctypes.byref(form)) == 0
+        return form.parts, form.cuts, form.q_cuts
+
+    for shape in ((1, 1, 256, 128), (1, 1, 1024, 128), (8, 8, 128, 128), (8, 8, 512, 128), (8, 2, 512, 128), (8, 2, 1024, 128), (32, 8, 128, 128)):
+        assert of(*shape, 0) == (4, 1, 1), shape
+    for shape, want in (((8, 8, 128, 128), (4, 1, 1)), ((8, 8, 512, 128), (4, 1, 1)), ((8, 2, 512, 128), (4, 6, 1)), ((32, 8, 128, 128), (4, 4, 1)),
+                        ((8, 2, 512, 64), (4, 6, 1)), ((8, 2, 2048, 64), (2, 6, 1)), ((1, 1, 1024, 128), (4, 4, 4)), ((1, 1, 1024, 64), (4, 4, 4))):
+        assert of(*shape, 128 << 20) == want, shape
+    sh = B.DfaShape(h_q=8, h_kv=8, s_q=512, s_k=512, d=128, dtype=B.DFA_F32, scale=1.0, causal=1)      # a sequence: sums, no 4 parts
+    assert lib.dfa_span_bwd_form(ctypes.byref(sh), 1, 1, 0, ctypes.byref(form)) == 0 and form.parts == 2
+    bad = lambda n=1, dq=1, dk=1, ws=0, f=ctypes.byref(form): lib.dfa_chunk_bwd_form(ctypes.byref(sh), n, dq, dk, ws, f)
+    assert bad(n=0) == bad(ws=-1) == bad(dq=0, dk=0) == -4 and bad(f=None) == -1
+
+
 def test_long_sequences_stay_step_by_step(monkeypatch):
     """A walk longer than a call's slice is not one call."""
     h, d, P, c = 2, 128, 4, 40000
