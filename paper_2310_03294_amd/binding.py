@@ -507,7 +507,17 @@ def dfa_schedule(P: int, worker_id: int, mode="balanced"):
     """Step list of one worker (host integers only).  mode: "balanced", "ring", or
     ("window", window_chunks) for the local sliding window (dfa_schedule_window)."""
     # (the schedules of up to 64 workers are kept: a pass of all workers asks for each of them twice, 3 to 4 us each time)
+    mode = plain_mode(mode)
     return list((_kept_steps if type(P) is int and P <= 64 else _steps)(P, worker_id, mode))
+
+
+def plain_mode(mode):
+    """A mode as strings and integers, which stay what they are (a window may come as a tensor or an array)."""
+    if isinstance(mode, tuple):
+        if mode[0] != "window":
+            raise ValueError(mode)
+        return "window", int(mode[1])
+    return mode
 
 
 def _steps(P, worker_id, mode):
@@ -515,9 +525,7 @@ def _steps(P, worker_id, mode):
     cap = max(1, P + 1)
     buf = (DfaStep * cap)()
     if isinstance(mode, tuple):
-        if mode[0] != "window":
-            raise ValueError(mode)
-        n = lib.dfa_schedule_window(P, worker_id, int(mode[1]), buf, cap)
+        n = lib.dfa_schedule_window(P, worker_id, mode[1], buf, cap)
     else:
         n = lib.dfa_schedule_mode({"balanced": 0, "ring": 1}[mode], P, worker_id, buf, cap)
     if n < 0:

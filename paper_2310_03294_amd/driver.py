@@ -291,7 +291,7 @@ def backward_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced"):
     99 / 30.
     Otherwise time step by time step: first the pairs of the owners, then those of the helpers.  Each of the two
     groups has every query chunk and every key/value chunk at most once, so its pairs go out as one launch."""
-    grads = (bufs.dQ, bufs.dK, bufs.dV)
+    mode, grads = B.plain_mode(mode), (bufs.dQ, bufs.dK, bufs.dV)
     if _whole_triangle(P, mode) and _fits_a_call(P * bufs.c, Q, K, *grads):
         bwd = B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, *grads, P * bufs.c, scale)
         bwd.launch([(0, 0, False, False)], None if P > 1 else True)
@@ -347,7 +347,7 @@ def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backw
     608 / 503, 8 over 2 x 8 x 2048 596 / 479, 32 x 8 x 300 141 / 72, 8 x 4 x 512 38 / 32; not in fp32, where the walks cut
     the keys of the last rows in parts: 8 over 2 heads x 4 x 1024 385 / 478, d = 64, 2 over 1 x 3 x 700 43 / 74);
     otherwise time step by time step, pair by pair."""
-    c = bufs.c
+    c, mode = bufs.c, B.plain_mode(mode)
     scheds = [B.dfa_schedule(P, w, mode) for w in range(P)]
     nsteps = len(scheds[0])
     one_call, walks = _how_at_once(Q, K, bufs, P, mode) if fused else (False, False)

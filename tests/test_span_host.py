@@ -1,6 +1,7 @@
 """Host side of walks over several key/value chunks, without a GPU: which pairs the driver computes, and what is refused."""
 import ctypes
 
+import numpy as np
 import pytest
 import torch
 
@@ -197,6 +198,18 @@ def test_span_arguments():
     # what a pair's backward refused it still refuses
     y = B.DfaBwdPair(*[4096] * 9, 0, 0)
     assert lib.dfa_chunk_bwd_batch(ctypes.byref(shape(s_k=128, causal=1)), ctypes.byref(y), 1, None, 0, None) == -4
+
+
+def test_a_schedule_is_that_of_the_mode_as_it_is_now():
+    """Kept schedules go by the window's value; a window comes as any kind of number."""
+    window = torch.tensor(1)
+    for n in (1, 4):
+        window.fill_(n)
+        assert dfa.dfa_schedule(8, 7, ("window", window)) == dfa.dfa_schedule(8, 7, ("window", np.array(n))) == dfa.dfa_schedule(8, 7, ("window", n))
+        assert len(dfa.dfa_schedule(8, 7, ("window", n))) == n + 1
+    for bad, error in ((("other", 1), ValueError), ("other", KeyError)):
+        with pytest.raises(error):
+            dfa.dfa_schedule(8, 7, bad)
 
 
 def test_a_schedule_is_the_callers_own():
