@@ -282,17 +282,17 @@ def _how_at_once(Q, K, bufs: Buffers, P, mode):
     return one, c <= 768 or len(lists) == 1
 
 
-def backward_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced"):
+def backward_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", at_once=True):
     """The backward of all P workers' pairs on one device, from the merged O and L and the D of every chunk.
     Where the pairs are those of every chunk with itself and all earlier ones, they are one causal call over the P
     chunks: the sums of a chunk's pairs then stay in registers instead of going through memory pair by pair, and the
     pairs of small chunks, which leave most of the device idle, run side by side.  us in the kernels, time steps / one
     call: 32 over 8 heads x 8192, P = 8, 1960 / 1684; fp32, 4 heads x 8000, P = 8, 2924 / 2318, one head x 1024, P = 4,
     99 / 30.
-    Otherwise time step by time step: first the pairs of the owners, then those of the helpers.  Each of the two
-    groups has every query chunk and every key/value chunk at most once, so its pairs go out as one launch."""
+    Otherwise (at_once False: always) time step by time step: first the pairs of the owners, then those of the helpers.  Each of
+    the two groups has every query chunk and every key/value chunk at most once, so its pairs go out as one launch."""
     mode, grads = B.plain_mode(mode), (bufs.dQ, bufs.dK, bufs.dV)
-    if _whole_triangle(P, mode) and _fits_a_call(P * bufs.c, Q, K, *grads):
+    if at_once and _whole_triangle(P, mode) and _fits_a_call(P * bufs.c, Q, K, *grads):
         bwd = B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, *grads, P * bufs.c, scale)
         bwd.launch([(0, 0, False, False)], None if P > 1 else True)
         return
@@ -338,7 +338,7 @@ def _forward_at_once(fwd, state, scheds, bufs: Buffers):
         walks, helped = [], helped[len(now):]
 
 
-def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backward=True, fused=True):
+def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backward=True, fused=True, at_once=True):
     """The whole schedule of all P workers on one GPU.
     fused: OWN pairs continue from the owner's state instead of partial + merge, and pairs that do not wait for each other go
     out as one launch (a pair of small chunks alone leaves most of one device idle): all of the owners' as one walk
@@ -346,19 +346,21 @@ def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backw
     causal call (where that is as precise: _how_at_once), which has no partials to write, read and merge (us, forward, walks / one call: 32 over 8 heads x 8 x 1024
     608 / 503, 8 over 2 x 8 x 2048 596 / 479, 32 x 8 x 300 141 / 72, 8 x 4 x 512 38 / 32; not in fp32, where the walks cut
     the keys of the last rows in parts: 8 over 2 heads x 4 x 1024 385 / 478, d = 64, 2 over 1 x 3 x 700 43 / 74);
-    otherwise time step by time step, pair by pair."""
+    otherwise time step by time step, pair by pair.
+    at_once False: the schedule as it is written, fused or not: every pair computed as such at its time step, the partials of the
+    helpers written, handed over and merged at theirs, and the backward's pairs in the same order."""
     c, mode = bufs.c, B.plain_mode(mode)
     scheds = [B.dfa_schedule(P, w, mode) for w in range(P)]
     nsteps = len(scheds[0])
-    one_call, walks = _how_at_once(Q, K, bufs, P, mode) if fused else (False, False)
+    one_call, walks = _how_at_once(Q, K, bufs, P, mode) if fused and at_once else (False, False)
     fwd = B.ForwardChunks(Q, K, V, P * c if one_call else c, scale)
     state = fwd.dest(bufs.O, bufs.L)
-    at_once = one_call or (walks and _fits_a_call(nsteps * c, K))
+    whole = one_call or (walks and _fits_a_call(nsteps * c, K))
     if one_call:
         fwd.launch([(0, 0, state, 0, False)], True if P == 1 else None)
-    elif at_once:
+    elif whole:
         _forward_at_once(fwd, state, scheds, bufs)
-    for t in range(0 if at_once else nsteps):
+    for t in range(0 if whole else nsteps):
         steps = [scheds[w][t] for w in range(P)]
         for w, st in enumerate(steps):
             assert st.kind != B.DFA_STEP_HELP or steps[st.send_to].recv_from == w
@@ -378,4 +380,4 @@ def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backw
     if backward:
         # a helper's backward needs D of the chunk it helped, so all D vectors come first
         delta_all_chunks(bufs.O, dO, bufs.delta, c, P)
-        backward_all_workers(Q, K, V, dO, scale, P, bufs, mode)
+        backward_all_workers(Q, K, V, dO, scale, P, bufs, mode, at_once=fused and at_once)

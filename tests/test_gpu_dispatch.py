@@ -294,9 +294,11 @@ def test_bf16_backward_parts(shape):
 
 @pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 128)])
 @pytest.mark.parametrize("p,c", [(19, 24), (5, 70), (2, 130)])
-def test_schedule_in_batches(dtype, d, p, c):
+@pytest.mark.parametrize("at_once", [False, True])
+def test_schedule_in_batches(dtype, d, p, c, at_once):
     """All workers' pairs of a time step in one launch: more pairs than one launch takes (19 diagonal chunks), ragged
-    chunks, operands that are slices with strides of their own; a second pass over the same buffers."""
+    chunks, operands that are slices with strides of their own; a second pass over the same buffers.  at_once: the walks or the one
+    call that stand for them."""
     h_q, h_kv, n = 4, 2, p * c
     scale = d ** -0.5
     q, k, v, do = case(9500 + n, h_q, h_kv, n, n, d, dtype)
@@ -312,7 +314,7 @@ def test_schedule_in_batches(dtype, d, p, c):
     bufs = driver.Buffers(h_q, h_kv, n, d, p, dev())
     tol = TOL[dtype]
     for _ in range(2):
-        driver.run_all_workers(Q, K, V, dO, scale, p, bufs)
+        driver.run_all_workers(Q, K, V, dO, scale, p, bufs, at_once=at_once)
         assert maxerr(bufs.O, O) <= tol and maxerr(bufs.L, L) <= tol
         for got, w in zip((bufs.dQ, bufs.dK, bufs.dV), want):
             assert maxerr(got, w) <= tol * max(1.0, abs(w).max() / 4)

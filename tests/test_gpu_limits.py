@@ -77,10 +77,11 @@ def test_many_heads(dtype, d):
     assert all(errs[n] <= tol * mag.get(n, 1.0) for n in errs), (errs, mag)
 
 
-def test_sequence_longer_than_a_slice():
+@pytest.mark.parametrize("p", [2, 4])
+def test_sequence_longer_than_a_slice(p):
     """The whole schedule on q, dO whose rows lie 2^22 elements apart (stored [N, heads, d] with many heads): 128 rows
-    span 2^29 elements, more than one call takes, each chunk of 64 half of that."""
-    n, p, h, d, pitch = 128, 2, 1, 128, 1 << 22
+    span 2^29 elements, more than one call takes, each chunk of 64 (32, with helpers) half (a quarter) of that."""
+    n, h, d, pitch = 128, 1, 128, 1 << 22
     scale = d ** -0.5
     q, k, v, do = case(23, h, h, n, n, d, torch.bfloat16)
     big = torch.empty(n * pitch, dtype=torch.bfloat16, device=dev())         # 1 GiB: q and, d elements further on, dO

@@ -202,7 +202,7 @@ def test_config4_worker_share_full_size():
 
 
 def test_config5_gqa_all_workers_full_size():
-    """Config 5: GQA 32/8 heads, N = 262144, P = 16: the whole balanced schedule, outputs merged."""
+    """Config 5: GQA 32/8 heads, N = 262144, P = 16: the whole balanced schedule, its pairs at their time steps, outputs merged."""
     w = dfa_inputs.CONFIGS[4]
     P, c, n, g = w.p, w.chunk, w.n_total, w.h_q // w.h_kv
     heads = [2, 29]
@@ -211,7 +211,7 @@ def test_config5_gqa_all_workers_full_size():
     case = Case(w, list(range(P)), list(range(P)), keep)
     bufs = driver.Buffers(w.h_q, w.h_kv, n, w.d, P, dev())
     t0 = time.time()
-    driver.run_all_workers(case.Q, case.K, case.V, case.dO, w.scale, P, bufs)
+    driver.run_all_workers(case.Q, case.K, case.V, case.dO, w.scale, P, bufs, at_once=False)
     torch.cuda.synchronize()
     _log(f"{w.name}: whole schedule on the GPU in {time.time() - t0:.2f} s")
     rows = np.unique(np.concatenate([_sample_rows(0, c, 4, 1), _sample_rows(7 * c, 8 * c, 4, 2),

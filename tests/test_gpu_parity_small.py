@@ -169,11 +169,11 @@ def test_empty_key_chunk_gives_merge_identity(dtype):
     assert torch.equal(o2, ref_o) and torch.equal(l2, ref_l)
 
 
-def _schedule_case(w: dfa_inputs.Workload, mode="balanced", fused=True):
+def _schedule_case(w: dfa_inputs.Workload, mode="balanced", fused=True, at_once=True):
     q, k, v, do = (dfa_inputs.full_sequence(w, t) for t in range(4))
     Q, K, V, dO = (t.to(dev()) for t in (q, k, v, do))
     bufs = driver.Buffers(w.h_q, w.h_kv, w.n_total, w.d, w.p, dev())
-    driver.run_all_workers(Q, K, V, dO, w.scale, w.p, bufs, mode=mode, fused=fused)
+    driver.run_all_workers(Q, K, V, dO, w.scale, w.p, bufs, mode=mode, fused=fused, at_once=at_once)
     torch.cuda.synchronize()
     q64, k64, v64, do64 = (np64(t) for t in (q, k, v, do))
     if isinstance(mode, tuple):     # ("window", W): attention local to the W preceding chunks
@@ -219,6 +219,19 @@ def test_balanced_schedule_odd_even_gqa(P, dtype):
     _schedule_case(w)
     if P in (3, 8):
         _schedule_case(w, fused=False)
+
+
+@pytest.mark.parametrize("P", [3, 4, 8])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_schedule_by_time_steps(P, dtype):
+    """The pairs of the owners and helpers at their time steps, partials merged, backward in the same order; then the forward as
+    walks beside the helpers' pairs, whatever the driver would choose."""
+    w = dfa_inputs.Workload(f"t_s{P}", 4, 2, 128, 150 * P, P, dtype, 5321 + P)
+    _schedule_case(w, at_once=False)
+    _schedule_case(w, mode="ring", at_once=False)
+    with pytest.MonkeyPatch.context() as m:
+        m.setattr(driver, "_how_at_once", lambda *a: (False, True))
+        _schedule_case(w)
 
 
 @pytest.mark.parametrize("dtype,d,o_dtype", [(torch.float32, 64, torch.float32), (torch.float32, 128, torch.float32),

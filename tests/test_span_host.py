@@ -102,18 +102,49 @@ def test_forms_of_the_f32_diagonal():
 
 
 def test_long_sequences_stay_step_by_step(monkeypatch):
-    """A walk longer than a call's slice is not one call."""
-    h, d, P, c = 2, 128, 4, 40000
+    """A walk longer than a call's slice is not one call: the time steps' lists, each way."""
+    h, d, P, c = 2, 128, 4, 45000
     t = torch.empty_strided((h, P * c, d), (d, 4096, 1), dtype=torch.bfloat16, device="meta")
-    assert P * c * 4096 > B.MAX_SLICE >= c * 4096
+    assert len(dfa.dfa_schedule(P, 0)) * c * 4096 > B.MAX_SLICE >= c * 4096
     calls = []
-    monkeypatch.setattr(B.ForwardChunks, "launch", lambda self, items, causal, stream=None: calls.append(("fwd", causal, len(items))))
-    monkeypatch.setattr(B.BackwardChunks, "launch", lambda self, items, causal, stream=None: calls.append(("bwd", causal, len(items))))
+    monkeypatch.setattr(B.ForwardChunks, "launch", lambda self, items, causal, stream=None: items and calls.append(("fwd", causal, len(items))))
+    monkeypatch.setattr(B.BackwardChunks, "launch", lambda self, items, causal, stream=None: items and calls.append(("bwd", causal, len(items))))
     monkeypatch.setattr(B, "dfa_merge_batch", lambda *a, **kw: None)
     monkeypatch.setattr(B, "dfa_delta", lambda *a, **kw: None)
     bufs = driver.Buffers(h, h, P * c, d, P, "meta")
     driver.run_all_workers(t, t, t, t, 1.0, P, bufs)
-    assert [x[1] for x in calls if x[0] == "bwd"][0] is True and len([x for x in calls if x[0] == "bwd"]) > 1
+    _assert_time_steps(calls, P)
+
+
+def _assert_time_steps(calls, P):
+    """The launches of the balanced schedule of P = 4 workers: lists of diagonal pairs, of the owners' and helpers' pairs."""
+    assert P == 4
+    assert [x[1:] for x in calls if x[0] == "fwd"] == [(True, 4), (False, 4), (False, 2)]
+    assert [x[1:] for x in calls if x[0] == "bwd"] == [(True, 4), (False, 3), (False, 1), (False, 2)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_the_schedule_as_it_is_written(monkeypatch, dtype):
+    """at_once=False: pairs of time steps and merges of partials, fused or pair by pair; by default neither."""
+    h, d, P, c, calls = 2, 128, 4, 64, []
+    t = torch.empty((h, P * c, d), dtype=dtype, device="meta")
+    monkeypatch.setattr(B.ForwardChunks, "launch", lambda self, items, causal, stream=None: items and calls.append(("fwd", causal, len(items))))
+    monkeypatch.setattr(B.BackwardChunks, "launch", lambda self, items, causal, stream=None: items and calls.append(("bwd", causal, len(items))))
+    monkeypatch.setattr(B, "dfa_merge_batch", lambda o, l, rows, parts: parts and calls.append(("merge", len(parts))))
+    monkeypatch.setattr(B, "dfa_merge", lambda *a, **kw: calls.append(("merge", 1)))
+    monkeypatch.setattr(B, "dfa_chunk_fwd", lambda *a, **kw: calls.append(("pair",)))
+    monkeypatch.setattr(B, "dfa_delta", lambda *a, **kw: None)
+    bufs = driver.Buffers(h, h, P * c, d, P, "meta")
+    driver.run_all_workers(t, t, t, t, 1.0, P, bufs, at_once=False)
+    _assert_time_steps(calls, P)
+    assert [x for x in calls if x[0] == "merge"] == [("merge", 1)]
+    calls.clear()
+    driver.run_all_workers(t, t, t, t, 1.0, P, bufs, fused=False)
+    assert calls.count(("pair",)) == 10 and calls.count(("merge", 1)) == 6
+    assert [x[1:] for x in calls if x[0] == "bwd"] == [(True, 4), (False, 3), (False, 1), (False, 2)]
+    calls.clear()
+    driver.run_all_workers(t, t, t, t, 1.0, P, bufs)
+    assert [x for x in calls if x[0] == "bwd"] == [("bwd", None, 1)] and len([x for x in calls if x[0] == "fwd"]) == 1
 
 
 @pytest.mark.parametrize("mode", ["balanced", "ring", ("window", 1), ("window", 3)])
