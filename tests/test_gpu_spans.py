@@ -21,27 +21,34 @@ def _visible(lo, hi, qc, c):
     return qc * c + np.arange(c) if qc == hi else np.full(c, (hi + 1) * c - 1)
 
 
-# dtype, d, heads, chunk, walks (query chunk, first and last key/value chunk); which of them continue from a state
+# dtype, d, heads, chunk, walks (query chunk, first and last key/value chunk); which of them continue from a state; the form: query
+# rows of a workgroup, parts of a tile, parts that the keys are cut in (test_span_host checks that it is the one taken)
 FWD = [
-    (BF16, 128, 4, 2, 200, [(5, 0, 5), (4, 4, 4), (3, 0, 2), (2, 1, 2)], (1, 3)),      # 64 rows, the longer ones cut in parts
-    (BF16, 128, 3, 1, 70, [(1, 0, 1), (0, 0, 0), (2, 0, 0)], ()),                      # 64 rows, heads that do not divide into XCDs
-    (BF16, 128, 8, 8, 512, [(4, 0, 4)], ()),                                           # cut at chunk ends
-    (BF16, 128, 8, 2, 128, [(i, max(0, i - 2), i) for i in range(18)], (0, 7)),        # more walks than a launch takes
-    (BF16, 128, 64, 16, 300, [(2, 0, 2)], (0,)),                                       # 128 rows, sums of the rounded weights
-    (BF16, 128, 40, 8, 300, [(2, 0, 2), (0, 0, 0), (1, 0, 0)], (2,)),                  # 128 rows, fp32 sums
-    (BF16, 128, 64, 64, 1024, [(3, 0, 3)], (0,)),                                      # 256 rows, whole tiles
-    (BF16, 128, 64, 16, 1000, [(3, 0, 3)], ()),                                        # 256 rows, ragged
-    (BF16, 128, 64, 64, 1024, [(3, 0, 3), (0, 0, 0)], (1,)),                           # 256 rows, fp32 sums
-    (F32, 128, 2, 1, 100, [(4, 0, 4), (1, 1, 1), (3, 0, 2)], (0,)),                    # 4 parts, cut
-    (F32, 64, 3, 3, 70, [(2, 0, 2), (0, 0, 0)], (1,)),
-    (F32, 128, 40, 20, 200, [(2, 0, 2), (1, 0, 0), (0, 0, 0)], (1,)),                  # 2 parts
-    (F32, 64, 48, 16, 300, [(2, 0, 2)], ()),
+    (BF16, 128, 4, 2, 200, [(5, 0, 5), (4, 4, 4), (3, 0, 2), (2, 1, 2)], (1, 3), (64, 4, 6)),
+    (BF16, 128, 3, 1, 70, [(1, 0, 1), (0, 0, 0), (2, 0, 0)], (), (64, 4, 1)),          # heads that do not divide into XCDs
+    (BF16, 128, 8, 8, 512, [(4, 0, 4)], (), (64, 4, 4)),                               # cut at chunk ends
+    (BF16, 128, 8, 2, 128, [(i, max(0, i - 2), i) for i in range(18)], (0, 7), (64, 4, 1)),      # more walks than a launch takes
+    (BF16, 128, 40, 8, 300, [(2, 0, 2), (0, 0, 0), (1, 0, 0)], (2,), (64, 4, 1)),
+    (BF16, 128, 64, 16, 300, [(2, 0, 2)], (0,), (128, 2, 1)),
+    (BF16, 128, 64, 8, 300, [(2, 0, 2), (0, 0, 0), (1, 0, 0)], (2,), (128, 2, 1)),     # with a diagonal alone and no own keys
+    (BF16, 128, 64, 64, 1024, [(3, 0, 3), (0, 0, 0)], (1,), (128, 2, 1)),
+    (BF16, 128, 64, 64, 1024, [(3, 0, 3)], (0,), (256, 1, 1)),                         # whole tiles
+    (BF16, 128, 64, 16, 1000, [(3, 0, 3)], (), (256, 1, 1)),                           # ragged
+    (BF16, 128, 64, 16, 1280, [(2, 0, 2), (0, 0, 0)], (1,), (256, 1, 1)),              # whole tiles, with a diagonal alone
+    (BF16, 128, 64, 64, 1000, [(3, 0, 3), (2, 0, 2), (1, 0, 1), (0, 0, 0)], (2,), (256, 1, 1)),
+    (BF16, 128, 8, 2, 2304, [(2, 0, 2)], (0,), (256, 1, 3)),                           # the diagonal pair apart, the keys before it cut
+    (BF16, 128, 8, 4, 2200, [(2, 0, 2), (1, 0, 0)], (1,), (128, 2, 1)),                # the diagonal pair apart
+    (F32, 128, 2, 1, 100, [(4, 0, 4), (1, 1, 1), (3, 0, 2)], (0,), (32, 4, 4)),
+    (F32, 64, 3, 3, 70, [(2, 0, 2), (0, 0, 0)], (1,), (32, 4, 1)),
+    (F32, 128, 40, 20, 200, [(2, 0, 2), (1, 0, 0), (0, 0, 0)], (1,), (32, 4, 1)),
+    (F32, 128, 48, 16, 300, [(2, 0, 2)], (0,), (64, 2, 1)),
+    (F32, 64, 48, 16, 300, [(2, 0, 2)], (), (64, 2, 1)),
 ]
 
 
 @pytest.mark.parametrize("o_dtype", [F32, BF16])
-@pytest.mark.parametrize("dtype,d,h_q,h_kv,c,walks,acc", FWD)
-def test_forward_walks(dtype, d, h_q, h_kv, c, walks, acc, o_dtype):
+@pytest.mark.parametrize("dtype,d,h_q,h_kv,c,walks,acc,form", FWD)
+def test_forward_walks(dtype, d, h_q, h_kv, c, walks, acc, form, o_dtype):
     """Every second walk's result goes to a buffer of its own; two heads against the oracle."""
     n, scale, tol = max(w[0] for w in walks) + 1, d ** -0.5, 2e-2 if o_dtype == BF16 else TOL[dtype]
     q, k, v, _ = case(700 + c + h_q, h_q, h_kv, n * c, n * c, d, dtype)

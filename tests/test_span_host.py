@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import paper_2310_03294_amd as dfa
+import test_gpu_spans
 from paper_2310_03294_amd import binding as B, driver
 
 
@@ -175,6 +176,25 @@ def test_no_way_of_all_workers_drops_remainders(P, mode):
                 assert lib.dfa_span_fwd_form(ctypes.byref(sh), arr, len(spans), 0, ctypes.byref(form)) == 0
                 assert not full or form.rows == 64, (h_q, c)
     assert (True, True) in seen or isinstance(mode, tuple)
+
+
+@pytest.mark.parametrize("dtype,d,h_q,h_kv,c,walks,acc,form", test_gpu_spans.FWD)
+def test_walks_take_the_forms_they_are_tested_in(dtype, d, h_q, h_kv, c, walks, acc, form):
+    """The table of the GPU tests, with all the scratch that is asked for: a change of the estimates shows here."""
+    lib, got, n = dfa.load_library(), B.DfaForm(), max(w[0] for w in walks) + 1
+    arr = (B.DfaFwdSpan * len(walks))(*[B.DfaFwdSpan(n_keys=(hi - lo + 1) * c, own=hi == qc, accumulate=i in acc)
+                                        for i, (qc, lo, hi) in enumerate(walks)])
+    sh = B.DfaShape(h_q, h_kv, c, c, d, B.DFA_BF16 if dtype == torch.bfloat16 else B.DFA_F32, B.DFA_F32, 0, d ** -0.5, 0, n * c * d, d,
+                    n * c * d, d)
+    ws = lib.dfa_span_fwd_workspace(ctypes.byref(sh), arr, len(walks))
+    assert lib.dfa_span_fwd_form(ctypes.byref(sh), arr, len(walks), ws, ctypes.byref(got)) == 0
+    assert (got.rows, got.parts, got.cuts) == form and (ws > 0) == (form[2] > 1)
+
+
+def test_every_form_of_walks_is_tested():
+    forms = {(dtype, d, form[:2]) for dtype, d, _, _, _, _, _, form in test_gpu_spans.FWD}
+    bf16, f32 = torch.bfloat16, torch.float32
+    assert forms == {(bf16, 128, x) for x in ((64, 4), (128, 2), (256, 1))} | {(f32, d, x) for d in (64, 128) for x in ((32, 4), (64, 2))}
 
 
 @pytest.mark.parametrize("pairs", [
