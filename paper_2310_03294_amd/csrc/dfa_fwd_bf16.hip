@@ -138,7 +138,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
   const int bid = blockIdx.x;
   int item = xcd_item(a.map, bid);
   if (item >= a.map.total) return;
-  const auto& p = pair_of(a, item);
+  const FwdParams& p = pair_of(a, item);
   const int head = item / p.ntq;
   int tq = item % p.ntq;
   if (p.causal) tq = p.ntq - 1 - tq;      // longest rows first
@@ -190,8 +190,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
     }
   }
 
-  const int off = off_of(p);
-  const int k_end = p.causal ? min(p.s_k, q0 + BM + off) : p.s_k;
+  const int k_end = p.causal ? min(p.s_k, q0 + BM) : p.s_k;
   const int ntiles = (k_end + BN - 1) / BN;
 
   // K/V tiles go from global memory straight into LDS; key rows past s_k are clamped to the last
@@ -245,7 +244,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const int kvi = kbase + (j >> 2) * 8 + hh * 4 + (j & 3);
-      if (kvi >= p.s_k || (p.causal && kvi > qrow + off)) s[j] = -INFINITY;
+      if (kvi >= p.s_k || (p.causal && kvi > qrow)) s[j] = -INFINITY;
     }
   };
 
@@ -264,14 +263,14 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
     const TileCopy ck = tile_copy_plan(kg, kv_rowbytes, kn0, p.s_k - 1, tl, Kn, wave, lane);
     const TileCopy cv = tile_copy_plan(vg, kv_rowbytes, kn0, p.s_k - 1, tl, Kn + TILE_BYTES, wave, lane);
 
-    const bool active = !(p.causal && k0 > q0w + 31 + off);
+    const bool active = !(p.causal && k0 > q0w + 31);
     if (!active) {      // nothing to compute for this wavefront's rows: only its share of the copies
       tile_copy_piece<0>(ck); tile_copy_piece<1>(ck); tile_copy_piece<2>(ck); tile_copy_piece<3>(ck);
       tile_copy_piece<0>(cv); tile_copy_piece<1>(cv); tile_copy_piece<2>(cv); tile_copy_piece<3>(cv);
       if (wave == 0) { tile_copy_piece<4>(ck); tile_copy_piece<4>(cv); }
     }
     if (active) {
-      const bool need_mask = (k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w + off);
+      const bool need_mask = (k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w);
       // Software pipeline over the two 32-key blocks of the tile: the MFMAs of one block run
       // under the softmax arithmetic of the other; LDS operand reads run ahead of their MFMAs.
       bf16x8 ka[4], gv[2], pb0[2], pb1[2];
