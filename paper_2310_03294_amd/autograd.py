@@ -1,9 +1,10 @@
 """Causal attention over P virtual workers as a torch.autograd.Function, with the
 rematerialization-aware placement of the gradient checkpoint (Section 3.3).
 
-The forward runs the load-balanced schedule (Section 3.2) through the library and saves
-(q, k, v, O, logsumexp); the backward needs nothing else (Appendix A): it never re-runs the
-attention forward.  `CheckpointedBlock` shows the two checkpoint placements of Section 3.3 on a
+The forward computes what the P workers of the load-balanced schedule (Section 3.2) compute, all on one
+device and through the library (driver.run_all_workers: as one causal call or as walks, where these stand for all
+pairs), and saves (q, k, v, O, logsumexp); the backward needs nothing else (Appendix A): it never
+re-runs the attention forward.  `CheckpointedBlock` shows the two checkpoint placements of Section 3.3 on a
 block  y = f(attention(q, k, v))  whose activations are dropped in the forward pass:
 
   * placement "layer_boundary" (the usual one): the backward first recomputes the whole block,
@@ -19,8 +20,8 @@ import torch
 
 from . import driver
 
-# pairs computed by dfa_chunk_fwd / dfa_chunk_fwd_acc since the last reset (for tests and for
-# showing what each checkpoint placement re-runs)
+# chunk pairs that the attention forwards since the last reset stand for, P (P + 1) / 2 each, in however many launches (for tests
+# and for showing what each checkpoint placement re-runs)
 forward_pair_calls = 0
 # When set, every backward leaves its gradients here as the library produced them (fp32 dq, dk, dv),
 # before they are rounded to the dtype of the inputs they are handed to.
@@ -29,7 +30,7 @@ last_fp32_grads = None
 
 
 def _forward(q, k, v, scale, P):
-    """Runs the whole balanced schedule; returns the merged output and logsumexp, both fp32 (the
+    """The forward of all workers' pairs; returns the merged output and logsumexp, both fp32 (the
     state the schedule carries and the backward reuses; callers get the output in q's dtype)."""
     global forward_pair_calls
     h_q, n, d = q.shape

@@ -262,10 +262,12 @@ def _whole_triangle(P, mode):
 @functools.lru_cache(maxsize=64, typed=True)
 def _lists_with_remainders(h_q, h_kv, c, P, mode):
     """Whether the bf16 forward's lists of pairs, time step by time step, multiply V by weights of 16 bits (64-row form): the set of
-    what the lists say.  (They get shorter with the steps: to P / 2 pairs, in the ring schedule to one.)"""
+    what the lists say (they get shorter with the steps: to P / 2 pairs, in the ring schedule to one), and whether the
+    sequence as one call does."""
     lists = {(kind == B.DFA_STEP_DIAG, n) for steps in zip(*(B.dfa_schedule(P, w, mode) for w in range(P)))
              for kind, n in collections.Counter(min(st.kind, B.DFA_STEP_OWN) for st in steps if st.kind != B.DFA_STEP_IDLE).items()}
-    return {B.forward_form(h_q, h_kv, c, 128, B.DFA_BF16, causal, n).rows == 64 for causal, n in lists}
+    return ({B.forward_form(h_q, h_kv, c, 128, B.DFA_BF16, causal, n).rows == 64 for causal, n in lists},
+            B.sequence_form(h_q, h_kv, P * c, 128, B.DFA_BF16).rows == 64)
 
 
 def _how_at_once(Q, K, bufs: Buffers, P, mode):
@@ -276,9 +278,8 @@ def _how_at_once(Q, K, bufs: Buffers, P, mode):
     c = bufs.c
     if Q.dtype != torch.bfloat16 or c < 1:
         return False, True
-    lists = _lists_with_remainders(Q.shape[0], K.shape[0], c, P, mode)
-    one = (_whole_triangle(P, mode) and _fits_a_call(P * c, Q, K, bufs.O)
-           and (True not in lists or B.sequence_form(Q.shape[0], K.shape[0], P * c, 128, B.DFA_BF16).rows == 64))
+    lists, sequence = _lists_with_remainders(Q.shape[0], K.shape[0], c, P, mode)
+    one = _whole_triangle(P, mode) and _fits_a_call(P * c, Q, K, bufs.O) and (sequence or True not in lists)
     return one, c <= 768 or len(lists) == 1
 
 
