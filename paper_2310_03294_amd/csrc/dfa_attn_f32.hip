@@ -831,63 +831,67 @@ double uneven(int64_t groups) {
   return groups <= 2 ? 1.0 : (whole + rest * (2 - rest)) / g;
 }
 
-struct Call {
-  int d, group, s_q, s_k, h_q, h_kv, pairs;
-  bool dq, dk;
-  double mean;            // of a walk: the query chunk's own keys are half visible
+// A call with `parts` parts of every tile, undivided: what the divisions of a plan have in common.
+struct Undivided {
+  int parts, group, h_q, h_kv;
+  int64_t n_kv, n_q, q_tiles, bytes;      // workgroups of dk, dv and of dq; key tiles; a dk/dv workgroup's sums (dq: half)
+  double walk_kv, walk_q, mean;           // mean: of a walk, the query chunk's own keys are half visible
   int64_t ws_bytes;
 };
+Undivided undivided(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes, int parts) {
+  const int rows = 128 / parts, tile = 32 * parts, group = sh.h_q / sh.h_kv;
+  const double width = sh.d == 128 ? 1.0 : 0.55;
+  const int64_t q_tiles = blocks_of(sh.s_k, tile);
+  return {parts, group, sh.h_q, sh.h_kv, dk ? blocks_of(sh.s_k, rows) * sh.h_kv * pairs : 0, dq ? blocks_of(sh.s_q, rows) * sh.h_q * pairs : 0,
+          q_tiles, static_cast<int64_t>(rows) * 2 * sh.d * 4,
+          width * (parts == 1 ? 9.3 : parts == 2 ? 10.3 : 12.2) * group * blocks_of(sh.s_q, tile),
+          width * (parts == 1 ? 7.0 : parts == 2 ? 7.7 : 9.7) * q_tiles, sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0, ws_bytes};
+}
+int64_t sums_of(const Undivided& c, int shares, int q_shares) {
+  return (shares > 1 ? c.n_kv * shares * c.bytes : 0) + (q_shares > 1 ? c.n_q * q_shares * (c.bytes / 2) : 0);
+}
 // diagonal: a causal call of all gradients, of which dq's workgroups come after those of dk, dv, the longest of them first.
-Plan estimate(const Call& c, int parts, int shares, int q_shares, bool diagonal) {
-  const int rows = 128 / parts, tile = 32 * parts;
-  const double width = c.d == 128 ? 1.0 : 0.55;
-  const double walk_kv = width * (parts == 1 ? 9.3 : parts == 2 ? 10.3 : 12.2) * c.group * blocks_of(c.s_q, tile);
-  const double walk_q = width * (parts == 1 ? 7.0 : parts == 2 ? 7.7 : 9.7) * blocks_of(c.s_k, tile);
-  const int64_t n_kv = c.dk ? blocks_of(c.s_k, rows) * c.h_kv * c.pairs * shares : 0;
-  const int64_t n_q = c.dq ? blocks_of(c.s_q, rows) * c.h_q * c.pairs * q_shares : 0;
-  const int64_t bytes = static_cast<int64_t>(rows) * 2 * c.d * 4;       // of a dk/dv workgroup's sums; dq: half
-  const int64_t sums = (shares > 1 ? n_kv * bytes : 0) + (q_shares > 1 ? n_q * (bytes / 2) : 0);
-  const double t_kv = c.dk ? 6 + walk_kv / shares : 0., t_q = c.dq ? 6 + walk_q / q_shares : 0.;
-  Plan x{parts, shares, q_shares, std::max(t_kv, t_q), sums};
+double estimate(const Undivided& c, int shares, int q_shares, bool diagonal) {
+  const int64_t n_kv = c.n_kv * shares, n_q = c.n_q * q_shares, sums = sums_of(c, shares, q_shares);
+  const double w_kv = c.walk_kv / shares, w_q = c.walk_q / q_shares, t_kv = n_kv ? 6 + w_kv : 0., t_q = n_q ? 6 + w_q : 0.;
+  double us = std::max(t_kv, t_q);
   if (n_kv + n_q > 256) {
-    const double even_kv = n_kv * (6 + walk_kv * c.mean / shares) / 256, even_q = n_q * (6 + walk_q * c.mean / q_shares) / 256;
-    const double last = diagonal ? even_kv * uneven(c.h_kv * shares) + std::max(t_q, even_q * uneven(c.h_q * q_shares) + 0.3 * t_q)
-                                 : even_kv + even_q + 0.45 * x.us;
-    x.us = std::max(x.us, last);
+    const double even_kv = n_kv * (6 + w_kv * c.mean) / 256, even_q = n_q * (6 + w_q * c.mean) / 256;
+    us = std::max(us, diagonal ? even_kv * uneven(c.h_kv * shares) + std::max(t_q, even_q * uneven(c.h_q * q_shares) + 0.3 * t_q)
+                               : even_kv + even_q + 0.45 * us);
   }
-  if (sums > 0) x.us = (x.us + 4 * ((shares > 1) + (q_shares > 1)) + 2 * sums / 2.5e6) / 0.92;
-  return x;
+  return sums > 0 ? (us + 4 * ((shares > 1) + (q_shares > 1)) + 2 * sums / 2.5e6) / 0.92 : us;
 }
-bool feasible(const Call& c, const Plan& x) {
-  const int rows = 128 / x.parts, tile = 32 * x.parts;
-  if (x.shares > 1 && (!c.dk || x.shares > 4 * c.group || blocks_of(c.s_k, rows) * c.h_kv * c.pairs * x.shares > 1024)) return false;
-  if (x.q_shares > 1 && (blocks_of(c.s_q, rows) * c.h_q * c.pairs * x.q_shares > 1024 || x.q_shares > blocks_of(c.s_k, tile))) return false;
-  return x.bytes <= c.ws_bytes;
-}
-Plan best_of(const Call& c, int most_parts, int most_q, bool diagonal) {
+Plan best_of(const Undivided* calls, int n, int most_q, bool diagonal) {
   Plan best{0, 0, 0, 0., 0};
-  for (int parts = 1; parts <= most_parts; parts *= 2)
-    for (int q_shares = 1; q_shares <= most_q; q_shares *= 2)
+  for (const Undivided* c = calls; c < calls + n; ++c)
+    for (int q_shares = 1; q_shares <= most_q; q_shares *= 2) {
+      if (q_shares > 1 && (c->n_q * q_shares > 1024 || q_shares > c->q_tiles)) break;
       for (int shares : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-        const Plan x = estimate(c, parts, shares, q_shares, diagonal);
-        if (!feasible(c, x)) break;
-        if (!best.parts || x.us < best.us) best = x;
+        if (shares > 1 && (!c->n_kv || shares > 4 * c->group || c->n_kv * shares > 1024)) break;
+        const int64_t sums = sums_of(*c, shares, q_shares);
+        if (sums > c->ws_bytes) break;
+        const double us = estimate(*c, shares, q_shares, diagonal);
+        if (!best.parts || us < best.us) best = {c->parts, shares, q_shares, us, sums};
       }
+    }
   return best;
 }
 
 // sequence: a causal call that stands for the pairs of several chunks; dk, dv as sums (no 4 parts at d = 128).
 Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes, bool sequence) {
-  const Call c{sh.d, sh.h_q / sh.h_kv, sh.s_q, sh.s_k, sh.h_q, sh.h_kv, pairs, dq, dk, sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0,
-               std::min(ws_bytes, int64_t{128} << 20)};
+  ws_bytes = std::min(ws_bytes, int64_t{128} << 20);
+  const Undivided calls[] = {undivided(sh, pairs, dq, dk, ws_bytes, 1), undivided(sh, pairs, dq, dk, ws_bytes, 2),
+                             undivided(sh, pairs, dq, dk, ws_bytes, 4)};
   const bool few = dq && sh.s_k / 8 >= sh.s_q, diagonal = sh.causal && dq && dk && pairs == 1 && !few;
-  if (sequence) return best_of(c, sh.d == 128 ? 2 : 4, diagonal ? 8 : few ? 64 : 1, diagonal);
-  const Plan best = best_of(c, 4, few ? 64 : 1, false);
+  if (sequence) return best_of(calls, sh.d == 128 ? 2 : 3, diagonal ? 8 : few ? 64 : 1, diagonal);
+  if (diagonal && sh.s_k > sh.s_q) return best_of(calls, 3, 8, true);
+  const Plan best = best_of(calls, 3, few ? 64 : 1, false);
   if (!diagonal) return best;
-  // A diagonal pair: only where the gain is beyond what the estimate errs (0.78 of it: 8 over 2 heads x 2048 412 -> 425 us); a
-  // span: always (32 over 8 heads, 5 x 512 918 -> 771, one by one 825).
-  const Plan shared = best_of(c, 4, 8, true);
-  return sh.s_k > sh.s_q || shared.us < 0.77 * estimate(c, best.parts, best.shares, 1, true).us ? shared : best;
+  // A diagonal pair shares dq's walk only where the gain is beyond what the estimate errs (0.78 of it: 8 over 2 heads x 2048 412 ->
+  // 425 us); a span takes the best (32 over 8 heads, 5 x 512 918 -> 771, one by one 825).
+  const Plan shared = best_of(calls, 3, 8, true);
+  return shared.us < 0.77 * estimate(calls[best.parts / 2], best.shares, 1, true) ? shared : best;
 }
 
 }  // namespace

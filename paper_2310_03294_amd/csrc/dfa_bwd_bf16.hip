@@ -883,26 +883,26 @@ bool split_dq(int64_t n_kv, int64_t n256, int64_t n128) {
 // over 1 heads, 5 x 8192 1928 / 1781, 16 over 4, 5 x 2048 545 / 484, 8 over 2, 5 x 700 136 / 50, 8 heads, 5 x 2777 588 / 450, 32 heads,
 // 5 x 1024 338 / 268.
 struct Call {
-  int group, s_k;
+  int group;
   int64_t kv1, n256, n128;      // workgroups of dk, dv undivided, of dq by 256 and by 128 rows
+  double walk_kv, k_tiles;      // of dk, dv undivided; key tiles
   double mean;                  // of a walk: the query chunk's own keys are half visible
   int64_t ws_bytes;
-  int tiles_q;
 };
-bool feasible(const Call& c, int parts, int q_parts, int64_t bytes) {
+bool feasible(const Call& c, int parts, int q_parts) {
   return (parts == 1 || (c.kv1 && parts <= 4 * c.group && c.kv1 * parts <= 1024)) && (q_parts == 1 || c.n128 * q_parts <= 1024) &&
-         bytes <= c.ws_bytes;
+         (q_parts > 1 ? c.n128 * q_parts * QPART_F4 * 16 : 0) + (parts > 1 ? c.kv1 * parts * PART_BYTES : 0) <= c.ws_bytes;
 }
 Plan estimate(const Call& c, int parts, int q_parts, bool split, bool span) {
   const int64_t n_kv = c.kv1 * parts, n_q = split ? c.n128 * q_parts : c.n256;
   const int64_t q_bytes = q_parts > 1 ? n_q * QPART_F4 * 16 : 0, kv_bytes = parts > 1 ? n_kv * PART_BYTES : 0;
   Plan x{split, parts, 0., q_parts, kv_bytes + q_bytes, false};
-  const double walk_kv = 1.35 * c.group * c.tiles_q, walk_q = (span ? 2.1 : 1.9) * blocks_of(c.s_k, qs::BN);
-  const double w_q = split ? walk_q / 2 / q_parts * (span ? 1.1 : 1.0) : walk_q;
-  const double t_kv = n_kv ? 8 + walk_kv / parts : 0, t_q = n_q ? 8 + w_q : 0;
+  const double walk_q = (span ? 2.1 : 1.9) * c.k_tiles, w_kv = c.walk_kv / parts;
+  const double w_q = split ? walk_q / (2 * q_parts) * (span ? 1.1 : 1.0) : walk_q;
+  const double t_kv = n_kv ? 8 + w_kv : 0, t_q = n_q ? 8 + w_q : 0;
   x.us = std::max(t_kv, t_q);
   if (n_kv + n_q > 256) {
-    const double share = (n_kv * (8 + walk_kv * c.mean / parts) + n_q * (8 + w_q * c.mean)) / 256;
+    const double share = (n_kv * (8 + w_kv * c.mean) + n_q * (8 + w_q * c.mean)) / 256;
     x.us = std::max(x.us, share + (span ? 0.8 * std::min(t_kv, t_q) : 0.45 * x.us));
   }
   if (parts > 1) x.us = (x.us + 4 + 2 * kv_bytes / 2.5e6) * (c.group % parts && !span ? 1.15 : 1.0);
@@ -913,21 +913,23 @@ Plan estimate(const Call& c, int parts, int q_parts, bool split, bool span) {
 constexpr int PARTS[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
 
 Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
-  Call c{sh.h_q / sh.h_kv, sh.s_k, dk ? blocks_of(sh.s_k, kv::BN) * sh.h_kv * pairs : 0, dq ? blocks_of(sh.s_q, 256) * sh.h_q * pairs : 0,
-         dq ? blocks_of(sh.s_q, 128) * sh.h_q * pairs : 0, sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0,
-         std::min(ws_bytes, int64_t{128} << 20), static_cast<int>(blocks_of(sh.s_q, kv::BM))};
+  const int group = sh.h_q / sh.h_kv;
+  const Call c{group, dk ? blocks_of(sh.s_k, kv::BN) * sh.h_kv * pairs : 0, dq ? blocks_of(sh.s_q, 256) * sh.h_q * pairs : 0,
+               dq ? blocks_of(sh.s_q, 128) * sh.h_q * pairs : 0, 1.35 * group * blocks_of(sh.s_q, kv::BM),
+               static_cast<double>(blocks_of(sh.s_k, qs::BN)), sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0,
+               std::min(ws_bytes, int64_t{128} << 20)};
   Plan best{};
   for (int parts : PARTS) {
+    if (!feasible(c, parts, 1)) break;
     const Plan x = estimate(c, parts, 1, dq && split_dq(c.kv1 * parts, c.n256, c.n128), false);
-    if (!feasible(c, parts, 1, x.bytes)) break;
     if (parts == 1 || x.us < (best.parts == 1 ? 0.92 : 1.0) * best.us) best = x;
   }
   if (!dq || !dk || pairs > 1 || sh.s_k / 2 < sh.s_q) return best;
   Plan span = estimate(c, 1, 1, false, true);
-  for (int q_parts = 1; q_parts <= 16; ++q_parts)
+  for (int q_parts = 1; q_parts <= 16 && feasible(c, 1, q_parts); ++q_parts)
     for (int parts : PARTS) {
+      if (!feasible(c, parts, q_parts)) break;
       Plan x = estimate(c, parts, q_parts, true, true);
-      if (!feasible(c, parts, q_parts, x.bytes)) break;
       if (q_parts == 1) {
         const Plan y = estimate(c, parts, 1, false, true);
         if (y.us <= x.us || c.n256 > 256) x = y;      // (many rounds of 256-row workgroups: 32 over 8 heads, 3 x 5000 2 % slower split)
