@@ -382,10 +382,13 @@ class ForwardChunks:
         if causal is None:
             return self._launch_spans(pairs, stream)
         sh.causal, sh.o_dtype = int(bool(causal)), pairs[0][2][3]
-        if any(dest[3] != sh.o_dtype for _, _, dest, _, _ in pairs):
-            raise ValueError("outputs of a launch share their dtype")
-        arr = (DfaFwdPair * len(pairs))(*[
-            (self.q[qc], self.k[kc], self.v[kc], dest[0][c], dest[1][c], *dest[2], bool(acc)) for qc, kc, dest, c, acc in pairs])
+        arr = (DfaFwdPair * len(pairs))()          # (member by member: from tuples it takes twice as long)
+        for a, (qc, kc, dest, c, acc) in zip(arr, pairs):
+            if dest[3] != sh.o_dtype:
+                raise ValueError("outputs of a launch share their dtype")
+            a.q, a.k, a.v, a.o, a.lse = self.q[qc], self.k[kc], self.v[kc], dest[0][c], dest[1][c]
+            a.o_stride_h, a.o_stride_s, a.lse_stride_h = dest[2]
+            a.accumulate = bool(acc)
         _check(self.lib.dfa_chunk_fwd_batch(ctypes.byref(sh), arr, len(pairs), _stream(stream)), "dfa_chunk_fwd_batch")
 
     def _launch_spans(self, pairs, stream):
@@ -423,14 +426,13 @@ def dfa_merge_batch(o, lse, rows, parts, stream=None):
     like, lse_like = parts[0][1].stride(), parts[0][2].stride()
     md = DfaMergeDesc(*shape, _dt(o), *_hsd(o, "o"), lse.stride(0), *_hsd(parts[0][1], "o_b"), lse_like[0])
     co, cl = _Chunks(o, rows), _Chunks(lse, rows)
-    pairs = []
-    for c, ob, lb in parts:
+    arr = (DfaMergePair * len(parts))()
+    for a, (c, ob, lb) in zip(arr, parts):
         if ob.shape != shape or ob.dtype != o.dtype or ob.stride() != like or lb.shape != lse_shape or lb.stride() != lse_like:
             raise ValueError("merge operands must match")
-        pairs.append((co[c], cl[c], ob.data_ptr(), lb.data_ptr()))
+        a.o_a, a.lse_a, a.o_b, a.lse_b = co[c], cl[c], ob.data_ptr(), lb.data_ptr()
     if lse.stride(1) != 1 or lse_like[1] != 1:
         raise ValueError("lse must have unit innermost stride")
-    arr = (DfaMergePair * len(pairs))(*pairs)
     _check(lib.dfa_merge_batch(ctypes.byref(md), arr, len(parts), _stream(stream)), "dfa_merge_batch")
 
 
@@ -447,11 +449,13 @@ class BackwardChunks:
         self.by_q = [by_q, _Chunks(lse, rows), _Chunks(delta, rows), by_q.of(dO), _Chunks(dq, rows)]
         self.by_kv = [by_k, by_k.of(v), by_dk, by_dk.of(dv)]
 
-    def _pair(self, qc, kc, acc_q, acc_kv):
-        """The members of a DfaBwdPair."""
-        q, lse, delta, dO, dq = (t[qc] for t in self.by_q)
-        k, v, dk, dv = (t[kc] for t in self.by_kv)
-        return q, k, v, lse, delta, dO, dq, dk, dv, bool(acc_q), bool(acc_kv)
+    def _pairs(self, pairs):
+        arr = (DfaBwdPair * len(pairs))()
+        for a, (qc, kc, acc_q, acc_kv) in zip(arr, pairs):
+            a.q, a.lse, a.delta, a.dO, a.dq = (t[qc] for t in self.by_q)
+            a.k, a.v, a.dk, a.dv = (t[kc] for t in self.by_kv)
+            a.accumulate_dq, a.accumulate_dkv = bool(acc_q), bool(acc_kv)
+        return arr
 
     def launch(self, pairs, causal, stream=None):
         """The pairs as one launch: (q_chunk, kv_chunk, accumulate_dq, accumulate_dkv); no query chunk and no
@@ -464,7 +468,7 @@ class BackwardChunks:
             (qc, kc, acc_q, acc_kv), = pairs
             return self.launch_span(qc, kc, qc, acc_q, acc_kv, stream)
         sh.causal = int(bool(causal))
-        arr = (DfaBwdPair * len(pairs))(*[self._pair(*pair) for pair in pairs])
+        arr = self._pairs(pairs)
         ws, n = _workspace(self.lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), len(pairs), 1, 1), stream)
         _check(self.lib.dfa_chunk_bwd_batch(ctypes.byref(sh), arr, len(pairs), _ptr(ws), n, _stream(stream)),
                "dfa_chunk_bwd_batch")
@@ -474,10 +478,10 @@ class BackwardChunks:
         sh, rows = self.sh, self.sh.s_q
         sh.s_k, sh.causal = (hi - lo + 1) * rows, int(qc == hi)
         try:
-            a = DfaBwdPair(*self._pair(qc, lo, acc_q, acc_kv))
+            a = self._pairs([(qc, lo, acc_q, acc_kv)])
             self.by_kv[0][hi]                        # (in range)
             ws, n = _workspace(self.lib.dfa_span_bwd_workspace(ctypes.byref(sh), 1, 1), stream)
-            _check(self.lib.dfa_span_bwd(ctypes.byref(sh), ctypes.byref(a), _ptr(ws), n, _stream(stream)), "dfa_span_bwd")
+            _check(self.lib.dfa_span_bwd(ctypes.byref(sh), a, _ptr(ws), n, _stream(stream)), "dfa_span_bwd")
         finally:
             sh.s_k = rows
 
