@@ -134,7 +134,7 @@ def _forward_at_hand(Q, K, V, scale, sched, w, bufs: Buffers, remote):
             po = torch.empty_like(bufs.part_o[0]); pl = torch.empty_like(bufs.part_l[0])
             pairs.append((st.q_chunk, w, fwd.dest(po, pl), 0, False))
             sent[st.send_to] = (po, pl)
-    fwd.launch(pairs, None)
+    fwd.launch(pairs, None if len(pairs) > 1 else True)      # (its own chunk alone is no sequence of several)
     if remote is not None:
         parts = [remote[st.recv_from] for st in sched if st.recv_from >= 0]
         if len({(o.stride(), l.stride()) for o, l in parts}) == 1:
@@ -184,7 +184,7 @@ def _backward_at_hand(Q, K, V, dO, scale, sched, w, bufs: Buffers):
     B.dfa_delta(_chunk(bufs.O, w, c), _chunk(dO, w, c), delta=_chunk(bufs.delta, w, c))
     bwd = B.BackwardChunks(Q, K, V, bufs.L, bufs.delta, dO, bufs.dQ, bufs.dK, bufs.dV, c, scale)
     own = [st.kv_chunk for st in sched if st.kind in (B.DFA_STEP_DIAG, B.DFA_STEP_OWN)]
-    if Q.dtype == torch.bfloat16 and K.shape[0] % 8 and Q.shape[0] * c * c > 3 << 27:
+    if len(own) == 1 or (Q.dtype == torch.bfloat16 and K.shape[0] % 8 and Q.shape[0] * c * c > 3 << 27):
         for kc in own:
             bwd.launch([(w, kc, kc != w, False)], kc == w)
     else:
@@ -271,11 +271,13 @@ def _lists_with_remainders(h_q, h_kv, c, P, mode):
 
 
 def _how_at_once(Q, K, bufs: Buffers, P, mode):
-    """(as one causal call, as walks): how the forward of all workers goes out.  In bf16 neither may hold less of the weights than the
+    """(as one causal call, as walks): how the forward of all workers goes out.  (One worker's only pair is that call.)  In bf16 neither may hold less of the weights than the
     lists of pairs do; walks take all in the form of the shortest list, which is the slower one for the others of
     long chunks (ring, us, steps / walks: 32 over 8 heads x 8 x 512 292 / 288, 16 over 4 x 8 x 700 292 / 263, 8 over 2 x 16 x
     1000 879 / 968)."""
     c = bufs.c
+    if P == 1:
+        return True, True
     if Q.dtype != torch.bfloat16 or c < 1:
         return False, True
     lists, sequence = _lists_with_remainders(Q.shape[0], K.shape[0], c, P, mode)

@@ -22,15 +22,17 @@ def test_share_computes_the_schedules_pairs(monkeypatch, P):
     log = []
 
     def span(self, qc, lo, hi, acc_q, acc_kv, stream=None):
-        assert not acc_q and not acc_kv
+        assert not acc_q and not acc_kv and lo < hi
         log.extend(("bwd", qc, kc) for kc in range(lo, hi + 1))
 
     def pairs(self, items, causal, stream=None):
-        assert not causal and all(acc_kv and not acc_q for _, _, acc_q, acc_kv in items)
+        if causal:      # its own chunk alone: a pair, not a sequence of several chunks
+            assert items == [(w, w, False, False)]
+        assert causal or all(acc_kv and not acc_q for _, _, acc_q, acc_kv in items)
         log.extend(("bwd", qc, kc) for qc, kc, _, _ in items)
 
     monkeypatch.setattr(B.ForwardChunks, "launch", lambda self, items, causal, stream=None: log.extend(
-        ("fwd", qc, kc, dest[4][0] is bufs.O, acc) for qc, kc, dest, _, acc in items))
+        ("fwd", qc, kc, dest[4][0] is bufs.O, acc) for qc, kc, dest, _, acc in items if causal is (None if len(items) > 1 else True)))
     monkeypatch.setattr(B.BackwardChunks, "launch_span", span)
     monkeypatch.setattr(B.BackwardChunks, "launch", pairs)
     monkeypatch.setattr(B, "dfa_merge_batch", lambda o, lse, rows, parts: log.extend(("merge", i) for i, _, _ in parts))
