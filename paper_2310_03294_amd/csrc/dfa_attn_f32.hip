@@ -736,26 +736,31 @@ int fwd_form(Args& p, const dfa_shape& sh, hipStream_t st) {
   return parts == 4 ? fwd<64, 4, Args>(p, st) : parts == 2 ? fwd<64, 2, Args>(p, st) : fwd<64, 1, Args>(p, st);
 }
 
-// Spans.  Parts per tile (NS) and parts that the keys of a span are cut in, by an estimate with what one box measured at d =
-// 128: 6 us per workgroup and, per tile of a walk, 8 us with 4 parts of 32 keys, 6.1 with 2 (11.4 where two workgroups share a
-// CU); a launch that runs in one round takes its longest walk, a longer one the device's even share and half a walk; the
-// merge 5 us and 3 TB/s.
+// Spans.  Parts per tile (NS) and parts that the keys of a span are cut in, by an estimate launch by launch, fitted to 130 forwards of
+// shares and of all workers, every division timed (chosen / best 1.02 in the mean): 6 us per workgroup and, per tile of a walk at d =
+// 128, 9 us with 4 parts of 32 keys, 6.1 with 2 (9.8 where two workgroups share a CU); a launch that runs in one round takes its
+// longest walk, a longer one the device's even share and a third of a walk; the merge 5 us and 3 TB/s.  (Taking all spans as
+// one launch and keys as they are made tiny and many-launch calls slower than their pairs: 64 over 8 heads x 8 x 94, window 1,
+// forward 99 pairs, 113 so; one head x 8 x 445, ring 179 / 188.)  One part of each tile (128 rows) was timed too: within
+// 3 % either way of two parts on the longest shares, slower elsewhere.
 struct SpanPlan { int ns, parts; double us; };
 SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_t ws_bytes) {
   SpanPlan best{0, 1, 0.};
   const double width = sh.d == 128 ? 1.0 : 0.55;
   for (int ns : {4, 2}) {
     const int64_t blocks = blocks_of(sh.s_q, 128 / ns) * sh.h_q;
-    for (int parts = 1; parts <= MAX_SPAN_PARTS; ++parts) {
-      const SpanWork w = span_work(sh, spans, n, parts, blocks);
-      if (parts > 1 && (!w.cut || w.part_bytes > ws_bytes)) break;
-      const bool shared = ns == 2 && w.workgroups > 256;
-      const double tile = width * (ns == 4 ? 8.0 : shared ? 11.4 : 6.1) / (32 * ns);      // per key
-      SpanPlan x{ns, parts, 6 + w.longest * tile};
-      if (w.workgroups > (ns == 4 ? 256 : 512))
-        x.us = std::max(x.us, 6 + w.keys * tile / (shared ? 512 : 256) + 0.45 * w.longest * tile);
-      if (w.cut) x.us += 5 + 2 * w.part_bytes / 3e6;
-      if (!best.ns || x.us < best.us) best = x;
+    const int keys_of_tile = ns == 4 ? 128 : 64;
+    for (int parts : {1, 2, 3, 4, 6, 8, 12, 16}) {
+      int64_t bytes = 0;
+      const double us = sum_of_launches(sh, spans, n, parts, MAX_PAIRS, blocks, keys_of_tile, bytes, [&](const SpanWork& w) {
+        const bool shared = ns == 2 && w.workgroups > 256;
+        const double tile = width * (ns == 4 ? 9.0 : shared ? 9.8 : 6.1) / keys_of_tile;      // per key
+        double x = 6 + w.longest * tile;
+        if (w.workgroups > (ns == 4 ? 256 : 512)) x = std::max(x, 6 + w.keys * tile / (shared ? 512 : 256) + 0.3 * w.longest * tile);
+        return x + (w.cut ? 5 + 2 * w.part_bytes / 3e6 : 0);
+      });
+      if (parts > 1 && (!bytes || bytes > ws_bytes)) break;
+      if (!best.ns || us < best.us) best = {ns, parts, us};
     }
   }
   return best;

@@ -64,6 +64,35 @@ inline SpanWork span_work(const dfa_shape& sh, const dfa_fwd_span* spans, int n,
   return w;
 }
 
+// The same launch by launch, as run_spans makes them of up to `per` parts, keys counted in whole tiles: us_of(work of a launch) summed
+// up; bytes: of the parts' results of all.
+template <class F>
+double sum_of_launches(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int parts, int per, int64_t blocks, int tile, int64_t& bytes, F us_of) {
+  SpanWork w{0, 0., 0., 0, false};
+  double us = 0;
+  int count = 0;
+  bytes = 0;
+  for (int i = 0; i < n; ++i) {
+    const int np = span_parts(sh, spans[i], parts);
+    if (count + np > per) {
+      us += us_of(w);
+      w = SpanWork{0, 0., 0., 0, false};
+      count = 0;
+    }
+    for (int j = 0, k0 = 0; j < np; ++j) {
+      const int k1 = span_cut(sh, spans[i], np, j + 1);
+      const double keys = static_cast<double>((k1 - k0 + tile - 1) / tile * tile);
+      w.longest = std::max(w.longest, keys);
+      w.keys += blocks * (keys - (j + 1 == np && spans[i].own ? sh.s_q / 2 / tile * tile : 0));
+      k0 = k1;
+    }
+    w.workgroups += blocks * np;
+    if (np > 1) { w.part_bytes += np * part_floats(sh) * 4; bytes += np * part_floats(sh) * 4; w.cut = true; }
+    count += np;
+  }
+  return us + us_of(w);
+}
+
 // The spans' parts, up to PER to a launch (launch(parts, count)), each launch followed by the merge of the spans that were
 // cut, through ws.
 template <int PER, class Launch>

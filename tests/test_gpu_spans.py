@@ -38,9 +38,9 @@ FWD = [
     (BF16, 128, 64, 64, 1000, [(3, 0, 3), (2, 0, 2), (1, 0, 1), (0, 0, 0)], (2,), (256, 1, 1)),
     (BF16, 128, 8, 2, 2304, [(2, 0, 2)], (0,), (256, 1, 3)),                           # the diagonal pair apart, the keys before it cut
     (BF16, 128, 8, 4, 2200, [(2, 0, 2), (1, 0, 0)], (1,), (128, 2, 1)),                # the diagonal pair apart
-    (F32, 128, 2, 1, 100, [(4, 0, 4), (1, 1, 1), (3, 0, 2)], (0,), (32, 4, 4)),
+    (F32, 128, 2, 1, 100, [(4, 0, 4), (1, 1, 1), (3, 0, 2)], (0,), (32, 4, 3)),
     (F32, 64, 3, 3, 70, [(2, 0, 2), (0, 0, 0)], (1,), (32, 4, 1)),
-    (F32, 128, 40, 20, 200, [(2, 0, 2), (1, 0, 0), (0, 0, 0)], (1,), (32, 4, 1)),
+    (F32, 128, 40, 20, 200, [(2, 0, 2), (1, 0, 0), (0, 0, 0)], (1,), (64, 2, 4)),
     (F32, 128, 48, 16, 300, [(2, 0, 2)], (0,), (64, 2, 1)),
     (F32, 64, 48, 16, 300, [(2, 0, 2)], (), (64, 2, 1)),
 ]
