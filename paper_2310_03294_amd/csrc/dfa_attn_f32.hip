@@ -750,16 +750,16 @@ SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_
   for (int ns : {4, 2}) {
     const int64_t blocks = blocks_of(sh.s_q, 128 / ns) * sh.h_q;
     const int keys_of_tile = ns == 4 ? 128 : 64;
-    for (int parts : {1, 2, 3, 4, 6, 8, 12, 16}) {
-      int64_t bytes = 0;
-      const double us = sum_of_launches(sh, spans, n, parts, MAX_PAIRS, blocks, keys_of_tile, bytes, [&](const SpanWork& w) {
+    for (int parts : SPAN_CUTS) {
+      const int64_t bytes = parts_bytes(sh, spans, n, parts);
+      if (parts > 1 && (!bytes || bytes > ws_bytes)) break;
+      const double us = sum_of_launches(sh, spans, n, parts, MAX_PAIRS, blocks, keys_of_tile, [&](const LaunchWork& w) {
         const bool shared = ns == 2 && w.workgroups > 256;
         const double tile = width * (ns == 4 ? 9.0 : shared ? 9.8 : 6.1) / keys_of_tile;      // per key
         double x = 6 + w.longest * tile;
         if (w.workgroups > (ns == 4 ? 256 : 512)) x = std::max(x, 6 + w.keys * tile / (shared ? 512 : 256) + 0.3 * w.longest * tile);
         return x + (w.cut ? 5 + 2 * w.part_bytes / 3e6 : 0);
       });
-      if (parts > 1 && (!bytes || bytes > ws_bytes)) break;
       if (!best.ns || us < best.us) best = {ns, parts, us};
     }
   }
@@ -977,7 +977,7 @@ int launch_span_f32(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void*
 }
 
 int64_t span_f32_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
-  return span_work(sh, spans, n, span_plan(sh, spans, n, MAX_SPAN_BYTES).parts, 1).part_bytes;
+  return parts_bytes(sh, spans, n, span_plan(sh, spans, n, MAX_SPAN_BYTES).parts);
 }
 
 dfa_form fwd_f32_form(const dfa_shape& sh, int n) {

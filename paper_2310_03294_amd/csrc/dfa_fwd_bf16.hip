@@ -1063,25 +1063,30 @@ Remainders remainders(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
   return owners && causal_with_remainders(sh.s_q, n64 * last_launch(owners)) ? Remainders::OWN : Remainders::NONE;
 }
 
-// The spans of a launch.  Which form, and in how many parts the keys of a span are cut (the parts are merged afterwards):
-// by an estimate, with what one box measured for its terms: 8 us per workgroup and, per 64 keys, 0.95 us with 64-row
-// workgroups (four key parts), 1.1 with 128-row ones (two) and 1.9 with 256-row ones; a launch that runs in one round takes its
-// longest walk, a longer one the device's even share and about half a walk; the merge 5 us and 3 TB/s.
+// Which form, and in how many parts the keys of a span are cut (the parts are merged afterwards): by an estimate launch by launch,
+// fitted to 154 forwards of shares and windows of 64 to 5000 rows, every division timed (chosen / best 1.004 in the mean, none
+// slower than the pairs one by one): 8 us and, per tile of 64 keys, 1.0 us with 64-row workgroups (four key parts), 1.3 with
+// 128-row ones (two) and 1.7 with 256-row ones; a launch that runs in one round takes its longest walk, a longer one the device's
+// even share and about half a walk; the merge 8 us and 3 TB/s.  (With 1.1 and 1.9, as measured on walks that fill the device less,
+// 128 rows were taken too often: us, pairs / so / now: 32 over 8 heads, 3 chunks of 3200 476 / 550 / 431, 64 over 8, 2 of 704
+// 53 / 59 / 40, 16 over 4, 3 of 4158 493 / 551 / 402.)
 struct SpanPlan { int rows, parts; double us; };
 
 SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, bool all_remainders, int64_t ws_bytes) {
   SpanPlan best{};
   for (int rows : {64, 128, 256}) {
     if (rows > 64 && all_remainders) break;
-    const double tile = rows == 64 ? 0.95 : rows == 128 ? 1.1 : 1.9;
+    const double tile = (rows == 64 ? 1.0 : rows == 128 ? 1.3 : 1.7) / BN;      // per key
     const int64_t blocks = (static_cast<int64_t>(sh.s_q) + rows - 1) / rows * sh.h_q;
-    for (int parts = 1; parts <= MAX_SPAN_PARTS; ++parts) {
-      const SpanWork w = span_work(sh, spans, n, parts, blocks);
-      if (parts > 1 && (!w.cut || w.part_bytes > ws_bytes)) break;
-      SpanPlan x{rows, parts, 8 + w.longest / 64 * tile};
-      if (w.workgroups > 256) x.us = std::max(x.us, 8 + w.keys / 64 * tile / 256 + 0.45 * w.longest / 64 * tile);
-      if (w.cut) x.us += 5 + 2 * w.part_bytes / 3e6;
-      if (!best.rows || x.us < best.us) best = x;
+    for (int parts : SPAN_CUTS) {
+      const int64_t bytes = parts_bytes(sh, spans, n, parts);
+      if (parts > 1 && (!bytes || bytes > ws_bytes)) break;
+      const double us = sum_of_launches(sh, spans, n, parts, MAX_PAIRS, blocks, BN, [&](const LaunchWork& w) {
+        double x = 8 + w.longest * tile;
+        if (w.workgroups > 256) x = std::max(x, 8 + w.keys * tile / 256 + 0.45 * w.longest * tile);
+        return x + (w.cut ? 8 + 2 * w.part_bytes / 3e6 : 0);
+      });
+      if (!best.rows || us < best.us) best = {rows, parts, us};
     }
   }
   return best;
@@ -1108,6 +1113,7 @@ struct WithoutOwn {
   dfa_fwd_pair pair[MAX_PAIRS];
   dfa_fwd_span rest[MAX_PAIRS];
   int pairs = 0, spans = 0;
+  bool chunks = true;      // what is left are single chunks: full pairs
   WithoutOwn(const dfa_shape& sh, const dfa_fwd_span* spans_, int n) {
     for (int i = 0; i < n; ++i) {
       dfa_fwd_span x = spans_[i];
@@ -1120,6 +1126,7 @@ struct WithoutOwn {
         x.accumulate = 1;
       }
       if (x.n_keys > 0) rest[spans++] = x;
+      chunks &= x.n_keys == 0 || x.n_keys == sh.s_q;
     }
   }
 };
@@ -1198,7 +1205,7 @@ int run_spans_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, bool a
 }
 
 int64_t span_bytes(const dfa_shape& sh, const dfa_fwd_span* spans, int n, bool all_remainders) {
-  return span_work(sh, spans, n, span_plan(sh, spans, n, all_remainders, MAX_SPAN_BYTES).parts, 1).part_bytes;
+  return parts_bytes(sh, spans, n, span_plan(sh, spans, n, all_remainders, MAX_SPAN_BYTES).parts);
 }
 
 dfa_shape own_pair(dfa_shape sh) {
@@ -1219,7 +1226,20 @@ int launch_span_bf16(const dfa_shape& sh, const dfa_fwd_span* spans, int n, void
   for (int i = 0; i < n; i += MAX_PAIRS) {
     const WithoutOwn x(sh, spans + i, std::min(MAX_PAIRS, n - i));
     int rc = x.pairs ? launch_pairs(own, x.pair, x.pairs, false, st) : DFA_OK;
-    if (rc == DFA_OK && x.spans) rc = run_spans_bf16(sh, x.rest, x.spans, false, ws, ws_bytes, st);
+    if (rc == DFA_OK && x.spans) {
+      if (x.chunks) {      // (8 heads x 2048, four helpers' pairs 125 us as walks, 91 as a list with the diagonal)
+        dfa_shape full = own;
+        full.causal = 0;
+        dfa_fwd_pair pairs[MAX_PAIRS];
+        for (int j = 0; j < x.spans; ++j) {
+          const dfa_fwd_span& y = x.rest[j];
+          pairs[j] = {y.q, y.k, y.v, y.o, y.lse, y.o_stride_h, y.o_stride_s, y.lse_stride_h, y.accumulate, 0};
+        }
+        rc = launch_pairs(full, pairs, x.spans, false, st);
+      } else {
+        rc = run_spans_bf16(sh, x.rest, x.spans, false, ws, ws_bytes, st);
+      }
+    }
     if (rc) return rc;
   }
   return DFA_OK;
@@ -1232,7 +1252,7 @@ int64_t span_bf16_workspace(const dfa_shape& sh, const dfa_fwd_span* spans, int 
   int64_t most = 0;
   for (int i = 0; i < n; i += MAX_PAIRS) {
     const WithoutOwn x(sh, spans + i, std::min(MAX_PAIRS, n - i));
-    if (x.spans) most = std::max(most, span_bytes(sh, x.rest, x.spans, false));
+    if (x.spans && !x.chunks) most = std::max(most, span_bytes(sh, x.rest, x.spans, false));
   }
   return most;
 }
@@ -1256,7 +1276,10 @@ dfa_form span_bf16_form(const dfa_shape& sh, const dfa_fwd_span* spans, int n, i
   };
   if (rem != Remainders::OWN) return of(spans, n);
   const WithoutOwn x(sh, spans, std::min(MAX_PAIRS, n));
-  return x.spans ? of(x.rest, x.spans) : fwd_bf16_form(own_pair(sh), x.pairs);
+  dfa_shape pair = own_pair(sh);
+  if (!x.spans) return fwd_bf16_form(pair, x.pairs);
+  pair.causal = 0;
+  return x.chunks ? fwd_bf16_form(pair, x.spans) : of(x.rest, x.spans);
 }
 
 }  // namespace dfa

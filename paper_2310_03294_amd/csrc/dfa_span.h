@@ -42,41 +42,35 @@ inline int span_cut(const dfa_shape& sh, const dfa_fwd_span& x, int parts, int i
   return static_cast<int>(std::min<int64_t>(std::max<int64_t>(visible * i / parts / 128, i), tiles - (parts - 1 - i) + (x.own ? 0 : -1)) * 128);
 }
 
-// What a cut in at most `parts` gives, with `blocks` workgroups per part: workgroups, their keys, the longest walk, bytes of
-// the parts' results; cut: whether any span is in more than one part.
-struct SpanWork { int64_t workgroups; double keys, longest; int64_t part_bytes; bool cut; };
 inline int64_t part_floats(const dfa_shape& sh) {
   const int64_t o = static_cast<int64_t>(sh.h_q) * sh.s_q * sh.d, lse = static_cast<int64_t>(sh.h_q) * sh.s_q;
   return o + (lse + 3) / 4 * 4;      // keeps the next part's o on 16 bytes
 }
-inline SpanWork span_work(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int parts, int64_t blocks) {
-  SpanWork w{0, 0., 0., 0, false};
+// Bytes of the parts' results of a cut in at most `parts`.
+inline int64_t parts_bytes(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int parts) {
+  int64_t results = 0;
   for (int i = 0; i < n; ++i) {
     const int np = span_parts(sh, spans[i], parts);
-    for (int j = 0; j < np; ++j) {
-      const int keys = span_cut(sh, spans[i], np, j + 1) - span_cut(sh, spans[i], np, j);
-      w.longest = std::max(w.longest, static_cast<double>(keys));
-      w.keys += static_cast<double>(blocks) * (keys - (j + 1 == np && spans[i].own ? sh.s_q / 2 : 0));
-    }
-    w.workgroups += blocks * np;
-    if (np > 1) { w.part_bytes += np * part_floats(sh) * 4; w.cut = true; }
+    results += np > 1 ? np : 0;
   }
-  return w;
+  return results * part_floats(sh) * 4;
 }
 
-// The same launch by launch, as run_spans makes them of up to `per` parts, keys counted in whole tiles: us_of(work of a launch) summed
-// up; bytes: of the parts' results of all.
+// What a launch does: workgroups, their keys in whole tiles, the longest walk, bytes of the parts' results; cut: whether any of its
+// spans is in more than one part.
+struct LaunchWork { int64_t workgroups; double keys, longest; int64_t part_bytes; bool cut; };
+// The launches that run_spans makes of a cut in at most `parts`, up to `per` parts to a launch, with `blocks` workgroups per part:
+// us_of(LaunchWork) summed up.
 template <class F>
-double sum_of_launches(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int parts, int per, int64_t blocks, int tile, int64_t& bytes, F us_of) {
-  SpanWork w{0, 0., 0., 0, false};
+double sum_of_launches(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int parts, int per, int64_t blocks, int tile, F us_of) {
+  LaunchWork w{0, 0., 0., 0, false};
   double us = 0;
   int count = 0;
-  bytes = 0;
   for (int i = 0; i < n; ++i) {
     const int np = span_parts(sh, spans[i], parts);
     if (count + np > per) {
       us += us_of(w);
-      w = SpanWork{0, 0., 0., 0, false};
+      w = LaunchWork{0, 0., 0., 0, false};
       count = 0;
     }
     for (int j = 0, k0 = 0; j < np; ++j) {
@@ -87,11 +81,12 @@ double sum_of_launches(const dfa_shape& sh, const dfa_fwd_span* spans, int n, in
       k0 = k1;
     }
     w.workgroups += blocks * np;
-    if (np > 1) { w.part_bytes += np * part_floats(sh) * 4; bytes += np * part_floats(sh) * 4; w.cut = true; }
+    if (np > 1) { w.part_bytes += np * part_floats(sh) * 4; w.cut = true; }
     count += np;
   }
   return us + us_of(w);
 }
+constexpr int SPAN_CUTS[] = {1, 2, 3, 4, 6, 8, 12, MAX_SPAN_PARTS};      // numbers of parts that are tried
 
 // The spans' parts, up to PER to a launch (launch(parts, count)), each launch followed by the merge of the spans that were
 // cut, through ws.

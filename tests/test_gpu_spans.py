@@ -31,13 +31,14 @@ FWD = [
     (BF16, 128, 40, 8, 300, [(2, 0, 2), (0, 0, 0), (1, 0, 0)], (2,), (64, 4, 1)),
     (BF16, 128, 64, 16, 300, [(2, 0, 2)], (0,), (128, 2, 1)),
     (BF16, 128, 64, 8, 300, [(2, 0, 2), (0, 0, 0), (1, 0, 0)], (2,), (128, 2, 1)),     # with a diagonal alone and no own keys
-    (BF16, 128, 64, 64, 1024, [(3, 0, 3), (0, 0, 0)], (1,), (128, 2, 1)),
+    (BF16, 128, 40, 8, 600, [(2, 0, 2)], (0,), (128, 2, 1)),
     (BF16, 128, 64, 64, 1024, [(3, 0, 3)], (0,), (256, 1, 1)),                         # whole tiles
     (BF16, 128, 64, 16, 1000, [(3, 0, 3)], (), (256, 1, 1)),                           # ragged
     (BF16, 128, 64, 16, 1280, [(2, 0, 2), (0, 0, 0)], (1,), (256, 1, 1)),              # whole tiles, with a diagonal alone
     (BF16, 128, 64, 64, 1000, [(3, 0, 3), (2, 0, 2), (1, 0, 1), (0, 0, 0)], (2,), (256, 1, 1)),
     (BF16, 128, 8, 2, 2304, [(2, 0, 2)], (0,), (256, 1, 3)),                           # the diagonal pair apart, the keys before it cut
-    (BF16, 128, 8, 4, 2200, [(2, 0, 2), (1, 0, 0)], (1,), (128, 2, 1)),                # the diagonal pair apart
+    (BF16, 128, 8, 4, 2200, [(2, 0, 2), (1, 0, 0)], (1,), (256, 1, 2)),                # the same beside a pair
+    (BF16, 128, 8, 4, 2100, [(2, 1, 2), (1, 0, 0), (0, 0, 0)], (1,), (128, 2, 1)),     # diagonal and full pairs alone: lists
     (F32, 128, 2, 1, 100, [(4, 0, 4), (1, 1, 1), (3, 0, 2)], (0,), (32, 4, 3)),
     (F32, 64, 3, 3, 70, [(2, 0, 2), (0, 0, 0)], (1,), (32, 4, 1)),
     (F32, 128, 40, 20, 200, [(2, 0, 2), (1, 0, 0), (0, 0, 0)], (1,), (64, 2, 4)),
