@@ -98,6 +98,42 @@ int main() {
     EXPECT(dfa_delta(&sh, fake, nullptr, ffake, nullptr) == DFA_ERR_NULL);
     EXPECT(dfa_chunk_fwd(nullptr, fake, fake, fake, fake, ffake, nullptr) == DFA_ERR_NULL);
   }
+  // ---- forms and scratch of lists and spans: what the plans calculate with, at the ends of the ranges
+  for (int dtype : {DFA_BF16, DFA_F32}) {
+    for (int causal = 0; causal < 2; ++causal) {
+      for (int32_t heads : {1, 5, 1 << 20, INT32_MAX}) {
+        for (int32_t s_q : {1, 31, 64, 1 << 22, INT32_MAX}) {
+          for (int32_t s_k : {1, s_q, INT32_MAX}) {
+            dfa_shape sh = base_shape();
+            sh.h_q = heads; sh.h_kv = heads % 2 ? 1 : heads / 2; sh.d = 128; sh.dtype = dtype; sh.causal = causal;
+            sh.s_q = s_q; sh.s_k = s_k;
+            sh.q_stride_s = sh.kv_stride_s = sh.o_stride_s = sh.dq_stride_s = sh.dkv_stride_s = 128;
+            dfa_fwd_span spans[17];
+            std::memset(spans, 0, sizeof(spans));
+            for (dfa_fwd_span& x : spans) {
+              x.q = x.k = x.v = x.o = fake; x.lse = ffake; x.lse_stride_h = s_q;
+              x.o_stride_h = int64_t{128} * s_q; x.o_stride_s = 128; x.n_keys = s_k; x.own = causal;
+            }
+            for (int32_t n : {1, 2, 17, INT32_MAX}) {
+              for (int64_t ws : {int64_t{0}, int64_t{1}, int64_t{1} << 27, INT64_MAX}) {
+                dfa_form f{-1, -1, -1, -1};
+                if (dfa_chunk_fwd_form(&sh, n, &f) == DFA_OK) EXPECT(f.rows > 0 && f.parts > 0 && f.q_cuts == 0);
+                for (int want = 1; want < 4; ++want) {
+                  if (dfa_chunk_bwd_form(&sh, n, want & 1, want & 2, ws, &f) == DFA_OK) EXPECT(f.rows > 0 && f.cuts > 0 && f.q_cuts > 0);
+                  if (dfa_span_bwd_form(&sh, want & 1, want & 2, ws, &f) == DFA_OK) EXPECT(f.rows > 0 && f.cuts > 0 && f.q_cuts > 0);
+                  EXPECT(dfa_chunk_bwd_workspace(&sh, n, want & 1, want & 2) <= int64_t{1} << 27);
+                  EXPECT(dfa_span_bwd_workspace(&sh, want & 1, want & 2) <= int64_t{1} << 27);
+                }
+                if (n > 17) continue;
+                if (dfa_span_fwd_form(&sh, spans, n, ws, &f) == DFA_OK) EXPECT(f.rows > 0 && f.cuts > 0 && f.q_cuts == 0);
+                EXPECT(dfa_span_fwd_workspace(&sh, spans, n) <= int64_t{1} << 27);
+              }
+            }
+          }
+        }
+      }
+    }
+  }
   {
     double flop = -1.0;
     EXPECT(dfa_mfma_probe(nullptr, 1 << 20, 10, &flop, nullptr) == DFA_ERR_NULL);
