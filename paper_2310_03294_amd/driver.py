@@ -199,7 +199,7 @@ def run_worker_share(Q, K, V, dO, scale, P, w, bufs: Buffers, remote, fused=True
     the D pre-pass and the backward of the same pairs.  The gradient chunks the share touches are
     overwritten with the share's own sums (first contribution overwrites, the rest accumulate).
     fused: all chunks and partials being there, the worker's pairs are one walk each way (a short chunk's step by step: 8 heads x 512,
-    P = 8, 183 us, as one walk 72); otherwise step by step."""
+    P = 8, 183 us, as one walk 74); otherwise step by step."""
     sched = B.dfa_schedule(P, w)
     if fused and _fits_a_call(len(sched) * bufs.c, K, bufs.dK):
         _forward_at_hand(Q, K, V, scale, sched, w, bufs, remote)
@@ -271,10 +271,10 @@ def _lists_with_remainders(h_q, h_kv, c, P, mode):
 
 
 def _how_at_once(Q, K, bufs: Buffers, P, mode):
-    """(as one causal call, as walks): how the forward of all workers goes out.  (One worker's only pair is that call.)  In bf16 neither may hold less of the weights than the
-    lists of pairs do; walks take all in the form of the shortest list, which is the slower one for the others of
-    long chunks (ring, us, steps / walks: 32 over 8 heads x 8 x 512 292 / 288, 16 over 4 x 8 x 700 292 / 263, 8 over 2 x 16 x
-    1000 879 / 968)."""
+    """(as one causal call, as walks): how the forward of all workers goes out.  (One worker's only pair is that call.)  In
+    bf16 neither may hold less of the weights than the lists of pairs do; walks take all in the form of the shortest list,
+    which is the slower one for the others of long chunks (ring, us, steps / walks: 32 over 8 heads x 8 x 512 292 / 288,
+    16 over 4 x 8 x 700 292 / 263, 8 over 2 x 16 x 1000 879 / 968)."""
     c = bufs.c
     if P == 1:
         return True, True
