@@ -346,9 +346,10 @@ def run_all_workers(Q, K, V, dO, scale, P, bufs: Buffers, mode="balanced", backw
     fused: OWN pairs continue from the owner's state instead of partial + merge, and pairs that do not wait for each other go
     out as one launch (a pair of small chunks alone leaves most of one device idle): all of the owners' as one walk
     per owner, or, in bf16 and where the pairs are those of every chunk with itself and all earlier ones, all pairs as one
-    causal call (where that is as precise: _how_at_once), which has no partials to write, read and merge (us, forward, walks / one call: 32 over 8 heads x 8 x 1024
-    608 / 503, 8 over 2 x 8 x 2048 596 / 479, 32 x 8 x 300 141 / 72, 8 x 4 x 512 38 / 32; not in fp32, where the walks cut
-    the keys of the last rows in parts: 8 over 2 heads x 4 x 1024 385 / 478, d = 64, 2 over 1 x 3 x 700 43 / 74);
+    causal call (where that is as precise: _how_at_once), which has no partials to write, read and merge (us, forward,
+    walks / one call: 32 over 8 heads x 8 x 1024 608 / 503, 8 over 2 x 8 x 2048 596 / 479, 32 x 8 x 300 141 / 72, 8 x 4 x 512
+    38 / 32; not in fp32, where the walks cut the keys of the last rows in parts: 8 over 2 heads x 4 x 1024 385 / 478, d = 64,
+    2 over 1 x 3 x 700 43 / 74);
     otherwise time step by time step, pair by pair.
     at_once False: the schedule as it is written, fused or not: every pair computed as such at its time step, the partials of the
     helpers written, handed over and merged at theirs, and the backward's pairs in the same order."""
