@@ -12,16 +12,17 @@
 //                                        to its partner through LDS, dV^T += dO^T P
 //    "dP" wavefront (V^T in registers):  dP - D = dO V^T - D (the MFMA chains start from -D),
 //                                        dS = P o (dP - D), dK^T += Q^T dS
-//  (queries x keys tiles on v_mfma_f32_32x32x16_bf16: each lane holds 16 queries of ONE key; P
+//  (queries x keys tiles on v_mfma_f32_16x16x32_bf16: each lane holds 16 queries of TWO keys; P
 //  and dS are fed back from registers as B operands; dO^T, Q^T are gathered from LDS with the
-//  transposing read).  The dP wavefronts run one tile behind, so one barrier per tile suffices.
+//  transposing read; with 32x32x16 products a full pair of 32 heads x 16384 took 12216 us, 11492
+//  so).  The dP wavefronts run one tile behind, so one barrier per tile suffices.
 //  Wavefronts raise their priority while they issue MFMAs, so that the other kind's VALU work
 //  fills the gaps instead of delaying them.
 //  dv / dk are written once per workgroup (summed over the group's query heads in registers).
 //
 //  k_bwd_dq_bf16 (query-stationary).  A workgroup owns 128 or 256 query rows of one head (Q^T, dO^T,
 //  lse, D in registers) and walks over the key/value chunk in tiles of 64 rows in LDS: S^T = K Q^T,
-//  dP^T = V dO^T (keys x queries: each lane holds 16 keys of ONE query, so lse and D are per-lane
+//  dP^T = V dO^T (keys x queries: each lane holds 8 keys of TWO queries, so lse and D are per-lane
 //  scalars), dS^T from registers as the B operand of dQ^T += K^T dS^T.
 //
 // The fused alternative (one kernel, dq by fp32 atomics) was measured first: the L2 atomic units
@@ -82,7 +83,7 @@ namespace kv {
 constexpr int NT = 512;     // 8 wavefronts: 4 "S" wavefronts (dV) and 4 "dP" wavefronts (dK)
 constexpr int BN = 128;     // key rows per workgroup, 32 per wavefront pair
 constexpr int BM = 64;      // query rows per LDS tile
-constexpr int QTILE_BYTES = BM * kRowBytes;   // rows padded to 272 B
+constexpr int QTILE_BYTES = kTile64;
 constexpr int LD_BYTES = 1024;                // lse'[64], -D[64], 128 spare floats
 constexpr int PX_BYTES = 4 * 4096;            // P hand-over: 4 key blocks x (64 x 32 bf16)
 // LDS map.  Tile t lives in Q slot t % 3, dO slot t % 2, lse/D slot t % 3, P slot t % 2.
@@ -96,10 +97,8 @@ constexpr int PART_F4 = 8 * 16 * 64;
 
 // The Q and dO tiles go from global memory straight into LDS (global_load_lds_dwordx4: every
 // lane supplies its own global address, the wavefront's 64 x 16 bytes land contiguously at the
-// LDS address in M0).  A padded tile is 17 such 1 KB pieces; of the four wavefronts that copy a
-// tile, wavefront w moves pieces 4w .. 4w + 3 and (w = 0 only) 16.  Byte 16 s of the tile is chunk
-// s % 17 of physical row s / 17; chunk 16 is the pad (it receives a copy of chunk 15).  Only
-// lse / D pass through a register.  The S wavefronts copy the Q tiles, the dP wavefronts the dO
+// LDS address in M0).  A tile is 16 such 1 KB pieces; of the four wavefronts that copy a
+// tile, wavefront w moves the four of its rows 16w .. 16w + 15.  Only lse / D pass through a register.  The S wavefronts copy the Q tiles, the dP wavefronts the dO
 // tiles, each piece issued from inline assembly between two MFMAs of a product (the memory pipe
 // takes ~17 cycles per piece and CU: issued in a burst, the pieces stall the wavefront) and waited
 // for just before the slot's barrier.  Measured with time stamps per phase: all staging at the top
@@ -135,11 +134,11 @@ __device__ __forceinline__ void qtile_advance_if(QTileCursor& cur, bool adv, con
 
 // Rows past s_q are clamped to the last row instead of zero-filled: their lse' is +inf, so P and
 // dS vanish for them whatever (finite) Q and dO the tile holds.  Qs, Gs: LDS tiles to fill.
-__device__ __forceinline__ void qtile_copy(const QTileCursor& cur, const TileLane& m, const BwdParams& p,
+__device__ __forceinline__ void qtile_copy(const QTileCursor& cur, const TileLane16& m, const BwdParams& p,
                                            char* Qs, char* Gs, int w, int lane) {
   const uint32_t rowbytes = static_cast<uint32_t>(p.q_ss) * 2;
-  tile_dma(cur.qh, rowbytes, cur.q0, p.s_q - 1, m, Qs, w, lane);
-  tile_dma(cur.gh, rowbytes, cur.q0, p.s_q - 1, m, Gs, w, lane);
+  tile16_copy(tile16_copy_plan(cur.qh, rowbytes, cur.q0, p.s_q - 1, m, Qs, w, lane));
+  tile16_copy(tile16_copy_plan(cur.gh, rowbytes, cur.q0, p.s_q - 1, m, Gs, w, lane));
 }
 
 // lse (S wavefronts 0, 2, 3) or D (S wavefront 1) of the tile's 64 rows, one per lane, into a
@@ -160,62 +159,60 @@ __device__ __forceinline__ void qtile_store(const QTileRegs& t, float* LDs, int 
   LDs[tid] = is_d ? d : l;
 }
 
-// C[qb] += X[qb rows] * B^T over d for both 32-row blocks of the tile: X rows are read from LDS
-// (A operand), B is the wavefront's K^T or V^T held in registers; the caller sets what the chains
-// start from (zero, or -D for the dP products).
+// c[mb][nb] += X[16-row block mb] * B^T[16-key block nb] over d for the tile's 64 rows: X rows are read from LDS
+// (A operand, each for two products), B is the wavefront's K^T or V^T held in registers; the caller sets what the
+// chains start from (zero, or -D for the dP products).
 struct NoHook { __device__ __forceinline__ void operator()(int) const {} };
-// hook(ks) runs after the MFMAs of step ks (the callers issue their tile-copy pieces there)
+// hook(n) runs after the MFMAs of step n = 4 s + mb (the callers issue their tile-copy pieces there)
 template <class Hook = NoHook>
-__device__ __forceinline__ void row_products(f32x16& c0, f32x16& c1, const char* Xs, int a_base,
-                                             const bf16x8 (&bT)[8], Hook hook = Hook()) {
-  constexpr int AHEAD = 3;                      // LDS reads run this many d-steps ahead of the MFMAs
-  bf16x8 x0[AHEAD + 1], x1[AHEAD + 1];
+__device__ __forceinline__ void row_products(f32x4 (&c)[4][2], const char* Xs, int a_base,
+                                             const bf16x8 (&bT)[4][2], Hook hook = Hook()) {
+  constexpr int AHEAD = 6;                      // LDS reads run this many steps ahead of the MFMAs
+  const char* x0 = Xs + a_base;
+  auto off = [](int n) { return (n & 3) * kBlock16 + step16_off(n >> 2); };
+  bf16x8 x[AHEAD + 1];
 #pragma unroll
-  for (int ks = 0; ks < AHEAD; ++ks) {
-    x0[ks] = lds_read_b128(Xs, a_base + ks * 32);
-    x1[ks] = lds_read_b128(Xs, a_base + 32 * kRowBytes + ks * 32);
-  }
+  for (int n = 0; n < AHEAD; ++n) x[n] = lds_read_b128(x0, off(n));
   DFA_SCHED_FENCE();
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) {
-    if (ks + AHEAD < 8) {
-      x0[(ks + AHEAD) % (AHEAD + 1)] = lds_read_b128(Xs, a_base + (ks + AHEAD) * 32);
-      x1[(ks + AHEAD) % (AHEAD + 1)] = lds_read_b128(Xs, a_base + 32 * kRowBytes + (ks + AHEAD) * 32);
-    }
-    c0 = mfma32(x0[ks % (AHEAD + 1)], bT[ks], c0);
-    c1 = mfma32(x1[ks % (AHEAD + 1)], bT[ks], c1);
-    hook(ks);
+  for (int n = 0; n < 16; ++n) {
+    if (n + AHEAD < 16) x[(n + AHEAD) % (AHEAD + 1)] = lds_read_b128(x0, off(n + AHEAD));
+    c[n & 3][0] = mfma16(x[n % (AHEAD + 1)], bT[n >> 2][0], c[n & 3][0]);
+    c[n & 3][1] = mfma16(x[n % (AHEAD + 1)], bT[n >> 2][1], c[n & 3][1]);
+    hook(n);
     DFA_SCHED_FENCE();
   }
 }
 
-// acc[db] += Y^T[db block of d][64 queries] * W[64 queries][32 keys]: Y^T is gathered from the
+// acc[db][nb] += Y^T[16 columns db of d][64 queries] * W[64 queries][16 keys nb]: Y^T is gathered from the
 // row-major LDS tile with the transposing read, W (P or dS) comes from registers in the order
-// an MFMA result tile has (w[qb][half] = rows (e/4)*8 + 4h + e%4 of 16-row half `half`).
-constexpr int COL_AHEAD = 4;              // gathers run this many MFMAs ahead
-__device__ __forceinline__ int col_off(int g_base, int n) {       // n = qb * 8 + half * 4 + db
-  return g_base + ((n >> 3) * 32 + ((n >> 2) & 1) * 16) * kRowBytes + (n & 3) * 64;
+// two MFMA result tiles have (w[u][nb] = query blocks 2u and 2u + 1).
+constexpr int COL_AHEAD = 4;              // gathers run this many steps ahead
+__device__ __forceinline__ bf16x8 col_gather(const char* Ys, const Gather16& m, int n) {       // n = u * 8 + db
+  return gather16(Ys, m, 2 * (n >> 3), n & 7);
 }
 // The first COL_AHEAD gathers of col_products, issued early (e.g. before a barrier) so that the
 // products can start without waiting for LDS.
 // (The pieces are kept as raw 32-bit vectors: carried around a loop as bf16 vectors they would be
 // taken apart into 16-bit halves and put together again.)
-__device__ __forceinline__ void col_prefetch(u32x4 (&y)[COL_AHEAD + 1], const char* Ys, int g_base) {
+__device__ __forceinline__ void col_prefetch(u32x4 (&y)[COL_AHEAD + 1], const char* Ys, const Gather16& m) {
 #pragma unroll
-  for (int n = 0; n < COL_AHEAD; ++n) y[n] = __builtin_bit_cast(u32x4, lds_gather(Ys, col_off(g_base, n)));
+  for (int n = 0; n < COL_AHEAD; ++n) y[n] = __builtin_bit_cast(u32x4, col_gather(Ys, m, n));
 }
 template <bool PRE, class Hook = NoHook>
-__device__ __forceinline__ void col_products(f32x16 (&acc)[4], const char* Ys, int g_base,
+__device__ __forceinline__ void col_products(f32x4 (&acc)[8][2], const char* Ys, const Gather16& m,
                                              const bf16x8 (&w)[2][2], u32x4 (&y)[COL_AHEAD + 1],
                                              Hook hook = Hook()) {
   constexpr int AHEAD = COL_AHEAD;
-  if (!PRE) col_prefetch(y, Ys, g_base);
+  if (!PRE) col_prefetch(y, Ys, m);
   DFA_SCHED_FENCE();
 #pragma unroll
   for (int n = 0; n < 16; ++n) {
     if (n + AHEAD < 16)
-      y[(n + AHEAD) % (AHEAD + 1)] = __builtin_bit_cast(u32x4, lds_gather(Ys, col_off(g_base, n + AHEAD)));
-    acc[n & 3] = mfma32(__builtin_bit_cast(bf16x8, y[n % (AHEAD + 1)]), w[n >> 3][(n >> 2) & 1], acc[n & 3]);
+      y[(n + AHEAD) % (AHEAD + 1)] = __builtin_bit_cast(u32x4, col_gather(Ys, m, n + AHEAD));
+    const bf16x8 a = __builtin_bit_cast(bf16x8, y[n % (AHEAD + 1)]);
+    acc[n & 7][0] = mfma16(a, w[n >> 3][0], acc[n & 7][0]);
+    acc[n & 7][1] = mfma16(a, w[n >> 3][1], acc[n & 7][1]);
     hook(n);
     DFA_SCHED_FENCE();
   }
@@ -234,32 +231,31 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: role branches stay scalar
   const int kb = wave & 3;            // 32-key block of this wavefront
   const bool dp_wave = wave >= 4;     // false: S, P, dV;  true: dP, dS, dK
-  const int r32 = lane & 31, hh = lane >> 5;
-  const int kvrow = k0 + kb * 32 + r32;
-  const bool kvalid = kvrow < p.s_k;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int kvrow = k0 + kb * 32 + r16;                       // and kvrow + 16
   // per-lane LDS bases; everything else in an LDS address is a compile-time constant
-  const int a_base = tile_off(r32, hh);                       // row reads (A operand of S, dP)
-  const int g_base = gather_base(lane);                       // transposed gathers of Q, dO
+  const int a_base = row16_base(lane);                        // row reads (A operand of S, dP)
+  const Gather16 g_base = gather16_bases(lane);               // transposed gathers of Q, dO
 
   // B operands over d of this wavefront's 32 keys: K^T for an S wavefront, V^T for a dP wavefront
-  bf16x8 bT[8];
-  {
-    const __bf16* src = dp_wave ? pr.v : pr.k;
-    const int64_t off = kh * p.kv_sh + static_cast<int64_t>(kvalid ? kvrow : 0) * p.kv_ss + 8 * hh;
+  bf16x8 bT[4][2];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      uint4 a = *reinterpret_cast<const uint4*>(src + off + 16 * ks);
-      if (!kvalid) a = make_uint4(0, 0, 0, 0);
-      bT[ks] = __builtin_bit_cast(bf16x8, a);
+  for (int nb = 0; nb < 2; ++nb) {
+    const int row = kvrow + 16 * nb;
+    const bool ok = row < p.s_k;
+    const __bf16* src = (dp_wave ? pr.v : pr.k) + kh * p.kv_sh + static_cast<int64_t>(ok ? row : 0) * p.kv_ss;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      uint4 a = *reinterpret_cast<const uint4*>(src + step16_col(s, g));
+      if (!ok) a = make_uint4(0, 0, 0, 0);
+      bT[s][nb] = __builtin_bit_cast(bf16x8, a);
     }
   }
 
-  // dV^T (S wavefront) or dK^T (dP wavefront): [d block][d within block][key]
-  f32x16 acc[4];
+  // dV^T (S wavefront) or dK^T (dP wavefront): [d block][key block]
+  f32x4 acc[8][2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 16; ++j) acc[i][j] = 0.f;
+  for (int i = 0; i < 8; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const float c2 = p.scale * LOG2E;
   const int off = p.off;
@@ -292,7 +288,7 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
   }
   const int q_end = q_begin + ntq * BM;
   const uint32_t q_rowbytes = static_cast<uint32_t>(p.q_ss) * 2;
-  const TileLane tl = tile_lane(kb, lane, q_rowbytes);
+  const TileLane16 tl = tile16_lane(kb, lane, q_rowbytes);
   if (!dp_wave) {
     qtile_load_ld(tr, curl, p, tid);
     qtile_store(tr, reinterpret_cast<float*>(smem + OFF_LD), tid, kb == 1);
@@ -311,9 +307,6 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
   // the MFMAs of the other.  Both kinds run niter + 1 slots (the S wavefronts idle in the last,
   // the dP wavefronts have no dS/dK in the first); each kind has its own straight-line loop.
   int slot = 0;            // t % 3
-  f32x16 zero;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) zero[j] = 0.f;
   if (!dp_wave) {
     int q0 = q_begin + it0 % ntq * BM;      // first query row of tile `it`
     for (int it = 0; it < niter; ++it) {
@@ -329,46 +322,49 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
       // compiler's wait for that register would otherwise wait for the copies too.  Then the Q
       // tile it + 1 into ring slot `next`, one piece every other step.
       qtile_advance_if(cur, more, p, q_begin, q_end);
-      const TileCopy cq = tile_copy_plan<RAGGED>(cur.qh, q_rowbytes, cur.q0, p.s_q - 1, tl,
-                                                 smem + OFF_Q + next * QTILE_BYTES, kb, lane);
-      f32x16 c0 = zero, c1 = zero;
+      const TileCopy16 cq = tile16_copy_plan<RAGGED>(cur.qh, q_rowbytes, cur.q0, p.s_q - 1, tl,
+                                                     smem + OFF_Q + next * QTILE_BYTES, kb, lane);
+      f32x4 c[4][2];
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb) c[mb][0] = c[mb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
       __builtin_amdgcn_s_setprio(3);
-      row_products(c0, c1, Qs, a_base, bT, [&](int ks) {          // S = Q K^T
-        if (ks == 0) {
+      row_products(c, Qs, a_base, bT, [&](int n) {          // S = Q K^T
+        if (n == 1) {
           qtile_store(tr, reinterpret_cast<float*>(smem + OFF_LD + next * LD_BYTES), tid, kb == 1);
           qtile_advance_if(curl, it + 2 < niter, p, q_begin, q_end);
           qtile_load_ld(tr, curl, p, tid);
         }
-        if (ks == 1) tile_copy_piece<0>(cq);
-        if (ks == 2 && kb == 0) tile_copy_piece<4>(cq);
-        if (ks == 3) tile_copy_piece<1>(cq);
-        if (ks == 5) tile_copy_piece<2>(cq);
-        if (ks == 7) tile_copy_piece<3>(cq);
+        if (n == 3) tile16_copy_piece<0>(cq);
+        if (n == 7) tile16_copy_piece<1>(cq);
+        if (n == 11) tile16_copy_piece<2>(cq);
+        if (n == 15) tile16_copy_piece<3>(cq);
       });
       __builtin_amdgcn_s_setprio(0);
       // Only the causal diagonal needs a mask: query rows past s_q carry lse' = +inf (P = 0)
       // and key rows past s_k only feed dk/dv rows that are never written.
       if (p.causal && q0 + off < k0 + BN - 1) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int qrow = q0 + off + (j >> 2) * 8 + hh * 4 + (j & 3);
-          c0[j] = kvrow > qrow ? -INFINITY : c0[j];
-          c1[j] = kvrow > qrow + 32 ? -INFINITY : c1[j];
-        }
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int qrow = q0 + off + mb * 16 + g * 4 + i;
+            if (kvrow > qrow) c[mb][0][i] = -INFINITY;
+            if (kvrow + 16 > qrow) c[mb][1][i] = -INFINITY;
+          }
       }
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const f32x4 l0 = *reinterpret_cast<const f32x4*>(Ls + g4 * 8 + hh * 4);
-        const f32x4 l1 = *reinterpret_cast<const f32x4*>(Ls + 32 + g4 * 8 + hh * 4);
+      for (int mb = 0; mb < 4; ++mb) {
+        const f32x4 l = *reinterpret_cast<const f32x4*>(Ls + mb * 16 + g * 4);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          c0[g4 * 4 + e] = __builtin_amdgcn_exp2f(fmaf(c0[g4 * 4 + e], c2, -l0[e]));
-          c1[g4 * 4 + e] = __builtin_amdgcn_exp2f(fmaf(c1[g4 * 4 + e], c2, -l1[e]));
-        }
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) c[mb][nb][i] = __builtin_amdgcn_exp2f(fmaf(c[mb][nb][i], c2, -l[i]));
       }
       bf16x8 w[2][2];
-      w[0][0] = pack8(c0, 0); w[0][1] = pack8(c0, 8);
-      w[1][0] = pack8(c1, 0); w[1][1] = pack8(c1, 8);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) w[u][nb] = pack16(c[2 * u][nb], c[2 * u + 1][nb]);
       {  // hand P to the dP wavefront of the same key block: lane-private, any layout will do
         char* px = smem + OFF_PX + (it & 1) * PX_BYTES + kb * 4096 + lane * 16;
 #pragma unroll
@@ -385,33 +381,29 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
     }
     __syncthreads();      // the dP wavefronts' last slot
   } else {
-    f32x16 c0, c1;        // dP of the tile in flight, carried over the barrier
+    f32x4 c[4][2];        // dP of the tile in flight, carried over the barrier
     bf16x8 w[2][2];
     // -D of a tile's 64 query rows in the accumulator layout: the dP chains start from it, so what
     // they end with is dP - D
-    auto neg_d = [&](f32x16& d0, f32x16& d1, int ld_slot) {
+    auto neg_d = [&](int ld_slot) {
       // One base register: OFF_LD is beyond the reach of the instruction's offset, and the compiler would add it to each of
-      // the eight addresses (32 over 8 heads x 12000 6902 -> 6835 us, 64 over 8 x 3800 x 22659 8395 -> 8327).
-      const uint32_t Ds = lds_pin(lds_addr(smem + OFF_LD + ld_slot * LD_BYTES) + 256 + hh * 16);
+      // the addresses (32 over 8 heads x 12000 6902 -> 6835 us, 64 over 8 x 3800 x 22659 8395 -> 8327).
+      const uint32_t Ds = lds_pin(lds_addr(smem + OFF_LD + ld_slot * LD_BYTES) + 256 + g * 16);
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const f32x4 a = *(DFA_LDS const f32x4*)(Ds + g4 * 32);
-        const f32x4 b = *(DFA_LDS const f32x4*)(Ds + 128 + g4 * 32);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { d0[g4 * 4 + e] = a[e]; d1[g4 * 4 + e] = b[e]; }
-      }
+      for (int mb = 0; mb < 4; ++mb) c[mb][0] = c[mb][1] = *(DFA_LDS const f32x4*)(Ds + mb * 64);
     };
     auto dS_prev = [&](int it) {                     // dS of tile it - 1 from P (LDS) and dP - D (registers)
       const char* px = smem + OFF_PX + ((it & 1) ^ 1) * PX_BYTES + kb * 4096 + lane * 16;
 #pragma unroll
       for (int j = 0; j < 4; ++j) w[j >> 1][j & 1] = *reinterpret_cast<const bf16x8*>(px + j * 1024);
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        c0[j] = static_cast<float>(w[0][j >> 3][j & 7]) * c0[j];
-        c1[j] = static_cast<float>(w[1][j >> 3][j & 7]) * c1[j];
-      }
-      w[0][0] = pack8(c0, 0); w[0][1] = pack8(c0, 8);
-      w[1][0] = pack8(c1, 0); w[1][1] = pack8(c1, 8);
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) c[2 * u + (e >> 2)][nb][e & 3] *= static_cast<float>(w[u][nb][e]);
+          w[u][nb] = pack16(c[2 * u][nb], c[2 * u + 1][nb]);
+        }
     };
     // The first Q^T gathers of the next slot's dK products are issued before the barrier (that Q
     // tile has been in LDS for a whole slot), so after the barrier only P has to be waited for.
@@ -420,15 +412,14 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
     // products (past the last tile the cursor stays: the same tile goes into the unused slot).
     {  // slot 0: dP of tile 0 only
       qtile_advance_if(cur, niter > 1, p, q_begin, q_end);
-      const TileCopy cg = tile_copy_plan<RAGGED>(cur.gh, q_rowbytes, cur.q0, p.s_q - 1, tl,
-                                                 smem + OFF_G + QTILE_BYTES, kb, lane);
-      if (kb == 0) tile_copy_piece<4>(cg);
-      neg_d(c0, c1, 0);
-      row_products(c0, c1, smem + OFF_G, a_base, bT, [&](int ks) {
-        if (ks == 0) tile_copy_piece<0>(cg);
-        if (ks == 2) tile_copy_piece<1>(cg);
-        if (ks == 4) tile_copy_piece<2>(cg);
-        if (ks == 6) tile_copy_piece<3>(cg);
+      const TileCopy16 cg = tile16_copy_plan<RAGGED>(cur.gh, q_rowbytes, cur.q0, p.s_q - 1, tl,
+                                                     smem + OFF_G + QTILE_BYTES, kb, lane);
+      neg_d(0);
+      row_products(c, smem + OFF_G, a_base, bT, [&](int n) {
+        if (n == 1) tile16_copy_piece<0>(cg);
+        if (n == 5) tile16_copy_piece<1>(cg);
+        if (n == 9) tile16_copy_piece<2>(cg);
+        if (n == 13) tile16_copy_piece<3>(cg);
       });
       col_prefetch(y, smem + OFF_Q, g_base);
       lds_dma_wait();
@@ -438,19 +429,18 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
     for (int it = 1; it < niter; ++it) {
       const int prev = slot == 0 ? 2 : slot - 1, next = slot == 2 ? 0 : slot + 1;
       qtile_advance_if(cur, it + 1 < niter, p, q_begin, q_end);
-      const TileCopy cg = tile_copy_plan<RAGGED>(cur.gh, q_rowbytes, cur.q0, p.s_q - 1, tl,
-                                                 smem + OFF_G + ((it + 1) & 1) * QTILE_BYTES, kb, lane);
-      if (kb == 0) tile_copy_piece<4>(cg);
+      const TileCopy16 cg = tile16_copy_plan<RAGGED>(cur.gh, q_rowbytes, cur.q0, p.s_q - 1, tl,
+                                                     smem + OFF_G + ((it + 1) & 1) * QTILE_BYTES, kb, lane);
       __builtin_amdgcn_s_setprio(3);
       dS_prev(it);
-      neg_d(c0, c1, slot);                       // read straight into the accumulators, under the dK products
+      neg_d(slot);                               // read straight into the accumulators, under the dK products
       col_products<true>(acc, smem + OFF_Q + prev * QTILE_BYTES, g_base, w, y, [&](int n) {  // dK^T += Q^T dS
-        if (n == 1) tile_copy_piece<0>(cg);
-        if (n == 5) tile_copy_piece<1>(cg);
-        if (n == 9) tile_copy_piece<2>(cg);
-        if (n == 13) tile_copy_piece<3>(cg);
+        if (n == 1) tile16_copy_piece<0>(cg);
+        if (n == 5) tile16_copy_piece<1>(cg);
+        if (n == 9) tile16_copy_piece<2>(cg);
+        if (n == 13) tile16_copy_piece<3>(cg);
       });
-      row_products(c0, c1, smem + OFF_G + (it & 1) * QTILE_BYTES, a_base, bT);   // dP - D = dO V^T - D
+      row_products(c, smem + OFF_G + (it & 1) * QTILE_BYTES, a_base, bT);   // dP - D = dO V^T - D
       col_prefetch(y, smem + OFF_Q + slot * QTILE_BYTES, g_base);
       __builtin_amdgcn_s_setprio(0);
       lds_dma_wait();                            // this wavefront's copies into LDS have landed
@@ -464,28 +454,21 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
 
   if constexpr (PARTS) {     // k_reduce_dkdv adds the parts up
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      f32x4 a;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = acc[i >> 2][(i & 3) * 4 + e];
-      partial[(wave * 16 + i) * 64 + lane] = a;
-    }
-  } else if (kvalid) {
-    float* dst = (dp_wave ? pr.dk : pr.dv) + kh * p.dkv_sh + static_cast<int64_t>(kvrow) * p.dkv_ss;
+    for (int i = 0; i < 16; ++i) partial[(wave * 16 + i) * 64 + lane] = acc[i >> 1][i & 1];
+  } else {
     const float f = dp_wave ? p.scale : 1.f;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int nb = 0; nb < 2; ++nb) {
+      const int row = kvrow + 16 * nb;
+      if (row >= p.s_k) break;
+      float* dst = (dp_wave ? pr.dk : pr.dv) + kh * p.dkv_sh + static_cast<int64_t>(row) * p.dkv_ss + g * 4;
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int col = db * 32 + g4 * 8 + hh * 4;
-        float4 a = make_float4(acc[db][g4 * 4] * f, acc[db][g4 * 4 + 1] * f, acc[db][g4 * 4 + 2] * f,
-                               acc[db][g4 * 4 + 3] * f);
-        if (pr.acc_kv) {
-          const float4 a0 = *reinterpret_cast<const float4*>(dst + col);
-          a.x += a0.x; a.y += a0.y; a.z += a0.z; a.w += a0.w;
-        }
-        *reinterpret_cast<float4*>(dst + col) = a;
+      for (int db = 0; db < 8; ++db) {
+        f32x4 a = acc[db][nb] * f;
+        if (pr.acc_kv) a += *reinterpret_cast<const f32x4*>(dst + db * 16);
+        *reinterpret_cast<f32x4*>(dst + db * 16) = a;
       }
+    }
   }
 }
 
@@ -497,7 +480,7 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
 namespace qs {
 
 constexpr int BN = 64;      // key rows per LDS tile
-constexpr int TILE_BYTES = BN * kRowBytes;
+constexpr int TILE_BYTES = kTile64;
 
 // NW wavefronts, NW / NS row blocks of 32 query rows each times NS parts of every key tile; two wavefronts
 // per SIMD either way: NW = 4 (128 rows, two workgroups per CU, scheduled independently of each other) or
@@ -519,13 +502,12 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps tile branches scalar
-  const int r32 = lane & 31, hh = lane >> 5;
+  const int r16 = lane & 15, g = lane >> 4;
   const int rb = wave % (NW / NS), part = wave / (NW / NS);    // row block, part of every key tile
   const int q0w = q0 + rb * 32;
-  const int qrow = q0w + r32;
-  const bool qvalid = qrow < p.s_q;
-  const int a_base = tile_off(r32, hh);
-  const int g_base = gather_base(lane);
+  const int qrow = q0w + r16;                                  // and qrow + 16
+  const int a_base = row16_base(lane);
+  const Gather16 g_base = gather16_bases(lane);
 
   const char* kg = reinterpret_cast<const char*>(pr.k + kh * p.kv_sh);
   const char* vg = reinterpret_cast<const char*>(pr.v + kh * p.kv_sh);
@@ -533,38 +515,38 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
   // Tile copies: with 4 wavefronts each moves its quarter of the K tile and of the V tile; with 8,
   // wavefronts 0-3 move the K tile and 4-7 the V tile.
   const int cw = wave & 3;
-  const TileLane tl = tile_lane(cw, lane, kv_rowbytes);
+  const TileLane16 tl = tile16_lane(cw, lane, kv_rowbytes);
 
-  // Q^T and dO^T operands: lane holds row qrow, columns 16 ks + 8 hh .. +7; lse' and D of that row
-  bf16x8 qB[8], gB[8];
-  {
-    const int64_t off = head * p.q_sh + static_cast<int64_t>(qvalid ? qrow : 0) * p.q_ss + 8 * hh;
+  // Q^T and dO^T operands of the lane's two rows; lse' and -D of them (-D in every element: the accumulator the dP^T
+  // products start from, which saves the subtraction per score)
+  bf16x8 qB[4][2], gB[4][2];
+  float Lr[2];
+  f32x4 negD[2];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      uint4 a = *reinterpret_cast<const uint4*>(pr.q + off + 16 * ks);
-      uint4 b = *reinterpret_cast<const uint4*>(pr.dO + off + 16 * ks);
-      if (!qvalid) { a = make_uint4(0, 0, 0, 0); b = make_uint4(0, 0, 0, 0); }
-      qB[ks] = __builtin_bit_cast(bf16x8, a);
-      gB[ks] = __builtin_bit_cast(bf16x8, b);
+  for (int nb = 0; nb < 2; ++nb) {
+    const int row = qrow + 16 * nb;
+    const bool ok = row < p.s_q;
+    const int64_t off = head * p.q_sh + static_cast<int64_t>(ok ? row : 0) * p.q_ss;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      uint4 a = *reinterpret_cast<const uint4*>(pr.q + off + step16_col(s, g));
+      uint4 b = *reinterpret_cast<const uint4*>(pr.dO + off + step16_col(s, g));
+      if (!ok) { a = make_uint4(0, 0, 0, 0); b = make_uint4(0, 0, 0, 0); }
+      qB[s][nb] = __builtin_bit_cast(bf16x8, a);
+      gB[s][nb] = __builtin_bit_cast(bf16x8, b);
     }
+    Lr[nb] = INFINITY;                    // +inf makes P exactly 0 for rows past the end
+    float d = 0.f;
+    if (ok) {
+      const float L = pr.lse[head * p.l_sh + row];
+      Lr[nb] = L > -INFINITY ? L * LOG2E : INFINITY;
+      d = pr.delta[head * p.l_sh + row];
+    }
+    negD[nb] = f32x4{-d, -d, -d, -d};
   }
-  float Lr = INFINITY, Dr = 0.f;          // +inf makes P exactly 0 for rows past the end
-  if (qvalid) {
-    const float L = pr.lse[head * p.l_sh + qrow];
-    Lr = L > -INFINITY ? L * LOG2E : INFINITY;
-    Dr = pr.delta[head * p.l_sh + qrow];
-  }
-
-  // -D of the lane's query row in every element: the accumulator the dP^T products start from,
-  // which saves the subtraction per score
-  f32x16 negD;
+  f32x4 dqT[8][2];
 #pragma unroll
-  for (int j = 0; j < 16; ++j) negD[j] = -Dr;
-  f32x16 dqT[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 16; ++j) dqT[i][j] = 0.f;
+  for (int i = 0; i < 8; ++i) dqT[i][0] = dqT[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   const float c2 = p.scale * LOG2E;
 
   const int off = p.off;
@@ -575,8 +557,8 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
   // K/V tiles go from global memory straight into LDS; key rows past s_k are clamped to the last
   // row and masked below.  Tile t + 1 is on its way while tile t is computed on.
   const char* first = smem + (PARTS ? (it0 & 1) * 2 * TILE_BYTES : 0);
-  if (NW == 4 || wave < 4) tile_dma(kg, kv_rowbytes, it0 * BN, p.s_k - 1, tl, first, cw, lane);
-  if (NW == 4 || wave >= 4) tile_dma(vg, kv_rowbytes, it0 * BN, p.s_k - 1, tl, first + TILE_BYTES, cw, lane);
+  if (NW == 4 || wave < 4) tile16_copy(tile16_copy_plan(kg, kv_rowbytes, it0 * BN, p.s_k - 1, tl, first, cw, lane));
+  if (NW == 4 || wave >= 4) tile16_copy(tile16_copy_plan(vg, kv_rowbytes, it0 * BN, p.s_k - 1, tl, first + TILE_BYTES, cw, lane));
   lds_dma_wait();
   __syncthreads();
 
@@ -596,80 +578,81 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
     // ck: the pieces issued under the first 32 keys, cv: those under the second 32 (NW == 4: K and V;
     // NW == 8: this wavefront's one tile under the first, nothing under the second)
     const bool v_wave = NW == 8 && wave >= 4;
-    const TileCopy ck = tile_copy_plan(v_wave ? vg : kg, kv_rowbytes, kn0, p.s_k - 1, tl,
-                                       v_wave ? Kn + TILE_BYTES : Kn, cw, lane);
-    const TileCopy cv = tile_copy_plan(vg, kv_rowbytes, kn0, p.s_k - 1, tl, Kn + TILE_BYTES, cw, lane);
+    const TileCopy16 ck = tile16_copy_plan(v_wave ? vg : kg, kv_rowbytes, kn0, p.s_k - 1, tl,
+                                           v_wave ? Kn + TILE_BYTES : Kn, cw, lane);
+    const TileCopy16 cv = tile16_copy_plan(vg, kv_rowbytes, kn0, p.s_k - 1, tl, Kn + TILE_BYTES, cw, lane);
 
     const bool active = it < seen;
     if (!active) {      // nothing to compute for this wavefront's rows: only its share of the copies
-      tile_copy_piece<0>(ck); tile_copy_piece<1>(ck); tile_copy_piece<2>(ck); tile_copy_piece<3>(ck);
-      if (cw == 0) tile_copy_piece<4>(ck);
-      if (NW == 4) {
-        tile_copy_piece<0>(cv); tile_copy_piece<1>(cv); tile_copy_piece<2>(cv); tile_copy_piece<3>(cv);
-        if (cw == 0) tile_copy_piece<4>(cv);
-      }
+      tile16_copy(ck);
+      if (NW == 4) tile16_copy(cv);
     }
     if (active) {
       const bool need_mask = (k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w + off);
 #pragma unroll
       for (int n = 0; n < 2 / NS; ++n) {
-        const int nb = NS == 2 ? part : n;       // 32-key block of the tile
+        const int nk = NS == 2 ? part : n;       // 32-key block of the tile
         // S^T = K Q^T, dP^T = V dO^T for 32 keys; row reads run 4 steps ahead
+        const char* kr = Ks + a_base + nk * 2 * kBlock16;
+        const char* vr = Vs + a_base + nk * 2 * kBlock16;
+        auto roff = [](int t) { return (t & 1) * kBlock16 + step16_off(t >> 1); };      // step t = 2 s + mb
         bf16x8 ka[4], va[4];
-        f32x16 s, dp;
+        f32x4 s[2][2], dp[2][2];                 // [key block][row block]
 #pragma unroll
-        for (int j = 0; j < 16; ++j) s[j] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const int off = a_base + nb * 32 * kRowBytes + ks * 32;
-          ka[ks] = lds_read_b128(Ks, off);
-          va[ks] = lds_read_b128(Vs, off);
+        for (int t = 0; t < 4; ++t) {
+          ka[t] = lds_read_b128(kr, roff(t));
+          va[t] = lds_read_b128(vr, roff(t));
         }
         DFA_SCHED_FENCE();
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-          s = mfma32(ka[ks & 3], qB[ks], s);
-          dp = mfma32(va[ks & 3], gB[ks], ks == 0 ? negD : dp);      // the chain starts from -D
+        for (int t = 0; t < 8; ++t) {
+          const int mb = t & 1;
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb) s[mb][nb] = mfma16(ka[t & 3], qB[t >> 1][nb], t < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[mb][nb]);
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb) dp[mb][nb] = mfma16(va[t & 3], gB[t >> 1][nb], t < 2 ? negD[nb] : dp[mb][nb]);      // from -D
           if (NW == 4 || n == 0) {   // one piece of the next tiles every other step
-            const TileCopy& c = n == 0 ? ck : cv;
-            if (ks == 0) tile_copy_piece<0>(c);
-            if (ks == 2) tile_copy_piece<1>(c);
-            if (ks == 4) tile_copy_piece<2>(c);
-            if (ks == 6) tile_copy_piece<3>(c);
+            const TileCopy16& c = n == 0 ? ck : cv;
+            if (t == 0) tile16_copy_piece<0>(c);
+            if (t == 2) tile16_copy_piece<1>(c);
+            if (t == 4) tile16_copy_piece<2>(c);
+            if (t == 6) tile16_copy_piece<3>(c);
           }
-          if (ks < 4) {
-            const int off = a_base + nb * 32 * kRowBytes + (ks + 4) * 32;
-            ka[ks & 3] = lds_read_b128(Ks, off);
-            va[ks & 3] = lds_read_b128(Vs, off);
+          if (t < 4) {
+            ka[t & 3] = lds_read_b128(kr, roff(t + 4));
+            va[t & 3] = lds_read_b128(vr, roff(t + 4));
           }
           DFA_SCHED_FENCE();
         }
         // dS^T = P^T o (dP^T - D): lse' is a per-lane scalar here, -D came in through the accumulator
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const float pr = __builtin_amdgcn_exp2f(fmaf(s[j], c2, -Lr));
-          dp[j] = pr * dp[j];
-        }
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dp[mb][nb][i] *= __builtin_amdgcn_exp2f(fmaf(s[mb][nb][i], c2, -Lr[nb]));
         if (need_mask) {
 #pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            const int kvi = k0 + nb * 32 + (j >> 2) * 8 + hh * 4 + (j & 3);
-            if (kvi >= p.s_k || (p.causal && kvi > qrow + off)) dp[j] = 0.f;
-          }
-        }
-        if (cw == 0 && (NW == 4 || n == 0)) tile_copy_piece<4>(n == 0 ? ck : cv);
-        // dQ^T += K^T dS^T: 2 contraction steps of 16 keys, 4 blocks of 32 columns
-        bf16x8 sb[2], gk[2];
-        sb[0] = pack8(dp, 0); sb[1] = pack8(dp, 8);
+          for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) gk[i] = lds_gather(Ks, g_base + (nb * 32) * kRowBytes + i * 64);
+            for (int i = 0; i < 4; ++i) {
+              const int kvi = k0 + nk * 32 + mb * 16 + g * 4 + i;
+#pragma unroll
+              for (int nb = 0; nb < 2; ++nb)
+                if (kvi >= p.s_k || (p.causal && kvi > qrow + 16 * nb + off)) dp[mb][nb][i] = 0.f;
+            }
+        }
+        // dQ^T += K^T dS^T over the 32 keys, 8 blocks of 16 columns
+        const bf16x8 sb[2] = {pack16(dp[0][0], dp[1][0]), pack16(dp[0][1], dp[1][1])};
+        bf16x8 gk[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) gk[i] = gather16(Ks, g_base, 2 * nk, i);
         DFA_SCHED_FENCE();
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int u = i >> 2, db = i & 3;
-          dqT[db] = mfma32(gk[i & 1], sb[u], dqT[db]);
-          if (i + 2 < 8)
-            gk[i & 1] = lds_gather(Ks, g_base + (nb * 32 + ((i + 2) >> 2) * 16) * kRowBytes + ((i + 2) & 3) * 64);
+        for (int db = 0; db < 8; ++db) {
+          dqT[db][0] = mfma16(gk[db & 1], sb[0], dqT[db][0]);
+          dqT[db][1] = mfma16(gk[db & 1], sb[1], dqT[db][1]);
+          if (db + 2 < 8) gk[db & 1] = gather16(Ks, g_base, 2 * nk, db + 2);
           DFA_SCHED_FENCE();
         }
       }
@@ -679,45 +662,32 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
   }
 
   if constexpr (NS == 2) {      // the second part's sums through LDS (the tiles are no longer needed)
-    float* x = reinterpret_cast<float*>(smem) + rb * 4096 + lane;
+    f32x4* x = reinterpret_cast<f32x4*>(smem) + rb * 1024 + lane;
     if (part == 1) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) x[(i * 16 + j) * 64] = dqT[i][j];
+      for (int i = 0; i < 16; ++i) x[i * 64] = dqT[i >> 1][i & 1];
     }
     __syncthreads();
     if (part == 1) return;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 16; ++j) dqT[i][j] += x[(i * 16 + j) * 64];
+    for (int i = 0; i < 16; ++i) dqT[i >> 1][i & 1] += x[i * 64];
   }
   if constexpr (PARTS) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      f32x4 a;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = dqT[i >> 2][(i & 3) * 4 + e];
-      partial[(rb * 16 + i) * 64 + lane] = a;
-    }
+    for (int i = 0; i < 16; ++i) partial[(rb * 16 + i) * 64 + lane] = dqT[i >> 1][i & 1];
     return;
   }
-  if (qvalid) {
-    float* dst = pr.dq + head * p.dq_sh + static_cast<int64_t>(qrow) * p.dq_ss;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+  for (int nb = 0; nb < 2; ++nb) {
+    const int row = qrow + 16 * nb;
+    if (row >= p.s_q) break;
+    float* dst = pr.dq + head * p.dq_sh + static_cast<int64_t>(row) * p.dq_ss + g * 4;
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int col = db * 32 + g4 * 8 + hh * 4;
-        float4 a = make_float4(dqT[db][g4 * 4] * p.scale, dqT[db][g4 * 4 + 1] * p.scale,
-                               dqT[db][g4 * 4 + 2] * p.scale, dqT[db][g4 * 4 + 3] * p.scale);
-        if (pr.acc_q) {
-          const float4 a0 = *reinterpret_cast<const float4*>(dst + col);
-          a.x += a0.x; a.y += a0.y; a.z += a0.z; a.w += a0.w;
-        }
-        *reinterpret_cast<float4*>(dst + col) = a;
-      }
+    for (int db = 0; db < 8; ++db) {
+      f32x4 a = dqT[db][nb] * p.scale;
+      if (pr.acc_q) a += *reinterpret_cast<const f32x4*>(dst + db * 16);
+      *reinterpret_cast<f32x4*>(dst + db * 16) = a;
+    }
   }
 }
 
@@ -730,7 +700,7 @@ __global__ void __launch_bounds__(kv::NT) k_reduce_dkdv(BwdPairs<MAX_PAIRS> p) {
   const int tk = tile % p.kv_items.ntile, pk = tile / p.kv_items.ntile;      // pk: pair * h_kv + kv head
   const Pair& pr = p.pair[pk / p.h_kv];
   const bool is_dk = wave >= 4;
-  const int row = tk * kv::BN + (wave & 3) * 32 + (lane & 31);
+  const int row = tk * kv::BN + (wave & 3) * 32 + (lane & 15);       // and row + 16
   if (row >= p.s_k) return;
   const int64_t step = static_cast<int64_t>(p.kv_items.ntile) * kv::PART_F4;
   const f32x4* src = p.partial + (static_cast<int64_t>(pk) * p.parts * p.kv_items.ntile + tk) * kv::PART_F4 +
@@ -744,11 +714,12 @@ __global__ void __launch_bounds__(kv::NT) k_reduce_dkdv(BwdPairs<MAX_PAIRS> p) {
     for (int i = 0; i < 4; ++i) a[i] += src[i * 64];
   }
   float* dst = (is_dk ? pr.dk : pr.dv) + (pk % p.h_kv) * p.dkv_sh + static_cast<int64_t>(row) * p.dkv_ss +
-               blockIdx.x * 32 + (lane >> 5) * 4;
+               blockIdx.x * 32 + (lane >> 4) * 4;
   const float f = is_dk ? p.scale : 1.f;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    f32x4* d = reinterpret_cast<f32x4*>(dst + i * 8);
+  for (int i = 0; i < 4; ++i) {      // column block 2 blockIdx.x + i / 2, row block i % 2
+    if (row + 16 * (i & 1) >= p.s_k) continue;
+    f32x4* d = reinterpret_cast<f32x4*>(dst + (i & 1) * 16 * p.dkv_ss + (i >> 1) * 16);
     f32x4 x = a[i] * f;
     if (pr.acc_kv) x += *d;
     *d = x;
@@ -760,7 +731,7 @@ constexpr int QPART_F4 = 4 * 16 * 64;
 __global__ void __launch_bounds__(256) k_reduce_dq(BwdPairs<1> p) {
   const int ntile = p.q_items.ntile, tid = threadIdx.x, lane = tid & 63, rb = tid >> 6;
   const int head = blockIdx.y / ntile, slot = blockIdx.y % ntile, tq = p.causal ? ntile - 1 - slot : slot;
-  const int row = tq * 128 + rb * 32 + (lane & 31);
+  const int row = tq * 128 + rb * 32 + (lane & 15);      // and row + 16
   if (row >= p.s_q) return;
   const f32x4* src = p.q_partial + (static_cast<int64_t>(head) * p.q_parts * ntile + slot) * QPART_F4 + (rb * 16 + blockIdx.x * 4) * 64 + lane;
   f32x4 a[4];
@@ -772,10 +743,11 @@ __global__ void __launch_bounds__(256) k_reduce_dq(BwdPairs<1> p) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) a[i] += src[i * 64];
   }
-  float* dst = p.pair[0].dq + head * p.dq_sh + static_cast<int64_t>(row) * p.dq_ss + blockIdx.x * 32 + (lane >> 5) * 4;
+  float* dst = p.pair[0].dq + head * p.dq_sh + static_cast<int64_t>(row) * p.dq_ss + blockIdx.x * 32 + (lane >> 4) * 4;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    f32x4* d = reinterpret_cast<f32x4*>(dst + i * 8);
+    if (row + 16 * (i & 1) >= p.s_q) continue;
+    f32x4* d = reinterpret_cast<f32x4*>(dst + (i & 1) * 16 * p.dq_ss + (i >> 1) * 16);
     f32x4 x = a[i] * p.scale;
     if (p.pair[0].acc_q) x += *d;
     *d = x;

@@ -242,6 +242,120 @@ __device__ __forceinline__ void tile_copy_piece(const TileCopy& c) {
                  :: "s"(c.lds16), "v"(c.v[4]), "s"(c.g) : "memory", "m0");
 }
 
+// ---- 16x16x32 tiles -------------------------------------------------------------------------
+// v_mfma_f32_16x16x32_bf16 computes C[16x16] += A[16x32] B[32x16]; with lane l, r = l % 16, g = l / 16:
+//   A operand (8 bf16): A[r][8g .. 8g+7]     B operand (8 bf16): B[8g .. 8g+7][r]
+//   C/D (4 fp32):       C[4g + i][r]
+// Why two of these rather than one 32x32x16 of the same work: the device holds its power limit by lowering the
+// clock, and a product of this shape costs less energy (half as many accumulator reads and writes per
+// multiplication).  On N(0,1) operands the matrix pipes sustain 1.95-2.06 PFLOP/s with it, 1.68-1.80 with the
+// larger shape (register-resident stream, 36 ms launches, one device).
+// Two C tiles of 16 rows each, one below the other, are fed back as a B operand: the eight values of lane
+// group g are rows 4g .. 4g+3 of the first and of the second tile, and the A operand is gathered in that order.
+//
+// LDS tile: blocks of 16 rows of 128 bf16.  Row r of a block lies at row16_off(r / 4) + 256 (r % 4), its 16-byte
+// chunk c at c ^ 2 (r % 4); a row read takes step s of a product over d from chunk 8 (s / 2) + 2g + s % 2.  With that
+// a row read (16 rows x 4 chunks, ds_read_b128) and a gather (16 rows x 32 bytes, ds_read_b64_tr_b16) meet
+// every bank once per pass, every address is a per-lane base (one, and one per pair of column blocks) plus a constant, and
+// the four rows of a 1 KB piece of a copy lie together: a tile of 64 rows is 16 pieces, no padding is copied.
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+constexpr int kBlock16 = 4608;                        // bytes of a 16-row block
+constexpr int kTile64 = 4 * kBlock16;                 // of a 64-row tile
+__host__ __device__ constexpr int row16_off(int k) { return 1024 * k + 128 * (k & 1) + 144 * (k >> 1); }      // 0, 1152, 2192, 3344
+
+// element that step s of a product over d takes first in lane group g (8 from there on)
+__device__ __forceinline__ int step16_col(int s, int g) { return 64 * (s >> 1) + 16 * g + 8 * (s & 1); }
+// per-lane base of row reads; block b, step s: + b * kBlock16 + step16_off(s)
+__device__ __forceinline__ int row16_base(int lane) {
+  const int r = lane & 15, g = lane >> 4;
+  return row16_off(r >> 2) + 256 * (r & 3) + 32 * (g ^ (r & 3));
+}
+__host__ __device__ constexpr int step16_off(int s) { return 128 * (s >> 1) + 16 * (s & 1); }
+
+// Gathers: the 8 values  tile[row0 + 16 (e/4) + 4g + e%4][16 db + lane%16],  e = 0..7, of two 16-row blocks.
+struct Gather16 { int base[4]; };                     // by db % 4
+__device__ __forceinline__ Gather16 gather16_bases(int lane) {
+  const int g = lane >> 4, q = (lane >> 2) & 3, j = lane & 3;
+  Gather16 m;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) m.base[b] = row16_off(g) + 256 * q + 32 * (b ^ q) + 8 * j;
+  return m;
+}
+__device__ __forceinline__ bf16x8 gather16(const char* tile, const Gather16& m, int block, int db) {
+  const char* p = tile + m.base[db & 3];
+  const int off = block * kBlock16 + 128 * (db >> 2);
+  const bf16x4 lo = lds_read_tr(p, off), hi = lds_read_tr(p, off + kBlock16);
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+__device__ __forceinline__ bf16x8 pack16(f32x4 a, f32x4 b) {
+  bf16x8 r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { r[e] = static_cast<__bf16>(a[e]); r[4 + e] = static_cast<__bf16>(b[e]); }
+  return r;
+}
+
+// Copies of such tiles: of 4 copying wavefronts, wavefront w moves block w in four pieces.  (As above, the immediate
+// offset moves the global address too, so piece j's lane offset carries the difference and the scalar base is early.)
+struct TileLane16 { uint32_t voff[4]; };
+constexpr int kEarly16 = row16_off(3);
+
+__device__ __forceinline__ void tile16_lane_rc(int w, int lane, int j, int& row, uint32_t& cb) {
+  const int q = lane >> 4;
+  row = 16 * w + 4 * j + q;
+  cb = static_cast<uint32_t>((lane & 15) ^ (2 * q)) * 16 + (kEarly16 - row16_off(j));
+}
+__device__ __forceinline__ TileLane16 tile16_lane(int w, int lane, uint32_t rowbytes) {
+  TileLane16 m;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    int row; uint32_t cb;
+    tile16_lane_rc(w, lane, j, row, cb);
+    m.voff[j] = static_cast<uint32_t>(row) * rowbytes + cb;
+  }
+  return m;
+}
+
+struct TileCopy16 {
+  const char* g;        // scalar base, kEarly16 bytes early
+  uint32_t v[4];        // per-lane byte offsets of the four pieces
+  uint32_t lds;         // LDS address of block w
+};
+// Rows row0 .. row0 + 63 of a [rows, 128] bf16 matrix at gbase; rows past `last` are clamped to it (RAGGED false: there are none).
+template <bool RAGGED = true>
+__device__ __forceinline__ TileCopy16 tile16_copy_plan(const char* gbase, uint32_t rowbytes, int row0, int last,
+                                                       const TileLane16& m, const char* tile, int w, int lane) {
+  TileCopy16 c;
+  c.lds = lds_addr(tile) + w * kBlock16;
+  const char* g = gbase - kEarly16;
+  if (!RAGGED || row0 + 63 <= last) {
+    c.g = g + static_cast<uint64_t>(static_cast<uint32_t>(row0)) * rowbytes;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c.v[j] = m.voff[j];
+  } else {
+    c.g = g;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      int row; uint32_t cb;
+      tile16_lane_rc(w, lane, j, row, cb);
+      const int r = row0 + row;
+      c.v[j] = static_cast<uint32_t>(r < last ? r : last) * rowbytes + cb;
+    }
+  }
+  return c;
+}
+template <int J>
+__device__ __forceinline__ void tile16_copy_piece(const TileCopy16& c) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
+               :: "s"(c.lds), "v"(c.v[J]), "s"(c.g), "n"(row16_off(J)) : "memory", "m0");
+}
+__device__ __forceinline__ void tile16_copy(const TileCopy16& c) {
+  tile16_copy_piece<0>(c); tile16_copy_piece<1>(c); tile16_copy_piece<2>(c); tile16_copy_piece<3>(c);
+}
+
 __device__ __forceinline__ void lds_dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // acc + the sum of the eight bf16 values of v, in fp32: v_dot2c_f32_bf16 against a pair of ones adds
