@@ -165,18 +165,17 @@ __device__ __forceinline__ void qtile_store(const QTileRegs& t, float* LDs, int 
 struct NoHook { __device__ __forceinline__ void operator()(int) const {} };
 // hook(n) runs after the MFMAs of step n = 4 s + mb (the callers issue their tile-copy pieces there)
 template <class Hook = NoHook>
-__device__ __forceinline__ void row_products(f32x4 (&c)[4][2], const char* Xs, int a_base,
+__device__ __forceinline__ void row_products(f32x4 (&c)[4][2], const char* Xs, uint32_t a_base,
                                              const bf16x8 (&bT)[4][2], Hook hook = Hook()) {
   constexpr int AHEAD = 6;                      // LDS reads run this many steps ahead of the MFMAs
-  const char* x0 = Xs + a_base;
-  auto off = [](int n) { return (n & 3) * kBlock16 + step16_off(n >> 2); };
+  const Rows16 rows(Xs, a_base);
   bf16x8 x[AHEAD + 1];
 #pragma unroll
-  for (int n = 0; n < AHEAD; ++n) x[n] = lds_read_b128(x0, off(n));
+  for (int n = 0; n < AHEAD; ++n) x[n] = rows.read(n & 3, n >> 2);
   DFA_SCHED_FENCE();
 #pragma unroll
   for (int n = 0; n < 16; ++n) {
-    if (n + AHEAD < 16) x[(n + AHEAD) % (AHEAD + 1)] = lds_read_b128(x0, off(n + AHEAD));
+    if (n + AHEAD < 16) x[(n + AHEAD) % (AHEAD + 1)] = rows.read((n + AHEAD) & 3, (n + AHEAD) >> 2);
     c[n & 3][0] = mfma16(x[n % (AHEAD + 1)], bT[n >> 2][0], c[n & 3][0]);
     c[n & 3][1] = mfma16(x[n % (AHEAD + 1)], bT[n >> 2][1], c[n & 3][1]);
     hook(n);
@@ -188,28 +187,27 @@ __device__ __forceinline__ void row_products(f32x4 (&c)[4][2], const char* Xs, i
 // row-major LDS tile with the transposing read, W (P or dS) comes from registers in the order
 // two MFMA result tiles have (w[u][nb] = query blocks 2u and 2u + 1).
 constexpr int COL_AHEAD = 4;              // gathers run this many steps ahead
-__device__ __forceinline__ bf16x8 col_gather(const char* Ys, const Gather16& m, int n) {       // n = u * 8 + db
-  return gather16(Ys, m, 2 * (n >> 3), n & 7);
+__device__ __forceinline__ u32x4 col_gather(const Gather16& cols, int n) {       // n = u * 8 + db
+  return __builtin_bit_cast(u32x4, cols.read(2 * (n >> 3), n & 7));
 }
 // The first COL_AHEAD gathers of col_products, issued early (e.g. before a barrier) so that the
 // products can start without waiting for LDS.
 // (The pieces are kept as raw 32-bit vectors: carried around a loop as bf16 vectors they would be
 // taken apart into 16-bit halves and put together again.)
-__device__ __forceinline__ void col_prefetch(u32x4 (&y)[COL_AHEAD + 1], const char* Ys, const Gather16& m) {
+__device__ __forceinline__ void col_prefetch(u32x4 (&y)[COL_AHEAD + 1], const Gather16& cols) {
 #pragma unroll
-  for (int n = 0; n < COL_AHEAD; ++n) y[n] = __builtin_bit_cast(u32x4, col_gather(Ys, m, n));
+  for (int n = 0; n < COL_AHEAD; ++n) y[n] = col_gather(cols, n);
 }
 template <bool PRE, class Hook = NoHook>
-__device__ __forceinline__ void col_products(f32x4 (&acc)[8][2], const char* Ys, const Gather16& m,
+__device__ __forceinline__ void col_products(f32x4 (&acc)[8][2], const Gather16& cols,
                                              const bf16x8 (&w)[2][2], u32x4 (&y)[COL_AHEAD + 1],
                                              Hook hook = Hook()) {
   constexpr int AHEAD = COL_AHEAD;
-  if (!PRE) col_prefetch(y, Ys, m);
+  if (!PRE) col_prefetch(y, cols);
   DFA_SCHED_FENCE();
 #pragma unroll
   for (int n = 0; n < 16; ++n) {
-    if (n + AHEAD < 16)
-      y[(n + AHEAD) % (AHEAD + 1)] = __builtin_bit_cast(u32x4, col_gather(Ys, m, n + AHEAD));
+    if (n + AHEAD < 16) y[(n + AHEAD) % (AHEAD + 1)] = col_gather(cols, n + AHEAD);
     const bf16x8 a = __builtin_bit_cast(bf16x8, y[n % (AHEAD + 1)]);
     acc[n & 7][0] = mfma16(a, w[n >> 3][0], acc[n & 7][0]);
     acc[n & 7][1] = mfma16(a, w[n >> 3][1], acc[n & 7][1]);
@@ -234,8 +232,8 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
   const int r16 = lane & 15, g = lane >> 4;
   const int kvrow = k0 + kb * 32 + r16;                       // and kvrow + 16
   // per-lane LDS bases; everything else in an LDS address is a compile-time constant
-  const int a_base = row16_base(lane);                        // row reads (A operand of S, dP)
-  const Gather16 g_base = gather16_bases(lane);               // transposed gathers of Q, dO
+  const uint32_t a_base = row16_base(lane);                   // row reads (A operand of S, dP)
+  const uint32_t g_base = gather16_base(lane);                // transposed gathers of Q, dO
 
   // B operands over d of this wavefront's 32 keys: K^T for an S wavefront, V^T for a dP wavefront
   bf16x8 bT[4][2];
@@ -372,7 +370,7 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
       }
       u32x4 y[COL_AHEAD + 1];
       __builtin_amdgcn_s_setprio(3);
-      col_products<false>(acc, Gs, g_base, w, y);    // dV^T += dO^T P
+      col_products<false>(acc, Gather16(Gs, g_base), w, y);    // dV^T += dO^T P
       __builtin_amdgcn_s_setprio(0);
       lds_dma_wait();                                // this wavefront's copies into LDS have landed
       __syncthreads();
@@ -421,7 +419,7 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
         if (n == 9) tile16_copy_piece<2>(cg);
         if (n == 13) tile16_copy_piece<3>(cg);
       });
-      col_prefetch(y, smem + OFF_Q, g_base);
+      col_prefetch(y, Gather16(smem + OFF_Q, g_base));
       lds_dma_wait();
       DFA_BARRIER_NO_DRAIN();
       slot = 1;
@@ -434,21 +432,21 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
       __builtin_amdgcn_s_setprio(3);
       dS_prev(it);
       neg_d(slot);                               // read straight into the accumulators, under the dK products
-      col_products<true>(acc, smem + OFF_Q + prev * QTILE_BYTES, g_base, w, y, [&](int n) {  // dK^T += Q^T dS
+      col_products<true>(acc, Gather16(smem + OFF_Q + prev * QTILE_BYTES, g_base), w, y, [&](int n) {  // dK^T += Q^T dS
         if (n == 1) tile16_copy_piece<0>(cg);
         if (n == 5) tile16_copy_piece<1>(cg);
         if (n == 9) tile16_copy_piece<2>(cg);
         if (n == 13) tile16_copy_piece<3>(cg);
       });
       row_products(c, smem + OFF_G + (it & 1) * QTILE_BYTES, a_base, bT);   // dP - D = dO V^T - D
-      col_prefetch(y, smem + OFF_Q + slot * QTILE_BYTES, g_base);
+      col_prefetch(y, Gather16(smem + OFF_Q + slot * QTILE_BYTES, g_base));
       __builtin_amdgcn_s_setprio(0);
       lds_dma_wait();                            // this wavefront's copies into LDS have landed
       DFA_BARRIER_NO_DRAIN();                    // nothing else it wrote has to be seen by the others
       slot = next;
     }
     dS_prev(niter);
-    col_products<true>(acc, smem + OFF_Q + (slot == 0 ? 2 : slot - 1) * QTILE_BYTES, g_base, w, y);
+    col_products<true>(acc, Gather16(smem + OFF_Q + (slot == 0 ? 2 : slot - 1) * QTILE_BYTES, g_base), w, y);
     __syncthreads();
   }
 
@@ -506,8 +504,7 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
   const int rb = wave % (NW / NS), part = wave / (NW / NS);    // row block, part of every key tile
   const int q0w = q0 + rb * 32;
   const int qrow = q0w + r16;                                  // and qrow + 16
-  const int a_base = row16_base(lane);
-  const Gather16 g_base = gather16_bases(lane);
+  const uint32_t a_base = row16_base(lane), g_base = gather16_base(lane);
 
   const char* kg = reinterpret_cast<const char*>(pr.k + kh * p.kv_sh);
   const char* vg = reinterpret_cast<const char*>(pr.v + kh * p.kv_sh);
@@ -593,15 +590,14 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
       for (int n = 0; n < 2 / NS; ++n) {
         const int nk = NS == 2 ? part : n;       // 32-key block of the tile
         // S^T = K Q^T, dP^T = V dO^T for 32 keys; row reads run 4 steps ahead
-        const char* kr = Ks + a_base + nk * 2 * kBlock16;
-        const char* vr = Vs + a_base + nk * 2 * kBlock16;
-        auto roff = [](int t) { return (t & 1) * kBlock16 + step16_off(t >> 1); };      // step t = 2 s + mb
+        const Rows16 kr(Ks, a_base), vr(Vs, a_base);      // step t = 2 s + mb
+        const int b0 = 2 * nk;                   // first 16-key block
         bf16x8 ka[4], va[4];
         f32x4 s[2][2], dp[2][2];                 // [key block][row block]
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          ka[t] = lds_read_b128(kr, roff(t));
-          va[t] = lds_read_b128(vr, roff(t));
+          ka[t] = kr.read(b0 + (t & 1), t >> 1);
+          va[t] = vr.read(b0 + (t & 1), t >> 1);
         }
         DFA_SCHED_FENCE();
 #pragma unroll
@@ -619,8 +615,8 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
             if (t == 6) tile16_copy_piece<3>(c);
           }
           if (t < 4) {
-            ka[t & 3] = lds_read_b128(kr, roff(t + 4));
-            va[t & 3] = lds_read_b128(vr, roff(t + 4));
+            ka[t & 3] = kr.read(b0 + (t & 1), (t + 4) >> 1);
+            va[t & 3] = vr.read(b0 + (t & 1), (t + 4) >> 1);
           }
           DFA_SCHED_FENCE();
         }
@@ -644,15 +640,16 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
         }
         // dQ^T += K^T dS^T over the 32 keys, 8 blocks of 16 columns
         const bf16x8 sb[2] = {pack16(dp[0][0], dp[1][0]), pack16(dp[0][1], dp[1][1])};
+        const Gather16 kc(Ks, g_base);
         bf16x8 gk[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) gk[i] = gather16(Ks, g_base, 2 * nk, i);
+        for (int i = 0; i < 2; ++i) gk[i] = kc.read(b0, i);
         DFA_SCHED_FENCE();
 #pragma unroll
         for (int db = 0; db < 8; ++db) {
           dqT[db][0] = mfma16(gk[db & 1], sb[0], dqT[db][0]);
           dqT[db][1] = mfma16(gk[db & 1], sb[1], dqT[db][1]);
-          if (db + 2 < 8) gk[db & 1] = gather16(Ks, g_base, 2 * nk, db + 2);
+          if (db + 2 < 8) gk[db & 1] = kc.read(b0, db + 2);
           DFA_SCHED_FENCE();
         }
       }

@@ -129,6 +129,47 @@ __device__ __forceinline__ void store_o(const f32x16 (&o)[4], const FwdParams& p
     }
 }
 
+// The same for 16x16 tiles of O^T, o[16 columns of d][16 rows] of the rows qrow + 16 nb (those that there are; load_o: that
+// have a state).
+template <int RB>
+__device__ __forceinline__ void load_o(f32x4 (&o)[8][RB], const FwdParams& p, int head, int qrow, int g, const bool (&has)[RB]) {
+#pragma unroll
+  for (int nb = 0; nb < RB; ++nb) {
+    if (!has[nb]) continue;
+    const int64_t at = head * p.o_sh + static_cast<int64_t>(qrow + 16 * nb) * p.o_ss + 4 * g;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) {
+      if (p.o_bf16) {
+        const bf16x4 b = *reinterpret_cast<const bf16x4*>(static_cast<const __bf16*>(p.o) + at + 16 * db);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[db][nb][e] = static_cast<float>(b[e]);
+      } else {
+        o[db][nb] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.o) + at + 16 * db);
+      }
+    }
+  }
+}
+template <int RB>
+__device__ __forceinline__ void store_o(const f32x4 (&o)[8][RB], const FwdParams& p, int head, int qrow, int g, const float (&inv)[RB]) {
+#pragma unroll
+  for (int nb = 0; nb < RB; ++nb) {
+    if (qrow + 16 * nb >= p.s_q) break;
+    const int64_t at = head * p.o_sh + static_cast<int64_t>(qrow + 16 * nb) * p.o_ss + 4 * g;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) {
+      const f32x4 x = o[db][nb] * inv[nb];
+      if (p.o_bf16) {
+        bf16x4 b;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) b[e] = static_cast<__bf16>(x[e]);
+        *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o) + at + 16 * db) = b;
+      } else {
+        *reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + at + 16 * db) = x;
+      }
+    }
+  }
+}
+
 // FULL: a full pair.  Its row sums are taken over the bf16-rounded weights that multiply V, those of the diagonal pair
 // over the fp32 weights (the same in the other forms of 128 and 256 rows).
 template <bool FULL, class Args>
@@ -365,40 +406,44 @@ __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
 }
 
 // ============================================================================================
-// Wavefront-specialised forward for full (unmasked) pairs: 16 wavefronts on 256 query rows, four
-// per SIMD.
-//   8 "S" wavefronts (32 query rows each, Q^T in registers): S^T = K Q^T, online softmax (one
-//     reference update per 64-key tile), and the exponentiated tile P^T handed over through LDS as
-//     bf16 together with the factor by which the running maximum moved; wavefronts 0-3 also issue
-//     the global -> LDS copies of the K tiles, 4-7 those of the V tiles;
-//   8 "PV" wavefronts (the same 32 rows each): O^T = O^T * factor + V^T P^T, one tile behind their
-//     S wavefront, so one barrier per tile suffices; with only O^T to hold they read V^T six steps
-//     ahead of their MFMAs.
-// A wavefront overlaps nothing with itself (measured), different wavefronts of a SIMD do: here the
-// exponentials of two S wavefronts run under the MFMAs of all four.  Measured against the
-// 4-wavefront kernel above: 10 % faster on a 4096 x 4096 pair in spite of a lower clock under
-// load (1.8 GHz).  On the causal diagonal pair its 256-row granularity costs half a row block per row
-// of tiles: slower than the kernel above up to about 6000 rows, 8 % faster at 16384.
+// Wavefront-specialised forward for full (unmasked) pairs: 8 wavefronts on 256 query rows, two per SIMD.
+//   4 "S" wavefronts (64 query rows each, Q^T in registers): S^T = K Q^T and the exponentials, 32 keys of one between
+//     32 keys of the other (each pipe waits for the other otherwise: one wavefront overlaps its own vector instructions with
+//     its own MFMAs only where they stand between them and do not depend on one another); the exponentiated tile P^T goes
+//     to the PV wavefront through LDS as bf16.  They also issue the global -> LDS copies of the K tiles;
+//   4 "PV" wavefronts (the same 64 rows each): O^T = O^T * factor + V^T P^T and the row sums, one tile behind, so one
+//     barrier per tile suffices; they copy the V tiles.
+// 64 rows per wavefront: a row of K or V that is read from LDS serves four products.  With 32 rows (16 wavefronts, twice the
+// LDS reads, no interleaving) a full pair of 32 heads x 65536 takes 58.2 ms, 56.2 so; all products of a tile before its
+// exponentials 58.7; one kind of wavefront that does both (one per SIMD, 512 registers, no hand-over) 64.8; 32x32x16
+// products, 16 wavefronts 59.2.  The matrix pipes are 66 % busy at 1.9 GHz.
+// On the causal diagonal pair the 256-row granularity costs half a row block per row
+// of tiles: slower than the kernel above up to about 6000 rows, faster at 16384.
 // ============================================================================================
 namespace full_pair {
 
-constexpr int NT = 1024;
+constexpr int NT = 512;
+constexpr int TILE_BYTES = kTile64;
 constexpr int BMW = 256;                       // query rows per workgroup
-constexpr int PX_BYTES = 8 * 4096;             // P^T hand-over: 8 query blocks x (64 keys x 32 queries bf16)
-constexpr int AL_BYTES = 8 * 32 * 4;           // rescale factor per query row
-// LDS map.  Tile t: K slot t % 2, V slot t % 3, P^T / factor slot t % 2; row statistics at the end.
+constexpr int WROWS = 64;                      // of a wavefront
+constexpr int RB = WROWS / 16;                 // its 16-row blocks
+constexpr int PX_WAVE = BN * WROWS * 2;        // P^T hand-over of a wavefront
+constexpr int PX_BYTES = BMW / WROWS * PX_WAVE;
+constexpr int AL_BYTES = BMW * 4;              // rescale factor per query row
+// LDS map.  Tile t: K slot t % 3, V slot t % 2, P^T / factor slot t % 2; row statistics at the end.
 constexpr int OFF_K = 0;
-constexpr int OFF_V = OFF_K + 2 * TILE_BYTES;
-constexpr int OFF_PX = OFF_V + 3 * TILE_BYTES;
+constexpr int OFF_V = OFF_K + 3 * TILE_BYTES;
+constexpr int OFF_PX = OFF_V + 2 * TILE_BYTES;
 constexpr int OFF_AL = OFF_PX + 2 * PX_BYTES;
-constexpr int OFF_ST = OFF_AL + 2 * AL_BYTES;  // 1 / row sum, written once by the S wavefronts
-constexpr int SMEM_BYTES = OFF_ST + AL_BYTES;
+constexpr int OFF_ST = OFF_AL + 2 * AL_BYTES;  // (reference, row sum) as the S wavefronts have them, written once
+constexpr int OFF_MV = OFF_ST + 2 * AL_BYTES;  // per tile slot and wavefront: a factor is not 1
+constexpr int SMEM_BYTES = OFF_MV + 2 * 4 * 4;
 
 // RAGGED: s_k is no multiple of the 64-row tile, so the last K/V tile has rows past the end.
 // CAUSAL: the diagonal pair; its row sums are taken over the fp32 weights, as in the other causal forms (of a span: where a tile
 // has keys of the chunk's own; before them over the rounded weights, as for full pairs).
 template <bool RAGGED, bool CAUSAL, class Args>
-__global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
+__global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
   extern __shared__ __align__(16) char smem[];
 
   const int bid = blockIdx.x;
@@ -413,242 +458,391 @@ __global__ void __launch_bounds__(NT, 1) k_fwd_bf16(Args a) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: role branches stay scalar
-  const bool pv_wave = wave >= 8;
-  const int r32 = lane & 31, hh = lane >> 5;
+  const bool pv_wave = wave >= 4;
+  const int sw = wave & 3;                                     // row block of the wavefront
+  const int r16 = lane & 15, g = lane >> 4;
   const float c2 = p.scale * LOG2E;
+  const int q0w = q0 + sw * WROWS;
+  const int qrow = q0w + r16;                                  // and qrow + 16, + 32, + 48
 
   const int off = off_of(p);
   const int k_end = CAUSAL ? min(p.s_k, q0 + BMW + off) : p.s_k;
   const int ntiles = (k_end + BN - 1) / BN;
+  const uint32_t kv_rowbytes = static_cast<uint32_t>(p.kv_ss) * 2;
+  const TileLane16 tl = tile16_lane(sw, lane, kv_rowbytes);
+  const int last = p.s_k - 1;
+  // tiles that have keys which the wavefront's rows see: the first ones
+  const int seen = CAUSAL ? min(ntiles, (q0w + WROWS - 1 + off) / BN + 1) : ntiles;
 
   if (!pv_wave) {
     // ------------------------------------------------------------------ S wavefront
-    const int q0w = q0 + wave * 32;
-    const int qrow = q0w + r32;
-    const bool qvalid = qrow < p.s_q;
-    const int a_base = tile_off(r32, hh);
-    bf16x8 qreg[8];      // Q^T operand: lane holds Q[qrow][16 ks + 8 hh .. +7]
-    {
-      const __bf16* qp = p.q + head * p.q_sh + static_cast<int64_t>(qvalid ? qrow : 0) * p.q_ss + 8 * hh;
+    const uint32_t a_base = row16_base(lane);
+    bf16x8 qreg[4][RB];                      // Q^T operand of the lane's rows
+    float m_run[RB];                         // running maxima of the raw scores q.k
+    float l_run[RB];                         // this lane's quarter of the running sums of unrounded weights
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        uint4 raw = *reinterpret_cast<const uint4*>(qp + 16 * ks);
-        if (!qvalid) raw = make_uint4(0, 0, 0, 0);
-        qreg[ks] = __builtin_bit_cast(bf16x8, raw);
+    for (int nb = 0; nb < RB; ++nb) {
+      const int row = qrow + 16 * nb;
+      const bool ok = row < p.s_q;
+      const __bf16* qp = p.q + head * p.q_sh + static_cast<int64_t>(ok ? row : 0) * p.q_ss;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        uint4 raw = *reinterpret_cast<const uint4*>(qp + step16_col(s, g));
+        if (!ok) raw = make_uint4(0, 0, 0, 0);
+        qreg[s][nb] = __builtin_bit_cast(bf16x8, raw);
+      }
+      m_run[nb] = -INFINITY;
+      l_run[nb] = 0.f;
+      if (p.accumulate && ok) {
+        // state of the earlier key/value chunks: running (o, m, l) with m = lse (raw-score units), l = 1
+        const float L = p.lse[head * p.l_sh + row];
+        if (L > -INFINITY) { m_run[nb] = L / p.scale; l_run[nb] = g == 0 ? 1.f : 0.f; }
       }
     }
-    float m_run = -INFINITY;     // running maximum of the raw scores q.k
-    float l_run = 0.f;           // this lane's half of the running row sum
-    if (p.accumulate && qvalid) {
-      // state of the earlier key/value chunks: running (o, m, l) with m = lse (raw-score units), l = 1
-      const float L = p.lse[head * p.l_sh + qrow];
-      if (L > -INFINITY) { m_run = L / p.scale; l_run = hh == 0 ? 1.f : 0.f; }
-    }
-    float* al = reinterpret_cast<float*>(smem + OFF_AL) + wave * 32 + r32;
-    // the S wavefronts (registers to spare) issue the global -> LDS copies of the K/V tiles
-    const char* kg = reinterpret_cast<const char*>(p.k + kh * p.kv_sh);
-    const char* vg = reinterpret_cast<const char*>(p.v + kh * p.kv_sh);
-    const uint32_t kv_rowbytes = static_cast<uint32_t>(p.kv_ss) * 2;
-    const TileLane tl = tile_lane(wave & 3, lane, kv_rowbytes);
-    const char* cg = wave < 4 ? kg : vg;      // wavefronts 0-3 copy K tiles, 4-7 V tiles
-    const int last = p.s_k - 1;
-    tile_dma(cg, kv_rowbytes, 0, last, tl, wave < 4 ? smem + OFF_K : smem + OFF_V, wave & 3, lane);
+    float* al = reinterpret_cast<float*>(smem + OFF_AL) + sw * WROWS + r16;      // factors by which what was accumulated so far shrinks
+    int* mv = reinterpret_cast<int*>(smem + OFF_MV) + sw;
+    const char* kg = uniform_ptr(p.k + kh * p.kv_sh);
+    auto k_plan = [&](int t, int slot) {     // (past the last tile the same once more, into a slot that is not read again)
+      return tile16_copy_plan<RAGGED>(kg, kv_rowbytes, min(t, ntiles - 1) * BN, last, tl, smem + OFF_K + slot * TILE_BYTES, sw, lane);
+    };
+    tile16_copy(k_plan(0, 0));
+    tile16_copy(k_plan(1, 1));
     lds_dma_wait();
-    __syncthreads();                         // tile 0 is in LDS
-    for (int it = 0; it < ntiles; ++it) {
-      const int k0 = it * BN;
-      const char* Ks = smem + OFF_K + (it & 1) * TILE_BYTES;
-      // This wavefront's pieces of the next K (or V) tile, issued one at a time between the MFMAs
-      // below: in a burst they would stall it while the memory pipe takes them in.  After the last
-      // tile the same tile goes once more into a ring slot nobody reads (no branch around the copies).
-      const TileCopy cn = tile_copy_plan<RAGGED>(cg, kv_rowbytes, it + 1 < ntiles ? k0 + BN : k0, last, tl,
-                                         wave < 4 ? smem + OFF_K + ((it + 1) & 1) * TILE_BYTES
-                                                  : smem + OFF_V + ((it + 1) % 3) * TILE_BYTES,
-                                         wave & 3, lane);
-      const bool active = !(CAUSAL && k0 > q0w + 31 + off);   // else: the whole tile lies above this block's diagonal
-      if (!active) {
-        tile_copy_piece<0>(cn); tile_copy_piece<1>(cn); tile_copy_piece<2>(cn); tile_copy_piece<3>(cn);
-        if ((wave & 3) == 0) tile_copy_piece<4>(cn);
-      }
-      if (active) {
-        f32x16 s0, s1;
-        // S^T = K Q^T of the tile's two 32-key blocks.  COPIES: this wavefront's pieces of the next
-        // tile's copy go out between the MFMAs (false when the products are done a second time).
-        auto s_products = [&](auto copies) {
-          constexpr bool COPIES = decltype(copies)::value;
-          bf16x8 x0[4], x1[4];
-          f32x16 zero;
-#pragma unroll
-          for (int j = 0; j < 16; ++j) zero[j] = 0.f;
-#pragma unroll
-          for (int ks = 0; ks < 3; ++ks) {
-            x0[ks] = lds_read_b128(Ks, a_base + ks * 32);
-            x1[ks] = lds_read_b128(Ks, a_base + 32 * kRowBytes + ks * 32);
-          }
-          DFA_SCHED_FENCE();
-          __builtin_amdgcn_s_setprio(3);         // MFMAs first: the other wavefronts' VALU work fills the gaps
-#pragma unroll
-          for (int ks = 0; ks < 8; ++ks) {
-            if (ks + 3 < 8) {
-              x0[(ks + 3) & 3] = lds_read_b128(Ks, a_base + (ks + 3) * 32);
-              x1[(ks + 3) & 3] = lds_read_b128(Ks, a_base + 32 * kRowBytes + (ks + 3) * 32);
-            }
-            s0 = mfma32(x0[ks & 3], qreg[ks], ks == 0 ? zero : s0);
-            s1 = mfma32(x1[ks & 3], qreg[ks], ks == 0 ? zero : s1);
-            if (COPIES) {
-              if (ks == 0) tile_copy_piece<0>(cn);
-              if (ks == 2) tile_copy_piece<1>(cn);
-              if (ks == 4) tile_copy_piece<2>(cn);
-              if (ks == 6) tile_copy_piece<3>(cn);
-            }
-            DFA_SCHED_FENCE();
-          }
-          __builtin_amdgcn_s_setprio(0);
-          if (COPIES && (wave & 3) == 0) tile_copy_piece<4>(cn);
-          if ((k0 + BN > p.s_k) || (CAUSAL && k0 + BN - 1 > q0w + off)) {
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-              const int kvi = k0 + (j >> 2) * 8 + hh * 4 + (j & 3);
-              if (kvi >= p.s_k || (CAUSAL && kvi > qrow + off)) s0[j] = -INFINITY;
-              if (kvi + 32 >= p.s_k || (CAUSAL && kvi + 32 > qrow + off)) s1[j] = -INFINITY;
-            }
-          }
-        };
-        // Moves the reference maximum up to the tile's row maxima; returns the factor by which what
-        // has been accumulated against the old reference shrinks.
-        auto new_reference = [&]() {
-          float mx = fmaxf(s0[0], s1[0]);
-#pragma unroll
-          for (int j = 1; j < 16; ++j) mx = fmaxf(fmaxf(mx, s0[j]), s1[j]);
-          mx = fmaxf(mx, __shfl_xor(mx, 32));
-          const float m_new = fmaxf(m_run, mx);
-          const float mc_new = (m_new == -INFINITY) ? 0.f : m_new * c2;
-          const float a = __builtin_amdgcn_exp2f(m_run * c2 - mc_new);
-          m_run = m_new;
-          l_run *= a;
-          return a;
-        };
-        // P^T = exp2(S^T c - reference) rounded to bf16, and this lane's half of the tile's row sum, taken
-        // over the ROUNDED values (v_dot2c_f32_bf16 against a pair of ones: one instruction per two
-        // scores), so that the sum that normalises O is the sum of exactly the weights that multiply V.
-        bf16x8 p0, p1, p2, p3;
-        const bool rounded = kSpans<Args> ? k0 + BN <= off : !CAUSAL;
-        auto exponentials = [&]() {
-          const float mc = (m_run == -INFINITY) ? 0.f : m_run * c2;
-#pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            s0[j] = __builtin_amdgcn_exp2f(fmaf(s0[j], c2, -mc));
-            s1[j] = __builtin_amdgcn_exp2f(fmaf(s1[j], c2, -mc));
-          }
-          p0 = pack8(s0, 0); p1 = pack8(s0, 8); p2 = pack8(s1, 0); p3 = pack8(s1, 8);
-          // independent chains, so that the adds do not wait for one another
-          if (!rounded) {
-            float a[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int j = 0; j < 16; ++j) { a[j & 1] += s0[j]; a[2 + (j & 1)] += s1[j]; }
-            return (a[0] + a[1]) + (a[2] + a[3]);
-          }
-          const float sa = sum8(p2, sum8(p0, 0.f)), sb = sum8(p3, sum8(p1, 0.f));
-          return sa + sb;
-        };
-        // Online softmax of the 64-key tile (exp2 domain) against a reference maximum that is only
-        // moved when it has to be.  A tile is first exponentiated against the reference as it stands,
-        // without looking for its maximum: as long as no score lies more than 2^14 above the
-        // reference, the exponentials are harmless in fp32 / bf16, O needs no rescaling, and the final
-        // division by the row sum removes the reference.  The reference is derived from the scores
-        // themselves (row maximum, one exchange between the two half rows) on a row's first tile -
-        // so the largest weight seen is at least 1 and later tiles cannot underflow the row sum - and
-        // again when a tile's half-row sum shows a score far above it (or is no number): that tile's
-        // products are then done once more and the tile is redone with the moved reference.
-        float alpha = 1.f;
-        s_products(std::true_type{});
-        const bool fresh = __any(m_run == -INFINITY);
-        if (fresh) alpha = new_reference();
-        float sum = exponentials();
-        if (!fresh && __any(!(sum <= 16384.f))) {
-          s_products(std::false_type{});
-          alpha = new_reference();
-          sum = exponentials();
-        }
-        l_run += sum;
-        // hand P^T and the factor to the PV wavefront: lane-private, any layout will do
-        char* px = smem + OFF_PX + (it & 1) * PX_BYTES + wave * 4096 + lane * 16;
-        *reinterpret_cast<bf16x8*>(px) = p0;
-        *reinterpret_cast<bf16x8*>(px + 1024) = p1;
-        *reinterpret_cast<bf16x8*>(px + 2048) = p2;
-        *reinterpret_cast<bf16x8*>(px + 3072) = p3;
-        if (hh == 0) al[(it & 1) * (AL_BYTES / 4)] = alpha;
-      }
-      lds_dma_wait();
-      __syncthreads();
-    }
-    // row statistics: logsumexp to memory, 1 / row sum to the PV wavefront
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (hh == 0) {
-      reinterpret_cast<float*>(smem + OFF_ST)[wave * 32 + r32] = l_tot > 0.f ? 1.f / l_tot : 0.f;
-      if (qvalid) p.lse[head * p.l_sh + qrow] = l_tot > 0.f ? m_run * p.scale + logf(l_tot) : -INFINITY;
-    }
-    __syncthreads();                         // the PV wavefronts' last slot
-  } else {
-    // ------------------------------------------------------------------ PV wavefront
-    const int sw = wave - 8;                 // serves S wavefront sw: the same 32 query rows
-    const int q0w = q0 + sw * 32;
-    const int qrow = q0w + r32;
-    const bool qvalid = qrow < p.s_q;
-    const int g_base = gather_base(lane);
+    __syncthreads();                         // K tiles 0 and 1 are in LDS
 
-    f32x16 o[4];         // O^T: [d block][d within block][query]
+    // A tile goes in two halves of 32 keys: the products of one are issued between the exponentials of the other, a
+    // product and a score at a time, so that both pipes and the LDS are busy all along.  (All products of a tile first,
+    // its exponentials after them: the matrix pipes are 52 % busy, at 2.2 GHz.)
+    typedef f32x4 Half[2][RB];               // [16-key block][16-row block]
+    constexpr int AHEAD = 3;                 // row reads run this many steps (of RB products) ahead, into the next half
+    u32x4 x[AHEAD + 1];
+    auto read_ahead = [&](const Rows16& rows, int half, int n) {
+      x[n & AHEAD] = __builtin_bit_cast(u32x4, rows.read(2 * half + (n & 1), n >> 1));
+    };
+    // step n of S^T = K Q^T of a half: 16-key block n % 2, 32 elements of d from n / 2
+    auto product = [&](Half& s, bf16x8 k, int n, int nb) {
+      s[n & 1][nb] = mfma16(k, qreg[n >> 1][nb], n < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[n & 1][nb]);
+    };
+    auto products = [&](Half& s, const char* Ks, int half) {
+      const Rows16 rows(Ks, a_base);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+      for (int n = 0; n < 8; ++n) {
+        const bf16x8 k = rows.read(2 * half + (n & 1), n >> 1);
 #pragma unroll
-      for (int j = 0; j < 16; ++j) o[i][j] = 0.f;
-    if (p.accumulate && qvalid && p.lse[head * p.l_sh + qrow] > -INFINITY) load_o(o, p, head, qrow, hh);
-    // O^T = O^T * factor + V^T P^T for tile t (skipped when the tile lies above the block's diagonal)
-    auto pv_tile = [&](int t) {
-      const int k0 = t * BN;
-      if (CAUSAL && k0 > q0w + 31 + off) return;
-      const char* Vs = smem + OFF_V + (t % 3) * TILE_BYTES;
-      const char* px = smem + OFF_PX + (t & 1) * PX_BYTES + sw * 4096 + lane * 16;
-      const float a = reinterpret_cast<const float*>(smem + OFF_AL)[(t & 1) * (AL_BYTES / 4) + sw * 32 + r32];
-      constexpr int AHEAD = 6;               // V^T gathers run this many steps ahead of their MFMAs
-      const uint32_t vb = lds_pin(lds_addr(Vs) + g_base);
-      auto voff = [&](int n) {               // n = key block * 8 + half * 4 + d block
-        return ((n >> 3) * 32 + ((n >> 2) & 1) * 16) * kRowBytes + (n & 3) * 64;
-      };
-      bf16x8 y[AHEAD + 1], pa[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) pa[j] = *reinterpret_cast<const bf16x8*>(px + j * 1024);
-#pragma unroll
-      for (int n = 0; n < AHEAD; ++n) y[n] = lds_gather_at(vb, voff(n));
-      if (__any(a != 1.f)) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 16; ++j) o[i][j] *= a;
+        for (int nb = 0; nb < RB; ++nb) product(s, k, n, nb);
       }
-      DFA_SCHED_FENCE();
-      __builtin_amdgcn_s_setprio(3);
+    };
+    auto mask = [&](Half& s, int k0) {
+      if ((k0 + 32 > p.s_k) || (CAUSAL && k0 + 31 > q0w + off)) {
 #pragma unroll
-      for (int n = 0; n < 16; ++n) {
-        if (n + AHEAD < 16) y[(n + AHEAD) % (AHEAD + 1)] = lds_gather_at(vb, voff(n + AHEAD));
-        o[n & 3] = mfma32(y[n % (AHEAD + 1)], pa[n >> 2], o[n & 3]);
-        DFA_SCHED_FENCE();
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int kvi = k0 + mb * 16 + g * 4 + i;
+#pragma unroll
+            for (int nb = 0; nb < RB; ++nb)
+              if (kvi >= p.s_k || (CAUSAL && kvi > qrow + 16 * nb + off)) s[mb][nb][i] = -INFINITY;
+          }
       }
-      __builtin_amdgcn_s_setprio(0);
+    };
+    auto row_max = [&](const Half& s, int nb) {
+      float mx = s[0][nb][0];
+#pragma unroll
+      for (int j = 1; j < 8; ++j) mx = fmaxf(mx, s[j >> 2][nb][j & 3]);
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      return fmaxf(mx, __shfl_xor(mx, 32));
+    };
+    float mc[RB];                            // the references in the exponents' units
+#pragma unroll
+    for (int nb = 0; nb < RB; ++nb) mc[nb] = m_run[nb] == -INFINITY ? 0.f : m_run[nb] * c2;
+    // Rows without a reference take the maximum of the half's scores for one.
+    bool open = true;                        // there are such rows
+    auto first_reference = [&](const Half& s) {
+      if (!open) return;
+      bool none = false;
+#pragma unroll
+      for (int nb = 0; nb < RB; ++nb) {
+        const float mx = row_max(s, nb);
+        if (m_run[nb] == -INFINITY) m_run[nb] = mx;
+        mc[nb] = m_run[nb] == -INFINITY ? 0.f : m_run[nb] * c2;
+        none |= m_run[nb] == -INFINITY;
+      }
+      open = __any(none);
+    };
+    // P^T = exp2(S^T c - reference) rounded to bf16, score j of the lane's 8 RB (a row's 8 keys one after the other) between
+    // the products of the other half, handed to the PV wavefront through LDS (lane-private, any layout will do).  The row
+    // sum that normalises O is the sum of exactly the weights that multiply V: the PV wavefront, which has vector
+    // instructions to spare, adds up the ROUNDED weights; on a diagonal it is the sum of the fp32 values, here.
+    // (v_dot2c_f32_bf16, which adds two of them at once, waits until the matrix pipe of the SIMD is empty: with 32 of them
+    // per tile in here a full pair of 32 heads x 65536 takes 71 ms instead of 59.)
+    // Step j takes the exponential of score j, the exponent of the next and the rounding of the two before: what depends on
+    // an instruction comes a product later, or the wavefront would wait for it.
+    float ready, top;                        // the exponent of the next score; the largest weight
+    u32x4 word;
+    auto begin = [&](const Half& s) { ready = fmaf(s[0][0][0], c2, -mc[0]); };
+    auto pair = [&](Half& s, int j, char* px) {      // weights j - 2 and j - 1
+      const int nb = (j - 2) >> 3, e = (j - 2) & 7;
+      const float w0 = s[e >> 2][nb][e & 3], w1 = s[e >> 2][nb][(e & 3) + 1];
+      bf16x2 two;
+      two[0] = static_cast<__bf16>(w0);
+      two[1] = static_cast<__bf16>(w1);
+      top = fmaxf(fmaxf(top, w0), w1);
+      word[e >> 1] = __builtin_bit_cast(uint32_t, two);
+      if (e == 6) *reinterpret_cast<u32x4*>(px + nb * 1024) = word;
+    };
+    auto score = [&](auto rounded, Half& s, float (&sum)[RB], int j, char* px) {
+      const int nb = j >> 3, e = j & 7;
+      const float w = __builtin_amdgcn_exp2f(ready);
+      if (j + 1 < 8 * RB) ready = fmaf(s[((j + 1) >> 2) & 1][(j + 1) >> 3][(j + 1) & 3], c2, -mc[(j + 1) >> 3]);
+      if (j >= 2 && !(j & 1)) pair(s, j, px);
+      if (!decltype(rounded)::value && j > 0) {      // the weight before
+        const int b = (j - 1) >> 3, i = (j - 1) & 7;
+        sum[b] = i ? sum[b] + s[i >> 2][b][i & 3] : s[0][b][0];
+      }
+      s[e >> 2][nb][e & 3] = w;
+    };
+    auto end = [&](auto rounded, Half& s, float (&sum)[RB], char* px) {
+      pair(s, 8 * RB, px);
+      if (!decltype(rounded)::value) sum[RB - 1] += s[1][RB - 1][3];
     };
 
-    __syncthreads();                         // tile 0 is in LDS
-    for (int it = 0; it < ntiles; ++it) {    // slot it: finish tile it - 1
-      if (it > 0) pv_tile(it - 1);
-      __syncthreads();
+    // Online softmax (exp2 domain) against a reference maximum that is only
+    // moved when it has to be.  A half is first exponentiated against the reference as it stands,
+    // without looking for its maximum: as long as no score lies more than 2^14 above the
+    // reference, the exponentials are harmless in fp32 / bf16, O needs no rescaling, and the final
+    // division by the row sum removes the reference.  The reference is derived from the scores
+    // themselves (row maximum, exchanged between the lanes of a row) on a row's first keys -
+    // so the largest weight seen is at least 1 and later keys cannot underflow the row sum - and
+    // again when the largest weight of a tile shows a score far above it (or is no number): the tile's
+    // products are then done once more and taken against the moved reference.
+    Half sa, sb;                             // the scores of keys 0 .. 31 and 32 .. 63 of a tile
+    products(sa, smem + OFF_K, 0);
+    {
+      const Rows16 rows(smem + OFF_K, a_base);
+#pragma unroll
+      for (int n = 0; n < AHEAD; ++n) read_ahead(rows, 1, n);
     }
-    pv_tile(ntiles - 1);
-    __syncthreads();                         // row statistics are in LDS
+    int it = 0, k_slot = 0;
+    auto tile = [&](auto rounded) {
+      const int k0 = it * BN, next = k_slot == 2 ? 0 : k_slot + 1;
+      const char* Ks = smem + OFF_K + k_slot * TILE_BYTES;
+      const char* Kn = smem + OFF_K + next * TILE_BYTES;
+      // This wavefront's pieces of the K tile after the next, issued one at a time between the products: in a burst they
+      // would stall it while the memory pipe takes them in.
+      const TileCopy16 cn = k_plan(it + 2, next == 2 ? 0 : next + 1);
+      const Rows16 rows(Ks, a_base), rows_next(Kn, a_base);
+      char* px = smem + OFF_PX + (it & 1) * PX_BYTES + sw * PX_WAVE + lane * 16;
+      float sum0[RB], sum1[RB];
+      top = 0.f;
 
-    if (qvalid) {
-      const float inv = reinterpret_cast<const float*>(smem + OFF_ST)[sw * 32 + r32];
-      store_o(o, p, head, qrow, hh, inv);
+      mask(sa, k0);
+      first_reference(sa);
+      begin(sa);
+#pragma unroll
+      for (int n = 0; n < 8; ++n) {
+        // The slot's barrier: not at its end, where the last weights are still on their way into LDS, but behind
+        // the first products of the next.  (No row reads are in flight here.)
+        if (n == 1) {
+          lds_dma_wait();
+          __syncthreads();
+          read_ahead(rows, 1, AHEAD);
+        }
+        if (n > 0) {
+          if (n + AHEAD < 8) read_ahead(rows, 1, n + AHEAD);
+          else read_ahead(rows_next, 0, n + AHEAD - 8);
+        }
+#pragma unroll
+        for (int nb = 0; nb < RB; ++nb) {
+          product(sb, __builtin_bit_cast(bf16x8, x[n & AHEAD]), n, nb);
+          score(rounded, sa, sum0, RB * n + nb, px);
+          DFA_SCHED_FENCE();
+        }
+        if (n == 1) tile16_copy_piece<0>(cn);
+        if (n == 3) tile16_copy_piece<1>(cn);
+        if (n == 5) tile16_copy_piece<2>(cn);
+        if (n == 7) tile16_copy_piece<3>(cn);
+      }
+      end(rounded, sa, sum0, px);
+      mask(sb, k0 + 32);
+      first_reference(sb);
+      begin(sb);
+#pragma unroll
+      for (int n = 0; n < 8; ++n) {
+        if (n + AHEAD < 8) read_ahead(rows_next, 0, n + AHEAD);
+        else read_ahead(rows_next, 1, n + AHEAD - 8);
+#pragma unroll
+        for (int nb = 0; nb < RB; ++nb) {
+          product(sa, __builtin_bit_cast(bf16x8, x[n & AHEAD]), n, nb);
+          score(rounded, sb, sum1, RB * n + nb, px + RB * 1024);
+          DFA_SCHED_FENCE();
+        }
+      }
+      end(rounded, sb, sum1, px + RB * 1024);
+      const bool moved = __any(top > 16384.f);
+      if (moved) {
+        float mx[RB];
+        products(sb, Ks, 0);
+        mask(sb, k0);
+#pragma unroll
+        for (int nb = 0; nb < RB; ++nb) mx[nb] = row_max(sb, nb);
+        products(sb, Ks, 1);
+        mask(sb, k0 + 32);
+#pragma unroll
+        for (int nb = 0; nb < RB; ++nb) {
+          const float m_new = fmaxf(fmaxf(m_run[nb], mx[nb]), row_max(sb, nb));
+          const float mc_new = (m_new == -INFINITY) ? 0.f : m_new * c2;
+          const float alpha = __builtin_amdgcn_exp2f(m_run[nb] * c2 - mc_new);
+          m_run[nb] = m_new;
+          mc[nb] = mc_new;
+          l_run[nb] *= alpha;
+          if (g == 0) al[(it & 1) * (AL_BYTES / 4) + nb * 16] = alpha;
+        }
+        begin(sb);
+#pragma unroll
+        for (int j = 0; j < 8 * RB; ++j) score(rounded, sb, sum1, j, px + RB * 1024);
+        end(rounded, sb, sum1, px + RB * 1024);
+        products(sb, Ks, 0);
+        mask(sb, k0);
+        begin(sb);
+#pragma unroll
+        for (int j = 0; j < 8 * RB; ++j) score(rounded, sb, sum0, j, px);
+        end(rounded, sb, sum0, px);
+      }
+      if (!decltype(rounded)::value)
+#pragma unroll
+        for (int nb = 0; nb < RB; ++nb) l_run[nb] += sum0[nb] + sum1[nb];
+      if (lane == 0) mv[(it & 1) * 4] = moved;
+      k_slot = next;
+    };
+    __builtin_amdgcn_s_setprio(3);           // before the PV wavefront, which fills the gaps
+    if constexpr (kSpans<Args>) {
+      const int before = min(seen, off / BN);      // tiles before the chunk's own keys
+      for (; it < before; ++it) tile(std::true_type{});
     }
+    for (; it < seen; ++it) tile(std::bool_constant<!CAUSAL>{});
+    for (; CAUSAL && it < ntiles; ++it) {    // tiles above this block's diagonal: only the copies
+      const int next = k_slot == 2 ? 0 : k_slot + 1;
+      lds_dma_wait();
+      __syncthreads();
+      tile16_copy(k_plan(it + 2, next == 2 ? 0 : next + 1));
+      k_slot = next;
+    }
+    // references and row sums to the PV wavefront
+#pragma unroll
+    for (int nb = 0; nb < RB; ++nb) {
+      float l_tot = l_run[nb] + __shfl_xor(l_run[nb], 16);
+      l_tot += __shfl_xor(l_tot, 32);
+      float* st = reinterpret_cast<float*>(smem + OFF_ST) + sw * WROWS + nb * 16 + r16;
+      if (g == 0) { st[0] = m_run[nb]; st[BMW] = l_tot; }
+    }
+    lds_dma_wait();
+    __syncthreads();                         // the PV wavefronts' last slot
+  } else {
+    // ------------------------------------------------------------------ PV wavefront: the rows of S wavefront sw
+    const uint32_t g_base = gather16_base(lane);
+    const char* vg = uniform_ptr(p.v + kh * p.kv_sh);
+
+    f32x4 o[8][RB];      // O^T: [16 columns of d][16 rows]
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int nb = 0; nb < RB; ++nb) o[i][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (p.accumulate) {
+      bool has[RB];
+#pragma unroll
+      for (int nb = 0; nb < RB; ++nb) has[nb] = qrow + 16 * nb < p.s_q && p.lse[head * p.l_sh + qrow + 16 * nb] > -INFINITY;
+      load_o(o, p, head, qrow, g, has);
+    }
+    auto v_plan = [&](int it) {
+      return tile16_copy_plan<RAGGED>(vg, kv_rowbytes, min(it, ntiles - 1) * BN, last, tl, smem + OFF_V + (it & 1) * TILE_BYTES, sw, lane);
+    };
+    __syncthreads();                         // K tiles 0 and 1 are in LDS
+    tile16_copy(v_plan(0));
+    lds_dma_wait();
+    __syncthreads();
+    // Slot it, from the barrier at which P of tile it - 1 is there: V tile `it` on its way (after the last the same once more,
+    // into the slot that nobody reads), O^T = O^T * factor + V^T P^T for tile it - 1, and the row sums of its rounded weights.
+    // Sums: v_mfma_f32_4x4x4_16b_bf16 against ones adds up a lane's four weights, in each of four registers (in 8 cycles of a
+    // pipe that has 2048 to do; taking the weights apart for v_add_f32 takes 128 vector instructions a tile).
+    f32x4 l_run[RB];                         // this lane's quarter of the rows' sums, four times
+#pragma unroll
+    for (int nb = 0; nb < RB; ++nb) l_run[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int it = 1;
+    auto slot = [&](auto rounded) {
+      lds_dma_wait();
+      __syncthreads();
+      __builtin_amdgcn_s_setprio(3);         // up to the products, or the S wavefront leaves it no room to get there
+      const TileCopy16 cn = v_plan(it);
+      const int t = it - 1;
+      const char* Vs = smem + OFF_V + (t & 1) * TILE_BYTES;
+      const char* px = smem + OFF_PX + (t & 1) * PX_BYTES + sw * PX_WAVE + lane * 16;
+      const float* al = reinterpret_cast<const float*>(smem + OFF_AL) + (t & 1) * (AL_BYTES / 4) + sw * WROWS + r16;
+      constexpr int AHEAD = 3;               // V^T gathers run this many steps ahead of their MFMAs
+      const Gather16 cols(Vs, g_base);       // step n = 8 * (32-key block) + d block
+      auto gather = [&](int n) { return cols.read(2 * (n >> 3), n & 7); };
+      bf16x8 y[AHEAD + 1];
+      u32x4 pa[2][RB];
+      const int moved = *(reinterpret_cast<const int*>(smem + OFF_MV) + (t & 1) * 4 + sw);
+#pragma unroll
+      for (int n = 0; n < AHEAD; ++n) y[n] = gather(n);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int nb = 0; nb < RB; ++nb) pa[u][nb] = *reinterpret_cast<const u32x4*>(px + (u * RB + nb) * 1024);
+      if (__builtin_amdgcn_readfirstlane(moved)) {
+#pragma unroll
+        for (int nb = 0; nb < RB; ++nb) {
+          const float a = al[nb * 16];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) o[i][nb] *= a;
+          l_run[nb] *= a;
+        }
+      }
+      __builtin_amdgcn_s_setprio(0);
+      DFA_SCHED_FENCE();
+#pragma unroll
+      for (int n = 0; n < 16; ++n) {
+        if (n + AHEAD < 16) y[(n + AHEAD) % (AHEAD + 1)] = gather(n + AHEAD);
+#pragma unroll
+        for (int nb = 0; nb < RB; ++nb) {
+          o[n & 7][nb] = mfma16(y[n % (AHEAD + 1)], __builtin_bit_cast(bf16x8, pa[n >> 3][nb]), o[n & 7][nb]);
+          if (decltype(rounded)::value && !(n & 3)) {      // half of the row's weights of 32 keys
+            const u32x4 w = pa[n >> 3][nb];
+            l_run[nb] = mfma_sum4(n & 4 ? u32x2{w[2], w[3]} : u32x2{w[0], w[1]}, l_run[nb]);
+          }
+          DFA_SCHED_FENCE();
+        }
+        if (n == 0) tile16_copy_piece<0>(cn);
+        if (n == 2) tile16_copy_piece<1>(cn);
+        if (n == 4) tile16_copy_piece<2>(cn);
+        if (n == 6) tile16_copy_piece<3>(cn);
+      }
+    };
+    if constexpr (kSpans<Args>) {
+      const int before = min(seen, off / BN);
+      for (; it <= before; ++it) slot(std::true_type{});
+    }
+    for (; it <= seen; ++it) slot(std::bool_constant<!CAUSAL>{});
+    for (; CAUSAL && it <= ntiles; ++it) {
+      lds_dma_wait();
+      __syncthreads();
+      tile16_copy(v_plan(it));
+    }
+    lds_dma_wait();                          // nothing is left on its way into LDS
+    // logsumexp and 1 / row sum
+    float inv[RB];
+#pragma unroll
+    for (int nb = 0; nb < RB; ++nb) {
+      float l_tot = l_run[nb][0];
+      l_tot += __shfl_xor(l_tot, 16);
+      l_tot += __shfl_xor(l_tot, 32);
+      const float* st = reinterpret_cast<const float*>(smem + OFF_ST) + sw * WROWS + nb * 16 + r16;
+      l_tot += st[BMW];
+      inv[nb] = l_tot > 0.f ? 1.f / l_tot : 0.f;
+      const int row = qrow + 16 * nb;
+      if (g == 0 && row < p.s_q) p.lse[head * p.l_sh + row] = l_tot > 0.f ? st[0] * p.scale + logf(l_tot) : -INFINITY;
+    }
+    store_o(o, p, head, qrow, g, inv);
   }
 }
 

@@ -29,6 +29,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // an operand piece as raw bits (for values carried around a loop)
 
 #define DFA_LDS __attribute__((address_space(3)))
@@ -40,6 +41,9 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // (Inline-assembly forms of the MFMA with operand register files fixed by hand were tried and
 // dropped: hipcc places accumulator copies next to such statements without the wait states the
 // hardware needs there, which gave wrong results; the builtin above is the only form used.)
+
+// for lambdas that work on register arrays
+#define DFA_INLINE __attribute__((always_inline))
 
 #define DFA_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 // Workgroup barrier without the wait for this wavefront's outstanding memory operations that
@@ -55,6 +59,10 @@ __device__ __forceinline__ int prow(int r) { return (r & ~15) | ((r & 3) << 2) |
 
 // byte offset of 16-byte chunk c of logical row r
 __device__ __forceinline__ int tile_off(int r, int c) { return prow(r) * kRowBytes + (c << 4); }
+
+__device__ __forceinline__ uint32_t lds_addr(const char* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((DFA_LDS const char*)p));
+}
 
 __device__ __forceinline__ bf16x8 lds_read_b128(const char* base, int off) {
   return *reinterpret_cast<const bf16x8*>(base + off);
@@ -139,10 +147,6 @@ __device__ __forceinline__ TileLane tile_lane(int w, int lane, uint32_t rowbytes
     m.voff[j] = static_cast<uint32_t>(row) * rowbytes + cb + (j < 4 ? 3072 - 1024 * j : 3072);
   }
   return m;
-}
-
-__device__ __forceinline__ uint32_t lds_addr(const char* p) {
-  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((DFA_LDS const char*)p));
 }
 
 // gbase and lds must be wave-uniform; v* are this lane's byte offsets from gbase.
@@ -242,6 +246,13 @@ __device__ __forceinline__ void tile_copy_piece(const TileCopy& c) {
                  :: "s"(c.lds16), "v"(c.v[4]), "s"(c.g) : "memory", "m0");
 }
 
+// A pointer that is the same in all lanes, in scalar registers whatever the compiler can prove of it.
+__device__ __forceinline__ const char* uniform_ptr(const void* p) {
+  const uint64_t x = reinterpret_cast<uintptr_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(x)), hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(x >> 32));
+  return reinterpret_cast<const char*>(static_cast<uint64_t>(hi) << 32 | lo);
+}
+
 // ---- 16x16x32 tiles -------------------------------------------------------------------------
 // v_mfma_f32_16x16x32_bf16 computes C[16x16] += A[16x32] B[32x16]; with lane l, r = l % 16, g = l / 16:
 //   A operand (8 bf16): A[r][8g .. 8g+7]     B operand (8 bf16): B[8g .. 8g+7][r]
@@ -254,42 +265,58 @@ __device__ __forceinline__ void tile_copy_piece(const TileCopy& c) {
 // group g are rows 4g .. 4g+3 of the first and of the second tile, and the A operand is gathered in that order.
 //
 // LDS tile: blocks of 16 rows of 128 bf16.  Row r of a block lies at row16_off(r / 4) + 256 (r % 4), its 16-byte
-// chunk c at c ^ 2 (r % 4); a row read takes step s of a product over d from chunk 8 (s / 2) + 2g + s % 2.  With that
-// a row read (16 rows x 4 chunks, ds_read_b128) and a gather (16 rows x 32 bytes, ds_read_b64_tr_b16) meet
-// every bank once per pass, every address is a per-lane base (one, and one per pair of column blocks) plus a constant, and
-// the four rows of a 1 KB piece of a copy lie together: a tile of 64 rows is 16 pieces, no padding is copied.
+// chunk c at c ^ 2 (r % 4) ^ (r / 8); a row read takes step s of a product over d from chunk 8 (s / 2) + 2g + s % 2.  With
+// that a row read (16 rows x 4 chunks, ds_read_b128) and a gather (16 rows x 32 bytes, ds_read_b64_tr_b16) meet every bank
+// once per pass, every address is one of two (row reads) or four (gathers) per-lane bases, an exclusive or apart, plus a
+// constant, and the four rows of a 1 KB piece of a copy lie together: a tile of 64 rows is 16 pieces, no padding is
+// copied.  Tiles start at multiples of 128 bytes.
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// c[i] + the sum of the lane's four bf16 values, for each i (a product against ones).
+__device__ __forceinline__ f32x4 mfma_sum4(u32x2 w, f32x4 c) {
+  const s16x4 ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4, w), c, 0, 0, 0);
+}
+
 constexpr int kBlock16 = 4608;                        // bytes of a 16-row block
 constexpr int kTile64 = 4 * kBlock16;                 // of a 64-row tile
-__host__ __device__ constexpr int row16_off(int k) { return 1024 * k + 128 * (k & 1) + 144 * (k >> 1); }      // 0, 1152, 2192, 3344
+__host__ __device__ constexpr int row16_off(int k) { return 1152 * k; }
 
 // element that step s of a product over d takes first in lane group g (8 from there on)
 __device__ __forceinline__ int step16_col(int s, int g) { return 64 * (s >> 1) + 16 * g + 8 * (s & 1); }
-// per-lane base of row reads; block b, step s: + b * kBlock16 + step16_off(s)
-__device__ __forceinline__ int row16_base(int lane) {
-  const int r = lane & 15, g = lane >> 4;
-  return row16_off(r >> 2) + 256 * (r & 3) + 32 * (g ^ (r & 3));
-}
-__host__ __device__ constexpr int step16_off(int s) { return 128 * (s >> 1) + 16 * (s & 1); }
 
-// Gathers: the 8 values  tile[row0 + 16 (e/4) + 4g + e%4][16 db + lane%16],  e = 0..7, of two 16-row blocks.
-struct Gather16 { int base[4]; };                     // by db % 4
-__device__ __forceinline__ Gather16 gather16_bases(int lane) {
+// Row reads: rows[r] = X[16 block + lane % 16][step16_col(s, g) ..  + 7].  row16_base: the per-lane part of an address.
+__device__ __forceinline__ uint32_t row16_base(int lane) {
+  const int r = lane & 15, g = lane >> 4;
+  return row16_off(r >> 2) + 256 * (r & 3) + 32 * (g ^ (r & 3)) + 16 * (r >> 3);
+}
+struct Rows16 {
+  uint32_t a[2];                                      // by s % 2
+  __device__ __forceinline__ Rows16(const char* tile, uint32_t base) { a[0] = lds_addr(tile) + base; a[1] = a[0] ^ 16; }
+  __device__ __forceinline__ bf16x8 read(int block, int s) const {
+    return *(DFA_LDS const bf16x8*)(a[s & 1] + block * kBlock16 + 128 * (s >> 1));
+  }
+};
+
+// Gathers: the 8 values  X[16 block + 16 (e/4) + 4g + e%4][16 db + lane%16],  e = 0..7, of two 16-row blocks.
+__device__ __forceinline__ uint32_t gather16_base(int lane) {
   const int g = lane >> 4, q = (lane >> 2) & 3, j = lane & 3;
-  Gather16 m;
+  return row16_off(g) + 256 * q + 32 * q + 16 * ((j >> 1) ^ (g >> 1)) + 8 * (j & 1);
+}
+struct Gather16 {
+  uint32_t a[4];                                      // by db % 4
+  __device__ __forceinline__ Gather16(const char* tile, uint32_t base) {
 #pragma unroll
-  for (int b = 0; b < 4; ++b) m.base[b] = row16_off(g) + 256 * q + 32 * (b ^ q) + 8 * j;
-  return m;
-}
-__device__ __forceinline__ bf16x8 gather16(const char* tile, const Gather16& m, int block, int db) {
-  const char* p = tile + m.base[db & 3];
-  const int off = block * kBlock16 + 128 * (db >> 2);
-  const bf16x4 lo = lds_read_tr(p, off), hi = lds_read_tr(p, off + kBlock16);
-  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
+    for (int b = 0; b < 4; ++b) a[b] = (lds_addr(tile) + base) ^ (32 * b);
+  }
+  __device__ __forceinline__ bf16x8 read(int block, int db) const {
+    const int at = block * kBlock16 + 128 * (db >> 2);
+    const bf16x4 lo = lds_read_tr_at(a[db & 3], at), hi = lds_read_tr_at(a[db & 3], at + kBlock16);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  }
+};
 
 __device__ __forceinline__ bf16x8 pack16(f32x4 a, f32x4 b) {
   bf16x8 r;
@@ -306,7 +333,7 @@ constexpr int kEarly16 = row16_off(3);
 __device__ __forceinline__ void tile16_lane_rc(int w, int lane, int j, int& row, uint32_t& cb) {
   const int q = lane >> 4;
   row = 16 * w + 4 * j + q;
-  cb = static_cast<uint32_t>((lane & 15) ^ (2 * q)) * 16 + (kEarly16 - row16_off(j));
+  cb = static_cast<uint32_t>((lane & 15) ^ (2 * q) ^ (j >> 1)) * 16 + (kEarly16 - row16_off(j));
 }
 __device__ __forceinline__ TileLane16 tile16_lane(int w, int lane, uint32_t rowbytes) {
   TileLane16 m;
