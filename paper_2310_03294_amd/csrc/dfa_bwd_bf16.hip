@@ -14,8 +14,7 @@
 //                                        dS = P o (dP - D), dK^T += Q^T dS
 //  (queries x keys tiles on v_mfma_f32_16x16x32_bf16: each lane holds 16 queries of TWO keys; P
 //  and dS are fed back from registers as B operands; dO^T, Q^T are gathered from LDS with the
-//  transposing read; with 32x32x16 products a full pair of 32 heads x 16384 took 12216 us, 11492
-//  so).  The dP wavefronts run one tile behind, so one barrier per tile suffices.
+//  transposing read; with 32x32x16 products a full pair of 32 heads x 16384 took 6 % longer).  The dP wavefronts run one tile behind, so one barrier per tile suffices.
 //  Wavefronts raise their priority while they issue MFMAs, so that the other kind's VALU work
 //  fills the gaps instead of delaying them.
 //  dv / dk are written once per workgroup (summed over the group's query heads in registers).
@@ -86,9 +85,9 @@ constexpr int BM = 64;      // query rows per LDS tile
 constexpr int QTILE_BYTES = kTile64;
 constexpr int LD_BYTES = 1024;                // lse'[64], -D[64], 128 spare floats
 constexpr int PX_BYTES = 4 * 4096;            // P hand-over: 4 key blocks x (64 x 32 bf16)
-// LDS map.  Tile t lives in Q slot t % 3, dO slot t % 2, lse/D slot t % 3, P slot t % 2.
+// LDS map.  Tile t lives in Q slot t % 4, dO slot t % 2, lse/D slot t % 3, P slot t % 2.
 constexpr int OFF_Q = 0;
-constexpr int OFF_G = OFF_Q + 3 * QTILE_BYTES;
+constexpr int OFF_G = OFF_Q + 4 * QTILE_BYTES;
 constexpr int OFF_LD = OFF_G + 2 * QTILE_BYTES;
 constexpr int OFF_PX = OFF_LD + 3 * LD_BYTES;
 constexpr int SMEM_BYTES = OFF_PX + 2 * PX_BYTES;
@@ -133,12 +132,10 @@ __device__ __forceinline__ void qtile_advance_if(QTileCursor& cur, bool adv, con
 }
 
 // Rows past s_q are clamped to the last row instead of zero-filled: their lse' is +inf, so P and
-// dS vanish for them whatever (finite) Q and dO the tile holds.  Qs, Gs: LDS tiles to fill.
-__device__ __forceinline__ void qtile_copy(const QTileCursor& cur, const TileLane16& m, const BwdParams& p,
-                                           char* Qs, char* Gs, int w, int lane) {
-  const uint32_t rowbytes = static_cast<uint32_t>(p.q_ss) * 2;
-  tile16_copy(tile16_copy_plan(cur.qh, rowbytes, cur.q0, p.s_q - 1, m, Qs, w, lane));
-  tile16_copy(tile16_copy_plan(cur.gh, rowbytes, cur.q0, p.s_q - 1, m, Gs, w, lane));
+// dS vanish for them whatever (finite) Q and dO the tile holds.  head: Q or dO of the cursor's head.
+__device__ __forceinline__ void qtile_copy(const char* head, const QTileCursor& cur, const TileLane16& m, const BwdParams& p,
+                                           char* tile, int w, int lane) {
+  tile16_copy(tile16_copy_plan(head, static_cast<uint32_t>(p.q_ss) * 2, cur.q0, p.s_q - 1, m, tile, w, lane));
 }
 
 // lse (S wavefronts 0, 2, 3) or D (S wavefront 1) of the tile's 64 rows, one per lane, into a
@@ -159,25 +156,32 @@ __device__ __forceinline__ void qtile_store(const QTileRegs& t, float* LDs, int 
   LDs[tid] = is_d ? d : l;
 }
 
-// c[mb][nb] += X[16-row block mb] * B^T[16-key block nb] over d for the tile's 64 rows: X rows are read from LDS
-// (A operand, each for two products), B is the wavefront's K^T or V^T held in registers; the caller sets what the
-// chains start from (zero, or -D for the dP products).
+// A wavefront's stream of A operands: per slot 16 row reads (of a product over d) and 16 gathers (of a product over the
+// tile's rows), each for two products, in the order in which they are used.  An LDS read that was asked for LEAD operands
+// ago has arrived even with all wavefronts reading (about 330 cycles; the LDS itself is busy a third of the time): with
+// 6 row reads and 4 gathers ahead every product waited for its operand.  With this and the same in dq a full pair of 32 heads
+// x 16384 takes 11150 us instead of 11300, a diagonal of 32 over 8 heads x 1500 98.0 instead of 101.4; the matrix pipes
+// are 64 (dk, dv) and 68 % (dq) busy at 1.95 GHz.
+// (Kept as raw 32-bit vectors: carried around a loop as bf16 vectors they would be taken apart into 16-bit halves and put
+// together again.)
+constexpr int RING = 16, LEAD = 14;
+typedef u32x4 Ring[RING];
 struct NoHook { __device__ __forceinline__ void operator()(int) const {} };
-// hook(n) runs after the MFMAs of step n = 4 s + mb (the callers issue their tile-copy pieces there)
-template <class Hook = NoHook>
-__device__ __forceinline__ void row_products(f32x4 (&c)[4][2], const char* Xs, uint32_t a_base,
-                                             const bf16x8 (&bT)[4][2], Hook hook = Hook()) {
-  constexpr int AHEAD = 6;                      // LDS reads run this many steps ahead of the MFMAs
-  const Rows16 rows(Xs, a_base);
-  bf16x8 x[AHEAD + 1];
-#pragma unroll
-  for (int n = 0; n < AHEAD; ++n) x[n] = rows.read(n & 3, n >> 2);
-  DFA_SCHED_FENCE();
+
+// c[mb][nb] += X[16-row block mb] * B^T[16-key block nb] over d for the tile's 64 rows: X rows are read from LDS
+// (A operand), B is the wavefront's K^T or V^T held in registers; the caller sets what the
+// chains start from (zero, or -D for the dP products).  Step n = 4 s + mb.
+__device__ __forceinline__ u32x4 row_operand(const Rows16& rows, int n) { return __builtin_bit_cast(u32x4, rows.read(n & 3, n >> 2)); }
+// read(i): operand i of the stream, counted from the step's own slot; hook(n) runs after the MFMAs of step n (the callers issue
+// their tile-copy pieces there)
+template <int AT, class Read, class Hook = NoHook>
+__device__ __forceinline__ void row_products(f32x4 (&c)[4][2], Ring& z, const bf16x8 (&bT)[4][2], Read read, Hook hook = Hook()) {
 #pragma unroll
   for (int n = 0; n < 16; ++n) {
-    if (n + AHEAD < 16) x[(n + AHEAD) % (AHEAD + 1)] = rows.read((n + AHEAD) & 3, (n + AHEAD) >> 2);
-    c[n & 3][0] = mfma16(x[n % (AHEAD + 1)], bT[n >> 2][0], c[n & 3][0]);
-    c[n & 3][1] = mfma16(x[n % (AHEAD + 1)], bT[n >> 2][1], c[n & 3][1]);
+    z[(n + LEAD) % RING] = read(AT + n + LEAD);
+    const bf16x8 a = __builtin_bit_cast(bf16x8, z[n]);
+    c[n & 3][0] = mfma16(a, bT[n >> 2][0], c[n & 3][0]);
+    c[n & 3][1] = mfma16(a, bT[n >> 2][1], c[n & 3][1]);
     hook(n);
     DFA_SCHED_FENCE();
   }
@@ -185,30 +189,14 @@ __device__ __forceinline__ void row_products(f32x4 (&c)[4][2], const char* Xs, u
 
 // acc[db][nb] += Y^T[16 columns db of d][64 queries] * W[64 queries][16 keys nb]: Y^T is gathered from the
 // row-major LDS tile with the transposing read, W (P or dS) comes from registers in the order
-// two MFMA result tiles have (w[u][nb] = query blocks 2u and 2u + 1).
-constexpr int COL_AHEAD = 4;              // gathers run this many steps ahead
-__device__ __forceinline__ u32x4 col_gather(const Gather16& cols, int n) {       // n = u * 8 + db
-  return __builtin_bit_cast(u32x4, cols.read(2 * (n >> 3), n & 7));
-}
-// The first COL_AHEAD gathers of col_products, issued early (e.g. before a barrier) so that the
-// products can start without waiting for LDS.
-// (The pieces are kept as raw 32-bit vectors: carried around a loop as bf16 vectors they would be
-// taken apart into 16-bit halves and put together again.)
-__device__ __forceinline__ void col_prefetch(u32x4 (&y)[COL_AHEAD + 1], const Gather16& cols) {
-#pragma unroll
-  for (int n = 0; n < COL_AHEAD; ++n) y[n] = col_gather(cols, n);
-}
-template <bool PRE, class Hook = NoHook>
-__device__ __forceinline__ void col_products(f32x4 (&acc)[8][2], const Gather16& cols,
-                                             const bf16x8 (&w)[2][2], u32x4 (&y)[COL_AHEAD + 1],
-                                             Hook hook = Hook()) {
-  constexpr int AHEAD = COL_AHEAD;
-  if (!PRE) col_prefetch(y, cols);
-  DFA_SCHED_FENCE();
+// two MFMA result tiles have (w[u][nb] = query blocks 2u and 2u + 1).  Step n = 8 u + db.
+__device__ __forceinline__ u32x4 col_operand(const Gather16& cols, int n) { return __builtin_bit_cast(u32x4, cols.read(2 * (n >> 3), n & 7)); }
+template <int AT, class Read, class Hook = NoHook>
+__device__ __forceinline__ void col_products(f32x4 (&acc)[8][2], Ring& z, const bf16x8 (&w)[2][2], Read read, Hook hook = Hook()) {
 #pragma unroll
   for (int n = 0; n < 16; ++n) {
-    if (n + AHEAD < 16) y[(n + AHEAD) % (AHEAD + 1)] = col_gather(cols, n + AHEAD);
-    const bf16x8 a = __builtin_bit_cast(bf16x8, y[n % (AHEAD + 1)]);
+    z[(n + LEAD) % RING] = read(AT + n + LEAD);
+    const bf16x8 a = __builtin_bit_cast(bf16x8, z[n]);
     acc[n & 7][0] = mfma16(a, w[n >> 3][0], acc[n & 7][0]);
     acc[n & 7][1] = mfma16(a, w[n >> 3][1], acc[n & 7][1]);
     hook(n);
@@ -269,8 +257,8 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
     return;
   }
 
-  // Tile staging.  Two cursors: `cur` for the tile copies (tile t + 1 during slot t; Q by the S
-  // wavefronts, dO by the dP wavefronts), `curl` for lse / D (S wavefronts), which pass through a
+  // Tile staging.  Two cursors: `cur` for the tile copies (during slot t Q tile t + 2 by the S wavefronts, which read a
+  // tile's first operands before its slot begins, and dO tile t + 1 by the dP wavefronts), `curl` for lse / D (S wavefronts), which pass through a
   // register and run one tile further ahead.  Order inside a slot: store the held lse / D, load
   // the next ones, THEN issue the copies - the compiler knows nothing of the copies, so any wait
   // it places for its own loads must come before them or it would wait for them too.
@@ -294,7 +282,10 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
       qtile_advance(curl, p, q_begin, q_end);
       qtile_load_ld(tr, curl, p, tid);           // lse / D of tile 1, stored in slot 0
     }
-    qtile_copy(cur, tl, p, smem + OFF_Q, smem + OFF_G, kb, lane);
+    qtile_copy(cur.qh, cur, tl, p, smem + OFF_Q, kb, lane);
+    qtile_copy(cur.gh, cur, tl, p, smem + OFF_G, kb, lane);
+    if (niter > 1) qtile_advance(cur, p, q_begin, q_end);
+    qtile_copy(cur.qh, cur, tl, p, smem + OFF_Q + QTILE_BYTES, kb, lane);
     lds_dma_wait();                                // this wavefront's copies into LDS have landed
   }
   __syncthreads();
@@ -305,28 +296,33 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
   // the MFMAs of the other.  Both kinds run niter + 1 slots (the S wavefronts idle in the last,
   // the dP wavefronts have no dS/dK in the first); each kind has its own straight-line loop.
   int slot = 0;            // t % 3
+  auto q_tile = [&](int t) { return smem + OFF_Q + (t & 3) * QTILE_BYTES; };
+  Ring z;
   if (!dp_wave) {
     int q0 = q_begin + it0 % ntq * BM;      // first query row of tile `it`
+    {
+      const Rows16 rows(q_tile(0), a_base);
+#pragma unroll
+      for (int n = 0; n < LEAD; ++n) z[n] = row_operand(rows, n);
+    }
     for (int it = 0; it < niter; ++it) {
-      const bool more = it + 1 < niter;
       const int next = slot == 2 ? 0 : slot + 1;
-      const char* Qs = smem + OFF_Q + slot * QTILE_BYTES;
-      const char* Gs = smem + OFF_G + (it & 1) * QTILE_BYTES;
+      const Rows16 rows(q_tile(it), a_base), rows_next(q_tile(it + 1), a_base);
+      const Gather16 cols(smem + OFF_G + (it & 1) * QTILE_BYTES, g_base);
       const float* Ls = reinterpret_cast<const float*>(smem + OFF_LD + slot * LD_BYTES);
       // Staging, all of it inside the S products so that it costs no time of its own, and without
       // branches (past the last tile the cursors stay: the same tile, lse and D go once more into
       // ring slots nobody reads).  First (step 0) lse / D: tile it + 1 from the register into
       // LDS, tile it + 2 into the register - before the first copy of the slot, because the
       // compiler's wait for that register would otherwise wait for the copies too.  Then the Q
-      // tile it + 1 into ring slot `next`, one piece every other step.
-      qtile_advance_if(cur, more, p, q_begin, q_end);
-      const TileCopy16 cq = tile16_copy_plan<RAGGED>(cur.qh, q_rowbytes, cur.q0, p.s_q - 1, tl,
-                                                     smem + OFF_Q + next * QTILE_BYTES, kb, lane);
+      // tile it + 2, one piece every fourth step.
+      qtile_advance_if(cur, it + 2 < niter, p, q_begin, q_end);
+      const TileCopy16 cq = tile16_copy_plan<RAGGED>(cur.qh, q_rowbytes, cur.q0, p.s_q - 1, tl, q_tile(it + 2), kb, lane);
       f32x4 c[4][2];
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb) c[mb][0] = c[mb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
       __builtin_amdgcn_s_setprio(3);
-      row_products(c, Qs, a_base, bT, [&](int n) {          // S = Q K^T
+      row_products<0>(c, z, bT, [&](int i) DFA_INLINE { return i < 16 ? row_operand(rows, i) : col_operand(cols, i - 16); }, [&](int n) {          // S = Q K^T
         if (n == 1) {
           qtile_store(tr, reinterpret_cast<float*>(smem + OFF_LD + next * LD_BYTES), tid, kb == 1);
           qtile_advance_if(curl, it + 2 < niter, p, q_begin, q_end);
@@ -368,12 +364,13 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
 #pragma unroll
         for (int j = 0; j < 4; ++j) *reinterpret_cast<bf16x8*>(px + j * 1024) = w[j >> 1][j & 1];
       }
-      u32x4 y[COL_AHEAD + 1];
       __builtin_amdgcn_s_setprio(3);
-      col_products<false>(acc, Gather16(Gs, g_base), w, y);    // dV^T += dO^T P
+      col_products<16>(acc, z, w, [&](int i) DFA_INLINE { return i < 32 ? col_operand(cols, i - 16) : row_operand(rows_next, i - 32); });    // dV^T += dO^T P
       __builtin_amdgcn_s_setprio(0);
       lds_dma_wait();                                // this wavefront's copies into LDS have landed
-      __syncthreads();
+      // P and lse / D are in LDS: operands read after they were written have been used (a wavefront's LDS operations
+      // are done in order); what is still on its way is the next tile's.
+      DFA_BARRIER_NO_DRAIN();
       slot = next;
       q0 = q0 + BM >= q_end ? q_begin : q0 + BM;
     }
@@ -403,9 +400,6 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
           w[u][nb] = pack16(c[2 * u][nb], c[2 * u + 1][nb]);
         }
     };
-    // The first Q^T gathers of the next slot's dK products are issued before the barrier (that Q
-    // tile has been in LDS for a whole slot), so after the barrier only P has to be waited for.
-    u32x4 y[COL_AHEAD + 1];
     // The dP wavefronts copy the dO tiles: tile t + 1 during slot t, its pieces spread over the
     // products (past the last tile the cursor stays: the same tile goes into the unused slot).
     {  // slot 0: dP of tile 0 only
@@ -413,40 +407,45 @@ __device__ __forceinline__ void dkdv(const BwdParams& p, const Pair& pr, int ite
       const TileCopy16 cg = tile16_copy_plan<RAGGED>(cur.gh, q_rowbytes, cur.q0, p.s_q - 1, tl,
                                                      smem + OFF_G + QTILE_BYTES, kb, lane);
       neg_d(0);
-      row_products(c, smem + OFF_G, a_base, bT, [&](int n) {
+      const Rows16 rows(smem + OFF_G, a_base);
+      const Gather16 cols(q_tile(0), g_base);
+#pragma unroll
+      for (int n = 0; n < LEAD; ++n) z[n] = row_operand(rows, n);
+      row_products<16>(c, z, bT, [&](int i) DFA_INLINE { return i < 32 ? row_operand(rows, i - 16) : col_operand(cols, i - 32); }, [&](int n) {
         if (n == 1) tile16_copy_piece<0>(cg);
         if (n == 5) tile16_copy_piece<1>(cg);
         if (n == 9) tile16_copy_piece<2>(cg);
         if (n == 13) tile16_copy_piece<3>(cg);
       });
-      col_prefetch(y, Gather16(smem + OFF_Q, g_base));
       lds_dma_wait();
       DFA_BARRIER_NO_DRAIN();
       slot = 1;
     }
     for (int it = 1; it < niter; ++it) {
-      const int prev = slot == 0 ? 2 : slot - 1, next = slot == 2 ? 0 : slot + 1;
+      const int next = slot == 2 ? 0 : slot + 1;
+      const Rows16 rows(smem + OFF_G + (it & 1) * QTILE_BYTES, a_base);
+      const Gather16 cols(q_tile(it - 1), g_base), cols_next(q_tile(it), g_base);
       qtile_advance_if(cur, it + 1 < niter, p, q_begin, q_end);
       const TileCopy16 cg = tile16_copy_plan<RAGGED>(cur.gh, q_rowbytes, cur.q0, p.s_q - 1, tl,
                                                      smem + OFF_G + ((it + 1) & 1) * QTILE_BYTES, kb, lane);
       __builtin_amdgcn_s_setprio(3);
       dS_prev(it);
       neg_d(slot);                               // read straight into the accumulators, under the dK products
-      col_products<true>(acc, Gather16(smem + OFF_Q + prev * QTILE_BYTES, g_base), w, y, [&](int n) {  // dK^T += Q^T dS
+      col_products<0>(acc, z, w, [&](int i) DFA_INLINE { return i < 16 ? col_operand(cols, i) : row_operand(rows, i - 16); }, [&](int n) {  // dK^T += Q^T dS
         if (n == 1) tile16_copy_piece<0>(cg);
         if (n == 5) tile16_copy_piece<1>(cg);
         if (n == 9) tile16_copy_piece<2>(cg);
         if (n == 13) tile16_copy_piece<3>(cg);
       });
-      row_products(c, smem + OFF_G + (it & 1) * QTILE_BYTES, a_base, bT);   // dP - D = dO V^T - D
-      col_prefetch(y, Gather16(smem + OFF_Q + slot * QTILE_BYTES, g_base));
+      row_products<16>(c, z, bT, [&](int i) DFA_INLINE { return i < 32 ? row_operand(rows, i - 16) : col_operand(cols_next, i - 32); });   // dP - D = dO V^T - D
       __builtin_amdgcn_s_setprio(0);
       lds_dma_wait();                            // this wavefront's copies into LDS have landed
       DFA_BARRIER_NO_DRAIN();                    // nothing else it wrote has to be seen by the others
       slot = next;
     }
     dS_prev(niter);
-    col_products<true>(acc, Gather16(smem + OFF_Q + (slot == 0 ? 2 : slot - 1) * QTILE_BYTES, g_base), w, y);
+    const Gather16 cols(q_tile(niter - 1), g_base);
+    col_products<0>(acc, z, w, [&](int i) DFA_INLINE { return col_operand(cols, i & 15); });
     __syncthreads();
   }
 
@@ -512,7 +511,6 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
   // Tile copies: with 4 wavefronts each moves its quarter of the K tile and of the V tile; with 8,
   // wavefronts 0-3 move the K tile and 4-7 the V tile.
   const int cw = wave & 3;
-  const TileLane16 tl = tile16_lane(cw, lane, kv_rowbytes);
 
   // Q^T and dO^T operands of the lane's two rows; lse' and -D of them (-D in every element: the accumulator the dP^T
   // products start from, which saves the subtraction per score)
@@ -552,111 +550,150 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
   const int it0 = PARTS ? all * share / p.q_parts : 0, ntiles = PARTS ? all * (share + 1) / p.q_parts : all;
 
   // K/V tiles go from global memory straight into LDS; key rows past s_k are clamped to the last
-  // row and masked below.  Tile t + 1 is on its way while tile t is computed on.
-  const char* first = smem + (PARTS ? (it0 & 1) * 2 * TILE_BYTES : 0);
-  if (NW == 4 || wave < 4) tile16_copy(tile16_copy_plan(kg, kv_rowbytes, it0 * BN, p.s_k - 1, tl, first, cw, lane));
-  if (NW == 4 || wave >= 4) tile16_copy(tile16_copy_plan(vg, kv_rowbytes, it0 * BN, p.s_k - 1, tl, first + TILE_BYTES, cw, lane));
+  // row and masked below.  With one workgroup per CU three tiles are there: the one that is computed on, the next, whose
+  // first operands are read ahead, and the one after it on its way; one barrier per tile, in the middle of its work.  With two
+  // workgroups per CU there is room for two, and the barrier stands at the end of a tile.
+  constexpr bool WIDE = NW == 8;
+  constexpr int SLOTS = WIDE ? 3 : 2;
+  const int end = max(ntiles - 1, it0);            // (a share may have no tile)
+  auto at = [&](int slot, bool v) DFA_INLINE { return smem + (2 * slot + v) * TILE_BYTES; };
+  auto plan = [&](int it, int slot, bool v) DFA_INLINE {
+    return TileRows16(v ? vg : kg, kv_rowbytes, min(it, end) * BN, p.s_k - 1, at(slot, v), cw, lane);
+  };
+  const bool v_wave = WIDE && wave >= 4;           // with 8 wavefronts: this wavefront's tile
+#pragma unroll
+  for (int i = 0; i < SLOTS - 1; ++i) {
+    plan(it0 + i, i, v_wave).all();
+    if (!WIDE) plan(it0 + i, i, true).all();
+  }
   lds_dma_wait();
   __syncthreads();
 
   // Tiles that have keys which the wavefront's rows see, counted once: compared with the offset in every tile, the form with two
   // parts spilled 6 registers (8 heads x 1000 x 1900 47.2 us, 39.7 so).
-  const int seen = p.causal ? (q0w + 31 + off - (NS == 2 ? part * 32 : 0) + BN) / BN : ntiles;
-  for (int it = it0; it < ntiles; ++it) {
+  const int seen = p.causal ? min(ntiles, (q0w + 31 + off - (NS == 2 ? part * 32 : 0) + BN) / BN) : ntiles;
+  // The stream of A operands, 24 per 32 keys: K and V rows in turn (S^T = K Q^T, dP^T = V dO^T: step t = 2 s + mb takes
+  // two) and 8 gathers of K (dQ^T += K^T dS^T), each read LEAD operands before it is used.
+  constexpr int RING = WIDE ? 12 : 8, LEAD = RING - 2;
+  u32x4 z[RING];
+  auto operand = [&](const Rows16& kr, const Rows16& vr, const Gather16& kc, int nk, int e) DFA_INLINE {
+    const bf16x8 x = e >= 16 ? kc.read(2 * nk, e - 16) : (e & 1 ? vr : kr).read(2 * nk + ((e >> 1) & 1), e >> 2);
+    return __builtin_bit_cast(u32x4, x);
+  };
+  int slot = 0, it = it0;
+  auto read_first = [&](int slot) DFA_INLINE {
+    const Rows16 kr(at(slot, false), a_base), vr(at(slot, true), a_base);
+    const Gather16 kc(at(slot, false), g_base);
+#pragma unroll
+    for (int e = 0; e < LEAD; ++e) z[e] = operand(kr, vr, kc, NS == 2 ? part : 0, e);
+  };
+  if (WIDE) read_first(0);
+  for (; it < seen; ++it) {
     const int k0 = it * BN;
-    const char* Ks = smem + (it & 1) * 2 * TILE_BYTES;
-    const char* Vs = Ks + TILE_BYTES;
-    // The next K and V tiles into the other buffer, their pieces spread between the MFMAs below
-    // (issued in a burst they stall the wavefront while the memory pipe takes them in).  After the
-    // last tile the same tile goes once more into the idle buffer, which keeps the loop free of
-    // branches around the copies.
-    const int kn0 = it + 1 < ntiles ? k0 + BN : k0;
-    const char* Kn = smem + ((it + 1) & 1) * 2 * TILE_BYTES;
-    // ck: the pieces issued under the first 32 keys, cv: those under the second 32 (NW == 4: K and V;
-    // NW == 8: this wavefront's one tile under the first, nothing under the second)
-    const bool v_wave = NW == 8 && wave >= 4;
-    const TileCopy16 ck = tile16_copy_plan(v_wave ? vg : kg, kv_rowbytes, kn0, p.s_k - 1, tl,
-                                           v_wave ? Kn + TILE_BYTES : Kn, cw, lane);
-    const TileCopy16 cv = tile16_copy_plan(vg, kv_rowbytes, kn0, p.s_k - 1, tl, Kn + TILE_BYTES, cw, lane);
-
-    const bool active = it < seen;
-    if (!active) {      // nothing to compute for this wavefront's rows: only its share of the copies
-      tile16_copy(ck);
-      if (NW == 4) tile16_copy(cv);
-    }
-    if (active) {
-      const bool need_mask = (k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w + off);
+    const int next = slot + 1 == SLOTS ? 0 : slot + 1, free = next + 1 == SLOTS ? 0 : next + 1;
+    const Rows16 kr(at(slot, false), a_base), vr(at(slot, true), a_base);
+    const Gather16 kc(at(slot, false), g_base);
+    // The pieces of a tile on its way are spread between the MFMAs (issued in a burst they stall the wavefront while the
+    // memory pipe takes them in).  After the last tile the same tile goes once more into a slot that is not read
+    // again, which keeps the loop free of branches around the copies.
+    const TileRows16 ck = WIDE ? plan(it + 2, free, v_wave) : plan(it + 1, next, false);
+    const TileRows16 cv = plan(it + 1, next, true);      // (two workgroups per CU)
+    if (!WIDE) read_first(slot);
+    const bool need_mask = (k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w + off);
 #pragma unroll
-      for (int n = 0; n < 2 / NS; ++n) {
-        const int nk = NS == 2 ? part : n;       // 32-key block of the tile
-        // S^T = K Q^T, dP^T = V dO^T for 32 keys; row reads run 4 steps ahead
-        const Rows16 kr(Ks, a_base), vr(Vs, a_base);      // step t = 2 s + mb
-        const int b0 = 2 * nk;                   // first 16-key block
-        bf16x8 ka[4], va[4];
-        f32x4 s[2][2], dp[2][2];                 // [key block][row block]
+    for (int n = 0; n < 2 / NS; ++n) {
+      const int nk = NS == 2 ? part : n;         // 32-key block of the tile
+      const bool last_half = n == 2 / NS - 1;
+      auto read_ahead = [&](int e) DFA_INLINE {
+        if (e < 24) z[e % RING] = operand(kr, vr, kc, nk, e);
+        else if (!last_half) z[e % RING] = operand(kr, vr, kc, nk + 1, e - 24);
+        else if (WIDE) {
+          const Rows16 kn(at(next, false), a_base), vn(at(next, true), a_base);
+          z[e % RING] = operand(kn, vn, kc, NS == 2 ? part : 0, e - 24);
+        }
+      };
+      f32x4 s[2][2], dp[2][2];                   // [key block][row block]
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          ka[t] = kr.read(b0 + (t & 1), t >> 1);
-          va[t] = vr.read(b0 + (t & 1), t >> 1);
+      for (int t = 0; t < 8; ++t) {
+        if (WIDE && last_half && t == 6) {       // the next tile is there, nobody reads the one before any more
+          lds_dma_wait();
+          DFA_BARRIER_NO_DRAIN();
+        }
+        const int mb = t & 1;
+        read_ahead(2 * t + LEAD);
+        read_ahead(2 * t + 1 + LEAD);
+        const bf16x8 ka = __builtin_bit_cast(bf16x8, z[2 * t % RING]), va = __builtin_bit_cast(bf16x8, z[(2 * t + 1) % RING]);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) s[mb][nb] = mfma16(ka, qB[t >> 1][nb], t < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[mb][nb]);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) dp[mb][nb] = mfma16(va, gB[t >> 1][nb], t < 2 ? negD[nb] : dp[mb][nb]);      // from -D
+        if (!WIDE) {                             // one piece of the next tiles every other step
+          const TileRows16& c = n == 0 ? ck : cv;
+          if (t == 0) c.piece<0>();
+          if (t == 2) c.piece<1>();
+          if (t == 4) c.piece<2>();
+          if (t == 6) c.piece<3>();
         }
         DFA_SCHED_FENCE();
+      }
+      // dS^T = P^T o (dP^T - D): lse' is a per-lane scalar here, -D came in through the accumulator
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int mb = t & 1;
+      for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-          for (int nb = 0; nb < 2; ++nb) s[mb][nb] = mfma16(ka[t & 3], qB[t >> 1][nb], t < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[mb][nb]);
+        for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-          for (int nb = 0; nb < 2; ++nb) dp[mb][nb] = mfma16(va[t & 3], gB[t >> 1][nb], t < 2 ? negD[nb] : dp[mb][nb]);      // from -D
-          if (NW == 4 || n == 0) {   // one piece of the next tiles every other step
-            const TileCopy16& c = n == 0 ? ck : cv;
-            if (t == 0) tile16_copy_piece<0>(c);
-            if (t == 2) tile16_copy_piece<1>(c);
-            if (t == 4) tile16_copy_piece<2>(c);
-            if (t == 6) tile16_copy_piece<3>(c);
-          }
-          if (t < 4) {
-            ka[t & 3] = kr.read(b0 + (t & 1), (t + 4) >> 1);
-            va[t & 3] = vr.read(b0 + (t & 1), (t + 4) >> 1);
-          }
-          DFA_SCHED_FENCE();
-        }
-        // dS^T = P^T o (dP^T - D): lse' is a per-lane scalar here, -D came in through the accumulator
+          for (int i = 0; i < 4; ++i) dp[mb][nb][i] *= __builtin_amdgcn_exp2f(fmaf(s[mb][nb][i], c2, -Lr[nb]));
+      if (need_mask) {
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-          for (int nb = 0; nb < 2; ++nb)
+          for (int i = 0; i < 4; ++i) {
+            const int kvi = k0 + nk * 32 + mb * 16 + g * 4 + i;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) dp[mb][nb][i] *= __builtin_amdgcn_exp2f(fmaf(s[mb][nb][i], c2, -Lr[nb]));
-        if (need_mask) {
+            for (int nb = 0; nb < 2; ++nb)
+              if (kvi >= p.s_k || (p.causal && kvi > qrow + 16 * nb + off)) dp[mb][nb][i] = 0.f;
+          }
+      }
+      // dQ^T += K^T dS^T over the 32 keys, 8 blocks of 16 columns
+      const bf16x8 sb[2] = {pack16(dp[0][0], dp[1][0]), pack16(dp[0][1], dp[1][1])};
+      DFA_SCHED_FENCE();
 #pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int kvi = k0 + nk * 32 + mb * 16 + g * 4 + i;
-#pragma unroll
-              for (int nb = 0; nb < 2; ++nb)
-                if (kvi >= p.s_k || (p.causal && kvi > qrow + 16 * nb + off)) dp[mb][nb][i] = 0.f;
-            }
+      for (int db = 0; db < 8; ++db) {
+        read_ahead(16 + db + LEAD);
+        const bf16x8 gk = __builtin_bit_cast(bf16x8, z[(16 + db) % RING]);
+        dqT[db][0] = mfma16(gk, sb[0], dqT[db][0]);
+        dqT[db][1] = mfma16(gk, sb[1], dqT[db][1]);
+        if (WIDE && last_half) {
+          if (db == 0) ck.piece<0>();
+          if (db == 2) ck.piece<1>();
+          if (db == 4) ck.piece<2>();
+          if (db == 6) ck.piece<3>();
         }
-        // dQ^T += K^T dS^T over the 32 keys, 8 blocks of 16 columns
-        const bf16x8 sb[2] = {pack16(dp[0][0], dp[1][0]), pack16(dp[0][1], dp[1][1])};
-        const Gather16 kc(Ks, g_base);
-        bf16x8 gk[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) gk[i] = kc.read(b0, i);
         DFA_SCHED_FENCE();
-#pragma unroll
-        for (int db = 0; db < 8; ++db) {
-          dqT[db][0] = mfma16(gk[db & 1], sb[0], dqT[db][0]);
-          dqT[db][1] = mfma16(gk[db & 1], sb[1], dqT[db][1]);
-          if (db + 2 < 8) gk[db & 1] = kc.read(b0, db + 2);
-          DFA_SCHED_FENCE();
-        }
       }
     }
-    lds_dma_wait();
-    __syncthreads();
+    slot = next;
+    if (!WIDE) {
+      lds_dma_wait();
+      __syncthreads();
+    }
   }
+  for (; it < ntiles; ++it) {                      // nothing to compute for this wavefront's rows: only its share of the copies
+    const int next = slot + 1 == SLOTS ? 0 : slot + 1, free = next + 1 == SLOTS ? 0 : next + 1;
+    if (WIDE) {
+      lds_dma_wait();
+      DFA_BARRIER_NO_DRAIN();
+      plan(it + 2, free, v_wave).all();
+    } else {
+      plan(it + 1, next, false).all();
+      plan(it + 1, next, true).all();
+      lds_dma_wait();
+      __syncthreads();
+    }
+    slot = next;
+  }
+  if (WIDE) lds_dma_wait();                        // nothing is left on its way into LDS
+  if (NS == 2) __syncthreads();
 
   if constexpr (NS == 2) {      // the second part's sums through LDS (the tiles are no longer needed)
     f32x4* x = reinterpret_cast<f32x4*>(smem) + rb * 1024 + lane;
@@ -998,7 +1035,7 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
     const bool wide = (!sh.causal || sh.s_k / 2 >= sh.s_q) && blocks_of(sh.s_q, 256) * sh.h_q * n >= 1024;
     if (!make_items(p.q_items, sh.s_q, wide ? 256 : 128, sh.h_q, n, sh.causal)) return static_cast<int>(DFA_ERR_SHAPE);
     const int64_t blocks = xcd_blocks(p.q_items.map);
-    return wide ? launch<NP, k_bwd_dq_bf16<8, NP>>(p, blocks, 512, 4 * qs::TILE_BYTES, st)
+    return wide ? launch<NP, k_bwd_dq_bf16<8, NP>>(p, blocks, 512, 6 * qs::TILE_BYTES, st)
                 : launch<NP, k_bwd_dq_bf16<4, NP>>(p, blocks, 256, 4 * qs::TILE_BYTES, st);
   });
 }
