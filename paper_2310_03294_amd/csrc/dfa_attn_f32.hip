@@ -1,18 +1,26 @@
-// fp32 mode of the chunk kernels: fp32 operands, products and sums throughout, any s_q / s_k.
+// fp32 mode of the chunk kernels: fp32 operands, results and sums, products of all 24 bits, any s_q / s_k.
 // This is the precision-reference mode of the library (1e-5 agreement with fp64); the bf16 kernels
 // are the fast path.
 //
-// All products run on v_mfma_f32_32x32x2_f32 (64 cycles each, 256 FLOP per clock and CU: with the
-// packed vector forms unused it is twice the vector rate, and it needs a 64th of the operand reads of
-// a 4x4 micro-tile).  Its layout, lane l, r = l % 32, h = l / 32:
-//   A operand: A[r][h]    B operand: B[h][r]    C/D (16 fp32): C[(i/4)*8 + 4h + i%4][r]
-// Two consequences shape every kernel here:
-//  * the contraction index only has to match between A and B, so a product over d takes d = 8t + 4h + e
-//    in step 4t + e: one 16-byte read of a row serves four steps, and a C tile is fed back as B
-//    operands register by register (register i holds contraction rows (i/4)*8 + 4h + i%4);
-//  * the rows of C may be any rows: column block j of a d-wide result holds d = NB m + j
-//    (NB = d / 32), so the A operands of all NB blocks come from ONE read of NB consecutive floats
-//    and the results leave in runs of NB floats.
+// Products of the backward.  An fp32 value is the exact sum of three bf16 ones: its upper 16 bits, the rounded rest, what that leaves.  Of the nine
+// products of two such sums the six largest (the others are below 2^-23 of the product, of either sign) run on
+// v_mfma_f32_32x32x16_bf16, the largest as one chain and the five small ones as another, added at the end.  That is 192 cycles per
+// 32x32x16 against 512 of v_mfma_f32_32x32x2_f32, and closer to the exact sum: relative error of a product over 128 / 1024
+// N(0,1) values 6.5e-8 / 1.9e-7 against 2.0e-7 / 5.7e-7 (a chain is rounded once per 16 terms instead of every two).
+// Infinities and NaN: the largest product has them as the fp32 one would, the chain of the small ones is bounded before it is
+// added.  us, fp32 products / these: 32 heads x 4096 8785 / 5779, 32 over 8 x 2048 2200 / 1467, 8 over 2 x 1024 diagonal 141 / 109,
+// one head x 256 diagonal at d = 64 19.4 / 16.5; the gradients are half as far from the exact ones.
+// fp32 products (v_mfma_f32_32x32x2_f32) are left in the backward with 128-row tiles at d = 128, for which three values per
+// element do not fit the LDS, and in the forward: there the split tiles leave room for one workgroup per CU, whose exponentials
+// nobody's products cover (walks of 8 over 2 heads x 4096 359 us, 440 split).
+//
+// Layout of either, lane l, r = l % 32, h = l / 32: C/D (16 fp32): C[(i/4)*8 + 4h + i%4][r].  The contraction index only has to
+// match between A and B, so a C tile is fed back as B operand: its registers 8u .. 8u+7 hold rows 16u + (e/4)*8 + 4h + e%4, and
+// the A operand (of the bf16 product) is gathered in that order by the transposing LDS read.
+// fp32 product: A operand A[r][h], B operand B[h][r];
+//  * a product over d takes d = 8t + 4h + e in step 4t + e: one 16-byte read of a row serves four steps;
+//  * column block j of a d-wide result holds d = NB m + j (NB = d / 32), so the A operands of all NB blocks come from
+//    ONE read of NB consecutive floats.
 // A wavefront owns 32 rows of the stationary operand and walks over 32-row blocks of the other,
 // which four wavefronts share through LDS (rows padded by 4 floats: both kinds of reads are free of
 // bank conflicts).  The four wavefronts of a workgroup are NR row blocks x NS = 4 / NR parts of every
@@ -22,6 +30,7 @@
 #include <mutex>
 
 #include "dfa_internal.h"
+#include "dfa_mfma.h"
 #include "dfa_span.h"
 
 namespace dfa {
@@ -29,8 +38,8 @@ namespace {
 
 constexpr int NT = 256;        // threads per workgroup: 4 wavefronts
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Products of split values (see above); else fp32 products.
+template <int D, int NS> constexpr bool kSplit = !(D == 128 && NS == 4);
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
@@ -127,6 +136,8 @@ __device__ __forceinline__ void load_rows(f32x4 (&b)[D / 8], const float* src, i
   }
 }
 
+template <int D, int ROWS> struct Planes;
+
 // A pair of ROWS x D tiles on their way from global memory to LDS.  load() issues the reads of a tile
 // while the tile before it is computed on; store() writes what has arrived.  Rows past the end are zero.
 template <int D, int ROWS>
@@ -142,6 +153,16 @@ struct TilePair {
       b[n] = *reinterpret_cast<const f32x4*>(B + off);
     }
   }
+  __device__ __forceinline__ void store_split(char* As, char* Bs, int row0, int nrows) const {
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const int i = threadIdx.x + n * NT, r = i / C4, c = (i % C4) * 4;
+      const bool ok = row0 + r < nrows;
+      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+      Planes<D, ROWS>::put(As, r, c, ok ? a[n] : z);
+      Planes<D, ROWS>::put(Bs, r, c, ok ? b[n] : z);
+    }
+  }
   __device__ __forceinline__ void store(float* As, float* Bs, int row0, int nrows) const {
 #pragma unroll
     for (int n = 0; n < N; ++n) {
@@ -153,6 +174,147 @@ struct TilePair {
     }
   }
 };
+
+// ---- split values ----
+struct Split8 { bf16x8 h, m, l; };
+// Two values: upper halves, rounded rests, what is left.
+__device__ __forceinline__ void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+  const uint32_t ua = __builtin_bit_cast(uint32_t, a), ub = __builtin_bit_cast(uint32_t, b);
+  h = __builtin_amdgcn_perm(ub, ua, 0x07060302);
+  const float ra = a - __builtin_bit_cast(float, ua & 0xffff0000u), rb = b - __builtin_bit_cast(float, ub & 0xffff0000u);
+  bf16x2 t;
+  t[0] = static_cast<__bf16>(ra); t[1] = static_cast<__bf16>(rb);
+  m = __builtin_bit_cast(uint32_t, t);
+  t[0] = static_cast<__bf16>(ra - __builtin_bit_cast(float, m << 16));
+  t[1] = static_cast<__bf16>(rb - __builtin_bit_cast(float, m & 0xffff0000u));
+  l = __builtin_bit_cast(uint32_t, t);
+}
+template <class F>
+__device__ __forceinline__ Split8 split8(F value) {      // value(e), e = 0 .. 7
+  u32x4 h, m, l;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint32_t x, y, z;
+    split2(value(2 * e), value(2 * e + 1), x, y, z);
+    h[e] = x; m[e] = y; l[e] = z;
+  }
+  return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+// main += the largest product, rest += the five small ones, the smallest first
+__device__ __forceinline__ void mfma_split(const Split8& a, const Split8& b, f32x16& main, f32x16& rest) {
+  rest = mfma32(a.l, b.h, rest);
+  rest = mfma32(a.h, b.l, rest);
+  rest = mfma32(a.m, b.m, rest);
+  rest = mfma32(a.m, b.h, rest);
+  rest = mfma32(a.h, b.m, rest);
+  main = mfma32(a.h, b.h, main);
+}
+__device__ __forceinline__ float bounded(float x) { return __builtin_amdgcn_fmed3f(x, -3.402823466e38f, 3.402823466e38f); }
+
+// A ROWS x D tile in LDS as three bf16 tiles of 272-byte rows (at d = 64 the first two share theirs).
+template <int D, int ROWS> struct Planes {
+  static constexpr int BYTES = (D == 128 ? 3 : 2) * ROWS * kRowBytes;
+  static constexpr int at(int plane) { return D == 128 ? plane * ROWS * kRowBytes : plane == 2 ? ROWS * kRowBytes : plane * 128; }
+  __device__ static __forceinline__ Split8 rows(const char* t, int off) {      // off: tile_off(row, h) + 32 ks
+    return {lds_read_b128(t, off + at(0)), lds_read_b128(t, off + at(1)), lds_read_b128(t, off + at(2))};
+  }
+  __device__ static __forceinline__ Split8 cols(const char* t, int off) {      // off: gather_base + row0 * kRowBytes + 64 db
+    return {lds_gather(t, off + at(0)), lds_gather(t, off + at(1)), lds_gather(t, off + at(2))};
+  }
+  // four consecutive values of a row, from column c
+  __device__ static __forceinline__ void put(char* t, int r, int c, f32x4 x) {
+    uint32_t h[2], m[2], l[2];
+    split2(x[0], x[1], h[0], m[0], l[0]);
+    split2(x[2], x[3], h[1], m[1], l[1]);
+    char* p = t + prow(r) * kRowBytes + 2 * c;
+    *reinterpret_cast<u32x2*>(p + at(0)) = u32x2{h[0], h[1]};
+    *reinterpret_cast<u32x2*>(p + at(1)) = u32x2{m[0], m[1]};
+    *reinterpret_cast<u32x2*>(p + at(2)) = u32x2{l[0], l[1]};
+  }
+};
+
+// One 32-row block as a split B operand over d, straight from global memory: lane holds row `row`, d = 16 ks + 8h .. +7.
+template <int D>
+__device__ __forceinline__ void load_rows(Split8 (&b)[D / 16], const float* src, int64_t ss, int row, bool ok, int hh) {
+  const float* p = src + static_cast<int64_t>(ok ? row : 0) * ss + 8 * hh;
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks) {
+    f32x4 x = *reinterpret_cast<const f32x4*>(p + 16 * ks), y = *reinterpret_cast<const f32x4*>(p + 16 * ks + 4);
+    if (!ok) x = y = f32x4{0.f, 0.f, 0.f, 0.f};
+    b[ks] = split8([&](int e) { return e < 4 ? x[e] : y[e - 4]; });
+  }
+}
+
+// The columns of 32 rows' W as a B operand: w[u] of rows 16u + (e/4)*8 + 4h + e%4.
+__device__ __forceinline__ void split_tile(Split8 (&b)[2], const f32x16& w) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u) b[u] = split8([&](int e) { return w[8 * u + e]; });
+}
+__device__ __forceinline__ f32x16 zero16() {
+  f32x16 z;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) z[i] = 0.f;
+  return z;
+}
+
+// A operands in the order of their use, each read from LDS AHEAD steps (of six products, 192 cycles) before it is used: with one
+// wavefront per SIMD nobody else's work covers a read that is waited for.
+template <int N, int AHEAD, class Read, class Use>
+__device__ __forceinline__ void stream(Read read, Use use) {
+  Split8 z[AHEAD + 1];
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) z[i] = read(i);
+  DFA_SCHED_FENCE();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i + AHEAD < N) z[(i + AHEAD) % (AHEAD + 1)] = read(i + AHEAD);
+    use(i, z[i % (AHEAD + 1)]);
+    DFA_SCHED_FENCE();
+  }
+}
+
+// acc^T += X^T W, one 32-column block after the other, two steps of 16 rows each: the sums of a block's 32 rows (SUM: the largest
+// products' too) are added while the next block's products run.
+template <int D, bool SUM> struct ColSums {
+  f32x16 main[2], rest[2];
+  __device__ __forceinline__ void add(f32x16 (&acc)[D / 32], int db) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float x = main[db & 1][i] + bounded(rest[db & 1][i]);
+      acc[db][i] = SUM ? acc[db][i] + x : x;
+    }
+  }
+  // step c = 2 db + u
+  __device__ __forceinline__ void step(f32x16 (&acc)[D / 32], int c, const Split8& x, const Split8 (&w)[2]) {
+    const int db = c >> 1, u = c & 1;
+    if (u == 0) {
+      rest[db & 1] = zero16();
+      if constexpr (SUM) main[db & 1] = zero16();
+      else main[db & 1] = acc[db];
+    }
+    mfma_split(x, w[u], main[db & 1], rest[db & 1]);
+    if (u == 0 && db > 0) add(acc, db - 1);
+    if (c == D / 16 - 1) add(acc, db);
+  }
+};
+
+// ---- runs: a d-wide result leaves in D / 8 runs of four consecutive floats per lane ----
+template <int D, bool SPLIT>
+__device__ __forceinline__ f32x4 run_of(const f32x16 (&c)[D / 32], int k) {
+  if constexpr (SPLIT) return f32x4{c[k >> 2][4 * (k & 3)], c[k >> 2][4 * (k & 3) + 1], c[k >> 2][4 * (k & 3) + 2], c[k >> 2][4 * (k & 3) + 3]};
+  else return f32x4{c[0][k], c[1][k], c[2][k], c[3][k]};
+}
+template <int D, bool SPLIT>
+__device__ __forceinline__ void set_run(f32x16 (&c)[D / 32], int k, f32x4 x) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (SPLIT) c[k >> 2][4 * (k & 3) + e] = x[e];
+    else c[e][k] = x[e];
+  }
+}
+template <bool SPLIT> __device__ __forceinline__ int run_col(int k, int hh) {
+  return SPLIT ? (k >> 2) * 32 + (k & 3) * 8 + 4 * hh : 4 * ((k >> 2) * 8 + 4 * hh + (k & 3));
+}
 
 // C += X Y^T over d: X is a 32-row block in LDS (row r of it for lane r), Y a register operand.
 template <int D>
@@ -196,26 +358,6 @@ __device__ __forceinline__ void col_product(f32x16 (&acc)[D / 32], const float* 
   }
 }
 
-// The same with the 32 rows' products as a sum of their own, added to acc; two column blocks at a time, which keeps it to 32 registers.
-template <int D>
-__device__ __forceinline__ void col_sum(f32x16 (&acc)[D / 32], const float* Xs, const f32x16& w, int r32, int hh) {
-  constexpr int NB = D / 32;
-#pragma unroll
-  for (int j = 0; j < NB; j += 2) {
-    f32x16 t[2];
-    zero(t);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const f32x2 a = *reinterpret_cast<const f32x2*>(Xs + ((i >> 2) * 8 + 4 * hh + (i & 3)) * (D + 4) + NB * r32 + j);
-      t[0] = mfma_f32(a.x, w[i], t[0]);
-      t[1] = mfma_f32(a.y, w[i], t[1]);
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) { acc[j][i] += t[0][i]; acc[j + 1][i] += t[1][i]; }
-    __builtin_amdgcn_sched_barrier(0);      // (else the reads of what follows are hoisted above it and registers spill: 5 % at d = 128)
-  }
-}
-
 // Sum of a result over the NS parts of a row block, left in part 0: `x` is LDS space for
 // 4 * NV * 64 floats (NV registers of the result per lane).
 template <int NB>
@@ -234,18 +376,14 @@ __device__ __forceinline__ void add_result(const float* x, f32x16 (&c)[NB], int 
 }
 
 // Row `dst` (+)= f * result
-template <int D>
+template <int D, bool SPLIT>
 __device__ __forceinline__ void write_grad(float* dst, const f32x16 (&c)[D / 32], float f, int accumulate, int hh) {
-  constexpr int NB = D / 32;
-  typedef typename Run<NB>::type run_t;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    float* p = dst + NB * ((i >> 2) * 8 + 4 * hh + (i & 3));
-    run_t x;
-#pragma unroll
-    for (int j = 0; j < NB; ++j) x[j] = c[j][i] * f;
-    if (accumulate) x += *reinterpret_cast<const run_t*>(p);
-    *reinterpret_cast<run_t*>(p) = x;
+  for (int k = 0; k < D / 8; ++k) {
+    f32x4* p = reinterpret_cast<f32x4*>(dst + run_col<SPLIT>(k, hh));
+    f32x4 x = run_of<D, SPLIT>(c, k) * f;
+    if (accumulate) x += *p;
+    *p = x;
   }
 }
 
@@ -254,7 +392,13 @@ __device__ __forceinline__ void write_grad(float* dst, const f32x16 (&c)[D / 32]
 template <int NS> constexpr int kTile = NS == 4 ? 128 : 64;
 
 template <int D, int ROWS>
-constexpr size_t smem_bytes() { return sizeof(float) * (2 * ROWS * (D + 4) + 2 * ROWS); }
+constexpr size_t fwd_smem() { return sizeof(float) * 2 * ROWS * (D + 4); }
+// The backward: two tiles of 32 NS rows and two floats per row.
+template <int D, int NS>
+constexpr size_t smem_bytes() {
+  constexpr int ROWS = 32 * NS;
+  return (kSplit<D, NS> ? 2 * Planes<D, ROWS>::BYTES : sizeof(float) * 2 * ROWS * (D + 4)) + sizeof(float) * 2 * ROWS;
+}
 
 // Forward.  Online softmax as in the pseudo-code of Appendix A (running row maximum m and row sum l,
 // old terms multiplied by exp(m_old - m_new)); a lane holds the scores of ONE query.
@@ -393,24 +537,27 @@ __global__ void __launch_bounds__(NT, NS == 4 ? 1 : 2) k_fwd_f32(Args a) {
 
 // dk, dv of one workgroup's key rows: K and V rows in registers, Q / dO tiles (with lse and D) in LDS,
 // summed over the query heads of the group.
-// V_LDS: at d = 128 with 128-row tiles K, V, dK, dV and the tile on its way are more registers than
-// there are; V (the same 32 rows for all four wavefronts) then stays in LDS.
-template <int D, int NS> constexpr bool kVLds = D == 128 && NS == 4;
+// V_LDS: at d = 128 K, V (of three values each), dK, dV and the tile on its way are more registers than
+// there are; V then stays in LDS (with split values, of all of the workgroup's rows).
+template <int D, int NS> constexpr bool kVLds = D == 128;
+template <int D, int NS> constexpr size_t v_bytes() {
+  return !kVLds<D, NS> ? 0 : kSplit<D, NS> ? Planes<D, 128 / NS>::BYTES : sizeof(float) * 32 * (D + 4);
+}
 // SHARED: p.shares workgroups share the query tiles of a row block.
 // SUMS (a sequence that stands for the pairs of several chunks): dk, dv as sums of 32 query rows each, added up.  The rounding
-// errors of one chain over all rows grow with its length.  Relative error of dk, dv in a schedule of 4 heads x 8000, d = 128: one chain
-// 1.6e-6, sums 5.8e-7 and 5.1e-7 (pair by pair, 1000 rows each in one chain, 7.0e-7 and 6.6e-7).  They take 7 to 8 % of a
-// backward at d = 128 (full pair of 32 heads x 4096 8766 / 9421 us) and 1 to 2 % at d = 64, so a pair, whose chain is no longer
-// than it ever was, goes without.
+// errors of one chain over all rows grow with its length.  Relative error of dk, dv in a schedule of 4 heads x 8000, d = 128, with
+// fp32 products: one chain 1.6e-6, sums 5.8e-7 and 5.1e-7 (pair by pair, 1000 rows each in one chain, 7.0e-7 and 6.6e-7).  They
+// took 7 to 8 % of a backward at d = 128 and 1 to 2 % at d = 64, so a pair, whose chain is no longer than it ever was, goes without.
 template <int D, int NS, bool SHARED, bool SUMS>
 __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int item, float* partial, float* smem) {
   constexpr int NR = 4 / NS, NB = D / 32, LD = D + 4, BQ = 32 * NS;
-  constexpr bool V_LDS = kVLds<D, NS>;
+  constexpr bool V_LDS = kVLds<D, NS>, SPLIT = kSplit<D, NS>;
+  char* Qp = reinterpret_cast<char*>(smem);
+  char* Gp = Qp + (SPLIT ? Planes<D, BQ>::BYTES : 0);
   float* Qs = smem;
   float* Gs = Qs + BQ * LD;
-  float* Ls = Gs + BQ * LD;
-  float* Ds = Ls + BQ;
-  float* Vs = Ds + BQ;
+  float* Ls = SPLIT ? reinterpret_cast<float*>(Gp + Planes<D, BQ>::BYTES) : Gs + BQ * LD;
+  float* Vs = Ls + 2 * BQ;                   // after lse and D
   const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rb = wave % NR, part = wave / NR;
   const int share = SHARED ? item / p.nx_kv % p.shares : 0, kh = SHARED ? item / p.nx_kv / p.shares : item / p.nx_kv;
@@ -440,14 +587,18 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
     if (left > 0) { hq += it0 / ntq; q0 += it0 % ntq * BQ; }       // (else a tile is loaded, and not used)
   }
   load(hq, q0);
-  f32x4 k[D / 8], v[V_LDS ? 1 : D / 8];
+  const int a_base = tile_off(r32, hh), g_base = gather_base(lane);
+  std::conditional_t<SPLIT, Split8[D / 16], f32x4[D / 8]> k;
+  std::conditional_t<SPLIT, Split8[V_LDS ? 1 : D / 16], f32x4[V_LDS ? 1 : D / 8]> v;
+  char* Vp = reinterpret_cast<char*>(Vs);
   load_rows<D>(k, pr.k + kh * p.kv_sh, p.kv_ss, kvrow, kvalid, hh);
   if constexpr (V_LDS) {
-    for (int i = tid; i < 32 * (D / 4); i += NT) {
+    for (int i = tid; i < NR * 32 * (D / 4); i += NT) {
       const int r = k0 + i / (D / 4), c = (i % (D / 4)) * 4;
       f32x4 x = {0.f, 0.f, 0.f, 0.f};
       if (r < p.s_k) x = *reinterpret_cast<const f32x4*>(pr.v + kh * p.kv_sh + static_cast<int64_t>(r) * p.kv_ss + c);
-      *reinterpret_cast<f32x4*>(Vs + (r - k0) * LD + c) = x;
+      if constexpr (SPLIT) Planes<D, NR * 32>::put(Vp, r - k0, c, x);
+      else *reinterpret_cast<f32x4*>(Vs + (r - k0) * LD + c) = x;
     }
   } else {
     load_rows<D>(v, pr.v + kh * p.kv_sh, p.kv_ss, kvrow, kvalid, hh);
@@ -457,8 +608,9 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
   zero(dv);
   for (bool first = true; SHARED ? left > 0 : hq < h_end; first = false) {
     if (!first) __syncthreads();
-    tile.store(Qs, Gs, q0, p.s_q);
-    if (tid < 2 * BQ) Ls[tid] = ld;          // Ds follows Ls
+    if constexpr (SPLIT) tile.store_split(Qp, Gp, q0, p.s_q);
+    else tile.store(Qs, Gs, q0, p.s_q);
+    if (tid < 2 * BQ) Ls[tid] = ld;          // lse, then D
     __syncthreads();
     const int q0t = q0 + part * 32;          // this wavefront's 32 rows of the tile
     q0 += BQ;
@@ -468,24 +620,82 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
     const float* Qw = Qs + part * 32 * LD;
     const float* Gw = Gs + part * 32 * LD;
     f32x16 s, dp;
+    auto weights = [&]() DFA_INLINE {          // s: P, dp: dS
+      // (the rows' L and D four at a time, hidden scores as -inf: a branch and a read of their own for each of the 16 took
+      // longer than the products)
+      const float* row = Ls + part * 32 + 4 * hh;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
-    row_product<D>(s, Qw, k, r32, hh);
-    if constexpr (V_LDS) row_product<D>(dp, Gw, Vs, r32, hh);
-    else row_product<D>(dp, Gw, v, r32, hh);
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 L = *reinterpret_cast<const f32x4*>(row + 8 * j);      // -inf for rows past the end and empty rows
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int r = (i >> 2) * 8 + 4 * hh + (i & 3);
-      const float L = Ls[part * 32 + r];      // -inf for rows past the end and empty rows
-      const bool vis = L > -INFINITY && !(p.causal && kvrow > q0t + r + off);
-      s[i] = vis ? expf(s[i] * p.scale - L) : 0.f;
-      dp[i] = s[i] * (dp[i] - Ds[part * 32 + r]);
-    }
-    if constexpr (SUMS) {
-      static_assert(!V_LDS, "no registers left for the sums");
-      col_sum<D>(dv, Gw, s, r32, hh);
-      col_sum<D>(dk, Qw, dp, r32, hh);
+        for (int e = 0; e < 4; ++e) s[4 * j + e] = L[e] > -INFINITY ? s[4 * j + e] * p.scale - L[e] : -INFINITY;
+      }
+      if (p.causal && k0w + 31 > q0t + off) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (kvrow > q0t + (i >> 2) * 8 + 4 * hh + (i & 3) + off) s[i] = -INFINITY;
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 D4 = *reinterpret_cast<const f32x4*>(row + BQ + 8 * j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s[4 * j + e] = expf(s[4 * j + e]);
+          dp[4 * j + e] = s[4 * j + e] * (dp[4 * j + e] - D4[e]);
+        }
+      }
+    };
+    if constexpr (SPLIT) {
+      constexpr int KS = D / 16;
+      constexpr int AHEAD = D == 128 && NS == 2 ? 1 : 2;      // (no registers left for two)
+      typedef Planes<D, BQ> Tile;
+      f32x16 sr = zero16(), dpr = zero16();
+      Split8 vz, w[2], x[2];
+      ColSums<D, SUMS> cs;
+      s = zero16(); dp = zero16();
+      const int row0 = part * 32 * kRowBytes;
+      stream<2 * KS + 4 * NB, AHEAD>([&](int i) DFA_INLINE {
+        if (i < 2 * KS) return Tile::rows(i & 1 ? Gp : Qp, a_base + row0 + (i >> 1) * 32);
+        const int c = i - 2 * KS, db = (c >> 1) % NB;
+        return Tile::cols(c < 2 * NB ? Gp : Qp, g_base + row0 + 16 * (c & 1) * kRowBytes + db * 64);
+      }, [&](int i, const Split8& a) DFA_INLINE {
+        if (i < 2 * KS) {
+          if (!(i & 1)) {
+            if constexpr (V_LDS) vz = Planes<D, NR * 32>::rows(Vp, a_base + rb * 32 * kRowBytes + (i >> 1) * 32);
+            mfma_split(a, k[i >> 1], s, sr);
+          } else if constexpr (V_LDS) {
+            mfma_split(a, vz, dp, dpr);
+          } else {
+            mfma_split(a, v[i >> 1], dp, dpr);
+          }
+          return;
+        }
+        const int c = i - 2 * KS;
+        if (c == 0) {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) { s[e] += bounded(sr[e]); dp[e] += bounded(dpr[e]); }
+          weights();
+          split_tile(w, s);
+        }
+        if (c < 2 * NB) cs.step(dv, c, a, w);
+        else cs.step(dk, c - 2 * NB, a, x);
+        if (c == 0) split_tile(x, dp);
+      });
     } else {
+      static_assert(SPLIT || !SUMS, "no registers left for the sums");
+#pragma unroll
+      for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
+      row_product<D>(s, Qw, k, r32, hh);
+      if constexpr (V_LDS) row_product<D>(dp, Gw, Vs, r32, hh);
+      else row_product<D>(dp, Gw, v, r32, hh);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = (i >> 2) * 8 + 4 * hh + (i & 3);
+        const float L = Ls[part * 32 + r];
+        const bool vis = L > -INFINITY && !(p.causal && kvrow > q0t + r + off);
+        s[i] = vis ? expf(s[i] * p.scale - L) : 0.f;
+        dp[i] = s[i] * (dp[i] - Ls[BQ + part * 32 + r]);
+      }
       col_product<D>(dv, Gw, s, r32, hh);
       col_product<D>(dk, Qw, dp, r32, hh);
     }
@@ -508,22 +718,19 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
     }
   }
   if constexpr (SHARED) {       // k_reduce_f32 adds the shares up
-    typedef typename Run<NB>::type run_t;
-    run_t* x = reinterpret_cast<run_t*>(partial) + rb * 2 * 16 * 64 + lane;
+    constexpr int RUNS = D / 8;
+    f32x4* x = reinterpret_cast<f32x4*>(partial) + rb * 2 * RUNS * 64 + lane;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      run_t a, b;
-#pragma unroll
-      for (int j = 0; j < NB; ++j) { a[j] = dk[j][i]; b[j] = dv[j][i]; }
-      x[i * 64] = a;
-      x[(16 + i) * 64] = b;
+    for (int i = 0; i < RUNS; ++i) {
+      x[i * 64] = run_of<D, SPLIT>(dk, i);
+      x[(RUNS + i) * 64] = run_of<D, SPLIT>(dv, i);
     }
     return;
   }
   if (!kvalid) return;
   const int64_t dst = kh * p.dkv_sh + static_cast<int64_t>(kvrow) * p.dkv_ss;
-  write_grad<D>(pr.dk + dst, dk, p.scale, pr.acc_kv, hh);
-  write_grad<D>(pr.dv + dst, dv, 1.f, pr.acc_kv, hh);
+  write_grad<D, SPLIT>(pr.dk + dst, dk, p.scale, pr.acc_kv, hh);
+  write_grad<D, SPLIT>(pr.dv + dst, dv, 1.f, pr.acc_kv, hh);
 }
 
 // dq of one workgroup's query rows: Q and dO rows in registers, K / V tiles in LDS.
@@ -531,6 +738,9 @@ __device__ __forceinline__ void bwd_dkdv(const F32Params& p, const Pair& pr, int
 template <int D, int NS>
 __device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int item, float* partial, float* smem) {
   constexpr int NR = 4 / NS, NB = D / 32, LD = D + 4, BK = 32 * NS;
+  constexpr bool SPLIT = kSplit<D, NS>;
+  char* Kp = reinterpret_cast<char*>(smem);
+  char* Vp = Kp + (SPLIT ? Planes<D, BK>::BYTES : 0);
   float* Ks = smem;
   float* Vs = Ks + BK * LD;
   const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
@@ -552,45 +762,85 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int i
 
   TilePair<D, BK> tile;
   tile.load(kg, vg, p.kv_ss, k_begin, p.s_k);
-  f32x4 q[D / 8], g[D / 8];
+  const int a_base = tile_off(r32, hh), g_base = gather_base(lane);
+  std::conditional_t<SPLIT, Split8[D / 16], f32x4[D / 8]> q, g;
   load_rows<D>(q, pr.q + h * p.q_sh, p.q_ss, qrow, qvalid, hh);
   load_rows<D>(g, pr.dO + h * p.q_sh, p.q_ss, qrow, qvalid, hh);
   const float L = qvalid ? pr.lse[h * p.l_sh + qrow] : -INFINITY;
   const float Dr = qvalid ? pr.delta[h * p.l_sh + qrow] : 0.f;
-  // Sums of two tiles (64 keys of a part) each, added up: the rounding errors of one chain over all keys grow with its
-  // length.  Relative error of dq from exact lse and D, one chain / this: 2 over 1 heads, 300 x 16384 1.31e-6 / 6.3e-7, 8 heads x
-  // 4096 9.9e-7 / 5.9e-7 (with sums of eight tiles 6.4e-7, of four 6.1e-7); 8 heads x 4096, all gradients 2340 / 2389 us.
-  constexpr int RUN = 2;
-  f32x16 dq[NB], run[NB];
+  // fp32 products: sums of two tiles (64 keys of a part) each, added up, since the rounding errors of one chain over all keys grow
+  // with its length.  Relative error of dq from exact lse and D, one chain / this: 2 over 1 heads, 300 x 16384 1.31e-6 / 6.3e-7, 8
+  // heads x 4096 9.9e-7 / 5.9e-7 (with sums of eight tiles 6.4e-7, of four 6.1e-7).  Split products: sums of one tile.
+  constexpr int RUN = SPLIT ? 1 : 2;
+  f32x16 dq[NB], run[SPLIT ? 1 : NB];
   zero(dq);
   for (int k0 = k_begin; k0 < k_end;) {
-    zero(run);
+    if constexpr (!SPLIT) zero(run);
     for (int n = 0; n < RUN && k0 < k_end; ++n, k0 += BK) {
       if (k0 > k_begin) __syncthreads();
-      tile.store(Ks, Vs, k0, p.s_k);
+      if constexpr (SPLIT) tile.store_split(Kp, Vp, k0, p.s_k);
+      else tile.store(Ks, Vs, k0, p.s_k);
       __syncthreads();
       if (k0 + BK < k_end) tile.load(kg, vg, p.kv_ss, k0 + BK, p.s_k);
       const int kb0 = k0 + part * 32;
       if (kb0 >= p.s_k || (p.causal && kb0 > q0w + 31 + off)) continue;
       const float* Kw = Ks + part * 32 * LD;
       f32x16 s, dp;
+      auto weights = [&]() DFA_INLINE {        // dp: dS
 #pragma unroll
-      for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
-      row_product<D>(s, Kw, q, r32, hh);
-      row_product<D>(dp, Vs + part * 32 * LD, g, r32, hh);
+        for (int i = 0; i < 16; ++i) s[i] = L > -INFINITY ? s[i] * p.scale - L : -INFINITY;
+        if (kb0 + 32 > p.s_k || (p.causal && kb0 + 31 > q0w + off)) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int kvi = kb0 + (i >> 2) * 8 + 4 * hh + (i & 3);
-        const bool vis = kvi < p.s_k && L > -INFINITY && !(p.causal && kvi > qrow + off);
-        const float pr = vis ? expf(s[i] * p.scale - L) : 0.f;
-        dp[i] = pr * (dp[i] - Dr);
+          for (int i = 0; i < 16; ++i) {
+            const int kvi = kb0 + (i >> 2) * 8 + 4 * hh + (i & 3);
+            if (kvi >= p.s_k || (p.causal && kvi > qrow + off)) s[i] = -INFINITY;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dp[i] = expf(s[i]) * (dp[i] - Dr);
+      };
+      if constexpr (SPLIT) {
+        constexpr int KS = D / 16;
+        constexpr int AHEAD = D == 128 && NS == 2 ? 1 : 2;
+        typedef Planes<D, BK> Tile;
+        f32x16 sr = zero16(), dpr = zero16();
+        Split8 w[2];
+        ColSums<D, true> cs;
+        s = zero16(); dp = zero16();
+        const int row0 = part * 32 * kRowBytes;
+        stream<2 * KS + 2 * NB, AHEAD>([&](int i) DFA_INLINE {
+          if (i < 2 * KS) return Tile::rows(i & 1 ? Vp : Kp, a_base + row0 + (i >> 1) * 32);
+          const int c = i - 2 * KS;
+          return Tile::cols(Kp, g_base + row0 + 16 * (c & 1) * kRowBytes + (c >> 1) * 64);
+        }, [&](int i, const Split8& a) DFA_INLINE {
+          if (i < 2 * KS) {
+            if (i & 1) mfma_split(a, g[i >> 1], dp, dpr);
+            else mfma_split(a, q[i >> 1], s, sr);
+            return;
+          }
+          if (i == 2 * KS) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) { s[e] += bounded(sr[e]); dp[e] += bounded(dpr[e]); }
+            weights();
+            split_tile(w, dp);
+          }
+          cs.step(dq, i - 2 * KS, a, w);
+        });
+      } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
+        row_product<D>(s, Kw, q, r32, hh);
+        row_product<D>(dp, Vs + part * 32 * LD, g, r32, hh);
+        weights();
+        col_product<D>(run, Kw, dp, r32, hh);
       }
-      col_product<D>(run, Kw, dp, r32, hh);
     }
+    if constexpr (!SPLIT) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) dq[j][i] += run[j][i];
+        for (int i = 0; i < 16; ++i) dq[j][i] += run[j][i];
+    }
   }
   if constexpr (NS > 1) {
     constexpr int NV = NB * 16;
@@ -602,19 +852,14 @@ __device__ __forceinline__ void bwd_dq(const F32Params& p, const Pair& pr, int i
     for (int s = 1; s < NS; ++s) add_result<NB>(smem + (s * NR + rb) * NV * 64, dq, lane, 1.f);
   }
   if (p.q_shares > 1) {
-    typedef typename Run<NB>::type run_t;
-    run_t* x = reinterpret_cast<run_t*>(partial) + rb * 16 * 64 + lane;
+    constexpr int RUNS = D / 8;
+    f32x4* x = reinterpret_cast<f32x4*>(partial) + rb * RUNS * 64 + lane;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      run_t a;
-#pragma unroll
-      for (int j = 0; j < NB; ++j) a[j] = dq[j][i];
-      x[i * 64] = a;
-    }
+    for (int i = 0; i < RUNS; ++i) x[i * 64] = run_of<D, SPLIT>(dq, i);
     return;
   }
   if (!qvalid) return;
-  write_grad<D>(pr.dq + h * p.dq_sh + static_cast<int64_t>(qrow) * p.dq_ss, dq, p.scale, pr.acc_q, hh);
+  write_grad<D, SPLIT>(pr.dq + h * p.dq_sh + static_cast<int64_t>(qrow) * p.dq_ss, dq, p.scale, pr.acc_q, hh);
 }
 
 // Backward: 7 products in two kinds of workgroups of ONE launch (dk/dv first, they are the longer
@@ -638,40 +883,39 @@ __global__ void __launch_bounds__(NT, 1) k_bwd_f32(F32BwdParams p) {
 }
 
 // dk, dv (KV: blockIdx.y = 2 * 32-row block + dv) or dq (blockIdx.y = 32-row block) of a block of NR * 32 rows from the sums of
-// its shares: blockIdx.x = row block, 256 threads, each four of a lane's sixteen runs.  The order of the sum is that of the shares.
+// its shares: blockIdx.x = row block, 256 threads, each a quarter of a lane's runs.  The order of the sum is that of the shares.
 template <int D, int NR, bool KV>
 __global__ void __launch_bounds__(NT) k_reduce_f32(F32BwdParams p) {
-  constexpr int NB = D / 32;
-  typedef typename Run<NB>::type run_t;
+  constexpr int RUNS = D / 8, MINE = RUNS / 4;
+  constexpr bool SPLIT = kSplit<D, 4 / NR>;
   const int nx = KV ? p.nx_kv : p.nx_q, heads = KV ? p.h_kv : p.h_q, shares = KV ? p.shares : p.q_shares;
   const int xr = blockIdx.x % nx, ph = blockIdx.x / nx;                // ph: pair * heads + head
   const Pair& pr = p.pair[ph / heads];
   const int rb = KV ? blockIdx.y >> 1 : blockIdx.y, is_dv = KV ? blockIdx.y & 1 : 0;
-  const int lane = threadIdx.x & 63, i0 = (threadIdx.x >> 6) * 4;
+  const int lane = threadIdx.x & 63, i0 = (threadIdx.x >> 6) * MINE;
   const int xrow = !KV && p.causal ? nx - 1 - xr : xr;      // (dq: the longest rows come first)
   const int row = (xrow * NR + rb) * 32 + (lane & 31);
   if (row >= (KV ? p.s_k : p.s_q)) return;
-  const int64_t block = NR * (KV ? 2 : 1) * 16 * 64, step = static_cast<int64_t>(nx) * block;      // in runs
-  const run_t* src = reinterpret_cast<const run_t*>(KV ? p.partial : p.q_partial) +
-                     (static_cast<int64_t>(ph) * shares * nx + xr) * block + (blockIdx.y * 16 + i0) * 64 + lane;
-  run_t a[4];
+  const int64_t block = NR * (KV ? 2 : 1) * RUNS * 64, step = static_cast<int64_t>(nx) * block;      // in runs
+  const f32x4* src = reinterpret_cast<const f32x4*>(KV ? p.partial : p.q_partial) +
+                     (static_cast<int64_t>(ph) * shares * nx + xr) * block + (blockIdx.y * RUNS + i0) * 64 + lane;
+  f32x4 a[MINE];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) a[i] = src[i * 64];
+  for (int i = 0; i < MINE; ++i) a[i] = src[i * 64];
 #pragma unroll 4      // (the reads of four shares on their way)
   for (int s = 1; s < shares; ++s) {
     src += step;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] += src[i * 64];
+    for (int i = 0; i < MINE; ++i) a[i] += src[i * 64];
   }
   float* out = KV ? (is_dv ? pr.dv : pr.dk) : pr.dq;
-  float* dst = out + (ph % heads) * (KV ? p.dkv_sh : p.dq_sh) + static_cast<int64_t>(row) * (KV ? p.dkv_ss : p.dq_ss) +
-               NB * (i0 * 2 + 4 * (lane >> 5));
+  float* dst = out + (ph % heads) * (KV ? p.dkv_sh : p.dq_sh) + static_cast<int64_t>(row) * (KV ? p.dkv_ss : p.dq_ss);
   const float f = is_dv ? 1.f : p.scale;
   const int add = KV ? pr.acc_kv : pr.acc_q;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    run_t* d = reinterpret_cast<run_t*>(dst + NB * i);
-    run_t x = a[i] * f;
+  for (int i = 0; i < MINE; ++i) {
+    f32x4* d = reinterpret_cast<f32x4*>(dst + run_col<SPLIT>(i0 + i, lane >> 5));
+    f32x4 x = a[i] * f;
     if (add) x += *d;
     *d = x;
   }
@@ -709,7 +953,7 @@ int fwd(Args& p, hipStream_t st) {
   const int rows = 32 * (4 / NS);
   // tiles; the combination of the parts takes 4 results and 256 floats of row statistics
   const size_t comb = NS > 1 ? sizeof(float) * (4 * (D / 32) * 16 * 64 + 256) : 0;
-  const size_t tiles = smem_bytes<D, kTile<NS>>();
+  const size_t tiles = fwd_smem<D, kTile<NS>>();
   p.nx_q = static_cast<int>(blocks_of(p.s_q, rows));
   const int64_t n_q = static_cast<int64_t>(p.nx_q) * p.h_q;
   if (n_q * p.pairs > (1 << 30)) return DFA_ERR_SHAPE;
@@ -769,7 +1013,7 @@ SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, int64_
 template <int D, int NS>
 int fwd_spans(F32FwdSpans& p, int n, hipStream_t st) {
   const int rows = 32 * (4 / NS);
-  const size_t comb = sizeof(float) * (4 * (D / 32) * 16 * 64 + 256), tiles = smem_bytes<D, kTile<NS>>();
+  const size_t comb = sizeof(float) * (4 * (D / 32) * 16 * 64 + 256), tiles = fwd_smem<D, kTile<NS>>();
   p.nx_q = static_cast<int>(blocks_of(p.s_q, rows));
   const int64_t n_q = static_cast<int64_t>(p.nx_q) * p.h_q;
   if (n_q * n > (1 << 30)) return DFA_ERR_SHAPE;
@@ -784,7 +1028,7 @@ template <int D, int NS, bool SUMS>
 int bwd(F32BwdParams p, hipStream_t st) {
   const int rows = 32 * (4 / NS);
   const size_t comb = NS > 1 ? sizeof(float) * (4 - 4 / NS) * 2 * (D / 32) * 16 * 64 : 0;
-  const size_t tiles = smem_bytes<D, 32 * NS>() + (kVLds<D, NS> ? sizeof(float) * 32 * (D + 4) : 0);
+  const size_t tiles = smem_bytes<D, NS>() + v_bytes<D, NS>();
   p.nx_kv = static_cast<int>(blocks_of(p.s_k, rows));
   p.nx_q = static_cast<int>(blocks_of(p.s_q, rows));
   const int64_t n_kv = p.pair[0].dk ? static_cast<int64_t>(p.nx_kv) * p.h_kv * p.shares : 0;
@@ -817,7 +1061,9 @@ int bwd(F32BwdParams p, hipStream_t st) {
 //   8 / 2 heads x 1024 rows 1183 / 647 / 371,  32 x 256 87 / 57 / 72,  32 x 1024 547 / 604 / 725,
 //   32 x 4096 8370 / 9210 / 11380 (82 TFLOP/s with 1);  shared, 8 / 2 x 1024 178, x 2048 1310 -> 623, four
 //   diagonal chunks of 1024 1220 -> 443.
-// At d = 128 the 4-part form with a shared walk spills 52 registers and takes longer than estimated (8 / 2 x 256 44 us
+// (Timed with fp32 products, as were the walks above; the terms' ratios are what decides, and split products shorten the 1- and
+// the 2-part form alike.)
+// At d = 128 the 4-part form with a shared walk spills 23 registers and takes longer than estimated (8 / 2 x 256 44 us
 // for 35).  Where it is chosen it is the better form all the same: 4 against 2 parts 44 / 45 there, 8 / 2 x 512 diagonal
 // 57 / 65, 8 x 512 diagonal 56 / 66, 4 / 1 x 768 75 / 109, x 1024 129 / 141; without scratch 8 / 2 x 1024 diagonal 375 / 649, one head
 // x 1024 99 / 171.

@@ -117,3 +117,47 @@ def test_f32_gradients_of_one_call_are_no_further_off_than_the_pairs(d):
         driver.run_all_workers(q, k, v, do, scale, P, bufs, at_once=at_once)
         errs.append([((g.double() - w).norm() / w.norm()).item() for g, w in zip((bufs.dQ, bufs.dK, bufs.dV), want)])
     assert all(a <= 1.05 * b for a, b in zip(*errs)), errs
+
+
+# (h_q, h_kv, s_q, s_k, d, causal): single rows, blocks of 32 and one row more or less, ragged, both row divisions and shared walks
+SPLIT = [(1, 1, 1, 1, 64, False), (2, 1, 31, 33, 64, False), (1, 1, 32, 65, 64, False), (2, 2, 97, 97, 64, True), (32, 8, 300, 300, 64, True),
+         (32, 32, 256, 256, 128, False), (32, 8, 333, 301, 128, False), (8, 2, 1024, 1024, 128, True), (32, 32, 513, 511, 128, False)]
+
+
+def _f32_backward(q, k, v, do, lse, delta, causal):
+    grads = [torch.empty_like(t) for t in (q, k, v)]
+    B.dfa_chunk_bwd(q, k, v, lse, delta, do, *grads, causal, q.shape[-1] ** -0.5, accumulate=False)
+    return grads
+
+
+@pytest.mark.parametrize("shape", SPLIT, ids=lambda s: "-".join(map(str, s)))
+def test_f32_backward_of_split_values(shape):
+    """Products of values taken apart into three bf16 ones.  Bound: the exponents, of magnitude up to 16, are rounded to 24 bits (2^-21
+    at most, a quarter of it in the mean square), the products' own errors are a fifth of that; fp32 products were 4e-7 to 7.5e-7
+    off.  dO of 2^100 and V of 2^-100 (their exponents change, no bit else does) give the same gradients but for those factors;
+    an infinite dO is that infinity in the dv of every key that its row sees and touches no other column."""
+    h_q, h_kv, s_q, s_k, d, causal = shape
+    q, k, v, do = (t.to(dev()) for t in case(4400 + s_q + s_k, h_q, h_kv, s_q, s_k, d, torch.float32))
+    q64, k64, v64, do64 = (t.double() for t in (q, k.repeat_interleave(h_q // h_kv, 0), v.repeat_interleave(h_q // h_kv, 0), do))
+    s = q64 @ k64.transpose(1, 2).contiguous() * d ** -0.5
+    if causal:
+        s = s.masked_fill(torch.ones(s_q, s_k, dtype=torch.bool, device=dev()).triu(1), -float("inf"))
+    lse = s.logsumexp(-1).float()
+    p = torch.exp(s - lse.double()[..., None])
+    dp = do64 @ v64.transpose(1, 2).contiguous()
+    delta = (p * dp).sum(-1).float()
+    ds = p * (dp - delta.double()[..., None]) * d ** -0.5
+    group = lambda t: t.view(h_kv, h_q // h_kv, s_k, d).sum(1)
+    want = [ds @ k64, group(ds.transpose(1, 2).contiguous() @ q64), group(p.transpose(1, 2).contiguous() @ do64)]
+    got = _f32_backward(q, k, v, do, lse, delta, causal)
+    for g, w in zip(got, want):       # (a single key's dS is zero but for rounding)
+        assert (g.double() - w).norm().item() <= 2 ** -21 * max(w.norm().item(), 2.0 ** -3 * w.numel() ** 0.5)
+    big = 2.0 ** 100
+    dq, dk, dv = _f32_backward(q, k, v / big, do * big, lse, delta, causal)
+    assert torch.equal(dq, got[0]) and torch.equal(dk, got[1]) and torch.equal(dv, got[2] * big)
+    do[:, s_q // 2, 5] = float("inf")
+    dv = _f32_backward(q, k, v, do, lse, delta, causal)[2]
+    last = s_q // 2 + 1 if causal else s_k
+    assert bool((dv[:, :last, 5] == float("inf")).all())
+    others = [c for c in range(d) if c != 5]
+    assert torch.equal(dv[..., others], got[2][..., others])
