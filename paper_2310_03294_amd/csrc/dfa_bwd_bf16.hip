@@ -488,7 +488,7 @@ constexpr int TILE_BYTES = kTile64;
 // the device; the sums of the two parts are added through LDS at the end.
 // PARTS: q_parts workgroups share the key tiles of a row block; k_reduce_dq adds their sums up.
 template <int NW, int NS, bool PARTS>
-__device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item, f32x4* partial, char* smem) {   // smem: two (K tile, V tile) buffers
+__device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item, f32x4* partial, char* smem) {   // smem: (K tile, V tile) buffers, three with 8 wavefronts, two with 4
   constexpr int BM = NW / NS * 32;     // query rows per workgroup
   const int share = PARTS ? item / p.q_items.ntile % p.q_parts : 0;
   const int head = PARTS ? item / p.q_items.ntile / p.q_parts : item / p.q_items.ntile;
@@ -503,7 +503,9 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
   const int rb = wave % (NW / NS), part = wave / (NW / NS);    // row block, part of every key tile
   const int q0w = q0 + rb * 32;
   const int qrow = q0w + r16;                                  // and qrow + 16
-  const uint32_t a_base = row16_base(lane), g_base = gather16_base(lane);
+  // (with two parts the part's rows come in here, once: as a block index they would be added to every address of every tile)
+  const uint32_t of_part = NS == 2 ? part * 2 * kBlock16 : 0;
+  const uint32_t a_base = row16_base(lane) + of_part, g_base = gather16_base(lane) + of_part;
 
   const char* kg = reinterpret_cast<const char*>(pr.k + kh * p.kv_sh);
   const char* vg = reinterpret_cast<const char*>(pr.v + kh * p.kv_sh);
@@ -556,9 +558,10 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
   constexpr bool WIDE = NW == 8;
   constexpr int SLOTS = WIDE ? 3 : 2;
   const int end = max(ntiles - 1, it0);            // (a share may have no tile)
+  const uint32_t lane_row = sat32(static_cast<uint64_t>(16 * cw + (lane >> 4)) * kv_rowbytes);
   auto at = [&](int slot, bool v) DFA_INLINE { return smem + (2 * slot + v) * TILE_BYTES; };
   auto plan = [&](int it, int slot, bool v) DFA_INLINE {
-    return TileRows16(v ? vg : kg, kv_rowbytes, min(it, end) * BN, p.s_k - 1, at(slot, v), cw, lane);
+    return TileRows16(v ? vg : kg, kv_rowbytes, min(it, end) * BN, p.s_k - 1, at(slot, v), cw, lane, lane_row);
   };
   const bool v_wave = WIDE && wave >= 4;           // with 8 wavefronts: this wavefront's tile
 #pragma unroll
@@ -576,22 +579,23 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
   // two) and 8 gathers of K (dQ^T += K^T dS^T), each read LEAD operands before it is used.
   constexpr int RING = WIDE ? 12 : 8, LEAD = RING - 2;
   u32x4 z[RING];
-  auto operand = [&](const Rows16& kr, const Rows16& vr, const Gather16& kc, int nk, int e) DFA_INLINE {
-    const bf16x8 x = e >= 16 ? kc.read(2 * nk, e - 16) : (e & 1 ? vr : kr).read(2 * nk + ((e >> 1) & 1), e >> 2);
+  // (rows of the slot's K tile, its V tile behind it)
+  auto operand = [&](const Rows16& rows, const Gather16& kc, int nk, int e) DFA_INLINE {
+    const bf16x8 x = e >= 16 ? kc.read(2 * nk, e - 16) : rows.read(2 * nk + ((e >> 1) & 1), e >> 2, e & 1);
     return __builtin_bit_cast(u32x4, x);
   };
   int slot = 0, it = it0;
   auto read_first = [&](int slot) DFA_INLINE {
-    const Rows16 kr(at(slot, false), a_base), vr(at(slot, true), a_base);
+    const Rows16 rows(at(slot, false), a_base);
     const Gather16 kc(at(slot, false), g_base);
 #pragma unroll
-    for (int e = 0; e < LEAD; ++e) z[e] = operand(kr, vr, kc, NS == 2 ? part : 0, e);
+    for (int e = 0; e < LEAD; ++e) z[e] = operand(rows, kc, 0, e);
   };
   if (WIDE) read_first(0);
   for (; it < seen; ++it) {
     const int k0 = it * BN;
     const int next = slot + 1 == SLOTS ? 0 : slot + 1, free = next + 1 == SLOTS ? 0 : next + 1;
-    const Rows16 kr(at(slot, false), a_base), vr(at(slot, true), a_base);
+    const Rows16 rows(at(slot, false), a_base), rows_next(at(next, false), a_base);
     const Gather16 kc(at(slot, false), g_base);
     // The pieces of a tile on its way are spread between the MFMAs (issued in a burst they stall the wavefront while the
     // memory pipe takes them in).  After the last tile the same tile goes once more into a slot that is not read
@@ -602,15 +606,12 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
     const bool need_mask = (k0 + BN > p.s_k) || (p.causal && k0 + BN - 1 > q0w + off);
 #pragma unroll
     for (int n = 0; n < 2 / NS; ++n) {
-      const int nk = NS == 2 ? part : n;         // 32-key block of the tile
+      const int key0 = k0 + (NS == 2 ? part : n) * 32;      // of this 32-key block
       const bool last_half = n == 2 / NS - 1;
       auto read_ahead = [&](int e) DFA_INLINE {
-        if (e < 24) z[e % RING] = operand(kr, vr, kc, nk, e);
-        else if (!last_half) z[e % RING] = operand(kr, vr, kc, nk + 1, e - 24);
-        else if (WIDE) {
-          const Rows16 kn(at(next, false), a_base), vn(at(next, true), a_base);
-          z[e % RING] = operand(kn, vn, kc, NS == 2 ? part : 0, e - 24);
-        }
+        if (e < 24) z[e % RING] = operand(rows, kc, n, e);
+        else if (!last_half) z[e % RING] = operand(rows, kc, n + 1, e - 24);
+        else if (WIDE) z[e % RING] = operand(rows_next, kc, 0, e - 24);
       };
       f32x4 s[2][2], dp[2][2];                   // [key block][row block]
 #pragma unroll
@@ -648,7 +649,7 @@ __device__ __forceinline__ void dq(const BwdParams& p, const Pair& pr, int item,
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int kvi = k0 + nk * 32 + mb * 16 + g * 4 + i;
+            const int kvi = key0 + mb * 16 + g * 4 + i;
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb)
               if (kvi >= p.s_k || (p.causal && kvi > qrow + 16 * nb + off)) dp[mb][nb][i] = 0.f;
@@ -1031,8 +1032,9 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
       });
       return rc ? rc : reduce();
     }
-    // dq alone: 256-row workgroups for long unmasked chunks (at least four of them per CU), 128 rows otherwise
-    const bool wide = (!sh.causal || sh.s_k / 2 >= sh.s_q) && blocks_of(sh.s_q, 256) * sh.h_q * n >= 1024;
+    // dq alone: 256-row workgroups for long unmasked chunks (two of them per CU: whole shares, 128 / 256 rows, 32 heads x 8 x 4096
+    // 4540 / 4482 us, 32 over 8 x 8 x 5000 7115 / 6985, 16 over 4 x 16 x 4700 5771 / 5700), 128 rows otherwise
+    const bool wide = (!sh.causal || sh.s_k / 2 >= sh.s_q) && blocks_of(sh.s_q, 256) * sh.h_q * n >= 512;
     if (!make_items(p.q_items, sh.s_q, wide ? 256 : 128, sh.h_q, n, sh.causal)) return static_cast<int>(DFA_ERR_SHAPE);
     const int64_t blocks = xcd_blocks(p.q_items.map);
     return wide ? launch<NP, k_bwd_dq_bf16<8, NP>>(p, blocks, 512, 6 * qs::TILE_BYTES, st)

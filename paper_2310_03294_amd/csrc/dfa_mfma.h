@@ -295,8 +295,9 @@ __device__ __forceinline__ uint32_t row16_base(int lane) {
 struct Rows16 {
   uint32_t a[2];                                      // by s % 2
   __device__ __forceinline__ Rows16(const char* tile, uint32_t base) { a[0] = lds_addr(tile) + base; a[1] = a[0] ^ 16; }
-  __device__ __forceinline__ bf16x8 read(int block, int s) const {
-    return *(DFA_LDS const bf16x8*)(a[s & 1] + block * kBlock16 + 128 * (s >> 1));
+  // tile: of several that lie one after the other (the constant goes into the instruction's offset)
+  __device__ __forceinline__ bf16x8 read(int block, int s, int tile = 0) const {
+    return *(DFA_LDS const bf16x8*)(a[s & 1] + tile * kTile64 + block * kBlock16 + 128 * (s >> 1));
   }
 };
 
@@ -379,18 +380,21 @@ __device__ __forceinline__ void tile16_copy_piece(const TileCopy16& c) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
                :: "s"(c.lds), "v"(c.v[J]), "s"(c.g), "n"(row16_off(J)) : "memory", "m0");
 }
-// The same without per-lane offsets kept for each piece, every row clamped as it goes (four vector instructions a piece,
-// eight registers fewer).
+// The same without per-lane offsets kept for each piece (seven registers fewer): a row's offset from the first one's, clamped to the
+// last row's, as bytes (what passes 2^32 stays there: a few rows far apart).
+__device__ __forceinline__ uint32_t sat32(uint64_t x) { return x < 0xffffffffu ? static_cast<uint32_t>(x) : 0xffffffffu; }
 struct TileRows16 {
   const char* g;        // scalar base, kEarly16 bytes early
-  uint32_t rowbytes, cb, lds;
-  int row, last;        // row: of the lane's first piece
-  __device__ __forceinline__ TileRows16(const char* gbase, uint32_t rowbytes, int row0, int last, const char* tile, int w, int lane)
-      : g(gbase - kEarly16), rowbytes(rowbytes), cb(16 * ((lane & 15) ^ (2 * (lane >> 4)))), lds(lds_addr(tile) + w * kBlock16),
-        row(row0 + 16 * w + (lane >> 4)), last(last) {}
+  uint32_t rowbytes, last, row, cb, lds;      // row: of the lane's first piece
+  // lane_row: sat32 of (16 w + lane / 16) * rowbytes
+  __device__ __forceinline__ TileRows16(const char* gbase, uint32_t rowbytes, int row0, int last_row, const char* tile, int w, int lane,
+                                        uint32_t lane_row)
+      : g(gbase - kEarly16), rowbytes(rowbytes), last(static_cast<uint32_t>(last_row) * rowbytes),
+        row(__builtin_elementwise_add_sat(static_cast<uint32_t>(row0 < last_row ? row0 : last_row) * rowbytes, lane_row)),
+        cb(16 * ((lane & 15) ^ (2 * (lane >> 4)))), lds(lds_addr(tile) + w * kBlock16) {}
   template <int J> __device__ __forceinline__ void piece() const {
-    const int r = row + 4 * J;
-    const uint32_t v = static_cast<uint32_t>(r < last ? r : last) * rowbytes + (cb ^ (16 * (J >> 1))) + (kEarly16 - row16_off(J));
+    const uint32_t r = __builtin_elementwise_add_sat(row, sat32(static_cast<uint64_t>(4 * J) * rowbytes));
+    const uint32_t v = (r < last ? r : last) + (cb ^ (16 * (J >> 1))) + (kEarly16 - row16_off(J));
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
                  :: "s"(lds), "v"(v), "s"(g), "n"(row16_off(J)) : "memory", "m0");
   }
