@@ -516,14 +516,14 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
     typedef f32x4 Half[2][RB];               // [16-key block][16-row block]
     constexpr int AHEAD = 3;                 // row reads run this many steps (of RB products) ahead, into the next half
     u32x4 x[AHEAD + 1];
-    auto read_ahead = [&](const Rows16& rows, int half, int n) {
+    auto read_ahead = [&](const Rows16& rows, int half, int n) DFA_INLINE {
       x[n & AHEAD] = __builtin_bit_cast(u32x4, rows.read(2 * half + (n & 1), n >> 1));
     };
     // step n of S^T = K Q^T of a half: 16-key block n % 2, 32 elements of d from n / 2
-    auto product = [&](Half& s, bf16x8 k, int n, int nb) {
+    auto product = [&](Half& s, bf16x8 k, int n, int nb) DFA_INLINE {
       s[n & 1][nb] = mfma16(k, qreg[n >> 1][nb], n < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[n & 1][nb]);
     };
-    auto products = [&](Half& s, const char* Ks, int half) {
+    auto products = [&](Half& s, const char* Ks, int half) DFA_INLINE {
       const Rows16 rows(Ks, a_base);
 #pragma unroll
       for (int n = 0; n < 8; ++n) {
@@ -532,7 +532,7 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
         for (int nb = 0; nb < RB; ++nb) product(s, k, n, nb);
       }
     };
-    auto mask = [&](Half& s, int k0) {
+    auto mask = [&](Half& s, int k0) DFA_INLINE {
       if ((k0 + 32 > p.s_k) || (CAUSAL && k0 + 31 > q0w + off)) {
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
@@ -545,7 +545,7 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
           }
       }
     };
-    auto row_max = [&](const Half& s, int nb) {
+    auto row_max = [&](const Half& s, int nb) DFA_INLINE {
       float mx = s[0][nb][0];
 #pragma unroll
       for (int j = 1; j < 8; ++j) mx = fmaxf(mx, s[j >> 2][nb][j & 3]);
@@ -555,19 +555,22 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
     float mc[RB];                            // the references in the exponents' units
 #pragma unroll
     for (int nb = 0; nb < RB; ++nb) mc[nb] = m_run[nb] == -INFINITY ? 0.f : m_run[nb] * c2;
-    // Rows without a reference take the maximum of the half's scores for one.
-    bool open = true;                        // there are such rows
-    auto first_reference = [&](const Half& s) {
-      if (!open) return;
+    // Rows without a reference take the maximum of the tile's scores for one, so that its largest weight is exactly 1 (of the first
+    // 32 keys' scores only, the largest weight and all others relative to it are rounded: 1 % more error in short rows).  The
+    // second half's products are done here and, as always, between the exponentials of the first: half a tile per walk.
+    int open = 1;                            // there are such rows
+    auto first_reference = [&](const Half& s, Half& t, const char* Ks, int k0) DFA_INLINE {
+      products(t, Ks, 1);
+      mask(t, k0 + 32);
       bool none = false;
 #pragma unroll
       for (int nb = 0; nb < RB; ++nb) {
-        const float mx = row_max(s, nb);
+        const float mx = fmaxf(row_max(s, nb), row_max(t, nb));
         if (m_run[nb] == -INFINITY) m_run[nb] = mx;
         mc[nb] = m_run[nb] == -INFINITY ? 0.f : m_run[nb] * c2;
         none |= m_run[nb] == -INFINITY;
       }
-      open = __any(none);
+      open = __builtin_amdgcn_readfirstlane(__any(none));
     };
     // P^T = exp2(S^T c - reference) rounded to bf16, score j of the lane's 8 RB (a row's 8 keys one after the other) between
     // the products of the other half, handed to the PV wavefront through LDS (lane-private, any layout will do).  The row
@@ -579,8 +582,8 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
     // an instruction comes a product later, or the wavefront would wait for it.
     float ready, top;                        // the exponent of the next score; the largest weight, unrounded: sum of eight
     u32x4 word;
-    auto begin = [&](const Half& s) { ready = fmaf(s[0][0][0], c2, -mc[0]); };
-    auto pair = [&](auto rounded, Half& s, int j, char* px) {      // weights j - 2 and j - 1
+    auto begin = [&](const Half& s) DFA_INLINE { ready = fmaf(s[0][0][0], c2, -mc[0]); };
+    auto pair = [&](auto rounded, Half& s, int j, char* px) DFA_INLINE {      // weights j - 2 and j - 1
       const int nb = (j - 2) >> 3, e = (j - 2) & 7;
       const float w0 = s[e >> 2][nb][e & 3], w1 = s[e >> 2][nb][(e & 3) + 1];
       bf16x2 two;
@@ -590,7 +593,7 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
       word[e >> 1] = __builtin_bit_cast(uint32_t, two);
       if (e == 6) *reinterpret_cast<u32x4*>(px + nb * 1024) = word;
     };
-    auto score = [&](auto rounded, Half& s, float (&sum)[RB], int j, char* px) {
+    auto score = [&](auto rounded, Half& s, float (&sum)[RB], int j, char* px) DFA_INLINE {
       const int nb = j >> 3, e = j & 7;
       const float w = __builtin_amdgcn_exp2f(ready);
       if (j + 1 < 8 * RB) ready = fmaf(s[((j + 1) >> 2) & 1][(j + 1) >> 3][(j + 1) & 3], c2, -mc[(j + 1) >> 3]);
@@ -601,7 +604,7 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
       }
       s[e >> 2][nb][e & 3] = w;
     };
-    auto end = [&](auto rounded, Half& s, float (&sum)[RB], char* px) {
+    auto end = [&](auto rounded, Half& s, float (&sum)[RB], char* px) DFA_INLINE {
       pair(rounded, s, 8 * RB, px);
       if (!decltype(rounded)::value) {       // (32 comparisons fewer: diagonal of 32 heads x 16384 1912 -> 1879 us)
         sum[RB - 1] += s[1][RB - 1][3];
@@ -615,10 +618,11 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
     // without looking for its maximum: as long as no score lies more than 2^14 above the
     // reference, the exponentials are harmless in fp32 / bf16, O needs no rescaling, and the final
     // division by the row sum removes the reference.  The reference is derived from the scores
-    // themselves (row maximum, exchanged between the lanes of a row) on a row's first keys -
+    // themselves (row maximum, exchanged between the lanes of a row) on a row's first tile -
     // so the largest weight seen is at least 1 and later keys cannot underflow the row sum - and
-    // again when the largest weight of a tile shows a score far above it (or is no number): the tile's
-    // products are then done once more and taken against the moved reference.
+    // again when the largest weight of a tile shows a score far above it: the tile's
+    // products are then done once more and taken against the moved reference.  (A weight that is no number moves
+    // nothing: its row is none either way.)
     Half sa, sb;                             // the scores of keys 0 .. 31 and 32 .. 63 of a tile
     products(sa, smem + OFF_K, 0);
     {
@@ -640,7 +644,7 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
       top = 0.f;
 
       mask(sa, k0);
-      first_reference(sa);
+      if (open) first_reference(sa, sb, Ks, k0);
       begin(sa);
 #pragma unroll
       for (int n = 0; n < 8; ++n) {
@@ -668,7 +672,6 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
       }
       end(rounded, sa, sum0, px);
       mask(sb, k0 + 32);
-      first_reference(sb);
       begin(sb);
 #pragma unroll
       for (int n = 0; n < 8; ++n) {
@@ -767,10 +770,11 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
     // Slot it, from the barrier at which P of tile it - 1 is there: V tile `it` on its way (after the last the same once more,
     // into the slot that nobody reads), O^T = O^T * factor + V^T P^T for tile it - 1, and the row sums of its rounded weights.
     // Sums: v_mfma_f32_4x4x4_16b_bf16 against ones adds up a lane's four weights, in each of four registers (in 8 cycles of a
-    // pipe that has 2048 to do; taking the weights apart for v_add_f32 takes 128 vector instructions a tile).
-    f32x4 l_run[RB];                         // this lane's quarter of the rows' sums, four times
+    // pipe that has 2048 to do; taking the weights apart for v_add_f32 takes 128 vector instructions a tile).  A tile's weights
+    // make a sum of their own: the running sum is rounded once per tile, not four times.
+    float l_run[RB];                         // this lane's quarter of the rows' sums
 #pragma unroll
-    for (int nb = 0; nb < RB; ++nb) l_run[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int nb = 0; nb < RB; ++nb) l_run[nb] = 0.f;
     int it = 1;
     auto slot = [&](auto rounded) {
       lds_dma_wait();
@@ -786,6 +790,7 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
       auto gather = [&](int n) { return cols.read(2 * (n >> 3), n & 7); };
       bf16x8 y[AHEAD + 1];
       u32x4 pa[2][RB];
+      f32x4 sum[RB];                         // of the tile, in each register
       const int moved = *(reinterpret_cast<const int*>(smem + OFF_MV) + (t & 1) * 4 + sw);
 #pragma unroll
       for (int n = 0; n < AHEAD; ++n) y[n] = gather(n);
@@ -812,7 +817,7 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
           o[n & 7][nb] = mfma16(y[n % (AHEAD + 1)], __builtin_bit_cast(bf16x8, pa[n >> 3][nb]), o[n & 7][nb]);
           if (decltype(rounded)::value && !(n & 3)) {      // half of the row's weights of 32 keys
             const u32x4 w = pa[n >> 3][nb];
-            l_run[nb] = mfma_sum4(n & 4 ? u32x2{w[2], w[3]} : u32x2{w[0], w[1]}, l_run[nb]);
+            sum[nb] = mfma_sum4(n & 4 ? u32x2{w[2], w[3]} : u32x2{w[0], w[1]}, n == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum[nb]);
           }
           DFA_SCHED_FENCE();
         }
@@ -820,6 +825,10 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
         if (n == 2) tile16_copy_piece<1>(cn);
         if (n == 4) tile16_copy_piece<2>(cn);
         if (n == 6) tile16_copy_piece<3>(cn);
+      }
+      if (decltype(rounded)::value) {
+#pragma unroll
+        for (int nb = 0; nb < RB; ++nb) l_run[nb] += sum[nb][0];
       }
     };
     if constexpr (kSpans<Args>) {
@@ -837,7 +846,7 @@ __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
     float inv[RB];
 #pragma unroll
     for (int nb = 0; nb < RB; ++nb) {
-      float l_tot = l_run[nb][0];
+      float l_tot = l_run[nb];
       l_tot += __shfl_xor(l_tot, 16);
       l_tot += __shfl_xor(l_tot, 32);
       const float* st = reinterpret_cast<const float*>(smem + OFF_ST) + sw * WROWS + nb * 16 + r16;

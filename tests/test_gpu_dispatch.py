@@ -171,6 +171,55 @@ def test_bf16_forward_wide_reference_jumps(shape, top):
         assert maxerr(o[h, rows], O) <= tol and maxerr(lse[h, rows], L) <= max(tol, abs(L).max() * 2.0 ** -17)
 
 
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("where", ["halves", "second half of the first tile", "one key", "one key of the first tile"])
+@pytest.mark.parametrize("shape", WIDE + [(200, 100, 300, 129, False)])
+def test_bf16_forward_wide_reference_jumps_inside_a_tile(shape, where, accumulate):
+    """The same with jumps at 32 keys, half of a tile: a level of its own for every 32 keys, one half (the first tile's second), one
+    key (of which a lane of a diagonal's wavefront has one weight in a sum of eight), from the empty state and from one that lies
+    far below the jump and has not seen anything in every fifth row."""
+    h_q, h_kv, s_q, s_k, causal = shape
+    d, tol, scale = 128, TOL[torch.bfloat16], 128 ** -0.5
+    q, k, v, _ = case(6700 + s_q + s_k, h_q, h_kv, s_q, s_k, d, torch.bfloat16)
+    g = torch.Generator().manual_seed(12)
+    u, level = torch.ones(d) / d ** 0.5, torch.zeros(s_k)
+    if where == "halves":
+        level = (150 * torch.rand((s_k + 31) // 32, generator=g)).repeat_interleave(32)[:s_k]
+    elif where == "second half of the first tile":
+        level[32:64] = 150.0
+    else:
+        level[37 if "first" in where else min(s_k, 1000) // 64 * 64 - 21] = 150.0
+    q, k = (q + 4.0 * u).to(torch.bfloat16), (0.3 * k + level.view(1, s_k, 1) * u).to(torch.bfloat16)
+    o0, lse0 = 0.1 * torch.randn(h_q, s_q, d, generator=g), torch.randn(h_q, s_q, generator=g) + 6
+    lse0[:, ::5] = -math.inf
+    o, lse = o0.to(dev()), lse0.to(dev())
+    f = dfa.dfa_chunk_fwd_acc if accumulate else dfa.dfa_chunk_fwd
+    f(*(t.to(dev()) for t in (q, k, v)), causal, scale, o=o, lse=lse)
+    rows = sorted({0, 31, 32, 37, 63, 64, 127, 128, 255, 256, 299, s_q // 3, s_q // 2, s_q - 65, s_q - 1})
+    for h in (0, h_q // 2, h_q - 1):
+        want = _sampled(q, k, v, h, h * h_kv // h_q, rows, scale, causal)
+        if accumulate:
+            want = A.merge(np64(o0[h, rows]), np64(lse0[h, rows]), *want)
+        assert maxerr(o[h, rows], want[0]) <= tol and maxerr(lse[h, rows], want[1]) <= max(tol, abs(want[1]).max() * 2.0 ** -17)
+
+
+@pytest.mark.parametrize("key", [5, 40, 63])
+def test_bf16_forward_wide_first_reference(key):
+    """256-row workgroups: a row's weights are relative to the largest of its first 64, which is 1 and not rounded.  One key has
+    e^7.5 times the others' weight; those (e^(x - 7.5) for N(0, 1) scores x, and one in a few hundred rows more than the key's own
+    noise allows) are off by 2^-9 / sqrt(3) each, independently: of the sum, (128 keys) 128 e^0.5 e^-7.5 = 0.12 of it times
+    1.1e-3 e^0.5 / sqrt(128), 2e-5.  A rounded largest weight alone makes 1.1e-3 of 0.9 of the sum."""
+    h_q, h_kv, s_q, s_k, scale = 200, 100, 300, 129, 128 ** -0.5
+    q, k, v, _ = case(6800 + key, h_q, h_kv, s_q, s_k, 128, torch.bfloat16)
+    q[..., 0], k[..., 0] = 8.0, 0.0
+    k[:, key, 0] = 10.625
+    sh, form = B.DfaShape(h_q, h_kv, s_q, s_k, 128, B.DFA_BF16, B.DFA_F32, 0, scale), B.DfaForm()
+    assert dfa.load_library().dfa_chunk_fwd_form(ctypes.byref(sh), 1, ctypes.byref(form)) == 0 and form.rows == 256
+    _, lse = dfa.dfa_chunk_fwd(*(t.to(dev()) for t in (q, k, v)), False, scale)
+    _, L = A.attention_fwd(np64(q), np64(k), np64(v), scale, causal=False)
+    assert np.sqrt(((np64(lse) - L) ** 2).mean()) <= 8e-5
+
+
 @pytest.mark.parametrize("shape", [(4, 4, 64, 640, False), (4, 4, 640, 640, True)])
 def test_bf16_forward_parts_far_apart(shape):
     """Parts of the keys whose scores differ by hundreds: the other parts' weights underflow."""

@@ -27,6 +27,11 @@ def test_bf16_backward_spills_nothing(tmp_path):
     assert {k: n for k, n in _spills("dfa_bwd_bf16.hip", tmp_path).items() if n} == {}
 
 
+def test_bf16_forward_spills_nothing(tmp_path):
+    """The 256-row form of lists of pairs stands at 254 of 256 registers."""
+    assert {k: n for k, n in _spills("dfa_fwd_bf16.hip", tmp_path).items() if n} == {}
+
+
 def test_f32_sums_are_for_sequences_alone(tmp_path):
     """dk, dv as sums of 32 rows (7 % of a backward at d = 128) in kernels of their own, and no form of theirs spills."""
     spills = {k: n for k, n in _spills("dfa_attn_f32.hip", tmp_path).items() if "k_bwd_f32" in k}
