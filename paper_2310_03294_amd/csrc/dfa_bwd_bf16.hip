@@ -29,6 +29,7 @@
 // which caps a 128-key workgroup tile at ~400 TFLOP/s no matter how the rest is scheduled.
 // Recomputing S and dP in a second kernel costs 7 products instead of 5 but has no such cap.
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -866,92 +867,139 @@ int64_t blocks_of(int rows, int per) { return (static_cast<int64_t>(rows) + per 
 
 constexpr int64_t PART_BYTES = kv::PART_F4 * 16;
 
-// How a call's work is divided: dq by 128-row workgroups with two key parts (split) or 256-row ones, and
-// `parts` workgroups per key tile for dk, dv.
+// How a call's work is divided: dq by 128-row workgroups with two key parts (split) or by 256-row ones, `parts` workgroups per
+// key tile for dk, dv, `q_parts` per row block for dq; which kind's workgroups come first.
 struct Plan { bool split; int parts; double us; int q_parts; int64_t bytes; bool q_first; };
 
-// dq by 128-row workgroups with two key parts while all workgroups still run at once (8 heads x 2048: 60
-// us, with 256 rows 72), by 256-row ones if that makes them (8 x 2304: 84, with 128 rows 108), then by
-// 128-row ones again as long as they are the smaller steps to balance (8 x 2777: 130 against 146; at
-// 32 x 2048 227 against 217).
-bool split_dq(int64_t n_kv, int64_t n256, int64_t n128) {
-  return n_kv + n128 <= 256 || (n_kv + n256 > 256 && n256 <= 128);
-}
-
-// Parts.  A dk/dv workgroup walks over the query tiles of its whole group of heads, and with grouped heads
-// there are few of them.  `parts` workgroups share the walk, and their sums (128 KB each) go through
-// memory and a second launch: worth it where a few long workgroups would be alone on the device at the end.
-// The estimate, with what one box measured for its terms: 8 us per workgroup and 1.35 per query tile (dk,
-// dv) or 1.9 per key tile (dq, 256 rows); a call that runs in one round takes its longest workgroup, a
-// longer one the device's even share and about half a workgroup; the sums move at 2.5 TB/s.  Parts that
-// do not divide the group stride over heads and share less in the L2 (15 %).  us per call with 1 / 2 / 4
-// parts: 8 over 2 heads x 1024 87 / 51 / 35, x 4096 341 / 217 / 212, x 8192 814 / 761 / 767; 32 over 8 x
-// 1024 91 / 66 / 73, x 1500 diagonal 135 / 101 / 103, x 4096 756 / 779 / 810; 8 heads of their own x 1024
-// 31 / 36 / 38.
-// Few query rows against many keys, from two keys per row on (a span of chunks): the walk of a row block of dq over all of them
-// may be the whole call, and `q_parts` workgroups of 128 rows share it.  Such calls run in many rounds, the longer kind of
-// workgroups first and the shorter filling the end, so they have an estimate of their own, with constants fitted to 40 spans of 2
-// to 9 chunks of 256 to 8192 rows with every division timed (chosen / best 1.025 in the mean).  us, pairs one by one / span: 4
-// over 1 heads, 5 x 8192 1928 / 1781, 16 over 4, 5 x 2048 545 / 484, 8 over 2, 5 x 700 136 / 50, 8 heads, 5 x 2777 588 / 450, 32 heads,
-// 5 x 1024 338 / 268.
+// A dk/dv workgroup walks over the query tiles of its whole group of heads, and with grouped heads there are few of them; the walk
+// of a row block of dq over many keys may be the whole call.  Several workgroups share such a walk, and their sums (128 KB, 64 KB
+// each) go through memory and a further launch.  What a division takes is estimated by placing its workgroups as the hardware does:
+// in order, one per CU, each XCD its range of them.  The constants are fitted to 262 calls of 1 to 32 heads (own or grouped) x 200 to
+// 9000 rows and 56 spans of 2 to 9 chunks, every division timed: chosen / best 1.003 in the mean for full pairs, 1.005 for
+// diagonals, 1.03 for spans (an estimate by even shares, fitted to kernels on 32x32x16 products, 1.03, 1.03 and 1.045).
+// us, as it chose / so: one head x 3000 72.3 / 59.4, 32 over 8 heads x 640 diagonal 39.2 / 32.9, x 1280 118.6 / 102.0, 16 over 4 x 2304
+// 182 / 143, x 1500 diagonal 65.7 / 57.2, 8 over 2 x 4352 x 5322 381 / 300; span of 4 x 237 33.2 / 25.1.
 struct Call {
-  int group;
+  int group, s_q, s_k, causal, kv_heads, q_heads;      // heads: of all pairs
   int64_t kv1, n256, n128;      // workgroups of dk, dv undivided, of dq by 256 and by 128 rows
-  double walk_kv, k_tiles;      // of dk, dv undivided; key tiles
+  int64_t q_tiles, k_tiles;     // that an undivided dk/dv workgroup and one of dq walk over
   double mean;                  // of a walk: the query chunk's own keys are half visible
   int64_t ws_bytes;
+  bool longest_first;           // (else the kind of which there are fewer per head)
 };
+constexpr int XCDS = 8, CUS = 32;      // CUs of an XCD
+
+// When na workgroups of `a` us and then nb of `b` are done on an XCD.
+double placed(int64_t na, double a, int64_t nb, double b) {
+  const int64_t late = na % CUS, early = CUS - late;                 // CUs that are free at t1, at t2
+  const double t1 = static_cast<double>(na / CUS) * a, t2 = late ? t1 + a : t1;
+  if (!nb) return t2;
+  double least = t1 + nb * b / early;
+  if (least > t2) least = (nb * b + early * t1 + late * t2) / CUS;
+  double end = 1e30;
+  for (double t0 : {t1, t2}) {         // a workgroup of the second kind ends last, on a CU of either sort
+    double n = std::max(1., std::ceil((least - t0) / b - 1e-9));
+    for (int k = 0; k < 3; ++k, ++n) {
+      const double t = t0 + n * b;
+      const int64_t done = early * static_cast<int64_t>((t - t1) / b + 1e-9) + (t > t2 ? late * static_cast<int64_t>((t - t2) / b + 1e-9) : 0);
+      if (done >= nb) { end = std::min(end, t); break; }
+    }
+  }
+  return std::max(t2, end);
+}
+
+// A causal call's (head, part) groups go to the XCDs in ranges, longest tiles first: with a part of a group left over, an XCD that
+// gets its first tiles has so much more than an even share.
+double uneven(int64_t groups) {
+  const double g = static_cast<double>(groups) / XCDS, whole = static_cast<double>(groups / XCDS), rest = g - whole;
+  return groups <= 2 ? 1.0 : (whole + rest * (2 - rest)) / g;
+}
+
 bool feasible(const Call& c, int parts, int q_parts) {
   return (parts == 1 || (c.kv1 && parts <= 4 * c.group && c.kv1 * parts <= 1024)) && (q_parts == 1 || c.n128 * q_parts <= 1024) &&
          (q_parts > 1 ? c.n128 * q_parts * QPART_F4 * 16 : 0) + (parts > 1 ? c.kv1 * parts * PART_BYTES : 0) <= c.ws_bytes;
 }
-Plan estimate(const Call& c, int parts, int q_parts, bool split, bool span) {
+// 256-row workgroups of dq where there are many of them or all workgroups run at once.  (In between they are few and long, and
+// the estimate has them too short: 32 heads x 900 diagonal 62.2 us, 57.8 split, x 1024 63.0, 60.0.)
+bool wide_dq(const Call& c, int parts) { return c.n256 > 128 || c.kv1 * parts + c.n256 <= XCDS * CUS; }
+
+// us: of a workgroup, and per tile of its walk (slower by `slow` with 256 workgroups and more, dq's 128 rows by `many` with four
+// rounds of them); `tail`, `late`: see below; of the sums' launches, per part, and their GB/ms; what divisions have to gain.
+struct Terms { double f_kv, tile_kv, f_wide, tile_wide, f_split, tile_split, f_slow, slow, many, tail, late, sums_kv, part_kv, sums_q, part_q, rate, gain; };
+constexpr Terms PAIR{7.8, 1.356, 14.6, 1.90, 13.7, 0.894, 0.11, 0.01, 0.21, 0.32, 0.32, 1.7, 0.10, 0, 0, 12.8, 0.98};
+constexpr Terms SPAN{7.3, 1.343, 6.9, 1.88, 6.7, 1.126, 0.04, 0.02, 0.083, 0.47, 0.66, 2.7, 0.64, 3.2, 0.22, 12.5, 1.0};
+
+Plan estimate(const Call& c, int parts, int q_parts, bool split) {
+  const Terms& k = c.longest_first ? SPAN : PAIR;
   const int64_t n_kv = c.kv1 * parts, n_q = split ? c.n128 * q_parts : c.n256;
   const int64_t q_bytes = q_parts > 1 ? n_q * QPART_F4 * 16 : 0, kv_bytes = parts > 1 ? n_kv * PART_BYTES : 0;
   Plan x{split, parts, 0., q_parts, kv_bytes + q_bytes, false};
-  const double walk_q = (span ? 2.1 : 1.9) * c.k_tiles, w_kv = c.walk_kv / parts;
-  const double w_q = split ? walk_q / (2 * q_parts) * (span ? 1.1 : 1.0) : walk_q;
-  const double t_kv = n_kv ? 8 + w_kv : 0, t_q = n_q ? 8 + w_q : 0;
-  x.us = std::max(t_kv, t_q);
-  if (n_kv + n_q > 256) {
-    const double share = (n_kv * (8 + w_kv * c.mean) + n_q * (8 + w_q * c.mean)) / 256;
-    x.us = std::max(x.us, share + (span ? 0.8 * std::min(t_kv, t_q) : 0.45 * x.us));
+  const double rounds = static_cast<double>(n_kv + n_q) / (XCDS * CUS), busy = std::min(1., std::max(0., 2 * rounds - 1));
+  const double slow = 1 + k.slow * busy, f_slow = 1 + k.f_slow * busy;
+  const double f_kv = k.f_kv * f_slow, tile_kv = k.tile_kv * slow, f_q = (split ? k.f_split : k.f_wide) * f_slow;
+  const double tile_q = (split ? k.tile_split * (1 + k.many * std::min(1., std::max(0., (rounds - 1) / 3))) : k.tile_wide) * slow;
+  const double w_kv = tile_kv * c.q_tiles / parts, w_q = tile_q * c.k_tiles / q_parts;
+  x.q_first = c.longest_first ? f_q + w_q > f_kv + w_kv : c.group <= parts;
+  struct Kind { int64_t n; double longest, mean; int64_t per_head; };
+  const Kind kv{(n_kv + XCDS - 1) / XCDS, f_kv + w_kv, (f_kv + w_kv * c.mean) * (c.causal ? uneven(static_cast<int64_t>(c.kv_heads) * parts) : 1.0),
+                blocks_of(c.s_k, kv::BN)};
+  const Kind q{(n_q + XCDS - 1) / XCDS, f_q + w_q, (f_q + w_q * c.mean) * (c.causal ? uneven(static_cast<int64_t>(c.q_heads) * q_parts) : 1.0),
+               blocks_of(c.s_q, split ? 128 : 256)};
+  const Kind &a = x.q_first ? q : kv, &b = x.q_first ? kv : q;
+  if (!c.causal) {
+    x.us = placed(a.n, a.longest, b.n, b.longest);
+  } else {
+    // Workgroups of all lengths: the even share and some of the shorter kind's longest, but the last head's longest workgroup may
+    // begin late.
+    x.us = std::max(a.n ? a.longest : 0., b.n ? b.longest : 0.);
+    if (a.n + b.n > CUS) {
+      const int64_t before = std::max<int64_t>(0, b.n - b.per_head);      // of the second kind, before the last head's
+      const double share = (a.n * a.mean + b.n * b.mean) / CUS;
+      const double begin = a.n + before < CUS ? 0.
+                           : std::max(f_kv + 2 * k.tile_kv, (a.n * a.mean + before * b.mean) / CUS - k.late * (before < CUS ? a : b).mean);
+      x.us = std::max(x.us, std::max(begin + (b.n ? b.longest : 0.), share + k.tail * std::min(a.longest, b.longest)));
+    }
   }
-  if (parts > 1) x.us = (x.us + 4 + 2 * kv_bytes / 2.5e6) * (c.group % parts && !span ? 1.15 : 1.0);
-  if (q_parts > 1) x.us += 4 + 2 * q_bytes / 2.5e6;
-  x.q_first = span ? t_q > t_kv : c.group <= parts;      // (the longer workgroups first)
+  if (parts > 1 || q_parts > 1) x.us /= k.gain;
+  if (parts > 1) x.us += k.sums_kv + k.part_kv * parts + 2 * kv_bytes / (k.rate * 1e6);
+  if (q_parts > 1) x.us += k.sums_q + k.part_q * q_parts + 2 * q_bytes / (k.rate * 1e6);
   return x;
 }
 constexpr int PARTS[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+constexpr int Q_PARTS[] = {1, 2, 3, 4, 6, 8, 12, 16};
+
+Plan best_of(const Call& c, bool dq, int most_q) {
+  Plan best{};
+  for (int q_parts : Q_PARTS) {
+    if (q_parts > most_q || !feasible(c, 1, q_parts)) break;
+    for (int parts : PARTS) {
+      if (!feasible(c, parts, q_parts)) break;
+      double least = 1e30;
+      for (bool split : {false, true}) {
+        if (split ? !dq : q_parts > 1 || (dq && !wide_dq(c, parts))) continue;
+        const Plan x = estimate(c, parts, q_parts, split);
+        if (!best.parts || x.us < best.us) best = x;
+        least = std::min(least, x.us);
+      }
+      if (least > 1.5 * best.us) break;      // (nor with more)
+    }
+  }
+  return best;
+}
 
 Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
   const int group = sh.h_q / sh.h_kv;
-  const Call c{group, dk ? blocks_of(sh.s_k, kv::BN) * sh.h_kv * pairs : 0, dq ? blocks_of(sh.s_q, 256) * sh.h_q * pairs : 0,
-               dq ? blocks_of(sh.s_q, 128) * sh.h_q * pairs : 0, 1.35 * group * blocks_of(sh.s_q, kv::BM),
-               static_cast<double>(blocks_of(sh.s_k, qs::BN)), sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0,
-               std::min(ws_bytes, int64_t{128} << 20)};
-  Plan best{};
-  for (int parts : PARTS) {
-    if (!feasible(c, parts, 1)) break;
-    const Plan x = estimate(c, parts, 1, dq && split_dq(c.kv1 * parts, c.n256, c.n128), false);
-    if (parts == 1 || x.us < (best.parts == 1 ? 0.92 : 1.0) * best.us) best = x;
-  }
+  Call c{group, sh.s_q, sh.s_k, sh.causal, sh.h_kv * pairs, sh.h_q * pairs,
+         dk ? blocks_of(sh.s_k, kv::BN) * sh.h_kv * pairs : 0, dq ? blocks_of(sh.s_q, 256) * sh.h_q * pairs : 0,
+         dq ? blocks_of(sh.s_q, 128) * sh.h_q * pairs : 0, group * blocks_of(sh.s_q, kv::BM), blocks_of(sh.s_k, qs::BN),
+         sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0, std::min(ws_bytes, int64_t{128} << 20), false};
+  const Plan best = best_of(c, dq, 1);
+  // From two keys per row on (a span of chunks) dq's walks may be shared
   if (!dq || !dk || pairs > 1 || sh.s_k / 2 < sh.s_q) return best;
-  Plan span = estimate(c, 1, 1, false, true);
-  for (int q_parts = 1; q_parts <= 16 && feasible(c, 1, q_parts); ++q_parts)
-    for (int parts : PARTS) {
-      if (!feasible(c, parts, q_parts)) break;
-      Plan x = estimate(c, parts, q_parts, true, true);
-      if (q_parts == 1) {
-        const Plan y = estimate(c, parts, 1, false, true);
-        if (y.us <= x.us || c.n256 > 256) x = y;      // (many rounds of 256-row workgroups: 32 over 8 heads, 3 x 5000 2 % slower split)
-      }
-      const bool whole = span.parts == 1 && span.q_parts == 1;
-      if (x.us < span.us * (whole && (parts > 1 || q_parts > 1) ? 0.97 : 1.0)) span = x;
-    }
-  // A pair of chunks: only where the gain is beyond what the estimate errs (8 over 2 heads x 4096 x 16384, 0.89 of it: 770 -> 795).
-  if (!sh.causal && span.us >= 0.88 * estimate(c, best.parts, 1, best.split, true).us) return best;
-  return span;
+  c.longest_first = true;
+  const Plan span = best_of(c, dq, 16);
+  // A pair of chunks: only where the gain is beyond what the estimate errs.
+  return sh.causal || span.us < 0.88 * best.us ? span : best;
 }
 
 }  // namespace

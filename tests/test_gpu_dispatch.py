@@ -341,6 +341,24 @@ def test_bf16_backward_parts(shape):
                 assert (got[i] - alone[i]).abs().max().item() <= 1e-5 * max(1.0, abs(want[i]).max())
 
 
+@pytest.mark.parametrize("h,s_q,s_k,causal", [(1, 1000, 700, False), (1, 1300, 1300, True), (2, 1920, 65, False)])
+def test_bf16_backward_parts_of_one_head(h, s_q, s_k, causal):
+    """dk, dv of heads of their own by several workgroups per key tile, whose shares are ranges of one head's query tiles."""
+    d, tol, scale = 128, TOL[torch.bfloat16], 128 ** -0.5
+    q, k, v, do = case(9200 + s_q, h, h, s_q, s_k, d, torch.bfloat16)
+    x64 = [np64(t) for t in (q, k, v, do)]
+    O, L = A.attention_fwd(*x64[:3], scale, causal=causal)
+    want = A.attention_bwd(*x64, scale, causal=causal)
+    x = [t.to(dev()) for t in (q, k, v, torch.from_numpy(L).float(), torch.from_numpy(A.delta_rows(O, x64[3])).float(), do)]
+    sh, form = B._bwd_shape(*x, torch.empty(h, s_q, d, device=dev()), *(torch.empty(h, s_k, d, device=dev()) for _ in range(2)), causal, scale), B.DfaForm()
+    assert B.load_library().dfa_chunk_bwd_form(ctypes.byref(sh), 1, 1, 1, 128 << 20, ctypes.byref(form)) == 0 and form.cuts > 1
+    for acc in (False, True):
+        got = [torch.full(w.shape, 0.5, device=dev()) for w in want]
+        dfa.dfa_chunk_bwd(*x, *got, causal, scale, accumulate=acc)
+        for g, w in zip(got, want):
+            assert maxerr(g, w + (0.5 if acc else 0.0)) <= tol * max(1.0, abs(w).max() / 4)
+
+
 @pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 128)])
 @pytest.mark.parametrize("p,c", [(19, 24), (5, 70), (2, 130)])
 @pytest.mark.parametrize("at_once", [False, True])

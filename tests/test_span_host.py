@@ -84,6 +84,21 @@ def test_divisions_of_the_backward():
         assert ask(*shape, 1) > 0, shape
 
 
+def test_divisions_of_short_backward_calls():
+    """(rows of dq's workgroups, workgroups per key tile) where the wrong ones cost 10 % and more.  us, with one, two or four per tile as
+    an estimate by even shares chose / so: 32 over 8 heads x 640 diagonal 39.2 / 32.9, one head x 3000 72.8 / 61.6, 16 over 4 x 2304 182.6
+    / 142.7, x 1500 diagonal 65.7 / 57.2, 32 over 8 x 1280 118.6 / 102.0; and calls that are right undivided."""
+    lib, form = dfa.load_library(), B.DfaForm()
+    for shape, want in (((32, 8, 640, 640, 1), (128, 3)), ((1, 1, 3000, 3000, 0), (128, 2)), ((1, 1, 1500, 1500, 1), (128, 2)),
+                        ((16, 4, 2304, 2304, 0), (128, 3)), ((16, 4, 1500, 1500, 1), (128, 3)), ((32, 8, 1280, 1280, 0), (256, 4)),
+                        ((8, 8, 1000, 1900, 0), (128, 1)), ((32, 32, 1024, 1024, 1), (128, 1)), ((32, 32, 4096, 4096, 0), (256, 1))):
+        h_q, h_kv, s_q, s_k, causal = shape
+        sh = B.DfaShape(h_q=h_q, h_kv=h_kv, s_q=s_q, s_k=s_k, d=128, dtype=B.DFA_BF16, scale=1.0, causal=causal)
+        assert lib.dfa_chunk_bwd_form(ctypes.byref(sh), 1, 1, 1, 128 << 20, ctypes.byref(form)) == 0
+        assert (form.rows, form.cuts) == want, shape
+        assert lib.dfa_chunk_bwd_form(ctypes.byref(sh), 1, 1, 1, 0, ctypes.byref(form)) == 0 and form.cuts == 1
+
+
 def test_forms_of_the_f32_diagonal():
     """Short diagonals of few heads are in the 4-part form, with scratch and above all without; sharing dq's walk only where it gains."""
     lib, form = dfa.load_library(), B.DfaForm()
