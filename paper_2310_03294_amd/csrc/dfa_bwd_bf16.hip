@@ -987,6 +987,15 @@ Plan best_of(const Call& c, bool dq, int most_q) {
   return best;
 }
 
+// dq alone: 256-row workgroups for walks of 128 key tiles and more, not on a diagonal, where they fill whole rounds of the device
+// (a last round of few of them takes as long as any other; two 128-row workgroups per CU share it better).  256 / 128 rows, 32 heads and
+// lists of them: 256 workgroups x 8192 keys 0.96, 512 and 768 0.98, 1024 to 2560 0.98 to 1.00, x 16384 and more 0.95 to 0.99; but 320
+// 1.22, 384 1.16, 640 1.10; x 6000 0.98 to 1.015, x 4096 0.98 to 1.02, x 2048 1.02 to 1.08, 32 heads x 16 pairs of 128 rows 1.7.
+bool wide_alone(const dfa_shape& sh, int pairs) {
+  const int64_t rows = static_cast<int64_t>(sh.s_q) * sh.h_q * pairs, rounds = (blocks_of(sh.s_q, 256) * sh.h_q * pairs + 255) / 256;
+  return (!sh.causal || sh.s_k / 2 >= sh.s_q) && sh.s_k >= 8192 && rounds * (256 * 256) <= rows + rows / 32;
+}
+
 Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes) {
   const int group = sh.h_q / sh.h_kv;
   Call c{group, sh.s_q, sh.s_k, sh.causal, sh.h_kv * pairs, sh.h_q * pairs,
@@ -1085,9 +1094,7 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
       });
       return rc ? rc : reduce();
     }
-    // dq alone: 256-row workgroups for long unmasked chunks (two of them per CU: whole shares, 128 / 256 rows, 32 heads x 8 x 4096
-    // 4540 / 4482 us, 32 over 8 x 8 x 5000 7115 / 6985, 16 over 4 x 16 x 4700 5771 / 5700), 128 rows otherwise
-    const bool wide = (!sh.causal || sh.s_k / 2 >= sh.s_q) && blocks_of(sh.s_q, 256) * sh.h_q * n >= 512;
+    const bool wide = wide_alone(sh, n);
     if (!make_items(p.q_items, sh.s_q, wide ? 256 : 128, sh.h_q, n, sh.causal)) return static_cast<int>(DFA_ERR_SHAPE);
     const int64_t blocks = xcd_blocks(p.q_items.map);
     return wide ? launch<NP, k_bwd_dq_bf16<8, NP>>(p, blocks, 512, 6 * qs::TILE_BYTES, st)
@@ -1096,7 +1103,9 @@ int launch_bwd_bf16(const dfa_shape& sh, const dfa_bwd_pair* pairs, int n, void*
 }
 
 dfa_form bwd_bf16_form(const dfa_shape& sh, int n, bool dq, bool dk, int64_t ws_bytes) {
-  const Plan x = plan(sh, (n - 1) % MAX_PAIRS + 1, dq, dk, ws_bytes);
+  n = (n - 1) % MAX_PAIRS + 1;
+  if (!dk) return {wide_alone(sh, n) ? 256 : 128, 1, 1, 1};
+  const Plan x = plan(sh, n, dq, dk, ws_bytes);
   return {x.split ? 128 : 256, x.split ? 2 : 1, x.parts, x.q_parts};
 }
 

@@ -359,6 +359,35 @@ def test_bf16_backward_parts_of_one_head(h, s_q, s_k, causal):
             assert maxerr(g, w + (0.5 if acc else 0.0)) <= tol * max(1.0, abs(w).max() / 4)
 
 
+@pytest.mark.parametrize("h_q,h_kv,s_q,s_k,n,rows", [
+    (64, 16, 1000, 8201, 1, 256), (64, 64, 512, 8192, 2, 256), (64, 16, 500, 8199, 2, 256),      # whole rounds of 256-row workgroups
+    (64, 16, 1100, 8201, 1, 128), (64, 16, 500, 8191, 2, 128),                                   # a round and a few more; a key too few
+])
+def test_bf16_dq_alone_forms(h_q, h_kv, s_q, s_k, n, rows):
+    """dq alone of one pair and of lists, 256 and 128 rows, by sampled rows; overwriting and adding; nothing written past the rows."""
+    d, tol, scale = 128, TOL[torch.bfloat16], 128 ** -0.5
+    g = torch.Generator(device=dev()).manual_seed(s_q + s_k)
+    rand = lambda *shape: torch.randn(shape, generator=g, device=dev()).to(torch.bfloat16)
+    at = sorted({0, 1, 31, 32, 63, 64, 127, 128, 255, 256, s_q // 2, s_q - 1})
+    ops, outs, pairs = [], [], (B.DfaBwdPair * n)()
+    for i in range(n):
+        q, do, k, v = rand(h_q, s_q, d), rand(h_q, s_q, d), rand(h_kv, s_k, d), rand(h_kv, s_k, d)
+        lse = math.log(s_k) + 0.5 * (q.float() ** 2).mean(-1)                 # what N(0, 1) keys give a row
+        delta = 0.1 * torch.randn(h_q, s_q, generator=g, device=dev())
+        ops.append((q, do, k, v, lse, delta))
+        outs.append(torch.full((h_q, s_q + 1, d), 0.5, device=dev()))
+        pairs[i] = B.DfaBwdPair(q.data_ptr(), k.data_ptr(), v.data_ptr(), lse.data_ptr(), delta.data_ptr(), do.data_ptr(), outs[i].data_ptr(), None, None, i % 2, 0)
+    sh, form, lib = B._make_shape(ops[0][0], ops[0][2], False, scale, B.DFA_BF16, lse=ops[0][4], dq=outs[0][:, :s_q], dkv=outs[0]), B.DfaForm(), B.load_library()
+    assert lib.dfa_chunk_bwd_form(ctypes.byref(sh), n, 1, 0, 0, ctypes.byref(form)) == 0 and form.rows == rows
+    assert lib.dfa_chunk_bwd_batch(ctypes.byref(sh), pairs, n, None, 0, torch.cuda.current_stream().cuda_stream) == 0
+    for i, (q, do, k, v, lse, delta) in enumerate(ops):
+        for h in (0, h_q // 2, h_q - 1):
+            kh = h * h_kv // h_q
+            want = A.rows_dq(np64(q[h, at]), np.full(len(at), s_k - 1), np64(do[h, at]), np64(lse[h, at]), np64(delta[h, at]), np64(k[kh]), np64(v[kh]), scale)
+            assert maxerr(outs[i][h, at], want + (0.5 if i % 2 else 0.0)) <= 0.02 * abs(want).max()
+        assert bool((outs[i][:, s_q] == 0.5).all())
+
+
 @pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 128)])
 @pytest.mark.parametrize("p,c", [(19, 24), (5, 70), (2, 130)])
 @pytest.mark.parametrize("at_once", [False, True])

@@ -99,6 +99,19 @@ def test_divisions_of_short_backward_calls():
         assert lib.dfa_chunk_bwd_form(ctypes.byref(sh), 1, 1, 1, 0, ctypes.byref(form)) == 0 and form.cuts == 1
 
 
+def test_forms_of_dq_alone():
+    """256 rows where they are the faster ones: long walks and whole rounds of the device; a list of 16 pairs of 32 heads x 128 rows takes
+    1.7 times as long with them, 32 heads x 5000 rows 1.1, x 2048 keys 1.05."""
+    lib, form = dfa.load_library(), B.DfaForm()
+    for shape, rows in (((32, 32, 16384, 16384, 1), 256), ((32, 8, 8192, 8192, 1), 256), ((32, 32, 4096, 20480, 1), 256), ((32, 32, 2048, 8192, 1), 256),
+                        ((8, 2, 10000, 16384, 4), 256), ((32, 8, 128, 128, 16), 128), ((32, 32, 1024, 1024, 4), 128), ((32, 32, 5000, 25000, 1), 128),
+                        ((32, 32, 4096, 4096, 1), 128), ((16, 4, 6000, 6000, 4), 128), ((32, 32, 2100, 16384, 1), 128)):
+        h_q, h_kv, s_q, s_k, n = shape
+        sh = B.DfaShape(h_q=h_q, h_kv=h_kv, s_q=s_q, s_k=s_k, d=128, dtype=B.DFA_BF16, scale=1.0)
+        assert lib.dfa_chunk_bwd_form(ctypes.byref(sh), n, 1, 0, 0, ctypes.byref(form)) == 0
+        assert (form.rows, form.parts, form.cuts, form.q_cuts) == (rows, 1, 1, 1), shape
+
+
 def test_forms_of_the_f32_diagonal():
     """Short diagonals of few heads are in the 4-part form, with scratch and above all without; sharing dq's walk only where it gains."""
     lib, form = dfa.load_library(), B.DfaForm()
