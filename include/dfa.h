@@ -81,7 +81,9 @@ typedef struct {
  *   o [h_q,s_q,d] : sh->o_dtype, written;  lse [h_q,s_q] : fp32, natural log, written
  * s_q == 0 is a no-op; s_k == 0 writes o = 0, lse = -inf (the merge identity) and
  * accepts NULL k, v.
- * bf16 inputs use bf16 MFMA with fp32 accumulation; fp32 inputs use fp32 arithmetic.
+ * bf16 inputs use bf16 MFMA with fp32 accumulation; fp32 inputs use fp32 arithmetic. (The backward's
+ * products take fp32 values as sums of three bf16 ones, which have all 24 bits of values from 2^-110 in magnitude on; of smaller ones what
+ * lies below 2^-133 is lost.)
  */
 int dfa_chunk_fwd(const dfa_shape* sh, const void* q, const void* k, const void* v,
                   void* o, float* lse, void* stream);

@@ -1,14 +1,17 @@
-// fp32 mode of the chunk kernels: fp32 operands, results and sums, products of all 24 bits, any s_q / s_k.
+// fp32 mode of the chunk kernels: fp32 operands, results and sums, products of all 24 bits (backward: of values from 2^-110 on), any s_q / s_k.
 // This is the precision-reference mode of the library (1e-5 agreement with fp64); the bf16 kernels
 // are the fast path.
 //
-// Products of the backward.  An fp32 value is the exact sum of three bf16 ones: its upper 16 bits, the rounded rest, what that leaves.  Of the nine
+// Products of the backward.  An fp32 value is the exact sum of three bf16 ones: its upper 16 bits, the rounded rest, what that leaves (a
+// value below 2^-110 in magnitude but for what lies below 2^-133, the smallest bf16 number: with dO of 2^-112 dv is 2.5e-7 off, dq and dk,
+// whose factors P (dP - D) are smaller, 2.7e-6; with dO of 2^-118 9e-6 and 1.7e-4).  The split is a published one: Henry, Tang, Heinecke,
+// "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", 2019.  Of the nine
 // products of two such sums the six largest (the others are below 2^-23 of the product, of either sign) run on
 // v_mfma_f32_32x32x16_bf16, the largest as one chain and the five small ones as another, added at the end.  That is 192 cycles per
 // 32x32x16 against 512 of v_mfma_f32_32x32x2_f32, and closer to the exact sum: relative error of a product over 128 / 1024
 // N(0,1) values 6.5e-8 / 1.9e-7 against 2.0e-7 / 5.7e-7 (a chain is rounded once per 16 terms instead of every two).
-// Infinities and NaN: the largest product has them as the fp32 one would, the chain of the small ones is bounded before it is
-// added.  us, fp32 products / these: 32 heads x 4096 8785 / 5779, 32 over 8 x 2048 2200 / 1467, 8 over 2 x 1024 diagonal 141 / 109,
+// Infinities and NaN: the largest product has them as the fp32 one would (signalling NaN are made quiet first), the chain of the small
+// ones is bounded before it is added.  us, fp32 products / these: 32 heads x 4096 8785 / 5779, 32 over 8 x 2048 2200 / 1467, 8 over 2 x 1024 diagonal 141 / 109,
 // one head x 256 diagonal at d = 64 19.4 / 16.5; the gradients are half as far from the exact ones.
 // fp32 products (v_mfma_f32_32x32x2_f32) are left in the backward with 128-row tiles at d = 128, for which three values per
 // element do not fit the LDS, and in the forward: there the split tiles leave room for one workgroup per CU, whose exponentials
@@ -28,6 +31,7 @@
 // for calls with few rows: it gives four times the workgroups, each with a quarter of the serial work.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "dfa_internal.h"
 #include "dfa_mfma.h"
@@ -153,15 +157,20 @@ struct TilePair {
       b[n] = *reinterpret_cast<const f32x4*>(B + off);
     }
   }
+  // (Whole tiles apart: the selections would be an instruction per value.)
   __device__ __forceinline__ void store_split(char* As, char* Bs, int row0, int nrows) const {
+    auto put = [&](auto whole) DFA_INLINE {
 #pragma unroll
-    for (int n = 0; n < N; ++n) {
-      const int i = threadIdx.x + n * NT, r = i / C4, c = (i % C4) * 4;
-      const bool ok = row0 + r < nrows;
-      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-      Planes<D, ROWS>::put(As, r, c, ok ? a[n] : z);
-      Planes<D, ROWS>::put(Bs, r, c, ok ? b[n] : z);
-    }
+      for (int n = 0; n < N; ++n) {
+        const int i = threadIdx.x + n * NT, r = i / C4, c = (i % C4) * 4;
+        const bool ok = decltype(whole)::value || row0 + r < nrows;
+        const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+        Planes<D, ROWS>::put(As, r, c, ok ? a[n] : z);
+        Planes<D, ROWS>::put(Bs, r, c, ok ? b[n] : z);
+      }
+    };
+    if (row0 + ROWS <= nrows) put(std::true_type{});
+    else put(std::false_type{});
   }
   __device__ __forceinline__ void store(float* As, float* Bs, int row0, int nrows) const {
 #pragma unroll
@@ -177,8 +186,11 @@ struct TilePair {
 
 // ---- split values ----
 struct Split8 { bf16x8 h, m, l; };
-// Two values: upper halves, rounded rests, what is left.
+// Two values: upper halves, rounded rests, what is left.  (A NaN is made a quiet one, whose upper half is one too; of a signalling one
+// with its payload in the lower half that would be an infinity.)
 __device__ __forceinline__ void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+  a = __builtin_canonicalizef(a);
+  b = __builtin_canonicalizef(b);
   const uint32_t ua = __builtin_bit_cast(uint32_t, a), ub = __builtin_bit_cast(uint32_t, b);
   h = __builtin_amdgcn_perm(ub, ua, 0x07060302);
   const float ra = a - __builtin_bit_cast(float, ua & 0xffff0000u), rb = b - __builtin_bit_cast(float, ub & 0xffff0000u);

@@ -161,3 +161,35 @@ def test_f32_backward_of_split_values(shape):
     assert bool((dv[:, :last, 5] == float("inf")).all())
     others = [c for c in range(d) if c != 5]
     assert torch.equal(dv[..., others], got[2][..., others])
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 200, 256, 64, False), (2, 1, 130, 130, 64, True), (32, 8, 300, 301, 128, False), (8, 8, 2048, 64, 128, False)],
+                         ids=lambda s: "-".join(map(str, s)))
+def test_f32_backward_of_nan_and_small_values(shape):
+    """A NaN stays one whatever its payload, in the operand's rows and columns that it touches and in no other.  dO of 2^-112: of a value
+    what lies below 2^-133 is lost, an error of 2^-134 / sqrt(3) each: 2^-22 of dO, and so of dv, 2^-14 at most of P (dP - D), which
+    is smaller by P, of the order of 1 / s_k (2^-8)."""
+    h_q, h_kv, s_q, s_k, d, causal = shape
+    x = [t.to(dev()) for t in case(4500 + s_q + s_k, h_q, h_kv, s_q, s_k, d, torch.float32)]
+    q, k, v, do = x
+    lse, delta = np.log(s_k) + 0.5 * (q * q).mean(-1), 0.1 * do[..., 0]
+    got = _f32_backward(q, k, v, do, lse, delta, causal)
+    assert all(bool(g.isfinite().all()) for g in got)
+    row, g = s_q // 2, h_q // h_kv
+    last = row + 1 if causal else s_k                     # keys that the row sees
+    for payload in (0x7f800001, 0x7fc00000, -1):          # signalling with the payload in the lower half, quiet
+        bad = do.clone()
+        bad.view(torch.int32)[0, row, 5] = payload
+        dq, dk, dv = _f32_backward(q, k, v, bad, lse, delta, causal)
+        assert bool(dv[0, :last, 5].isnan().all()) and bool(dq[0, row].isnan().all()) and bool(dk[0, :last].isnan().all())
+        assert torch.equal(dv[0, :, 6:], got[2][0, :, 6:]) and torch.equal(dq[0, :row], got[0][0, :row])
+        assert all(torch.equal(a[1:], b[1:]) for a, b in zip((dk, dv), got[1:])) and torch.equal(dq[1:], got[0][1:])
+        bad = k.clone()
+        bad.view(torch.int32)[h_kv - 1, 0, 3] = payload
+        dq, dk, dv = _f32_backward(q, bad, v, do, lse, delta, causal)
+        assert bool(dq[-g:].isnan().all()) and bool(dk[-1, 0].isnan().all()) and bool(dv[-1, 0].isnan().all())
+        assert torch.equal(dk[-1, 1:], got[1][-1, 1:]) and torch.equal(dv[-1, 1:], got[2][-1, 1:])
+    small = 2.0 ** -112
+    tiny = _f32_backward(q, k, v, do * small, lse, delta * small, causal)
+    for a, b, bound in zip(tiny, got, (2 ** -14, 2 ** -14, 2 ** -20)):
+        assert (a.double() / small - b.double()).norm().item() <= bound * b.double().norm().item()
