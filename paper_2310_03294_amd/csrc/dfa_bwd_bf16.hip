@@ -972,6 +972,7 @@ Plan best_of(const Call& c, bool dq, int most_q) {
   Plan best{};
   for (int q_parts : Q_PARTS) {
     if (q_parts > most_q || !feasible(c, 1, q_parts)) break;
+    double low = 1e30;
     for (int parts : PARTS) {
       if (!feasible(c, parts, q_parts)) break;
       double least = 1e30;
@@ -981,7 +982,8 @@ Plan best_of(const Call& c, bool dq, int most_q) {
         if (!best.parts || x.us < best.us) best = x;
         least = std::min(least, x.us);
       }
-      if (least > 1.5 * best.us) break;      // (nor with more)
+      low = std::min(low, least);
+      if (least > 1.5 * low) break;      // (nor with more)
     }
   }
   return best;

@@ -99,6 +99,18 @@ def test_divisions_of_short_backward_calls():
         assert lib.dfa_chunk_bwd_form(ctypes.byref(sh), 1, 1, 1, 0, ctypes.byref(form)) == 0 and form.cuts == 1
 
 
+def test_divisions_of_short_walks_by_both_kinds_parts():
+    """(workgroups per key tile, per row tile of dq) where the first division of dk, dv with dq's in parts is far from the best one.  us,
+    in the division that a search cut off there found / so: 4 heads over 1 x 1571 rows x 4713 keys 89.0 / 61.5, 4 over 1 x 1645 x 3290
+    67.5 / 55.0, 32 over 1 x 84 x 2941 58.5 / 37.3."""
+    lib, form = dfa.load_library(), B.DfaForm()
+    for shape, want in (((4, 1, 1571, 4713), (4, 2)), ((4, 1, 1645, 3290), (4, 2)), ((32, 1, 84, 2941), (6, 3))):
+        h_q, h_kv, s_q, s_k = shape
+        sh = B.DfaShape(h_q=h_q, h_kv=h_kv, s_q=s_q, s_k=s_k, d=128, dtype=B.DFA_BF16, scale=1.0)
+        assert lib.dfa_chunk_bwd_form(ctypes.byref(sh), 1, 1, 1, 128 << 20, ctypes.byref(form)) == 0
+        assert (form.cuts, form.q_cuts) == want, shape
+
+
 def test_forms_of_dq_alone():
     """256 rows where they are the faster ones: long walks and whole rounds of the device; a list of 16 pairs of 32 heads x 128 rows takes
     1.7 times as long with them, 32 heads x 5000 rows 1.1, x 2048 keys 1.05."""
