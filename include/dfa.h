@@ -298,7 +298,7 @@ int dfa_schedule_mode(int32_t mode, int32_t P, int32_t worker_id, dfa_step* out,
 int dfa_schedule_window(int32_t P, int32_t worker_id, int32_t window_chunks, dfa_step* out, int32_t cap);
 
 /* Measurement aid (no part of the method): launches a register-resident stream of bf16
- * 32x32x16 MFMAs on every SIMD of the device (512 workgroups of 256 lanes, 4 * iters MFMAs per
+ * 16x16x32 MFMAs on every SIMD of the device (512 workgroups of 256 lanes, 8 * iters MFMAs per
  * wavefront, no memory traffic in the loop) on `stream`.  Timed by the caller, *flop / time is
  * the matrix throughput the device sustains at its clock under load, the on-box ceiling quoted
  * next to the published peak.  `out`: DEVICE buffer of n_out >= 131072 floats, overwritten with
@@ -309,7 +309,7 @@ int dfa_mfma_probe(float* out, int64_t n_out, int32_t iters, double* flop, void*
 /* Measurement aid (no part of the method): the same register-resident MFMA stream fed with operand
  * VALUES of the caller's choosing.  Every wavefront loads eight A and eight B operands from
  * `operands` (DEVICE, bf16 values, 16-byte aligned, operand_bytes >= 1 MiB; a power-of-two prefix of
- * it is used) and rotates through them, 8 * iters MFMAs per wavefront.  The device keeps its power
+ * it is used) and rotates through them, 16 * iters MFMAs per wavefront.  The device keeps its power
  * limit by lowering the clock, and how much power an MFMA draws depends on how many operand bits
  * toggle: with i.i.d. N(0,1) operands (the workload's values) the sustained rate is what the
  * attention kernels can at best reach, well below what the plain probe's near-constant operands

@@ -1,6 +1,6 @@
 // Measurement aid for the MFMA roofline: a register-resident stream of
-// v_mfma_f32_32x32x16_bf16 on every SIMD of the device (2 wavefronts per SIMD, four independent
-// accumulator tiles each, no memory traffic inside the loop).  Timed by the caller, it gives what
+// v_mfma_f32_16x16x32_bf16, the product of the kernels that dominate a share, on every SIMD of the device (2 wavefronts per
+// SIMD, eight independent accumulator tiles each, no memory traffic inside the loop).  Timed by the caller, it gives what
 // the matrix pipes deliver at the clock the device sustains under this load, which sits below the
 // published peak (that one assumes the maximum clock).
 #include <hip/hip_runtime.h>
@@ -20,14 +20,15 @@ __global__ void __launch_bounds__(PROBE_BLOCK, 2) k_mfma_probe(float* out, int i
     a[i] = static_cast<__bf16>(1.0f / 1024.0f * static_cast<float>((lane + i) & 7));
     b[i] = static_cast<__bf16>(1.0f / 1024.0f * static_cast<float>((lane * 3 + i) & 7));
   }
-  f32x16 c0 = {}, c1 = {}, c2 = {}, c3 = {};
+  f32x4 c[8] = {};
   for (int it = 0; it < iters; ++it) {
-    c0 = mfma32(a, b, c0);
-    c1 = mfma32(a, b, c1);
-    c2 = mfma32(a, b, c2);
-    c3 = mfma32(a, b, c3);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) c[i] = mfma16(a, b, c[i]);
   }
-  out[blockIdx.x * PROBE_BLOCK + threadIdx.x] = c0[0] + c1[5] + c2[10] + c3[15];
+  float x = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) x += c[i][i & 3];
+  out[blockIdx.x * PROBE_BLOCK + threadIdx.x] = x;
 }
 
 // The same stream fed with caller-supplied operand values: every wavefront loads eight A and eight B
@@ -44,21 +45,22 @@ __global__ void __launch_bounds__(PROBE_BLOCK, 2) k_mfma_probe_data(const uint4*
     a[i] = __builtin_bit_cast(bf16x8, ops[(t + i * 4099u) & mask]);
     b[i] = __builtin_bit_cast(bf16x8, ops[(t + i * 4099u + 31337u) & mask]);
   }
-  f32x16 c0 = {}, c1 = {}, c2 = {}, c3 = {};
+  f32x4 c[8] = {};
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
-    for (int i = 0; i < 8; i += 4) {
-      c0 = mfma32(a[i], b[i], c0);
-      c1 = mfma32(a[i + 1], b[i + 1], c1);
-      c2 = mfma32(a[i + 2], b[i + 2], c2);
-      c3 = mfma32(a[i + 3], b[i + 3], c3);
+    for (int i = 0; i < 8; ++i) {      // one A operand for two of B, as the kernels have it
+      c[i] = mfma16(a[i], b[i], c[i]);
+      c[(i + 4) & 7] = mfma16(a[i], b[(i + 1) & 7], c[(i + 4) & 7]);
     }
     if ((it & 255) == 255) {      // keep the accumulators in range, whatever the operands are
 #pragma unroll
-      for (int j = 0; j < 16; ++j) { c0[j] *= 0.001f; c1[j] *= 0.001f; c2[j] *= 0.001f; c3[j] *= 0.001f; }
+      for (int i = 0; i < 8; ++i) c[i] *= 0.001f;
     }
   }
-  out[t] = c0[0] + c1[5] + c2[10] + c3[15];
+  float x = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) x += c[i][i & 3];
+  out[t] = x;
 }
 }  // namespace
 }  // namespace dfa
@@ -71,7 +73,7 @@ extern "C" int dfa_mfma_probe(float* out, int64_t n_out, int32_t iters, double* 
   k_mfma_probe<<<PROBE_GRID, PROBE_BLOCK, 0, st>>>(out, iters);
   if (hipGetLastError() != hipSuccess) return DFA_ERR_HIP;
   if (flop != nullptr)
-    *flop = 2.0 * 32 * 32 * 16 * 4.0 * iters * (PROBE_GRID * (PROBE_BLOCK / 64));   // 4 MFMAs per iteration and wavefront
+    *flop = 2.0 * 16 * 16 * 32 * 8.0 * iters * (PROBE_GRID * (PROBE_BLOCK / 64));   // 8 MFMAs per iteration and wavefront
   return DFA_OK;
 }
 
@@ -90,6 +92,6 @@ extern "C" int dfa_mfma_probe_data(const void* operands, int64_t operand_bytes, 
                                                         static_cast<uint32_t>(pieces - 1), out, iters);
   if (hipGetLastError() != hipSuccess) return DFA_ERR_HIP;
   if (flop != nullptr)
-    *flop = 2.0 * 32 * 32 * 16 * 8.0 * iters * (PROBE_GRID * (PROBE_BLOCK / 64));   // 8 MFMAs per iteration and wavefront
+    *flop = 2.0 * 16 * 16 * 32 * 16.0 * iters * (PROBE_GRID * (PROBE_BLOCK / 64));   // 16 MFMAs per iteration and wavefront
   return DFA_OK;
 }
