@@ -35,6 +35,7 @@
 
 #include "dfa_internal.h"
 #include "dfa_mfma.h"
+#include "dfa_place.h"
 #include "dfa_span.h"
 
 namespace dfa {
@@ -315,14 +316,6 @@ template <int D, bool SPLIT>
 __device__ __forceinline__ f32x4 run_of(const f32x16 (&c)[D / 32], int k) {
   if constexpr (SPLIT) return f32x4{c[k >> 2][4 * (k & 3)], c[k >> 2][4 * (k & 3) + 1], c[k >> 2][4 * (k & 3) + 2], c[k >> 2][4 * (k & 3) + 3]};
   else return f32x4{c[0][k], c[1][k], c[2][k], c[3][k]};
-}
-template <int D, bool SPLIT>
-__device__ __forceinline__ void set_run(f32x16 (&c)[D / 32], int k, f32x4 x) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    if constexpr (SPLIT) c[k >> 2][4 * (k & 3) + e] = x[e];
-    else c[e][k] = x[e];
-  }
 }
 template <bool SPLIT> __device__ __forceinline__ int run_col(int k, int hh) {
   return SPLIT ? (k >> 2) * 32 + (k & 3) * 8 + 4 * hh : 4 * ((k >> 2) * 8 + 4 * hh + (k & 3));
@@ -1064,97 +1057,83 @@ int bwd(F32BwdParams p, hipStream_t st) {
 }
 
 // How a backward is divided: parts of every tile inside a workgroup, and workgroups that share the query tiles of
-// a block of key rows.  A dk/dv workgroup walks over all query heads of its group, so with grouped heads a few
-// workgroups would run long after the others; sharing the walk sends their sums (2 D floats per key row)
-// through memory and a second launch.  The estimate, with what one box measured for its terms at d = 128: 6 us
-// per workgroup and, with 1 / 2 / 4 parts, 9.3 / 10.3 / 12.2 us per query tile (dk, dv) and 7 / 7.7 / 9.7 per
-// key tile (dq); calls of one round take their longest workgroup, longer ones the device's even share and about
-// half a workgroup.  us per full pair (dk, dv and dq), d = 128, with 1 / 2 / 4 parts and nothing shared:
-//   8 / 2 heads x 1024 rows 1183 / 647 / 371,  32 x 256 87 / 57 / 72,  32 x 1024 547 / 604 / 725,
-//   32 x 4096 8370 / 9210 / 11380 (82 TFLOP/s with 1);  shared, 8 / 2 x 1024 178, x 2048 1310 -> 623, four
-//   diagonal chunks of 1024 1220 -> 443.
-// (Timed with fp32 products, as were the walks above; the terms' ratios are what decides, and split products shorten the 1- and
-// the 2-part form alike.)
-// At d = 128 the 4-part form with a shared walk spills 23 registers and takes longer than estimated (8 / 2 x 256 44 us
-// for 35).  Where it is chosen it is the better form all the same: 4 against 2 parts 44 / 45 there, 8 / 2 x 512 diagonal
-// 57 / 65, 8 x 512 diagonal 56 / 66, 4 / 1 x 768 75 / 109, x 1024 129 / 141; without scratch 8 / 2 x 1024 diagonal 375 / 649, one head
-// x 1024 99 / 171.
-// The vector-FMA kernel this one replaced (dq by atomics) took 2.9 ms at 8 / 2 x 1024.
-// dq by several workgroups per row block: a few query rows against many keys, where a row block's walk over all of them would be
-// the whole call (us with one walk / shared, d = 128; dq by atomics took the third): 1 head x 32 x 16384 1278 / 76 / 47,
-// x 256 x 32768 2615 / 195 / 430, 8 x 64 x 16384 1573 / 260 / 525, 2 over 1 x 47 x 2011 161 / 34 / 103.  From eight keys per row
-// on: below, the row blocks are enough (4 heads x 500 x 1000 88, and 393 with atomics), but for diagonal chunks of few heads, whose
-// last row blocks have the whole chunk to walk over (one head x 1024 86 / 47, d = 64 47 / 28; 4 / 1 x 1536 202 / 136).
+// a block of key rows or the keys of a row block of dq.  A dk/dv workgroup walks over all query heads of its group, so with grouped
+// heads a few workgroups would run long after the others, and the walk of a row block of dq over many keys, or of a diagonal's last
+// rows, may be the whole call; sharing a walk sends its sums (2 D floats per key row, D per query row) through memory and a further
+// launch.  The estimate places the workgroups (dfa_place.h), with constants fitted to 322 calls at d = 128 and 253 at d = 64 (pairs,
+// diagonals, sequences, spans, few rows against many keys), every division timed: chosen / best 1.010 and 1.013 in the mean; of 130
+// other calls 1.031 (an estimate by even shares, fitted to fp32 products in every form: 1.087, 1.041 and 1.077).  The 4-part form, on
+// fp32 products at d = 128, is the best one there of calls that are short and whose walks cannot be shared: without scratch 8 heads x
+// 512 diagonal 60.7 us, 71.5 with 2 parts.  us, as the even shares chose / so: 8 heads x 512 diagonal 60.7 / 51.1, 4 x 1024 104.7 / 64.2,
+// 4 x 1536 198.6 / 108.7, 32 over 8 x 333 107.5 / 68.5, 8 over 2 x 768 95.2 / 75.7, x 2048 at d = 64 182 / 163, full pair
+// of 32 over 8 x 1024 459 / 389.
 struct Plan { int parts, shares, q_shares; double us; int64_t bytes; };
 
-// A causal call's (head, share) groups go to the XCDs in ranges, longest row blocks first: with a part of a group left over, an
-// XCD that gets its first blocks has so much more than an even share.
-double uneven(int64_t groups) {
-  const double g = groups / 8., whole = static_cast<double>(groups / 8), rest = g - whole;
-  return groups <= 2 ? 1.0 : (whole + rest * (2 - rest)) / g;
-}
+// us: of a workgroup, of a tile of the walks of dk, dv and of dq, with 1, 2 and 4 parts (slower by `slow` with 256 workgroups and
+// more); `tail` and `late` of dfa_place.h; of the sums' launches, per share, and their GB/ms.
+struct Terms { double start[3], kv[3], q[3], slow, tail, late, sums, per_share, per_q_share, rate; };
+constexpr Terms D128{{11.77, 11.49, 10.2}, {6.5, 7.38, 11.71}, {4.37, 5.32, 9.71}, 0.01, 0.36, 0.24, 1.54, 0.16, 0.17, 8.21};
+constexpr Terms D64{{6.63, 6.61, 6.08}, {3.53, 4.24, 5.58}, {2.87, 3.11, 3.98}, 0, 0.16, 0.35, 3.92, 0.04, 0.04, 10.26};
 
 // A call with `parts` parts of every tile, undivided: what the divisions of a plan have in common.
 struct Undivided {
-  int parts, group, h_q, h_kv;
-  int64_t n_kv, n_q, q_tiles, bytes;      // workgroups of dk, dv and of dq; key tiles; a dk/dv workgroup's sums (dq: half)
-  double walk_kv, walk_q, mean;           // mean: of a walk, the query chunk's own keys are half visible
+  int parts, form, d, group, causal;
+  int64_t kv_heads, q_heads;              // of all pairs
+  int64_t n_kv, n_q, q_blocks, q_tiles, bytes;      // workgroups of dk, dv and of dq (and per head); key tiles; a dk/dv workgroup's sums (dq: half)
+  double walk_kv, walk_q, mean;           // tiles; mean: of a walk, the query chunk's own keys are half visible
   int64_t ws_bytes;
 };
 Undivided undivided(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes, int parts) {
   const int rows = 128 / parts, tile = 32 * parts, group = sh.h_q / sh.h_kv;
-  const double width = sh.d == 128 ? 1.0 : 0.55;
   const int64_t q_tiles = blocks_of(sh.s_k, tile);
-  return {parts, group, sh.h_q, sh.h_kv, dk ? blocks_of(sh.s_k, rows) * sh.h_kv * pairs : 0, dq ? blocks_of(sh.s_q, rows) * sh.h_q * pairs : 0,
-          q_tiles, static_cast<int64_t>(rows) * 2 * sh.d * 4,
-          width * (parts == 1 ? 9.3 : parts == 2 ? 10.3 : 12.2) * group * blocks_of(sh.s_q, tile),
-          width * (parts == 1 ? 7.0 : parts == 2 ? 7.7 : 9.7) * q_tiles, sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0, ws_bytes};
+  return {parts, parts / 2, sh.d, group, sh.causal, static_cast<int64_t>(sh.h_kv) * pairs, static_cast<int64_t>(sh.h_q) * pairs,
+          dk ? blocks_of(sh.s_k, rows) * sh.h_kv * pairs : 0, dq ? blocks_of(sh.s_q, rows) * sh.h_q * pairs : 0, blocks_of(sh.s_q, rows),
+          q_tiles, static_cast<int64_t>(rows) * 2 * sh.d * 4, static_cast<double>(group * blocks_of(sh.s_q, tile)), static_cast<double>(q_tiles),
+          sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0, ws_bytes};
 }
 int64_t sums_of(const Undivided& c, int shares, int q_shares) {
   return (shares > 1 ? c.n_kv * shares * c.bytes : 0) + (q_shares > 1 ? c.n_q * q_shares * (c.bytes / 2) : 0);
 }
-// diagonal: a causal call of all gradients, of which dq's workgroups come after those of dk, dv, the longest of them first.
-double estimate(const Undivided& c, int shares, int q_shares, bool diagonal) {
-  const int64_t n_kv = c.n_kv * shares, n_q = c.n_q * q_shares, sums = sums_of(c, shares, q_shares);
-  const double w_kv = c.walk_kv / shares, w_q = c.walk_q / q_shares, t_kv = n_kv ? 6 + w_kv : 0., t_q = n_q ? 6 + w_q : 0.;
-  double us = std::max(t_kv, t_q);
-  if (n_kv + n_q > 256) {
-    const double even_kv = n_kv * (6 + w_kv * c.mean) / 256, even_q = n_q * (6 + w_q * c.mean) / 256;
-    us = std::max(us, diagonal ? even_kv * uneven(c.h_kv * shares) + std::max(t_q, even_q * uneven(c.h_q * q_shares) + 0.3 * t_q)
-                               : even_kv + even_q + 0.45 * us);
-  }
-  return sums > 0 ? (us + 4 * ((shares > 1) + (q_shares > 1)) + 2 * sums / 2.5e6) / 0.92 : us;
+double estimate(const Undivided& c, int shares, int q_shares) {
+  const Terms& k = c.d == 128 ? D128 : D64;
+  const int64_t n_kv = c.n_kv * shares, n_q = c.n_q * q_shares;
+  const double slow = 1 + k.slow * std::min(1., std::max(0., 2. * (n_kv + n_q) / (XCDS * CUS) - 1));
+  const double start = k.start[c.form], w_kv = k.kv[c.form] * slow * c.walk_kv / shares, w_q = k.q[c.form] * slow * c.walk_q / q_shares;
+  const Kind kv{(n_kv + XCDS - 1) / XCDS, start + w_kv, (start + w_kv * c.mean) * (c.causal ? uneven(c.kv_heads * shares) : 1.0), 0};
+  const Kind q{(n_q + XCDS - 1) / XCDS, start + w_q, (start + w_q * c.mean) * (c.causal ? uneven(c.q_heads * q_shares) : 1.0), c.q_blocks};
+  double us = makespan(kv, q, c.causal, start + 2 * k.kv[c.form], k.tail, k.late);
+  if (shares > 1 || q_shares > 1) us += 2 * sums_of(c, shares, q_shares) / (k.rate * 1e6);
+  if (shares > 1) us += k.sums + k.per_share * shares;
+  if (q_shares > 1) us += k.sums + k.per_q_share * q_shares;
+  return us;
 }
-Plan best_of(const Undivided* calls, int n, int most_q, bool diagonal) {
+Plan best_of(const Undivided* calls, int n, int most_q) {
   Plan best{0, 0, 0, 0., 0};
   for (const Undivided* c = calls; c < calls + n; ++c)
     for (int q_shares = 1; q_shares <= most_q; q_shares *= 2) {
       if (q_shares > 1 && (c->n_q * q_shares > 1024 || q_shares > c->q_tiles)) break;
+      double low = 1e30;
       for (int shares : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
         if (shares > 1 && (!c->n_kv || shares > 4 * c->group || c->n_kv * shares > 1024)) break;
         const int64_t sums = sums_of(*c, shares, q_shares);
         if (sums > c->ws_bytes) break;
-        const double us = estimate(*c, shares, q_shares, diagonal);
+        const double us = estimate(*c, shares, q_shares);
         if (!best.parts || us < best.us) best = {c->parts, shares, q_shares, us, sums};
+        low = std::min(low, us);
+        if (us > 1.5 * low) break;      // (nor with more)
       }
     }
   return best;
 }
 
-// sequence: a causal call that stands for the pairs of several chunks; dk, dv as sums (no 4 parts at d = 128).
+// sequence: a causal call that stands for the pairs of several chunks; dk, dv as sums (no 4 parts at d = 128).  dq's walks may be shared
+// with a few rows against many keys, and of a causal call of all gradients.
 Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes, bool sequence) {
   ws_bytes = std::min(ws_bytes, int64_t{128} << 20);
   const Undivided calls[] = {undivided(sh, pairs, dq, dk, ws_bytes, 1), undivided(sh, pairs, dq, dk, ws_bytes, 2),
                              undivided(sh, pairs, dq, dk, ws_bytes, 4)};
-  const bool few = dq && sh.s_k / 8 >= sh.s_q, diagonal = sh.causal && dq && dk && pairs == 1 && !few;
-  if (sequence) return best_of(calls, sh.d == 128 ? 2 : 3, diagonal ? 8 : few ? 64 : 1, diagonal);
-  if (diagonal && sh.s_k > sh.s_q) return best_of(calls, 3, 8, true);
-  const Plan best = best_of(calls, 3, few ? 64 : 1, false);
-  if (!diagonal) return best;
-  // A diagonal pair shares dq's walk only where the gain is beyond what the estimate errs (0.78 of it: 8 over 2 heads x 2048 412 ->
-  // 425 us); a span takes the best (32 over 8 heads, 5 x 512 918 -> 771, one by one 825).
-  const Plan shared = best_of(calls, 3, 8, true);
-  return shared.us < 0.77 * estimate(calls[best.parts / 2], best.shares, 1, true) ? shared : best;
+  const bool few = dq && sh.s_k / 8 >= sh.s_q, diagonal = sh.causal && dq && dk && pairs == 1;
+  return best_of(calls, sequence && sh.d == 128 ? 2 : 3, few ? 64 : diagonal ? 8 : 1);
 }
 
 }  // namespace

@@ -29,12 +29,12 @@
 // which caps a 128-key workgroup tile at ~400 TFLOP/s no matter how the rest is scheduled.
 // Recomputing S and dP in a second kernel costs 7 products instead of 5 but has no such cap.
 #include <algorithm>
-#include <cmath>
 #include <mutex>
 #include <type_traits>
 
 #include "dfa_internal.h"
 #include "dfa_mfma.h"
+#include "dfa_place.h"
 
 namespace dfa {
 namespace {
@@ -887,33 +887,6 @@ struct Call {
   int64_t ws_bytes;
   bool longest_first;           // (else the kind of which there are fewer per head)
 };
-constexpr int XCDS = 8, CUS = 32;      // CUs of an XCD
-
-// When na workgroups of `a` us and then nb of `b` are done on an XCD.
-double placed(int64_t na, double a, int64_t nb, double b) {
-  const int64_t late = na % CUS, early = CUS - late;                 // CUs that are free at t1, at t2
-  const double t1 = static_cast<double>(na / CUS) * a, t2 = late ? t1 + a : t1;
-  if (!nb) return t2;
-  double least = t1 + nb * b / early;
-  if (least > t2) least = (nb * b + early * t1 + late * t2) / CUS;
-  double end = 1e30;
-  for (double t0 : {t1, t2}) {         // a workgroup of the second kind ends last, on a CU of either sort
-    double n = std::max(1., std::ceil((least - t0) / b - 1e-9));
-    for (int k = 0; k < 3; ++k, ++n) {
-      const double t = t0 + n * b;
-      const int64_t done = early * static_cast<int64_t>((t - t1) / b + 1e-9) + (t > t2 ? late * static_cast<int64_t>((t - t2) / b + 1e-9) : 0);
-      if (done >= nb) { end = std::min(end, t); break; }
-    }
-  }
-  return std::max(t2, end);
-}
-
-// A causal call's (head, part) groups go to the XCDs in ranges, longest tiles first: with a part of a group left over, an XCD that
-// gets its first tiles has so much more than an even share.
-double uneven(int64_t groups) {
-  const double g = static_cast<double>(groups) / XCDS, whole = static_cast<double>(groups / XCDS), rest = g - whole;
-  return groups <= 2 ? 1.0 : (whole + rest * (2 - rest)) / g;
-}
 
 bool feasible(const Call& c, int parts, int q_parts) {
   return (parts == 1 || (c.kv1 && parts <= 4 * c.group && c.kv1 * parts <= 1024)) && (q_parts == 1 || c.n128 * q_parts <= 1024) &&
@@ -940,26 +913,11 @@ Plan estimate(const Call& c, int parts, int q_parts, bool split) {
   const double tile_q = (split ? k.tile_split * (1 + k.many * std::min(1., std::max(0., (rounds - 1) / 3))) : k.tile_wide) * slow;
   const double w_kv = tile_kv * c.q_tiles / parts, w_q = tile_q * c.k_tiles / q_parts;
   x.q_first = c.longest_first ? f_q + w_q > f_kv + w_kv : c.group <= parts;
-  struct Kind { int64_t n; double longest, mean; int64_t per_head; };
   const Kind kv{(n_kv + XCDS - 1) / XCDS, f_kv + w_kv, (f_kv + w_kv * c.mean) * (c.causal ? uneven(static_cast<int64_t>(c.kv_heads) * parts) : 1.0),
                 blocks_of(c.s_k, kv::BN)};
   const Kind q{(n_q + XCDS - 1) / XCDS, f_q + w_q, (f_q + w_q * c.mean) * (c.causal ? uneven(static_cast<int64_t>(c.q_heads) * q_parts) : 1.0),
                blocks_of(c.s_q, split ? 128 : 256)};
-  const Kind &a = x.q_first ? q : kv, &b = x.q_first ? kv : q;
-  if (!c.causal) {
-    x.us = placed(a.n, a.longest, b.n, b.longest);
-  } else {
-    // Workgroups of all lengths: the even share and some of the shorter kind's longest, but the last head's longest workgroup may
-    // begin late.
-    x.us = std::max(a.n ? a.longest : 0., b.n ? b.longest : 0.);
-    if (a.n + b.n > CUS) {
-      const int64_t before = std::max<int64_t>(0, b.n - b.per_head);      // of the second kind, before the last head's
-      const double share = (a.n * a.mean + b.n * b.mean) / CUS;
-      const double begin = a.n + before < CUS ? 0.
-                           : std::max(f_kv + 2 * k.tile_kv, (a.n * a.mean + before * b.mean) / CUS - k.late * (before < CUS ? a : b).mean);
-      x.us = std::max(x.us, std::max(begin + (b.n ? b.longest : 0.), share + k.tail * std::min(a.longest, b.longest)));
-    }
-  }
+  x.us = makespan(x.q_first ? q : kv, x.q_first ? kv : q, c.causal, f_kv + 2 * k.tile_kv, k.tail, k.late);
   if (parts > 1 || q_parts > 1) x.us /= k.gain;
   if (parts > 1) x.us += k.sums_kv + k.part_kv * parts + 2 * kv_bytes / (k.rate * 1e6);
   if (q_parts > 1) x.us += k.sums_q + k.part_q * q_parts + 2 * q_bytes / (k.rate * 1e6);

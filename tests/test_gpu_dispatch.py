@@ -16,14 +16,14 @@ from test_gpu_parity_small import _run_pair
 pytestmark = pytest.mark.gpu
 
 # fp32: 1, 2 or 4 parts per tile, chosen by the number of workgroups.  The comment gives the parts of the
-# (forward, backward).
+# (forward, backward at d = 128).
 F32_PARTS = [
     (130, 130, 150, 150, False),   # (2, 1)
     (260, 130, 150, 77, False),    # (1, 1), grouped heads
-    (40, 20, 130, 161, False),     # (4, 4), grouped heads
+    (40, 20, 130, 161, False),     # (4, 2), grouped heads
     (40, 40, 130, 161, False),     # (4, 2)
-    (520, 520, 130, 130, True),    # (2, 2): causal, 64-row blocks
-    (130, 65, 33, 33, True),       # (2, 4): one row past a block
+    (520, 520, 130, 130, True),    # (2, 1): causal, 64-row blocks of the forward
+    (130, 65, 33, 33, True),       # (2, 2): one row past a block of the forward
 ]
 
 
@@ -449,6 +449,48 @@ def test_f32_backward_shares(shape, d):
                               accumulate=acc)
             for i in (0, 1, 2) if want_dq else (1, 2):
                 assert maxerr(got[i], want[i] + (0.5 if acc else 0.0)) <= bound[i]
+
+
+# fp32 backward at d = 128: parts of a tile, shares of the walks of dk, dv and of dq
+F32_BWD_FORMS = [
+    (4, 1, 97, 97, True, (4, 6, 1)),
+    (8, 2, 200, 200, True, (4, 8, 2)),
+    (1, 1, 70, 145, False, (2, 1, 1)),
+    (1, 1, 300, 300, False, (2, 2, 1)),
+    (2, 1, 130, 130, True, None),
+    (1, 1, 161, 161, True, (2, 3, 2)),
+    (16, 4, 333, 333, True, (1, 12, 2)),
+    (32, 8, 300, 300, True, (1, 6, 1)),
+    (8, 2, 161, 327, False, None),
+]
+
+
+@pytest.mark.parametrize("h_q,h_kv,s_q,s_k,causal,form", F32_BWD_FORMS)
+def test_f32_backward_forms(h_q, h_kv, s_q, s_k, causal, form):
+    """Against the oracle, with all scratch and with none (1, 2 and 4 parts undivided), overwriting and adding."""
+    d, lib = 128, B.load_library()
+    scale = d ** -0.5
+    x = case(9950 + s_q + s_k, h_q, h_kv, s_q, s_k, d, torch.float32)
+    x64 = [np64(t) for t in x]
+    O, L = A.attention_fwd(*x64[:3], scale, causal=causal)
+    want = A.attention_bwd(*x64, scale, causal=causal)
+    q, k, v, do = (t.to(dev()) for t in x)
+    lse, delta = torch.from_numpy(L).float().to(dev()), torch.from_numpy(A.delta_rows(O, x64[3])).float().to(dev())
+    sh = B._make_shape(q, k, causal, scale, B.DFA_F32, lse=lse, dq=q, dkv=k)
+    got_form = B.DfaForm()
+    assert lib.dfa_chunk_bwd_form(ctypes.byref(sh), 1, 1, 1, 128 << 20, ctypes.byref(got_form)) == 0
+    assert form is None or (got_form.parts, got_form.cuts, got_form.q_cuts) == form
+    n = lib.dfa_chunk_bwd_workspace(ctypes.byref(sh), 1, 1, 1)
+    stream = torch.cuda.current_stream().cuda_stream
+    for n_bytes, acc in ((n, False), (n, True), (0, False), (0, True)):
+        ws = torch.full((n_bytes // 4 + 256,), 7.0, device=dev())
+        got = [torch.full(w.shape, 0.5, device=dev()) for w in want]
+        pair = B.DfaBwdPair(*(t.data_ptr() for t in (q, k, v, lse, delta, do, *got)), acc, acc)
+        assert lib.dfa_chunk_bwd_batch(ctypes.byref(sh), ctypes.byref(pair), 1, ws.data_ptr() if n_bytes else None, n_bytes, stream) == 0
+        assert bool((ws[n_bytes // 4:] == 7.0).all())
+        for g, w in zip(got, want):
+            bound = TOL[torch.float32] * max(1.0, abs(w).max())      # grows with the magnitude of the sums
+            assert maxerr(g, w + (0.5 if acc else 0.0)) <= bound
 
 
 # fp32 dq by several workgroups per row block, from eight keys per query row on: (heads, rows, keys, pairs)

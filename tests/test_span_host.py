@@ -125,7 +125,8 @@ def test_forms_of_dq_alone():
 
 
 def test_forms_of_the_f32_diagonal():
-    """Short diagonals of few heads are in the 4-part form, with scratch and above all without; sharing dq's walk only where it gains."""
+    """Short diagonals of few heads are in the 4-part form without scratch; with scratch the walks are shared where it gains (8 heads x 512
+    60.7 us in 4 parts, 51.1 in two, both walks shared; 8 over 2 x 2048 at d = 64 182 with 6 shares, 163 with 4)."""
     lib, form = dfa.load_library(), B.DfaForm()
 
     def of(h_q, h_kv, s, d, ws):
@@ -135,8 +136,9 @@ def test_forms_of_the_f32_diagonal():
 
     for shape in ((1, 1, 256, 128), (1, 1, 1024, 128), (8, 8, 128, 128), (8, 8, 512, 128), (8, 2, 512, 128), (8, 2, 1024, 128), (32, 8, 128, 128)):
         assert of(*shape, 0) == (4, 1, 1), shape
-    for shape, want in (((8, 8, 128, 128), (4, 1, 1)), ((8, 8, 512, 128), (4, 1, 1)), ((8, 2, 512, 128), (4, 6, 1)), ((32, 8, 128, 128), (4, 4, 1)),
-                        ((8, 2, 512, 64), (4, 6, 1)), ((8, 2, 2048, 64), (2, 6, 1)), ((1, 1, 1024, 128), (4, 4, 4)), ((1, 1, 1024, 64), (4, 4, 4))):
+    for shape, want in (((8, 8, 128, 128), (2, 3, 2)), ((8, 8, 512, 128), (2, 2, 2)), ((8, 2, 512, 128), (2, 8, 2)), ((32, 8, 128, 128), (4, 4, 1)),
+                        ((8, 2, 512, 64), (4, 6, 1)), ((8, 2, 2048, 64), (2, 4, 1)), ((4, 4, 1024, 128), (2, 3, 2)), ((4, 4, 1536, 128), (2, 2, 2)),
+                        ((32, 8, 333, 128), (1, 6, 1)), ((1, 1, 1024, 128), (4, 4, 4)), ((1, 1, 1024, 64), (4, 4, 4))):
         assert of(*shape, 128 << 20) == want, shape
     sh = B.DfaShape(h_q=8, h_kv=8, s_q=512, s_k=512, d=128, dtype=B.DFA_F32, scale=1.0, causal=1)      # a sequence: sums, no 4 parts
     assert lib.dfa_span_bwd_form(ctypes.byref(sh), 1, 1, 0, ctypes.byref(form)) == 0 and form.parts == 2
