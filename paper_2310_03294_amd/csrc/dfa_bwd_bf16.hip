@@ -813,19 +813,19 @@ __device__ __forceinline__ void run_dq(const BwdPairs<NP>& p, int bid, char* sme
 
 template <bool RAGGED, bool PARTS, int NP>
 __global__ void __launch_bounds__(kv::NT, 2) k_bwd_dkdv_bf16(BwdPairs<NP> p) {
-  extern __shared__ __align__(16) char smem[];
+  extern __shared__ __align__(128) char smem[];
   run_dkdv<RAGGED, PARTS, NP>(p, blockIdx.x, smem);
 }
 
 template <int NW, int NP>
 __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_bwd_dq_bf16(BwdPairs<NP> p) {
-  extern __shared__ __align__(16) char smem[];
+  extern __shared__ __align__(128) char smem[];
   run_dq<NW, 1, false, NP>(p, blockIdx.x, smem);
 }
 
 template <bool RAGGED, int NS, bool PARTS, int NP, bool Q_PARTS = false>
 __global__ void __launch_bounds__(kv::NT, 2) k_bwd_bf16(BwdPairs<NP> p) {
-  extern __shared__ __align__(16) char smem[];
+  extern __shared__ __align__(128) char smem[];
   const int n_kv = p.kv_items.map.per_xcd * 8, n_q = p.q_items.map.per_xcd * 8;
   const int bid = blockIdx.x;
   if (p.q_first ? bid >= n_q : bid < n_kv) run_dkdv<RAGGED, PARTS, NP>(p, p.q_first ? bid - n_q : bid, smem);

@@ -174,7 +174,7 @@ __device__ __forceinline__ void store_o(const f32x4 (&o)[8][RB], const FwdParams
 // over the fp32 weights (the same in the other forms of 128 and 256 rows).
 template <bool FULL, class Args>
 __global__ void __launch_bounds__(NTHREADS, 2) k_fwd_bf16(Args a) {
-  extern __shared__ __align__(16) char smem[];   // two (K tile, V tile) buffers
+  extern __shared__ __align__(128) char smem[];   // two (K tile, V tile) buffers
 
   const int bid = blockIdx.x;
   int item = xcd_item(a.map, bid);
@@ -444,7 +444,7 @@ constexpr int SMEM_BYTES = OFF_MV + 2 * 4 * 4;
 // has keys of the chunk's own; before them over the rounded weights, as for full pairs).
 template <bool RAGGED, bool CAUSAL, class Args>
 __global__ void __launch_bounds__(NT, 2) k_fwd_bf16(Args a) {
-  extern __shared__ __align__(16) char smem[];
+  extern __shared__ __align__(128) char smem[];
 
   const int bid = blockIdx.x;
   int item = xcd_item(a.map, bid);
@@ -891,7 +891,7 @@ __global__ void __launch_bounds__(RB * NS * 64, RB * NS == 4 ? 2 : 1) k_fwd_bf16
   constexpr int BMS = RB * 32;                 // query rows per workgroup
   constexpr bool LO = RB == 2;
   constexpr int SUB = kKeys<NS> / BN;          // 64-row sub-tiles of a K (or V) tile
-  extern __shared__ __align__(16) char smem[]; // two buffers of (SUB K sub-tiles, SUB V sub-tiles)
+  extern __shared__ __align__(128) char smem[]; // two buffers of (SUB K sub-tiles, SUB V sub-tiles)
 
   const int bid = blockIdx.x;
   int item = xcd_item(a.map, bid);

@@ -93,11 +93,6 @@ __device__ __forceinline__ bf16x4 lds_read_tr_at(uint32_t addr, int off) {
   s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((DFA_LDS s16x4*)(addr + off));
   return __builtin_bit_cast(bf16x4, v);
 }
-__device__ __forceinline__ bf16x8 lds_gather_at(uint32_t addr, int off) {
-  const bf16x4 lo = lds_read_tr_at(addr, off);
-  const bf16x4 hi = lds_read_tr_at(addr, off + 2 * kRowBytes);
-  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
 // Makes `addr` opaque to the compiler, so that it stays THE base register of the reads that
 // follow.  Left alone, the compiler may pick a base above them and spend one v_add per read on
 // the (negative, not encodable) differences.
