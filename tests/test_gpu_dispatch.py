@@ -77,7 +77,7 @@ def test_bf16_forward_forms(shape):
         assert maxerr(o, O) <= tol and maxerr(lse, L + math.log(2)) <= tol
 
 
-@pytest.mark.parametrize("h_q,s", [(8, 3300), (22, 6150), (22, 6144), (16, 4608), (16, 4610)])
+@pytest.mark.parametrize("h_q,s", [(8, 3300), (22, 6150), (22, 6144)])
 def test_bf16_forward_forms_long_causal(h_q, s):
     """64-row workgroups with 4 parts on a long diagonal chunk, 256-row workgroups (ragged and whole tiles)."""
     d, tol = 128, TOL[torch.bfloat16]

@@ -84,17 +84,6 @@ def test_divisions_of_the_backward():
         assert ask(*shape, 1) > 0, shape
 
 
-def test_forms_of_long_diagonals():
-    """256-row workgroups from 4608 rows on where every XCD has whole pairs of heads (16 heads x 6144 173 us with 128 rows, 156 with 256),
-    else from two rounds of workgroups and 6144 rows on (14 heads x 5376 164 / 185); whole tiles only."""
-    lib, form = dfa.load_library(), B.DfaForm()
-    for h, s, n, rows in ((16, 4608, 1, 256), (16, 4544, 1, 128), (16, 4610, 1, 128), (32, 5376, 1, 256), (8, 5120, 2, 256), (14, 5376, 1, 128),
-                          (24, 5120, 1, 128), (20, 6144, 1, 128), (22, 6144, 1, 256), (8, 8192, 1, 128), (32, 4096, 1, 128), (48, 6144, 1, 256)):
-        sh = B.DfaShape(h_q=h, h_kv=h, s_q=s, s_k=s, d=128, dtype=B.DFA_BF16, scale=1.0, causal=1)
-        assert lib.dfa_chunk_fwd_form(ctypes.byref(sh), n, ctypes.byref(form)) == 0
-        assert form.rows == rows, (h, s, n)
-
-
 def test_divisions_of_short_backward_calls():
     """(rows of dq's workgroups, workgroups per key tile) where the wrong ones cost 10 % and more.  us, with one, two or four per tile as
     an estimate by even shares chose / so: 32 over 8 heads x 640 diagonal 39.2 / 32.9, one head x 3000 72.8 / 61.6, 16 over 4 x 2304 182.6
