@@ -1061,19 +1061,19 @@ int bwd(F32BwdParams p, hipStream_t st) {
 // heads a few workgroups would run long after the others, and the walk of a row block of dq over many keys, or of a diagonal's last
 // rows, may be the whole call; sharing a walk sends its sums (2 D floats per key row, D per query row) through memory and a further
 // launch.  The estimate places the workgroups (dfa_place.h), with constants fitted to 322 calls at d = 128 and 253 at d = 64 (pairs,
-// diagonals, sequences, spans, few rows against many keys), every division timed: chosen / best 1.010 and 1.013 in the mean; of 130
-// other calls 1.031 (an estimate by even shares, fitted to fp32 products in every form: 1.087, 1.041 and 1.077).  The 4-part form, on
+// diagonals, sequences, spans, few rows against many keys), every division timed: chosen / best 1.010 and 1.013 in the mean; of 110
+// other calls 1.028 (an estimate by even shares, fitted to fp32 products in every form: 1.087, 1.041 and 1.067).  The 4-part form, on
 // fp32 products at d = 128, is the best one there of calls that are short and whose walks cannot be shared: without scratch 8 heads x
 // 512 diagonal 60.7 us, 71.5 with 2 parts.  us, as the even shares chose / so: 8 heads x 512 diagonal 60.7 / 51.1, 4 x 1024 104.7 / 64.2,
 // 4 x 1536 198.6 / 108.7, 32 over 8 x 333 107.5 / 68.5, 8 over 2 x 768 95.2 / 75.7, x 2048 at d = 64 182 / 163, full pair
 // of 32 over 8 x 1024 459 / 389.
 struct Plan { int parts, shares, q_shares; double us; int64_t bytes; };
 
-// us: of a workgroup, of a tile of the walks of dk, dv and of dq, with 1, 2 and 4 parts (slower by `slow` with 256 workgroups and
-// more); `tail` and `late` of dfa_place.h; of the sums' launches, per share, and their GB/ms.
-struct Terms { double start[3], kv[3], q[3], slow, tail, late, sums, per_share, per_q_share, rate; };
-constexpr Terms D128{{11.77, 11.49, 10.2}, {6.5, 7.38, 11.71}, {4.37, 5.32, 9.71}, 0.01, 0.36, 0.24, 1.54, 0.16, 0.17, 8.21};
-constexpr Terms D64{{6.63, 6.61, 6.08}, {3.53, 4.24, 5.58}, {2.87, 3.11, 3.98}, 0, 0.16, 0.35, 3.92, 0.04, 0.04, 10.26};
+// us: of a workgroup, of a tile of the walks of dk, dv and of dq, with 1, 2 and 4 parts; `tail` and `late` of dfa_place.h; of the
+// sums' launches, per share, and their GB/ms.
+struct Terms { double start[3], kv[3], q[3], tail, late, sums, per_share, per_q_share, rate; };
+constexpr Terms D128{{11.77, 11.49, 10.2}, {6.5, 7.38, 11.71}, {4.37, 5.32, 9.71}, 0.36, 0.24, 1.54, 0.16, 0.17, 8.21};
+constexpr Terms D64{{6.63, 6.61, 6.08}, {3.53, 4.24, 5.58}, {2.87, 3.11, 3.98}, 0.16, 0.35, 3.92, 0.04, 0.04, 10.26};
 
 // A call with `parts` parts of every tile, undivided: what the divisions of a plan have in common.
 struct Undivided {
@@ -1091,38 +1091,66 @@ Undivided undivided(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws
           q_tiles, static_cast<int64_t>(rows) * 2 * sh.d * 4, static_cast<double>(group * blocks_of(sh.s_q, tile)), static_cast<double>(q_tiles),
           sh.causal ? 1 - 0.5 * sh.s_q / sh.s_k : 1.0, ws_bytes};
 }
-int64_t sums_of(const Undivided& c, int shares, int q_shares) {
-  return (shares > 1 ? c.n_kv * shares * c.bytes : 0) + (q_shares > 1 ? c.n_q * q_shares * (c.bytes / 2) : 0);
-}
-double estimate(const Undivided& c, int shares, int q_shares) {
+// The walks of one kind of workgroup in `shares`: its workgroups, their sums' bytes and the us that these take.
+struct Shared { Kind kind; int shares; int64_t bytes; double us; };
+Shared shared(const Undivided& c, bool kv, int shares) {
   const Terms& k = c.d == 128 ? D128 : D64;
-  const int64_t n_kv = c.n_kv * shares, n_q = c.n_q * q_shares;
-  const double slow = 1 + k.slow * std::min(1., std::max(0., 2. * (n_kv + n_q) / (XCDS * CUS) - 1));
-  const double start = k.start[c.form], w_kv = k.kv[c.form] * slow * c.walk_kv / shares, w_q = k.q[c.form] * slow * c.walk_q / q_shares;
-  const Kind kv{(n_kv + XCDS - 1) / XCDS, start + w_kv, (start + w_kv * c.mean) * (c.causal ? uneven(c.kv_heads * shares) : 1.0), 0};
-  const Kind q{(n_q + XCDS - 1) / XCDS, start + w_q, (start + w_q * c.mean) * (c.causal ? uneven(c.q_heads * q_shares) : 1.0), c.q_blocks};
-  double us = makespan(kv, q, c.causal, start + 2 * k.kv[c.form], k.tail, k.late);
-  if (shares > 1 || q_shares > 1) us += 2 * sums_of(c, shares, q_shares) / (k.rate * 1e6);
-  if (shares > 1) us += k.sums + k.per_share * shares;
-  if (q_shares > 1) us += k.sums + k.per_q_share * q_shares;
-  return us;
+  const int64_t n = (kv ? c.n_kv : c.n_q) * shares;
+  const double start = k.start[c.form], walk = (kv ? k.kv[c.form] * c.walk_kv : k.q[c.form] * c.walk_q) / shares;
+  const double mean = (start + walk * c.mean) * (c.causal ? uneven((kv ? c.kv_heads : c.q_heads) * shares) : 1.0);
+  const int64_t bytes = shares > 1 ? n * (kv ? c.bytes : c.bytes / 2) : 0;
+  return {{(n + XCDS - 1) / XCDS, start + walk, mean, kv ? 0 : c.q_blocks}, shares, bytes,
+          shares > 1 ? k.sums + (kv ? k.per_share : k.per_q_share) * shares + 2 * bytes / (k.rate * 1e6) : 0.};
 }
-Plan best_of(const Undivided* calls, int n, int most_q) {
+// The same by even shares, without a look at rounds: 6 us per workgroup, us per tile for 1, 2 and 4 parts (at d = 64 0.55 of them),
+// half a workgroup beyond the device's share.  For calls whose forms still stand in the old proportions, as all take split products:
+// sequences, and walks of several chunks at d = 64.  Placed, 70 sequences at d = 128 took 0.98 of the time in the mean, but some far
+// more (4 heads x 926 59 -> 73 us, 4 over 1 x 922 61 -> 75), and 82 walks at d = 64 1.005 (one head x 922 x 4610 55 -> 72).
+double even_shares(const Undivided& c, const Shared& kv, const Shared& q, bool diagonal) {
+  constexpr double per_kv[3] = {9.3, 10.3, 12.2}, per_q[3] = {7, 7.7, 9.7};
+  const double width = c.d == 128 ? 1.0 : 0.55;
+  const int64_t n_kv = c.n_kv * kv.shares, n_q = c.n_q * q.shares, sums = kv.bytes + q.bytes;
+  const double w_kv = width * per_kv[c.form] * c.walk_kv / kv.shares, w_q = width * per_q[c.form] * c.walk_q / q.shares;
+  const double t_kv = n_kv ? 6 + w_kv : 0., t_q = n_q ? 6 + w_q : 0.;
+  double us = std::max(t_kv, t_q);
+  if (n_kv + n_q > XCDS * CUS) {
+    const double even_kv = n_kv * (6 + w_kv * c.mean) / (XCDS * CUS), even_q = n_q * (6 + w_q * c.mean) / (XCDS * CUS);
+    us = std::max(us, diagonal ? even_kv * uneven(c.kv_heads * kv.shares) + std::max(t_q, even_q * uneven(c.q_heads * q.shares) + 0.3 * t_q)
+                               : even_kv + even_q + 0.45 * us);
+  }
+  return sums > 0 ? (us + 4 * ((kv.shares > 1) + (q.shares > 1)) + 2 * sums / 2.5e6) / 0.92 : us;
+}
+Plan best_of(const Undivided* calls, int n, int most_q, bool even, bool diagonal) {
   Plan best{0, 0, 0, 0., 0};
-  for (const Undivided* c = calls; c < calls + n; ++c)
+  for (const Undivided* c = calls; c < calls + n; ++c) {
+    const Terms& k = c->d == 128 ? D128 : D64;
+    // Of a causal call whose walks are about equally long (many keys before the chunk's own) whole rounds count too.
+    const double equal = c->causal ? std::max(0., 2 * c->mean - 1) * std::max(0., 2 * c->mean - 1) : 0.;
+    Shared kv[10];
+    int n_kv = 0;
+    for (int shares : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+      if (shares > 1 && (!c->n_kv || shares > 4 * c->group || c->n_kv * shares > 1024)) break;
+      kv[n_kv++] = shared(*c, true, shares);
+    }
     for (int q_shares = 1; q_shares <= most_q; q_shares *= 2) {
       if (q_shares > 1 && (c->n_q * q_shares > 1024 || q_shares > c->q_tiles)) break;
+      const Shared q = shared(*c, false, q_shares);
       double low = 1e30;
-      for (int shares : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-        if (shares > 1 && (!c->n_kv || shares > 4 * c->group || c->n_kv * shares > 1024)) break;
-        const int64_t sums = sums_of(*c, shares, q_shares);
-        if (sums > c->ws_bytes) break;
-        const double us = estimate(*c, shares, q_shares);
-        if (!best.parts || us < best.us) best = {c->parts, shares, q_shares, us, sums};
+      for (int i = 0; i < n_kv && kv[i].bytes + q.bytes <= c->ws_bytes; ++i) {
+        if (even) {
+          const double us = even_shares(*c, kv[i], q, diagonal);
+          if (!best.parts || us < best.us) best = {c->parts, kv[i].shares, q_shares, us, kv[i].bytes + q.bytes};
+          continue;
+        }
+        double us = makespan(kv[i].kind, q.kind, c->causal, k.start[c->form] + 2 * k.kv[c->form], k.tail, k.late);
+        if (equal > 0) us += equal * std::max(0., placed(kv[i].kind.n, kv[i].kind.longest, q.kind.n, q.kind.longest) - us);
+        us += kv[i].us + q.us;
+        if (!best.parts || us < best.us) best = {c->parts, kv[i].shares, q_shares, us, kv[i].bytes + q.bytes};
         low = std::min(low, us);
         if (us > 1.5 * low) break;      // (nor with more)
       }
     }
+  }
   return best;
 }
 
@@ -1133,7 +1161,8 @@ Plan plan(const dfa_shape& sh, int pairs, bool dq, bool dk, int64_t ws_bytes, bo
   const Undivided calls[] = {undivided(sh, pairs, dq, dk, ws_bytes, 1), undivided(sh, pairs, dq, dk, ws_bytes, 2),
                              undivided(sh, pairs, dq, dk, ws_bytes, 4)};
   const bool few = dq && sh.s_k / 8 >= sh.s_q, diagonal = sh.causal && dq && dk && pairs == 1;
-  return best_of(calls, sequence && sh.d == 128 ? 2 : 3, few ? 64 : diagonal ? 8 : 1);
+  const bool even = sequence || (sh.d == 64 && sh.causal && sh.s_k > sh.s_q);
+  return best_of(calls, sequence && sh.d == 128 ? 2 : 3, few ? 64 : diagonal ? 8 : 1, even, diagonal && !few);
 }
 
 }  // namespace
