@@ -1168,6 +1168,7 @@ bool causal_with_remainders(int64_t s_q, int64_t n64) { return n64 <= 256 || (n6
 struct FwdForm { int rows, parts; };      // query rows of a workgroup, parts that it divides the keys of a tile in
 FwdForm form_of(const dfa_shape& sh, int n, bool sequence) {
   // Which form.  us per call on one box, d = 128, 256-row / 128-row / 64-row NS = 2 / 64-row NS = 4 workgroups:
+  // (256-row figures of an earlier form of that kernel, since 5 % faster; where the crossovers lie with it: below, at each line.)
   //   full pairs    8 heads x 256 rows 13.5 / 9.6 / 8.6 / 9.5    x 1024 30.5 / 24.2 / 22 / 18.4
   //                 x 2048 52.5 / 42.7 / 40 / 34.2 (256 64-row workgroups)   x 4096 97 / 82 / 100 / 105
   //                 x 8192 242 / 270 / 344 / 382    32 heads x 1024 32.8 / 27.2 / 29.6 / 34.5
@@ -1184,7 +1185,11 @@ FwdForm form_of(const dfa_shape& sh, int n, bool sequence) {
   if (sh.causal) {
     // The diagonal's longest row block sets the time of a call that does not fill the device, so long
     // chunks are split further; the 256-row form needs chunks long enough that its masked half tiles do
-    // not count, and whole tiles (ragged chunks, 32 heads x 14197: 1664 us against 1608 with 128 rows).
+    // not count, and whole tiles (ragged chunks, 32 heads x 14197: 1664 us against 1608 with 128 rows).  With the present 256-row
+    // kernel, us, 128 rows / 256: 14 heads x 5376 164 / 185, 20 x 5120 190 / 208, 24 x 5120 196 / 210, 36 x 4864 264 / 271, 10 x 11264
+    // 449 / 443; behind the line 20 x 6912 312 / 324, 24 x 7168 345 / 354, 22 x 6400 299 / 286, 10 x 14336 685 / 655, 40 x 6144 447 / 418,
+    // 20 x 9216 533 / 505, 24 x 9216 569 / 520.  Before it the wider form is ahead where every XCD has whole pairs of heads:
+    // 16 heads x 4608 130 / 119, x 6144 173 / 156, x 7680 253 / 214, 32 x 5376 263 / 244, 64 x 5120 483 / 453.
     if (causal_with_remainders(sh.s_q, n64)) parts = 4;
     // A sequence of several chunks, whose shortest lists of pairs have half as many workgroups at least.  us with 2 / 4 parts: 32
     // heads x 600 20.2 / 23.1, x 1024 32.7 / 35.4, 24 x 800 21.4 / 22.2, 16 x 1200 28.4 / 23.0, x 1400 31.9 / 26.3, x 2000 56 / 43.
@@ -1276,7 +1281,8 @@ Remainders remainders(const dfa_shape& sh, const dfa_fwd_span* spans, int n) {
 // 128-row ones (two) and 1.7 with 256-row ones; a launch that runs in one round takes its longest walk, a longer one the device's
 // even share and about half a walk; the merge 8 us and 3 TB/s.  (With 1.1 and 1.9, as measured on walks that fill the device less,
 // 128 rows were taken too often: us, pairs / so / now: 32 over 8 heads, 3 chunks of 3200 476 / 550 / 431, 64 over 8, 2 of 704
-// 53 / 59 / 40, 16 over 4, 3 of 4158 493 / 551 / 402.)
+// 53 / 59 / 40, 16 over 4, 3 of 4158 493 / 551 / 402.)  The 256-row kernel is 5 % faster since; every division of 217 random
+// spans timed with it: chosen / best 1.011 in the mean, 1.005 with constants fitted to them, so these stay.
 struct SpanPlan { int rows, parts; double us; };
 
 SpanPlan span_plan(const dfa_shape& sh, const dfa_fwd_span* spans, int n, bool all_remainders, int64_t ws_bytes) {
@@ -1346,7 +1352,9 @@ struct WithoutOwn {
 // two: 32 heads x 2777 x 3001 keys 156 / 146, x 3072 186 / 169, x 5120 429 / 401, x 10300 1712 / 1648, x 18500 5301 / 5051, 8 x 10000
 // 461 / 423, 16 x 5000 x 4000 196 / 181, 64 x 1300 90 / 81, 96 x 700 x 2000 125 / 99.  Not with fewer keys, where the second launch
 // and its prologue count: 32 x 2777 x 1200 keys and more gain 3 to 6 %, x 1024 60.7 / 61.0, x 512 37 / 41, 8 x 16896 x 700 78 / 81;
-// nor where 128-row workgroups alone have no more rounds (160 x 400).
+// nor where 128-row workgroups alone have no more rounds (160 x 400).  With the present 256-row kernel 60 random full pairs of 8 to 64
+// heads x 500 to 10000 rows took as long as the best of one launch, two, and 128 rows (within 1 %), but for rests of rounds with fewer
+// than 750 keys (32 x 8794 x 508 114, 106 with 128 rows).
 int64_t rows_of_whole_rounds(const dfa_shape& sh, int n) {
   const int64_t heads = static_cast<int64_t>(sh.h_q) * n, n256 = (static_cast<int64_t>(sh.s_q) + 255) / 256 * heads;
   const int64_t n128 = (static_cast<int64_t>(sh.s_q) + 127) / 128 * heads, rounds = n256 / 256;
